@@ -121,7 +121,7 @@ int32_t he_ctx_create(he_ctx** out, uint32_t logN, const uint64_t* h_q, uint32_t
         }
     }
     // host tables first, so that a failed host allocation leaves nothing behind
-    std::vector<u64> tw((size_t)M * N), tw_sh((size_t)M * N), itw((size_t)M * N), itw_sh((size_t)M * N);
+    std::vector<ulonglong2> tw((size_t)M * N), itw((size_t)M * N);
     he_ctx* c = new (std::nothrow) he_ctx();
     if (!c) return he_fail(nullptr, HE_ERR_ALLOC, "he_ctx_create: host allocation failed");
     struct Owner {                                      // destroys the half-built context on every early exit
@@ -131,7 +131,7 @@ int32_t he_ctx_create(he_ctx** out, uint32_t logN, const uint64_t* h_q, uint32_t
     c->logN = logN; c->N = N; c->nq = nq; c->np = np; c->dnum = dnum; c->M = M;
     c->alpha = (nq + dnum - 1) / dnum;
     c->stream = (hipStream_t)hip_stream;
-    c->d_mc = nullptr; c->d_tw = c->d_tw_sh = c->d_itw = c->d_itw_sh = nullptr;
+    c->d_mc = nullptr; c->d_tw = c->d_itw = nullptr;
     c->d_ws = nullptr; c->ws_bytes = 0;
     c->d_up_hat = c->d_dn_hat = c->d_pinv = c->d_pinv_sh = c->d_qlinv = c->d_qlinv_sh = nullptr;
     memset(&c->cnt, 0, sizeof(c->cnt));
@@ -153,12 +153,12 @@ int32_t he_ctx_create(he_ctx** out, uint32_t logN, const uint64_t* h_q, uint32_t
         c->psi[i] = psi;
         u64 ipsi = h_invmod(psi, m);
         u64 pw = 1, ipw = 1;
-        u64* t = &tw[(size_t)i * N]; u64* ts = &tw_sh[(size_t)i * N];
-        u64* it = &itw[(size_t)i * N]; u64* its = &itw_sh[(size_t)i * N];
+        ulonglong2* t = &tw[(size_t)i * N];
+        ulonglong2* it = &itw[(size_t)i * N];
         for (uint32_t e = 0; e < N; e++) {                      // psi^e stored at bitrev(e)
             uint32_t pos = bitrev(e, logN);
-            t[pos] = pw; ts[pos] = h_shoup(pw, m);
-            it[pos] = ipw; its[pos] = h_shoup(ipw, m);
+            t[pos] = make_ulonglong2(pw, h_shoup(pw, m));
+            it[pos] = make_ulonglong2(ipw, h_shoup(ipw, m));
             pw = h_mulmod(pw, psi, m);
             ipw = h_mulmod(ipw, ipsi, m);
         }
@@ -172,20 +172,16 @@ int32_t he_ctx_create(he_ctx** out, uint32_t logN, const uint64_t* h_q, uint32_t
         mc.ninv_w = h_mulmod(mc.ninv, c->itw1[i], m);
         mc.ninv_w_sh = h_shoup(mc.ninv_w, m);
         mc.one_sh = h_shoup(1, m);
-        mc.pad = 0;
+        mc.rec = (uint32_t)(((u128)1 << (mc.bits + 31)) / m);
     }
-    size_t tb = (size_t)M * N * sizeof(u64);
+    size_t tb = (size_t)M * N * sizeof(ulonglong2);
     hipError_t e = hipSuccess;
     if (e == hipSuccess) e = hipMalloc(&c->d_mc, sizeof(ModConst) * M);
     if (e == hipSuccess) e = hipMalloc(&c->d_tw, tb);
-    if (e == hipSuccess) e = hipMalloc(&c->d_tw_sh, tb);
     if (e == hipSuccess) e = hipMalloc(&c->d_itw, tb);
-    if (e == hipSuccess) e = hipMalloc(&c->d_itw_sh, tb);
     if (e == hipSuccess) e = hipMemcpy(c->d_mc, c->h_mc, sizeof(ModConst) * M, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(c->d_tw, tw.data(), tb, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(c->d_tw_sh, tw_sh.data(), tb, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(c->d_itw, itw.data(), tb, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(c->d_itw_sh, itw_sh.data(), tb, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipDeviceSynchronize();
     if (e != hipSuccess) {
         he_fail(nullptr, e == hipErrorOutOfMemory ? HE_ERR_ALLOC : HE_ERR_HIP, "he_ctx_create: %s", hipGetErrorString(e));
@@ -229,9 +225,7 @@ int32_t he_ctx_destroy(he_ctx* c) {
     (void)hipStreamSynchronize(c->stream);
     if (c->d_mc) (void)hipFree(c->d_mc);
     if (c->d_tw) (void)hipFree(c->d_tw);
-    if (c->d_tw_sh) (void)hipFree(c->d_tw_sh);
     if (c->d_itw) (void)hipFree(c->d_itw);
-    if (c->d_itw_sh) (void)hipFree(c->d_itw_sh);
     if (c->d_ws) (void)hipFree(c->d_ws);
     for (auto& s : c->prof_events) { (void)hipEventDestroy(s.e0); (void)hipEventDestroy(s.e1); }
     ks_free_tables(c);

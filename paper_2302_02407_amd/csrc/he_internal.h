@@ -26,7 +26,7 @@ struct ModConst {
     u64 ninv_w_sh;
     u64 one_sh;     // floor(2^64 / q): Shoup companion of the constant 1 (a quotient step for any 64-bit value)
     uint32_t bits;  // bit length of q
-    uint32_t pad;
+    uint32_t rec;   // floor(2^(bits+31) / q): 32-bit reciprocal for small quotients
 };
 
 // Modulus index of each limb of a launch, passed by value in the kernel arguments.
@@ -60,10 +60,8 @@ struct he_ctx {
     ModConst h_mc[HE_MAX_MODULI];
     // device tables
     ModConst* d_mc;    // [M]
-    u64* d_tw;         // [M][N]  psi^bitrev(i)
-    u64* d_tw_sh;      // [M][N]  Shoup companions
-    u64* d_itw;        // [M][N]  psi^-bitrev(i)
-    u64* d_itw_sh;     // [M][N]
+    ulonglong2* d_tw;  // [M][N]  psi^bitrev(i) and its Shoup companion, one 16-byte load
+    ulonglong2* d_itw; // [M][N]  psi^-bitrev(i), likewise
     // basis-conversion tables (keyswitch.hip); present when np > 0
     u64* d_up_hat;     // [dnum][alpha][alpha][M]: (Q_j/q_i) mod m for digit j holding sz limbs, [j][sz-1][i][m]
     std::vector<u64> h_up_invhat; // [dnum][alpha][alpha]: ((Q_j/q_i)^-1 mod q_i), [j][sz-1][i]
@@ -94,6 +92,9 @@ u64 h_powmod(u64 a, u64 e, u64 m);
 u64 h_invmod(u64 a, u64 m);
 u64 h_shoup(u64 w, u64 m);
 uint32_t h_galois_of_step(const he_ctx* ctx, int32_t step);
+
+// Rings whose limb does not fit one work group's LDS: two launches per transform (ntt2p.hip)
+static inline bool two_pass(const he_ctx* c) { return c->logN > 12; }
 
 // Every extern "C" body runs inside he_guard: no C++ exception (a failed host allocation in a
 // std::vector / std::map / std::string) crosses the C ABI; it comes back as HE_ERR_ALLOC.
@@ -140,7 +141,7 @@ struct ModDownEpilogue {
     u64* out0[HE_MAX_KS_JOBS];
     u64* out1[HE_MAX_KS_JOBS];
     uint32_t g[HE_MAX_KS_JOBS];
-    // N = 2^16 path only.  fused != 0: the q-limbs of acc are never materialised; the epilogue computes
+    // Two-launch transforms only.  fused != 0: the q-limbs of acc are never materialised; the epilogue computes
     // acc_c[r] = sum_j digit_j[r] (gathered by the Galois map) * evk_j,c[r] itself, digit j's own limbs
     // taken from the switched polynomial.  beta <= 8.
     uint32_t fused, beta, alpha, M;
@@ -154,7 +155,7 @@ struct ModDownEpilogue {
 };
 
 // Key-switch inner product of the special-prime limbs computed by the first pass of their inverse transform
-// (N = 2^16 path): limb i of the launch is job i/(2k), component (i/k)&1, special prime i%k; its input value at
+// (two-launch transforms): limb i of the launch is job i/(2k), component (i/k)&1, special prime i%k; its input value at
 // position n is sum_j raised_j[L1 + i%k][galois(n)] * evk_j,comp[nq + i%k][n] and is never stored.  beta <= 8.
 struct IpPrologue {
     const u64* raised[HE_MAX_KS_JOBS];  // [beta][R][N]
@@ -178,12 +179,12 @@ struct TransformDesc {
     const ScaleList* scale;      // inverse only: limb i is multiplied by scale[i % scale_period]
     uint32_t scale_period;       //   (must include N^-1); nullptr = plain N^-1
     const ModDownEpilogue* ep;   // forward only, or nullptr
-    const IpPrologue* ip;        // inverse on the N = 2^16 path only, or nullptr: inputs are computed, not read
-    bool lazy_out;               // forward only: outputs may stay unreduced (below 2^7 q) where the
-                                 // consumers' 128-bit accumulations leave room; internal buffers only
-    uint32_t only_pass;          // N = 2^16 path: 0 = both passes; 1 = the first pass only (inverse: rows, reading the
+    const IpPrologue* ip;        // inverse, two-launch transforms only, or nullptr: inputs are computed, not read
+    bool lazy_out;               // forward only: outputs may stay below 2q for moduli of at most 57 bits
+                                 // (internal buffers whose consumers allow for it)
+    uint32_t only_pass;          // two-launch transforms: 0 = both passes; 1 = the first pass only (inverse: rows, reading the
                                  // sources; forward: columns); 2 = the second pass only, in place at dst
-    uint32_t rescale_from;       // N = 2^16 path, forward only: l + 1 when the sources are coefficient-form limbs of
+    uint32_t rescale_from;       // two-launch transforms, forward only: l + 1 when the sources are coefficient-form limbs of
                                  // modulus l and limb i (modulus r) transforms ((t + h) mod q_l) mod q_r - (h mod q_r),
                                  // h = floor(q_l / 2): the rounding term of Rescale, negated; 0 = sources as they are
 };
@@ -211,12 +212,12 @@ struct ColFuse {
     uint8_t tgt_limb[CF_MAX_SETS][HE_MAX_MODULI];     // indexed per wavefront: vector loads
     uint8_t tgt_mod[CF_MAX_SETS][HE_MAX_MODULI];
 };
-int32_t launch_colfuse(he_ctx* ctx, const ColFuse& cf, const ScaleList& sc, uint32_t limb_passes);   // ntt16.hip
+int32_t launch_colfuse(he_ctx* ctx, const ColFuse& cf, const ScaleList& sc, uint32_t limb_passes);   // ntt2p.hip
 // fills w / w_sh of entry i from s (modulus index mi)
 void scale_entry(const he_ctx* c, ScaleList& sc, uint32_t i, uint32_t mi, u64 s);
 int32_t launch_transform(he_ctx* ctx, const TransformDesc& d);
-int32_t launch_transform16(he_ctx* ctx, const TransformDesc& d);   // N = 2^16 fast path
-int32_t probe_butterfly_rates(he_ctx* ctx, u64* d_out, uint32_t groups, double rate_out[3]);   // ntt16.hip
+int32_t launch_transform2p(he_ctx* ctx, const TransformDesc& d);   // N = 2^13 .. 2^17 (ntt2p.hip)
+int32_t probe_butterfly_rates(he_ctx* ctx, u64* d_out, uint32_t groups, double rate_out[3]);   // ntt2p.hip
 int32_t launch_moddown_final(he_ctx* ctx, const u64* conv, uint32_t n_jobs, const ModDownEpilogue& ep);
 
 // in-place conveniences

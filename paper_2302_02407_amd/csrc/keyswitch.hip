@@ -343,7 +343,7 @@ void ks_free_tables(he_ctx* c) {
 static int32_t launch_baseconv(he_ctx* c, const ConvBatch& b, uint32_t nt_max, uint32_t ns_max) {
     dim3 grid((c->N + 2 * KS_THREADS - 1) / (2 * KS_THREADS), (nt_max + CONV_TGT_PER_BLOCK - 1) / CONV_TGT_PER_BLOCK,
               b.njobs * b.reps), block(KS_THREADS);
-    if (ns_max <= 8 && c->logN == 16) hipLaunchKernelGGL((baseconv_kernel<true, true>), grid, block, 0, c->stream, b, c->d_mc, c->logN);
+    if (ns_max <= 8 && two_pass(c)) hipLaunchKernelGGL((baseconv_kernel<true, true>), grid, block, 0, c->stream, b, c->d_mc, c->logN);
     else if (ns_max <= 8) hipLaunchKernelGGL((baseconv_kernel<true, false>), grid, block, 0, c->stream, b, c->d_mc, c->logN);
     else hipLaunchKernelGGL((baseconv_kernel<false, false>), grid, block, 0, c->stream, b, c->d_mc, c->logN);
     HE_HIP(c, hipGetLastError());
@@ -617,7 +617,7 @@ static int32_t inner_moddown_batch(he_ctx* c, uint32_t level, const KsSrc* srcs,
     // On the N = 2^16 path no accumulator is materialised: the special-prime limbs of the inner product are
     // computed by the first pass of their inverse transform, the q-limbs inside the ModDown epilogue (they would
     // only be written here and read back there).  Other rings run the stand-alone kernel.
-    const bool fused = c->logN == 16 && beta <= 8;
+    const bool fused = two_pass(c) && beta <= 8;
     // small rings: inner product, ModDown and epilogue of every output limb in one work group, one launch
     const bool small = !fused && small_ring_path(c, level);
     IpPrologue ip = {};
@@ -747,7 +747,7 @@ static uint32_t rot_sum_cb(const he_ctx* c, uint32_t level, uint32_t n_rot) {
     return cb;
 }
 static bool rot_sum_fused(const he_ctx* c, uint32_t level, uint32_t n_rot) {
-    return c->logN == 16 && num_digits(c, level) <= 8 && n_rot <= HE_MAX_KS_JOBS;
+    return two_pass(c) && num_digits(c, level) <= 8 && n_rot <= HE_MAX_KS_JOBS;
 }
 
 // raised[n_rot][beta][R] + tmp_up[cb][L1] + s0[L1] + s1[L1] + tmp_dn[2][k] + conv[2][L1] (+ acc[1 + min(n_rot,16)][2][R]
@@ -921,7 +921,6 @@ __global__ __launch_bounds__(KS_THREADS, 3) void hoisted_sum_ip_local_kernel(Hoi
     const uint32_t n = blockIdx.x * KS_THREADS + threadIdx.x, r = sel.r[blockIdx.y];
     const uint32_t mi = r <= level ? r : nq + (r - level - 1);
     const ModConst m = mc[mi];
-    const uint32_t mrec = (1u << 24) / ((uint32_t)(m.q >> (m.bits - 8)) + 1);
     const uint32_t h = m.bits > 54 ? 30u : 27u, period = m.bits > 54 ? 6u : 32u;
     const u64 lo_h = (1ull << h) - 1;
     const size_t ro = ((size_t)r << logN) + n, cstride = (size_t)R << logN;
@@ -931,7 +930,7 @@ __global__ __launch_bounds__(KS_THREADS, 3) void hoisted_sum_ip_local_kernel(Hoi
 #pragma unroll
         for (int i = 0; i < JT; i++) {
             if ((uint32_t)i < a.J) {
-                const u64 v = reduce_small((own_digit ? a.own[i] : a.raised[i])[doff], m.q, m.bits, mrec);
+                const u64 v = reduce_full<7>((own_digit ? a.own[i] : a.raised[i])[doff], m.q, m.bits, m.rec);
                 dig[(j * a.J + i) * KS_THREADS + threadIdx.x] = (v & lo_h) | ((v >> h) << 32);
             }
         }
@@ -992,7 +991,7 @@ __global__ __launch_bounds__(KS_THREADS, 3) void hoisted_sum_ip_local_kernel(Hoi
     auto fold1 = [&](u64& lo, u64& mid_s, u64& hi) {
         u64 mid = mid_s + lo + hi;
         mid += lo >> h; lo &= lo_h;
-        hi = reduce_small_lazy(hi + (mid >> h), m.q, m.bits, mrec); mid &= lo_h;
+        hi = reduce_lazy<7>(hi + (mid >> h), m.q, m.bits, m.rec); mid &= lo_h;
         mid_s = mid - lo - hi;
     };
     auto fold = [&]() {
@@ -1264,7 +1263,7 @@ int32_t rescale_batch(he_ctx* ctx, const u64* const* cts, u64* const* outs, uint
         // accumulator (component stride level+1 limbs), q_l^-1 mod q_r the constant of the final product.  At N = 2^16
         // the first pass forms -delta from the dropped limb's coefficients as it reads them; otherwise a kernel does.
         const uint32_t total = 2 * nb * level;
-        const bool fused_delta = ctx->logN == 16;
+        const bool fused_delta = two_pass(ctx);
         std::vector<uint32_t> dm(total);
         std::vector<uint16_t> dsrc(total);
         for (uint32_t i = 0; i < total; i++) { dm[i] = i % level; dsrc[i] = (uint16_t)(i / level); }

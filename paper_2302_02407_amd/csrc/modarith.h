@@ -16,7 +16,22 @@ __device__ __forceinline__ u64 shoup_lazy(u64 y, u64 w, u64 w_sh, u64 q) {
     return w * y - h * q;
 }
 
-__device__ __forceinline__ u64 csub(u64 x, u64 q) { return x >= q ? x - q : x; }
+// x >= q ? x - q : x for x < q + 2^63.  The sign of the difference, spread over a word, masks the q that is added back:
+// four instructions with no carry flag for the uniform form (the subtraction is an addition of -q, which the compiler
+// must not turn back into a borrow chain), against compare, two selects, subtract with borrow and the wait states a flag
+// needs.  csub takes any q, csub_u a q that is the same for the whole wavefront.
+__device__ __forceinline__ u64 mask_add(u64 d, u64 q) { return d + (q & (u64)((int64_t)d >> 63)); }
+__device__ __forceinline__ u64 csub(u64 x, u64 q) { return mask_add(x - q, q); }
+__device__ __forceinline__ u64 neg_u(u64 q) {
+    u64 n = 0 - q;
+    asm("" : "+s"(n));
+    return n;
+}
+// a value that is the same for the whole wavefront, in scalar registers (loads after a store come back in vector ones)
+__device__ __forceinline__ u64 uni64(u64 v) {
+    return ((u64)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(v >> 32)) << 32) | (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)v);
+}
+__device__ __forceinline__ u64 csub_u(u64 x, u64 q) { return mask_add(x + neg_u(q), q); }
 
 // High word of a*b from three 32x32 products (the low*low product and the carries out of the
 // middle column are dropped): never above the true value, at most 2 below it.
@@ -26,12 +41,30 @@ __device__ __forceinline__ u64 mulhi64_approx(u64 a, u64 b) {
     return (u64)ah * bh + mid;
 }
 
-// w*y mod q in [0, 4q): Shoup's product with the approximate quotient above (one multiply fewer
-// and no carry chain; the quotient is at most 2 short, each unit adds q to the remainder).
-__device__ __forceinline__ u64 shoup_lazy4(u64 y, u64 w, u64 w_sh, u64 q) {
-    u64 h = mulhi64_approx(w_sh, y);
-    return w * y - h * q;
+// a + b + c as one instruction.  Opaque on purpose: sums of 32-bit products written in C become 64-bit multiply-adds with
+// moves around them (7 instructions instead of 6 for the high word below, 12 where nothing is added first).
+__device__ __forceinline__ uint32_t add3(uint32_t a, uint32_t b, uint32_t c) {
+    uint32_t r;
+    asm("v_add3_u32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
 }
+
+// x + (w*y mod q), the product in [0, 4q): Shoup's product with the approximate quotient above (one multiply fewer and
+// no carry chain; the quotient is at most 2 short, each unit adds q to the remainder).  One multiply-add chain modulo
+// 2^64 with x as its first addend and -q as the quotient's factor: two wide multiply-adds for the low columns, four
+// 32-bit products for the high word.
+__device__ __forceinline__ u64 shoup_acc(u64 x, u64 y, u64 w, u64 w_sh, u64 q) {
+    const u64 h = mulhi64_approx(w_sh, y), nq = 0 - q;
+    const uint32_t w0 = (uint32_t)w, w1 = (uint32_t)(w >> 32), y0 = (uint32_t)y, y1 = (uint32_t)(y >> 32);
+    const uint32_t h0 = (uint32_t)h, h1 = (uint32_t)(h >> 32), n0 = (uint32_t)nq, n1 = (uint32_t)(nq >> 32);
+    u64 s = (u64)w0 * y0 + x;
+    s += (u64)h0 * n0;
+    const uint32_t hi = add3(add3((uint32_t)(s >> 32), w0 * y1, w1 * y0), h0 * n1, h1 * n0);
+    return ((u64)hi << 32) | (uint32_t)s;
+}
+
+// w*y mod q in [0, 4q)
+__device__ __forceinline__ u64 shoup_lazy4(u64 y, u64 w, u64 w_sh, u64 q) { return shoup_acc(0, y, w, w_sh, q); }
 
 // canonical w*y mod q
 __device__ __forceinline__ u64 shoup_mul(u64 y, u64 w, u64 w_sh, u64 q) { return csub(shoup_lazy(y, w, w_sh, q), q); }

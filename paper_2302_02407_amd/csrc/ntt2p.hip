@@ -1,0 +1,932 @@
+// Two-launch negacyclic NTT / iNTT (ring of paper Section 2.1) for rings whose limb does not fit one work group:
+// N = 2^13 .. 2^17.
+//
+// The limb is viewed as 2^LC rows of 256 (row-major, LC = logN - 8).  A transform is two launches:
+//   forward : column pass (stages 0 .. LC-1, row distance 2^(LC-1) .. 1), row pass (stages LC .. LC+7);
+//   inverse : row pass (stages LC+7 .. LC), column pass (stages LC-1 .. 0) with the output scaling.
+// Inside a pass every thread keeps 16 points of one sub-transform in registers and runs up to 4 butterfly stages on
+// them, then the threads of the sub-transform exchange points through LDS and run the others: one LDS round trip
+// replaces eight (two for the 9-stage columns of N = 2^17).  Points are held either "strided" (thread t holds t + k*16 of
+// a row, t + k*2^(LC-4) of a column) or "contiguous" (16t + j).
+//
+// What bounds a pass is how far loads run ahead of arithmetic.  A row pass needs 240 bytes of twiddles per thread for 128
+// bytes of points; fetched where they are used they cost 40 us of 104 (384 limbs, N = 2^16, measured with the factors
+// taken out), so they are requested a block ahead, as the registers of the previous block's factors come free: 81 us,
+// where a copy of the same limbs through LDS takes 61.
+//
+// Arithmetic: ntt_blocks.h.  Forward values are never reduced inside a transform for moduli below 2^57 (16 or 17 stages end
+// below 73q < 2^64) and once in two stages above; a small-quotient step makes them canonical at the end.
+#include <algorithm>
+
+#include "modarith.h"
+#include "ntt_blocks.h"
+
+#define P2_THREADS 256
+#define SCHED_FENCE() __builtin_amdgcn_sched_barrier(0)   // loads above it are issued before the arithmetic below it
+
+// Limbs of a launch, sorted by modulus: destination limb (bits 0-8), modulus (9-14), source segment (27-30) and limb in it
+// (15-26), wide modulus (31).  One 32-bit word per limb, so that a work group gets all of it in one scalar load, and
+// branches to the code of its modulus' width before it loads anything else (a branch between the loads and their use
+// doubles the registers that are live across it).  No entry is all ones: modulus 63 with segment 15 is never built.
+struct LimbTab {
+    const u64* seg[HE_MAX_SEGS];
+    uint32_t e[HE_MAX_LAUNCH_LIMBS];
+};
+#define TAB_NONE 0xFFFFFFFFu
+#define TAB_WIDE 0x80000000u
+struct P2Args {
+    u64* dst;
+    const ModConst* mc;
+    const ulonglong2* tw;     // [M][N] forward or inverse twiddles
+    uint32_t logN;
+    uint32_t lazy;            // forward, last pass: outputs may stay below 2q
+    uint32_t rs_mod;          // forward, first pass reading the Rescale rounding term: modulus index of the dropped limb
+    uint32_t log_chunk;       // row passes, see row_decode
+};
+// Keeps the loads of the two width branches apart: merged above the branch (they look alike) they would stay live across
+// all of it, 240 registers instead of 109.
+template <bool WIDE>
+__device__ __forceinline__ uint32_t branch_pin(uint32_t e) {
+    if (WIDE) asm("; wide" : "+s"(e));
+    else asm("; narrow" : "+s"(e));
+    return e;
+}
+__device__ __forceinline__ uint32_t tab_dst(uint32_t e) { return e & 511u; }
+__device__ __forceinline__ uint32_t tab_mod(uint32_t e) { return (e >> 9) & 63u; }
+__device__ __forceinline__ const u64* tab_src(const LimbTab& tab, uint32_t e, uint32_t logN) {
+    return tab.seg[(e >> 27) & 15u] + ((size_t)((e >> 15) & 0xFFFu) << logN);
+}
+
+// Work order of the row passes.  Their twiddles depend on (modulus, tile), so limbs that share a modulus should run the same
+// tile back to back on the same XCD (one L2 per XCD; workgroups are handed to the 8 XCDs round-robin).  The table is
+// padded with TAB_NONE to a multiple of the chunk size C = 1 << log_chunk; the linear work index
+// L = (chunk_of_limbs*tiles + tile)*C + j walks the C limbs of a chunk for one tile, and
+// workgroup id -> L keeps each run of C consecutive L on one XCD.
+__device__ __forceinline__ uint32_t row_decode(const LimbTab& tab, const P2Args& a, uint32_t& tile) {
+    const uint32_t lc = a.log_chunk, idx = blockIdx.x, lt = a.logN - 12;
+    const uint32_t xcd = idx & 7u, slot = idx >> 3;
+    const uint32_t L = ((((slot >> lc) << 3) + xcd) << lc) | (slot & ((1u << lc) - 1u));
+    const uint32_t pchunk = L >> (lt + lc), rem = L & ((1u << (lt + lc)) - 1u);
+    tile = rem >> lc;
+    return __builtin_amdgcn_readfirstlane(tab.e[(pchunk << lc) + (rem & ((1u << lc) - 1u))]);
+}
+
+__device__ __forceinline__ uint32_t galois_pos(uint32_t j, uint32_t g, uint32_t logN) {
+    const uint32_t k = __brev(j) >> (32 - logN);
+    const uint32_t kp = (g * k + ((g - 1) >> 1)) & ((1u << logN) - 1u);
+    return __brev(kp) >> (32 - logN);
+}
+
+// ---------------------------------------------------------------- column passes
+// Tile of a column pass: all 2^LC rows of C = 4096 / 2^LC adjacent columns.  LDS position of (row, column): one spare row
+// per 16 keeps the row groups that a wavefront reads back at once on different banks (with 32 or more columns a half
+// wavefront stays inside one row).
+template <int LC>
+struct Col {
+    static constexpr int LCOLS = 12 - LC, C = 1 << LCOLS, LT = LC - 4, T = 1 << LT;   // T threads share a column
+    static constexpr int U0 = LC < 8 ? 8 - LC : 0;                                   // first stage of the second block
+    static constexpr int LDS = C >= 32 ? 4096 : 4096 + 256;
+    static __device__ __forceinline__ uint32_t pos(uint32_t r, uint32_t cl) { return (C >= 32 ? r : r + (r >> 4)) * C + cl; }
+};
+
+// RS: the source is the coefficient form of the limb that Rescale drops (modulus ml); what is transformed is the negated
+// rounding term ((v + h) mod q_l) mod q - (h mod q), h = floor(q_l / 2), of this limb's modulus m.
+template <int LC, bool RS, bool WIDE>
+__device__ __forceinline__ void col_fwd(const P2Args& a, const LimbTab& tab, uint32_t e, uint32_t tile, u64* sm) {
+    using G = Col<LC>;
+    const uint32_t mi = tab_mod(e), logN = LC + 8;
+    const u64* src = tab_src(tab, e, logN);
+    const ulonglong2* tw = a.tw + ((size_t)mi << logN);
+    const uint32_t t = threadIdx.x >> G::LCOLS, cl = threadIdx.x & (G::C - 1), c = tile * G::C + cl;
+    u64 x[16];
+#pragma unroll
+    for (int k = 0; k < 16; k++) x[k] = (src + ((size_t)k << (G::LT + 8)))[t * 256 + c];
+    ulonglong2 w1[15], w2[15];                           // w1: the same for the whole limb (scalar registers)
+    if (LC <= 8) tw_load<G::U0, 4>(w2, tw, LC - 4, t);
+    else tw_load<0, 4>(w2, tw, 4, t >> 1);
+    tw_load<0, 4>(w1, tw, 0, 0);
+    const ModConst m = a.mc[mi];
+    const ModConst ml = a.mc[RS ? a.rs_mod : mi];
+    u64* dst = a.dst + ((size_t)tab_dst(e) << logN);
+    const u64 q = uni64(m.q);
+    if (RS) {
+        const u64 h = ml.q >> 1, hr = barrett64(h, q, m.mu, m.bits);
+#pragma unroll
+        for (int k = 0; k < 16; k++) x[k] = submod(barrett64(addmod(x[k], h, ml.q), q, m.mu, m.bits), hr, q);
+    }
+    fwd_stages<WIDE, 0, 4>(x, w1, q);
+#pragma unroll
+    for (int k = 0; k < 16; k++) sm[G::pos(t + (k << G::LT), cl)] = x[k];
+    __syncthreads();
+    if (LC <= 8) {
+#pragma unroll
+        for (int j = 0; j < 16; j++) x[j] = sm[G::pos(16 * t + j, cl)];
+        fwd_stages<WIDE, G::U0, 4>(x, w2, q);
+    } else {
+        // nine stages: rows 32G + e + 2j for stages 4..7 (t = 2G + e), then contiguous rows for stage 8
+        const uint32_t r0 = (t >> 1) * 32 + (t & 1);
+#pragma unroll
+        for (int j = 0; j < 16; j++) x[j] = sm[G::pos(r0 + 2 * j, cl)];
+        fwd_stages<WIDE, 0, 4>(x, w2, q);
+        ulonglong2 w3[15];
+        tw_load<3, 4>(w3, tw, 5, t);
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < 16; j++) sm[G::pos(r0 + 2 * j, cl)] = x[j];
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < 16; j++) x[j] = sm[G::pos(16 * t + j, cl)];
+        fwd_stages<WIDE, 3, 4>(x, w3, q);
+    }
+#pragma unroll
+    for (int j = 0; j < 16; j++) (dst + j * 256)[t * 4096 + c] = x[j];
+}
+
+template <int LC, bool RS>
+__global__ __launch_bounds__(P2_THREADS) void ntt_col_fwd_kernel(P2Args a, LimbTab tab) {
+    using G = Col<LC>;
+    __shared__ u64 sm[G::LDS];
+    const uint32_t tile = blockIdx.x & (G::T - 1), e = __builtin_amdgcn_readfirstlane(tab.e[blockIdx.x >> G::LT]);
+    if (e & TAB_WIDE) col_fwd<LC, RS, true>(a, tab, branch_pin<true>(e), tile, sm);
+    else col_fwd<LC, RS, false>(a, tab, branch_pin<false>(e), tile, sm);
+}
+
+// Inverse column stages and output scaling: inputs below 4q, results canonical.  Stage 0 (one twiddle for the whole limb)
+// carries the scaling: the sum is multiplied by the scale, the difference by scale * twiddle.  Narrow moduli: bounds
+// 4 -> at most 64 (128 for N = 2^17) -> 1024, where the last sum still fits 64 bits.
+template <int LC, bool CUSTOM_SCALE, bool WIDE>
+__device__ __forceinline__ void col_inv(const P2Args& a, uint32_t e, uint32_t tile, u64* sm, const ScaleList& sc, uint32_t scale_period) {
+    using G = Col<LC>;
+    const uint32_t mi = tab_mod(e), logN = LC + 8, limb = tab_dst(e);
+    u64* data = a.dst + ((size_t)limb << logN);
+    const ulonglong2* tw = a.tw + ((size_t)mi << logN);
+    const uint32_t t = threadIdx.x >> G::LCOLS, cl = threadIdx.x & (G::C - 1), c = tile * G::C + cl;
+    u64 x[16];
+#pragma unroll
+    for (int j = 0; j < 16; j++) x[j] = (data + j * 256)[t * 4096 + c];
+    ulonglong2 w1[15], w2[15];
+    if (LC <= 8) tw_load<G::U0, 4>(w2, tw, LC - 4, t);
+    else tw_load<0, 4>(w2, tw, 4, t >> 1);
+    const ModConst m = a.mc[mi];
+    const uint32_t si = CUSTOM_SCALE ? limb % scale_period : 0;
+    const u64 cs = CUSTOM_SCALE ? sc.s[si] : m.ninv, cs_sh = CUSTOM_SCALE ? sc.s_sh[si] : m.ninv_sh;
+    const u64 cw = CUSTOM_SCALE ? sc.w[si] : m.ninv_w, cw_sh = CUSTOM_SCALE ? sc.w_sh[si] : m.ninv_w_sh;
+    const u64 q = uni64(m.q);
+    int bd[16];
+    bounds_all(bd, 4);
+    int after;                                           // bound of every point after the exchange, narrow moduli
+    if (LC <= 8) {
+        inv_stages<WIDE, G::U0, 4>(x, bd, w2, q);
+        if (WIDE) settle4(x, bd, q);
+#pragma unroll
+        for (int j = 0; j < 16; j++) sm[G::pos(16 * t + j, cl)] = x[j];
+        after = 4 << (4 - G::U0);
+    } else {
+        ulonglong2 w3[15];
+        tw_load<3, 4>(w3, tw, 5, t);
+        inv_stages<WIDE, 3, 4>(x, bd, w3, q);
+        if (WIDE) settle4(x, bd, q);
+        const uint32_t r0 = (t >> 1) * 32 + (t & 1);
+#pragma unroll
+        for (int j = 0; j < 16; j++) sm[G::pos(16 * t + j, cl)] = x[j];
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < 16; j++) x[j] = sm[G::pos(r0 + 2 * j, cl)];
+        bounds_all(bd, WIDE ? 4 : 8);
+        inv_stages<WIDE, 0, 4>(x, bd, w2, q);
+        if (WIDE) settle4(x, bd, q);
+        else {
+#pragma unroll
+            for (int j = 0; j < 16; j++) x[j] = reduce_lazy<10>(x[j], q, m.bits, m.rec);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < 16; j++) sm[G::pos(r0 + 2 * j, cl)] = x[j];
+        after = 2;
+    }
+    tw_load<1, 4>(w1, tw, 0, 0);                         // the same for the whole limb (scalar registers)
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 16; k++) x[k] = sm[G::pos(t + (k << G::LT), cl)];
+    bounds_all(bd, WIDE ? 4 : after);
+    inv_stages<WIDE, 1, 4>(x, bd, w1, q);
+    if (WIDE) settle4(x, bd, q);
+    const u64 bq = WIDE ? 4 * q : 512 * q;
+#pragma unroll
+    for (int k = 0; k < 8; k++) {
+        const u64 X = x[k], Y = x[k + 8];
+        x[k] = shoup_lazy4(X + Y, cs, cs_sh, q);
+        x[k + 8] = shoup_lazy4((X + bq) - Y, cw, cw_sh, q);
+    }
+#pragma unroll
+    for (int k = 0; k < 16; k++) (data + ((size_t)k << (G::LT + 8)))[t * 256 + c] = csub_u(csub_u(x[k], 2 * q), q);
+}
+
+template <int LC, bool CUSTOM_SCALE>
+__global__ __launch_bounds__(P2_THREADS, 4) void ntt_col_inv_kernel(P2Args a, LimbTab tab, ScaleList sc, uint32_t scale_period) {
+    using G = Col<LC>;
+    __shared__ u64 sm[G::LDS];
+    const uint32_t tile = blockIdx.x & (G::T - 1), e = __builtin_amdgcn_readfirstlane(tab.e[blockIdx.x >> G::LT]);
+    if (e & TAB_WIDE) col_inv<LC, CUSTOM_SCALE, true>(a, branch_pin<true>(e), tile, sm, sc, scale_period);
+    else col_inv<LC, CUSTOM_SCALE, false>(a, branch_pin<false>(e), tile, sm, sc, scale_period);
+}
+
+// ---------------------------------------------------------------- key-switch inner products inside the row passes
+// sum over the digits of digit_j (gathered by the Galois map) * key_j for adjacent pairs of positions.  An aligned pair of
+// positions comes from an aligned pair, in order or swapped, so a digit's two values are one 16-byte load; they are
+// multiplied in the order they arrive ("slots": slot s belongs to output position pos + (s ^ swap)) and the key is read in
+// that order.  Values are split in halves of 30 bits and their products summed in three 64-bit words that the
+// multiply-adds feed directly: 4 instructions per product, where a 128-bit sum takes 14.  Digits are below 2q for moduli
+// of at most 57 bits and canonical above, keys canonical: a0 and a2 take below 2^60 per product, a1 below 2^61 (wide) or
+// 2^59 (narrow), so 7 (wide) or 15 products fit.
+#define IP_H 30
+struct IpSum {
+    u64 a0, a1, a2;
+};
+__device__ __forceinline__ void ip_mac(IpSum& s, u64 d, u64 k) {
+    const uint32_t M = (1u << IP_H) - 1;
+    const uint32_t d0 = (uint32_t)d & M, d1 = (uint32_t)(d >> IP_H), k0 = (uint32_t)k & M, k1 = (uint32_t)(k >> IP_H);
+    s.a0 += (u64)d0 * k0;
+    s.a1 += (u64)d0 * k1;
+    s.a1 += (u64)d1 * k0;
+    s.a2 += (u64)d1 * k1;
+}
+__device__ __forceinline__ u128 ip_value(const IpSum& s) { return (u128)s.a0 + ((u128)s.a1 << IP_H) + ((u128)s.a2 << (2 * IP_H)); }
+// below 5q
+__device__ __forceinline__ u64 ip_reduce(const IpSum& s, const ModConst& m) { return barrett128_lazy(ip_value(s), m.q, m.mu, m.bits); }
+
+// What one (polynomial, key) term contributes to a limb: base pointers of the digits and keys of this limb.
+struct IpTerm {
+    const u64 *raised, *own, *key;                       // own: digit own_j's limb, which is not materialised in raised
+    uint32_t own_j, g;
+};
+// Two pairs of positions (4 points) of a row: positions row0 + e and row0 + e + 32.
+template <int NJ>
+struct IpLoad {
+    ulonglong2 d[NJ][2];
+    u64 k[NJ][2][2];
+};
+__device__ __forceinline__ void ip_map(uint32_t (&src)[2], uint32_t (&swp)[2], uint32_t pos, uint32_t g, uint32_t logN) {
+#pragma unroll
+    for (int p = 0; p < 2; p++) {
+        const uint32_t s = galois_pos(pos + 32 * p, g, logN);
+        src[p] = s & ~1u;
+        swp[p] = s & 1u;
+    }
+}
+template <int NJ>
+__device__ __forceinline__ void ip_request(IpLoad<NJ>& L, const IpTerm& tm, uint32_t j0, uint32_t nj, uint32_t pos, const uint32_t (&src)[2],
+                                           const uint32_t (&swp)[2], size_t dig_stride, size_t key_stride) {
+#pragma unroll
+    for (int jj = 0; jj < NJ; jj++) {
+        if ((uint32_t)jj < nj) {
+            const uint32_t j = j0 + jj;
+            const u64* dj = j == tm.own_j ? tm.own : tm.raised + j * dig_stride;
+            const u64* kj = tm.key + j * key_stride;
+#pragma unroll
+            for (int p = 0; p < 2; p++) {
+                L.d[jj][p] = *reinterpret_cast<const ulonglong2*>(dj + src[p]);
+                const uint32_t kp = (pos + 32 * p) | swp[p];
+                L.k[jj][p][0] = kj[kp];
+                L.k[jj][p][1] = kj[kp ^ 1u];
+            }
+        }
+    }
+}
+template <int NJ>
+__device__ __forceinline__ void ip_consume(IpSum (&s)[4], const IpLoad<NJ>& L, uint32_t nj) {
+#pragma unroll
+    for (int jj = 0; jj < NJ; jj++) {
+        if ((uint32_t)jj < nj) {
+#pragma unroll
+            for (int p = 0; p < 2; p++) {
+                ip_mac(s[2 * p], L.d[jj][p].x, L.k[jj][p][0]);
+                ip_mac(s[2 * p + 1], L.d[jj][p].y, L.k[jj][p][1]);
+            }
+        }
+    }
+}
+// the two slots of a pair in position order
+__device__ __forceinline__ ulonglong2 ip_order(u64 v0, u64 v1, uint32_t swp) {
+    return swp ? make_ulonglong2(v1, v0) : make_ulonglong2(v0, v1);
+}
+
+// The inner product of a row for one job: 4 chunks of 4 points per thread, the next chunk's operands requested before this
+// chunk's products.  BETA = 1, 2, 3: exactly that many digits; 0: any number up to 8, three at a time.  emit(chunk, pos, sums
+// below 5q in slot order, swaps).
+template <int BETA, class Emit>
+__device__ __forceinline__ void ip_row(const IpTerm& tm, uint32_t beta, uint32_t row0, uint32_t t, uint32_t logN, size_t dig_stride,
+                                       size_t key_stride, const ModConst& m, Emit&& emit) {
+    constexpr int NJ = BETA ? BETA : 3;
+    uint32_t src[2], swp[2];
+    if (BETA) {
+        IpLoad<NJ> cur, nxt;
+        ip_map(src, swp, row0 + 2 * t, tm.g, logN);
+        ip_request(cur, tm, 0, NJ, row0 + 2 * t, src, swp, dig_stride, key_stride);
+#pragma unroll
+        for (int ch = 0; ch < 4; ch++) {
+            const uint32_t pos = row0 + 2 * t + 64 * ch;
+            uint32_t nsrc[2] = {0, 0}, nswp[2] = {0, 0};
+            if (ch < 3) {
+                ip_map(nsrc, nswp, pos + 64, tm.g, logN);
+                ip_request(nxt, tm, 0, NJ, pos + 64, nsrc, nswp, dig_stride, key_stride);
+            }
+            SCHED_FENCE();
+            IpSum s[4] = {};
+            ip_consume(s, cur, NJ);
+            u64 v[4];
+#pragma unroll
+            for (int i = 0; i < 4; i++) v[i] = ip_reduce(s[i], m);
+            emit(ch, pos, v, src, swp);
+            if (ch < 3) {
+                cur = nxt;
+#pragma unroll
+                for (int p = 0; p < 2; p++) { src[p] = nsrc[p]; swp[p] = nswp[p]; }
+            }
+        }
+    } else {
+#pragma unroll
+        for (int ch = 0; ch < 4; ch++) {
+            const uint32_t pos = row0 + 2 * t + 64 * ch;
+            ip_map(src, swp, pos, tm.g, logN);
+            IpSum s[4] = {};
+            u64 v[4] = {0, 0, 0, 0};
+            for (uint32_t j0 = 0; j0 < beta; j0 += NJ) {
+                IpLoad<NJ> L;
+                const uint32_t nj = beta - j0 < NJ ? beta - j0 : NJ;
+                ip_request(L, tm, j0, nj, pos, src, swp, dig_stride, key_stride);
+                if (j0 == 6) {                           // seven products at most in one sum
+#pragma unroll
+                    for (int i = 0; i < 4; i++) { v[i] = ip_reduce(s[i], m); s[i] = IpSum{0, 0, 0}; }
+                }
+                ip_consume(s, L, nj);
+            }
+#pragma unroll
+            for (int i = 0; i < 4; i++) v[i] = beta > 6 ? reduce_lazy<7>(v[i] + ip_reduce(s[i], m), m.q, m.bits, m.rec) : ip_reduce(s[i], m);
+            emit(ch, pos, v, src, swp);
+        }
+    }
+}
+// The same for the sum over n_terms terms (a sum of rotations with one ModDown); term(i) describes term i.
+template <class Term, class Emit>
+__device__ __forceinline__ void ip_row_terms(Term&& term, uint32_t n_terms, uint32_t beta, uint32_t row0, uint32_t t, uint32_t logN,
+                                             size_t dig_stride, size_t key_stride, const ModConst& m, Emit&& emit) {
+    const uint32_t most = m.bits > 57 ? 7 : 15;
+#pragma unroll 1
+    for (int ch = 0; ch < 4; ch++) {
+        const uint32_t pos = row0 + 2 * t + 64 * ch;
+        u64 tot[4] = {0, 0, 0, 0};                       // in position order
+        for (uint32_t i = 0; i < n_terms; i++) {
+            const IpTerm tm = term(i);
+            uint32_t src[2], swp[2], pending = 0;
+            ip_map(src, swp, pos, tm.g, logN);
+            IpSum s[4] = {};
+            auto flush = [&]() {
+#pragma unroll
+                for (int p = 0; p < 2; p++) {
+                    const ulonglong2 v = ip_order(ip_reduce(s[2 * p], m), ip_reduce(s[2 * p + 1], m), swp[p]);
+                    tot[2 * p] = reduce_lazy<7>(tot[2 * p] + v.x, m.q, m.bits, m.rec);
+                    tot[2 * p + 1] = reduce_lazy<7>(tot[2 * p + 1] + v.y, m.q, m.bits, m.rec);
+                    s[2 * p] = s[2 * p + 1] = IpSum{0, 0, 0};
+                }
+                pending = 0;
+            };
+            for (uint32_t j0 = 0; j0 < beta; j0 += 3) {
+                IpLoad<3> L;
+                const uint32_t nj = beta - j0 < 3 ? beta - j0 : 3;
+                ip_request(L, tm, j0, nj, pos, src, swp, dig_stride, key_stride);
+                if (pending + nj > most) flush();
+                ip_consume(s, L, nj);
+                pending += nj;
+            }
+            flush();
+        }
+        const uint32_t src[2] = {pos, pos + 32}, swp[2] = {0, 0};
+        emit(ch, pos, tot, src, swp);
+    }
+}
+
+// ---------------------------------------------------------------- forward row pass
+// Pass B: workgroup = 16 consecutive rows (256-point blocks); tid = blk*16 + t.
+// EPI: 0 = plain transform; 1 = ModDown epilogue with the accumulator read from memory; 2 = ModDown epilogue that also
+// computes the accumulator (the key-switch inner product of this limb) from the raised digits and the key, so that the
+// q-limbs of the accumulator never exist in memory (BETA as in ip_row); 3 = the same for a sum over several terms.
+template <bool WIDE, int EPI, int BETA>
+__device__ __forceinline__ void row_fwd(const P2Args& a, uint32_t e, uint32_t tile, u64* sm, const ModDownEpilogue& ep) {
+    const uint32_t mi = tab_mod(e), limb = tab_dst(e), logN = a.logN, lc = logN - 8;
+    const ulonglong2* tw = a.tw + ((size_t)mi << logN);
+    const uint32_t blk = threadIdx.x >> 4, t = threadIdx.x & 15, b = tile * 16 + blk, G2 = 16 * b + t;
+    u64* row = a.dst + ((size_t)limb << logN) + (size_t)b * 256;
+    u64* s = sm + blk * 272;
+    u64 x[16];
+    ulonglong2 w1[15], w2[15];
+    tw_load<0, 4>(w1, tw, lc, b);
+#pragma unroll
+    for (int k = 0; k < 16; k++) x[k] = row[t + 16 * k];
+    const ModConst m = a.mc[mi];
+    const u64 q = uni64(m.q);
+    SCHED_FENCE();
+    fwd_stages<WIDE, 0, 3>(x, w1, q);
+    SCHED_FENCE();
+    tw_load<0, 3>(w2, tw, lc + 4, G2);                   // into the registers that the first three stages' factors leave
+    SCHED_FENCE();
+    fwd_stages<WIDE, 3, 4>(x, w1, q);
+    SCHED_FENCE();
+    tw_load<3, 4>(w2, tw, lc + 4, G2);
+    SCHED_FENCE();
+#pragma unroll
+    for (int k = 0; k < 16; k++) s[t + 17 * k] = x[k];
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 16; j++) x[j] = s[17 * t + j];
+    fwd_stages<WIDE, 0, 4>(x, w2, q);
+    if (EPI == 0) {
+        if (!WIDE && a.lazy) {
+#pragma unroll
+            for (int j = 0; j < 16; j++) x[j] = reduce_lazy<7>(x[j], q, m.bits, m.rec);
+        } else {
+#pragma unroll
+            for (int j = 0; j < 16; j++) x[j] = reduce_full<7>(x[j], q, m.bits, m.rec);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < 16; j++) s[17 * t + j] = x[j];
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < 16; k++) row[t + 16 * k] = s[t + 17 * k];
+        return;
+    }
+    // out = (acc - ntt) * P^-1 + sigma(c0) + self: the product is below 4q whatever its factor, so the transform value may
+    // stay as it is where 128q plus the accumulator fits 64 bits, else below 2q; the sum is below 6q
+    const bool raw = !WIDE && m.bits <= 55;
+    if (!raw) {
+#pragma unroll
+        for (int j = 0; j < 16; j++) x[j] = reduce_lazy<7>(x[j], q, m.bits, m.rec);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 16; j++) s[17 * t + j] = x[j];
+    const u64 bias = raw ? (q << 7) : 2 * q;
+    const uint32_t pc = limb / ep.L1, r = limb - pc * ep.L1, job = pc >> 1, comp = pc & 1u, row0 = b * 256;
+    const u64 pinv = ep.pinv[r], pinv_sh = ep.pinv_sh[r];
+    const size_t ro = (size_t)r << logN;
+    u64* out = (comp ? ep.out1[job] : ep.out0[job]) + ro;
+    const u64* c0p = comp == 0 ? ep.c0[job] : nullptr;
+    const u64* sp = comp ? ep.self1[job] : ep.self0[job];
+    const bool has_c0 = c0p != nullptr, has_self = sp != nullptr;
+    const u64* c0 = has_c0 ? c0p + ro : nullptr;
+    const u64* self = has_self ? sp + ro : nullptr;
+    __syncthreads();
+    // v: accumulator values in slot order, below 5q
+    auto emit = [&](int ch, uint32_t pos, const u64 (&v)[4], const uint32_t (&src)[2], const uint32_t (&swp)[2]) {
+        ulonglong2 cv[2], sv[2];
+#pragma unroll
+        for (int p = 0; p < 2; p++) {
+            cv[p] = has_c0 ? *reinterpret_cast<const ulonglong2*>(c0 + src[p]) : make_ulonglong2(0, 0);
+            sv[p] = has_self ? *reinterpret_cast<const ulonglong2*>(self + pos + 32 * p) : make_ulonglong2(0, 0);
+        }
+#pragma unroll
+        for (int p = 0; p < 2; p++) {
+            const uint32_t e = pos - row0 + 32 * p, l = e + (e >> 4);
+            const ulonglong2 acc = ip_order(v[2 * p], v[2 * p + 1], swp[p]), c = ip_order(cv[p].x, cv[p].y, swp[p]);
+            ulonglong2 o;
+            o.x = shoup_acc(c.x + sv[p].x, acc.x + bias - s[l], pinv, pinv_sh, q);
+            o.y = shoup_acc(c.y + sv[p].y, acc.y + bias - s[l + 1], pinv, pinv_sh, q);
+            o.x = reduce_full<7>(o.x, q, m.bits, m.rec);
+            o.y = reduce_full<7>(o.y, q, m.bits, m.rec);
+            *reinterpret_cast<ulonglong2*>(out + pos + 32 * p) = o;
+        }
+    };
+    const size_t dig_stride = (size_t)ep.R << logN, key_stride = (size_t)(2 * ep.M) << logN;
+    const size_t ko = (size_t)(comp * ep.M + r) << logN;
+    if (EPI == 1) {
+        const u64* acc = ep.acc + ((size_t)(pc * ep.R + r) << logN);
+        const uint32_t g = ep.g[job];
+        ulonglong2 av[8];
+#pragma unroll
+        for (int p = 0; p < 8; p++) av[p] = *reinterpret_cast<const ulonglong2*>(acc + row0 + 2 * t + 32 * p);
+#pragma unroll
+        for (int ch = 0; ch < 4; ch++) {
+            const uint32_t pos = row0 + 2 * t + 64 * ch;
+            uint32_t src[2] = {pos, pos + 32}, swp[2] = {0, 0};
+            u64 v[4] = {av[2 * ch].x, av[2 * ch].y, av[2 * ch + 1].x, av[2 * ch + 1].y};
+            if (has_c0 && g != 1) {                      // accumulator values into slot order
+                ip_map(src, swp, pos, g, logN);
+#pragma unroll
+                for (int p = 0; p < 2; p++) {
+                    const ulonglong2 o = ip_order(v[2 * p], v[2 * p + 1], swp[p]);
+                    v[2 * p] = o.x; v[2 * p + 1] = o.y;
+                }
+            }
+            emit(ch, pos, v, src, swp);
+        }
+    } else if (EPI == 2) {
+        const IpTerm tm = {ep.raised[job] + ro, ep.own[job] + ro, ep.evk[job] + ko, r / ep.alpha, ep.g[job]};
+        ip_row<BETA>(tm, ep.beta, row0, t, logN, dig_stride, key_stride, m, emit);
+    } else {
+        ip_row_terms([&](uint32_t i) { return IpTerm{ep.raised[i] + ro, ep.own[i] + ro, ep.evk[i] + ko, r / ep.alpha, ep.g[i]}; }, ep.n_terms,
+                     ep.beta, row0, t, logN, dig_stride, key_stride, m, emit);
+    }
+}
+
+template <int EPI, int BETA>
+__global__ __launch_bounds__(P2_THREADS, EPI >= 2 ? 3 : 4) void ntt_row_fwd_kernel(P2Args a, LimbTab tab, ModDownEpilogue ep) {
+    __shared__ u64 sm[16 * 272];                         // 16 groups of 17: conflict-free both ways
+    uint32_t tile;
+    const uint32_t e = row_decode(tab, a, tile);
+    if (e == TAB_NONE) return;
+    if (e & TAB_WIDE) row_fwd<true, EPI, BETA>(a, branch_pin<true>(e), tile, sm, ep);
+    else row_fwd<false, EPI, BETA>(a, branch_pin<false>(e), tile, sm, ep);
+}
+
+// ---------------------------------------------------------------- inverse row pass
+// Stages LC+7 .. LC+4 on contiguous points, exchange, stages LC+3 .. LC on strided points: inputs canonical, results below
+// 4q.  Narrow moduli: bounds 1 -> 32 after the first block, -> 512 after the second, one quotient step at the end.
+// With IP the inputs are not read: they are the key-switch inner product of the special-prime limbs, computed here from the
+// raised digits and the key.  IP: 0 = none, 1 = one job per limb (BETA as in ip_row), 2 = a sum over several terms.
+template <bool WIDE, int IP, int BETA>
+__device__ __forceinline__ void row_inv(const P2Args& a, const LimbTab& tab, uint32_t e, uint32_t tile, u64* sm, const IpPrologue& ip) {
+    const uint32_t mi = tab_mod(e), limb = tab_dst(e), logN = a.logN, lc = logN - 8;
+    const ModConst m = a.mc[mi];
+    const ulonglong2* tw = a.tw + ((size_t)mi << logN);
+    const uint32_t blk = threadIdx.x >> 4, t = threadIdx.x & 15, b = tile * 16 + blk;
+    u64* out = a.dst + ((size_t)limb << logN) + (size_t)b * 256;
+    u64* s = sm + blk * 272;
+    u64 x[16];
+    ulonglong2 w2[15];
+    if (IP == 0) {
+        const u64* in = tab_src(tab, e, logN) + (size_t)b * 256;
+#pragma unroll
+        for (int k = 0; k < 16; k++) x[k] = in[t + 16 * k];
+        tw_load<0, 4>(w2, tw, lc + 4, 16 * b + t);
+        SCHED_FENCE();
+#pragma unroll
+        for (int k = 0; k < 16; k++) s[t + 17 * k] = x[k];
+    } else {
+        const uint32_t pc = limb / ip.k, tp = limb - pc * ip.k, job = pc >> 1, comp = pc & 1u, row0 = b * 256;
+        const size_t dig_stride = (size_t)ip.R << logN, key_stride = (size_t)(2 * ip.M) << logN;
+        const size_t ro = (size_t)(ip.L1 + tp) << logN, ko = (size_t)(comp * ip.M + ip.nq + tp) << logN;
+        auto emit = [&](int, uint32_t pos, const u64 (&v)[4], const uint32_t (&)[2], const uint32_t (&swp)[2]) {
+#pragma unroll
+            for (int p = 0; p < 2; p++) {
+                const uint32_t at = pos - row0 + 32 * p, l = at + (at >> 4);
+                const ulonglong2 o = ip_order(v[2 * p], v[2 * p + 1], swp[p]);
+                s[l] = reduce_full<7>(o.x, m.q, m.bits, m.rec);
+                s[l + 1] = reduce_full<7>(o.y, m.q, m.bits, m.rec);
+            }
+        };
+        if (IP == 1) {
+            const IpTerm tm = {ip.raised[job] + ro, nullptr, ip.evk[job] + ko, 0xFFFFFFFFu, ip.g[job]};
+            ip_row<BETA>(tm, ip.beta, row0, t, logN, dig_stride, key_stride, m, emit);
+        } else {
+            ip_row_terms([&](uint32_t i) { return IpTerm{ip.raised[i] + ro, nullptr, ip.evk[i] + ko, 0xFFFFFFFFu, ip.g[i]}; }, ip.n_terms, ip.beta,
+                         row0, t, logN, dig_stride, key_stride, m, emit);
+        }
+        tw_load<0, 4>(w2, tw, lc + 4, 16 * b + t);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 16; j++) x[j] = s[17 * t + j];
+    const u64 q = uni64(m.q);
+    ulonglong2 w1[15];
+    int bd[16];
+    bounds_all(bd, 1);
+    inv_stages<WIDE, 2, 4>(x, bd, w2, q);
+    SCHED_FENCE();
+    tw_load<2, 4>(w1, tw, lc, b);                        // into the registers that the first two stages' factors leave
+    SCHED_FENCE();
+    inv_stages<WIDE, 0, 2>(x, bd, w2, q);
+    if (WIDE) settle4(x, bd, q);
+    SCHED_FENCE();
+    tw_load<0, 2>(w1, tw, lc, b);
+    SCHED_FENCE();
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 16; j++) s[17 * t + j] = x[j];
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 16; k++) x[k] = s[t + 17 * k];
+    bounds_all(bd, WIDE ? 4 : 32);
+    inv_stages<WIDE, 0, 4>(x, bd, w1, q);
+    if (WIDE) settle4(x, bd, q);
+    else {
+#pragma unroll
+        for (int k = 0; k < 16; k++) x[k] = reduce_lazy<10>(x[k], q, m.bits, m.rec);
+    }
+#pragma unroll
+    for (int k = 0; k < 16; k++) out[t + 16 * k] = x[k];
+}
+
+template <int IP, int BETA>
+__global__ __launch_bounds__(P2_THREADS, IP ? 3 : 4) void ntt_row_inv_kernel(P2Args a, LimbTab tab, IpPrologue ip) {
+    __shared__ u64 sm[16 * 272];
+    uint32_t tile;
+    const uint32_t e = row_decode(tab, a, tile);
+    if (e == TAB_NONE) return;
+    if (e & TAB_WIDE) row_inv<true, IP, BETA>(a, tab, branch_pin<true>(e), tile, sm, ip);
+    else row_inv<false, IP, BETA>(a, tab, branch_pin<false>(e), tile, sm, ip);
+}
+
+// ---------------------------------------------------------------- column passes fused around the basis conversion
+// Latency path for small launches (a few limbs: the low levels the paper's networks run at), where the chip is mostly
+// idle and a call is bound by its chain of dependent launches.  The last inverse pass, the basis conversion and the
+// first forward pass all work on columns of the 256 x 256 view, so one work group takes ONE column through all
+// three: every source limb of a group (a digit of ModUp, the special-prime limbs of one ModDown component; at most 8)
+// goes through the inverse column stages and its output scaling into LDS, then every target limb is converted from
+// those (128-bit sums, lazy Barrett), run through the forward column stages and written.  One launch instead of
+// three; the coefficient-form limbs and the converted limbs never exist in memory.  One wavefront per limb, four
+// points per lane (two stages in registers, then an exchange through LDS), so that a conversion of a single digit
+// already spreads over every compute unit; the 8-byte accesses this makes (a column is strided by 2 KiB) cost
+// bandwidth that a launch this small does not need.
+#define CF_THREADS 512
+#define CF_WAVES 8
+#define CF_EX 272            // 256 points + one spare per 16
+
+__device__ __forceinline__ uint32_t cf_pos(uint32_t i) { return i + (i >> 4); }
+
+__global__ __launch_bounds__(CF_THREADS) void ntt16_colfuse_kernel(ColFuse cf, ScaleList sc, const ModConst* mc, const ulonglong2* tw,
+                                                                   const ulonglong2* itw) {
+    __shared__ u64 ys[CF_WAVES * 256];
+    __shared__ u64 ex[CF_WAVES * CF_EX];
+    // work groups go to the XCDs round-robin: give each XCD 32 adjacent columns, so that the sixteen columns that
+    // share a 128-byte line are read and written through one L2
+    const uint32_t g = blockIdx.x >> 8, c = (blockIdx.x & 7) * 32 + ((blockIdx.x >> 3) & 31);
+    const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;   // w: the same for the wavefront
+    const CfGroup gp = cf.grp[g];
+    const uint32_t ns = gp.ns, set = gp.set, nt = cf.nt[set];
+    u64* exw = ex + w * CF_EX;
+    u64 x[4];
+    // Everything a wavefront will need is requested before anything is computed, so that the dependent memory round
+    // trips (arguments -> constants of the modulus -> data and twiddles) are paid once, not once per phase: the source
+    // limb's points and all its twiddles, and for the first target limb its modulus and conversion constants.
+    const bool src_on = w < ns;
+    const uint32_t mi = gp.mod0 + (src_on ? w : 0);
+    const u64* data = gp.src + ((size_t)(src_on ? w : 0) << 16) + c;
+    if (src_on) {
+#pragma unroll
+        for (int k = 0; k < 4; k++) x[k] = data[(size_t)(4 * lane + k) * 256];
+    }
+    u64 t1[4][6];
+#pragma unroll
+    for (int blk = 0; blk < 4; blk++) tw_block2(t1[blk], itw + ((size_t)mi << 16), 2 * blk, lane >> (6 - 2 * blk));
+    const ModConst m1 = mc[mi];
+    const uint32_t si = gp.sc0 + (src_on ? w : 0);
+    const u64 cs = sc.s[si], cs_sh = sc.s_sh[si];
+    uint32_t mr = __builtin_amdgcn_readfirstlane(cf.tgt_mod[set][w < nt ? w : 0]);
+    ModConst m2 = mc[mr];
+    u64 hat[CF_WAVES];                                       // a row of the table is padded to 8 entries, zeros past ns
+#pragma unroll
+    for (int i = 0; i < CF_WAVES; i++) hat[i] = gp.hat[(size_t)mr * cf.hat_w + i];
+    {   // inverse column stages 7..0 of source w (wavefronts beyond the group's sources idle through the barriers)
+        const u64 q = uni64(m1.q);
+#pragma unroll
+        for (int blk = 3; blk >= 0; blk--) {
+            const uint32_t s0 = 2 * blk, log_span = 6 - s0, span = 1u << log_span;
+            const uint32_t G = lane >> log_span, base = (G << (8 - s0)) + (lane & (span - 1));
+            if (blk < 3) {
+                __syncthreads();
+                if (src_on) {
+#pragma unroll
+                    for (int k = 0; k < 4; k++) x[k] = exw[cf_pos(base + (k << log_span))];
+                }
+            }
+            if (src_on) {
+                inv_block2_r(x, t1[blk], q);
+                if (blk > 0) {
+#pragma unroll
+                    for (int k = 0; k < 4; k++) exw[cf_pos(base + (k << log_span))] = x[k];
+                } else {
+#pragma unroll
+                    for (int k = 0; k < 4; k++) ys[w * 256 + lane + 64 * k] = csub(shoup_lazy(x[k], cs, cs_sh, q), q);
+                }
+            }
+        }
+    }
+    for (uint32_t t0 = 0; t0 < nt; t0 += CF_WAVES) {
+        const uint32_t ti = t0 + w;
+        const bool active = ti < nt;
+        if (t0) {                                            // later rounds fetch their constants as they start
+            mr = __builtin_amdgcn_readfirstlane(cf.tgt_mod[set][active ? ti : 0]);
+            m2 = mc[mr];
+#pragma unroll
+            for (int i = 0; i < CF_WAVES; i++) hat[i] = gp.hat[(size_t)mr * cf.hat_w + i];
+        }
+        u64 t2[4][6];
+#pragma unroll
+        for (int blk = 0; blk < 4; blk++) tw_block2(t2[blk], tw + ((size_t)mr << 16), 2 * blk, lane >> (6 - 2 * blk));
+        __syncthreads();                                     // the sources are in ys (first round)
+        const u64 q = uni64(m2.q), q4 = 4 * q;
+        const bool wide = m2.bits > 57;
+        if (active) {
+            u128 acc[4] = {};
+#pragma unroll
+            for (int i = 0; i < CF_WAVES; i++) {
+                if ((uint32_t)i < ns) {
+#pragma unroll
+                    for (int k = 0; k < 4; k++) acc[k] += (u128)ys[i * 256 + lane + 64 * k] * hat[i];
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < 4; k++) x[k] = barrett128_lazy(acc[k], q, m2.mu, m2.bits);      // below 5q
+        }
+#pragma unroll
+        for (int blk = 0; blk < 4; blk++) {
+            const uint32_t s0 = 2 * blk, log_span = 6 - s0, span = 1u << log_span;
+            const uint32_t G = lane >> log_span, base = (G << (8 - s0)) + (lane & (span - 1));
+            if (blk > 0) {
+                __syncthreads();
+                if (active) {
+#pragma unroll
+                    for (int k = 0; k < 4; k++) x[k] = exw[cf_pos(base + (k << log_span))];
+                }
+            }
+            if (active) {
+                if (wide) fwd_block2_r<true>(x, t2[blk], q, q4);
+                else fwd_block2_r<false>(x, t2[blk], q, q4);
+                if (blk < 3) {
+#pragma unroll
+                    for (int k = 0; k < 4; k++) exw[cf_pos(base + (k << log_span))] = x[k];
+                }
+            }
+        }
+        if (active) {
+            u64* dst = gp.dst + ((size_t)cf.tgt_limb[set][ti] << 16) + c;
+#pragma unroll
+            for (int k = 0; k < 4; k++) dst[(size_t)(4 * lane + k) * 256] = x[k];
+        }
+    }
+}
+
+int32_t launch_colfuse(he_ctx* ctx, const ColFuse& cf, const ScaleList& sc, uint32_t limb_passes) {
+    if (cf.n_groups == 0) return HE_OK;
+    if (cf.n_groups > CF_MAX_GROUPS) return he_fail(ctx, HE_ERR_BADARG, "column fusion: too many groups");
+    for (uint32_t g = 0; g < cf.n_groups; g++)
+        if (cf.grp[g].ns == 0 || cf.grp[g].ns > CF_WAVES || cf.grp[g].set >= CF_MAX_SETS || cf.grp[g].mod0 + cf.grp[g].ns > ctx->M ||
+            cf.grp[g].sc0 + cf.grp[g].ns > HE_MAX_MODULI || !cf.grp[g].src || !cf.grp[g].dst || !cf.grp[g].hat)
+            return he_fail(ctx, HE_ERR_BADARG, "column fusion: bad group %u", g);
+    hipEvent_t e0 = nullptr, e1 = nullptr;
+    if (ctx->prof_on) {
+        HE_HIP(ctx, hipEventCreate(&e0));
+        HE_HIP(ctx, hipEventCreate(&e1));
+        HE_HIP(ctx, hipEventRecord(e0, ctx->stream));
+    }
+    hipLaunchKernelGGL(ntt16_colfuse_kernel, dim3(cf.n_groups * 256), dim3(CF_THREADS), 0, ctx->stream, cf, sc, ctx->d_mc, ctx->d_tw,
+                       ctx->d_itw);
+    HE_HIP(ctx, hipGetLastError());
+    if (ctx->prof_on) {
+        HE_HIP(ctx, hipEventRecord(e1, ctx->stream));
+        ctx->prof_events.push_back({e0, e1, limb_passes, 0u, 0u});
+    }
+    return HE_OK;
+}
+
+// ---------------------------------------------------------------- butterfly-rate probe
+// The vector-ALU roof of the transforms, measured rather than derived: the register blocks of the passes
+// above (four stages on 16 points, twiddles from a 256-entry table that stays in the first-level cache)
+// run back to back with no other memory traffic.  Values wrap around after a few rounds; the timing does
+// not depend on them.
+template <bool FWD, bool WIDE>
+__global__ __launch_bounds__(P2_THREADS) void bfly_probe_kernel(const ulonglong2* __restrict__ tw, u64 q,
+                                                                 u64* __restrict__ out, uint32_t rounds) {
+    const uint32_t t = threadIdx.x & 15;
+    ulonglong2 w[15];
+    u64 x[16];
+    int bd[16];
+#pragma unroll
+    for (int k = 0; k < 16; k++) x[k] = (u64)(blockIdx.x * P2_THREADS + threadIdx.x) * 16 + k;
+    for (uint32_t r = 0; r < rounds; r++) {
+        tw_load<0, 4>(w, tw, 4, t);
+        if (FWD) fwd_stages<WIDE, 0, 4>(x, w, q);
+        else { bounds_all(bd, 4); inv_stages<WIDE, 0, 4>(x, bd, w, q); if (WIDE) settle4(x, bd, q); }
+    }
+    u64 v = 0;
+#pragma unroll
+    for (int k = 0; k < 16; k++) v ^= x[k];
+    out[blockIdx.x * P2_THREADS + threadIdx.x] = v;
+}
+
+int32_t probe_butterfly_rates(he_ctx* ctx, u64* d_out, uint32_t groups, double rate_out[3]) {
+    const uint32_t rounds = 64;                          // 32 butterflies per thread per round
+    uint32_t narrow = 0, wide = ctx->M;
+    for (uint32_t i = 0; i < ctx->M; i++) if (ctx->h_mc[i].bits > 57) { wide = i; break; }
+    hipEvent_t e0, e1;
+    HE_HIP(ctx, hipEventCreate(&e0));
+    HE_HIP(ctx, hipEventCreate(&e1));
+    for (int which = 0; which < 3; which++) {
+        const uint32_t mi = which == 2 ? wide : narrow;
+        rate_out[which] = 0.0;
+        if (mi >= ctx->M || (which != 2 && ctx->h_mc[mi].bits > 57)) continue;
+        const ulonglong2* tw = (which == 1 ? ctx->d_itw : ctx->d_tw) + (size_t)mi * ctx->N;
+        for (int rep = 0; rep < 2; rep++) {              // the first launch warms up
+            HE_HIP(ctx, hipEventRecord(e0, ctx->stream));
+            if (which == 0) hipLaunchKernelGGL((bfly_probe_kernel<true, false>), dim3(groups), dim3(P2_THREADS), 0, ctx->stream, tw, ctx->mod[mi], d_out, rounds);
+            else if (which == 1 && ctx->h_mc[mi].bits > 54) hipLaunchKernelGGL((bfly_probe_kernel<false, true>), dim3(groups), dim3(P2_THREADS), 0, ctx->stream, tw, ctx->mod[mi], d_out, rounds);
+            else if (which == 1) hipLaunchKernelGGL((bfly_probe_kernel<false, false>), dim3(groups), dim3(P2_THREADS), 0, ctx->stream, tw, ctx->mod[mi], d_out, rounds);
+            else hipLaunchKernelGGL((bfly_probe_kernel<true, true>), dim3(groups), dim3(P2_THREADS), 0, ctx->stream, tw, ctx->mod[mi], d_out, rounds);
+            HE_HIP(ctx, hipGetLastError());
+            HE_HIP(ctx, hipEventRecord(e1, ctx->stream));
+            HE_HIP(ctx, hipEventSynchronize(e1));
+        }
+        float ms = 0.f;
+        HE_HIP(ctx, hipEventElapsedTime(&ms, e0, e1));
+        rate_out[which] = (double)groups * P2_THREADS * 32.0 * rounds / (ms * 1e-3);
+    }
+    (void)hipEventDestroy(e0);
+    (void)hipEventDestroy(e1);
+    return HE_OK;
+}
+
+// ---------------------------------------------------------------- host
+#define COL_DISPATCH(K, SECOND, ...)                                                                              \
+    switch (ctx->logN - 8) {                                                                                         \
+    case 5: hipLaunchKernelGGL((K<5, SECOND>), __VA_ARGS__); break;                                                  \
+    case 6: hipLaunchKernelGGL((K<6, SECOND>), __VA_ARGS__); break;                                                  \
+    case 7: hipLaunchKernelGGL((K<7, SECOND>), __VA_ARGS__); break;                                                  \
+    case 8: hipLaunchKernelGGL((K<8, SECOND>), __VA_ARGS__); break;                                                  \
+    default: hipLaunchKernelGGL((K<9, SECOND>), __VA_ARGS__); break;                                                 \
+    }
+#define BETA_DISPATCH(K, FIRST, BETA_, ...)                                                                       \
+    switch (BETA_) {                                                                                                 \
+    case 1: hipLaunchKernelGGL((K<FIRST, 1>), __VA_ARGS__); break;                                                   \
+    case 2: hipLaunchKernelGGL((K<FIRST, 2>), __VA_ARGS__); break;                                                   \
+    case 3: hipLaunchKernelGGL((K<FIRST, 3>), __VA_ARGS__); break;                                                   \
+    default: hipLaunchKernelGGL((K<FIRST, 0>), __VA_ARGS__); break;                                                  \
+    }
+
+int32_t launch_transform2p(he_ctx* ctx, const TransformDesc& d) {
+    const uint32_t n = d.n, logN = ctx->logN;
+    const bool fwd = d.fwd;
+    if (d.rescale_from && (!fwd || d.rescale_from > ctx->M || d.only_pass == 2))
+        return he_fail(ctx, HE_ERR_BADARG, "transform: the Rescale rounding term is read by the first pass of a forward transform");
+    // live limbs sorted by modulus (stable counting sort)
+    LimbTab tab;
+    uint32_t count[HE_MAX_MODULI] = {0}, start[HE_MAX_MODULI], live = 0, distinct = 0;
+    for (uint32_t s = 0; s < HE_MAX_SEGS; s++) tab.seg[s] = s < d.n_seg ? d.seg[s] : d.seg[0];
+    for (uint32_t i = 0; i < n; i++) {
+        if (d.mod_idx[i] == 0xFFu) continue;
+        if (d.mod_idx[i] >= ctx->M) return he_fail(ctx, HE_ERR_BADARG, "transform: modulus index %u out of range", d.mod_idx[i]);
+        count[d.mod_idx[i]]++;
+    }
+    for (uint32_t m = 0; m < ctx->M; m++) { start[m] = live; live += count[m]; distinct += count[m] != 0; }
+    if (live == 0) return HE_OK;
+    for (uint32_t i = 0; i < n; i++) {
+        const uint32_t mi = d.mod_idx[i];
+        if (mi == 0xFFu) continue;
+        const uint32_t seg = d.src_seg ? d.src_seg[i] : 0, lim = d.src_limb ? d.src_limb[i] : i;
+        if (seg >= HE_MAX_SEGS || seg >= d.n_seg || lim >= 4096) return he_fail(ctx, HE_ERR_BADARG, "transform: source limb out of range");
+        tab.e[start[mi]++] = i | (mi << 9) | (lim << 15) | (seg << 27) | (ctx->h_mc[mi].bits > (fwd ? 57u : 54u) ? TAB_WIDE : 0u);
+    }
+    P2Args a;
+    a.dst = d.dst; a.mc = ctx->d_mc;
+    a.tw = fwd ? ctx->d_tw : ctx->d_itw;
+    a.logN = logN;
+    a.lazy = (fwd && d.lazy_out) ? 1u : 0u;
+    a.rs_mod = d.rescale_from ? d.rescale_from - 1 : 0;
+    uint32_t lc = 0;
+    while (lc < 4 && (2u << lc) * distinct <= live) lc++;      // chunk <= average group size, at most 16
+    a.log_chunk = lc;
+    // the work index of a workgroup runs over whole groups of 8 chunks x tiles: with the 2 tiles of the smallest ring the
+    // limbs are padded so that every index a launch can form lies inside the table
+    const uint32_t tiles = ctx->N >> 12, unit = std::max<uint32_t>(1u << lc, tiles < 8 ? (8u / tiles) << lc : 0u);
+    const uint32_t padded = (live + unit - 1) / unit * unit;
+    if (padded > HE_MAX_LAUNCH_LIMBS) return he_fail(ctx, HE_ERR_BADARG, "transform: too many limbs in one launch");
+    for (uint32_t i = live; i < padded; i++) tab.e[i] = TAB_NONE;
+    const dim3 block(P2_THREADS), grid_cols(live * tiles), grid_rows(padded * tiles);
+    for (int pass = 0; pass < 2; pass++) {
+        if (d.only_pass && d.only_pass != (uint32_t)pass + 1) continue;
+        hipEvent_t e0 = nullptr, e1 = nullptr;
+        if (ctx->prof_on) {
+            HE_HIP(ctx, hipEventCreate(&e0));
+            HE_HIP(ctx, hipEventCreate(&e1));
+            HE_HIP(ctx, hipEventRecord(e0, ctx->stream));
+        }
+        if (fwd && pass == 0) {
+            if (d.rescale_from) { COL_DISPATCH(ntt_col_fwd_kernel, true, grid_cols, block, 0, ctx->stream, a, tab) }
+            else { COL_DISPATCH(ntt_col_fwd_kernel, false, grid_cols, block, 0, ctx->stream, a, tab) }
+        } else if (fwd) {
+            if (d.ep && d.ep->fused && d.ep->n_terms) hipLaunchKernelGGL((ntt_row_fwd_kernel<3, 0>), grid_rows, block, 0, ctx->stream, a, tab, *d.ep);
+            else if (d.ep && d.ep->fused) { BETA_DISPATCH(ntt_row_fwd_kernel, 2, d.ep->beta, grid_rows, block, 0, ctx->stream, a, tab, *d.ep) }
+            else if (d.ep) hipLaunchKernelGGL((ntt_row_fwd_kernel<1, 0>), grid_rows, block, 0, ctx->stream, a, tab, *d.ep);
+            else { ModDownEpilogue none = {}; hipLaunchKernelGGL((ntt_row_fwd_kernel<0, 0>), grid_rows, block, 0, ctx->stream, a, tab, none); }
+        } else if (pass == 0) {
+            if (d.ip && d.ip->n_terms) hipLaunchKernelGGL((ntt_row_inv_kernel<2, 0>), grid_rows, block, 0, ctx->stream, a, tab, *d.ip);
+            else if (d.ip) { BETA_DISPATCH(ntt_row_inv_kernel, 1, d.ip->beta, grid_rows, block, 0, ctx->stream, a, tab, *d.ip) }
+            else { IpPrologue none = {}; hipLaunchKernelGGL((ntt_row_inv_kernel<0, 0>), grid_rows, block, 0, ctx->stream, a, tab, none); }
+        } else {
+            if (d.scale) { COL_DISPATCH(ntt_col_inv_kernel, true, grid_cols, block, 0, ctx->stream, a, tab, *d.scale, d.scale_period) }
+            else { ScaleList none; COL_DISPATCH(ntt_col_inv_kernel, false, grid_cols, block, 0, ctx->stream, a, tab, none, 1u) }
+        }
+        HE_HIP(ctx, hipGetLastError());
+        if (ctx->prof_on) {
+            HE_HIP(ctx, hipEventRecord(e1, ctx->stream));
+            // the two components of a job share the gathered digit limbs: beta per pair of limbs
+            uint32_t dig = 0;
+            if (!fwd && pass == 0 && d.ip) dig = d.ip->beta * (live / 2);
+            if (fwd && pass == 1 && d.ep && d.ep->fused) dig = d.ep->beta * (live / 2);
+            const uint32_t kind = fwd ? (pass == 0 ? 0u : (d.ep ? 2u : 1u)) : (pass == 0 ? (d.ip ? 4u : 3u) : 5u);
+            ctx->prof_events.push_back({e0, e1, live, dig, kind});
+        }
+    }
+    if (fwd) ctx->cnt.ntt_limbs += live; else ctx->cnt.intt_limbs += live;
+    return HE_OK;
+}

@@ -5,113 +5,154 @@
 #include "modarith.h"
 
 // q4 = 4q throughout this file.
-template <bool WIDE>
+//
+// A butterfly is counted in instructions: on gfx950 the 32-bit multiplies, v_mad_u64_u32 and v_lshl_add_u64 all issue at
+// one per lane and cycle (28-35 T/s measured), so what costs is how many there are.  The product enters the sum through
+// the multiply-adds' own addend (X + w*Y - h*q accumulated in one chain with -q as the factor), and the difference is
+// 2X + 4q minus that sum: 5 instructions for the quotient h, 8 for the sum, 3 for the difference, against 20 for a
+// product formed on its own and then added and subtracted.
+//
+// Ranges are kept in units of q and known when the code is compiled: a twiddle product is below 4q whatever its factor,
+// a forward stage therefore adds 4 to the bound of every point, an inverse stage adds the bounds of its two points.  A
+// conditional subtraction is made only where the next sum would leave 64 bits: nowhere for narrow moduli (forward: at
+// most 57 bits, 16 stages end below 69q; inverse: at most 54 bits, a pass ends below 512q), every other forward stage and
+// a few inverse points for wide ones (below 2^60, so that 16q fits).
 __device__ __forceinline__ void ct_bfly(u64& X, u64& Y, u64 w, u64 w_sh, u64 q, u64 q4) {
-    if (WIDE) X = csub(X, q4);
-    u64 T = shoup_lazy4(Y, w, w_sh, q);
-    Y = (X + q4) - T;
-    X = X + T;
+    const u64 S = shoup_acc(X, Y, w, w_sh, q);
+    Y = (X + X + q4) - S;
+    X = S;
+}
+// The same with X brought below 8q first (wide moduli; inputs below 16q) in every other stage.
+template <bool WIDE>
+__device__ __forceinline__ void ct_bfly_u(int n, u64& X, u64& Y, u64 w, u64 w_sh, u64 q, u64 q4) {
+    if (WIDE && (n & 1) == 0) X = csub_u(X, 2 * q4);
+    ct_bfly(X, Y, w, w_sh, q, q4);
 }
 
-__device__ __forceinline__ void gs_bfly(u64& X, u64& Y, u64 w, u64 w_sh, u64 q, u64 q4) {
-    u64 s = csub(X + Y, q4);
-    u64 d = (X + q4) - Y;
+// Inverse butterfly on points below bx*q and by*q; the bounds of the results replace them.  They are constants of the
+// unrolled code.
+template <bool WIDE>
+__device__ __forceinline__ void gs_bfly(u64& X, u64& Y, int& bx, int& by, u64 w, u64 w_sh, u64 q) {
+    if (WIDE) {
+#pragma unroll
+        for (int r = 0; r < 3; r++) {                    // at most three steps are ever needed; constants once unrolled
+            if (bx + by <= 16) continue;
+            if (bx >= by) { const int b = bx > 8 ? 8 : 4; X = csub_u(X, q * b); bx = b; }
+            else { const int b = by > 8 ? 8 : 4; Y = csub_u(Y, q * b); by = b; }
+        }
+    }
+    const u64 d = (X + q * (u64)by) - Y;
+    X = X + Y;
     Y = shoup_lazy4(d, w, w_sh, q);
-    X = s;
+    bx += by;
+    by = 4;
 }
-
-// Four forward stages on 16 register points; stage u pairs (k, k + (8>>u)); the twiddle of the
-// pair's group g = k >> (4-u) is tw[(1 << (s0+u)) + (G << u) + g], G = group of the 16 points at
-// stage s0.
-template <bool WIDE>
-__device__ __forceinline__ void fwd_block4(u64 (&x)[16], const u64* __restrict__ tw, const u64* __restrict__ tw_sh,
-                                           uint32_t s0, uint32_t G, u64 q, u64 q4) {
+// Every point of a register block below 4q again (wide moduli, before an exchange mixes the points).
+template <int N>
+__device__ __forceinline__ void settle4(u64 (&x)[N], int (&b)[N], u64 q) {
 #pragma unroll
-    for (int u = 0; u < 4; u++) {
-        const int dist = 8 >> u;
-        const uint32_t base = (1u << (s0 + u)) + (G << u);
-#pragma unroll
-        for (int g = 0; g < (1 << u); g++) {
-            const u64 w = tw[base + g], w_sh = tw_sh[base + g];
-#pragma unroll
-            for (int k = 0; k < dist; k++) {
-                const int a = g * 2 * dist + k;
-                ct_bfly<WIDE>(x[a], x[a + dist], w, w_sh, q, q4);
-            }
-        }
+    for (int k = 0; k < N; k++) {
+        if (b[k] > 8) x[k] = csub_u(x[k], q * 8);
+        if (b[k] > 4) x[k] = csub_u(x[k], q * 4);
+        b[k] = 4;
     }
 }
 
-// Four inverse stages (point distance 1,2,4,8 in register index), same twiddle indexing.
-__device__ __forceinline__ void inv_block4(u64 (&x)[16], const u64* __restrict__ tw, const u64* __restrict__ tw_sh,
-                                           uint32_t s0, uint32_t G, u64 q, u64 q4) {
+// Register blocks of four stages on 16 points.  Stage u pairs (k, k + (8>>u)); the twiddle of the pair's group g =
+// k >> (4-u) is tw[(1 << (s0+u)) + (G << u) + g], G = group of the 16 points at stage s0, kept at index (1 << u) - 1 + g.
+// A factor and its Shoup companion lie next to each other, one 16-byte load.  Loading is separate from use: a pass that
+// fetched its factors where it needs them spent 40 of 104 us (row pass, 384 limbs) waiting for them.
+template <int U0, int U1>
+__device__ __forceinline__ void tw_load(ulonglong2 (&w)[15], const ulonglong2* __restrict__ tw, uint32_t s0, uint32_t G) {
 #pragma unroll
-    for (int u = 3; u >= 0; u--) {
+    for (int u = U0; u < U1; u++) {
+        const ulonglong2* p = tw + ((1u << (s0 + u)) + (G << u));
+#pragma unroll
+        for (int g = 0; g < (1 << u); g++) w[(1 << u) - 1 + g] = p[g];
+    }
+}
+// Forward stages U0 .. U1-1.  Wide moduli: inputs and results below 16q.
+template <bool WIDE, int U0, int U1>
+__device__ __forceinline__ void fwd_stages(u64 (&x)[16], const ulonglong2 (&w)[15], u64 q) {
+    const u64 q4 = 4 * q;
+#pragma unroll
+    for (int u = U0; u < U1; u++) {
         const int dist = 8 >> u;
-        const uint32_t base = (1u << (s0 + u)) + (G << u);
 #pragma unroll
-        for (int g = 0; g < (1 << u); g++) {
-            const u64 w = tw[base + g], w_sh = tw_sh[base + g];
+        for (int g = 0; g < (1 << u); g++)
 #pragma unroll
             for (int k = 0; k < dist; k++) {
                 const int a = g * 2 * dist + k;
-                gs_bfly(x[a], x[a + dist], w, w_sh, q, q4);
+                ct_bfly_u<WIDE>(u - U0, x[a], x[a + dist], w[(1 << u) - 1 + g].x, w[(1 << u) - 1 + g].y, q, q4);
             }
-        }
     }
 }
-
-// Two forward / inverse stages on 4 register points (same pairing and twiddle indexing as the 16-point blocks).
-template <bool WIDE>
-__device__ __forceinline__ void fwd_block2(u64 (&x)[4], const u64* tw, const u64* tw_sh, uint32_t s0, uint32_t G, u64 q, u64 q4) {
-    const uint32_t b0 = (1u << s0) + G, b1 = (2u << s0) + 2 * G;
-    const u64 w0 = tw[b0], w0s = tw_sh[b0], w1 = tw[b1], w1s = tw_sh[b1], w2 = tw[b1 + 1], w2s = tw_sh[b1 + 1];
-    ct_bfly<WIDE>(x[0], x[2], w0, w0s, q, q4);
-    ct_bfly<WIDE>(x[1], x[3], w0, w0s, q, q4);
-    ct_bfly<WIDE>(x[0], x[1], w1, w1s, q, q4);
-    ct_bfly<WIDE>(x[2], x[3], w2, w2s, q, q4);
+// Inverse stages U1-1 down to U0, bounds b per point.
+template <bool WIDE, int U0, int U1>
+__device__ __forceinline__ void inv_stages(u64 (&x)[16], int (&b)[16], const ulonglong2 (&w)[15], u64 q) {
+#pragma unroll
+    for (int u = U1 - 1; u >= U0; u--) {
+        const int dist = 8 >> u;
+#pragma unroll
+        for (int g = 0; g < (1 << u); g++)
+#pragma unroll
+            for (int k = 0; k < dist; k++) {
+                const int a = g * 2 * dist + k;
+                gs_bfly<WIDE>(x[a], x[a + dist], b[a], b[a + dist], w[(1 << u) - 1 + g].x, w[(1 << u) - 1 + g].y, q);
+            }
+    }
+}
+// the largest bound of a block holds for all of its points once an exchange has mixed them
+template <int N>
+__device__ __forceinline__ void bounds_all(int (&b)[N], int v) {
+#pragma unroll
+    for (int k = 0; k < N; k++) b[k] = v;
 }
 
-__device__ __forceinline__ void inv_block2(u64 (&x)[4], const u64* tw, const u64* tw_sh, uint32_t s0, uint32_t G, u64 q, u64 q4) {
-    const uint32_t b0 = (1u << s0) + G, b1 = (2u << s0) + 2 * G;
-    const u64 w0 = tw[b0], w0s = tw_sh[b0], w1 = tw[b1], w1s = tw_sh[b1], w2 = tw[b1 + 1], w2s = tw_sh[b1 + 1];
-    gs_bfly(x[0], x[1], w1, w1s, q, q4);
-    gs_bfly(x[2], x[3], w2, w2s, q, q4);
-    gs_bfly(x[0], x[2], w0, w0s, q, q4);
-    gs_bfly(x[1], x[3], w0, w0s, q, q4);
-}
-
-// The same two-stage blocks with their three twiddles (and Shoup companions) fetched ahead of time: r = {w0, w0', w1,
-// w1', w2, w2'} as tw_block2 loads them.
-__device__ __forceinline__ void tw_block2(u64 (&r)[6], const u64* __restrict__ tw, const u64* __restrict__ tw_sh, uint32_t s0, uint32_t G) {
-    const uint32_t b0 = (1u << s0) + G, b1 = (2u << s0) + 2 * G;
-    r[0] = tw[b0]; r[1] = tw_sh[b0]; r[2] = tw[b1]; r[3] = tw_sh[b1]; r[4] = tw[b1 + 1]; r[5] = tw_sh[b1 + 1];
-}
+// Two forward / inverse stages on 4 register points (same pairing and twiddle indexing as the 16-point blocks).  Forward:
+// ranges as above.  Inverse: inputs and results below 4q, for any modulus below 2^60.
 template <bool WIDE>
 __device__ __forceinline__ void fwd_block2_r(u64 (&x)[4], const u64 (&r)[6], u64 q, u64 q4) {
-    ct_bfly<WIDE>(x[0], x[2], r[0], r[1], q, q4);
-    ct_bfly<WIDE>(x[1], x[3], r[0], r[1], q, q4);
-    ct_bfly<WIDE>(x[0], x[1], r[2], r[3], q, q4);
-    ct_bfly<WIDE>(x[2], x[3], r[4], r[5], q, q4);
+    ct_bfly_u<WIDE>(0, x[0], x[2], r[0], r[1], q, q4);
+    ct_bfly_u<WIDE>(0, x[1], x[3], r[0], r[1], q, q4);
+    ct_bfly_u<WIDE>(1, x[0], x[1], r[2], r[3], q, q4);
+    ct_bfly_u<WIDE>(1, x[2], x[3], r[4], r[5], q, q4);
 }
-__device__ __forceinline__ void inv_block2_r(u64 (&x)[4], const u64 (&r)[6], u64 q, u64 q4) {
-    gs_bfly(x[0], x[1], r[2], r[3], q, q4);
-    gs_bfly(x[2], x[3], r[4], r[5], q, q4);
-    gs_bfly(x[0], x[2], r[0], r[1], q, q4);
-    gs_bfly(x[1], x[3], r[0], r[1], q, q4);
+__device__ __forceinline__ void inv_block2_r(u64 (&x)[4], const u64 (&r)[6], u64 q) {
+    int b[4] = {4, 4, 4, 4};
+    gs_bfly<true>(x[0], x[1], b[0], b[1], r[2], r[3], q);
+    gs_bfly<true>(x[2], x[3], b[2], b[3], r[4], r[5], q);
+    gs_bfly<true>(x[0], x[2], b[0], b[2], r[0], r[1], q);
+    gs_bfly<true>(x[1], x[3], b[1], b[3], r[0], r[1], q);
+    settle4(x, b, q);
+}
+// the three twiddles of such a block (and Shoup companions): r = {w0, w0', w1, w1', w2, w2'}
+__device__ __forceinline__ void tw_block2(u64 (&r)[6], const ulonglong2* tw, uint32_t s0, uint32_t G) {
+    const uint32_t b0 = (1u << s0) + G, b1 = (2u << s0) + 2 * G;
+    const ulonglong2 w0 = tw[b0], w1 = tw[b1], w2 = tw[b1 + 1];
+    r[0] = w0.x; r[1] = w0.y; r[2] = w1.x; r[3] = w1.y; r[4] = w2.x; r[5] = w2.y;
+}
+template <bool WIDE>
+__device__ __forceinline__ void fwd_block2(u64 (&x)[4], const ulonglong2* tw, uint32_t s0, uint32_t G, u64 q, u64 q4) {
+    u64 r[6];
+    tw_block2(r, tw, s0, G);
+    fwd_block2_r<WIDE>(x, r, q, q4);
+}
+__device__ __forceinline__ void inv_block2(u64 (&x)[4], const ulonglong2* tw, uint32_t s0, uint32_t G, u64 q) {
+    u64 r[6];
+    tw_block2(r, tw, s0, G);
+    inv_block2_r(x, r, q);
 }
 
-// v mod q for v < 100q: a 7-bit quotient estimated from the top bits (never too large, at most 2
-// too small), then two conditional subtractions.  The lazy form stops before them: a value below 3q congruent to v.
-__device__ __forceinline__ u64 reduce_small_lazy(u64 v, u64 q, uint32_t bits, uint32_t mrec) {
-    const uint32_t sh = bits - 8;                       // q >> sh in [128, 256)
-    uint32_t v1 = (uint32_t)(v >> sh);                  // < 100 * 256
-    uint32_t qh = (v1 * mrec) >> 24;                    // mrec = floor(2^24 / ((q >> sh) + 1))
+// v mod q for v below 2^LOGV * 2^bits (and below 2^64): the quotient from the top 32 bits of v and rec =
+// floor(2^(bits+31) / q), at most one too small.  The lazy form stops before the correction: below 2q.
+template <int LOGV>
+__device__ __forceinline__ u64 reduce_lazy(u64 v, u64 q, uint32_t bits, uint32_t rec) {
+    const uint32_t sh = bits > 32 - LOGV ? bits - (32 - LOGV) : 0;
+    const uint32_t qh = __umulhi((uint32_t)(v >> sh), rec) >> (bits - 1 - sh);
     return v - (u64)qh * q;
 }
-__device__ __forceinline__ u64 reduce_small(u64 v, u64 q, uint32_t bits, uint32_t mrec) {
-    u64 r = reduce_small_lazy(v, q, bits, mrec);
-    r = csub(r, 2 * q);
-    return csub(r, q);
+template <int LOGV>
+__device__ __forceinline__ u64 reduce_full(u64 v, u64 q, uint32_t bits, uint32_t rec) {
+    return csub(reduce_lazy<LOGV>(v, q, bits, rec), q);
 }
-

@@ -30,18 +30,18 @@ __device__ __forceinline__ uint32_t sp(uint32_t i) { return i + (i >> 4); }
 // while the previous transform still uses the LDS copy, committed once that transform is done.
 struct TwRegs { u64 w[SR_PTS], s[SR_PTS]; };
 
-__device__ __forceinline__ void tw_fetch(TwRegs& r, const u64* __restrict__ tw, const u64* __restrict__ tw_sh, uint32_t N) {
+__device__ __forceinline__ void tw_fetch(TwRegs& r, const ulonglong2* __restrict__ tw, uint32_t N) {
 #pragma unroll
     for (uint32_t p = 0; p < SR_PTS; p++) {
         const uint32_t e = threadIdx.x + SR_THREADS * p;
-        if (e < N) { r.w[p] = tw[e]; r.s[p] = tw_sh[e]; }
+        if (e < N) { const ulonglong2 v = tw[e]; r.w[p] = v.x; r.s[p] = v.y; }
     }
 }
-__device__ __forceinline__ void tw_commit(const TwRegs& r, u64* twl, u64* twl_sh, uint32_t N) {
+__device__ __forceinline__ void tw_commit(const TwRegs& r, ulonglong2* twl, uint32_t N) {
 #pragma unroll
     for (uint32_t p = 0; p < SR_PTS; p++) {
         const uint32_t e = threadIdx.x + SR_THREADS * p;
-        if (e < N) { twl[e] = r.w[p]; twl_sh[e] = r.s[p]; }
+        if (e < N) twl[e] = make_ulonglong2(r.w[p], r.s[p]);
     }
 }
 
@@ -50,11 +50,10 @@ __device__ __forceinline__ void tw_commit(const TwRegs& r, u64* twl, u64* twl_sh
 // then one radix-2 stage when logN is odd.  Twiddles from the LDS table.  Inputs below 4q, results canonical.
 // Ends with a barrier.
 template <bool WIDE>
-__device__ __forceinline__ void lds_ntt_fwd_t(u64* sm, const u64* twl, const u64* twl_sh, const ModConst& m, uint32_t logN) {
+__device__ __forceinline__ void lds_ntt_fwd_t(u64* sm, const ulonglong2* twl, const ModConst& m, uint32_t logN) {
     const u64 q = m.q, q2 = 2 * q, q4 = 4 * q;
     const uint32_t N = 1u << logN, nb = logN >> 1;
-    // the blocks leave values below 52q (never reduced) or, for the widest moduli, below 8q
-    const uint32_t mrec = WIDE ? 0u : (1u << 24) / ((uint32_t)(q >> (m.bits - 8)) + 1);
+    // the blocks leave values below 52q (never reduced) or, for the widest moduli, below 16q
     for (uint32_t blk = 0; blk < nb; blk++) {
         const uint32_t s0 = 2 * blk, log_span = logN - s0 - 2, span = 1u << log_span;
         for (uint32_t tid = threadIdx.x; tid < (N >> 2); tid += SR_THREADS) {
@@ -62,10 +61,10 @@ __device__ __forceinline__ void lds_ntt_fwd_t(u64* sm, const u64* twl, const u64
             u64 x[4];
 #pragma unroll
             for (int k = 0; k < 4; k++) x[k] = sm[sp(base + (k << log_span))];
-            fwd_block2<WIDE>(x, twl, twl_sh, s0, G, q, q4);
+            fwd_block2<WIDE>(x, twl, s0, G, q, q4);
             if (blk + 1 == nb) {
 #pragma unroll
-                for (int k = 0; k < 4; k++) x[k] = WIDE ? csub(csub(csub(x[k], q4), q2), q) : reduce_small(x[k], q, m.bits, mrec);
+                for (int k = 0; k < 4; k++) x[k] = reduce_full<7>(x[k], q, m.bits, m.rec);
             }
 #pragma unroll
             for (int k = 0; k < 4; k++) sm[sp(base + (k << log_span))] = x[k];
@@ -77,24 +76,24 @@ __device__ __forceinline__ void lds_ntt_fwd_t(u64* sm, const u64* twl, const u64
         for (uint32_t b = threadIdx.x; b < (N >> 1); b += SR_THREADS) {
             const uint32_t e0 = sp(2 * b), e1 = sp(2 * b + 1), k = (1u << s) + b;
             const u64 x = sm[e0];
-            const u64 v = shoup_lazy(sm[e1], twl[k], twl_sh[k], q);
+            const u64 v = shoup_lazy(sm[e1], twl[k].x, twl[k].y, q);
             sm[e0] = csub(csub(x + v, q2), q);
             sm[e1] = csub(csub(x - v + q2, q2), q);
         }
         __syncthreads();
     }
 }
-__device__ __forceinline__ void lds_ntt_fwd(u64* sm, const u64* twl, const u64* twl_sh, const ModConst& m, uint32_t logN) {
-    if (m.bits > 57) lds_ntt_fwd_t<true>(sm, twl, twl_sh, m, logN);
-    else lds_ntt_fwd_t<false>(sm, twl, twl_sh, m, logN);
+__device__ __forceinline__ void lds_ntt_fwd(u64* sm, const ulonglong2* twl, const ModConst& m, uint32_t logN) {
+    if (m.bits > 57) lds_ntt_fwd_t<true>(sm, twl, m, logN);
+    else lds_ntt_fwd_t<false>(sm, twl, m, logN);
 }
 
 // Inverse transform in LDS (bit-reversed in, natural out): the last stage as a radix-2 stage first when logN is
 // odd, then the register blocks from the highest stages down; every value times `scale` (which carries N^-1) as
 // the last block stores it.  Inputs canonical, results canonical.  Ends with a barrier.
-__device__ __forceinline__ void lds_ntt_inv(u64* sm, const u64* twl, const u64* twl_sh, const ModConst& m, uint32_t logN, u64 scale,
+__device__ __forceinline__ void lds_ntt_inv(u64* sm, const ulonglong2* twl, const ModConst& m, uint32_t logN, u64 scale,
                                             u64 scale_sh) {
-    const u64 q = m.q, q2 = 2 * q, q4 = 4 * q;
+    const u64 q = m.q, q2 = 2 * q;
     const uint32_t N = 1u << logN, nb = logN >> 1;
     if (logN & 1u) {
         const uint32_t s = logN - 1;
@@ -102,7 +101,7 @@ __device__ __forceinline__ void lds_ntt_inv(u64* sm, const u64* twl, const u64* 
             const uint32_t e0 = sp(2 * b), e1 = sp(2 * b + 1), k = (1u << s) + b;
             const u64 x = sm[e0], y = sm[e1];
             sm[e0] = csub(x + y, q2);
-            sm[e1] = shoup_lazy(x - y + q2, twl[k], twl_sh[k], q);
+            sm[e1] = shoup_lazy(x - y + q2, twl[k].x, twl[k].y, q);
         }
         __syncthreads();
     }
@@ -113,7 +112,7 @@ __device__ __forceinline__ void lds_ntt_inv(u64* sm, const u64* twl, const u64* 
             u64 x[4];
 #pragma unroll
             for (int k = 0; k < 4; k++) x[k] = sm[sp(base + (k << log_span))];
-            inv_block2(x, twl, twl_sh, s0, G, q, q4);
+            inv_block2(x, twl, s0, G, q);
             if (blk == 0) {
 #pragma unroll
                 for (int k = 0; k < 4; k++) x[k] = csub(shoup_lazy(x[k], scale, scale_sh, q), q);
@@ -133,7 +132,7 @@ __device__ __forceinline__ uint32_t galois_src_sr(uint32_t j, uint32_t g, uint32
 
 struct SrTables {
     const ModConst* mc;
-    const u64 *tw, *tw_sh, *itw, *itw_sh;   // [M][N]
+    const ulonglong2 *tw, *itw;   // [M][N]: factor, Shoup companion
     uint32_t logN;
 };
 
@@ -150,7 +149,7 @@ struct SrUpArgs {
 
 __global__ __launch_bounds__(SR_THREADS) void sr_modup_kernel(SrUpArgs a, SrTables tb) {
     __shared__ u64 sm[SR_LDS];
-    __shared__ u64 twl[4096], twl_sh[4096];
+    __shared__ ulonglong2 twl[4096];
     const uint32_t N = 1u << tb.logN;
     const uint32_t s = blockIdx.x / a.n_out, o = blockIdx.x % a.n_out;
     const uint32_t j = a.oj[o], r = a.orr[o];
@@ -172,7 +171,7 @@ __global__ __launch_bounds__(SR_THREADS) void sr_modup_kernel(SrUpArgs a, SrTabl
         }
     }
     TwRegs tr;
-    tw_fetch(tr, tb.itw + ((size_t)lo << tb.logN), tb.itw_sh + ((size_t)lo << tb.logN), N);
+    tw_fetch(tr, tb.itw + ((size_t)lo << tb.logN), N);
     u128 acc[SR_PTS] = {};
 #pragma unroll
     for (uint32_t i = 0; i < SR_MAX_SRC; i++) {
@@ -184,12 +183,12 @@ __global__ __launch_bounds__(SR_THREADS) void sr_modup_kernel(SrUpArgs a, SrTabl
                 const uint32_t e = threadIdx.x + SR_THREADS * p;
                 if (e < N) sm[sp(e)] = in[i][p];
             }
-            tw_commit(tr, twl, twl_sh, N);
+            tw_commit(tr, twl, N);
             __syncthreads();
             // the table of the next transform travels while this one runs
-            if (i + 1 < sz) tw_fetch(tr, tb.itw + ((size_t)(mi + 1) << tb.logN), tb.itw_sh + ((size_t)(mi + 1) << tb.logN), N);
-            else tw_fetch(tr, tb.tw + ((size_t)mr << tb.logN), tb.tw_sh + ((size_t)mr << tb.logN), N);
-            lds_ntt_inv(sm, twl, twl_sh, mq, tb.logN, a.scale[mi], a.scale_sh[mi]);
+            if (i + 1 < sz) tw_fetch(tr, tb.itw + ((size_t)(mi + 1) << tb.logN), N);
+            else tw_fetch(tr, tb.tw + ((size_t)mr << tb.logN), N);
+            lds_ntt_inv(sm, twl, mq, tb.logN, a.scale[mi], a.scale_sh[mi]);
 #pragma unroll
             for (uint32_t p = 0; p < SR_PTS; p++) {
                 const uint32_t e = threadIdx.x + SR_THREADS * p;
@@ -203,9 +202,9 @@ __global__ __launch_bounds__(SR_THREADS) void sr_modup_kernel(SrUpArgs a, SrTabl
         const uint32_t e = threadIdx.x + SR_THREADS * p;
         if (e < N) sm[sp(e)] = barrett128(acc[p], m.q, m.mu, m.bits);
     }
-    tw_commit(tr, twl, twl_sh, N);
+    tw_commit(tr, twl, N);
     __syncthreads();
-    lds_ntt_fwd(sm, twl, twl_sh, m, tb.logN);
+    lds_ntt_fwd(sm, twl, m, tb.logN);
     u64* dst = a.raised + ((size_t)((s * a.beta + j) * a.R + r) << tb.logN);
     for (uint32_t e = threadIdx.x; e < N; e += SR_THREADS) dst[e] = sm[sp(e)];
 }
@@ -220,7 +219,7 @@ struct SrDownArgs {
 
 __global__ __launch_bounds__(SR_THREADS) void sr_moddown_kernel(ModDownEpilogue ep, SrDownArgs a, SrTables tb) {
     __shared__ u64 sm[SR_LDS];
-    __shared__ u64 twl[4096], twl_sh[4096];
+    __shared__ ulonglong2 twl[4096];
     const uint32_t N = 1u << tb.logN, L1 = ep.L1, R = ep.R, beta = ep.beta;
     const uint32_t pc = blockIdx.x / L1, r = blockIdx.x - pc * L1, job = pc >> 1, comp = pc & 1u;
     const ModConst m = tb.mc[r];
@@ -228,7 +227,7 @@ __global__ __launch_bounds__(SR_THREADS) void sr_moddown_kernel(ModDownEpilogue 
     const u64* raised = ep.raised[job];
     const u64* evk = ep.evk[job];
     TwRegs tr;
-    tw_fetch(tr, tb.itw + ((size_t)a.nq << tb.logN), tb.itw_sh + ((size_t)a.nq << tb.logN), N);
+    tw_fetch(tr, tb.itw + ((size_t)a.nq << tb.logN), N);
     uint32_t src[SR_PTS];
 #pragma unroll
     for (uint32_t p = 0; p < SR_PTS; p++) {
@@ -285,11 +284,11 @@ __global__ __launch_bounds__(SR_THREADS) void sr_moddown_kernel(ModDownEpilogue 
                 const uint32_t e = threadIdx.x + SR_THREADS * p;
                 if (e < N) sm[sp(e)] = pl[t][p];
             }
-            tw_commit(tr, twl, twl_sh, N);
+            tw_commit(tr, twl, N);
             __syncthreads();
-            if (t + 1 < a.k) tw_fetch(tr, tb.itw + ((size_t)(mt + 1) << tb.logN), tb.itw_sh + ((size_t)(mt + 1) << tb.logN), N);
-            else tw_fetch(tr, tb.tw + ((size_t)r << tb.logN), tb.tw_sh + ((size_t)r << tb.logN), N);
-            lds_ntt_inv(sm, twl, twl_sh, mp, tb.logN, a.scale[t], a.scale_sh[t]);
+            if (t + 1 < a.k) tw_fetch(tr, tb.itw + ((size_t)(mt + 1) << tb.logN), N);
+            else tw_fetch(tr, tb.tw + ((size_t)r << tb.logN), N);
+            lds_ntt_inv(sm, twl, mp, tb.logN, a.scale[t], a.scale_sh[t]);
             const u64 h = a.dn_hat[(size_t)r * a.pw + t];
 #pragma unroll
             for (uint32_t p = 0; p < SR_PTS; p++) {
@@ -304,9 +303,9 @@ __global__ __launch_bounds__(SR_THREADS) void sr_moddown_kernel(ModDownEpilogue 
         const uint32_t e = threadIdx.x + SR_THREADS * p;
         if (e < N) sm[sp(e)] = barrett128(acc[p], m.q, m.mu, m.bits);
     }
-    tw_commit(tr, twl, twl_sh, N);
+    tw_commit(tr, twl, N);
     __syncthreads();
-    lds_ntt_fwd(sm, twl, twl_sh, m, tb.logN);
+    lds_ntt_fwd(sm, twl, m, tb.logN);
     u64* out = (comp ? ep.out1[job] : ep.out0[job]) + ((size_t)r << tb.logN);
     const u64 pinv = ep.pinv[r], pinv_sh = ep.pinv_sh[r];
 #pragma unroll
@@ -331,7 +330,7 @@ struct SrRescaleArgs {
 
 __global__ __launch_bounds__(SR_THREADS) void sr_rescale_kernel(SrRescaleArgs a, SrTables tb) {
     __shared__ u64 sm[SR_LDS];
-    __shared__ u64 twl[4096], twl_sh[4096];
+    __shared__ ulonglong2 twl[4096];
     const uint32_t N = 1u << tb.logN, level = a.level;
     const uint32_t jc = blockIdx.x / level, r = blockIdx.x - jc * level, job = jc >> 1, comp = jc & 1u;
     const ModConst ml = tb.mc[level], mr = tb.mc[r];
@@ -339,7 +338,7 @@ __global__ __launch_bounds__(SR_THREADS) void sr_rescale_kernel(SrRescaleArgs a,
     const u64* in = a.ct[job] + ((size_t)(comp * (level + 1) + r) << tb.logN);
     const u64 qlinv = a.qlinv[r], qlinv_sh = a.qlinv_sh[r];
     TwRegs tr;
-    tw_fetch(tr, tb.itw + ((size_t)level << tb.logN), tb.itw_sh + ((size_t)level << tb.logN), N);
+    tw_fetch(tr, tb.itw + ((size_t)level << tb.logN), N);
     u64 cr[SR_PTS];
 #pragma unroll
     for (uint32_t p = 0; p < SR_PTS; p++) {
@@ -347,18 +346,18 @@ __global__ __launch_bounds__(SR_THREADS) void sr_rescale_kernel(SrRescaleArgs a,
         cr[p] = 0;
         if (e < N) { sm[sp(e)] = top[e]; cr[p] = in[e]; }
     }
-    tw_commit(tr, twl, twl_sh, N);
+    tw_commit(tr, twl, N);
     __syncthreads();
-    tw_fetch(tr, tb.tw + ((size_t)r << tb.logN), tb.tw_sh + ((size_t)r << tb.logN), N);
-    lds_ntt_inv(sm, twl, twl_sh, ml, tb.logN, ml.ninv, ml.ninv_sh);
+    tw_fetch(tr, tb.tw + ((size_t)r << tb.logN), N);
+    lds_ntt_inv(sm, twl, ml, tb.logN, ml.ninv, ml.ninv_sh);
     const u64 h = ml.q >> 1, hr = barrett64(h, mr.q, mr.mu, mr.bits);
     for (uint32_t e = threadIdx.x; e < N; e += SR_THREADS) {
         const u64 t = addmod(sm[sp(e)], h, ml.q);
         sm[sp(e)] = submod(hr, barrett64(t, mr.q, mr.mu, mr.bits), mr.q);
     }
-    tw_commit(tr, twl, twl_sh, N);
+    tw_commit(tr, twl, N);
     __syncthreads();
-    lds_ntt_fwd(sm, twl, twl_sh, mr, tb.logN);
+    lds_ntt_fwd(sm, twl, mr, tb.logN);
     u64* out = a.out[job] + ((size_t)(comp * level + r) << tb.logN);
 #pragma unroll
     for (uint32_t p = 0; p < SR_PTS; p++) {
@@ -368,7 +367,7 @@ __global__ __launch_bounds__(SR_THREADS) void sr_rescale_kernel(SrRescaleArgs a,
 }
 
 // ---------------------------------------------------------------- host
-static SrTables sr_tables(const he_ctx* c) { return {c->d_mc, c->d_tw, c->d_tw_sh, c->d_itw, c->d_itw_sh, c->logN}; }
+static SrTables sr_tables(const he_ctx* c) { return {c->d_mc, c->d_tw, c->d_itw, c->logN}; }
 
 bool small_ring_path(const he_ctx* c, uint32_t level) {
     const uint32_t beta = (level + c->alpha) / c->alpha;
