@@ -1,0 +1,247 @@
+// Basis conversion with its column passes: inverse column pass of the sources -> conversion -> forward column pass of every
+// target, in one launch (N = 2^13 .. 2^16, at most 8 sources).
+//
+// The three steps work on columns of the 2^LC x 256 view, so a work group takes a tile of 1024 points (C = 1024 / 2^LC
+// columns) of all its limbs through them and neither the coefficient-form sources nor the converted limbs ever reach
+// memory.  Separate kernels moved 24 + 24 + 24 + 72 + 72 + 72 limbs for one ModUp at the benchmark's top level, this one 24
+// + 72, and the conversion alone took 17 % of a rotation.
+//
+// One wavefront owns one limb during the transforms (16 points per lane), so that an exchange stays inside the wavefront and
+// needs no barrier.  The conversion is a contraction - every target residue is a fixed linear combination of the same 8
+// source residues - and runs on the matrix cores: with y_i = sum_a u_(i,a) 2^(8a) the bytes of source i,
+//     sum_i y_i * hat_i = sum_(i,a) u_(i,a) * V_(i,a)  (mod q),   V_(i,a) = hat_i * 2^(8a) mod q, centred,
+// is a product over k = (source, byte), 64 of them, whose right factors split into 8 signed base-256 digits b:
+// v_mfma_i32_16x16x64_i8 with the digits as rows and 16 points as columns.  A source residue in memory order IS the operand
+// (each byte minus 128, which the constant term returns).  Two instructions give 16 points x 4 targets x 8 digits, laid
+// out so that a lane gets the 8 digit sums of one (point, target); they are put together and reduced below 2q in 17
+// vector instructions, where the vector-unit form of the same sum takes 52.
+#include "modarith.h"
+#include "ntt_blocks.h"
+
+#define CC_THREADS 512
+#define CC_WAVES 8
+#define CC_REGION 1088            // LDS words of one limb's tile: 16 runs of 64, 4 spare words after each
+
+typedef int v4i __attribute__((ext_vector_type(4)));
+typedef u64 v2u64 __attribute__((ext_vector_type(2)));
+typedef const __attribute__((address_space(4))) v2u64* ctw_t;      // constant memory: scalar loads also after stores
+typedef const __attribute__((address_space(4))) u64* cu64_t;
+
+// Word of (run k, lane): a lane that holds rows t + k*T of column cl keeps them at run k, lane t*C + cl.
+__device__ __forceinline__ uint32_t cc_word(uint32_t k, uint32_t lane) { return 68 * k + lane; }
+// Row r of column cl.
+template <int LC>
+__device__ __forceinline__ uint32_t cc_row(uint32_t r, uint32_t cl) {
+    constexpr uint32_t LT = LC - 4, LCOLS = 10 - LC;
+    return cc_word(r >> LT, ((r & ((1u << LT) - 1u)) << LCOLS) + cl);
+}
+template <int U0, int U1>
+__device__ __forceinline__ void tw_load_c(ulonglong2 (&w)[15], ctw_t tw, uint32_t s0, uint32_t G) {
+#pragma unroll
+    for (int u = U0; u < U1; u++) {
+        ctw_t p = tw + ((1u << (s0 + u)) + (G << u));
+#pragma unroll
+        for (int g = 0; g < (1 << u); g++) { const v2u64 v = p[g]; w[(1 << u) - 1 + g] = make_ulonglong2(v.x, v.y); }
+    }
+}
+// Inverse column stages of one source limb, output scaling, canonical residues into the limb's LDS region.
+template <int LC, bool WIDE>
+__device__ __forceinline__ void cc_source(u64* reg, const u64* src, const ColConv& cc, const ScaleList& sc, uint32_t mi, uint32_t si,
+                                          uint32_t lane, uint32_t c0, const ModConst* mc, const ulonglong2* itw) {
+    constexpr int LT = LC - 4, LCOLS = 10 - LC, U0 = 8 - LC;
+    const uint32_t t = lane >> LCOLS, cl = lane & ((1u << LCOLS) - 1u), c = c0 + cl;
+    const ctw_t tw = (ctw_t)(uintptr_t)(itw + ((size_t)mi << (LC + 8)));
+    u64 x[16];
+#pragma unroll
+    for (int j = 0; j < 16; j++) x[j] = (src + j * 256)[t * 4096 + c];
+    ulonglong2 w1[15], w2[15];
+    tw_load_c<U0, 4>(w2, tw, LC - 4, t);
+    const cu64_t mp = (cu64_t)(uintptr_t)(mc + mi);
+    const u64 q = uni64(mp[0]);
+    const u64 cs = sc.s[si], cs_sh = sc.s_sh[si], cw = sc.w[si], cw_sh = sc.w_sh[si];
+    int bd[16];
+    bounds_all(bd, 4);
+    inv_stages<WIDE, U0, 4>(x, bd, w2, q);
+    if (WIDE) settle4(x, bd, q);
+#pragma unroll
+    for (int j = 0; j < 16; j++) reg[cc_row<LC>(16 * t + j, cl)] = x[j];
+    tw_load_c<1, 4>(w1, tw, 0, 0);
+    wave_exchange();
+#pragma unroll
+    for (int k = 0; k < 16; k++) x[k] = reg[cc_word(k, lane)];
+    bounds_all(bd, WIDE ? 4 : 4 << (4 - U0));
+    inv_stages<WIDE, 1, 4>(x, bd, w1, q);
+    if (WIDE) settle4(x, bd, q);
+    const u64 bq = WIDE ? 4 * q : 512 * q;
+#pragma unroll
+    for (int k = 0; k < 8; k++) {
+        const u64 X = x[k], Y = x[k + 8];
+        x[k] = shoup_lazy4(X + Y, cs, cs_sh, q);
+        x[k + 8] = shoup_lazy4((X + bq) - Y, cw, cw_sh, q);
+    }
+    // each byte less 128, as the signed operand of the matrix instruction
+#pragma unroll
+    for (int k = 0; k < 16; k++) reg[cc_word(k, lane)] = csub_u(csub_u(x[k], 2 * q), q) ^ 0x8080808080808080ull;
+    (void)LT;
+}
+
+// Forward column stages of one target limb from its LDS region (below 2q) to memory.
+template <int LC, bool WIDE>
+__device__ __forceinline__ void cc_target(u64* reg, u64* dst, uint32_t mi, uint32_t lane, uint32_t c0, const ModConst* mc, const ulonglong2* ftw) {
+    constexpr int LCOLS = 10 - LC, U0 = 8 - LC;
+    const uint32_t t = lane >> LCOLS, cl = lane & ((1u << LCOLS) - 1u), c = c0 + cl;
+    const ctw_t tw = (ctw_t)(uintptr_t)(ftw + ((size_t)mi << (LC + 8)));
+    const cu64_t mp = (cu64_t)(uintptr_t)(mc + mi);
+    const u64 q = uni64(mp[0]), q4 = 4 * q;
+    ulonglong2 w1[15], w2[15];
+    tw_load_c<(U0 < 3 ? U0 : 3), 3>(w2, tw, LC - 4, t);
+    tw_load_c<0, 4>(w1, tw, 0, 0);
+    u64 x[16];
+#pragma unroll
+    for (int k = 0; k < 16; k++) x[k] = reg[cc_word(k, lane)];
+    fwd_stages<WIDE, 0, 4>(x, w1, q);
+    wave_exchange();
+#pragma unroll
+    for (int k = 0; k < 16; k++) reg[cc_word(k, lane)] = x[k];
+    wave_exchange();
+#pragma unroll
+    for (int j = 0; j < 16; j++) x[j] = reg[cc_row<LC>(16 * t + j, cl)];
+    // the last stage's eight factors arrive in two halves, each into the registers that earlier factors leave: with the
+    // source bytes that stay for the next targets there is no room for all of them
+    if (U0 < 2) fwd_stages<WIDE, (U0 < 2 ? U0 : 2), 2>(x, w2, q);
+    ctw_t p3 = tw + ((1u << (LC - 1)) + (t << 3));
+    v2u64 wa[4], wb[4];
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int g = 0; g < 4; g++) wa[g] = p3[g];
+    __builtin_amdgcn_sched_barrier(0);
+    if (U0 < 3) fwd_stages<WIDE, (U0 < 2 ? 2 : U0), (U0 < 3 ? 3 : U0)>(x, w2, q);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int g = 0; g < 4; g++) wb[g] = p3[4 + g];
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int g = 0; g < 4; g++) ct_bfly_u<WIDE>(0, x[2 * g], x[2 * g + 1], wa[g].x, wa[g].y, q, q4);
+#pragma unroll
+    for (int g = 0; g < 4; g++) ct_bfly_u<WIDE>(0, x[8 + 2 * g], x[9 + 2 * g], wb[g].x, wb[g].y, q, q4);
+#pragma unroll
+    for (int j = 0; j < 16; j++) (dst + j * 256)[t * 4096 + c] = x[j];
+}
+
+template <bool WIDE>
+__device__ __forceinline__ uint32_t cc_pin(uint32_t v) {   // keeps the two widths' loads apart (see ntt2p.hip)
+    if (WIDE) asm("; wide" : "+s"(v));
+    else asm("; narrow" : "+s"(v));
+    return v;
+}
+
+// grid: groups * tiles.  Work groups go to the XCDs round-robin: each XCD gets neighbouring tiles of a group, so that the
+// tiles that share a memory line are read and written through one L2.
+template <int LC>
+__global__ __launch_bounds__(CC_THREADS, 4) void col_conv_kernel(ColConv cc, ScaleList sc, const ModConst* mc, const ulonglong2* ftw,
+                                                                 const ulonglong2* itw) {
+    constexpr int LCOLS = 10 - LC, TPX = (256 >> LCOLS) / 8;             // tiles of a group per XCD
+    __shared__ u64 lds[CC_WAVES * CC_REGION];
+    const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const uint32_t slot = blockIdx.x >> 3, tile = (blockIdx.x & 7u) * TPX + slot % TPX, grp = slot / TPX;
+    const uint32_t set = grp % cc.n_sets, rep = grp / cc.n_sets, c0 = tile << LCOLS;
+    const ColConvSet& st = cc.set[set];
+    u64* reg = lds + w * CC_REGION;
+    if (w < st.ns) {
+        const u64* src = st.src + (size_t)rep * cc.src_stride + ((size_t)w << (LC + 8));
+        const uint32_t mi = st.mod0 + w;
+        if (cc.wide_inv >> mi & 1u) cc_source<LC, true>(reg, src, cc, sc, cc_pin<true>(mi), st.sc0 + w, lane, c0, mc, itw);
+        else cc_source<LC, false>(reg, src, cc, sc, cc_pin<false>(mi), st.sc0 + w, lane, c0, mc, itw);
+    }
+    __syncthreads();
+    // this wavefront's 128 points of every source: runs 2w and 2w+1; lane group g = lane / 16 holds sources 2g, 2g+1 of 16
+    // points, in memory order the bytes k = 16g .. 16g+15 of the contraction
+    const uint32_t g = lane >> 4, p16 = lane & 15;
+    v4i frag[8];
+#pragma unroll
+    for (int b = 0; b < 8; b++) {
+        const uint32_t word = cc_word(2 * w + (b >> 2), 16 * (b & 3) + p16);
+        const u64 y0 = 2 * g < st.ns ? lds[(2 * g) * CC_REGION + word] : 0;
+        const u64 y1 = 2 * g + 1 < st.ns ? lds[(2 * g + 1) * CC_REGION + word] : 0;
+        frag[b] = v4i{(int)(uint32_t)y0, (int)(uint32_t)(y0 >> 32), (int)(uint32_t)y1, (int)(uint32_t)(y1 >> 32)};
+    }
+    const uint32_t nt = st.nt;
+    for (uint32_t t0 = 0; t0 < nt; t0 += CC_WAVES) {
+        // operands of this round's eight targets, four (s) at a time: lane group g works on target t0 + 4s + g and this lane
+        // supplies row lane % 16 = (target (lane % 16) / 4, digit lane % 4) of the left factor
+        v4i a0[2], a1[2], k0[2], k1[2];
+        uint32_t n0[2], n1[2], rec[2], bits[2];
+#pragma unroll
+        for (int s = 0; s < 2; s++) {
+            const uint32_t ta = t0 + 4 * s + (p16 >> 2), tg = t0 + 4 * s + g;
+            const uint32_t ma = st.mod[ta < nt ? ta : t0], mg = st.mod[tg < nt ? tg : t0];
+            const v4i* A = reinterpret_cast<const v4i*>(st.digits + (size_t)ma * 512 + (p16 & 3) * 64 + g * 16);
+            a0[s] = A[0]; a1[s] = A[16];                     // digits 0..3, digits 4..7 (256 bytes on)
+            const v4i* K = reinterpret_cast<const v4i*>(st.bias + (size_t)mg * 8);
+            k0[s] = K[0]; k1[s] = K[1];
+            const u64 nq = 0 - mc[mg].q;
+            n0[s] = (uint32_t)nq; n1[s] = (uint32_t)(nq >> 32);
+            rec[s] = mc[mg].rec; bits[s] = mc[mg].bits;
+        }
+        __syncthreads();                                     // the regions are free (operands read, last targets done)
+#pragma unroll
+        for (int s = 0; s < 2; s++) {
+            if (t0 + 4 * s >= nt) break;
+            const uint32_t tg = t0 + 4 * s + g;
+            // quotient of a value below 2^(bits+14) from its top: sh = bits - 18 (at least 32)
+            const uint32_t sh = bits[s] > 50 ? bits[s] - 18 : 32, e = bits[s] - 1 - sh;
+            u64* out = lds + (4 * s + g) * CC_REGION;
+#pragma unroll
+            for (int b = 0; b < 8; b++) {
+                const v4i d0 = __builtin_amdgcn_mfma_i32_16x16x64_i8(a0[s], frag[b], k0[s], 0, 0, 0);
+                const v4i d1 = __builtin_amdgcn_mfma_i32_16x16x64_i8(a1[s], frag[b], k1[s], 0, 0, 0);
+                const int p01 = d0.x + (d0.y << 8), p23 = d0.z + (d0.w << 8), p45 = d1.x + (d1.y << 8), p67 = d1.z + (d1.w << 8);
+                const int64_t lo = (int64_t)p23 * 65536 + p01, hi = (int64_t)p67 * 65536 + p45 + (lo >> 32);
+                const uint32_t qh = __umulhi((uint32_t)((u64)hi >> (sh - 32)), rec[s]) >> e;
+                u64 v = ((u64)(uint32_t)hi << 32) | (uint32_t)lo;
+                v += (u64)qh * n0[s];
+                v = ((u64)add3((uint32_t)(v >> 32), qh * n1[s], 0) << 32) | (uint32_t)v;
+                if (tg < nt) out[cc_word(2 * w + (b >> 2), 16 * (b & 3) + p16)] = v;
+            }
+        }
+        __syncthreads();
+        const uint32_t tw_ = t0 + w;
+        if (tw_ < nt) {
+            const uint32_t mi = __builtin_amdgcn_readfirstlane(st.mod[tw_]), li = __builtin_amdgcn_readfirstlane(st.limb[tw_]);
+            u64* dst = st.dst + (size_t)rep * cc.dst_stride + ((size_t)li << (LC + 8));
+            if (cc.wide_fwd >> mi & 1u) cc_target<LC, true>(reg, dst, cc_pin<true>(mi), lane, c0, mc, ftw);
+            else cc_target<LC, false>(reg, dst, cc_pin<false>(mi), lane, c0, mc, ftw);
+        }
+    }
+}
+
+int32_t launch_col_conv(he_ctx* ctx, const ColConv& cc, const ScaleList& sc, uint32_t reps, uint32_t limb_passes) {
+    const uint32_t groups = cc.n_sets * reps, LC = ctx->logN - 8;
+    if (groups == 0) return HE_OK;
+    if (LC < 5 || LC > 8 || cc.n_sets > CC_MAX_SETS) return he_fail(ctx, HE_ERR_BADARG, "column conversion: bad shape");
+    for (uint32_t s = 0; s < cc.n_sets; s++) {
+        const ColConvSet& st = cc.set[s];
+        if (st.ns == 0 || st.ns > CC_WAVES || st.nt == 0 || st.nt > HE_MAX_MODULI || st.mod0 + st.ns > ctx->M || st.sc0 + st.ns > HE_MAX_MODULI ||
+            !st.src || !st.dst || !st.digits || !st.bias)
+            return he_fail(ctx, HE_ERR_BADARG, "column conversion: bad group %u", s);
+    }
+    hipEvent_t e0 = nullptr, e1 = nullptr;
+    if (ctx->prof_on) {
+        HE_HIP(ctx, hipEventCreate(&e0));
+        HE_HIP(ctx, hipEventCreate(&e1));
+        HE_HIP(ctx, hipEventRecord(e0, ctx->stream));
+    }
+    const dim3 grid(groups << (LC - 2)), block(CC_THREADS);
+    switch (LC) {
+    case 5: hipLaunchKernelGGL(col_conv_kernel<5>, grid, block, 0, ctx->stream, cc, sc, ctx->d_mc, ctx->d_tw, ctx->d_itw); break;
+    case 6: hipLaunchKernelGGL(col_conv_kernel<6>, grid, block, 0, ctx->stream, cc, sc, ctx->d_mc, ctx->d_tw, ctx->d_itw); break;
+    case 7: hipLaunchKernelGGL(col_conv_kernel<7>, grid, block, 0, ctx->stream, cc, sc, ctx->d_mc, ctx->d_tw, ctx->d_itw); break;
+    default: hipLaunchKernelGGL(col_conv_kernel<8>, grid, block, 0, ctx->stream, cc, sc, ctx->d_mc, ctx->d_tw, ctx->d_itw); break;
+    }
+    HE_HIP(ctx, hipGetLastError());
+    if (ctx->prof_on) {
+        HE_HIP(ctx, hipEventRecord(e1, ctx->stream));
+        ctx->prof_events.push_back({e0, e1, limb_passes, 0u, 0u});
+    }
+    return HE_OK;
+}

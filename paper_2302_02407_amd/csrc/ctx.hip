@@ -133,6 +133,8 @@ int32_t he_ctx_create(he_ctx** out, uint32_t logN, const uint64_t* h_q, uint32_t
     c->stream = (hipStream_t)hip_stream;
     c->d_mc = nullptr; c->d_tw = c->d_itw = nullptr;
     c->d_ws = nullptr; c->ws_bytes = 0;
+    c->d_up_dig = c->d_dn_dig = nullptr;
+    c->d_up_bias = c->d_dn_bias = nullptr;
     c->d_up_hat = c->d_dn_hat = c->d_pinv = c->d_pinv_sh = c->d_qlinv = c->d_qlinv_sh = nullptr;
     memset(&c->cnt, 0, sizeof(c->cnt));
     c->prof_on = false;

@@ -67,6 +67,10 @@ struct he_ctx {
     std::vector<u64> h_up_invhat; // [dnum][alpha][alpha]: ((Q_j/q_i)^-1 mod q_i), [j][sz-1][i]
     u64* d_dn_hat;     // [np][M]: (P/p_t) mod m  (only m < nq used)
     std::vector<u64> h_dn_invhat; // [np]: (P/p_t)^-1 mod p_t
+    // the same constants as operands of the matrix instruction (colconv.hip): [dnum][alpha][M] and [M], null where that path
+    // does not apply
+    uint8_t *d_up_dig, *d_dn_dig;   // 512 bytes per modulus
+    int32_t *d_up_bias, *d_dn_bias; // 8 per modulus
     u64* d_pinv;       // [nq] P^-1 mod q_r
     u64* d_pinv_sh;    // [nq] Shoup companions
     // rescale tables: q_l^-1 mod q_r for r < l, [nq][nq]
@@ -212,6 +216,26 @@ struct ColFuse {
     uint8_t tgt_limb[CF_MAX_SETS][HE_MAX_MODULI];     // indexed per wavefront: vector loads
     uint8_t tgt_mod[CF_MAX_SETS][HE_MAX_MODULI];
 };
+// Basis conversion with the column passes around it (colconv.hip).  Set s (a digit of ModUp; the special primes of ModDown):
+// sources src + rep*src_stride + i*N (i < ns, moduli mod0 + i, output scaling sc entry sc0 + i) in the state the inverse
+// row pass leaves them; target t has modulus mod[t] and is written, in the state the forward column pass leaves it, at
+// dst + rep*dst_stride + limb[t]*N.  digits / bias: conversion constants per modulus (conv_operand).
+#define CC_MAX_SETS 8
+struct ColConvSet {
+    const u64* src;
+    u64* dst;
+    const uint8_t* digits;     // [modulus][512]
+    const int32_t* bias;       // [modulus][8]
+    uint32_t ns, mod0, sc0, nt;
+    uint8_t limb[HE_MAX_MODULI], mod[HE_MAX_MODULI];   // indexed per lane or wavefront: vector loads
+};
+struct ColConv {
+    ColConvSet set[CC_MAX_SETS];
+    size_t src_stride, dst_stride;
+    u64 wide_fwd, wide_inv;    // bit per modulus: wide in the forward (above 57 bits) / inverse (above 54) ranges
+    uint32_t n_sets, pad;
+};
+int32_t launch_col_conv(he_ctx* ctx, const ColConv& cc, const ScaleList& sc, uint32_t reps, uint32_t limb_passes);
 int32_t launch_colfuse(he_ctx* ctx, const ColFuse& cf, const ScaleList& sc, uint32_t limb_passes);   // ntt2p.hip
 // fills w / w_sh of entry i from s (modulus index mi)
 void scale_entry(const he_ctx* c, ScaleList& sc, uint32_t i, uint32_t mi, u64 s);

@@ -260,6 +260,30 @@ __global__ __launch_bounds__(KS_THREADS) void rescale_delta_kernel(const u64* __
 static uint32_t num_digits(const he_ctx* c, uint32_t level) { return (level + c->alpha) / c->alpha; }
 static uint32_t pad8(uint32_t x) { return (x + 7u) & ~7u; }
 
+// One target modulus of a conversion as the operand of the matrix instruction (colconv.hip): hat[i] = the factor of source i
+// (i < ns <= 8).  V_(i,a) = hat_i * 2^(8a) mod m, centred, in 8 signed base-256 digits; dig: [digit / 4][digit % 4][byte
+// group of 2 sources][16], bias: base-256 digits of 128 * sum V + 4096 m, which returns the 128 taken from every source
+// byte and keeps the sum from becoming negative (64 products of at most 128 and m/2).
+static void conv_operand(const u64* hat, uint32_t ns, u64 m, uint8_t* dig, int32_t* bias) {
+    u64 total = 0;
+    for (uint32_t i = 0; i < ns; i++) {
+        u64 v = hat[i] % m;
+        for (uint32_t a = 0; a < 8; a++) {
+            total = (total + v) % m;
+            int64_t sv = v > m / 2 ? (int64_t)v - (int64_t)m : (int64_t)v;
+            for (uint32_t b = 0; b < 8; b++) {
+                const int64_t low = (int64_t)(int8_t)(uint8_t)(sv & 0xFF);
+                dig[(b >> 2) * 256 + (b & 3) * 64 + i * 8 + a] = (uint8_t)low;
+                sv = (sv - low) >> 8;
+            }
+            v = h_mulmod(v, 256, m);
+        }
+    }
+    u128 k = (u128)h_mulmod(total, 128, m) + ((u128)m << 12);
+    for (uint32_t b = 0; b < 7; b++) { bias[b] = (int32_t)(k & 0xFF); k >>= 8; }
+    bias[7] = (int32_t)k;
+}
+
 int32_t ks_init_tables(he_ctx* c) {
     const uint32_t nq = c->nq, np = c->np, M = c->M, al = c->alpha, dn = c->dnum;
     // rescale: q_l^-1 mod q_r
@@ -318,6 +342,29 @@ int32_t ks_init_tables(he_ctx* c) {
         pinv[r] = h_invmod(P, c->mod[r]);
         pinv_sh[r] = h_shoup(pinv[r], c->mod[r]);
     }
+    // operands of the fused column conversion: rings of 2^13 .. 2^16, at most 8 sources, moduli of at least 36 bits
+    bool operands = two_pass(c) && c->logN <= 16;
+    for (uint32_t m = 0; m < M; m++) operands = operands && c->h_mc[m].bits >= 36;
+    if (operands && al <= 8) {
+        std::vector<uint8_t> dig((size_t)dn * al * M * 512, 0);
+        std::vector<int32_t> bias((size_t)dn * al * M * 8, 0);
+        for (uint32_t sl = 0; sl < dn * al; sl++)
+            for (uint32_t m = 0; m < M; m++)
+                conv_operand(&hat[((size_t)sl * M + m) * aw], sl % al + 1, c->mod[m], &dig[((size_t)sl * M + m) * 512], &bias[((size_t)sl * M + m) * 8]);
+        HE_HIP(c, hipMalloc(&c->d_up_dig, dig.size()));
+        HE_HIP(c, hipMalloc(&c->d_up_bias, bias.size() * sizeof(int32_t)));
+        HE_HIP(c, hipMemcpy(c->d_up_dig, dig.data(), dig.size(), hipMemcpyHostToDevice));
+        HE_HIP(c, hipMemcpy(c->d_up_bias, bias.data(), bias.size() * sizeof(int32_t), hipMemcpyHostToDevice));
+    }
+    if (operands && np <= 8) {
+        std::vector<uint8_t> dig((size_t)M * 512, 0);
+        std::vector<int32_t> bias((size_t)M * 8, 0);
+        for (uint32_t m = 0; m < M; m++) conv_operand(&dhat[(size_t)m * pw], np, c->mod[m], &dig[(size_t)m * 512], &bias[(size_t)m * 8]);
+        HE_HIP(c, hipMalloc(&c->d_dn_dig, dig.size()));
+        HE_HIP(c, hipMalloc(&c->d_dn_bias, bias.size() * sizeof(int32_t)));
+        HE_HIP(c, hipMemcpy(c->d_dn_dig, dig.data(), dig.size(), hipMemcpyHostToDevice));
+        HE_HIP(c, hipMemcpy(c->d_dn_bias, bias.data(), bias.size() * sizeof(int32_t), hipMemcpyHostToDevice));
+    }
     HE_HIP(c, hipMalloc(&c->d_up_hat, hat.size() * sizeof(u64)));
     HE_HIP(c, hipMalloc(&c->d_dn_hat, dhat.size() * sizeof(u64)));
     HE_HIP(c, hipMalloc(&c->d_pinv, nq * sizeof(u64)));
@@ -332,6 +379,10 @@ int32_t ks_init_tables(he_ctx* c) {
 void ks_free_tables(he_ctx* c) {
     if (c->d_up_hat) (void)hipFree(c->d_up_hat);
     if (c->d_dn_hat) (void)hipFree(c->d_dn_hat);
+    if (c->d_up_dig) (void)hipFree(c->d_up_dig);
+    if (c->d_up_bias) (void)hipFree(c->d_up_bias);
+    if (c->d_dn_dig) (void)hipFree(c->d_dn_dig);
+    if (c->d_dn_bias) (void)hipFree(c->d_dn_bias);
     if (c->d_pinv) (void)hipFree(c->d_pinv);
     if (c->d_pinv_sh) (void)hipFree(c->d_pinv_sh);
     if (c->d_qlinv) (void)hipFree(c->d_qlinv);
@@ -379,6 +430,13 @@ static bool colfuse_ok(const he_ctx* c, uint32_t groups, uint32_t sets, uint32_t
            nt <= c->cf_max_targets && nt <= HE_MAX_MODULI;
 }
 
+static void col_conv_widths(const he_ctx* c, ColConv& cc) {
+    for (uint32_t m = 0; m < c->M; m++) {
+        cc.wide_fwd |= (u64)(c->h_mc[m].bits > 57) << m;
+        cc.wide_inv |= (u64)(c->h_mc[m].bits > 54) << m;
+    }
+}
+
 // ModUp of `cb` sources at once.  raised [cb][beta][R][N] (own limbs left unwritten), tmp [cb][L1][N].
 static int32_t modup_batch(he_ctx* c, const KsSrc* srcs, uint32_t cb, uint32_t level, u64* raised, u64* tmp) {
     const uint32_t N = c->N, L1 = level + 1, R = L1 + c->np, beta = num_digits(c, level), al = c->alpha;
@@ -392,6 +450,7 @@ static int32_t modup_batch(he_ctx* c, const KsSrc* srcs, uint32_t cb, uint32_t l
     }
     // small launches at N = 2^16: the column passes and the conversion run as one launch between the two row passes
     const bool cf_on = colfuse_ok(c, cb * beta, beta, al, R) && cb * beta * R <= HE_MAX_LAUNCH_LIMBS;
+    const bool cc_on = !cf_on && c->d_up_dig && beta <= CC_MAX_SETS && beta * R <= HE_MAX_LAUNCH_LIMBS;
     {
         std::vector<uint32_t> mods(cb * L1);
         std::vector<uint8_t> seg(cb * L1);
@@ -404,12 +463,33 @@ static int32_t modup_batch(he_ctx* c, const KsSrc* srcs, uint32_t cb, uint32_t l
         }
         t.mod_idx = mods.data(); t.src_seg = seg.data(); t.src_limb = lim.data();
         t.scale = &sc; t.scale_period = L1;
-        t.only_pass = cf_on ? 1u : 0u;
+        t.only_pass = (cf_on || cc_on) ? 1u : 0u;
         int32_t rc = launch_transform(c, t);
         if (rc != HE_OK) return rc;
     }
     const uint32_t aw = pad8(al);
-    if (cf_on) {
+    if (cc_on) {
+        ColConv cc = {};
+        col_conv_widths(c, cc);
+        cc.n_sets = beta; cc.src_stride = (size_t)L1 * N; cc.dst_stride = (size_t)beta * R * N;
+        uint32_t passes = 0;
+        for (uint32_t j = 0; j < beta; j++) {
+            const uint32_t lo = j * al, hi = std::min((j + 1) * al, L1), sz = hi - lo;
+            const size_t slab = (size_t)(j * al + (sz - 1)) * c->M;
+            ColConvSet& st = cc.set[j];
+            st.src = tmp + (size_t)lo * N; st.dst = raised + (size_t)j * R * N;
+            st.digits = c->d_up_dig + slab * 512; st.bias = c->d_up_bias + slab * 8;
+            st.ns = sz; st.mod0 = lo; st.sc0 = lo;
+            for (uint32_t r = 0; r < R; r++) {
+                if (r >= lo && r < hi) continue;
+                st.limb[st.nt] = (uint8_t)r;
+                st.mod[st.nt++] = (uint8_t)(r <= level ? r : c->nq + (r - level - 1));
+            }
+            passes += sz + st.nt;
+        }
+        int32_t rc = launch_col_conv(c, cc, sc, cb, cb * passes);
+        if (rc != HE_OK) return rc;
+    } else if (cf_on) {
         ColFuse cf = {};
         cf.hat_w = aw; cf.n_groups = cb * beta;
         uint32_t passes = 0;
@@ -433,21 +513,7 @@ static int32_t modup_batch(he_ctx* c, const KsSrc* srcs, uint32_t cb, uint32_t l
         }
         int32_t rc = launch_colfuse(c, cf, sc, passes);
         if (rc != HE_OK) return rc;
-        std::vector<uint32_t> mods(cb * beta * R);
-        for (uint32_t s = 0; s < cb; s++)
-            for (uint32_t j = 0; j < beta; j++) {
-                uint32_t lo = j * al, hi = (j + 1) * al < L1 ? (j + 1) * al : L1;
-                for (uint32_t r = 0; r < R; r++)
-                    mods[(s * beta + j) * R + r] = (r >= lo && r < hi) ? 0xFFu : (r <= level ? r : c->nq + (r - level - 1));
-            }
-        TransformDesc t = {};
-        t.fwd = true; t.seg[0] = raised; t.n_seg = 1; t.dst = raised; t.n = cb * beta * R; t.mod_idx = mods.data();
-        t.lazy_out = true; t.only_pass = 2;
-        rc = launch_transform(c, t);
-        if (rc != HE_OK) return rc;
-        c->cnt.modup += cb;
-        return HE_OK;
-    }
+    } else {
     for (uint32_t j0 = 0; j0 < beta; j0 += CONV_MAX_JOBS) {
         ConvBatch b;
         b.njobs = beta - j0 < CONV_MAX_JOBS ? beta - j0 : CONV_MAX_JOBS;
@@ -476,7 +542,8 @@ static int32_t modup_batch(he_ctx* c, const KsSrc* srcs, uint32_t cb, uint32_t l
         int32_t rc = launch_baseconv(c, b, nt_max, ns_max);
         if (rc != HE_OK) return rc;
     }
-    // NTT of every converted limb; own limbs are marked "skip"
+    }
+    // NTT of every converted limb (its rows only where the columns are done); own limbs are marked "skip"
     const uint32_t per_src = beta * R;
     std::vector<uint32_t> mods(per_src);
     for (uint32_t j = 0; j < beta; j++) {
@@ -494,7 +561,8 @@ static int32_t modup_batch(he_ctx* c, const KsSrc* srcs, uint32_t cb, uint32_t l
             TransformDesc t = {};
             t.fwd = true; t.seg[0] = raised + (size_t)s0 * per_src * N; t.n_seg = 1; t.dst = raised + (size_t)s0 * per_src * N;
             t.n = ns * per_src; t.mod_idx = rep.data();
-            t.lazy_out = true;      // raised digits are only ever multiplied into 128-bit sums of at most 8 terms
+            t.lazy_out = true;      // raised digits are only ever multiplied into sums with room for values below 2q
+            t.only_pass = (cf_on || cc_on) ? 2u : 0u;
             int32_t rc = launch_transform(c, t);
             if (rc != HE_OK) return rc;
         }
@@ -534,6 +602,7 @@ static int32_t moddown_chain(he_ctx* c, uint32_t level, uint32_t J, u64* acc, u6
                              const ModDownEpilogue& ep) {
     const uint32_t N = c->N, L1 = level + 1, k = c->np, R = L1 + k;
     const bool cf_on = colfuse_ok(c, 2 * J, 1, k, L1) && 2 * J * std::max(k, L1) <= HE_MAX_LAUNCH_LIMBS;
+    const bool cc_on = !cf_on && c->d_dn_dig != nullptr;
     ScaleList sc;
     for (uint32_t t = 0; t < k; t++) {
         u64 p = c->mod[c->nq + t];
@@ -552,11 +621,21 @@ static int32_t moddown_chain(he_ctx* c, uint32_t level, uint32_t J, u64* acc, u6
         t.fwd = false; t.seg[0] = acc; t.n_seg = 1; t.dst = tmp_dn; t.n = n;
         t.mod_idx = mods.data(); t.src_limb = lim.data(); t.scale = &sc; t.scale_period = k;
         t.ip = ip;
-        t.only_pass = cf_on ? 1u : 0u;
+        t.only_pass = (cf_on || cc_on) ? 1u : 0u;
         int32_t rc = launch_transform(c, t);
         if (rc != HE_OK) return rc;
     }
-    if (cf_on) {
+    if (cc_on) {
+        ColConv cc = {};
+        col_conv_widths(c, cc);
+        cc.n_sets = 1; cc.src_stride = (size_t)k * N; cc.dst_stride = (size_t)L1 * N;
+        ColConvSet& st = cc.set[0];
+        st.src = tmp_dn; st.dst = conv; st.digits = c->d_dn_dig; st.bias = c->d_dn_bias;
+        st.ns = k; st.mod0 = c->nq; st.sc0 = 0; st.nt = L1;
+        for (uint32_t r = 0; r < L1; r++) { st.limb[r] = (uint8_t)r; st.mod[r] = (uint8_t)r; }
+        int32_t rc = launch_col_conv(c, cc, sc, 2 * J, 2 * J * (k + L1));
+        if (rc != HE_OK) return rc;
+    } else if (cf_on) {
         ColFuse cf = {};
         cf.hat_w = pad8(k); cf.n_groups = 2 * J;
         cf.nt[0] = L1;
@@ -587,7 +666,7 @@ static int32_t moddown_chain(he_ctx* c, uint32_t level, uint32_t J, u64* acc, u6
         TransformDesc t = {};
         t.fwd = true; t.seg[0] = conv; t.n_seg = 1; t.dst = conv; t.n = n; t.mod_idx = mods.data(); t.ep = &ep;
         t.lazy_out = true;
-        t.only_pass = cf_on ? 2u : 0u;
+        t.only_pass = (cf_on || cc_on) ? 2u : 0u;
         int32_t rc = launch_transform(c, t);
         if (rc != HE_OK) return rc;
     }

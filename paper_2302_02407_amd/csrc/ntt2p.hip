@@ -407,7 +407,8 @@ __device__ __forceinline__ void ip_row_terms(Term&& term, uint32_t n_terms, uint
 }
 
 // ---------------------------------------------------------------- forward row pass
-// Pass B: workgroup = 16 consecutive rows (256-point blocks); tid = blk*16 + t.
+// Pass B: workgroup = 16 consecutive rows (256-point blocks); tid = blk*16 + t.  A row stays inside 16 lanes of one wavefront,
+// so its exchanges need no barrier and the wavefronts run apart.
 // EPI: 0 = plain transform; 1 = ModDown epilogue with the accumulator read from memory; 2 = ModDown epilogue that also
 // computes the accumulator (the key-switch inner product of this limb) from the raised digits and the key, so that the
 // q-limbs of the accumulator never exist in memory (BETA as in ip_row); 3 = the same for a sum over several terms.
@@ -436,7 +437,7 @@ __device__ __forceinline__ void row_fwd(const P2Args& a, uint32_t e, uint32_t ti
     SCHED_FENCE();
 #pragma unroll
     for (int k = 0; k < 16; k++) s[t + 17 * k] = x[k];
-    __syncthreads();
+    wave_exchange();
 #pragma unroll
     for (int j = 0; j < 16; j++) x[j] = s[17 * t + j];
     fwd_stages<WIDE, 0, 4>(x, w2, q);
@@ -448,10 +449,10 @@ __device__ __forceinline__ void row_fwd(const P2Args& a, uint32_t e, uint32_t ti
 #pragma unroll
             for (int j = 0; j < 16; j++) x[j] = reduce_full<7>(x[j], q, m.bits, m.rec);
         }
-        __syncthreads();
+        wave_exchange();
 #pragma unroll
         for (int j = 0; j < 16; j++) s[17 * t + j] = x[j];
-        __syncthreads();
+        wave_exchange();
 #pragma unroll
         for (int k = 0; k < 16; k++) row[t + 16 * k] = s[t + 17 * k];
         return;
@@ -463,7 +464,7 @@ __device__ __forceinline__ void row_fwd(const P2Args& a, uint32_t e, uint32_t ti
 #pragma unroll
         for (int j = 0; j < 16; j++) x[j] = reduce_lazy<7>(x[j], q, m.bits, m.rec);
     }
-    __syncthreads();
+    wave_exchange();
 #pragma unroll
     for (int j = 0; j < 16; j++) s[17 * t + j] = x[j];
     const u64 bias = raw ? (q << 7) : 2 * q;
@@ -476,7 +477,7 @@ __device__ __forceinline__ void row_fwd(const P2Args& a, uint32_t e, uint32_t ti
     const bool has_c0 = c0p != nullptr, has_self = sp != nullptr;
     const u64* c0 = has_c0 ? c0p + ro : nullptr;
     const u64* self = has_self ? sp + ro : nullptr;
-    __syncthreads();
+    wave_exchange();
     // v: accumulator values in slot order, below 5q
     auto emit = [&](int ch, uint32_t pos, const u64 (&v)[4], const uint32_t (&src)[2], const uint32_t (&swp)[2]) {
         ulonglong2 cv[2], sv[2];
@@ -584,7 +585,7 @@ __device__ __forceinline__ void row_inv(const P2Args& a, const LimbTab& tab, uin
         }
         tw_load<0, 4>(w2, tw, lc + 4, 16 * b + t);
     }
-    __syncthreads();
+    wave_exchange();
 #pragma unroll
     for (int j = 0; j < 16; j++) x[j] = s[17 * t + j];
     const u64 q = uni64(m.q);
@@ -600,10 +601,10 @@ __device__ __forceinline__ void row_inv(const P2Args& a, const LimbTab& tab, uin
     SCHED_FENCE();
     tw_load<0, 2>(w1, tw, lc, b);
     SCHED_FENCE();
-    __syncthreads();
+    wave_exchange();
 #pragma unroll
     for (int j = 0; j < 16; j++) s[17 * t + j] = x[j];
-    __syncthreads();
+    wave_exchange();
 #pragma unroll
     for (int k = 0; k < 16; k++) x[k] = s[t + 17 * k];
     bounds_all(bd, WIDE ? 4 : 32);

@@ -156,3 +156,10 @@ template <int LOGV>
 __device__ __forceinline__ u64 reduce_full(u64 v, u64 q, uint32_t bits, uint32_t rec) {
     return csub(reduce_lazy<LOGV>(v, q, bits, rec), q);
 }
+
+// lanes of one wavefront exchange through LDS: its own accesses are in order, the compiler has to keep them so
+__device__ __forceinline__ void wave_exchange() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
