@@ -61,8 +61,7 @@ def _ct(level, N):
 def merge_outputs(ctx, outs, masks, level):
     """sum_o outs[o] (.) masks[o], rescaled: level -> level-1."""
     acc = _ct(level, ctx.N)
-    for o, (ct, m) in enumerate(zip(outs, masks)):
-        ctx.he_ptct_mac(acc, ct, m, level, init=(o == 0))
+    ctx.he_ptct_mac_rot(acc, outs, masks, [1] * len(outs), level)      # one pass over the sum instead of one per product
     return ctx.he_rescale(acc, level, _ct(level - 1, ctx.N))
 
 

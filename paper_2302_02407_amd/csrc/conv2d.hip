@@ -9,63 +9,119 @@
 #define CV_THREADS 256
 #define CV_MAX_TAPS 49
 
-#define CV_MAX_OUT_PER_LAUNCH 16
+#define CV_MAX_OUT_PER_LAUNCH 16                         // x 9 plaintexts = MAC_MAX_PT
 
-struct MacTaps {
-    const u64* ct[CV_MAX_TAPS];                          // rotated inputs [2][CL][N]
-    uint32_t n_taps, n_out;
-    uint32_t c1_tap;                                     // 0xFFFFFFFF: every tap has both components; else only this tap
-                                                         // has a second component (the others are [CL][N])
-    u64* acc[CV_MAX_OUT_PER_LAUNCH];                     // one accumulator [2][CL][N] per output
-};
-struct MacWeights {
-    const u64* pt[CV_MAX_OUT_PER_LAUNCH * 9];            // [out][tap] filter plaintexts [L1][N] (9-tap fast path)
+// Sums of products of a few ciphertexts with many plaintexts: acc_o = sum_i ct_i * pt_(o,i) for o < n_out, both components.
+#define MAC_MAX_IN 16
+#define MAC_MAX_PT 144
+struct MacMany {
+    const u64* ct[MAC_MAX_IN];                           // [2][CL][N]
+    const u64* pt[MAC_MAX_PT];                           // [o * NI + i], [CL][N]
+    u64* acc[MAC_MAX_IN];                                // [2][CL][N]
+    uint32_t n_in, n_out, init;                          // init = 0: continues from acc's current (canonical) contents
+    uint32_t c1_tap;                                     // 0xFFFFFFFF: every ct has both components; else only this one has a
+                                                         // second component (the others are [CL][N])
 };
 
-// MulFilter&Sum_f for several output ciphertexts at once (9 taps or fewer): the rotated inputs of a
-// coefficient are loaded once and reused for every output, acc_o,c[limb] = sum_t ct_t,c[limb] *
-// pt_o,t[limb], summed in 128 bits and reduced once per 8 taps.  grid: (N/256, CL).  Operands and outputs have CL
-// limbs per component: the level+1 ciphertext primes, followed by the special primes when the operands are
-// key-switch inner products still over the raised basis (CL = level+1+k).
-__global__ __launch_bounds__(CV_THREADS) void mac_taps9_kernel(MacTaps taps, MacWeights w, const ModConst* mc, uint32_t logN,
-                                                               uint32_t CL, uint32_t level, uint32_t nq) {
-    const uint32_t n = blockIdx.x * CV_THREADS + threadIdx.x;
+// MulFilter&Sum of several outputs at once: a thread keeps NC adjacent coefficients of both components of all (at most NI)
+// ciphertexts in registers and then reads the plaintexts of one output after the other, each byte of which is used once:
+// bound by reading them (non-temporal, so that they do not displace the ciphertexts and accumulators that other kernels
+// read next).  Operands and outputs have CL limbs per component: the level+1 ciphertext primes, followed by the special
+// primes when the operands are key-switch inner products still over the raised basis.  grid: (N/(256 NC), CL).
+typedef u64 mac_v2 __attribute__((ext_vector_type(2)));
+template <int NC>
+struct MacVec;
+template <>
+struct MacVec<1> {
+    u64 v[1];
+    __device__ __forceinline__ void load(const u64* p) { v[0] = *p; }
+    __device__ __forceinline__ void load_nt(const u64* p) { v[0] = __builtin_nontemporal_load(p); }
+    __device__ __forceinline__ void store(u64* p) const { *p = v[0]; }
+};
+template <>
+struct MacVec<2> {
+    u64 v[2];
+    __device__ __forceinline__ void load(const u64* p) { const mac_v2 t = *reinterpret_cast<const mac_v2*>(p); v[0] = t.x; v[1] = t.y; }
+    __device__ __forceinline__ void load_nt(const u64* p) {
+        const mac_v2 t = __builtin_nontemporal_load(reinterpret_cast<const mac_v2*>(p));
+        v[0] = t.x; v[1] = t.y;
+    }
+    __device__ __forceinline__ void store(u64* p) const { *reinterpret_cast<mac_v2*>(p) = mac_v2{v[0], v[1]}; }
+};
+template <int NI, int NC>
+__global__ __launch_bounds__(CV_THREADS) void mac_many_kernel(MacMany a, const ModConst* mc, uint32_t logN, uint32_t CL, uint32_t level, uint32_t nq) {
+    const uint32_t n = (blockIdx.x * CV_THREADS + threadIdx.x) * NC;
     const uint32_t limb = blockIdx.y;
+    if (n >> logN) return;
     const ModConst m = mc[limb <= level ? limb : nq + (limb - level - 1)];
     const size_t o0 = ((size_t)limb << logN) + n, o1 = ((size_t)(limb + CL) << logN) + n;
-    u64 c0[9], c1[9];
+    MacVec<NC> c0[NI], c1[NI];
 #pragma unroll
-    for (uint32_t t = 0; t < 9; t++) {
-        c0[t] = t < taps.n_taps ? taps.ct[t][o0] : 0;
-        c1[t] = (t < taps.n_taps && (taps.c1_tap == 0xFFFFFFFFu || taps.c1_tap == t)) ? taps.ct[t][o1] : 0;
-    }
-    for (uint32_t o = 0; o < taps.n_out; o++) {
-        u128 a0 = 0, a1 = 0;
+    for (uint32_t i = 0; i < NI; i++) {
+        if (i < a.n_in) c0[i].load(a.ct[i] + o0);
+        if (i < a.n_in && (a.c1_tap == 0xFFFFFFFFu || a.c1_tap == i)) c1[i].load(a.ct[i] + o1);
+        else {
 #pragma unroll
-        for (uint32_t t = 0; t < 9; t++) {
-            if (t == 8) {
-                a0 = barrett128(a0, m.q, m.mu, m.bits);
-                a1 = barrett128(a1, m.q, m.mu, m.bits);
-            }
-            if (t < taps.n_taps) {
-                u64 p = w.pt[o * 9 + t][o0];
-                a0 += (u128)c0[t] * p;
-                a1 += (u128)c1[t] * p;
-            }
+            for (int k = 0; k < NC; k++) { c1[i].v[k] = 0; if (i >= a.n_in) c0[i].v[k] = 0; }
         }
-        taps.acc[o][o0] = barrett128(a0, m.q, m.mu, m.bits);
-        taps.acc[o][o1] = barrett128(a1, m.q, m.mu, m.bits);
+    }
+    for (uint32_t o = 0; o < a.n_out; o++) {
+        MacVec<NC> p[NI], r0, r1;
+        // (their halves are formed anew for every output: kept, they would take twice the registers)
+#pragma unroll
+        for (uint32_t i = 0; i < NI; i++) {
+#pragma unroll
+            for (int k = 0; k < NC; k++) asm("" : "+v"(c0[i].v[k]), "+v"(c1[i].v[k]));
+        }
+#pragma unroll
+        for (uint32_t i = 0; i < NI; i++) {
+            if (i < a.n_in) p[i].load_nt(a.pt[o * NI + i] + o0);
+        }
+        if (a.init) {
+#pragma unroll
+            for (int k = 0; k < NC; k++) r0.v[k] = r1.v[k] = 0;
+        } else {
+            r0.load(a.acc[o] + o0);
+            r1.load(a.acc[o] + o1);
+        }
+#pragma unroll
+        for (int k = 0; k < NC; k++) {
+            SplitSum s0 = {0, 0, 0}, s1 = {0, 0, 0};
+#pragma unroll
+            for (uint32_t i = 0; i < NI; i++) {
+                if (i && i % SPLIT_MAX == 0) {           // running totals below q + 2*5q
+                    r0.v[k] += split_reduce(s0, m); r1.v[k] += split_reduce(s1, m);
+                    s0 = s1 = SplitSum{0, 0, 0};
+                }
+                if (i < a.n_in) { split_mac(s0, c0[i].v[k], p[i].v[k]); split_mac(s1, c1[i].v[k], p[i].v[k]); }
+            }
+            static_assert(NI <= 2 * SPLIT_MAX || NI == 16, "totals stay below 16q");
+            r0.v[k] = reduce_full<7>(r0.v[k] + split_reduce(s0, m), m.q, m.bits, m.rec);
+            r1.v[k] = reduce_full<7>(r1.v[k] + split_reduce(s1, m), m.q, m.bits, m.rec);
+        }
+        r0.store(a.acc[o] + o0);
+        r1.store(a.acc[o] + o1);
     }
 }
+
+// Two coefficients per thread while the ciphertexts' fit the registers (16-byte accesses), one with up to 16 of them.
+static void launch_mac_many(he_ctx* ctx, const MacMany& a, uint32_t CL, uint32_t level) {
+    const dim3 block(CV_THREADS), g1(ctx->N / CV_THREADS, CL), g2((ctx->N + 2 * CV_THREADS - 1) / (2 * CV_THREADS), CL);
+    if (a.n_in <= 8) hipLaunchKernelGGL((mac_many_kernel<8, 2>), g2, block, 0, ctx->stream, a, ctx->d_mc, ctx->logN, CL, level, ctx->nq);
+    else if (a.n_in <= 9) hipLaunchKernelGGL((mac_many_kernel<9, 2>), g2, block, 0, ctx->stream, a, ctx->d_mc, ctx->logN, CL, level, ctx->nq);
+    else hipLaunchKernelGGL((mac_many_kernel<16, 1>), g1, block, 0, ctx->stream, a, ctx->d_mc, ctx->logN, CL, level, ctx->nq);
+}
+// index of plaintext (o, i) in MacMany::pt for n_in ciphertexts
+static uint32_t mac_pt_index(uint32_t n_in, uint32_t o, uint32_t i) { return o * (n_in <= 8 ? 8 : n_in <= 9 ? 9 : 16) + i; }
 
 struct MacTapsAny {
     const u64* ct[CV_MAX_TAPS];
     const u64* pt[CV_MAX_TAPS];
     uint32_t n, init;
-    uint32_t c1_tap;                                     // as in MacTaps
+    uint32_t c1_tap;                                     // as in MacMany
 };
 // Any number of (ciphertext, plaintext) products, one output per launch; init = 0 continues from the
-// accumulator's current (canonical) contents.  CL, level, nq as in mac_taps9_kernel.
+// accumulator's current (canonical) contents.  CL, level, nq as in mac_many_kernel.
 __global__ __launch_bounds__(CV_THREADS) void mac_taps_kernel(MacTapsAny taps, u64* __restrict__ acc, const ModConst* mc,
                                                               uint32_t logN, uint32_t CL, uint32_t level, uint32_t nq) {
     const uint32_t n = blockIdx.x * CV_THREADS + threadIdx.x;
@@ -230,23 +286,22 @@ extern "C" int32_t he_conv2d(he_ctx* ctx, const he_conv_plan* plan, const uint64
         for (uint32_t o0 = 0; o0 < n_out; o0 += nb_max) {
             const uint32_t nb = std::min<uint32_t>(nb_max, n_out - o0);
             if (n_rot <= 9 && taps <= 9) {
-                MacTaps mt;
-                MacWeights mw;
-                mt.n_taps = n_rot; mt.n_out = nb; mt.c1_tap = 0xFFFFFFFFu;
+                MacMany mt = {};
+                mt.n_in = n_rot; mt.n_out = nb; mt.init = 1; mt.c1_tap = 0xFFFFFFFFu;
                 for (uint32_t i = 0; i < n_rot; i++) mt.ct[i] = A + (size_t)i * 2 * R * N;
                 for (uint32_t o = 0; o < nb; o++) {
                     mt.acc[o] = ACC + (size_t)o * 2 * R * N;
-                    for (uint32_t i = 0; i < n_rot; i++) mw.pt[o * 9 + i] = (const u64*)plan->h_d_weights[(size_t)(o0 + o) * taps + rot_tap[i]];
+                    for (uint32_t i = 0; i < n_rot; i++) mt.pt[mac_pt_index(n_rot, o, i)] = (const u64*)plan->h_d_weights[(size_t)(o0 + o) * taps + rot_tap[i]];
                 }
-                hipLaunchKernelGGL(mac_taps9_kernel, grid_r, block, 0, ctx->stream, mt, mw, ctx->d_mc, ctx->logN, R, level, ctx->nq);
+                launch_mac_many(ctx, mt, R, level);
                 HE_HIP(ctx, hipGetLastError());
-                mt.n_taps = taps; mt.c1_tap = centre;
+                mt.n_in = taps; mt.c1_tap = centre;
                 for (uint32_t t = 0; t < taps; t++) mt.ct[t] = plain_ct[t];
                 for (uint32_t o = 0; o < nb; o++) {
                     mt.acc[o] = plain + (size_t)o * 2 * L1 * N;
-                    for (uint32_t t = 0; t < taps; t++) mw.pt[o * 9 + t] = (const u64*)plan->h_d_weights[(size_t)(o0 + o) * taps + t];
+                    for (uint32_t t = 0; t < taps; t++) mt.pt[mac_pt_index(taps, o, t)] = (const u64*)plan->h_d_weights[(size_t)(o0 + o) * taps + t];
                 }
-                hipLaunchKernelGGL(mac_taps9_kernel, grid_q, block, 0, ctx->stream, mt, mw, ctx->d_mc, ctx->logN, L1, level, ctx->nq);
+                launch_mac_many(ctx, mt, L1, level);
                 HE_HIP(ctx, hipGetLastError());
             } else {
                 for (uint32_t o = 0; o < nb; o++) {
@@ -309,16 +364,15 @@ extern "C" int32_t he_conv2d(he_ctx* ctx, const he_conv_plan* plan, const uint64
             // the accumulators are already in place
         } else if (taps <= 9) {
             for (uint32_t o0 = 0; o0 < n_out; o0 += CV_MAX_OUT_PER_LAUNCH) {
-                MacTaps mt;
-                MacWeights mw;
-                mt.n_taps = taps; mt.c1_tap = 0xFFFFFFFFu;
+                MacMany mt = {};
+                mt.n_in = taps; mt.init = 1; mt.c1_tap = 0xFFFFFFFFu;
                 mt.n_out = std::min<uint32_t>(CV_MAX_OUT_PER_LAUNCH, n_out - o0);
                 for (uint32_t t = 0; t < taps; t++) mt.ct[t] = tap_ct[t];
                 for (uint32_t o = 0; o < mt.n_out; o++) {
                     mt.acc[o] = acc + (size_t)(o0 + o) * ct_e;
-                    for (uint32_t t = 0; t < taps; t++) mw.pt[o * 9 + t] = (const u64*)plan->h_d_weights[(size_t)(o0 + o) * taps + t];
+                    for (uint32_t t = 0; t < taps; t++) mt.pt[mac_pt_index(taps, o, t)] = (const u64*)plan->h_d_weights[(size_t)(o0 + o) * taps + t];
                 }
-                hipLaunchKernelGGL(mac_taps9_kernel, grid, block, 0, ctx->stream, mt, mw, ctx->d_mc, ctx->logN, L1, level, ctx->nq);
+                launch_mac_many(ctx, mt, L1, level);
                 HE_HIP(ctx, hipGetLastError());
             }
         } else {
@@ -367,53 +421,26 @@ extern "C" int32_t he_conv2d(he_ctx* ctx, const he_conv_plan* plan, const uint64
 }
 
 // ---------------------------------------------------------------- RAConv (Algorithm 2)
+// MulFilter&Sum_ci: for every tap the sum over the inputs of input x inversely rotated filter, RA_IN_PER_LAUNCH inputs and 9
+// taps per launch.  pt(i, t): plaintext of input i and tap t; acc(t): accumulator of tap t.
 #define RA_IN_PER_LAUNCH 16
-
-struct RaMac {
-    const u64* ct[RA_IN_PER_LAUNCH];                     // input ciphertexts [2][L1][N]
-    const u64* pt[RA_IN_PER_LAUNCH * 9];                 // [input][tap] inversely rotated filter plaintexts [L1][N]
-    u64* acc[9];                                         // one accumulator ciphertext per tap
-    uint32_t n_in, n_taps, init;
-};
-
-// MulFilter&Sum_ci for up to 9 taps: the coefficients of the (at most NI) inputs are loaded once and kept in registers;
-// each tap's accumulator is then their sum of products with that tap's plaintexts, in 128 bits with one Barrett step
-// per 8 inputs, so that only two sums are live at a time.  init = 0 continues from the accumulators' current
-// (canonical) contents.  grid: (N/256, L1).
-template <int NI>
-__global__ __launch_bounds__(CV_THREADS) void ra_mac9_kernel(RaMac a, const ModConst* mc, uint32_t logN, uint32_t L1) {
-    const uint32_t n = blockIdx.x * CV_THREADS + threadIdx.x;
-    const uint32_t limb = blockIdx.y;
-    const ModConst m = mc[limb];
-    const size_t o0 = ((size_t)limb << logN) + n, o1 = ((size_t)(limb + L1) << logN) + n;
-    u64 c0[NI], c1[NI];
-#pragma unroll
-    for (int i = 0; i < NI; i++) {
-        c0[i] = (uint32_t)i < a.n_in ? a.ct[i][o0] : 0;
-        c1[i] = (uint32_t)i < a.n_in ? a.ct[i][o1] : 0;
-    }
-    for (uint32_t t = 0; t < a.n_taps; t++) {
-        u128 s0 = a.init ? 0 : a.acc[t][o0], s1 = a.init ? 0 : a.acc[t][o1];
-#pragma unroll
-        for (int i = 0; i < NI; i++) {
-            if (i == 8) {
-                s0 = barrett128(s0, m.q, m.mu, m.bits);
-                s1 = barrett128(s1, m.q, m.mu, m.bits);
+template <class Ct, class Pt, class Acc>
+static int32_t ra_mac(he_ctx* ctx, uint32_t n_in, uint32_t taps, uint32_t level, bool fresh, Ct&& ct, Pt&& pt, Acc&& acc) {
+    for (uint32_t t0 = 0; t0 < taps; t0 += 9)
+        for (uint32_t i0 = 0; i0 < n_in; i0 += RA_IN_PER_LAUNCH) {
+            MacMany a = {};
+            a.n_out = std::min<uint32_t>(9, taps - t0);
+            a.n_in = std::min<uint32_t>(RA_IN_PER_LAUNCH, n_in - i0);
+            a.init = fresh && i0 == 0; a.c1_tap = 0xFFFFFFFFu;
+            for (uint32_t t = 0; t < a.n_out; t++) a.acc[t] = acc(t0 + t);
+            for (uint32_t i = 0; i < a.n_in; i++) {
+                a.ct[i] = ct(i0 + i);
+                for (uint32_t t = 0; t < a.n_out; t++) a.pt[mac_pt_index(a.n_in, t, i)] = pt(i0 + i, t0 + t);
             }
-            if ((uint32_t)i < a.n_in) {
-                const u64 p = a.pt[i * 9 + t][o0];
-                s0 += (u128)c0[i] * p;
-                s1 += (u128)c1[i] * p;
-            }
+            launch_mac_many(ctx, a, level + 1, level);
+            HE_HIP(ctx, hipGetLastError());
         }
-        a.acc[t][o0] = barrett128(s0, m.q, m.mu, m.bits);
-        a.acc[t][o1] = barrett128(s1, m.q, m.mu, m.bits);
-    }
-}
-
-static void launch_ra_mac9(he_ctx* ctx, const RaMac& a, dim3 grid, dim3 block, uint32_t L1) {
-    if (a.n_in <= 8) hipLaunchKernelGGL(ra_mac9_kernel<8>, grid, block, 0, ctx->stream, a, ctx->d_mc, ctx->logN, L1);
-    else hipLaunchKernelGGL(ra_mac9_kernel<RA_IN_PER_LAUNCH>, grid, block, 0, ctx->stream, a, ctx->d_mc, ctx->logN, L1);
+    return HE_OK;
 }
 
 struct SumList {
@@ -565,22 +592,10 @@ extern "C" int32_t he_raconv(he_ctx* ctx, const he_raconv_plan* plan, const uint
                                                                // (each element is read before it is written)
     // MulFilter&Sum_ci: per tap, the sum over all inputs of input x inversely rotated filter
     {
-        dim3 grid(N / CV_THREADS, L1), block(CV_THREADS);
-        for (uint32_t t0 = 0; t0 < taps; t0 += 9) {
-            for (uint32_t i0 = 0; i0 < n_in; i0 += RA_IN_PER_LAUNCH) {
-                RaMac a;
-                a.n_taps = std::min<uint32_t>(9, taps - t0);
-                a.n_in = std::min<uint32_t>(RA_IN_PER_LAUNCH, n_in - i0);
-                a.init = i0 == 0;
-                for (uint32_t t = 0; t < a.n_taps; t++) a.acc[t] = acc + (size_t)(t0 + t) * ct_e;
-                for (uint32_t i = 0; i < a.n_in; i++) {
-                    a.ct[i] = (const u64*)h_d_ct_in[i0 + i];
-                    for (uint32_t t = 0; t < a.n_taps; t++) a.pt[i * 9 + t] = (const u64*)plan->h_d_weights[(size_t)(i0 + i) * taps + t0 + t];
-                }
-                launch_ra_mac9(ctx, a, grid, block, L1);
-                HE_HIP(ctx, hipGetLastError());
-            }
-        }
+        rc = ra_mac(ctx, n_in, taps, level, true, [&](uint32_t i) { return (const u64*)h_d_ct_in[i]; },
+                    [&](uint32_t i, uint32_t t) { return (const u64*)plan->h_d_weights[(size_t)i * taps + t]; },
+                    [&](uint32_t t) { return acc + (size_t)t * ct_e; });
+        if (rc != HE_OK) return rc;
         ctx->cnt.mac += (uint64_t)taps * n_in;
     }
     // Slide_1&Sum_f: one rotation per off-centre tap (each accumulator is its own source) and additions
@@ -723,8 +738,6 @@ extern "C" int32_t he_ca_ra_block(he_ctx* ctx, const he_block_plan* plan, const 
             if (rc != HE_OK) return rc;
         }
     }
-    AffineConst kin;                                      // integer lift before the square, per limb
-    for (uint32_t r = 0; r <= lv; r++) { kin.mul[r] = plan->h_k_in[r]; kin.add[r] = 0; }
     for (uint32_t j0 = 0; j0 < n_ra; j0 += G) {
         const uint32_t g = std::min(G, n_ra - j0);
         // MulFilter&Sum_f over every input and tap, for the g intermediates of this group
@@ -732,16 +745,15 @@ extern "C" int32_t he_ca_ra_block(he_ctx* ctx, const he_block_plan* plan, const 
             dim3 grid(N / CV_THREADS, level + 1), block(CV_THREADS);
             if (n_ca == 1 && taps <= 9) {
                 for (uint32_t o0 = 0; o0 < g; o0 += CV_MAX_OUT_PER_LAUNCH) {
-                    MacTaps mt;
-                    MacWeights mw;
-                    mt.n_taps = taps; mt.c1_tap = 0xFFFFFFFFu;
+                    MacMany mt = {};
+                    mt.n_in = taps; mt.init = 1; mt.c1_tap = 0xFFFFFFFFu;
                     mt.n_out = std::min<uint32_t>(CV_MAX_OUT_PER_LAUNCH, g - o0);
                     for (uint32_t t = 0; t < taps; t++) mt.ct[t] = slid[t];
                     for (uint32_t o = 0; o < mt.n_out; o++) {
                         mt.acc[o] = acc + (size_t)(o0 + o) * ct_hi;
-                        for (uint32_t t = 0; t < taps; t++) mw.pt[o * 9 + t] = (const u64*)plan->h_d_w_ca[(size_t)(j0 + o0 + o) * taps + t];
+                        for (uint32_t t = 0; t < taps; t++) mt.pt[mac_pt_index(taps, o, t)] = (const u64*)plan->h_d_w_ca[(size_t)(j0 + o0 + o) * taps + t];
                     }
-                    hipLaunchKernelGGL(mac_taps9_kernel, grid, block, 0, ctx->stream, mt, mw, ctx->d_mc, ctx->logN, level + 1, level, ctx->nq);
+                    launch_mac_many(ctx, mt, level + 1, level);
                     HE_HIP(ctx, hipGetLastError());
                 }
             } else {
@@ -796,19 +808,16 @@ extern "C" int32_t he_ca_ra_block(he_ctx* ctx, const he_block_plan* plan, const 
             if (rc != HE_OK) return rc;
             std::swap(cur, nxt);
         }
-        // Square: integer lift, tensor product, relinearisation of all g at once, Rescale -> ct3
+        // Square: integer lift and tensor product, relinearisation, Rescale -> ct3, all g at once
         {
             std::vector<KsSrc> srcs(g);
             std::vector<KsJob> jobs(g);
             std::vector<const u64*> sq(g);
             std::vector<u64*> outs(g);
+            rc = launch_square_lift(ctx, cur[0], g, lv, (const u64*)plan->h_k_in, tens);   // cur[o] == pa + o*ct_mid
+            if (rc != HE_OK) return rc;
             for (uint32_t o = 0; o < g; o++) {
-                u64* u = cur[o];                          // == pa + o*ct_mid
-                rc = launch_affine(ctx, u, lv, kin, u);
-                if (rc != HE_OK) return rc;
                 u64* d = tens + (size_t)o * 3 * pe_mid;
-                rc = launch_tensor(ctx, u, u, lv, d);
-                if (rc != HE_OK) return rc;
                 u64* res = nxt[o];                        // the other level-1 buffer
                 srcs[o] = {nullptr, d + 2 * pe_mid, d, d + pe_mid};
                 jobs[o] = {o, 1, rl->second, res, res + pe_mid, 1};
@@ -822,23 +831,12 @@ extern "C" int32_t he_ca_ra_block(he_ctx* ctx, const he_block_plan* plan, const 
         }
         // forwarded into the f^2 accumulators of every output: MulFilter&Sum_ci with the inversely rotated filters
         {
-            dim3 grid(N / CV_THREADS, lo + 1), block(CV_THREADS);
-            for (uint32_t l = 0; l < n_ca; l++)
-                for (uint32_t t0 = 0; t0 < taps; t0 += 9)
-                    for (uint32_t i0 = 0; i0 < g; i0 += RA_IN_PER_LAUNCH) {
-                        RaMac a;
-                        a.n_taps = std::min<uint32_t>(9, taps - t0);
-                        a.n_in = std::min<uint32_t>(RA_IN_PER_LAUNCH, g - i0);
-                        a.init = (j0 == 0 && i0 == 0);
-                        for (uint32_t t = 0; t < a.n_taps; t++) a.acc[t] = ct4 + ((size_t)l * taps + t0 + t) * ct_lo;
-                        for (uint32_t i = 0; i < a.n_in; i++) {
-                            a.ct[i] = ct3 + (size_t)(i0 + i) * ct_lo;
-                            for (uint32_t t = 0; t < a.n_taps; t++)
-                                a.pt[i * 9 + t] = (const u64*)plan->h_d_w_ra[((size_t)l * n_ra + j0 + i0 + i) * taps + t0 + t];
-                        }
-                        launch_ra_mac9(ctx, a, grid, block, lo + 1);
-                        HE_HIP(ctx, hipGetLastError());
-                    }
+            for (uint32_t l = 0; l < n_ca; l++) {
+                rc = ra_mac(ctx, g, taps, lo, j0 == 0, [&](uint32_t i) { return ct3 + (size_t)i * ct_lo; },
+                            [&](uint32_t i, uint32_t t) { return (const u64*)plan->h_d_w_ra[((size_t)l * n_ra + j0 + i) * taps + t]; },
+                            [&](uint32_t t) { return ct4 + ((size_t)l * taps + t) * ct_lo; });
+                if (rc != HE_OK) return rc;
+            }
             ctx->cnt.mac += (uint64_t)g * n_ca * taps;
         }
     }

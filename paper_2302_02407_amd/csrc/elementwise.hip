@@ -56,7 +56,9 @@ __global__ __launch_bounds__(EW_THREADS) void ptct_mac_kernel(u64* __restrict__ 
 }
 
 // acc (+)= sum_i ct_i * sigma_{g_i}(pt_i): the plaintext is permuted as it is read (a plaintext rotation fused into
-// the product), products summed in 128 bits and reduced once per 8 terms.  limb = blockIdx.y.
+// the product).  A thread owns an aligned pair of positions, which an automorphism takes from an aligned pair in order or
+// swapped, so every access is 16 bytes; four terms' operands are requested before the first is used (bound by reading
+// them).  Products in split sums, reduced once per 4 terms.  limb = blockIdx.y.
 #define MACROT_MAX 16
 struct MacRot {
     const u64* ct[MACROT_MAX];   // [2][n_limbs][N]
@@ -66,23 +68,46 @@ struct MacRot {
 };
 __global__ __launch_bounds__(EW_THREADS) void ptct_mac_rot_kernel(u64* __restrict__ acc, MacRot mr, const ModConst* mc, uint32_t logN,
                                                                   uint32_t n_limbs, int init) {
-    const uint32_t n = blockIdx.x * EW_THREADS + threadIdx.x;
+    const uint32_t n = (blockIdx.x * EW_THREADS + threadIdx.x) * 2;
+    if (n >> logN) return;
     const uint32_t limb = blockIdx.y;
     const ModConst m = mc[limb];
-    const size_t o0 = ((size_t)limb << logN) + n, o1 = ((size_t)(limb + n_limbs) << logN) + n;
-    u128 a0 = init ? 0 : acc[o0], a1 = init ? 0 : acc[o1];
-    for (uint32_t i = 0; i < mr.n; i++) {
-        if (i && (i & 7) == 0) {
-            a0 = barrett128(a0, m.q, m.mu, m.bits);
-            a1 = barrett128(a1, m.q, m.mu, m.bits);
-        }
-        const uint32_t g = mr.g[i];
-        const u64 p = mr.pt[i][((size_t)limb << logN) + (g == 1 ? n : galois_src(n, g, logN))];
-        a0 += (u128)mr.ct[i][o0] * p;
-        a1 += (u128)mr.ct[i][o1] * p;
+    const size_t lo = (size_t)limb << logN, o0 = lo + n, o1 = ((size_t)(limb + n_limbs) << logN) + n;
+    ulonglong2 r0 = make_ulonglong2(0, 0), r1 = r0;
+    if (!init) {
+        r0 = *reinterpret_cast<const ulonglong2*>(acc + o0);
+        r1 = *reinterpret_cast<const ulonglong2*>(acc + o1);
     }
-    acc[o0] = barrett128(a0, m.q, m.mu, m.bits);
-    acc[o1] = barrett128(a1, m.q, m.mu, m.bits);
+    for (uint32_t i0 = 0; i0 < mr.n; i0 += 4) {
+        ulonglong2 c0[4], c1[4], p[4];
+        uint32_t swp[4];
+#pragma unroll
+        for (uint32_t k = 0; k < 4; k++) {
+            const uint32_t i = i0 + k;
+            if (i < mr.n) {
+                const uint32_t g = mr.g[i], src = g == 1 ? n : galois_src(n, g, logN);
+                c0[k] = *reinterpret_cast<const ulonglong2*>(mr.ct[i] + o0);
+                c1[k] = *reinterpret_cast<const ulonglong2*>(mr.ct[i] + o1);
+                p[k] = *reinterpret_cast<const ulonglong2*>(mr.pt[i] + lo + (src & ~1u));
+                swp[k] = src & 1u;
+            }
+        }
+        SplitSum s[4] = {};
+#pragma unroll
+        for (uint32_t k = 0; k < 4; k++) {
+            if (i0 + k < mr.n) {
+                const u64 px = swp[k] ? p[k].y : p[k].x, py = swp[k] ? p[k].x : p[k].y;
+                split_mac(s[0], c0[k].x, px); split_mac(s[1], c0[k].y, py);
+                split_mac(s[2], c1[k].x, px); split_mac(s[3], c1[k].y, py);
+            }
+        }
+        r0.x = reduce_full<7>(r0.x + split_reduce(s[0], m), m.q, m.bits, m.rec);
+        r0.y = reduce_full<7>(r0.y + split_reduce(s[1], m), m.q, m.bits, m.rec);
+        r1.x = reduce_full<7>(r1.x + split_reduce(s[2], m), m.q, m.bits, m.rec);
+        r1.y = reduce_full<7>(r1.y + split_reduce(s[3], m), m.q, m.bits, m.rec);
+    }
+    *reinterpret_cast<ulonglong2*>(acc + o0) = r0;
+    *reinterpret_cast<ulonglong2*>(acc + o1) = r1;
 }
 
 __global__ __launch_bounds__(EW_THREADS) void add_kernel(const u64* a, const u64* b, u64* out, const ModConst* mc,
@@ -121,6 +146,35 @@ __global__ __launch_bounds__(EW_THREADS) void tensor_kernel(const u64* __restric
 int32_t launch_tensor(he_ctx* ctx, const u64* a, const u64* b, uint32_t level, u64* d) {
     dim3 grid(ctx->N / EW_THREADS, level + 1), block(EW_THREADS);
     hipLaunchKernelGGL(tensor_kernel, grid, block, 0, ctx->stream, a, b, d, ctx->d_mc, ctx->logN, level + 1);
+    HE_HIP(ctx, hipGetLastError());
+    return HE_OK;
+}
+
+// Tensor square of k*u for n ciphertexts that lie one after the other: with v_c = u_c * k[r],
+// d = (v_0^2, 2 v_0 v_1, v_1^2).  One pass instead of a scaling and a tensor product per ciphertext.
+// grid: (N/256, L1, n); u [n][2][L1][N], d [n][3][L1][N].
+struct LiftArgs {
+    u64 mul[HE_MAX_MODULI], mul_sh[HE_MAX_MODULI];
+};
+__global__ __launch_bounds__(EW_THREADS) void square_lift_kernel(const u64* __restrict__ u, u64* __restrict__ d, LiftArgs k, const ModConst* mc,
+                                                                 uint32_t logN, uint32_t L1) {
+    const uint32_t n = blockIdx.x * EW_THREADS + threadIdx.x, r = blockIdx.y;
+    const size_t pe = (size_t)L1 << logN, o = ((size_t)r << logN) + n;
+    const ModConst m = mc[r];
+    u += 2 * pe * blockIdx.z;
+    d += 3 * pe * blockIdx.z;
+    const u64 v0 = shoup_mul(u[o], k.mul[r], k.mul_sh[r], m.q), v1 = shoup_mul(u[pe + o], k.mul[r], k.mul_sh[r], m.q);
+    const u64 x = mulmod(v0, v1, m);
+    d[o] = mulmod(v0, v0, m);
+    d[pe + o] = addmod(x, x, m.q);
+    d[2 * pe + o] = mulmod(v1, v1, m);
+}
+
+int32_t launch_square_lift(he_ctx* ctx, const u64* u, uint32_t n, uint32_t level, const u64* mul, u64* d) {
+    LiftArgs k;
+    for (uint32_t r = 0; r <= level; r++) { k.mul[r] = mul[r]; k.mul_sh[r] = h_shoup(mul[r], ctx->mod[r]); }
+    hipLaunchKernelGGL(square_lift_kernel, dim3(ctx->N / EW_THREADS, level + 1, n), dim3(EW_THREADS), 0, ctx->stream, u, d, k, ctx->d_mc, ctx->logN,
+                       level + 1);
     HE_HIP(ctx, hipGetLastError());
     return HE_OK;
 }
@@ -242,7 +296,7 @@ int32_t he_ptct_mac_rot(he_ctx* ctx, uint64_t* d_acc, const uint64_t* const* h_d
         if ((a < c + 2 * pb && c < a + 2 * pb) || (a < p + pb && p < a + 2 * pb))
             return he_fail(ctx, HE_ERR_BADARG, "he_ptct_mac_rot: the accumulator overlaps operand %u", i);
     }
-    dim3 grid(ctx->N / EW_THREADS, level + 1), block(EW_THREADS);
+    dim3 grid((ctx->N + 2 * EW_THREADS - 1) / (2 * EW_THREADS), level + 1), block(EW_THREADS);
     if (n == 0 && init) {                                  // an empty sum: the accumulator is cleared
         MacRot mr = {};
         hipLaunchKernelGGL(ptct_mac_rot_kernel, grid, block, 0, ctx->stream, (u64*)d_acc, mr, ctx->d_mc, ctx->logN, level + 1, 1);

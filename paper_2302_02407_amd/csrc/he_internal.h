@@ -252,6 +252,7 @@ struct AffineConst {
     u64 mul[HE_MAX_MODULI], add[HE_MAX_MODULI];
 };
 int32_t launch_affine(he_ctx* ctx, const u64* ct, uint32_t level, const AffineConst& k, u64* out);   // out may alias ct
+int32_t launch_square_lift(he_ctx* ctx, const u64* u, uint32_t n, uint32_t level, const u64* mul, u64* d);   // tensor squares of mul*u, n ciphertexts
 int32_t launch_tensor(he_ctx* ctx, const u64* a, const u64* b, uint32_t level, u64* d);   // d = [d0][d1][d2], each [level+1][N]
 int32_t launch_automorph_coef(he_ctx* ctx, const u64* in, u64* out, const uint32_t* mod_idx, uint32_t n, uint32_t g);
 

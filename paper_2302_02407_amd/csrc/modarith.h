@@ -92,3 +92,38 @@ __device__ __forceinline__ u64 addmod(u64 a, u64 b, u64 q) { return csub(a + b, 
 __device__ __forceinline__ u64 submod(u64 a, u64 b, u64 q) { return a >= b ? a - b : a + q - b; }
 
 __device__ __forceinline__ u64 mulmod(u64 a, u64 b, const ModConst& m) { return barrett128((u128)a * b, m.q, m.mu, m.bits); }
+
+// Sum of products of values below 2^60 (or below 2^61 with a factor that small primes keep low), halves of 30 bits summed
+// in three 64-bit words that the multiply-adds feed directly: 4 instructions per product besides the splitting, where a
+// 128-bit sum takes 14.  a0 and a2 take below 2^60 per product of canonical residues, a1 below 2^61: 7 products fit.
+#define SPLIT_H 30
+#define SPLIT_MAX 7
+struct SplitSum {
+    u64 a0, a1, a2;
+};
+__device__ __forceinline__ void split_mac(SplitSum& s, u64 d, u64 k) {
+    const uint32_t M = (1u << SPLIT_H) - 1;
+    const uint32_t d0 = (uint32_t)d & M, d1 = (uint32_t)(d >> SPLIT_H), k0 = (uint32_t)k & M, k1 = (uint32_t)(k >> SPLIT_H);
+    s.a0 += (u64)d0 * k0;
+    s.a1 += (u64)d0 * k1;
+    s.a1 += (u64)d1 * k0;
+    s.a2 += (u64)d1 * k1;
+}
+__device__ __forceinline__ u128 split_value(const SplitSum& s) {
+    return (u128)s.a0 + ((u128)s.a1 << SPLIT_H) + ((u128)s.a2 << (2 * SPLIT_H));
+}
+// congruent to the sum, below 5q
+__device__ __forceinline__ u64 split_reduce(const SplitSum& s, const ModConst& m) { return barrett128_lazy(split_value(s), m.q, m.mu, m.bits); }
+
+// v mod q for v below 2^LOGV * 2^bits (and below 2^64): the quotient from the top 32 bits of v and rec =
+// floor(2^(bits+31) / q), at most one too small.  The lazy form stops before the correction: below 2q.
+template <int LOGV>
+__device__ __forceinline__ u64 reduce_lazy(u64 v, u64 q, uint32_t bits, uint32_t rec) {
+    const uint32_t sh = bits > 32 - LOGV ? bits - (32 - LOGV) : 0;
+    const uint32_t qh = __umulhi((uint32_t)(v >> sh), rec) >> (bits - 1 - sh);
+    return v - (u64)qh * q;
+}
+template <int LOGV>
+__device__ __forceinline__ u64 reduce_full(u64 v, u64 q, uint32_t bits, uint32_t rec) {
+    return csub(reduce_lazy<LOGV>(v, q, bits, rec), q);
+}

@@ -235,26 +235,8 @@ __global__ __launch_bounds__(P2_THREADS, 4) void ntt_col_inv_kernel(P2Args a, Li
 // sum over the digits of digit_j (gathered by the Galois map) * key_j for adjacent pairs of positions.  An aligned pair of
 // positions comes from an aligned pair, in order or swapped, so a digit's two values are one 16-byte load; they are
 // multiplied in the order they arrive ("slots": slot s belongs to output position pos + (s ^ swap)) and the key is read in
-// that order.  Values are split in halves of 30 bits and their products summed in three 64-bit words that the
-// multiply-adds feed directly: 4 instructions per product, where a 128-bit sum takes 14.  Digits are below 2q for moduli
-// of at most 57 bits and canonical above, keys canonical: a0 and a2 take below 2^60 per product, a1 below 2^61 (wide) or
-// 2^59 (narrow), so 7 (wide) or 15 products fit.
-#define IP_H 30
-struct IpSum {
-    u64 a0, a1, a2;
-};
-__device__ __forceinline__ void ip_mac(IpSum& s, u64 d, u64 k) {
-    const uint32_t M = (1u << IP_H) - 1;
-    const uint32_t d0 = (uint32_t)d & M, d1 = (uint32_t)(d >> IP_H), k0 = (uint32_t)k & M, k1 = (uint32_t)(k >> IP_H);
-    s.a0 += (u64)d0 * k0;
-    s.a1 += (u64)d0 * k1;
-    s.a1 += (u64)d1 * k0;
-    s.a2 += (u64)d1 * k1;
-}
-__device__ __forceinline__ u128 ip_value(const IpSum& s) { return (u128)s.a0 + ((u128)s.a1 << IP_H) + ((u128)s.a2 << (2 * IP_H)); }
-// below 5q
-__device__ __forceinline__ u64 ip_reduce(const IpSum& s, const ModConst& m) { return barrett128_lazy(ip_value(s), m.q, m.mu, m.bits); }
-
+// that order.  Products go into split sums (modarith.h).  Digits are below 2q for moduli of at most 57 bits and canonical
+// above, keys canonical: SPLIT_MAX products fit, 15 for the narrow moduli.
 // What one (polynomial, key) term contributes to a limb: base pointers of the digits and keys of this limb.
 struct IpTerm {
     const u64 *raised, *own, *key;                       // own: digit own_j's limb, which is not materialised in raised
@@ -294,14 +276,14 @@ __device__ __forceinline__ void ip_request(IpLoad<NJ>& L, const IpTerm& tm, uint
     }
 }
 template <int NJ>
-__device__ __forceinline__ void ip_consume(IpSum (&s)[4], const IpLoad<NJ>& L, uint32_t nj) {
+__device__ __forceinline__ void ip_consume(SplitSum (&s)[4], const IpLoad<NJ>& L, uint32_t nj) {
 #pragma unroll
     for (int jj = 0; jj < NJ; jj++) {
         if ((uint32_t)jj < nj) {
 #pragma unroll
             for (int p = 0; p < 2; p++) {
-                ip_mac(s[2 * p], L.d[jj][p].x, L.k[jj][p][0]);
-                ip_mac(s[2 * p + 1], L.d[jj][p].y, L.k[jj][p][1]);
+                split_mac(s[2 * p], L.d[jj][p].x, L.k[jj][p][0]);
+                split_mac(s[2 * p + 1], L.d[jj][p].y, L.k[jj][p][1]);
             }
         }
     }
@@ -332,11 +314,11 @@ __device__ __forceinline__ void ip_row(const IpTerm& tm, uint32_t beta, uint32_t
                 ip_request(nxt, tm, 0, NJ, pos + 64, nsrc, nswp, dig_stride, key_stride);
             }
             SCHED_FENCE();
-            IpSum s[4] = {};
+            SplitSum s[4] = {};
             ip_consume(s, cur, NJ);
             u64 v[4];
 #pragma unroll
-            for (int i = 0; i < 4; i++) v[i] = ip_reduce(s[i], m);
+            for (int i = 0; i < 4; i++) v[i] = split_reduce(s[i], m);
             emit(ch, pos, v, src, swp);
             if (ch < 3) {
                 cur = nxt;
@@ -349,7 +331,7 @@ __device__ __forceinline__ void ip_row(const IpTerm& tm, uint32_t beta, uint32_t
         for (int ch = 0; ch < 4; ch++) {
             const uint32_t pos = row0 + 2 * t + 64 * ch;
             ip_map(src, swp, pos, tm.g, logN);
-            IpSum s[4] = {};
+            SplitSum s[4] = {};
             u64 v[4] = {0, 0, 0, 0};
             for (uint32_t j0 = 0; j0 < beta; j0 += NJ) {
                 IpLoad<NJ> L;
@@ -357,12 +339,12 @@ __device__ __forceinline__ void ip_row(const IpTerm& tm, uint32_t beta, uint32_t
                 ip_request(L, tm, j0, nj, pos, src, swp, dig_stride, key_stride);
                 if (j0 == 6) {                           // seven products at most in one sum
 #pragma unroll
-                    for (int i = 0; i < 4; i++) { v[i] = ip_reduce(s[i], m); s[i] = IpSum{0, 0, 0}; }
+                    for (int i = 0; i < 4; i++) { v[i] = split_reduce(s[i], m); s[i] = SplitSum{0, 0, 0}; }
                 }
                 ip_consume(s, L, nj);
             }
 #pragma unroll
-            for (int i = 0; i < 4; i++) v[i] = beta > 6 ? reduce_lazy<7>(v[i] + ip_reduce(s[i], m), m.q, m.bits, m.rec) : ip_reduce(s[i], m);
+            for (int i = 0; i < 4; i++) v[i] = beta > 6 ? reduce_lazy<7>(v[i] + split_reduce(s[i], m), m.q, m.bits, m.rec) : split_reduce(s[i], m);
             emit(ch, pos, v, src, swp);
         }
     }
@@ -371,7 +353,7 @@ __device__ __forceinline__ void ip_row(const IpTerm& tm, uint32_t beta, uint32_t
 template <class Term, class Emit>
 __device__ __forceinline__ void ip_row_terms(Term&& term, uint32_t n_terms, uint32_t beta, uint32_t row0, uint32_t t, uint32_t logN,
                                              size_t dig_stride, size_t key_stride, const ModConst& m, Emit&& emit) {
-    const uint32_t most = m.bits > 57 ? 7 : 15;
+    const uint32_t most = m.bits > 57 ? SPLIT_MAX : 15;
 #pragma unroll 1
     for (int ch = 0; ch < 4; ch++) {
         const uint32_t pos = row0 + 2 * t + 64 * ch;
@@ -380,14 +362,14 @@ __device__ __forceinline__ void ip_row_terms(Term&& term, uint32_t n_terms, uint
             const IpTerm tm = term(i);
             uint32_t src[2], swp[2], pending = 0;
             ip_map(src, swp, pos, tm.g, logN);
-            IpSum s[4] = {};
+            SplitSum s[4] = {};
             auto flush = [&]() {
 #pragma unroll
                 for (int p = 0; p < 2; p++) {
-                    const ulonglong2 v = ip_order(ip_reduce(s[2 * p], m), ip_reduce(s[2 * p + 1], m), swp[p]);
+                    const ulonglong2 v = ip_order(split_reduce(s[2 * p], m), split_reduce(s[2 * p + 1], m), swp[p]);
                     tot[2 * p] = reduce_lazy<7>(tot[2 * p] + v.x, m.q, m.bits, m.rec);
                     tot[2 * p + 1] = reduce_lazy<7>(tot[2 * p + 1] + v.y, m.q, m.bits, m.rec);
-                    s[2 * p] = s[2 * p + 1] = IpSum{0, 0, 0};
+                    s[2 * p] = s[2 * p + 1] = SplitSum{0, 0, 0};
                 }
                 pending = 0;
             };

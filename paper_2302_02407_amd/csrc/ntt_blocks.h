@@ -144,19 +144,6 @@ __device__ __forceinline__ void inv_block2(u64 (&x)[4], const ulonglong2* tw, ui
     inv_block2_r(x, r, q);
 }
 
-// v mod q for v below 2^LOGV * 2^bits (and below 2^64): the quotient from the top 32 bits of v and rec =
-// floor(2^(bits+31) / q), at most one too small.  The lazy form stops before the correction: below 2q.
-template <int LOGV>
-__device__ __forceinline__ u64 reduce_lazy(u64 v, u64 q, uint32_t bits, uint32_t rec) {
-    const uint32_t sh = bits > 32 - LOGV ? bits - (32 - LOGV) : 0;
-    const uint32_t qh = __umulhi((uint32_t)(v >> sh), rec) >> (bits - 1 - sh);
-    return v - (u64)qh * q;
-}
-template <int LOGV>
-__device__ __forceinline__ u64 reduce_full(u64 v, u64 q, uint32_t bits, uint32_t rec) {
-    return csub(reduce_lazy<LOGV>(v, q, bits, rec), q);
-}
-
 // lanes of one wavefront exchange through LDS: its own accesses are in order, the compiler has to keep them so
 __device__ __forceinline__ void wave_exchange() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
