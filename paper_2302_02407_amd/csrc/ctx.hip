@@ -130,6 +130,7 @@ int32_t he_ctx_create(he_ctx** out, uint32_t logN, const uint64_t* h_q, uint32_t
     } own{c};
     c->logN = logN; c->N = N; c->nq = nq; c->np = np; c->dnum = dnum; c->M = M;
     c->alpha = (nq + dnum - 1) / dnum;
+    c->srf = logN <= 12;
     c->stream = (hipStream_t)hip_stream;
     c->d_mc = nullptr; c->d_tw = c->d_itw = nullptr;
     c->d_ws = nullptr; c->ws_bytes = 0;
@@ -175,6 +176,8 @@ int32_t he_ctx_create(he_ctx** out, uint32_t logN, const uint64_t* h_q, uint32_t
         mc.ninv_w_sh = h_shoup(mc.ninv_w, m);
         mc.one_sh = h_shoup(1, m);
         mc.rec = (uint32_t)(((u128)1 << (mc.bits + 31)) / m);
+        mc.qinv = 1.0 / (double)m;
+        c->srf = c->srf && mc.bits <= HE_FP64_BITS;
     }
     size_t tb = (size_t)M * N * sizeof(ulonglong2);
     hipError_t e = hipSuccess;

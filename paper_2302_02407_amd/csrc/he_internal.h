@@ -27,7 +27,10 @@ struct ModConst {
     u64 one_sh;     // floor(2^64 / q): Shoup companion of the constant 1 (a quotient step for any 64-bit value)
     uint32_t bits;  // bit length of q
     uint32_t rec;   // floor(2^(bits+31) / q): 32-bit reciprocal for small quotients
+    double qinv;    // 1 / q
 };
+
+#define HE_FP64_BITS 45   // products modulo such primes are exact in FP64 with the ranges smallring.hip keeps
 
 // Modulus index of each limb of a launch, passed by value in the kernel arguments.
 struct LimbList {
@@ -52,6 +55,7 @@ struct ProfSpan {
 
 struct he_ctx {
     uint32_t logN, N, nq, np, dnum, alpha, M; // M = nq + np
+    bool srf;          // small ring whose moduli all have at most HE_FP64_BITS bits: FP64 kernels (smallring.hip)
     hipStream_t stream;
     int device;
     u64 mod[HE_MAX_MODULI];

@@ -366,8 +366,319 @@ __global__ __launch_bounds__(SR_THREADS) void sr_rescale_kernel(SrRescaleArgs a,
     }
 }
 
+// ---------------------------------------------------------------- moduli of at most 45 bits: FP64
+// One double holds any value below 2^53, so a twiddle product modulo q is h = y*w, l = y*w - h (exact by FMA), b = h/q
+// rounded to an integer, d = (h - b*q) + l: seven FP64 instructions (16 multiply-adds in 64-bit integers), all at full rate
+// and five deep where the integer chain is fifteen deep: these launches run two wavefronts per SIMD at most, so the
+// depth is what they wait for.  Every step is exact on integers: h - b*q is a multiple of 1 below 2^53, and only the choice of b depends on a rounding.
+//   With |y| < 2^49 and moduli below 2^45 the quotient is within 1/2 + 2^-3 of h/q, so |d| < 0.63 q.
+//   Forward: a stage adds 0.63 q; inputs below 2q end below 10q < 2^49.  Inverse: three stages turn values below q into
+//   sums below 8q < 2^48, then the sums are brought below 0.63 q again.
+// A limb is 8 points per thread in register blocks of 3 stages (512 threads at N = 2^12: 2 wavefronts per SIMD, 256
+// registers, nothing spilled).  Block b of thread t = G*R + r, R = N/8^(b+1), holds points G*8R + k*R + r; the last block, where
+// LN is no multiple of 3, the 8 points 8t + k and only its last stages.  From block 1 on a wavefront holds the same
+// 512 points in every block, so one barrier per transform is left; transformed limbs are read and written at 8t + k.
+// N = 2^12, one 40-bit limb per digit, one special prime: ModUp 20 -> 10.5 us, ModDown 29 -> 18.4, rescale 20 -> 10.2 against the
+// integer kernels above; what is left is two memory round trips, two transforms of about 2.5 us and the store.
+#pragma clang fp contract(off)
+#define SRF_LDS(LN) ((1 << (LN)) + (1 << ((LN) - 3)))
+#define SRF_DIG 3                  // digits whose operands are requested together
+#define EACH8(k) _Pragma("unroll") for (int k = 0; k < 8; k++)
+
+__device__ __forceinline__ void load8(u64 (&v)[8], const u64* __restrict__ p) {
+#pragma unroll
+    for (int k = 0; k < 8; k += 2) { const ulonglong2 u = *(const ulonglong2*)(p + k); v[k] = u.x; v[k + 1] = u.y; }
+}
+__device__ __forceinline__ void store8(u64* p, const u64 (&v)[8]) {
+#pragma unroll
+    for (int k = 0; k < 8; k += 2) *(ulonglong2*)(p + k) = make_ulonglong2(v[k], v[k + 1]);
+}
+struct FMod { double q, qi; u64 n; };
+__device__ __forceinline__ FMod f_mod(const ModConst& m) { return {(double)m.q, m.qinv, m.q}; }
+__device__ __forceinline__ double f_of(u64 v) { return __longlong_as_double((long long)(v | 0x4330000000000000ull)) - 4503599627370496.0; }   // v < 2^52
+__device__ __forceinline__ double f_round(double v) { return (v + 6755399441055744.0) - 6755399441055744.0; }                              // |v| < 2^51
+__device__ __forceinline__ double f_mul(double y, double w, const FMod& m) {
+    const double h = y * w, l = __builtin_fma(y, w, -h);
+    const double b = __builtin_fma(h, m.qi, 6755399441055744.0) - 6755399441055744.0;
+    return __builtin_fma(-b, m.q, h) + l;
+}
+__device__ __forceinline__ double f_red(double x, const FMod& m) { return __builtin_fma(-f_round(x * m.qi), m.q, x); }
+__device__ __forceinline__ u64 f_canon(double d, const FMod& m) {                      // |d| < q
+    const long long i = __double_as_longlong(d + 6755399441055744.0) - 0x4338000000000000ll;
+    return (u64)(i + ((i >> 63) & (long long)m.n));
+}
+__device__ __forceinline__ double f_nonneg(double d, const FMod& m) { return d < 0 ? d + m.q : d; }
+
+template <int LN>
+struct Srf {
+    static constexpr uint32_t N = 1u << LN, T = N / 8;
+    static constexpr int NB = (LN + 2) / 3, U0 = 3 * NB - LN;      // blocks; first stage of the last one
+    static __device__ __forceinline__ uint32_t word(uint32_t e) { return e + (e >> 3); }
+    static constexpr uint32_t R(int b) { return b + 1 < NB ? N >> (3 * b + 3) : 1; }
+    static __device__ __forceinline__ uint32_t pos(int b, uint32_t t, uint32_t k) { return word(t / R(b) * (8 * R(b)) + k * R(b) + t % R(b)); }
+    static constexpr int s0(int b) { return b + 1 < NB ? 3 * b : LN - 3; }
+    static constexpr int u0(int b) { return b + 1 < NB ? 0 : U0; }
+};
+// Factors of a transform's blocks 1 ... (block 0's are the same for every thread: scalar loads at their use).
+template <int LN>
+struct SrfTw { u64 w[Srf<LN>::NB][7]; };
+template <int LN, int B>
+__device__ __forceinline__ void srf_tw(u64 (&w)[7], const ulonglong2* __restrict__ tw, uint32_t t) {
+    const uint32_t G = t / Srf<LN>::R(B);
+#pragma unroll
+    for (int u = Srf<LN>::u0(B); u < 3; u++)
+#pragma unroll
+        for (int g = 0; g < (1 << u); g++) w[(1 << u) - 1 + g] = tw[(1u << (Srf<LN>::s0(B) + u)) + (G << u) + g].x;
+}
+template <int LN, int B = 1>
+__device__ __forceinline__ void srf_tw_all(SrfTw<LN>& w, const ulonglong2* __restrict__ tw, uint32_t t) {
+    srf_tw<LN, B>(w.w[B], tw, t);
+    if constexpr (B + 1 < Srf<LN>::NB) srf_tw_all<LN, B + 1>(w, tw, t);
+}
+// block B's points -> block D's
+template <int LN, int B, int D>
+__device__ __forceinline__ void srf_move(double (&x)[8], double* sm, uint32_t t) {
+    EACH8(k) sm[Srf<LN>::pos(B, t, k)] = x[k];
+    if (B == 0 || D == 0) __syncthreads();
+    else wave_exchange();
+    EACH8(k) x[k] = sm[Srf<LN>::pos(D, t, k)];
+}
+// In: strided points (block 0's) below 2q in size.  Out: points 8t + k, not reduced (below 10q).
+template <int LN, int B = 0>
+__device__ __forceinline__ void srf_fwd(double (&x)[8], SrfTw<LN>& tw, const ulonglong2* __restrict__ table, double* sm, uint32_t t, const FMod& m) {
+    if (B == 0) srf_tw<LN, 0>(tw.w[0], table, 0);
+    double w[7];
+#pragma unroll
+    for (int i = (1 << Srf<LN>::u0(B)) - 1; i < 7; i++) w[i] = f_of(tw.w[B][i]);
+#pragma unroll
+    for (int u = Srf<LN>::u0(B); u < 3; u++) {
+        const int dist = 4 >> u;
+        double d[4];
+#pragma unroll
+        for (int p = 0; p < 4; p++) d[p] = f_mul(x[p / dist * 2 * dist + p % dist + dist], w[(1 << u) - 1 + p / dist], m);
+#pragma unroll
+        for (int p = 0; p < 4; p++) {
+            const int a = p / dist * 2 * dist + p % dist;
+            x[a + dist] = x[a] - d[p];
+            x[a] = x[a] + d[p];
+        }
+    }
+    if constexpr (B + 1 < Srf<LN>::NB) {
+        srf_move<LN, B, B + 1>(x, sm, t);
+        srf_fwd<LN, B + 1>(x, tw, table, sm, t, m);
+    }
+}
+// In: points 8t + k below q in size.  Out: strided points times scale (which carries N^-1), in [0, q).  The factors of the
+// transform after this one (next) are requested as soon as this one has used its own.
+template <int LN, int B = Srf<LN>::NB - 1>
+__device__ __forceinline__ void srf_inv(double (&x)[8], SrfTw<LN>& tw, const ulonglong2* __restrict__ table, const ulonglong2* __restrict__ next, double scale,
+                                        double* sm, uint32_t t, const FMod& m) {
+    if (B == 0) srf_tw<LN, 0>(tw.w[0], table, 0);
+    double w[7];
+#pragma unroll
+    for (int i = (1 << Srf<LN>::u0(B)) - 1; i < 7; i++) w[i] = f_of(tw.w[B][i]);
+    if (B > 0) srf_tw<LN, B>(tw.w[B], next, t);
+#pragma unroll
+    for (int u = 2; u >= Srf<LN>::u0(B); u--) {
+        const int dist = 4 >> u;
+#pragma unroll
+        for (int p = 0; p < 4; p++) {
+            const int a = p / dist * 2 * dist + p % dist;
+            const double d = x[a] - x[a + dist];
+            x[a] = x[a] + x[a + dist];
+            x[a + dist] = d;
+        }
+#pragma unroll
+        for (int p = 0; p < 4; p++) {
+            const int a = p / dist * 2 * dist + p % dist + dist;
+            x[a] = f_mul(x[a], w[(1 << u) - 1 + p / dist], m);
+        }
+    }
+    if constexpr (B > 0) {
+        const int dist = 4 >> Srf<LN>::u0(B);
+#pragma unroll
+        for (int p = 0; p < 4; p++) { const int a = p / dist * 2 * dist + p % dist; x[a] = f_red(x[a], m); }
+        srf_move<LN, B, B - 1>(x, sm, t);
+        srf_inv<LN, B - 1>(x, tw, table, next, scale, sm, t, m);
+    } else {
+        EACH8(k) x[k] = f_nonneg(f_mul(x[k], scale, m), m);
+    }
+}
+// sum of x_i * h_i over the limbs of a conversion: the last one's digits in x, the others in keep.  Below 2q in size.
+template <int LN>
+__device__ __forceinline__ void srf_convert(double (&x)[8], const double* keep, const u64* h, uint32_t n, uint32_t t, const FMod& m) {
+    double s[8];
+    const double hl = f_of(h[n - 1]);
+    EACH8(k) s[k] = f_mul(x[k], hl, m);
+    for (uint32_t i = 0; i + 1 < n; i++) {
+        const double hi = f_of(h[i]);
+        EACH8(k) s[k] += f_mul(keep[i * Srf<LN>::N + t + k * Srf<LN>::T], hi, m);
+    }
+    EACH8(k) x[k] = n > 1 ? f_red(s[k], m) : s[k];
+}
+
+template <int LN>
+__global__ __launch_bounds__(Srf<LN>::T, 2) void srf_modup_kernel(SrUpArgs a, SrTables tb) {
+    using G = Srf<LN>;
+    __shared__ double sm[SRF_LDS(LN)], keep[(SR_MAX_SRC - 1) * G::N];
+    const uint32_t t = threadIdx.x;
+    const uint32_t s = blockIdx.x / a.n_out, o = blockIdx.x % a.n_out;
+    const uint32_t j = a.oj[o], r = a.orr[o];
+    const uint32_t lo = j * a.alpha, sz = min(a.alpha, a.L1 - lo);
+    const uint32_t mr = r <= a.level ? r : a.nq + (r - a.level - 1);
+    const u64* c1 = a.c1[s] + ((size_t)lo << LN) + 8 * t;
+    const ulonglong2 *itw = tb.itw + ((size_t)lo << LN), *ftw = tb.tw + ((size_t)mr << LN);
+    u64 in[8];
+    SrfTw<LN> w;
+    load8(in, c1);
+    srf_tw_all<LN>(w, itw, t);
+    const FMod m = f_mod(tb.mc[mr]);
+    const u64* hat = a.hat + ((size_t)(j * a.alpha + (sz - 1)) * a.M + mr) * a.aw;
+    double x[8];
+    for (uint32_t i = 0; i < sz; i++) {
+        const bool last = i + 1 == sz;
+        EACH8(k) x[k] = f_of(in[k]);
+        if (!last) load8(in, c1 += G::N);
+        if (i) __syncthreads();                    // the words of the transform before have been read
+        srf_inv<LN>(x, w, itw, last ? ftw : itw + G::N, f_of(a.scale[lo + i]), sm, t, f_mod(tb.mc[lo + i]));
+        itw += G::N;
+        if (!last) { EACH8(k) keep[i * G::N + t + k * G::T] = x[k]; }
+    }
+    srf_convert<LN>(x, keep, hat, sz, t, m);
+    srf_fwd<LN>(x, w, ftw, sm, t, m);
+    u64* dst = a.raised + ((size_t)((s * a.beta + j) * a.R + r) << LN) + 8 * t;
+    EACH8(k) in[k] = f_canon(f_red(x[k], m), m);
+    store8(dst, in);
+}
+
+// One limb's inner product at points 8t + k.  The operands of the first SRF_DIG digits are requested together, and a transform
+// ahead of their use.
+struct SrfOps { u64 d[SRF_DIG][8], kv[SRF_DIG][8]; };
+struct SrfInner {
+    const u64 *raised, *own, *key;     // this limb's digits (own: of digit own_j, null elsewhere) and key rows
+    uint32_t own_j;
+};
+__device__ __forceinline__ void srf_digit(u64 (&d)[8], u64 (&kv)[8], const SrfInner& in, uint32_t j, size_t ds, size_t ks, const uint32_t (&src)[8], uint32_t t) {
+    const u64* p = j == in.own_j ? in.own : in.raised + j * ds;
+    EACH8(k) d[k] = p[src[k]];
+    load8(kv, in.key + j * ks + 8 * t);
+}
+__device__ __forceinline__ void srf_request(SrfOps& o, const SrfInner& in, uint32_t beta, size_t ds, size_t ks, const uint32_t (&src)[8], uint32_t t) {
+#pragma unroll
+    for (uint32_t j = 0; j < SRF_DIG; j++)
+        if (j < beta) srf_digit(o.d[j], o.kv[j], in, j, ds, ks, src, t);
+}
+// |result| < q; o holds the first SRF_DIG digits
+__device__ __forceinline__ void srf_inner(double (&out)[8], const SrfOps& o, const SrfInner& in, uint32_t beta, size_t ds, size_t ks,
+                                          const uint32_t (&src)[8], uint32_t t, const FMod& m) {
+    EACH8(k) out[k] = f_mul(f_of(o.d[0][k]), f_of(o.kv[0][k]), m);
+#pragma unroll
+    for (uint32_t j = 1; j < SRF_DIG; j++)
+        if (j < beta) { EACH8(k) out[k] += f_mul(f_of(o.d[j][k]), f_of(o.kv[j][k]), m); }
+    for (uint32_t j = SRF_DIG; j < beta; j++) {
+        u64 d[8], kv[8];
+        srf_digit(d, kv, in, j, ds, ks, src, t);
+        EACH8(k) out[k] += f_mul(f_of(d[k]), f_of(kv[k]), m);
+    }
+    EACH8(k) out[k] = f_red(out[k], m);
+}
+
+template <int LN>
+__global__ __launch_bounds__(Srf<LN>::T, 2) void srf_moddown_kernel(ModDownEpilogue ep, SrDownArgs a, SrTables tb) {
+    using G = Srf<LN>;
+    __shared__ double sm[SRF_LDS(LN)], keep[(SR_MAX_SRC - 1) * G::N];
+    const uint32_t L1 = ep.L1, R = ep.R, beta = ep.beta, t = threadIdx.x;
+    const uint32_t pc = blockIdx.x / L1, r = blockIdx.x - pc * L1, job = pc >> 1, comp = pc & 1u;
+    const uint32_t g = ep.g[job];
+    const size_t ds = (size_t)R << LN, ks = (size_t)(2 * ep.M) << LN, ro = (size_t)r << LN;
+    const u64* raised = ep.raised[job];
+    const u64* evk = ep.evk[job] + ((size_t)(comp * ep.M) << LN);
+    const ulonglong2 *itw = tb.itw + ((size_t)a.nq << LN), *ftw = tb.tw + ro;
+    uint32_t src[8];
+    EACH8(k) src[k] = galois_src_sr(8 * t + k, g, LN);
+    SrfTw<LN> w;
+    SrfOps o;
+    SrfInner in = {raised + ((size_t)L1 << LN), nullptr, evk + ((size_t)a.nq << LN), 0xFFFFFFFFu};
+    srf_request(o, in, beta, ds, ks, src, t);
+    srf_tw_all<LN>(w, itw, t);
+    const FMod m = f_mod(tb.mc[r]);
+    double x[8];
+    for (uint32_t i = 0; i < a.k; i++) {
+        const bool last = i + 1 == a.k;
+        const FMod mp = f_mod(tb.mc[a.nq + i]);
+        srf_inner(x, o, in, beta, ds, ks, src, t, mp);
+        // next: another special-prime limb, or after them limb r
+        if (last) in = {raised + ro, ep.own[job] + ro, evk + ro, r / ep.alpha};
+        else { in.raised += G::N; in.key += G::N; }
+        srf_request(o, in, beta, ds, ks, src, t);
+        if (i) __syncthreads();
+        srf_inv<LN>(x, w, itw, last ? ftw : itw + G::N, f_of(a.scale[i]), sm, t, mp);
+        itw += G::N;
+        if (!last) { EACH8(k) keep[i * G::N + t + k * G::T] = x[k]; }
+    }
+    srf_convert<LN>(x, keep, a.dn_hat + (size_t)r * a.pw, a.k, t, m);
+    // the addends travel while the forward transform runs
+    const u64* c0 = comp == 0 ? ep.c0[job] : nullptr;
+    const u64* self = comp ? ep.self1[job] : ep.self0[job];
+    double aq[8];
+    srf_inner(aq, o, in, beta, ds, ks, src, t, m);
+    u64 add0[8], add1[8];
+    EACH8(k) add0[k] = add1[k] = 0;
+    if (c0) { EACH8(k) add0[k] = c0[ro + src[k]]; }
+    if (self) load8(add1, self + ro + 8 * t);
+    srf_fwd<LN>(x, w, ftw, sm, t, m);
+    u64* out = (comp ? ep.out1[job] : ep.out0[job]) + ro + 8 * t;
+    const double pinv = f_of(ep.pinv[r]);
+    EACH8(k) {
+        const double v = f_mul(aq[k] - x[k], pinv, m) + (f_of(add0[k]) + f_of(add1[k]));     // below 3q in size
+        add0[k] = f_canon(f_red(v, m), m);
+    }
+    store8(out, add0);
+}
+
+template <int LN>
+__global__ __launch_bounds__(Srf<LN>::T, 2) void srf_rescale_kernel(SrRescaleArgs a, SrTables tb) {
+    using G = Srf<LN>;
+    __shared__ double sm[SRF_LDS(LN)];
+    const uint32_t level = a.level, t = threadIdx.x;
+    const uint32_t jc = blockIdx.x / level, r = blockIdx.x - jc * level, job = jc >> 1, comp = jc & 1u;
+    const u64* top = a.ct[job] + ((size_t)(comp * (level + 1) + level) << LN) + 8 * t;
+    const u64* in = a.ct[job] + ((size_t)(comp * (level + 1) + r) << LN) + 8 * t;
+    const ulonglong2 *itw = tb.itw + ((size_t)level << LN), *ftw = tb.tw + ((size_t)r << LN);
+    u64 tp[8], cr[8];
+    SrfTw<LN> w;
+    load8(tp, top);
+    srf_tw_all<LN>(w, itw, t);
+    load8(cr, in);
+    const FMod ml = f_mod(tb.mc[level]), m = f_mod(tb.mc[r]);
+    const double qlinv = f_of(a.qlinv[r]), h = f_of(ml.n >> 1);
+    double x[8];
+    EACH8(k) x[k] = f_of(tp[k]);
+    srf_inv<LN>(x, w, itw, ftw, f_of(tb.mc[level].ninv), sm, t, ml);
+    EACH8(k) {                                       // (h mod q_r) - ((x + h mod q_l) mod q_r), below 2q_r in size
+        const double v = x[k] + h;
+        x[k] = f_red(h, m) - f_red(v < ml.q ? v : v - ml.q, m);
+    }
+    srf_fwd<LN>(x, w, ftw, sm, t, m);
+    u64* out = a.out[job] + ((size_t)(comp * level + r) << LN) + 8 * t;
+    EACH8(k) cr[k] = f_canon(f_mul(f_of(cr[k]) + x[k], qlinv, m), m);
+    store8(out, cr);
+}
+#pragma clang fp contract(on)
+
 // ---------------------------------------------------------------- host
 static SrTables sr_tables(const he_ctx* c) { return {c->d_mc, c->d_tw, c->d_itw, c->logN}; }
+
+// FP64 kernels where every modulus of the context allows them (their values stay exact up to 45 bits), else the integer ones
+#define SR_LAUNCH(NAME, GRID, ...)                                                                                             \
+    do {                                                                                                                       \
+        if (!c->srf) hipLaunchKernelGGL(sr_##NAME, GRID, dim3(SR_THREADS), 0, c->stream, __VA_ARGS__);                         \
+        else if (c->logN == 12) hipLaunchKernelGGL(srf_##NAME<12>, GRID, dim3(Srf<12>::T), 0, c->stream, __VA_ARGS__);         \
+        else if (c->logN == 11) hipLaunchKernelGGL(srf_##NAME<11>, GRID, dim3(Srf<11>::T), 0, c->stream, __VA_ARGS__);         \
+        else if (c->logN == 10) hipLaunchKernelGGL(srf_##NAME<10>, GRID, dim3(Srf<10>::T), 0, c->stream, __VA_ARGS__);         \
+        else if (c->logN == 9) hipLaunchKernelGGL(srf_##NAME<9>, GRID, dim3(Srf<9>::T), 0, c->stream, __VA_ARGS__);            \
+        else hipLaunchKernelGGL(srf_##NAME<8>, GRID, dim3(Srf<8>::T), 0, c->stream, __VA_ARGS__);                              \
+    } while (0)
 
 bool small_ring_path(const he_ctx* c, uint32_t level) {
     const uint32_t beta = (level + c->alpha) / c->alpha;
@@ -394,7 +705,7 @@ int32_t sr_modup(he_ctx* c, const KsSrc* srcs, uint32_t cb, uint32_t level, u64*
             a.oj[a.n_out] = (uint8_t)j; a.orr[a.n_out] = (uint8_t)r; a.n_out++;
         }
     }
-    hipLaunchKernelGGL(sr_modup_kernel, dim3(cb * a.n_out), dim3(SR_THREADS), 0, c->stream, a, sr_tables(c));
+    SR_LAUNCH(modup_kernel, dim3(cb * a.n_out), a, sr_tables(c));
     HE_HIP(c, hipGetLastError());
     // logical transform counts (each work group repeats the inverse transforms of its digit)
     c->cnt.intt_limbs += (uint64_t)cb * L1;
@@ -412,7 +723,7 @@ int32_t sr_moddown(he_ctx* c, uint32_t level, uint32_t J, const ModDownEpilogue&
         a.scale[t] = h_mulmod(c->h_mc[c->nq + t].ninv, c->h_dn_invhat[t], p);
         a.scale_sh[t] = h_shoup(a.scale[t], p);
     }
-    hipLaunchKernelGGL(sr_moddown_kernel, dim3(J * 2 * L1), dim3(SR_THREADS), 0, c->stream, ep, a, sr_tables(c));
+    SR_LAUNCH(moddown_kernel, dim3(J * 2 * L1), ep, a, sr_tables(c));
     HE_HIP(c, hipGetLastError());
     c->cnt.intt_limbs += (uint64_t)J * 2 * k;
     c->cnt.ntt_limbs += (uint64_t)J * 2 * L1;
@@ -426,7 +737,7 @@ int32_t sr_rescale(he_ctx* c, const u64* const* cts, u64* const* outs, uint32_t 
         SrRescaleArgs a;
         for (uint32_t i = 0; i < nb; i++) { a.ct[i] = cts[b0 + i]; a.out[i] = outs[b0 + i]; }
         a.qlinv = c->d_qlinv + (size_t)level * c->nq; a.qlinv_sh = c->d_qlinv_sh + (size_t)level * c->nq; a.level = level;
-        hipLaunchKernelGGL(sr_rescale_kernel, dim3(nb * 2 * level), dim3(SR_THREADS), 0, c->stream, a, sr_tables(c));
+        SR_LAUNCH(rescale_kernel, dim3(nb * 2 * level), a, sr_tables(c));
         HE_HIP(c, hipGetLastError());
         c->cnt.intt_limbs += (uint64_t)2 * nb;
         c->cnt.ntt_limbs += (uint64_t)2 * nb * level;
