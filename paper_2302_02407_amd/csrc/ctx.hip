@@ -100,6 +100,17 @@ extern "C" {
 
 const char* he_last_error(const he_ctx* ctx) { return ctx ? ctx->err.c_str() : g_create_err.c_str(); }
 
+// Place of twiddle i = 2^stage + position in its stage's table.  In the rings of the two-launch transforms the last four
+// stages are run by threads that each hold 16 adjacent points (group G of N/16): a thread's 2^u factors of stage
+// logN-4+u lie N/16 apart instead of side by side, so that one load by the 64 lanes of a wavefront is 1 KiB in a row instead
+// of 64 cache lines.
+static uint32_t tw_pos(uint32_t i, uint32_t logN) {
+    const uint32_t s0 = logN - 4;
+    if (logN <= 12 || i < (1u << s0)) return i;
+    const uint32_t s = 31 - __builtin_clz(i), u = s - s0, at = i - (1u << s);
+    return (1u << s) + ((at & ((1u << u) - 1u)) << s0) + (at >> u);
+}
+
 int32_t he_ctx_create(he_ctx** out, uint32_t logN, const uint64_t* h_q, uint32_t nq, const uint64_t* h_p,
                       uint32_t np, uint32_t dnum, void* hip_stream) {
     return he_guard(nullptr, "he_ctx_create: host allocation failed", [&]() -> int32_t {
@@ -159,7 +170,7 @@ int32_t he_ctx_create(he_ctx** out, uint32_t logN, const uint64_t* h_q, uint32_t
         ulonglong2* t = &tw[(size_t)i * N];
         ulonglong2* it = &itw[(size_t)i * N];
         for (uint32_t e = 0; e < N; e++) {                      // psi^e stored at bitrev(e)
-            uint32_t pos = bitrev(e, logN);
+            const uint32_t pos = tw_pos(bitrev(e, logN), logN);
             t[pos] = make_ulonglong2(pw, h_shoup(pw, m));
             it[pos] = make_ulonglong2(ipw, h_shoup(ipw, m));
             pw = h_mulmod(pw, psi, m);

@@ -12,7 +12,9 @@
 // What bounds a pass is how far loads run ahead of arithmetic.  A row pass needs 240 bytes of twiddles per thread for 128
 // bytes of points; fetched where they are used they cost 40 us of 104 (384 limbs, N = 2^16, measured with the factors
 // taken out), so they are requested a block ahead, as the registers of the previous block's factors come free: 81 us,
-// where a copy of the same limbs through LDS takes 61.
+// where a copy of the same limbs through LDS takes 61.  The second block's factors are every thread's own; kept one of every
+// thread after the other (ctx.hip, tw_pos) a load covers 8 cache lines where a thread's own side by side made it 64:
+// inverse row pass of 384 limbs 124 -> 102 us, forward 110 -> 105.
 //
 // Arithmetic: ntt_blocks.h.  Forward values are never reduced inside a transform for moduli below 2^57 (16 or 17 stages end
 // below 73q < 2^64) and once in two stages above; a small-quotient step makes them canonical at the end.
@@ -411,11 +413,11 @@ __device__ __forceinline__ void row_fwd(const P2Args& a, uint32_t e, uint32_t ti
     SCHED_FENCE();
     fwd_stages<WIDE, 0, 3>(x, w1, q);
     SCHED_FENCE();
-    tw_load<0, 3>(w2, tw, lc + 4, G2);                   // into the registers that the first three stages' factors leave
+    tw_load_last<0, 3>(w2, tw, lc + 4, G2);                   // into the registers that the first three stages' factors leave
     SCHED_FENCE();
     fwd_stages<WIDE, 3, 4>(x, w1, q);
     SCHED_FENCE();
-    tw_load<3, 4>(w2, tw, lc + 4, G2);
+    tw_load_last<3, 4>(w2, tw, lc + 4, G2);
     SCHED_FENCE();
 #pragma unroll
     for (int k = 0; k < 16; k++) s[t + 17 * k] = x[k];
@@ -541,7 +543,7 @@ __device__ __forceinline__ void row_inv(const P2Args& a, const LimbTab& tab, uin
         const u64* in = tab_src(tab, e, logN) + (size_t)b * 256;
 #pragma unroll
         for (int k = 0; k < 16; k++) x[k] = in[t + 16 * k];
-        tw_load<0, 4>(w2, tw, lc + 4, 16 * b + t);
+        tw_load_last<0, 4>(w2, tw, lc + 4, 16 * b + t);
         SCHED_FENCE();
 #pragma unroll
         for (int k = 0; k < 16; k++) s[t + 17 * k] = x[k];
@@ -565,7 +567,7 @@ __device__ __forceinline__ void row_inv(const P2Args& a, const LimbTab& tab, uin
             ip_row_terms([&](uint32_t i) { return IpTerm{ip.raised[i] + ro, nullptr, ip.evk[i] + ko, 0xFFFFFFFFu, ip.g[i]}; }, ip.n_terms, ip.beta,
                          row0, t, logN, dig_stride, key_stride, m, emit);
         }
-        tw_load<0, 4>(w2, tw, lc + 4, 16 * b + t);
+        tw_load_last<0, 4>(w2, tw, lc + 4, 16 * b + t);
     }
     wave_exchange();
 #pragma unroll

@@ -71,6 +71,16 @@ __device__ __forceinline__ void tw_load(ulonglong2 (&w)[15], const ulonglong2* _
         for (int g = 0; g < (1 << u); g++) w[(1 << u) - 1 + g] = p[g];
     }
 }
+// The same for the last four stages of the two-launch transforms, whose tables keep one factor of every group after the
+// other (ctx.hip, tw_pos); G of 2^s0 groups.
+template <int U0, int U1>
+__device__ __forceinline__ void tw_load_last(ulonglong2 (&w)[15], const ulonglong2* __restrict__ tw, uint32_t s0, uint32_t G) {
+    tw += (1u << s0) + G;
+#pragma unroll
+    for (int u = U0; u < U1; u++)
+#pragma unroll
+        for (int g = 0; g < (1 << u); g++) w[(1 << u) - 1 + g] = tw[(size_t)((1u << u) - 1u + g) << s0];
+}
 // Forward stages U0 .. U1-1.  Wide moduli: inputs and results below 16q.
 template <bool WIDE, int U0, int U1>
 __device__ __forceinline__ void fwd_stages(u64 (&x)[16], const ulonglong2 (&w)[15], u64 q) {
