@@ -15,6 +15,10 @@
 // (each byte minus 128, which the constant term returns).  Two instructions give 16 points x 4 targets x 8 digits, laid
 // out so that a lane gets the 8 digit sums of one (point, target); they are put together and reduced below 2q in 17
 // vector instructions, where the vector-unit form of the same sum takes 52.
+//
+// What bounds it is vector issue: about 6300 instructions per wavefront for 8 + 24 limbs, 4.5 cycles each, are 47 of the 50 us
+// that two work groups per compute unit take.  ModUp and ModDown of 8 rotations at the benchmark's top level: 162 -> 151 us
+// once a round's operands came without dependent vector loads and nothing was kept in scratch memory.
 #include "modarith.h"
 #include "ntt_blocks.h"
 
@@ -87,15 +91,14 @@ __device__ __forceinline__ void cc_source(u64* reg, const u64* src, const ColCon
 
 // Forward column stages of one target limb from its LDS region (below 2q) to memory.
 template <int LC, bool WIDE>
-__device__ __forceinline__ void cc_target(u64* reg, u64* dst, uint32_t mi, uint32_t lane, uint32_t c0, const ModConst* mc, const ulonglong2* ftw) {
+__device__ __forceinline__ void cc_target(u64* reg, u64* dst, uint32_t mi, const ulonglong2 (&w1)[15], uint32_t lane, uint32_t c0, const ModConst* mc, const ulonglong2* ftw) {
     constexpr int LCOLS = 10 - LC, U0 = 8 - LC;
     const uint32_t t = lane >> LCOLS, cl = lane & ((1u << LCOLS) - 1u), c = c0 + cl;
     const ctw_t tw = (ctw_t)(uintptr_t)(ftw + ((size_t)mi << (LC + 8)));
     const cu64_t mp = (cu64_t)(uintptr_t)(mc + mi);
     const u64 q = uni64(mp[0]), q4 = 4 * q;
-    ulonglong2 w1[15], w2[15];
+    ulonglong2 w2[15];
     tw_load_c<(U0 < 3 ? U0 : 3), 3>(w2, tw, LC - 4, t);
-    tw_load_c<0, 4>(w1, tw, 0, 0);
     u64 x[16];
 #pragma unroll
     for (int k = 0; k < 16; k++) x[k] = reg[cc_word(k, lane)];
@@ -156,25 +159,30 @@ __global__ __launch_bounds__(CC_THREADS, 4) void col_conv_kernel(ColConv cc, Sca
     __syncthreads();
     // this wavefront's 128 points of every source: runs 2w and 2w+1; lane group g = lane / 16 holds sources 2g, 2g+1 of 16
     // points, in memory order the bytes k = 16g .. 16g+15 of the contraction
-    const uint32_t g = lane >> 4, p16 = lane & 15;
     v4i frag[8];
 #pragma unroll
     for (int b = 0; b < 8; b++) {
-        const uint32_t word = cc_word(2 * w + (b >> 2), 16 * (b & 3) + p16);
+        const uint32_t g = lane >> 4, word = cc_word(2 * w + (b >> 2), 16 * (b & 3) + (lane & 15));
         const u64 y0 = 2 * g < st.ns ? lds[(2 * g) * CC_REGION + word] : 0;
         const u64 y1 = 2 * g + 1 < st.ns ? lds[(2 * g + 1) * CC_REGION + word] : 0;
         frag[b] = v4i{(int)(uint32_t)y0, (int)(uint32_t)(y0 >> 32), (int)(uint32_t)y1, (int)(uint32_t)(y1 >> 32)};
     }
     const uint32_t nt = st.nt;
+    uint32_t ln = lane;
     for (uint32_t t0 = 0; t0 < nt; t0 += CC_WAVES) {
+        asm("" : "+v"(ln));                                  // what follows from the lane is worked out anew, not kept in registers
+        const uint32_t g = ln >> 4, p16 = ln & 15;
         // operands of this round's eight targets, four (s) at a time: lane group g works on target t0 + 4s + g and this lane
         // supplies row lane % 16 = (target (lane % 16) / 4, digit lane % 4) of the left factor
+        const u64 mods = *reinterpret_cast<const u64*>(st.mod + t0), lims = *reinterpret_cast<const u64*>(st.limb + t0);
+        const uint32_t mod_first = (uint32_t)mods & 255u;
         v4i a0[2], a1[2], k0[2], k1[2];
         uint32_t n0[2], n1[2], rec[2], bits[2];
 #pragma unroll
         for (int s = 0; s < 2; s++) {
             const uint32_t ta = t0 + 4 * s + (p16 >> 2), tg = t0 + 4 * s + g;
-            const uint32_t ma = st.mod[ta < nt ? ta : t0], mg = st.mod[tg < nt ? tg : t0];
+            const uint32_t ma = ta < nt ? (uint32_t)(mods >> (8 * (4 * s + (p16 >> 2)))) & 255u : mod_first;
+            const uint32_t mg = tg < nt ? (uint32_t)(mods >> (8 * (4 * s + g))) & 255u : mod_first;
             const v4i* A = reinterpret_cast<const v4i*>(st.digits + (size_t)ma * 512 + (p16 & 3) * 64 + g * 16);
             a0[s] = A[0]; a1[s] = A[16];                     // digits 0..3, digits 4..7 (256 bytes on)
             const v4i* K = reinterpret_cast<const v4i*>(st.bias + (size_t)mg * 8);
@@ -183,6 +191,11 @@ __global__ __launch_bounds__(CC_THREADS, 4) void col_conv_kernel(ColConv cc, Sca
             n0[s] = (uint32_t)nq; n1[s] = (uint32_t)(nq >> 32);
             rec[s] = mc[mg].rec; bits[s] = mc[mg].bits;
         }
+        // this wavefront's target and the factors of its first block, which arrive during the conversion
+        const bool have = t0 + w < nt;
+        const uint32_t mi = have ? (uint32_t)(mods >> (8 * w)) & 255u : mod_first;
+        ulonglong2 w1[15];
+        tw_load_c<0, 4>(w1, (ctw_t)(uintptr_t)(ftw + ((size_t)mi << (LC + 8))), 0, 0);
         __syncthreads();                                     // the regions are free (operands read, last targets done)
 #pragma unroll
         for (int s = 0; s < 2; s++) {
@@ -205,12 +218,11 @@ __global__ __launch_bounds__(CC_THREADS, 4) void col_conv_kernel(ColConv cc, Sca
             }
         }
         __syncthreads();
-        const uint32_t tw_ = t0 + w;
-        if (tw_ < nt) {
-            const uint32_t mi = __builtin_amdgcn_readfirstlane(st.mod[tw_]), li = __builtin_amdgcn_readfirstlane(st.limb[tw_]);
+        if (have) {
+            const uint32_t li = (uint32_t)(lims >> (8 * w)) & 255u;
             u64* dst = st.dst + (size_t)rep * cc.dst_stride + ((size_t)li << (LC + 8));
-            if (cc.wide_fwd >> mi & 1u) cc_target<LC, true>(reg, dst, cc_pin<true>(mi), lane, c0, mc, ftw);
-            else cc_target<LC, false>(reg, dst, cc_pin<false>(mi), lane, c0, mc, ftw);
+            if (cc.wide_fwd >> mi & 1u) cc_target<LC, true>(reg, dst, cc_pin<true>(mi), w1, ln, c0, mc, ftw);
+            else cc_target<LC, false>(reg, dst, cc_pin<false>(mi), w1, ln, c0, mc, ftw);
         }
     }
 }
