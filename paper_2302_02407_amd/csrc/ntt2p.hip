@@ -612,6 +612,157 @@ __global__ __launch_bounds__(P2_THREADS, IP ? 3 : 4) void ntt_row_inv_kernel(P2A
     else row_inv<false, IP, BETA>(a, tab, branch_pin<false>(e), tile, sm, ip);
 }
 
+// ---------------------------------------------------------------- row passes of several limbs of one modulus
+// Plain row passes where a launch holds many limbs of each modulus (a batch of polynomials, the digits of several key
+// switches): a wavefront takes ONE row of 4 limbs at a time, 16 lanes each, and goes on with the same row of the next 4.
+// The first block's factors are then the same for the wavefront (scalar registers), the second block's are loaded once for
+// the whole run instead of once per limb.  384 limbs, N = 2^16, against the passes above: forward 105 -> 95 us, inverse
+// 102 -> 95, near what the points alone take (403 MB, 82 us at copy rate).  Asking for the next four limbs' points ahead
+// costs a third of the wavefronts and gave 110.
+struct RunTab {
+    uint32_t r[HE_MAX_LAUNCH_LIMBS / 4 + HE_MAX_MODULI];     // first entry of LimbTab (bits 0-8), limbs (9-13), wide (31)
+};
+// what entry 4*it + i of the run gives for lane quarter i (the last entry's again where the run has fewer)
+template <class F>
+__device__ __forceinline__ auto run_pick(const LimbTab& tab, uint32_t first, uint32_t n, uint32_t it, uint32_t quarter, F&& f) {
+    const auto v0 = f(tab.e[first + min(4 * it, n - 1)]), v1 = f(tab.e[first + min(4 * it + 1, n - 1)]);
+    const auto v2 = f(tab.e[first + min(4 * it + 2, n - 1)]), v3 = f(tab.e[first + min(4 * it + 3, n - 1)]);
+    return quarter & 2 ? (quarter & 1 ? v3 : v2) : (quarter & 1 ? v1 : v0);
+}
+// the first block's factors into scalar registers: through a pointer to constant memory, which no store can change
+typedef const __attribute__((address_space(4))) u64* const_u64;
+__device__ __forceinline__ void run_tw1(ulonglong2 (&w)[15], const ulonglong2* tw, uint32_t s0, uint32_t b) {
+#pragma unroll
+    for (int u = 0; u < 4; u++)
+#pragma unroll
+        for (int g = 0; g < (1 << u); g++) {
+            const const_u64 p = (const_u64)(uintptr_t)uni64((u64)(tw + ((1u << (s0 + u)) + (b << u) + g)));
+            w[(1 << u) - 1 + g] = make_ulonglong2(p[0], p[1]);
+        }
+}
+// The loop over a run uses the factors again and again: without this the compiler keeps the upper words of all of them in
+// registers of their own besides (30 more, which then spill).
+__device__ __forceinline__ void run_keep(ulonglong2 (&w)[15]) {
+#pragma unroll
+    for (int i = 0; i < 15; i++) asm("" : "+v"(w[i].x), "+v"(w[i].y));
+}
+template <bool WIDE, bool LAZY>
+__device__ __forceinline__ void row_run_fwd(const P2Args& a, const LimbTab& tab, uint32_t run, uint32_t b, u64* sm) {
+    const uint32_t first = run & 511u, n = (run >> 9) & 31u, logN = a.logN, lc = logN - 8, mi = tab_mod(tab.e[first]);
+    const uint32_t quarter = (threadIdx.x >> 4) & 3u, t = threadIdx.x & 15u;
+    const ulonglong2* tw = a.tw + ((size_t)mi << logN);
+    u64* s = sm + (threadIdx.x >> 4) * 272;
+    u64 x[16];
+    ulonglong2 w1[15], w2[15];
+    auto dst = [&](uint32_t e) { return tab_dst(__builtin_amdgcn_readfirstlane(e)); };
+    u64* base = a.dst + b * 256u + t;
+    run_tw1(w1, tw, lc, b);
+    tw_load_last<0, 4>(w2, tw, lc + 4, 16 * b + t);
+    const ModConst m = a.mc[mi];
+    const u64 q = uni64(m.q);
+    for (uint32_t it = 0;; it++) {
+        const uint32_t dl = run_pick(tab, first, n, it, quarter, dst);
+#pragma unroll
+        for (int k = 0; k < 16; k++) x[k] = base[((size_t)dl << logN) + 16 * k];
+        SCHED_FENCE();
+        fwd_stages<WIDE, 0, 4>(x, w1, q);
+#pragma unroll
+        for (int k = 0; k < 16; k++) s[t + 17 * k] = x[k];
+        wave_exchange();
+#pragma unroll
+        for (int j = 0; j < 16; j++) x[j] = s[17 * t + j];
+        SCHED_FENCE();
+        run_keep(w2);
+        fwd_stages<WIDE, 0, 4>(x, w2, q);
+        SCHED_FENCE();
+        if (!WIDE && LAZY) {
+#pragma unroll
+            for (int j = 0; j < 16; j++) x[j] = reduce_lazy<7>(x[j], q, m.bits, m.rec);
+        } else {
+#pragma unroll
+            for (int j = 0; j < 16; j++) x[j] = reduce_full<7>(x[j], q, m.bits, m.rec);
+        }
+        wave_exchange();
+#pragma unroll
+        for (int j = 0; j < 16; j++) s[17 * t + j] = x[j];
+        wave_exchange();
+        if (4 * it + quarter < n) {
+#pragma unroll
+            for (int k = 0; k < 16; k++) base[((size_t)dl << logN) + 16 * k] = s[t + 17 * k];
+        }
+        if (4 * (it + 1) >= n) return;
+        wave_exchange();
+    }
+}
+template <bool WIDE>
+__device__ __forceinline__ void row_run_inv(const P2Args& a, const LimbTab& tab, uint32_t run, uint32_t b, u64* sm) {
+    const uint32_t first = run & 511u, n = (run >> 9) & 31u, logN = a.logN, lc = logN - 8, mi = tab_mod(tab.e[first]);
+    const uint32_t quarter = (threadIdx.x >> 4) & 3u, t = threadIdx.x & 15u;
+    const ulonglong2* tw = a.tw + ((size_t)mi << logN);
+    u64* s = sm + (threadIdx.x >> 4) * 272;
+    u64 x[16];
+    ulonglong2 w1[15], w2[15];
+    const uint32_t at = b * 256u + t;
+    auto dst = [&](uint32_t e) { return tab_dst(__builtin_amdgcn_readfirstlane(e)); };
+    auto src = [&](uint32_t e) { return uni64((u64)tab_src(tab, e, logN)); };
+    tw_load_last<0, 4>(w2, tw, lc + 4, 16 * b + t);
+    run_tw1(w1, tw, lc, b);
+    const ModConst m = a.mc[mi];
+    const u64 q = uni64(m.q);
+    for (uint32_t it = 0;; it++) {
+        const u64* in = (const u64*)run_pick(tab, first, n, it, quarter, src) + at;
+#pragma unroll
+        for (int k = 0; k < 16; k++) x[k] = in[16 * k];
+        const uint32_t dl = run_pick(tab, first, n, it, quarter, dst);
+#pragma unroll
+        for (int k = 0; k < 16; k++) s[t + 17 * k] = x[k];
+        wave_exchange();
+        SCHED_FENCE();
+#pragma unroll
+        for (int j = 0; j < 16; j++) x[j] = s[17 * t + j];
+        int bd[16];
+        bounds_all(bd, 1);
+        run_keep(w2);
+        inv_stages<WIDE, 0, 4>(x, bd, w2, q);
+        SCHED_FENCE();
+        if (WIDE) settle4(x, bd, q);
+        wave_exchange();
+#pragma unroll
+        for (int j = 0; j < 16; j++) s[17 * t + j] = x[j];
+        wave_exchange();
+#pragma unroll
+        for (int k = 0; k < 16; k++) x[k] = s[t + 17 * k];
+        bounds_all(bd, WIDE ? 4 : 32);
+        inv_stages<WIDE, 0, 4>(x, bd, w1, q);
+        if (WIDE) settle4(x, bd, q);
+        else {
+#pragma unroll
+            for (int k = 0; k < 16; k++) x[k] = reduce_lazy<10>(x[k], q, m.bits, m.rec);
+        }
+        if (4 * it + quarter < n) {
+            u64* out = a.dst + ((size_t)dl << logN) + at;
+#pragma unroll
+            for (int k = 0; k < 16; k++) out[16 * k] = x[k];
+        }
+        if (4 * (it + 1) >= n) return;
+        wave_exchange();
+    }
+}
+// work group: 4 adjacent rows of one run
+template <bool FWD, bool LAZY>
+__global__ __launch_bounds__(P2_THREADS, 4) void ntt_row_run_kernel(P2Args a, LimbTab tab, RunTab runs) {
+    __shared__ u64 sm[16 * 272];
+    const uint32_t lb = a.logN - 10, b = (blockIdx.x & ((1u << lb) - 1u)) * 4u + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t run = __builtin_amdgcn_readfirstlane(runs.r[blockIdx.x >> lb]);
+    if (FWD) {
+        if (run & TAB_WIDE) row_run_fwd<true, LAZY>(a, tab, branch_pin<true>(run), b, sm);
+        else row_run_fwd<false, LAZY>(a, tab, branch_pin<false>(run), b, sm);
+    } else {
+        if (run & TAB_WIDE) row_run_inv<true>(a, tab, branch_pin<true>(run), b, sm);
+        else row_run_inv<false>(a, tab, branch_pin<false>(run), b, sm);
+    }
+}
+
 // ---------------------------------------------------------------- column passes fused around the basis conversion
 // Latency path for small launches (a few limbs: the low levels the paper's networks run at), where the chip is mostly
 // idle and a call is bound by its chain of dependent launches.  The last inverse pass, the basis conversion and the
@@ -861,6 +1012,20 @@ int32_t launch_transform2p(he_ctx* ctx, const TransformDesc& d) {
         if (seg >= HE_MAX_SEGS || seg >= d.n_seg || lim >= 4096) return he_fail(ctx, HE_ERR_BADARG, "transform: source limb out of range");
         tab.e[start[mi]++] = i | (mi << 9) | (lim << 15) | (seg << 27) | (ctx->h_mc[mi].bits > (fwd ? 57u : 54u) ? TAB_WIDE : 0u);
     }
+    // Plain row passes by runs of one modulus: fours of limbs, up to 16 in a run, shorter runs where the launch would not
+    // fill the chip four times over.  Where more than a quarter of the lanes would have no limb, one limb at a time.
+    RunTab runs;
+    uint32_t n_runs = 0, fours = 0;
+    for (uint32_t m = 0; m < ctx->M; m++) fours += (count[m] + 3) / 4;
+    const bool by_runs = live >= 3 * fours;
+    if (by_runs) {
+        uint32_t piece = 16;
+        const uint32_t groups = ctx->N >> 10;               // work groups per run
+        while (piece > 4 && (live / piece) * groups < 4 * 768) piece >>= 1;
+        for (uint32_t m = 0, at = 0; m < ctx->M; at += count[m++])
+            for (uint32_t i = 0; i < count[m]; i += piece)
+                runs.r[n_runs++] = (at + i) | (std::min(piece, count[m] - i) << 9) | (ctx->h_mc[m].bits > (fwd ? 57u : 54u) ? TAB_WIDE : 0u);
+    }
     P2Args a;
     a.dst = d.dst; a.mc = ctx->d_mc;
     a.tw = fwd ? ctx->d_tw : ctx->d_itw;
@@ -892,10 +1057,13 @@ int32_t launch_transform2p(he_ctx* ctx, const TransformDesc& d) {
             if (d.ep && d.ep->fused && d.ep->n_terms) hipLaunchKernelGGL((ntt_row_fwd_kernel<3, 0>), grid_rows, block, 0, ctx->stream, a, tab, *d.ep);
             else if (d.ep && d.ep->fused) { BETA_DISPATCH(ntt_row_fwd_kernel, 2, d.ep->beta, grid_rows, block, 0, ctx->stream, a, tab, *d.ep) }
             else if (d.ep) hipLaunchKernelGGL((ntt_row_fwd_kernel<1, 0>), grid_rows, block, 0, ctx->stream, a, tab, *d.ep);
+            else if (by_runs && a.lazy) hipLaunchKernelGGL((ntt_row_run_kernel<true, true>), dim3(n_runs * (ctx->N >> 10)), block, 0, ctx->stream, a, tab, runs);
+            else if (by_runs) hipLaunchKernelGGL((ntt_row_run_kernel<true, false>), dim3(n_runs * (ctx->N >> 10)), block, 0, ctx->stream, a, tab, runs);
             else { ModDownEpilogue none = {}; hipLaunchKernelGGL((ntt_row_fwd_kernel<0, 0>), grid_rows, block, 0, ctx->stream, a, tab, none); }
         } else if (pass == 0) {
             if (d.ip && d.ip->n_terms) hipLaunchKernelGGL((ntt_row_inv_kernel<2, 0>), grid_rows, block, 0, ctx->stream, a, tab, *d.ip);
             else if (d.ip) { BETA_DISPATCH(ntt_row_inv_kernel, 1, d.ip->beta, grid_rows, block, 0, ctx->stream, a, tab, *d.ip) }
+            else if (by_runs) hipLaunchKernelGGL((ntt_row_run_kernel<false, false>), dim3(n_runs * (ctx->N >> 10)), block, 0, ctx->stream, a, tab, runs);
             else { IpPrologue none = {}; hipLaunchKernelGGL((ntt_row_inv_kernel<0, 0>), grid_rows, block, 0, ctx->stream, a, tab, none); }
         } else {
             if (d.scale) { COL_DISPATCH(ntt_col_inv_kernel, true, grid_cols, block, 0, ctx->stream, a, tab, *d.scale, d.scale_period) }
