@@ -19,6 +19,8 @@
 // What bounds it is vector issue: about 6300 instructions per wavefront for 8 + 24 limbs, 4.5 cycles each, are 47 of the 50 us
 // that two work groups per compute unit take.  ModUp and ModDown of 8 rotations at the benchmark's top level: 162 -> 151 us
 // once a round's operands came without dependent vector loads and nothing was kept in scratch memory.
+#include <algorithm>
+
 #include "modarith.h"
 #include "ntt_blocks.h"
 
@@ -146,7 +148,7 @@ __global__ __launch_bounds__(CC_THREADS, 4) void col_conv_kernel(ColConv cc, Sca
     constexpr int LCOLS = 10 - LC, TPX = (256 >> LCOLS) / 8;             // tiles of a group per XCD
     __shared__ u64 lds[CC_WAVES * CC_REGION];
     const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const uint32_t slot = blockIdx.x >> 3, tile = (blockIdx.x & 7u) * TPX + slot % TPX, grp = slot / TPX;
+    const uint32_t slot = blockIdx.x >> 3, tile = (blockIdx.x & 7u) * TPX + slot % TPX, gp = slot / TPX, grp = gp / cc.parts;
     const uint32_t set = grp % cc.n_sets, rep = grp / cc.n_sets, c0 = tile << LCOLS;
     const ColConvSet& st = cc.set[set];
     u64* reg = lds + w * CC_REGION;
@@ -167,14 +169,14 @@ __global__ __launch_bounds__(CC_THREADS, 4) void col_conv_kernel(ColConv cc, Sca
         const u64 y1 = 2 * g + 1 < st.ns ? lds[(2 * g + 1) * CC_REGION + word] : 0;
         frag[b] = v4i{(int)(uint32_t)y0, (int)(uint32_t)(y0 >> 32), (int)(uint32_t)y1, (int)(uint32_t)(y1 >> 32)};
     }
-    const uint32_t nt = st.nt;
+    const uint32_t tb = (gp - grp * cc.parts) * cc.share, nt = min(st.nt, tb + cc.share);
     uint32_t ln = lane;
-    for (uint32_t t0 = 0; t0 < nt; t0 += CC_WAVES) {
+    for (uint32_t t0 = tb; t0 < nt; t0 += CC_WAVES) {
         asm("" : "+v"(ln));                                  // what follows from the lane is worked out anew, not kept in registers
         const uint32_t g = ln >> 4, p16 = ln & 15;
         // operands of this round's eight targets, four (s) at a time: lane group g works on target t0 + 4s + g and this lane
         // supplies row lane % 16 = (target (lane % 16) / 4, digit lane % 4) of the left factor
-        const u64 mods = *reinterpret_cast<const u64*>(st.mod + t0), lims = *reinterpret_cast<const u64*>(st.limb + t0);
+        const u64 mods = uni64(*reinterpret_cast<const u64*>(st.mod + t0)), lims = uni64(*reinterpret_cast<const u64*>(st.limb + t0));
         const uint32_t mod_first = (uint32_t)mods & 255u;
         v4i a0[2], a1[2], k0[2], k1[2];
         uint32_t n0[2], n1[2], rec[2], bits[2];
@@ -227,12 +229,14 @@ __global__ __launch_bounds__(CC_THREADS, 4) void col_conv_kernel(ColConv cc, Sca
     }
 }
 
-int32_t launch_col_conv(he_ctx* ctx, const ColConv& cc, const ScaleList& sc, uint32_t reps, uint32_t limb_passes) {
+int32_t launch_col_conv(he_ctx* ctx, ColConv& cc, const ScaleList& sc, uint32_t reps, uint32_t limb_passes) {
     const uint32_t groups = cc.n_sets * reps, LC = ctx->logN - 8;
     if (groups == 0) return HE_OK;
     if (LC < 5 || LC > 8 || cc.n_sets > CC_MAX_SETS) return he_fail(ctx, HE_ERR_BADARG, "column conversion: bad shape");
+    uint32_t rounds = 1;
     for (uint32_t s = 0; s < cc.n_sets; s++) {
         const ColConvSet& st = cc.set[s];
+        rounds = std::max(rounds, (st.nt + CC_WAVES - 1) / CC_WAVES);
         if (st.ns == 0 || st.ns > CC_WAVES || st.nt == 0 || st.nt > HE_MAX_MODULI || st.mod0 + st.ns > ctx->M || st.sc0 + st.ns > HE_MAX_MODULI ||
             !st.src || !st.dst || !st.digits || !st.bias)
             return he_fail(ctx, HE_ERR_BADARG, "column conversion: bad group %u", s);
@@ -243,7 +247,13 @@ int32_t launch_col_conv(he_ctx* ctx, const ColConv& cc, const ScaleList& sc, uin
         HE_HIP(ctx, hipEventCreate(&e1));
         HE_HIP(ctx, hipEventRecord(e0, ctx->stream));
     }
-    const dim3 grid(groups << (LC - 2)), block(CC_THREADS);
+    // while two work groups per compute unit have room for it, the rounds of a tile run side by side (a relinearisation at
+    // level 11 and its rescale: 161 -> 156 us)
+    const uint32_t work = groups << (LC - 2);
+    const uint32_t parts = std::max(1u, std::min(rounds, 512 / work));
+    cc.share = (rounds + parts - 1) / parts * CC_WAVES;
+    cc.parts = (rounds * CC_WAVES + cc.share - 1) / cc.share;
+    const dim3 grid(work * cc.parts), block(CC_THREADS);
     switch (LC) {
     case 5: hipLaunchKernelGGL(col_conv_kernel<5>, grid, block, 0, ctx->stream, cc, sc, ctx->d_mc, ctx->d_tw, ctx->d_itw); break;
     case 6: hipLaunchKernelGGL(col_conv_kernel<6>, grid, block, 0, ctx->stream, cc, sc, ctx->d_mc, ctx->d_tw, ctx->d_itw); break;

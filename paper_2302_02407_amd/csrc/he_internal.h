@@ -237,9 +237,10 @@ struct ColConv {
     ColConvSet set[CC_MAX_SETS];
     size_t src_stride, dst_stride;
     u64 wide_fwd, wide_inv;    // bit per modulus: wide in the forward (above 57 bits) / inverse (above 54) ranges
-    uint32_t n_sets, pad;
+    uint32_t n_sets;
+    uint32_t parts, share;     // work groups that share a tile's targets, `share` targets each (set by the launch)
 };
-int32_t launch_col_conv(he_ctx* ctx, const ColConv& cc, const ScaleList& sc, uint32_t reps, uint32_t limb_passes);
+int32_t launch_col_conv(he_ctx* ctx, ColConv& cc, const ScaleList& sc, uint32_t reps, uint32_t limb_passes);
 int32_t launch_colfuse(he_ctx* ctx, const ColFuse& cf, const ScaleList& sc, uint32_t limb_passes);   // ntt2p.hip
 // fills w / w_sh of entry i from s (modulus index mi)
 void scale_entry(const he_ctx* c, ScaleList& sc, uint32_t i, uint32_t mi, u64 s);
