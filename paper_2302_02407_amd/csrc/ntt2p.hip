@@ -64,8 +64,9 @@ __device__ __forceinline__ const u64* tab_src(const LimbTab& tab, uint32_t e, ui
 // padded with TAB_NONE to a multiple of the chunk size C = 1 << log_chunk; the linear work index
 // L = (chunk_of_limbs*tiles + tile)*C + j walks the C limbs of a chunk for one tile, and
 // workgroup id -> L keeps each run of C consecutive L on one XCD.
+template <int LANES>
 __device__ __forceinline__ uint32_t row_decode(const LimbTab& tab, const P2Args& a, uint32_t& tile) {
-    const uint32_t lc = a.log_chunk, idx = blockIdx.x, lt = a.logN - 12;
+    const uint32_t lc = a.log_chunk, idx = blockIdx.x, lt = a.logN - (LANES == 16 ? 12 : 10);
     const uint32_t xcd = idx & 7u, slot = idx >> 3;
     const uint32_t L = ((((slot >> lc) << 3) + xcd) << lc) | (slot & ((1u << lc) - 1u));
     const uint32_t pchunk = L >> (lt + lc), rem = L & ((1u << (lt + lc)) - 1u);
@@ -114,7 +115,7 @@ __device__ __forceinline__ void col_fwd(const P2Args& a, const LimbTab& tab, uin
     if (RS) {
         const u64 h = ml.q >> 1, hr = barrett64(h, q, m.mu, m.bits);
 #pragma unroll
-        for (int k = 0; k < 16; k++) x[k] = submod(barrett64(addmod(x[k], h, ml.q), q, m.mu, m.bits), hr, q);
+        for (int k = 0; k < 16; k++) x[k] = shoup_lazy4(addmod(x[k], h, ml.q), 1, m.one_sh, q) + (q - hr);      // below 5q
     }
     fwd_stages<WIDE, 0, 4>(x, w1, q);
 #pragma unroll
@@ -145,7 +146,7 @@ __device__ __forceinline__ void col_fwd(const P2Args& a, const LimbTab& tab, uin
 }
 
 template <int LC, bool RS>
-__global__ __launch_bounds__(P2_THREADS) void ntt_col_fwd_kernel(P2Args a, LimbTab tab) {
+__global__ __launch_bounds__(P2_THREADS, 4) void ntt_col_fwd_kernel(P2Args a, LimbTab tab) {
     using G = Col<LC>;
     __shared__ u64 sm[G::LDS];
     const uint32_t tile = blockIdx.x & (G::T - 1), e = __builtin_amdgcn_readfirstlane(tab.e[blockIdx.x >> G::LT]);
@@ -244,21 +245,23 @@ struct IpTerm {
     const u64 *raised, *own, *key;                       // own: digit own_j's limb, which is not materialised in raised
     uint32_t own_j, g;
 };
-// Two pairs of positions (4 points) of a row: positions row0 + e and row0 + e + 32.
+// Two pairs of positions (4 points) of a row: positions row0 + e and row0 + e + DP, where DP = 2 * (lanes that share the row)
+// and a thread has 128 / DP such chunks.
 template <int NJ>
 struct IpLoad {
     ulonglong2 d[NJ][2];
     u64 k[NJ][2][2];
 };
+template <int DP>
 __device__ __forceinline__ void ip_map(uint32_t (&src)[2], uint32_t (&swp)[2], uint32_t pos, uint32_t g, uint32_t logN) {
 #pragma unroll
     for (int p = 0; p < 2; p++) {
-        const uint32_t s = galois_pos(pos + 32 * p, g, logN);
+        const uint32_t s = galois_pos(pos + DP * p, g, logN);
         src[p] = s & ~1u;
         swp[p] = s & 1u;
     }
 }
-template <int NJ>
+template <int DP, int NJ>
 __device__ __forceinline__ void ip_request(IpLoad<NJ>& L, const IpTerm& tm, uint32_t j0, uint32_t nj, uint32_t pos, const uint32_t (&src)[2],
                                            const uint32_t (&swp)[2], size_t dig_stride, size_t key_stride) {
 #pragma unroll
@@ -270,7 +273,7 @@ __device__ __forceinline__ void ip_request(IpLoad<NJ>& L, const IpTerm& tm, uint
 #pragma unroll
             for (int p = 0; p < 2; p++) {
                 L.d[jj][p] = *reinterpret_cast<const ulonglong2*>(dj + src[p]);
-                const uint32_t kp = (pos + 32 * p) | swp[p];
+                const uint32_t kp = (pos + DP * p) | swp[p];
                 L.k[jj][p][0] = kj[kp];
                 L.k[jj][p][1] = kj[kp ^ 1u];
             }
@@ -295,25 +298,25 @@ __device__ __forceinline__ ulonglong2 ip_order(u64 v0, u64 v1, uint32_t swp) {
     return swp ? make_ulonglong2(v1, v0) : make_ulonglong2(v0, v1);
 }
 
-// The inner product of a row for one job: 4 chunks of 4 points per thread, the next chunk's operands requested before this
+// The inner product of a row for one job: chunks of 4 points per thread, the next chunk's operands requested before this
 // chunk's products.  BETA = 1, 2, 3: exactly that many digits; 0: any number up to 8, three at a time.  emit(chunk, pos, sums
 // below 5q in slot order, swaps).
-template <int BETA, class Emit>
+template <int DP, int BETA, class Emit>
 __device__ __forceinline__ void ip_row(const IpTerm& tm, uint32_t beta, uint32_t row0, uint32_t t, uint32_t logN, size_t dig_stride,
                                        size_t key_stride, const ModConst& m, Emit&& emit) {
-    constexpr int NJ = BETA ? BETA : 3;
+    constexpr int NJ = BETA ? BETA : 3, NCH = 128 / DP;
     uint32_t src[2], swp[2];
     if (BETA) {
         IpLoad<NJ> cur, nxt;
-        ip_map(src, swp, row0 + 2 * t, tm.g, logN);
-        ip_request(cur, tm, 0, NJ, row0 + 2 * t, src, swp, dig_stride, key_stride);
+        ip_map<DP>(src, swp, row0 + 2 * t, tm.g, logN);
+        ip_request<DP>(cur, tm, 0, NJ, row0 + 2 * t, src, swp, dig_stride, key_stride);
 #pragma unroll
-        for (int ch = 0; ch < 4; ch++) {
-            const uint32_t pos = row0 + 2 * t + 64 * ch;
+        for (int ch = 0; ch < NCH; ch++) {
+            const uint32_t pos = row0 + 2 * t + 2 * DP * ch;
             uint32_t nsrc[2] = {0, 0}, nswp[2] = {0, 0};
-            if (ch < 3) {
-                ip_map(nsrc, nswp, pos + 64, tm.g, logN);
-                ip_request(nxt, tm, 0, NJ, pos + 64, nsrc, nswp, dig_stride, key_stride);
+            if (ch + 1 < NCH) {
+                ip_map<DP>(nsrc, nswp, pos + 2 * DP, tm.g, logN);
+                ip_request<DP>(nxt, tm, 0, NJ, pos + 2 * DP, nsrc, nswp, dig_stride, key_stride);
             }
             SCHED_FENCE();
             SplitSum s[4] = {};
@@ -322,7 +325,7 @@ __device__ __forceinline__ void ip_row(const IpTerm& tm, uint32_t beta, uint32_t
 #pragma unroll
             for (int i = 0; i < 4; i++) v[i] = split_reduce(s[i], m);
             emit(ch, pos, v, src, swp);
-            if (ch < 3) {
+            if (ch + 1 < NCH) {
                 cur = nxt;
 #pragma unroll
                 for (int p = 0; p < 2; p++) { src[p] = nsrc[p]; swp[p] = nswp[p]; }
@@ -330,15 +333,15 @@ __device__ __forceinline__ void ip_row(const IpTerm& tm, uint32_t beta, uint32_t
         }
     } else {
 #pragma unroll
-        for (int ch = 0; ch < 4; ch++) {
-            const uint32_t pos = row0 + 2 * t + 64 * ch;
-            ip_map(src, swp, pos, tm.g, logN);
+        for (int ch = 0; ch < 128 / DP; ch++) {
+            const uint32_t pos = row0 + 2 * t + 2 * DP * ch;
+            ip_map<DP>(src, swp, pos, tm.g, logN);
             SplitSum s[4] = {};
             u64 v[4] = {0, 0, 0, 0};
             for (uint32_t j0 = 0; j0 < beta; j0 += NJ) {
                 IpLoad<NJ> L;
                 const uint32_t nj = beta - j0 < NJ ? beta - j0 : NJ;
-                ip_request(L, tm, j0, nj, pos, src, swp, dig_stride, key_stride);
+                ip_request<DP>(L, tm, j0, nj, pos, src, swp, dig_stride, key_stride);
                 if (j0 == 6) {                           // seven products at most in one sum
 #pragma unroll
                     for (int i = 0; i < 4; i++) { v[i] = split_reduce(s[i], m); s[i] = SplitSum{0, 0, 0}; }
@@ -352,18 +355,18 @@ __device__ __forceinline__ void ip_row(const IpTerm& tm, uint32_t beta, uint32_t
     }
 }
 // The same for the sum over n_terms terms (a sum of rotations with one ModDown); term(i) describes term i.
-template <class Term, class Emit>
+template <int DP, class Term, class Emit>
 __device__ __forceinline__ void ip_row_terms(Term&& term, uint32_t n_terms, uint32_t beta, uint32_t row0, uint32_t t, uint32_t logN,
                                              size_t dig_stride, size_t key_stride, const ModConst& m, Emit&& emit) {
     const uint32_t most = m.bits > 57 ? SPLIT_MAX : 15;
 #pragma unroll 1
-    for (int ch = 0; ch < 4; ch++) {
-        const uint32_t pos = row0 + 2 * t + 64 * ch;
+    for (int ch = 0; ch < 128 / DP; ch++) {
+        const uint32_t pos = row0 + 2 * t + 2 * DP * ch;
         u64 tot[4] = {0, 0, 0, 0};                       // in position order
         for (uint32_t i = 0; i < n_terms; i++) {
             const IpTerm tm = term(i);
             uint32_t src[2], swp[2], pending = 0;
-            ip_map(src, swp, pos, tm.g, logN);
+            ip_map<DP>(src, swp, pos, tm.g, logN);
             SplitSum s[4] = {};
             auto flush = [&]() {
 #pragma unroll
@@ -378,16 +381,32 @@ __device__ __forceinline__ void ip_row_terms(Term&& term, uint32_t n_terms, uint
             for (uint32_t j0 = 0; j0 < beta; j0 += 3) {
                 IpLoad<3> L;
                 const uint32_t nj = beta - j0 < 3 ? beta - j0 : 3;
-                ip_request(L, tm, j0, nj, pos, src, swp, dig_stride, key_stride);
+                ip_request<DP>(L, tm, j0, nj, pos, src, swp, dig_stride, key_stride);
                 if (pending + nj > most) flush();
                 ip_consume(s, L, nj);
                 pending += nj;
             }
             flush();
         }
-        const uint32_t src[2] = {pos, pos + 32}, swp[2] = {0, 0};
+        const uint32_t src[2] = {pos, pos + DP}, swp[2] = {0, 0};
         emit(ch, pos, tot, src, swp);
     }
+}
+
+// ---------------------------------------------------------------- rows with 4 points per thread
+// Factors of the four two-stage blocks of row b for thread t of 64, and the LDS word of point k before and after block i.
+__device__ __forceinline__ void tw_row4(u64 (&w)[4][6], const ulonglong2* __restrict__ tw, uint32_t lc, uint32_t b, uint32_t t) {
+    tw_block2(w[0], tw, lc, b);
+    tw_block2(w[1], tw, lc + 2, 4 * b + (t >> 4));
+    const uint32_t G = 16 * b + (t >> 2), g = t & 3u, NG = 1u << (lc + 4);      // the last four stages' order: tw_pos
+    const ulonglong2* p = tw + NG + G;
+    const ulonglong2 v[6] = {p[0], p[NG], p[2 * NG], p[(3 + g) * NG], p[(7 + 2 * g) * NG], p[(8 + 2 * g) * NG]};
+#pragma unroll
+    for (int i = 0; i < 6; i++) { w[2 + i / 3][2 * (i % 3)] = v[i].x; w[2 + i / 3][2 * (i % 3) + 1] = v[i].y; }
+}
+__device__ __forceinline__ uint32_t row4_at(int i, uint32_t t, int k) {
+    const uint32_t ls = 6 - 2 * i, e = ((t >> ls) << (ls + 2)) + (t & ((1u << ls) - 1u)) + ((uint32_t)k << ls);
+    return e + (e >> 4);
 }
 
 // ---------------------------------------------------------------- forward row pass
@@ -396,49 +415,79 @@ __device__ __forceinline__ void ip_row_terms(Term&& term, uint32_t n_terms, uint
 // EPI: 0 = plain transform; 1 = ModDown epilogue with the accumulator read from memory; 2 = ModDown epilogue that also
 // computes the accumulator (the key-switch inner product of this limb) from the raised digits and the key, so that the
 // q-limbs of the accumulator never exist in memory (BETA as in ip_row); 3 = the same for a sum over several terms.
-template <bool WIDE, int EPI, int BETA>
+// LANES: threads that share a row, 16 points each in two register blocks of four stages or, for small launches, 4 points each
+// in four blocks of two (see launch_transform2p).
+template <bool WIDE, int EPI, int BETA, int LANES>
 __device__ __forceinline__ void row_fwd(const P2Args& a, uint32_t e, uint32_t tile, u64* sm, const ModDownEpilogue& ep) {
     const uint32_t mi = tab_mod(e), limb = tab_dst(e), logN = a.logN, lc = logN - 8;
     const ulonglong2* tw = a.tw + ((size_t)mi << logN);
-    const uint32_t blk = threadIdx.x >> 4, t = threadIdx.x & 15, b = tile * 16 + blk, G2 = 16 * b + t;
+    constexpr int DP = 2 * LANES;
+    const uint32_t blk = threadIdx.x / LANES, t = threadIdx.x % LANES, b = tile * (P2_THREADS / LANES) + blk;
     u64* row = a.dst + ((size_t)limb << logN) + (size_t)b * 256;
     u64* s = sm + blk * 272;
-    u64 x[16];
-    ulonglong2 w1[15], w2[15];
-    tw_load<0, 4>(w1, tw, lc, b);
-#pragma unroll
-    for (int k = 0; k < 16; k++) x[k] = row[t + 16 * k];
     const ModConst m = a.mc[mi];
     const u64 q = uni64(m.q);
-    SCHED_FENCE();
-    fwd_stages<WIDE, 0, 3>(x, w1, q);
-    SCHED_FENCE();
-    tw_load_last<0, 3>(w2, tw, lc + 4, G2);                   // into the registers that the first three stages' factors leave
-    SCHED_FENCE();
-    fwd_stages<WIDE, 3, 4>(x, w1, q);
-    SCHED_FENCE();
-    tw_load_last<3, 4>(w2, tw, lc + 4, G2);
-    SCHED_FENCE();
+    // the transform: x[j] = point PTS*t + j of the row
+    constexpr int PTS = 256 / LANES;
+    u64 x[PTS];
+    if constexpr (LANES == 16) {
+        ulonglong2 w1[15], w2[15];
+        tw_load<0, 4>(w1, tw, lc, b);
 #pragma unroll
-    for (int k = 0; k < 16; k++) s[t + 17 * k] = x[k];
-    wave_exchange();
+        for (int k = 0; k < 16; k++) x[k] = row[t + 16 * k];
+        SCHED_FENCE();
+        fwd_stages<WIDE, 0, 3>(x, w1, q);
+        SCHED_FENCE();
+        tw_load_last<0, 3>(w2, tw, lc + 4, 16 * b + t);      // into the registers that the first three stages' factors leave
+        SCHED_FENCE();
+        fwd_stages<WIDE, 3, 4>(x, w1, q);
+        SCHED_FENCE();
+        tw_load_last<3, 4>(w2, tw, lc + 4, 16 * b + t);
+        SCHED_FENCE();
 #pragma unroll
-    for (int j = 0; j < 16; j++) x[j] = s[17 * t + j];
-    fwd_stages<WIDE, 0, 4>(x, w2, q);
+        for (int k = 0; k < 16; k++) s[t + 17 * k] = x[k];
+        wave_exchange();
+#pragma unroll
+        for (int j = 0; j < 16; j++) x[j] = s[17 * t + j];
+        fwd_stages<WIDE, 0, 4>(x, w2, q);
+    } else {
+        u64 w[4][6];
+#pragma unroll
+        for (int k = 0; k < 4; k++) x[k] = row[t + 64 * k];
+        tw_row4(w, tw, lc, b, t);
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            if (i) {
+                wave_exchange();
+#pragma unroll
+                for (int k = 0; k < 4; k++) x[k] = s[row4_at(i, t, k)];
+            }
+            fwd_block2_r<WIDE>(x, w[i], q, 4 * q);
+            if (i < 3) {
+#pragma unroll
+                for (int k = 0; k < 4; k++) s[row4_at(i, t, k)] = x[k];
+            }
+        }
+    }
     if (EPI == 0) {
         if (!WIDE && a.lazy) {
 #pragma unroll
-            for (int j = 0; j < 16; j++) x[j] = reduce_lazy<7>(x[j], q, m.bits, m.rec);
+            for (int j = 0; j < PTS; j++) x[j] = reduce_lazy<7>(x[j], q, m.bits, m.rec);
         } else {
 #pragma unroll
-            for (int j = 0; j < 16; j++) x[j] = reduce_full<7>(x[j], q, m.bits, m.rec);
+            for (int j = 0; j < PTS; j++) x[j] = reduce_full<7>(x[j], q, m.bits, m.rec);
         }
-        wave_exchange();
+        if constexpr (LANES == 16) {
+            wave_exchange();
 #pragma unroll
-        for (int j = 0; j < 16; j++) s[17 * t + j] = x[j];
-        wave_exchange();
+            for (int j = 0; j < 16; j++) s[17 * t + j] = x[j];
+            wave_exchange();
 #pragma unroll
-        for (int k = 0; k < 16; k++) row[t + 16 * k] = s[t + 17 * k];
+            for (int k = 0; k < 16; k++) row[t + 16 * k] = s[t + 17 * k];
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; j += 2) *reinterpret_cast<ulonglong2*>(row + 4 * t + j) = make_ulonglong2(x[j], x[j + 1]);
+        }
         return;
     }
     // out = (acc - ntt) * P^-1 + sigma(c0) + self: the product is below 4q whatever its factor, so the transform value may
@@ -446,11 +495,11 @@ __device__ __forceinline__ void row_fwd(const P2Args& a, uint32_t e, uint32_t ti
     const bool raw = !WIDE && m.bits <= 55;
     if (!raw) {
 #pragma unroll
-        for (int j = 0; j < 16; j++) x[j] = reduce_lazy<7>(x[j], q, m.bits, m.rec);
+        for (int j = 0; j < PTS; j++) x[j] = reduce_lazy<7>(x[j], q, m.bits, m.rec);
     }
     wave_exchange();
 #pragma unroll
-    for (int j = 0; j < 16; j++) s[17 * t + j] = x[j];
+    for (int j = 0; j < PTS; j++) s[PTS * t + j + ((PTS * t + j) >> 4)] = x[j];
     const u64 bias = raw ? (q << 7) : 2 * q;
     const uint32_t pc = limb / ep.L1, r = limb - pc * ep.L1, job = pc >> 1, comp = pc & 1u, row0 = b * 256;
     const u64 pinv = ep.pinv[r], pinv_sh = ep.pinv_sh[r];
@@ -468,18 +517,18 @@ __device__ __forceinline__ void row_fwd(const P2Args& a, uint32_t e, uint32_t ti
 #pragma unroll
         for (int p = 0; p < 2; p++) {
             cv[p] = has_c0 ? *reinterpret_cast<const ulonglong2*>(c0 + src[p]) : make_ulonglong2(0, 0);
-            sv[p] = has_self ? *reinterpret_cast<const ulonglong2*>(self + pos + 32 * p) : make_ulonglong2(0, 0);
+            sv[p] = has_self ? *reinterpret_cast<const ulonglong2*>(self + pos + DP * p) : make_ulonglong2(0, 0);
         }
 #pragma unroll
         for (int p = 0; p < 2; p++) {
-            const uint32_t e = pos - row0 + 32 * p, l = e + (e >> 4);
+            const uint32_t e = pos - row0 + DP * p, l = e + (e >> 4);
             const ulonglong2 acc = ip_order(v[2 * p], v[2 * p + 1], swp[p]), c = ip_order(cv[p].x, cv[p].y, swp[p]);
             ulonglong2 o;
             o.x = shoup_acc(c.x + sv[p].x, acc.x + bias - s[l], pinv, pinv_sh, q);
             o.y = shoup_acc(c.y + sv[p].y, acc.y + bias - s[l + 1], pinv, pinv_sh, q);
             o.x = reduce_full<7>(o.x, q, m.bits, m.rec);
             o.y = reduce_full<7>(o.y, q, m.bits, m.rec);
-            *reinterpret_cast<ulonglong2*>(out + pos + 32 * p) = o;
+            *reinterpret_cast<ulonglong2*>(out + pos + DP * p) = o;
         }
     };
     const size_t dig_stride = (size_t)ep.R << logN, key_stride = (size_t)(2 * ep.M) << logN;
@@ -487,16 +536,16 @@ __device__ __forceinline__ void row_fwd(const P2Args& a, uint32_t e, uint32_t ti
     if (EPI == 1) {
         const u64* acc = ep.acc + ((size_t)(pc * ep.R + r) << logN);
         const uint32_t g = ep.g[job];
-        ulonglong2 av[8];
+        ulonglong2 av[PTS / 2];
 #pragma unroll
-        for (int p = 0; p < 8; p++) av[p] = *reinterpret_cast<const ulonglong2*>(acc + row0 + 2 * t + 32 * p);
+        for (int p = 0; p < PTS / 2; p++) av[p] = *reinterpret_cast<const ulonglong2*>(acc + row0 + 2 * t + DP * p);
 #pragma unroll
-        for (int ch = 0; ch < 4; ch++) {
-            const uint32_t pos = row0 + 2 * t + 64 * ch;
-            uint32_t src[2] = {pos, pos + 32}, swp[2] = {0, 0};
+        for (int ch = 0; ch < PTS / 4; ch++) {
+            const uint32_t pos = row0 + 2 * t + 2 * DP * ch;
+            uint32_t src[2] = {pos, pos + DP}, swp[2] = {0, 0};
             u64 v[4] = {av[2 * ch].x, av[2 * ch].y, av[2 * ch + 1].x, av[2 * ch + 1].y};
             if (has_c0 && g != 1) {                      // accumulator values into slot order
-                ip_map(src, swp, pos, g, logN);
+                ip_map<DP>(src, swp, pos, g, logN);
 #pragma unroll
                 for (int p = 0; p < 2; p++) {
                     const ulonglong2 o = ip_order(v[2 * p], v[2 * p + 1], swp[p]);
@@ -507,21 +556,21 @@ __device__ __forceinline__ void row_fwd(const P2Args& a, uint32_t e, uint32_t ti
         }
     } else if (EPI == 2) {
         const IpTerm tm = {ep.raised[job] + ro, ep.own[job] + ro, ep.evk[job] + ko, r / ep.alpha, ep.g[job]};
-        ip_row<BETA>(tm, ep.beta, row0, t, logN, dig_stride, key_stride, m, emit);
+        ip_row<DP, BETA>(tm, ep.beta, row0, t, logN, dig_stride, key_stride, m, emit);
     } else {
-        ip_row_terms([&](uint32_t i) { return IpTerm{ep.raised[i] + ro, ep.own[i] + ro, ep.evk[i] + ko, r / ep.alpha, ep.g[i]}; }, ep.n_terms,
+        ip_row_terms<DP>([&](uint32_t i) { return IpTerm{ep.raised[i] + ro, ep.own[i] + ro, ep.evk[i] + ko, r / ep.alpha, ep.g[i]}; }, ep.n_terms,
                      ep.beta, row0, t, logN, dig_stride, key_stride, m, emit);
     }
 }
 
-template <int EPI, int BETA>
-__global__ __launch_bounds__(P2_THREADS, EPI >= 2 ? 3 : 4) void ntt_row_fwd_kernel(P2Args a, LimbTab tab, ModDownEpilogue ep) {
-    __shared__ u64 sm[16 * 272];                         // 16 groups of 17: conflict-free both ways
+template <int EPI, int BETA, int LANES>
+__global__ __launch_bounds__(P2_THREADS, LANES == 16 && EPI >= 2 ? 3 : 4) void ntt_row_fwd_kernel(P2Args a, LimbTab tab, ModDownEpilogue ep) {
+    __shared__ u64 sm[P2_THREADS / LANES * 272];         // 16 groups of 17: conflict-free both ways
     uint32_t tile;
-    const uint32_t e = row_decode(tab, a, tile);
+    const uint32_t e = row_decode<LANES>(tab, a, tile);
     if (e == TAB_NONE) return;
-    if (e & TAB_WIDE) row_fwd<true, EPI, BETA>(a, branch_pin<true>(e), tile, sm, ep);
-    else row_fwd<false, EPI, BETA>(a, branch_pin<false>(e), tile, sm, ep);
+    if (e & TAB_WIDE) row_fwd<true, EPI, BETA, LANES>(a, branch_pin<true>(e), tile, sm, ep);
+    else row_fwd<false, EPI, BETA, LANES>(a, branch_pin<false>(e), tile, sm, ep);
 }
 
 // ---------------------------------------------------------------- inverse row pass
@@ -529,24 +578,39 @@ __global__ __launch_bounds__(P2_THREADS, EPI >= 2 ? 3 : 4) void ntt_row_fwd_kern
 // 4q.  Narrow moduli: bounds 1 -> 32 after the first block, -> 512 after the second, one quotient step at the end.
 // With IP the inputs are not read: they are the key-switch inner product of the special-prime limbs, computed here from the
 // raised digits and the key.  IP: 0 = none, 1 = one job per limb (BETA as in ip_row), 2 = a sum over several terms.
-template <bool WIDE, int IP, int BETA>
+// LANES as in row_fwd.
+template <bool WIDE, int IP, int BETA, int LANES>
 __device__ __forceinline__ void row_inv(const P2Args& a, const LimbTab& tab, uint32_t e, uint32_t tile, u64* sm, const IpPrologue& ip) {
     const uint32_t mi = tab_mod(e), limb = tab_dst(e), logN = a.logN, lc = logN - 8;
     const ModConst m = a.mc[mi];
     const ulonglong2* tw = a.tw + ((size_t)mi << logN);
-    const uint32_t blk = threadIdx.x >> 4, t = threadIdx.x & 15, b = tile * 16 + blk;
+    constexpr int DP = 2 * LANES, PTS = 256 / LANES;
+    const uint32_t blk = threadIdx.x / LANES, t = threadIdx.x % LANES, b = tile * (P2_THREADS / LANES) + blk;
     u64* out = a.dst + ((size_t)limb << logN) + (size_t)b * 256;
     u64* s = sm + blk * 272;
-    u64 x[16];
-    ulonglong2 w2[15];
+    u64 x[PTS], w4[4][6];                                // w4: LANES == 64
+    ulonglong2 w2[15];                                   // LANES == 16
+    auto factors = [&]() {
+        if constexpr (LANES == 16) tw_load_last<0, 4>(w2, tw, lc + 4, 16 * b + t);
+        else tw_row4(w4, tw, lc, b, t);
+    };
     if (IP == 0) {
         const u64* in = tab_src(tab, e, logN) + (size_t)b * 256;
+        if constexpr (LANES == 16) {
 #pragma unroll
-        for (int k = 0; k < 16; k++) x[k] = in[t + 16 * k];
-        tw_load_last<0, 4>(w2, tw, lc + 4, 16 * b + t);
-        SCHED_FENCE();
+            for (int k = 0; k < 16; k++) x[k] = in[t + 16 * k];
+            factors();
+            SCHED_FENCE();
 #pragma unroll
-        for (int k = 0; k < 16; k++) s[t + 17 * k] = x[k];
+            for (int k = 0; k < 16; k++) s[t + 17 * k] = x[k];
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; j += 2) {
+                const ulonglong2 v = *reinterpret_cast<const ulonglong2*>(in + 4 * t + j);
+                x[j] = v.x; x[j + 1] = v.y;
+            }
+            factors();
+        }
     } else {
         const uint32_t pc = limb / ip.k, tp = limb - pc * ip.k, job = pc >> 1, comp = pc & 1u, row0 = b * 256;
         const size_t dig_stride = (size_t)ip.R << logN, key_stride = (size_t)(2 * ip.M) << logN;
@@ -554,7 +618,7 @@ __device__ __forceinline__ void row_inv(const P2Args& a, const LimbTab& tab, uin
         auto emit = [&](int, uint32_t pos, const u64 (&v)[4], const uint32_t (&)[2], const uint32_t (&swp)[2]) {
 #pragma unroll
             for (int p = 0; p < 2; p++) {
-                const uint32_t at = pos - row0 + 32 * p, l = at + (at >> 4);
+                const uint32_t at = pos - row0 + DP * p, l = at + (at >> 4);
                 const ulonglong2 o = ip_order(v[2 * p], v[2 * p + 1], swp[p]);
                 s[l] = reduce_full<7>(o.x, m.q, m.bits, m.rec);
                 s[l + 1] = reduce_full<7>(o.y, m.q, m.bits, m.rec);
@@ -562,54 +626,72 @@ __device__ __forceinline__ void row_inv(const P2Args& a, const LimbTab& tab, uin
         };
         if (IP == 1) {
             const IpTerm tm = {ip.raised[job] + ro, nullptr, ip.evk[job] + ko, 0xFFFFFFFFu, ip.g[job]};
-            ip_row<BETA>(tm, ip.beta, row0, t, logN, dig_stride, key_stride, m, emit);
+            ip_row<DP, BETA>(tm, ip.beta, row0, t, logN, dig_stride, key_stride, m, emit);
         } else {
-            ip_row_terms([&](uint32_t i) { return IpTerm{ip.raised[i] + ro, nullptr, ip.evk[i] + ko, 0xFFFFFFFFu, ip.g[i]}; }, ip.n_terms, ip.beta,
+            ip_row_terms<DP>([&](uint32_t i) { return IpTerm{ip.raised[i] + ro, nullptr, ip.evk[i] + ko, 0xFFFFFFFFu, ip.g[i]}; }, ip.n_terms, ip.beta,
                          row0, t, logN, dig_stride, key_stride, m, emit);
         }
-        tw_load_last<0, 4>(w2, tw, lc + 4, 16 * b + t);
+        factors();
     }
-    wave_exchange();
-#pragma unroll
-    for (int j = 0; j < 16; j++) x[j] = s[17 * t + j];
     const u64 q = uni64(m.q);
-    ulonglong2 w1[15];
-    int bd[16];
-    bounds_all(bd, 1);
-    inv_stages<WIDE, 2, 4>(x, bd, w2, q);
-    SCHED_FENCE();
-    tw_load<2, 4>(w1, tw, lc, b);                        // into the registers that the first two stages' factors leave
-    SCHED_FENCE();
-    inv_stages<WIDE, 0, 2>(x, bd, w2, q);
-    if (WIDE) settle4(x, bd, q);
-    SCHED_FENCE();
-    tw_load<0, 2>(w1, tw, lc, b);
-    SCHED_FENCE();
-    wave_exchange();
+    if constexpr (LANES == 16) {
+        wave_exchange();
 #pragma unroll
-    for (int j = 0; j < 16; j++) s[17 * t + j] = x[j];
-    wave_exchange();
+        for (int j = 0; j < 16; j++) x[j] = s[17 * t + j];
+        ulonglong2 w1[15];
+        int bd[16];
+        bounds_all(bd, 1);
+        inv_stages<WIDE, 2, 4>(x, bd, w2, q);
+        SCHED_FENCE();
+        tw_load<2, 4>(w1, tw, lc, b);                        // into the registers that the first two stages' factors leave
+        SCHED_FENCE();
+        inv_stages<WIDE, 0, 2>(x, bd, w2, q);
+        if (WIDE) settle4(x, bd, q);
+        SCHED_FENCE();
+        tw_load<0, 2>(w1, tw, lc, b);
+        SCHED_FENCE();
+        wave_exchange();
 #pragma unroll
-    for (int k = 0; k < 16; k++) x[k] = s[t + 17 * k];
-    bounds_all(bd, WIDE ? 4 : 32);
-    inv_stages<WIDE, 0, 4>(x, bd, w1, q);
-    if (WIDE) settle4(x, bd, q);
-    else {
+        for (int j = 0; j < 16; j++) s[17 * t + j] = x[j];
+        wave_exchange();
 #pragma unroll
-        for (int k = 0; k < 16; k++) x[k] = reduce_lazy<10>(x[k], q, m.bits, m.rec);
+        for (int k = 0; k < 16; k++) x[k] = s[t + 17 * k];
+        bounds_all(bd, WIDE ? 4 : 32);
+        inv_stages<WIDE, 0, 4>(x, bd, w1, q);
+        if (WIDE) settle4(x, bd, q);
+        else {
+#pragma unroll
+            for (int k = 0; k < 16; k++) x[k] = reduce_lazy<10>(x[k], q, m.bits, m.rec);
+        }
+#pragma unroll
+        for (int k = 0; k < 16; k++) out[t + 16 * k] = x[k];
+    } else {
+#pragma unroll
+        for (int i = 3; i >= 0; i--) {
+            if (i < 3 || IP) {
+                wave_exchange();
+#pragma unroll
+                for (int k = 0; k < 4; k++) x[k] = s[row4_at(i, t, k)];
+            }
+            inv_block2_r(x, w4[i], q);
+            if (i) {
+#pragma unroll
+                for (int k = 0; k < 4; k++) s[row4_at(i, t, k)] = x[k];
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < 4; k++) out[t + 64 * k] = x[k];
     }
-#pragma unroll
-    for (int k = 0; k < 16; k++) out[t + 16 * k] = x[k];
 }
 
-template <int IP, int BETA>
-__global__ __launch_bounds__(P2_THREADS, IP ? 3 : 4) void ntt_row_inv_kernel(P2Args a, LimbTab tab, IpPrologue ip) {
-    __shared__ u64 sm[16 * 272];
+template <int IP, int BETA, int LANES>
+__global__ __launch_bounds__(P2_THREADS, LANES == 16 && IP ? 3 : 4) void ntt_row_inv_kernel(P2Args a, LimbTab tab, IpPrologue ip) {
+    __shared__ u64 sm[P2_THREADS / LANES * 272];
     uint32_t tile;
-    const uint32_t e = row_decode(tab, a, tile);
+    const uint32_t e = row_decode<LANES>(tab, a, tile);
     if (e == TAB_NONE) return;
-    if (e & TAB_WIDE) row_inv<true, IP, BETA>(a, tab, branch_pin<true>(e), tile, sm, ip);
-    else row_inv<false, IP, BETA>(a, tab, branch_pin<false>(e), tile, sm, ip);
+    if (e & TAB_WIDE) row_inv<true, IP, BETA, LANES>(a, tab, branch_pin<true>(e), tile, sm, ip);
+    else row_inv<false, IP, BETA, LANES>(a, tab, branch_pin<false>(e), tile, sm, ip);
 }
 
 // ---------------------------------------------------------------- row passes of several limbs of one modulus
@@ -981,12 +1063,15 @@ int32_t probe_butterfly_rates(he_ctx* ctx, u64* d_out, uint32_t groups, double r
     case 8: hipLaunchKernelGGL((K<8, SECOND>), __VA_ARGS__); break;                                                  \
     default: hipLaunchKernelGGL((K<9, SECOND>), __VA_ARGS__); break;                                                 \
     }
+#define ROW_DISPATCH(K, FIRST, BETA_, ...)                                                                        \
+    if (wide_rows) hipLaunchKernelGGL((K<FIRST, BETA_, 64>), grid_rows, block, 0, ctx->stream, a, tab, __VA_ARGS__);  \
+    else hipLaunchKernelGGL((K<FIRST, BETA_, 16>), grid_rows, block, 0, ctx->stream, a, tab, __VA_ARGS__);
 #define BETA_DISPATCH(K, FIRST, BETA_, ...)                                                                       \
     switch (BETA_) {                                                                                                 \
-    case 1: hipLaunchKernelGGL((K<FIRST, 1>), __VA_ARGS__); break;                                                   \
-    case 2: hipLaunchKernelGGL((K<FIRST, 2>), __VA_ARGS__); break;                                                   \
-    case 3: hipLaunchKernelGGL((K<FIRST, 3>), __VA_ARGS__); break;                                                   \
-    default: hipLaunchKernelGGL((K<FIRST, 0>), __VA_ARGS__); break;                                                  \
+    case 1: ROW_DISPATCH(K, FIRST, 1, __VA_ARGS__) break;                                                            \
+    case 2: ROW_DISPATCH(K, FIRST, 2, __VA_ARGS__) break;                                                            \
+    case 3: ROW_DISPATCH(K, FIRST, 3, __VA_ARGS__) break;                                                            \
+    default: ROW_DISPATCH(K, FIRST, 0, __VA_ARGS__) break;                                                           \
     }
 
 int32_t launch_transform2p(he_ctx* ctx, const TransformDesc& d) {
@@ -1041,7 +1126,14 @@ int32_t launch_transform2p(he_ctx* ctx, const TransformDesc& d) {
     const uint32_t padded = (live + unit - 1) / unit * unit;
     if (padded > HE_MAX_LAUNCH_LIMBS) return he_fail(ctx, HE_ERR_BADARG, "transform: too many limbs in one launch");
     for (uint32_t i = live; i < padded; i++) tab.e[i] = TAB_NONE;
-    const dim3 block(P2_THREADS), grid_cols(live * tiles), grid_rows(padded * tiles);
+    // A row is shared by 64 threads instead of 16 while 16 would make at most 4 wavefronts per SIMD, about what the chip holds at
+    // once: such a launch is as long as one wavefront's chain of loads and butterflies, which is a fourth as long on four
+    // times the wavefronts.  One rotation at level 5: 72 -> 63 us; up to 2 wavefronts per SIMD a rotation pair at level 12
+    // took 174 us instead of 171, beyond 8 a block of layers 1262 instead of 1254.  A sum of several terms is always one
+    // output's limbs, each with a long chain of its own.
+    const bool terms = (d.ep && d.ep->fused && d.ep->n_terms) || (d.ip && d.ip->n_terms);
+    const bool wide_rows = terms || live * (ctx->N >> 10) <= 4096;
+    const dim3 block(P2_THREADS), grid_cols(live * tiles), grid_rows(padded * tiles * (wide_rows ? 4 : 1));
     for (int pass = 0; pass < 2; pass++) {
         if (d.only_pass && d.only_pass != (uint32_t)pass + 1) continue;
         hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -1054,17 +1146,17 @@ int32_t launch_transform2p(he_ctx* ctx, const TransformDesc& d) {
             if (d.rescale_from) { COL_DISPATCH(ntt_col_fwd_kernel, true, grid_cols, block, 0, ctx->stream, a, tab) }
             else { COL_DISPATCH(ntt_col_fwd_kernel, false, grid_cols, block, 0, ctx->stream, a, tab) }
         } else if (fwd) {
-            if (d.ep && d.ep->fused && d.ep->n_terms) hipLaunchKernelGGL((ntt_row_fwd_kernel<3, 0>), grid_rows, block, 0, ctx->stream, a, tab, *d.ep);
-            else if (d.ep && d.ep->fused) { BETA_DISPATCH(ntt_row_fwd_kernel, 2, d.ep->beta, grid_rows, block, 0, ctx->stream, a, tab, *d.ep) }
-            else if (d.ep) hipLaunchKernelGGL((ntt_row_fwd_kernel<1, 0>), grid_rows, block, 0, ctx->stream, a, tab, *d.ep);
-            else if (by_runs && a.lazy) hipLaunchKernelGGL((ntt_row_run_kernel<true, true>), dim3(n_runs * (ctx->N >> 10)), block, 0, ctx->stream, a, tab, runs);
-            else if (by_runs) hipLaunchKernelGGL((ntt_row_run_kernel<true, false>), dim3(n_runs * (ctx->N >> 10)), block, 0, ctx->stream, a, tab, runs);
-            else { ModDownEpilogue none = {}; hipLaunchKernelGGL((ntt_row_fwd_kernel<0, 0>), grid_rows, block, 0, ctx->stream, a, tab, none); }
+            if (d.ep && d.ep->fused && d.ep->n_terms) hipLaunchKernelGGL((ntt_row_fwd_kernel<3, 0, 64>), grid_rows, block, 0, ctx->stream, a, tab, *d.ep);
+            else if (d.ep && d.ep->fused) { BETA_DISPATCH(ntt_row_fwd_kernel, 2, d.ep->beta, *d.ep) }
+            else if (d.ep) { ROW_DISPATCH(ntt_row_fwd_kernel, 1, 0, *d.ep) }
+            else if (by_runs && !wide_rows && a.lazy) hipLaunchKernelGGL((ntt_row_run_kernel<true, true>), dim3(n_runs * (ctx->N >> 10)), block, 0, ctx->stream, a, tab, runs);
+            else if (by_runs && !wide_rows) hipLaunchKernelGGL((ntt_row_run_kernel<true, false>), dim3(n_runs * (ctx->N >> 10)), block, 0, ctx->stream, a, tab, runs);
+            else { ModDownEpilogue none = {}; ROW_DISPATCH(ntt_row_fwd_kernel, 0, 0, none) }
         } else if (pass == 0) {
-            if (d.ip && d.ip->n_terms) hipLaunchKernelGGL((ntt_row_inv_kernel<2, 0>), grid_rows, block, 0, ctx->stream, a, tab, *d.ip);
-            else if (d.ip) { BETA_DISPATCH(ntt_row_inv_kernel, 1, d.ip->beta, grid_rows, block, 0, ctx->stream, a, tab, *d.ip) }
-            else if (by_runs) hipLaunchKernelGGL((ntt_row_run_kernel<false, false>), dim3(n_runs * (ctx->N >> 10)), block, 0, ctx->stream, a, tab, runs);
-            else { IpPrologue none = {}; hipLaunchKernelGGL((ntt_row_inv_kernel<0, 0>), grid_rows, block, 0, ctx->stream, a, tab, none); }
+            if (d.ip && d.ip->n_terms) hipLaunchKernelGGL((ntt_row_inv_kernel<2, 0, 64>), grid_rows, block, 0, ctx->stream, a, tab, *d.ip);
+            else if (d.ip) { BETA_DISPATCH(ntt_row_inv_kernel, 1, d.ip->beta, *d.ip) }
+            else if (by_runs && !wide_rows) hipLaunchKernelGGL((ntt_row_run_kernel<false, false>), dim3(n_runs * (ctx->N >> 10)), block, 0, ctx->stream, a, tab, runs);
+            else { IpPrologue none = {}; ROW_DISPATCH(ntt_row_inv_kernel, 0, 0, none) }
         } else {
             if (d.scale) { COL_DISPATCH(ntt_col_inv_kernel, true, grid_cols, block, 0, ctx->stream, a, tab, *d.scale, d.scale_period) }
             else { ScaleList none; COL_DISPATCH(ntt_col_inv_kernel, false, grid_cols, block, 0, ctx->stream, a, tab, none, 1u) }

@@ -1,5 +1,5 @@
-"""GPU parity: transforms of launches whose row passes go by runs of one modulus (at least three limbs of every four lane
-quarters in use), at the edges of a run: 3 to 17 limbs of a modulus, narrow and wide moduli, extreme values - against the oracle."""
+"""GPU parity: transforms on both sides of the row passes' rules - rows of 64 threads for small launches, runs of one modulus
+for large ones - at the edges of a run, for narrow and wide moduli and extreme values, against the oracle."""
 import numpy as np
 import pytest
 
@@ -10,11 +10,12 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("logN,counts", [
-    (13, (4, 3, 3)),            # exactly three of four lanes
-    (13, (17, 16, 3)),          # one limb more than a run holds
-    (14, (8, 7, 5)),
-    (16, (1, 4, 16)),           # a lone limb among full runs
-    (17, (4, 4, 4)),
+    (13, (2, 1, 3)),            # few limbs: rows of 64 threads, the smallest ring
+    (14, (90, 91, 76)),         # one limb more than those take, runs of 16 with 10, 11 and 12 left over
+    (16, (21, 21, 22)),         # the last launch of 64 threads to a row ...
+    (16, (17, 16, 32)),         # ... and the first of runs, one limb more than a run holds
+    (16, (1, 34, 32)),          # a lone limb among full runs
+    (17, (12, 12, 9)),          # exactly three of four lanes in the last run
 ])
 def test_row_runs(logN, counts):
     from gpu_util import dev, host
