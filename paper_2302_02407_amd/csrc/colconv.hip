@@ -133,6 +133,79 @@ __device__ __forceinline__ void cc_target(u64* reg, u64* dst, uint32_t mi, const
     for (int j = 0; j < 16; j++) (dst + j * 256)[t * 4096 + c] = x[j];
 }
 
+// ---------------------------------------------------------------- tiles of 256 points, 4 per lane
+// For launches that leave the chip mostly idle: a fourth of the butterflies in a row and four times the work groups.  Point
+// e = row * C + column of the tile; block i runs stages 2i and 2i + 1 (with odd LC the last block only its first), where lane
+// t holds points c4_point(i, t, k).
+__device__ __forceinline__ uint32_t c4_point(int i, uint32_t t, int k) {
+    const uint32_t ls = 6 - 2 * i;
+    return ((t >> ls) << (ls + 2)) + (t & ((1u << ls) - 1u)) + ((uint32_t)k << ls);
+}
+__device__ __forceinline__ uint32_t c4_word(uint32_t e) { return e + (e >> 4); }
+template <int LC>
+struct C4 {
+    static constexpr int LCOLS = 8 - LC, NB = (LC + 1) / 2;
+    static __device__ __forceinline__ uint32_t at(uint32_t e, uint32_t c0) { return ((e >> LCOLS) << 8) + c0 + (e & ((1u << LCOLS) - 1u)); }
+};
+template <int LC>
+__device__ __forceinline__ void c4_factors(u64 (&w)[4][6], const ulonglong2* tw, uint32_t t) {
+#pragma unroll
+    for (int i = 0; i < C4<LC>::NB; i++) tw_block2(w[i], tw, 2 * i, t >> (6 - 2 * i));
+}
+template <int LC>
+__device__ __forceinline__ void c4_source(u64* reg, const u64* src, const ScaleList& sc, uint32_t mi, uint32_t si, uint32_t t, uint32_t c0,
+                                          const ModConst* mc, const ulonglong2* itw) {
+    using G = C4<LC>;
+    u64 x[4], w[4][6];
+#pragma unroll
+    for (int k = 0; k < 4; k++) x[k] = src[G::at(c4_point(G::NB - 1, t, k), c0)];
+    c4_factors<LC>(w, itw + ((size_t)mi << (LC + 8)), t);
+    const u64 q = uni64(mc[mi].q), cs = sc.s[si], cs_sh = sc.s_sh[si];
+#pragma unroll
+    for (int i = G::NB - 1; i >= 0; i--) {
+        if (i + 1 < G::NB) {
+            wave_exchange();
+#pragma unroll
+            for (int k = 0; k < 4; k++) x[k] = reg[c4_word(c4_point(i, t, k))];
+        }
+        if (2 * i + 1 < LC) {
+            inv_block2_r(x, w[i], q);
+        } else {
+            int b[4] = {4, 4, 4, 4};
+            gs_bfly<true>(x[0], x[2], b[0], b[2], w[i][0], w[i][1], q);
+            gs_bfly<true>(x[1], x[3], b[1], b[3], w[i][0], w[i][1], q);
+            settle4(x, b, q);
+        }
+#pragma unroll
+        for (int k = 0; k < 4; k++)
+            reg[c4_word(c4_point(i, t, k))] = i ? x[k] : csub(shoup_lazy(x[k], cs, cs_sh, q), q) ^ 0x8080808080808080ull;
+    }
+}
+template <int LC, bool WIDE>
+__device__ __forceinline__ void c4_target(u64* reg, u64* dst, uint32_t mi, const u64 (&w)[4][6], uint32_t t, uint32_t c0, const ModConst* mc) {
+    using G = C4<LC>;
+    const u64 q = uni64(mc[mi].q), q4 = 4 * q;
+    u64 x[4];
+#pragma unroll
+    for (int i = 0; i < G::NB; i++) {
+        if (i) wave_exchange();
+#pragma unroll
+        for (int k = 0; k < 4; k++) x[k] = reg[c4_word(c4_point(i, t, k))];
+        if (2 * i + 1 < LC) {
+            fwd_block2_r<WIDE>(x, w[i], q, q4);
+        } else {
+            ct_bfly_u<WIDE>(0, x[0], x[2], w[i][0], w[i][1], q, q4);
+            ct_bfly_u<WIDE>(0, x[1], x[3], w[i][0], w[i][1], q, q4);
+        }
+        if (i + 1 < G::NB) {
+#pragma unroll
+            for (int k = 0; k < 4; k++) reg[c4_word(c4_point(i, t, k))] = x[k];
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < 4; k++) dst[G::at(c4_point(G::NB - 1, t, k), c0)] = x[k];
+}
+
 template <bool WIDE>
 __device__ __forceinline__ uint32_t cc_pin(uint32_t v) {   // keeps the two widths' loads apart (see ntt2p.hip)
     if (WIDE) asm("; wide" : "+s"(v));
@@ -142,31 +215,36 @@ __device__ __forceinline__ uint32_t cc_pin(uint32_t v) {   // keeps the two widt
 
 // grid: groups * tiles.  Work groups go to the XCDs round-robin: each XCD gets neighbouring tiles of a group, so that the
 // tiles that share a memory line are read and written through one L2.
-template <int LC>
+template <int LC, int PTS>
 __global__ __launch_bounds__(CC_THREADS, 4) void col_conv_kernel(ColConv cc, ScaleList sc, const ModConst* mc, const ulonglong2* ftw,
                                                                  const ulonglong2* itw) {
-    constexpr int LCOLS = 10 - LC, TPX = (256 >> LCOLS) / 8;             // tiles of a group per XCD
-    __shared__ u64 lds[CC_WAVES * CC_REGION];
+    constexpr int LCOLS = (PTS == 16 ? 10 : 8) - LC, TPX = (256 >> LCOLS) / 8;       // tiles of a group per XCD
+    constexpr int REGION = PTS == 16 ? CC_REGION : 272, NB = PTS / 2;                // LDS words of a limb's tile, blocks of 16 points per wavefront
+    __shared__ u64 lds[CC_WAVES * REGION];
+    auto point = [](uint32_t w, int b, uint32_t p16) {
+        return PTS == 16 ? cc_word(2 * w + (b >> 2), 16 * (b & 3) + p16) : c4_word(32 * w + 16 * b + p16);
+    };
     const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const uint32_t slot = blockIdx.x >> 3, tile = (blockIdx.x & 7u) * TPX + slot % TPX, gp = slot / TPX, grp = gp / cc.parts;
     const uint32_t set = grp % cc.n_sets, rep = grp / cc.n_sets, c0 = tile << LCOLS;
     const ColConvSet& st = cc.set[set];
-    u64* reg = lds + w * CC_REGION;
+    u64* reg = lds + w * REGION;
     if (w < st.ns) {
         const u64* src = st.src + (size_t)rep * cc.src_stride + ((size_t)w << (LC + 8));
         const uint32_t mi = st.mod0 + w;
-        if (cc.wide_inv >> mi & 1u) cc_source<LC, true>(reg, src, cc, sc, cc_pin<true>(mi), st.sc0 + w, lane, c0, mc, itw);
+        if constexpr (PTS == 4) c4_source<LC>(reg, src, sc, mi, st.sc0 + w, lane, c0, mc, itw);
+        else if (cc.wide_inv >> mi & 1u) cc_source<LC, true>(reg, src, cc, sc, cc_pin<true>(mi), st.sc0 + w, lane, c0, mc, itw);
         else cc_source<LC, false>(reg, src, cc, sc, cc_pin<false>(mi), st.sc0 + w, lane, c0, mc, itw);
     }
     __syncthreads();
-    // this wavefront's 128 points of every source: runs 2w and 2w+1; lane group g = lane / 16 holds sources 2g, 2g+1 of 16
+    // this wavefront's eighth of the points of every source; lane group g = lane / 16 holds sources 2g, 2g+1 of 16
     // points, in memory order the bytes k = 16g .. 16g+15 of the contraction
-    v4i frag[8];
+    v4i frag[NB];
 #pragma unroll
-    for (int b = 0; b < 8; b++) {
-        const uint32_t g = lane >> 4, word = cc_word(2 * w + (b >> 2), 16 * (b & 3) + (lane & 15));
-        const u64 y0 = 2 * g < st.ns ? lds[(2 * g) * CC_REGION + word] : 0;
-        const u64 y1 = 2 * g + 1 < st.ns ? lds[(2 * g + 1) * CC_REGION + word] : 0;
+    for (int b = 0; b < NB; b++) {
+        const uint32_t g = lane >> 4, word = point(w, b, lane & 15);
+        const u64 y0 = 2 * g < st.ns ? lds[(2 * g) * REGION + word] : 0;
+        const u64 y1 = 2 * g + 1 < st.ns ? lds[(2 * g + 1) * REGION + word] : 0;
         frag[b] = v4i{(int)(uint32_t)y0, (int)(uint32_t)(y0 >> 32), (int)(uint32_t)y1, (int)(uint32_t)(y1 >> 32)};
     }
     const uint32_t tb = (gp - grp * cc.parts) * cc.share, nt = min(st.nt, tb + cc.share);
@@ -196,8 +274,10 @@ __global__ __launch_bounds__(CC_THREADS, 4) void col_conv_kernel(ColConv cc, Sca
         // this wavefront's target and the factors of its first block, which arrive during the conversion
         const bool have = t0 + w < nt;
         const uint32_t mi = have ? (uint32_t)(mods >> (8 * w)) & 255u : mod_first;
-        ulonglong2 w1[15];
-        tw_load_c<0, 4>(w1, (ctw_t)(uintptr_t)(ftw + ((size_t)mi << (LC + 8))), 0, 0);
+        ulonglong2 w1[15];                                   // 16 points per lane
+        u64 w4[4][6];                                        // 4 points: all factors
+        if constexpr (PTS == 16) tw_load_c<0, 4>(w1, (ctw_t)(uintptr_t)(ftw + ((size_t)mi << (LC + 8))), 0, 0);
+        else c4_factors<LC>(w4, ftw + ((size_t)mi << (LC + 8)), ln);
         __syncthreads();                                     // the regions are free (operands read, last targets done)
 #pragma unroll
         for (int s = 0; s < 2; s++) {
@@ -205,9 +285,9 @@ __global__ __launch_bounds__(CC_THREADS, 4) void col_conv_kernel(ColConv cc, Sca
             const uint32_t tg = t0 + 4 * s + g;
             // quotient of a value below 2^(bits+14) from its top: sh = bits - 18 (at least 32)
             const uint32_t sh = bits[s] > 50 ? bits[s] - 18 : 32, e = bits[s] - 1 - sh;
-            u64* out = lds + (4 * s + g) * CC_REGION;
+            u64* out = lds + (4 * s + g) * REGION;
 #pragma unroll
-            for (int b = 0; b < 8; b++) {
+            for (int b = 0; b < NB; b++) {
                 const v4i d0 = __builtin_amdgcn_mfma_i32_16x16x64_i8(a0[s], frag[b], k0[s], 0, 0, 0);
                 const v4i d1 = __builtin_amdgcn_mfma_i32_16x16x64_i8(a1[s], frag[b], k1[s], 0, 0, 0);
                 const int p01 = d0.x + (d0.y << 8), p23 = d0.z + (d0.w << 8), p45 = d1.x + (d1.y << 8), p67 = d1.z + (d1.w << 8);
@@ -216,14 +296,17 @@ __global__ __launch_bounds__(CC_THREADS, 4) void col_conv_kernel(ColConv cc, Sca
                 u64 v = ((u64)(uint32_t)hi << 32) | (uint32_t)lo;
                 v += (u64)qh * n0[s];
                 v = ((u64)add3((uint32_t)(v >> 32), qh * n1[s], 0) << 32) | (uint32_t)v;
-                if (tg < nt) out[cc_word(2 * w + (b >> 2), 16 * (b & 3) + p16)] = v;
+                if (tg < nt) out[point(w, b, p16)] = v;
             }
         }
         __syncthreads();
         if (have) {
             const uint32_t li = (uint32_t)(lims >> (8 * w)) & 255u;
             u64* dst = st.dst + (size_t)rep * cc.dst_stride + ((size_t)li << (LC + 8));
-            if (cc.wide_fwd >> mi & 1u) cc_target<LC, true>(reg, dst, cc_pin<true>(mi), w1, ln, c0, mc, ftw);
+            if constexpr (PTS == 4) {
+                if (cc.wide_fwd >> mi & 1u) c4_target<LC, true>(reg, dst, mi, w4, ln, c0, mc);
+                else c4_target<LC, false>(reg, dst, mi, w4, ln, c0, mc);
+            } else if (cc.wide_fwd >> mi & 1u) cc_target<LC, true>(reg, dst, cc_pin<true>(mi), w1, ln, c0, mc, ftw);
             else cc_target<LC, false>(reg, dst, cc_pin<false>(mi), w1, ln, c0, mc, ftw);
         }
     }
@@ -247,19 +330,23 @@ int32_t launch_col_conv(he_ctx* ctx, ColConv& cc, const ScaleList& sc, uint32_t 
         HE_HIP(ctx, hipEventCreate(&e1));
         HE_HIP(ctx, hipEventRecord(e0, ctx->stream));
     }
+    const uint32_t tiles16 = 1u << (LC - 2);
+    // Tiles of 256 points while the rounds of all 1024-point tiles would not give every second compute unit a work group: one
+    // rotation at level 5 66 -> 59 us; at twice that a ciphertext product (level 11) took 143 us instead of 136.
+    const bool small = groups * tiles16 * rounds <= 128;
+    const uint32_t work = groups * tiles16 * (small ? 4 : 1);
     // while two work groups per compute unit have room for it, the rounds of a tile run side by side (a relinearisation at
     // level 11 and its rescale: 161 -> 156 us)
-    const uint32_t work = groups << (LC - 2);
     const uint32_t parts = std::max(1u, std::min(rounds, 512 / work));
     cc.share = (rounds + parts - 1) / parts * CC_WAVES;
     cc.parts = (rounds * CC_WAVES + cc.share - 1) / cc.share;
     const dim3 grid(work * cc.parts), block(CC_THREADS);
-    switch (LC) {
-    case 5: hipLaunchKernelGGL(col_conv_kernel<5>, grid, block, 0, ctx->stream, cc, sc, ctx->d_mc, ctx->d_tw, ctx->d_itw); break;
-    case 6: hipLaunchKernelGGL(col_conv_kernel<6>, grid, block, 0, ctx->stream, cc, sc, ctx->d_mc, ctx->d_tw, ctx->d_itw); break;
-    case 7: hipLaunchKernelGGL(col_conv_kernel<7>, grid, block, 0, ctx->stream, cc, sc, ctx->d_mc, ctx->d_tw, ctx->d_itw); break;
-    default: hipLaunchKernelGGL(col_conv_kernel<8>, grid, block, 0, ctx->stream, cc, sc, ctx->d_mc, ctx->d_tw, ctx->d_itw); break;
-    }
+#define CC_LAUNCH(LC_)                                                                                                                        \
+    case LC_:                                                                                                                                 \
+        if (small) hipLaunchKernelGGL((col_conv_kernel<LC_, 4>), grid, block, 0, ctx->stream, cc, sc, ctx->d_mc, ctx->d_tw, ctx->d_itw);        \
+        else hipLaunchKernelGGL((col_conv_kernel<LC_, 16>), grid, block, 0, ctx->stream, cc, sc, ctx->d_mc, ctx->d_tw, ctx->d_itw);             \
+        break;
+    switch (LC) { CC_LAUNCH(5) CC_LAUNCH(6) CC_LAUNCH(7) CC_LAUNCH(8) }
     HE_HIP(ctx, hipGetLastError());
     if (ctx->prof_on) {
         HE_HIP(ctx, hipEventRecord(e1, ctx->stream));

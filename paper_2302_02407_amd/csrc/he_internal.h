@@ -88,7 +88,6 @@ struct he_ctx {
     bool prof_on;                       // time every transform launch with an event pair
     std::vector<ProfSpan> prof_events;
     uint64_t prof_key_limbs;            // key limbs the inner products had to read while timing was on (one pass per key per chunk)
-    uint32_t cf_max_groups, cf_max_targets;   // N = 2^16 latency path: largest conversion (groups, targets per group) that takes the single-launch column kernel
     std::string err;
 };
 
@@ -197,33 +196,12 @@ struct TransformDesc {
                                  // h = floor(q_l / 2): the rounding term of Rescale, negated; 0 = sources as they are
 };
 
-// N = 2^16 latency path: [inverse column pass -> basis conversion -> forward column pass] of several groups in one launch.
-// Group g: sources src + i*N (i < ns, moduli mod0 + i, output scaling sc entry sc0 + i) in the state the inverse row
-// pass leaves them; targets of its set: target t has modulus tgt_mod[set][t] and is written, in the state the forward
-// column pass leaves it, at dst + tgt_limb[set][t]*N; conversion constants hat[modulus*hat_w + i].
-#define CF_MAX_GROUPS 32
-#define CF_MAX_SETS 4
-// Per-group fields are all 32 or 64 bits wide on purpose.  The group index is uniform, so the compiler reads these
-// through scalar loads, and it is free to split an aligned address into a base register and an offset register
-// that are each misaligned (it did, for byte-sized per-group arrays: base = args + g, offset = 7g).  The hardware
-// drops the two low bits of each register separately, and the load then returns the wrong words.
-struct CfGroup {
-    const u64* src;
-    u64* dst;
-    const u64* hat;
-    uint32_t ns, mod0, sc0, set;
-};
-struct ColFuse {
-    CfGroup grp[CF_MAX_GROUPS];
-    uint32_t hat_w, n_groups;
-    uint32_t nt[CF_MAX_SETS];
-    uint8_t tgt_limb[CF_MAX_SETS][HE_MAX_MODULI];     // indexed per wavefront: vector loads
-    uint8_t tgt_mod[CF_MAX_SETS][HE_MAX_MODULI];
-};
 // Basis conversion with the column passes around it (colconv.hip).  Set s (a digit of ModUp; the special primes of ModDown):
 // sources src + rep*src_stride + i*N (i < ns, moduli mod0 + i, output scaling sc entry sc0 + i) in the state the inverse
 // row pass leaves them; target t has modulus mod[t] and is written, in the state the forward column pass leaves it, at
 // dst + rep*dst_stride + limb[t]*N.  digits / bias: conversion constants per modulus (conv_operand).
+// The arrays of bytes start at multiples of 8 and are read eight at a time: a scalar load of a narrower field could be split
+// into a base and an offset register that are each misaligned, whose low bits the hardware drops one by one.
 #define CC_MAX_SETS 8
 struct ColConvSet {
     const u64* src;
@@ -231,7 +209,7 @@ struct ColConvSet {
     const uint8_t* digits;     // [modulus][512]
     const int32_t* bias;       // [modulus][8]
     uint32_t ns, mod0, sc0, nt;
-    uint8_t limb[HE_MAX_MODULI], mod[HE_MAX_MODULI];   // indexed per lane or wavefront: vector loads
+    uint8_t limb[HE_MAX_MODULI], mod[HE_MAX_MODULI];
 };
 struct ColConv {
     ColConvSet set[CC_MAX_SETS];
@@ -241,7 +219,6 @@ struct ColConv {
     uint32_t parts, share;     // work groups that share a tile's targets, `share` targets each (set by the launch)
 };
 int32_t launch_col_conv(he_ctx* ctx, ColConv& cc, const ScaleList& sc, uint32_t reps, uint32_t limb_passes);
-int32_t launch_colfuse(he_ctx* ctx, const ColFuse& cf, const ScaleList& sc, uint32_t limb_passes);   // ntt2p.hip
 // fills w / w_sh of entry i from s (modulus index mi)
 void scale_entry(const he_ctx* c, ScaleList& sc, uint32_t i, uint32_t mi, u64 s);
 int32_t launch_transform(he_ctx* ctx, const TransformDesc& d);

@@ -4,10 +4,10 @@
 //   ModUp   : digit limbs -> coefficient form (iNTT with the factor (Q_j/q_i)^-1 folded into
 //             the N^-1 scaling) -> fast basis conversion to every other limb of
 //             {q_0..q_l, p_*} (128-bit accumulation, one Barrett step) -> NTT.
-//   inner   : acc_c[r] = sum_j sigma_g(raised_j)[r] * evk_j,c[r]   (sigma_g as a gather).  At N = 2^16 this
+//   inner   : acc_c[r] = sum_j sigma_g(raised_j)[r] * evk_j,c[r]   (sigma_g as a gather).  From N = 2^13 this
 //             sum is evaluated inside the transforms of ModDown that consume it (special-prime limbs as
 //             the first inverse pass loads its rows, q-limbs in the epilogue of the last forward pass)
-//             and acc is never stored; other ring sizes run the stand-alone kernels below.
+//             and acc is never stored; smaller rings run the stand-alone kernels below.
 //   ModDown : p-limbs -> coefficient form (iNTT with (P/p_t)^-1 folded in) -> conversion to
 //             q_0..q_l -> NTT -> (acc - conv) * P^-1 (+ sigma_g(c0) for a rotation).
 // Neither conversion corrects the overflow multiple; each term is a canonical residue and
@@ -57,7 +57,7 @@ struct ConvBatch {
 // the 128-bit sum is assembled once per output (all moduli are below 2^60).
 //
 // LAZY: outputs are left in [0, 5q) (congruent, not canonical); only for buffers whose sole consumer
-// is the N = 2^16 forward transform, whose lazy bounds absorb it.
+// is the two-launch forward transform (N >= 2^13), whose lazy bounds absorb it.
 template <bool ONE_CHUNK, bool LAZY>
 __global__ __launch_bounds__(KS_THREADS) void baseconv_kernel(ConvBatch b, const ModConst* mc, uint32_t logN) {
     __shared__ u64 s_hat[CONV_TGT_PER_BLOCK * 64];
@@ -422,14 +422,6 @@ size_t ks_engine_ws_elems(const he_ctx* c, uint32_t level, uint32_t n_src, uint3
     return ((size_t)cb * (beta * R + L1) + (size_t)jb * (2 * R + 2 * k + 2 * L1)) * c->N;
 }
 
-// Whether a conversion of `groups` groups (at most `ns` sources and `nt` targets each, `sets` target sets) takes the
-// single-launch column path: N = 2^16 only, and only while its work groups (256 per group, a few per compute unit)
-// fit the chip about once, beyond which the separate throughput kernels win.
-static bool colfuse_ok(const he_ctx* c, uint32_t groups, uint32_t sets, uint32_t ns, uint32_t nt) {
-    return c->logN == 16 && groups <= c->cf_max_groups && groups <= CF_MAX_GROUPS && sets <= CF_MAX_SETS && ns <= 8 &&
-           nt <= c->cf_max_targets && nt <= HE_MAX_MODULI;
-}
-
 static void col_conv_widths(const he_ctx* c, ColConv& cc) {
     for (uint32_t m = 0; m < c->M; m++) {
         cc.wide_fwd |= (u64)(c->h_mc[m].bits > 57) << m;
@@ -448,9 +440,7 @@ static int32_t modup_batch(he_ctx* c, const KsSrc* srcs, uint32_t cb, uint32_t l
         u64 qi = c->mod[i];
         scale_entry(c, sc, i, i, h_mulmod(c->h_mc[i].ninv, c->h_up_invhat[(size_t)(j * al + (sz - 1)) * al + (i - lo)], qi));
     }
-    // small launches at N = 2^16: the column passes and the conversion run as one launch between the two row passes
-    const bool cf_on = colfuse_ok(c, cb * beta, beta, al, R) && cb * beta * R <= HE_MAX_LAUNCH_LIMBS;
-    const bool cc_on = !cf_on && c->d_up_dig && beta <= CC_MAX_SETS && beta * R <= HE_MAX_LAUNCH_LIMBS;
+    const bool cc_on = c->d_up_dig && beta <= CC_MAX_SETS && beta * R <= HE_MAX_LAUNCH_LIMBS;
     {
         std::vector<uint32_t> mods(cb * L1);
         std::vector<uint8_t> seg(cb * L1);
@@ -463,7 +453,7 @@ static int32_t modup_batch(he_ctx* c, const KsSrc* srcs, uint32_t cb, uint32_t l
         }
         t.mod_idx = mods.data(); t.src_seg = seg.data(); t.src_limb = lim.data();
         t.scale = &sc; t.scale_period = L1;
-        t.only_pass = (cf_on || cc_on) ? 1u : 0u;
+        t.only_pass = cc_on ? 1u : 0u;
         int32_t rc = launch_transform(c, t);
         if (rc != HE_OK) return rc;
     }
@@ -488,30 +478,6 @@ static int32_t modup_batch(he_ctx* c, const KsSrc* srcs, uint32_t cb, uint32_t l
             passes += sz + st.nt;
         }
         int32_t rc = launch_col_conv(c, cc, sc, cb, cb * passes);
-        if (rc != HE_OK) return rc;
-    } else if (cf_on) {
-        ColFuse cf = {};
-        cf.hat_w = aw; cf.n_groups = cb * beta;
-        uint32_t passes = 0;
-        for (uint32_t j = 0; j < beta; j++) {
-            uint32_t lo = j * al, hi = (j + 1) * al < L1 ? (j + 1) * al : L1, sz = hi - lo, nt = 0;
-            for (uint32_t r = 0; r < R; r++) {
-                if (r >= lo && r < hi) continue;
-                cf.tgt_limb[j][nt] = (uint8_t)r;
-                cf.tgt_mod[j][nt] = (uint8_t)(r <= level ? r : c->nq + (r - level - 1));
-                nt++;
-            }
-            cf.nt[j] = nt;
-            for (uint32_t s = 0; s < cb; s++) {
-                const uint32_t g = s * beta + j;
-                cf.grp[g].src = tmp + ((size_t)s * L1 + lo) * N;
-                cf.grp[g].dst = raised + ((size_t)s * beta + j) * R * N;
-                cf.grp[g].hat = c->d_up_hat + (size_t)(j * al + (sz - 1)) * c->M * aw;
-                cf.grp[g].ns = sz; cf.grp[g].mod0 = lo; cf.grp[g].sc0 = lo; cf.grp[g].set = j;
-                passes += sz + nt;
-            }
-        }
-        int32_t rc = launch_colfuse(c, cf, sc, passes);
         if (rc != HE_OK) return rc;
     } else {
     for (uint32_t j0 = 0; j0 < beta; j0 += CONV_MAX_JOBS) {
@@ -562,7 +528,7 @@ static int32_t modup_batch(he_ctx* c, const KsSrc* srcs, uint32_t cb, uint32_t l
             t.fwd = true; t.seg[0] = raised + (size_t)s0 * per_src * N; t.n_seg = 1; t.dst = raised + (size_t)s0 * per_src * N;
             t.n = ns * per_src; t.mod_idx = rep.data();
             t.lazy_out = true;      // raised digits are only ever multiplied into sums with room for values below 2q
-            t.only_pass = (cf_on || cc_on) ? 2u : 0u;
+            t.only_pass = cc_on ? 2u : 0u;
             int32_t rc = launch_transform(c, t);
             if (rc != HE_OK) return rc;
         }
@@ -595,14 +561,13 @@ static int32_t launch_inner_product(he_ctx* c, uint32_t level, const IpBatch& ib
     return HE_OK;
 }
 
-// The ModDown of J accumulators (each [2][R][N]; on the fused N = 2^16 path they are never stored and `ip` / `ep`
+// The ModDown of J accumulators (each [2][R][N]; from N = 2^13 they are never stored and `ip` / `ep`
 // describe how the transforms compute them): special-prime limbs -> coefficient form (pre-multiplied by
 // N^-1 * (P/p_t)^-1), conversion to q_0..q_level, forward transform with the epilogue described by `ep`.
 static int32_t moddown_chain(he_ctx* c, uint32_t level, uint32_t J, u64* acc, u64* tmp_dn, u64* conv, const IpPrologue* ip,
                              const ModDownEpilogue& ep) {
     const uint32_t N = c->N, L1 = level + 1, k = c->np, R = L1 + k;
-    const bool cf_on = colfuse_ok(c, 2 * J, 1, k, L1) && 2 * J * std::max(k, L1) <= HE_MAX_LAUNCH_LIMBS;
-    const bool cc_on = !cf_on && c->d_dn_dig != nullptr;
+    const bool cc_on = c->d_dn_dig != nullptr;
     ScaleList sc;
     for (uint32_t t = 0; t < k; t++) {
         u64 p = c->mod[c->nq + t];
@@ -621,7 +586,7 @@ static int32_t moddown_chain(he_ctx* c, uint32_t level, uint32_t J, u64* acc, u6
         t.fwd = false; t.seg[0] = acc; t.n_seg = 1; t.dst = tmp_dn; t.n = n;
         t.mod_idx = mods.data(); t.src_limb = lim.data(); t.scale = &sc; t.scale_period = k;
         t.ip = ip;
-        t.only_pass = (cf_on || cc_on) ? 1u : 0u;
+        t.only_pass = cc_on ? 1u : 0u;
         int32_t rc = launch_transform(c, t);
         if (rc != HE_OK) return rc;
     }
@@ -634,19 +599,6 @@ static int32_t moddown_chain(he_ctx* c, uint32_t level, uint32_t J, u64* acc, u6
         st.ns = k; st.mod0 = c->nq; st.sc0 = 0; st.nt = L1;
         for (uint32_t r = 0; r < L1; r++) { st.limb[r] = (uint8_t)r; st.mod[r] = (uint8_t)r; }
         int32_t rc = launch_col_conv(c, cc, sc, 2 * J, 2 * J * (k + L1));
-        if (rc != HE_OK) return rc;
-    } else if (cf_on) {
-        ColFuse cf = {};
-        cf.hat_w = pad8(k); cf.n_groups = 2 * J;
-        cf.nt[0] = L1;
-        for (uint32_t r = 0; r < L1; r++) { cf.tgt_limb[0][r] = (uint8_t)r; cf.tgt_mod[0][r] = (uint8_t)r; }
-        for (uint32_t g = 0; g < 2 * J; g++) {
-            cf.grp[g].src = tmp_dn + (size_t)g * k * N;
-            cf.grp[g].dst = conv + (size_t)g * L1 * N;
-            cf.grp[g].hat = c->d_dn_hat;
-            cf.grp[g].ns = k; cf.grp[g].mod0 = c->nq; cf.grp[g].sc0 = 0; cf.grp[g].set = 0;
-        }
-        int32_t rc = launch_colfuse(c, cf, sc, 2 * J * (k + L1));
         if (rc != HE_OK) return rc;
     } else {
         ConvBatch b;
@@ -666,7 +618,7 @@ static int32_t moddown_chain(he_ctx* c, uint32_t level, uint32_t J, u64* acc, u6
         TransformDesc t = {};
         t.fwd = true; t.seg[0] = conv; t.n_seg = 1; t.dst = conv; t.n = n; t.mod_idx = mods.data(); t.ep = &ep;
         t.lazy_out = true;
-        t.only_pass = (cf_on || cc_on) ? 2u : 0u;
+        t.only_pass = cc_on ? 2u : 0u;
         int32_t rc = launch_transform(c, t);
         if (rc != HE_OK) return rc;
     }
@@ -693,7 +645,7 @@ static int32_t inner_moddown_batch(he_ctx* c, uint32_t level, const KsSrc* srcs,
         }
     }
     if (c->prof_on) c->prof_key_limbs += (uint64_t)groups * 2 * beta * R;
-    // On the N = 2^16 path no accumulator is materialised: the special-prime limbs of the inner product are
+    // From N = 2^13 no accumulator is materialised: the special-prime limbs of the inner product are
     // computed by the first pass of their inverse transform, the q-limbs inside the ModDown epilogue (they would
     // only be written here and read back there).  Other rings run the stand-alone kernel.
     const bool fused = two_pass(c) && beta <= 8;
@@ -1339,7 +1291,7 @@ int32_t rescale_batch(he_ctx* ctx, const u64* const* cts, u64* const* outs, uint
         int32_t rc = launch_transform(ctx, t);
         if (rc != HE_OK) return rc;
         // forward transform of -delta whose epilogue writes (c - (-delta)) * q_l^-1: the input limb plays the stored
-        // accumulator (component stride level+1 limbs), q_l^-1 mod q_r the constant of the final product.  At N = 2^16
+        // accumulator (component stride level+1 limbs), q_l^-1 mod q_r the constant of the final product.  From N = 2^13
         // the first pass forms -delta from the dropped limb's coefficients as it reads them; otherwise a kernel does.
         const uint32_t total = 2 * nb * level;
         const bool fused_delta = two_pass(ctx);

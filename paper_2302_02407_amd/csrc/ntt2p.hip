@@ -845,159 +845,6 @@ __global__ __launch_bounds__(P2_THREADS, 4) void ntt_row_run_kernel(P2Args a, Li
     }
 }
 
-// ---------------------------------------------------------------- column passes fused around the basis conversion
-// Latency path for small launches (a few limbs: the low levels the paper's networks run at), where the chip is mostly
-// idle and a call is bound by its chain of dependent launches.  The last inverse pass, the basis conversion and the
-// first forward pass all work on columns of the 256 x 256 view, so one work group takes ONE column through all
-// three: every source limb of a group (a digit of ModUp, the special-prime limbs of one ModDown component; at most 8)
-// goes through the inverse column stages and its output scaling into LDS, then every target limb is converted from
-// those (128-bit sums, lazy Barrett), run through the forward column stages and written.  One launch instead of
-// three; the coefficient-form limbs and the converted limbs never exist in memory.  One wavefront per limb, four
-// points per lane (two stages in registers, then an exchange through LDS), so that a conversion of a single digit
-// already spreads over every compute unit; the 8-byte accesses this makes (a column is strided by 2 KiB) cost
-// bandwidth that a launch this small does not need.
-#define CF_THREADS 512
-#define CF_WAVES 8
-#define CF_EX 272            // 256 points + one spare per 16
-
-__device__ __forceinline__ uint32_t cf_pos(uint32_t i) { return i + (i >> 4); }
-
-__global__ __launch_bounds__(CF_THREADS) void ntt16_colfuse_kernel(ColFuse cf, ScaleList sc, const ModConst* mc, const ulonglong2* tw,
-                                                                   const ulonglong2* itw) {
-    __shared__ u64 ys[CF_WAVES * 256];
-    __shared__ u64 ex[CF_WAVES * CF_EX];
-    // work groups go to the XCDs round-robin: give each XCD 32 adjacent columns, so that the sixteen columns that
-    // share a 128-byte line are read and written through one L2
-    const uint32_t g = blockIdx.x >> 8, c = (blockIdx.x & 7) * 32 + ((blockIdx.x >> 3) & 31);
-    const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;   // w: the same for the wavefront
-    const CfGroup gp = cf.grp[g];
-    const uint32_t ns = gp.ns, set = gp.set, nt = cf.nt[set];
-    u64* exw = ex + w * CF_EX;
-    u64 x[4];
-    // Everything a wavefront will need is requested before anything is computed, so that the dependent memory round
-    // trips (arguments -> constants of the modulus -> data and twiddles) are paid once, not once per phase: the source
-    // limb's points and all its twiddles, and for the first target limb its modulus and conversion constants.
-    const bool src_on = w < ns;
-    const uint32_t mi = gp.mod0 + (src_on ? w : 0);
-    const u64* data = gp.src + ((size_t)(src_on ? w : 0) << 16) + c;
-    if (src_on) {
-#pragma unroll
-        for (int k = 0; k < 4; k++) x[k] = data[(size_t)(4 * lane + k) * 256];
-    }
-    u64 t1[4][6];
-#pragma unroll
-    for (int blk = 0; blk < 4; blk++) tw_block2(t1[blk], itw + ((size_t)mi << 16), 2 * blk, lane >> (6 - 2 * blk));
-    const ModConst m1 = mc[mi];
-    const uint32_t si = gp.sc0 + (src_on ? w : 0);
-    const u64 cs = sc.s[si], cs_sh = sc.s_sh[si];
-    uint32_t mr = __builtin_amdgcn_readfirstlane(cf.tgt_mod[set][w < nt ? w : 0]);
-    ModConst m2 = mc[mr];
-    u64 hat[CF_WAVES];                                       // a row of the table is padded to 8 entries, zeros past ns
-#pragma unroll
-    for (int i = 0; i < CF_WAVES; i++) hat[i] = gp.hat[(size_t)mr * cf.hat_w + i];
-    {   // inverse column stages 7..0 of source w (wavefronts beyond the group's sources idle through the barriers)
-        const u64 q = uni64(m1.q);
-#pragma unroll
-        for (int blk = 3; blk >= 0; blk--) {
-            const uint32_t s0 = 2 * blk, log_span = 6 - s0, span = 1u << log_span;
-            const uint32_t G = lane >> log_span, base = (G << (8 - s0)) + (lane & (span - 1));
-            if (blk < 3) {
-                __syncthreads();
-                if (src_on) {
-#pragma unroll
-                    for (int k = 0; k < 4; k++) x[k] = exw[cf_pos(base + (k << log_span))];
-                }
-            }
-            if (src_on) {
-                inv_block2_r(x, t1[blk], q);
-                if (blk > 0) {
-#pragma unroll
-                    for (int k = 0; k < 4; k++) exw[cf_pos(base + (k << log_span))] = x[k];
-                } else {
-#pragma unroll
-                    for (int k = 0; k < 4; k++) ys[w * 256 + lane + 64 * k] = csub(shoup_lazy(x[k], cs, cs_sh, q), q);
-                }
-            }
-        }
-    }
-    for (uint32_t t0 = 0; t0 < nt; t0 += CF_WAVES) {
-        const uint32_t ti = t0 + w;
-        const bool active = ti < nt;
-        if (t0) {                                            // later rounds fetch their constants as they start
-            mr = __builtin_amdgcn_readfirstlane(cf.tgt_mod[set][active ? ti : 0]);
-            m2 = mc[mr];
-#pragma unroll
-            for (int i = 0; i < CF_WAVES; i++) hat[i] = gp.hat[(size_t)mr * cf.hat_w + i];
-        }
-        u64 t2[4][6];
-#pragma unroll
-        for (int blk = 0; blk < 4; blk++) tw_block2(t2[blk], tw + ((size_t)mr << 16), 2 * blk, lane >> (6 - 2 * blk));
-        __syncthreads();                                     // the sources are in ys (first round)
-        const u64 q = uni64(m2.q), q4 = 4 * q;
-        const bool wide = m2.bits > 57;
-        if (active) {
-            u128 acc[4] = {};
-#pragma unroll
-            for (int i = 0; i < CF_WAVES; i++) {
-                if ((uint32_t)i < ns) {
-#pragma unroll
-                    for (int k = 0; k < 4; k++) acc[k] += (u128)ys[i * 256 + lane + 64 * k] * hat[i];
-                }
-            }
-#pragma unroll
-            for (int k = 0; k < 4; k++) x[k] = barrett128_lazy(acc[k], q, m2.mu, m2.bits);      // below 5q
-        }
-#pragma unroll
-        for (int blk = 0; blk < 4; blk++) {
-            const uint32_t s0 = 2 * blk, log_span = 6 - s0, span = 1u << log_span;
-            const uint32_t G = lane >> log_span, base = (G << (8 - s0)) + (lane & (span - 1));
-            if (blk > 0) {
-                __syncthreads();
-                if (active) {
-#pragma unroll
-                    for (int k = 0; k < 4; k++) x[k] = exw[cf_pos(base + (k << log_span))];
-                }
-            }
-            if (active) {
-                if (wide) fwd_block2_r<true>(x, t2[blk], q, q4);
-                else fwd_block2_r<false>(x, t2[blk], q, q4);
-                if (blk < 3) {
-#pragma unroll
-                    for (int k = 0; k < 4; k++) exw[cf_pos(base + (k << log_span))] = x[k];
-                }
-            }
-        }
-        if (active) {
-            u64* dst = gp.dst + ((size_t)cf.tgt_limb[set][ti] << 16) + c;
-#pragma unroll
-            for (int k = 0; k < 4; k++) dst[(size_t)(4 * lane + k) * 256] = x[k];
-        }
-    }
-}
-
-int32_t launch_colfuse(he_ctx* ctx, const ColFuse& cf, const ScaleList& sc, uint32_t limb_passes) {
-    if (cf.n_groups == 0) return HE_OK;
-    if (cf.n_groups > CF_MAX_GROUPS) return he_fail(ctx, HE_ERR_BADARG, "column fusion: too many groups");
-    for (uint32_t g = 0; g < cf.n_groups; g++)
-        if (cf.grp[g].ns == 0 || cf.grp[g].ns > CF_WAVES || cf.grp[g].set >= CF_MAX_SETS || cf.grp[g].mod0 + cf.grp[g].ns > ctx->M ||
-            cf.grp[g].sc0 + cf.grp[g].ns > HE_MAX_MODULI || !cf.grp[g].src || !cf.grp[g].dst || !cf.grp[g].hat)
-            return he_fail(ctx, HE_ERR_BADARG, "column fusion: bad group %u", g);
-    hipEvent_t e0 = nullptr, e1 = nullptr;
-    if (ctx->prof_on) {
-        HE_HIP(ctx, hipEventCreate(&e0));
-        HE_HIP(ctx, hipEventCreate(&e1));
-        HE_HIP(ctx, hipEventRecord(e0, ctx->stream));
-    }
-    hipLaunchKernelGGL(ntt16_colfuse_kernel, dim3(cf.n_groups * 256), dim3(CF_THREADS), 0, ctx->stream, cf, sc, ctx->d_mc, ctx->d_tw,
-                       ctx->d_itw);
-    HE_HIP(ctx, hipGetLastError());
-    if (ctx->prof_on) {
-        HE_HIP(ctx, hipEventRecord(e1, ctx->stream));
-        ctx->prof_events.push_back({e0, e1, limb_passes, 0u, 0u});
-    }
-    return HE_OK;
-}
-
 // ---------------------------------------------------------------- butterfly-rate probe
 // The vector-ALU roof of the transforms, measured rather than derived: the register blocks of the passes
 // above (four stages on 16 points, twiddles from a 256-entry table that stays in the first-level cache)

@@ -1,4 +1,4 @@
-// Register blocks of the radix-2 negacyclic transforms shared by the N = 2^16 kernels and the small-ring kernels:
+// Register blocks of the radix-2 negacyclic transforms shared by the two-launch kernels, the column conversion and the small-ring kernels:
 // four butterfly stages on 16 points, or two on 4 points, held by one thread (Harvey butterflies, Shoup twiddle
 // products with the three-multiply approximate quotient, lazy ranges).
 #pragma once

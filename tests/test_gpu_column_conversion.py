@@ -18,13 +18,14 @@ pytestmark = pytest.mark.gpu
     (16, 54, 11, 60, 3, 2, (10, 5)),     # six and five sources, eight and nine targets
 ])
 @pytest.mark.parametrize("fill", ["uniform", "extreme"])
-def test_conversion_edges(logN, q_bits, nq, p_bits, np_, dnum, levels, fill):
+@pytest.mark.parametrize("n_ct", [1, 3])         # small tiles for the lowest level of one ciphertext, large ones otherwise
+def test_conversion_edges(logN, q_bits, nq, p_bits, np_, dnum, levels, n_ct, fill):
     from gpu_util import dev, host, zeros
     from oracle.he_oracle import Oracle
     from paper_2302_02407_amd.binding import HEContext
     prm = toy_params(logN=logN, q_bits=q_bits, nq=nq, p_bits=p_bits, np_=np_, dnum=dnum, hamming=64, seed=700 + logN)
     rng, orc, ctx = S.make_rng(700 + logN), Oracle.from_params(prm), HEContext.from_params(prm)
-    N, step, n_ct = prm.N, 3, 3
+    N, step = prm.N, 3
 
     def residues(moduli, n):
         if fill == "uniform":
