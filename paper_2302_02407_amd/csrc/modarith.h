@@ -34,11 +34,14 @@ __device__ __forceinline__ u64 uni64(u64 v) {
 __device__ __forceinline__ u64 csub_u(u64 x, u64 q) { return mask_add(x + neg_u(q), q); }
 
 // High word of a*b from three 32x32 products (the low*low product and the carries out of the
-// middle column are dropped): never above the true value, at most 2 below it.
+// middle column are dropped): never above the true value, at most 2 below it.  The last 32-bit term is added by a
+// multiply-add with the factor 1, which takes it as it is; written as an addition it is widened to a register pair first,
+// two moves per product (16-output convolution at level 5: 651 -> 638 us).
 __device__ __forceinline__ u64 mulhi64_approx(u64 a, u64 b) {
     const uint32_t al = (uint32_t)a, ah = (uint32_t)(a >> 32), bl = (uint32_t)b, bh = (uint32_t)(b >> 32);
-    const u64 mid = (u64)__umulhi(ah, bl) + (u64)__umulhi(al, bh);
-    return (u64)ah * bh + mid;
+    u64 r = (u64)ah * bh + __umulhi(ah, bl), carry;
+    asm("v_mad_u64_u32 %0, %1, %2, 1, %3" : "=v"(r), "=s"(carry) : "v"(__umulhi(al, bh)), "v"(r));
+    return r;
 }
 
 // a + b + c as one instruction.  Opaque on purpose: sums of 32-bit products written in C become 64-bit multiply-adds with
