@@ -405,11 +405,16 @@ static int32_t launch_baseconv(he_ctx* c, const ConvBatch& b, uint32_t nt_max, u
 static void engine_shape(const he_ctx* c, uint32_t level, uint32_t n_src, uint32_t n_jobs, uint32_t& cb, uint32_t& jb) {
     const uint32_t L1 = level + 1, k = c->np;
     cb = std::min<uint32_t>(std::min<uint32_t>(n_src, HE_MAX_SEGS), std::max<uint32_t>(1, HE_MAX_LAUNCH_LIMBS / L1));
-    cb = std::min<uint32_t>(cb, 8);
     jb = std::min<uint32_t>(n_jobs, HE_MAX_KS_JOBS);
     jb = std::min<uint32_t>(jb, std::max<uint32_t>(1, HE_MAX_LAUNCH_LIMBS / (2 * L1)));
     jb = std::min<uint32_t>(jb, std::max<uint32_t>(1, HE_MAX_LAUNCH_LIMBS / (2 * k)));
     jb = std::min<uint32_t>(jb, std::max<uint32_t>(1, 4096 / (2 * (L1 + k))));   // source limb offsets are 12 bits
+    // Sources that each serve one job come in launch sets as large as the jobs' where 16 jobs fit: smaller rings and lower
+    // levels do not fill the chip with 8 (six ciphertexts by eight rotations at N = 2^14: 460 -> 370 us, nine by six at level
+    // 5 of N = 2^16: 1512 -> 1377).  Sources that serve several jobs stay at 8, so that the jobs of one key are as many as the
+    // work groups that share its limbs' cache.
+    const bool pairs = n_src == n_jobs && jb == std::min<uint32_t>(n_jobs, HE_MAX_KS_JOBS);
+    cb = std::min<uint32_t>(cb, pairs ? HE_MAX_KS_JOBS : 8);
     if (cb == 0) cb = 1;
     if (jb == 0) jb = 1;
 }

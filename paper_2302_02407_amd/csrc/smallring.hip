@@ -138,7 +138,7 @@ struct SrTables {
 
 // ---------------------------------------------------------------- ModUp
 struct SrUpArgs {
-    const u64* c1[8];          // sources [L1][N], NTT form
+    const u64* c1[HE_MAX_KS_JOBS]; // sources [L1][N], NTT form
     u64* raised;               // [n_src][beta][R][N]; a digit's own limbs are left unwritten
     const u64* hat;            // conversion constants [digit][size-1][modulus][i padded to aw]
     u64 scale[HE_MAX_MODULI];  // per source limb: N^-1 * (Q_j/q_i)^-1 mod q_i, and its Shoup companion
@@ -688,8 +688,8 @@ bool small_ring_path(const he_ctx* c, uint32_t level) {
 int32_t sr_modup(he_ctx* c, const KsSrc* srcs, uint32_t cb, uint32_t level, u64* raised) {
     const uint32_t L1 = level + 1, R = L1 + c->np, al = c->alpha, beta = (level + al) / al;
     SrUpArgs a;
-    if (cb > 8) return he_fail(c, HE_ERR_BADARG, "small-ring ModUp: more than 8 sources");
-    for (uint32_t s = 0; s < 8; s++) a.c1[s] = srcs[s < cb ? s : 0].c1;
+    if (cb > HE_MAX_KS_JOBS) return he_fail(c, HE_ERR_BADARG, "small-ring ModUp: more than %d sources", HE_MAX_KS_JOBS);
+    for (uint32_t s = 0; s < HE_MAX_KS_JOBS; s++) a.c1[s] = srcs[s < cb ? s : 0].c1;
     a.raised = raised; a.hat = c->d_up_hat;
     a.L1 = L1; a.R = R; a.beta = beta; a.alpha = al; a.M = c->M; a.nq = c->nq; a.level = level; a.aw = (al + 7u) & ~7u;
     for (uint32_t i = 0; i < L1; i++) {
