@@ -168,6 +168,7 @@ int32_t he_sync(he_ctx* ctx);
  * synchronises the stream, frees and reallocates.  To keep that out of a timed or latency-critical
  * region, ask the matching he_ws_query_* for the size (bytes, host output) and call he_ws_reserve once
  * beforehand.  he_ws_reserve never shrinks the workspace; he_ws_bytes reports its current size.
+ * A size also serves the same call at that level with fewer ciphertexts, steps or outputs.
  * The queries return HE_ERR_LEVEL / HE_ERR_BADARG for shapes the call itself would refuse. */
 int32_t he_ws_bytes(const he_ctx* ctx, uint64_t* h_bytes);
 int32_t he_ws_reserve(he_ctx* ctx, uint64_t bytes);

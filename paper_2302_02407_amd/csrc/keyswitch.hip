@@ -419,10 +419,19 @@ static void engine_shape(const he_ctx* c, uint32_t level, uint32_t n_src, uint32
     if (jb == 0) jb = 1;
 }
 
-// raised[cb][beta][R] + tmp_up[cb][L1] + acc[jb][2][R] + tmp_dn[jb][2][k] + conv[jb][2][L1]
+// The most sources that any call with at most n_src sources and as many jobs as make launch sets of jb raises at once: what a
+// workspace is sized for, since one reserved for a batch serves smaller ones too (the last group of a block, steps of zero, which
+// have no job), and 10 one-job sources at a top level are raised together where 11 go 8 at a time.
+static uint32_t engine_most_sources(uint32_t level, uint32_t n_src, uint32_t jb) {
+    const uint32_t cap = std::max<uint32_t>(1, HE_MAX_LAUNCH_LIMBS / (level + 1));
+    return std::max<uint32_t>(1, std::min(std::min(n_src, cap), std::max<uint32_t>(8, jb)));
+}
+
+// raised[cb][beta][R] + tmp_up[cb][L1] + acc[jb][2][R] + tmp_dn[jb][2][k] + conv[jb][2][L1]; not less for a larger batch
 size_t ks_engine_ws_elems(const he_ctx* c, uint32_t level, uint32_t n_src, uint32_t n_jobs) {
     uint32_t cb, jb;
     engine_shape(c, level, n_src, n_jobs, cb, jb);
+    cb = engine_most_sources(level, n_src, jb);
     const size_t L1 = level + 1, k = c->np, R = L1 + k, beta = num_digits(c, level);
     return ((size_t)cb * (beta * R + L1) + (size_t)jb * (2 * R + 2 * k + 2 * L1)) * c->N;
 }
@@ -1109,6 +1118,7 @@ size_t ks_hoisted_sum_ws_elems(const he_ctx* c, uint32_t level, uint32_t J, uint
     (void)T;
     uint32_t cb, jb;
     engine_shape(c, level, J, J, cb, jb);
+    cb = engine_most_sources(level, J, jb);
     jb = hoisted_sum_jb(c, level, J);
     // raised [jb][beta][R] + tmp_up [cb][L1] + s0 [jb][L1] + acc [jb][2][R] + tmp_dn [jb][2][k] + conv [jb][2][L1]
     return ((size_t)jb * beta * R + (size_t)cb * L1 + (size_t)jb * L1 + (size_t)jb * 2 * R + (size_t)jb * 2 * k + (size_t)jb * 2 * L1) * c->N;

@@ -1,0 +1,34 @@
+"""The sizes that the workspace queries return, without a GPU: a query reads the ring degree, the prime counts and the digit
+width of its context and nothing else, so a block of memory that starts with those words stands in for one."""
+import ctypes as C
+
+import pytest
+
+# logN, ciphertext primes, special primes, digits
+SETS = [(16, 24, 8, 3), (16, 24, 4, 6), (15, 12, 4, 3), (9, 25, 1, 25), (12, 3, 1, 3), (17, 24, 8, 3)]
+
+
+def context(logN, nq, np_, dnum):
+    words = (C.c_uint32 * 65536)()
+    words[:7] = [logN, 1 << logN, nq, np_, dnum, -(-nq // dnum), nq + np_]
+    return words
+
+
+def query(name, ctx, *args):
+    from paper_2302_02407_amd import binding
+    v = C.c_uint64()
+    assert getattr(binding.load(), name)(C.addressof(ctx), *args, C.byref(v)) == 0
+    return v.value
+
+
+@pytest.mark.parametrize("prm", SETS)
+def test_a_batch_fits_what_a_larger_one_reserved(prm):
+    """Fewer ciphertexts, fewer steps (or steps of zero, which need no key switch) never need more."""
+    ctx = context(*prm)
+    for level in range(prm[1]):
+        for hoisted in (0, 1):
+            q = [[query("he_ws_query_rotate_batch", ctx, level, n, s, hoisted) for s in range(1, 5)] for n in range(1, 36)]
+            for n in range(35):
+                for s in range(4):
+                    assert n == 0 or q[n - 1][s] <= q[n][s], (level, hoisted, n + 1, s + 1)
+                    assert s == 0 or q[n][s - 1] <= q[n][s], (level, hoisted, n + 1, s + 1)
