@@ -627,8 +627,8 @@ static BlockShape block_shape(const he_ctx* ctx, const he_block_plan* p, uint32_
     b.G = (p->group == 0 || p->group > p->n_ra) ? p->n_ra : p->group;
     const size_t ct_hi = 2 * (size_t)(level + 1) * N, ct_mid = 2 * (size_t)level * N, ct_lo = 2 * (size_t)(level - 1) * N;
     b.eng_e = n_rot ? ks_engine_ws_elems(ctx, level, p->n_ca, p->n_ca * n_rot) : 0;
-    b.eng_e = std::max(b.eng_e, (p->hoisted_ras && p->C_a > 1) ? ks_hoisted_sum_ws_elems(ctx, level - 1, b.G, p->C_a - 1)
-                                                                : ks_engine_ws_elems(ctx, level - 1, b.G, b.G));
+    b.eng_e = std::max(b.eng_e, ks_engine_ws_elems(ctx, level - 1, b.G, b.G));   // rotate-and-sum steps, the square's relinearisation
+    if (p->hoisted_ras && p->C_a > 1) b.eng_e = std::max(b.eng_e, ks_hoisted_sum_ws_elems(ctx, level - 1, b.G, p->C_a - 1));
     b.eng_e = std::max(b.eng_e, slide1_sum_ws_elems(ctx, level - 2, n_rot, p->deferred_moddown != 0));
     b.rs_e = rescale_ws_elems(ctx, level, b.G);
     b.ct1_e = (size_t)p->n_ca * n_rot * ct_hi;

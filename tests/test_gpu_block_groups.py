@@ -11,6 +11,8 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("nq,np_,dnum,level,n_ra,group,hoisted", [
     (25, 1, 25, 24, 21, 11, False),      # 11 one-job sources go 8 at a time, the 10 left over all at once
+    (25, 1, 25, 24, 21, 11, True),       # a hoisted sum of one ciphertext at a time, squares 8 at a time
+    (8, 2, 4, 6, 40, 16, True),          # a hoisted sum of 8 at a time, squares 16 at a time; 8 left over
 ])
 def test_groups_and_their_rest(nq, np_, dnum, level, n_ra, group, hoisted):
     from gpu_util import dev, host, zeros

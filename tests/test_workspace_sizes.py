@@ -32,3 +32,18 @@ def test_a_batch_fits_what_a_larger_one_reserved(prm):
                 for s in range(4):
                     assert n == 0 or q[n - 1][s] <= q[n][s], (level, hoisted, n + 1, s + 1)
                     assert s == 0 or q[n][s - 1] <= q[n][s], (level, hoisted, n + 1, s + 1)
+
+
+@pytest.mark.parametrize("prm", SETS)
+def test_the_hoisted_sum_of_a_block_leaves_room_for_its_square(prm):
+    """Both forms of a block relinearise a group's squares with one launch set; the hoisted one does not get by with less than
+    the stepwise one, whose rotate-and-sum has that same shape."""
+    from paper_2302_02407_amd.binding import BlockPlan
+    ctx, slots = context(*prm), 1 << (prm[0] - 1)
+    for level in range(3, prm[1]):
+        for group in (1, 4, 8, 9, 16, 24):
+            need = []
+            for hoisted in (0, 1):
+                plan = BlockPlan(2, 8, slots // 16, 1, 3, 1, 2 * group, level, group, 0, hoisted)
+                need.append(query("he_ws_query_ca_ra_block", ctx, C.byref(plan)))
+            assert need[0] <= need[1], (level, group)
