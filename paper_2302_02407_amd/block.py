@@ -59,9 +59,10 @@ def _ct(level, N):
 
 
 def merge_outputs(ctx, outs, masks, level):
-    """sum_o outs[o] (.) masks[o], rescaled: level -> level-1."""
-    acc = _ct(level, ctx.N)
-    ctx.he_ptct_mac_rot(acc, outs, masks, [1] * len(outs), level)      # one pass over the sum instead of one per product
+    """sum_o outs[o] (.) masks[o], rescaled: level -> level-1.  Any iterables; the longer one's rest is left out."""
+    acc, pairs = _ct(level, ctx.N), list(zip(outs, masks))
+    # one pass over the sum instead of one per product
+    ctx.he_ptct_mac_rot(acc, [ct for ct, _ in pairs], [m for _, m in pairs], [1] * len(pairs), level)
     return ctx.he_rescale(acc, level, _ct(level - 1, ctx.N))
 
 
