@@ -16,8 +16,8 @@
  *  - Pointers named d_* are DEVICE pointers, h_* are HOST pointers.  The caller owns every
  *    buffer it passes; the context owns only its precomputed tables and its workspace.
  *  - A polynomial limb is N = 2^logN uint64 residues in [0, m) of one modulus m.  Buffers are
- *    limb-major: [poly][limb][N].  A ciphertext at level l is [2][l+1][N] (c0 then c1) over
- *    q_0..q_l.
+ *    limb-major: [poly][limb][N], aligned to a uint64 (8 bytes) and no further.  A ciphertext at
+ *    level l is [2][l+1][N] (c0 then c1) over q_0..q_l.
  *  - "NTT form": position j holds the evaluation at psi^(2*bitrev(j)+1), psi the primitive
  *    2N-th root of the modulus given by he_ctx_psi.  Ciphertexts, plaintexts and keys are in
  *    NTT form unless a call says otherwise.

@@ -28,7 +28,6 @@ struct MacMany {
 // bound by reading them (non-temporal, so that they do not displace the ciphertexts and accumulators that other kernels
 // read next).  Operands and outputs have CL limbs per component: the level+1 ciphertext primes, followed by the special
 // primes when the operands are key-switch inner products still over the raised basis.  grid: (N/(256 NC), CL).
-typedef u64 mac_v2 __attribute__((ext_vector_type(2)));
 template <int NC>
 struct MacVec;
 template <>
@@ -41,12 +40,9 @@ struct MacVec<1> {
 template <>
 struct MacVec<2> {
     u64 v[2];
-    __device__ __forceinline__ void load(const u64* p) { const mac_v2 t = *reinterpret_cast<const mac_v2*>(p); v[0] = t.x; v[1] = t.y; }
-    __device__ __forceinline__ void load_nt(const u64* p) {
-        const mac_v2 t = __builtin_nontemporal_load(reinterpret_cast<const mac_v2*>(p));
-        v[0] = t.x; v[1] = t.y;
-    }
-    __device__ __forceinline__ void store(u64* p) const { *reinterpret_cast<mac_v2*>(p) = mac_v2{v[0], v[1]}; }
+    __device__ __forceinline__ void load(const u64* p) { const ulonglong2 t = LOAD2(p); v[0] = t.x; v[1] = t.y; }
+    __device__ __forceinline__ void load_nt(const u64* p) { v[0] = __builtin_nontemporal_load(p); v[1] = __builtin_nontemporal_load(p + 1); }
+    __device__ __forceinline__ void store(u64* p) const { STORE2(p) = make_ulonglong2(v[0], v[1]); }
 };
 template <int NI, int NC>
 __global__ __launch_bounds__(CV_THREADS) void mac_many_kernel(MacMany a, const ModConst* mc, uint32_t logN, uint32_t CL, uint32_t level, uint32_t nq) {

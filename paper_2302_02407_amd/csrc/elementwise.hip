@@ -75,8 +75,8 @@ __global__ __launch_bounds__(EW_THREADS) void ptct_mac_rot_kernel(u64* __restric
     const size_t lo = (size_t)limb << logN, o0 = lo + n, o1 = ((size_t)(limb + n_limbs) << logN) + n;
     ulonglong2 r0 = make_ulonglong2(0, 0), r1 = r0;
     if (!init) {
-        r0 = *reinterpret_cast<const ulonglong2*>(acc + o0);
-        r1 = *reinterpret_cast<const ulonglong2*>(acc + o1);
+        r0 = LOAD2(acc + o0);
+        r1 = LOAD2(acc + o1);
     }
     for (uint32_t i0 = 0; i0 < mr.n; i0 += 4) {
         ulonglong2 c0[4], c1[4], p[4];
@@ -86,9 +86,9 @@ __global__ __launch_bounds__(EW_THREADS) void ptct_mac_rot_kernel(u64* __restric
             const uint32_t i = i0 + k;
             if (i < mr.n) {
                 const uint32_t g = mr.g[i], src = g == 1 ? n : galois_src(n, g, logN);
-                c0[k] = *reinterpret_cast<const ulonglong2*>(mr.ct[i] + o0);
-                c1[k] = *reinterpret_cast<const ulonglong2*>(mr.ct[i] + o1);
-                p[k] = *reinterpret_cast<const ulonglong2*>(mr.pt[i] + lo + (src & ~1u));
+                c0[k] = LOAD2(mr.ct[i] + o0);
+                c1[k] = LOAD2(mr.ct[i] + o1);
+                p[k] = LOAD2(mr.pt[i] + lo + (src & ~1u));
                 swp[k] = src & 1u;
             }
         }
@@ -106,8 +106,8 @@ __global__ __launch_bounds__(EW_THREADS) void ptct_mac_rot_kernel(u64* __restric
         r1.x = reduce_full<7>(r1.x + split_reduce(s[2], m), m.q, m.bits, m.rec);
         r1.y = reduce_full<7>(r1.y + split_reduce(s[3], m), m.q, m.bits, m.rec);
     }
-    *reinterpret_cast<ulonglong2*>(acc + o0) = r0;
-    *reinterpret_cast<ulonglong2*>(acc + o1) = r1;
+    STORE2(acc + o0) = r0;
+    STORE2(acc + o1) = r1;
 }
 
 __global__ __launch_bounds__(EW_THREADS) void add_kernel(const u64* a, const u64* b, u64* out, const ModConst* mc,

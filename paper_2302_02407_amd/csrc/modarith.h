@@ -10,6 +10,12 @@
 
 __device__ __forceinline__ u64 mulhi64(u64 a, u64 b) { return __umul64hi(a, b); }
 
+// Two adjacent residues of a buffer that the caller gave, which is aligned to a residue and no further: 8 bytes, as the type
+// says, so that nothing is concluded from 16.  Still one 16-byte access, which global memory takes at any multiple of 4.
+typedef ulonglong2 pair64 __attribute__((aligned(8)));
+#define LOAD2(p) (*reinterpret_cast<const pair64*>(p))
+#define STORE2(p) (*reinterpret_cast<pair64*>(p))
+
 // w*y mod q in [0, 2q) for any y < 2^64, given w < q and w_sh = floor(w*2^64/q)  (Shoup).
 __device__ __forceinline__ u64 shoup_lazy(u64 y, u64 w, u64 w_sh, u64 q) {
     u64 h = mulhi64(w_sh, y);

@@ -272,7 +272,7 @@ __device__ __forceinline__ void ip_request(IpLoad<NJ>& L, const IpTerm& tm, uint
             const u64* kj = tm.key + j * key_stride;
 #pragma unroll
             for (int p = 0; p < 2; p++) {
-                L.d[jj][p] = *reinterpret_cast<const ulonglong2*>(dj + src[p]);
+                L.d[jj][p] = LOAD2(dj + src[p]);
                 const uint32_t kp = (pos + DP * p) | swp[p];
                 L.k[jj][p][0] = kj[kp];
                 L.k[jj][p][1] = kj[kp ^ 1u];
@@ -486,7 +486,7 @@ __device__ __forceinline__ void row_fwd(const P2Args& a, uint32_t e, uint32_t ti
             for (int k = 0; k < 16; k++) row[t + 16 * k] = s[t + 17 * k];
         } else {
 #pragma unroll
-            for (int j = 0; j < 4; j += 2) *reinterpret_cast<ulonglong2*>(row + 4 * t + j) = make_ulonglong2(x[j], x[j + 1]);
+            for (int j = 0; j < 4; j += 2) STORE2(row + 4 * t + j) = make_ulonglong2(x[j], x[j + 1]);
         }
         return;
     }
@@ -516,8 +516,8 @@ __device__ __forceinline__ void row_fwd(const P2Args& a, uint32_t e, uint32_t ti
         ulonglong2 cv[2], sv[2];
 #pragma unroll
         for (int p = 0; p < 2; p++) {
-            cv[p] = has_c0 ? *reinterpret_cast<const ulonglong2*>(c0 + src[p]) : make_ulonglong2(0, 0);
-            sv[p] = has_self ? *reinterpret_cast<const ulonglong2*>(self + pos + DP * p) : make_ulonglong2(0, 0);
+            cv[p] = has_c0 ? LOAD2(c0 + src[p]) : make_ulonglong2(0, 0);
+            sv[p] = has_self ? LOAD2(self + pos + DP * p) : make_ulonglong2(0, 0);
         }
 #pragma unroll
         for (int p = 0; p < 2; p++) {
@@ -528,7 +528,7 @@ __device__ __forceinline__ void row_fwd(const P2Args& a, uint32_t e, uint32_t ti
             o.y = shoup_acc(c.y + sv[p].y, acc.y + bias - s[l + 1], pinv, pinv_sh, q);
             o.x = reduce_full<7>(o.x, q, m.bits, m.rec);
             o.y = reduce_full<7>(o.y, q, m.bits, m.rec);
-            *reinterpret_cast<ulonglong2*>(out + pos + DP * p) = o;
+            STORE2(out + pos + DP * p) = o;
         }
     };
     const size_t dig_stride = (size_t)ep.R << logN, key_stride = (size_t)(2 * ep.M) << logN;
@@ -538,7 +538,7 @@ __device__ __forceinline__ void row_fwd(const P2Args& a, uint32_t e, uint32_t ti
         const uint32_t g = ep.g[job];
         ulonglong2 av[PTS / 2];
 #pragma unroll
-        for (int p = 0; p < PTS / 2; p++) av[p] = *reinterpret_cast<const ulonglong2*>(acc + row0 + 2 * t + DP * p);
+        for (int p = 0; p < PTS / 2; p++) av[p] = LOAD2(acc + row0 + 2 * t + DP * p);
 #pragma unroll
         for (int ch = 0; ch < PTS / 4; ch++) {
             const uint32_t pos = row0 + 2 * t + 2 * DP * ch;
@@ -606,7 +606,7 @@ __device__ __forceinline__ void row_inv(const P2Args& a, const LimbTab& tab, uin
         } else {
 #pragma unroll
             for (int j = 0; j < 4; j += 2) {
-                const ulonglong2 v = *reinterpret_cast<const ulonglong2*>(in + 4 * t + j);
+                const ulonglong2 v = LOAD2(in + 4 * t + j);
                 x[j] = v.x; x[j + 1] = v.y;
             }
             factors();

@@ -387,11 +387,11 @@ __global__ __launch_bounds__(SR_THREADS) void sr_rescale_kernel(SrRescaleArgs a,
 
 __device__ __forceinline__ void load8(u64 (&v)[8], const u64* __restrict__ p) {
 #pragma unroll
-    for (int k = 0; k < 8; k += 2) { const ulonglong2 u = *(const ulonglong2*)(p + k); v[k] = u.x; v[k + 1] = u.y; }
+    for (int k = 0; k < 8; k += 2) { const ulonglong2 u = LOAD2(p + k); v[k] = u.x; v[k + 1] = u.y; }
 }
 __device__ __forceinline__ void store8(u64* p, const u64 (&v)[8]) {
 #pragma unroll
-    for (int k = 0; k < 8; k += 2) *(ulonglong2*)(p + k) = make_ulonglong2(v[k], v[k + 1]);
+    for (int k = 0; k < 8; k += 2) STORE2(p + k) = make_ulonglong2(v[k], v[k + 1]);
 }
 struct FMod { double q, qi; u64 n; };
 __device__ __forceinline__ FMod f_mod(const ModConst& m) { return {(double)m.q, m.qinv, m.q}; }
