@@ -401,14 +401,18 @@ static int32_t launch_baseconv(he_ctx* c, const ConvBatch& b, uint32_t nt_max, u
     return HE_OK;
 }
 
+// The most jobs whose ModDown one set of launches takes: both components of all their limbs in one list.
+static uint32_t moddown_most_jobs(const he_ctx* c, uint32_t level) {
+    const uint32_t L1 = level + 1, k = c->np;
+    uint32_t jb = std::min<uint32_t>(HE_MAX_KS_JOBS, HE_MAX_LAUNCH_LIMBS / (2 * std::max(L1, k)));
+    jb = std::min<uint32_t>(jb, 4096 / (2 * (L1 + k)));                          // source limb offsets are 12 bits
+    return std::max<uint32_t>(1, jb);
+}
+
 // How many sources are raised at once and how many jobs share one ModDown launch set.
 static void engine_shape(const he_ctx* c, uint32_t level, uint32_t n_src, uint32_t n_jobs, uint32_t& cb, uint32_t& jb) {
-    const uint32_t L1 = level + 1, k = c->np;
-    cb = std::min<uint32_t>(std::min<uint32_t>(n_src, HE_MAX_SEGS), std::max<uint32_t>(1, HE_MAX_LAUNCH_LIMBS / L1));
-    jb = std::min<uint32_t>(n_jobs, HE_MAX_KS_JOBS);
-    jb = std::min<uint32_t>(jb, std::max<uint32_t>(1, HE_MAX_LAUNCH_LIMBS / (2 * L1)));
-    jb = std::min<uint32_t>(jb, std::max<uint32_t>(1, HE_MAX_LAUNCH_LIMBS / (2 * k)));
-    jb = std::min<uint32_t>(jb, std::max<uint32_t>(1, 4096 / (2 * (L1 + k))));   // source limb offsets are 12 bits
+    cb = std::min<uint32_t>(std::min<uint32_t>(n_src, HE_MAX_SEGS), std::max<uint32_t>(1, HE_MAX_LAUNCH_LIMBS / (level + 1)));
+    jb = std::min<uint32_t>(n_jobs, moddown_most_jobs(c, level));
     // Sources that each serve one job come in launch sets as large as the jobs' where 16 jobs fit: smaller rings and lower
     // levels do not fill the chip with 8 (six ciphertexts by eight rotations at N = 2^14: 460 -> 370 us, nine by six at level
     // 5 of N = 2^16: 1512 -> 1377).  Sources that serve several jobs stay at 8, so that the jobs of one key are as many as the
@@ -1242,9 +1246,9 @@ int32_t ks_raised_products(he_ctx* c, uint32_t level, const u64* c1, const uint3
     return HE_OK;
 }
 
-// scratch of ks_moddown_stored for up to HE_MAX_KS_JOBS accumulators at once: tmp_dn [J][2][k][N] + conv [J][2][L1][N]
+// scratch of ks_moddown_stored: tmp_dn [nb][2][k][N] + conv [nb][2][L1][N] for the nb accumulators of one set of launches
 size_t ks_moddown_stored_ws_elems(const he_ctx* c, uint32_t level, uint32_t J) {
-    const size_t nb = std::min<uint32_t>(J ? J : 1, HE_MAX_KS_JOBS);
+    const size_t nb = std::min<uint32_t>(J ? J : 1, moddown_most_jobs(c, level));
     return nb * (2 * c->np + 2 * (level + 1)) * c->N;
 }
 
@@ -1254,8 +1258,9 @@ int32_t ks_moddown_stored(he_ctx* c, uint32_t level, uint32_t J, u64* acc, const
                           u64* const* out0, u64* const* out1, u64* ws) {
     const uint32_t N = c->N, L1 = level + 1, k = c->np, R = L1 + k;
     if (2 * k > HE_MAX_MODULI) return he_fail(c, HE_ERR_BADARG, "key switch: more than %d special primes", HE_MAX_MODULI / 2);
-    for (uint32_t j0 = 0; j0 < J; j0 += HE_MAX_KS_JOBS) {
-        const uint32_t nb = std::min<uint32_t>(HE_MAX_KS_JOBS, J - j0);
+    const uint32_t most = moddown_most_jobs(c, level);
+    for (uint32_t j0 = 0; j0 < J; j0 += most) {
+        const uint32_t nb = std::min<uint32_t>(most, J - j0);
         u64* a = acc + (size_t)j0 * 2 * R * N;
         u64* tmp_dn = ws;
         u64* conv = tmp_dn + (size_t)nb * 2 * k * N;

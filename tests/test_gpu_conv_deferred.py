@@ -94,3 +94,22 @@ def test_two_pass_ring():
 @pytest.mark.timeout(900)
 def test_config3_resnet20_layer():
     _run(config_params(3), C_a=16, H=32, W=32, c_out=16, level=23, w_std=(2.0 / (9 * 16)) ** 0.5, tol=1e-3)
+
+
+def test_more_outputs_than_one_set_of_moddowns():
+    """12 outputs of 25 limbs: both components are more limbs than one launch lists.  Uniform residues; every output is the one
+    that a call for it alone gives."""
+    from gpu_util import dev, host, zeros
+    from paper_2302_02407_amd.binding import HEContext
+    prm = toy_params(logN=9, q_bits=40, nq=25, p_bits=41, np_=1, dnum=25, hamming=16, seed=83)
+    rng, ctx, N, level, n_out = S.make_rng(83), HEContext.from_params(prm), prm.N, 24, 12
+    C_a, H, W, R, f = 2, 8, 16, 1, 3
+    steps = {((dy * W + dx) * R) % (N // 2) for dy in (-1, 0, 1) for dx in (-1, 0, 1)} - {0} | {H * W * R}
+    for s in sorted(steps):
+        ctx.he_evk_register(ctx.galois_elt(s), dev(S.uniform_limbs(rng, prm.moduli, N, 2 * prm.dnum).reshape(prm.dnum, 2, -1, N)))
+    w = [dev(x) for x in S.uniform_limbs(rng, prm.moduli, N, n_out * f * f)]
+    ct = dev(S.uniform_limbs(rng, prm.q, N, 2))
+    outs = ctx.he_conv2d(C_a, H, W, R, f, level, w, ct, [zeros(2, level, N) for _ in range(n_out)], deferred_taps=True)
+    for o in range(n_out):
+        one, = ctx.he_conv2d(C_a, H, W, R, f, level, w[o * f * f:(o + 1) * f * f], ct, [zeros(2, level, N)], deferred_taps=True)
+        assert (host(outs[o]) == host(one)).all(), o
