@@ -183,7 +183,7 @@ extern "C" int32_t he_ws_query_conv2d(const he_ctx* ctx, const he_conv_plan* pla
     return he_guard(ctx, "he_ws_query_conv2d: host allocation failed", [&]() -> int32_t {
     if (!ctx || !plan || !h_bytes) return HE_ERR_BADARG;
     if (plan->level == 0 || plan->level >= ctx->nq) return HE_ERR_LEVEL;
-    if ((plan->f & 1u) == 0 || plan->f * plan->f > CV_MAX_TAPS || plan->n_out == 0) return HE_ERR_BADARG;
+    if ((plan->f & 1u) == 0 || plan->f * plan->f > CV_MAX_TAPS || plan->n_out == 0 || ctx->np == 0) return HE_ERR_BADARG;
     uint32_t n_rot = 0;
     for (uint32_t st : tap_slot_steps(plan->W, plan->R, plan->f, ctx->N / 2)) n_rot += st != 0;
     *h_bytes = conv2d_ws_elems(ctx, plan->level, n_rot, plan->n_out, plan->deferred_taps != 0, hoisted_ras_terms(plan)) * sizeof(u64);
@@ -540,7 +540,7 @@ extern "C" int32_t he_ws_query_raconv(const he_ctx* ctx, const he_raconv_plan* p
     return he_guard(ctx, "he_ws_query_raconv: host allocation failed", [&]() -> int32_t {
     if (!ctx || !plan || !h_bytes) return HE_ERR_BADARG;
     if (plan->level == 0 || plan->level >= ctx->nq) return HE_ERR_LEVEL;
-    if ((plan->f & 1u) == 0 || plan->f * plan->f > CV_MAX_TAPS || plan->n_in == 0) return HE_ERR_BADARG;
+    if ((plan->f & 1u) == 0 || plan->f * plan->f > CV_MAX_TAPS || plan->n_in == 0 || ctx->np == 0) return HE_ERR_BADARG;
     uint32_t n_rot = 0;
     for (uint32_t st : tap_slot_steps(plan->W, plan->R, plan->f, ctx->N / 2)) n_rot += st != 0;
     *h_bytes = raconv_ws_elems(ctx, plan->level, plan->f * plan->f, n_rot, plan->deferred_moddown != 0) * sizeof(u64);
@@ -649,6 +649,7 @@ extern "C" int32_t he_ws_query_ca_ra_block(const he_ctx* ctx, const he_block_pla
     if (!ctx || !plan || !h_bytes) return HE_ERR_BADARG;
     int32_t rc = block_check(ctx, plan);
     if (rc != HE_OK) return rc;
+    if (ctx->np == 0) return HE_ERR_BADARG;
     uint32_t n_rot = 0;
     for (uint32_t st : tap_slot_steps(plan->W, plan->R, plan->f, ctx->N / 2)) n_rot += st != 0;
     *h_bytes = block_shape(ctx, plan, n_rot).total * sizeof(u64);

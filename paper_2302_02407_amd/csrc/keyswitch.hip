@@ -1457,6 +1457,7 @@ int32_t he_ws_query_rotate_batch(const he_ctx* ctx, uint32_t level, uint32_t n_c
     if (level >= ctx->nq) return HE_ERR_LEVEL;
     const uint64_t jobs = (uint64_t)n_ct * n_steps;
     if (jobs > 0xFFFFFFFFull) return HE_ERR_BADARG;
+    if (jobs && ctx->np == 0) return HE_ERR_BADARG;
     *h_bytes = jobs == 0 ? 0 : ks_engine_ws_elems(ctx, level, hoisted ? n_ct : (uint32_t)jobs, (uint32_t)jobs) * sizeof(u64);
     return HE_OK;
     });

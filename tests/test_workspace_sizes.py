@@ -47,3 +47,15 @@ def test_the_hoisted_sum_of_a_block_leaves_room_for_its_square(prm):
                 plan = BlockPlan(2, 8, slots // 16, 1, 3, 1, 2 * group, level, group, 0, hoisted)
                 need.append(query("he_ws_query_ca_ra_block", ctx, C.byref(plan)))
             assert need[0] <= need[1], (level, group)
+
+
+def test_a_chain_without_special_primes_is_refused():
+    """The calls refuse it and so do their queries."""
+    from paper_2302_02407_amd import binding
+    ctx, v, lib = context(12, 8, 0, 4), C.c_uint64(), binding.load()
+    plans = {"he_ws_query_conv2d": binding.ConvPlan(2, 8, 128, 1, 3, 2, 4), "he_ws_query_raconv": binding.RaConvPlan(2, 32, 1, 3, 4),
+             "he_ws_query_ca_ra_block": binding.BlockPlan(2, 8, 128, 1, 3, 1, 2, 4)}
+    for name, plan in plans.items():
+        assert getattr(lib, name)(C.addressof(ctx), C.byref(plan), C.byref(v)) == -1, name
+    assert lib.he_ws_query_rotate_batch(C.addressof(ctx), 4, 3, 2, 0, C.byref(v)) == -1
+    assert lib.he_ws_query_rotate_batch(C.addressof(ctx), 4, 0, 2, 0, C.byref(v)) == 0 and v.value == 0
