@@ -41,3 +41,31 @@ def test_conversion_edges(logN, q_bits, nq, p_bits, np_, dnum, levels, n_ct, fil
         ctx.he_rotate_batch([dev(c) for c in cts], level, [step], outs, hoisted=False)
         for c, o in zip(cts, outs):
             assert (host(o) == orc.rotate(c, level, orc.galois_elt(step), key)).all(), level
+
+
+@pytest.mark.parametrize("logN,bits,n_ct", [(13, 60, 6), (13, 36, 6), (15, 60, 2), (16, 36, 1)])
+@pytest.mark.parametrize("fill", ["top", "mixed"])
+def test_full_contraction_of_the_widest_primes(logN, bits, n_ct, fill):
+    """Eight sources and sixteen targets in tiles of 1024 points (the smallest ring among them, whose small batches all take the
+    small tiles), primes just below 2^60 and 2^36, every residue at its top or at zero."""
+    from gpu_util import dev, host, zeros
+    from oracle.he_oracle import Oracle
+    from paper_2302_02407_amd.binding import HEContext
+    from test_gpu_widest_primes import primes_below
+    m = primes_below(1 << bits, 2 << logN, 24)
+    q, p, dnum, level, step = m[8:], m[:8], 2, 15, 5
+    rng, orc, ctx, N = S.make_rng(800 + logN + bits), Oracle(logN, q, p, dnum), HEContext(logN, q, p, dnum), 1 << logN
+
+    def residues(moduli, n):
+        top = np.broadcast_to(np.array(moduli, dtype=np.uint64)[None, :, None] - np.uint64(1), (n, len(moduli), N)).copy()
+        if fill == "mixed":
+            top[rng.integers(0, 2, size=top.shape) == 1] = 0
+        return top
+
+    key = residues(q + p, 2 * dnum).reshape(dnum, 2, 24, N)
+    ctx.he_evk_register(ctx.galois_elt(step), dev(key))
+    cts = [residues(q, 2) for _ in range(n_ct)]
+    outs = [zeros(2, level + 1, N) for _ in cts]
+    ctx.he_rotate_batch([dev(c) for c in cts], level, [step], outs, hoisted=False)
+    for c, o in zip(cts, outs):
+        assert (host(o) == orc.rotate(c, level, orc.galois_elt(step), key)).all()

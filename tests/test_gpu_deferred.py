@@ -81,6 +81,17 @@ def test_rotate_sum_two_pass_ring():
     _sum_case(prm, 71, 4, [1, 2, 0, 100])
 
 
+@pytest.mark.parametrize("logN,q_bits,nq,p_bits,np_,dnum,level,steps", [
+    (14, 54, 8, 60, 1, 8, 7, [1, 2, 3, 0, 5, 4097, 7]),     # eight digits, three at a time
+    (15, 60, 4, 59, 2, 2, 3, list(range(1, 17)) + [0]),     # wide moduli, as many terms as one launch takes
+    (17, 57, 5, 58, 2, 3, 4, [3, 0, 2, 65535]),             # the largest ring, three digits, the last of one limb
+])
+def test_rotate_sum_rings_between(logN, q_bits, nq, p_bits, np_, dnum, level, steps):
+    """The other rings whose transforms compute the summed accumulator."""
+    prm = toy_params(logN=logN, q_bits=q_bits, nq=nq, p_bits=p_bits, np_=np_, dnum=dnum, hamming=32, seed=74)
+    _sum_case(prm, 74 + logN, level, steps)
+
+
 @pytest.mark.parametrize("level,steps", [
     (22, [2, 62, 64, 66, 0, 32766, 32706, 32704, 32702]),     # the 9 taps of the 3x3 layer on 32x32 with R = 2
     (5, [1, 0, 2, 4]),

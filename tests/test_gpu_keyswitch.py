@@ -410,10 +410,10 @@ def test_random_parameter_sets_match_oracle(case):
 
 @pytest.mark.parametrize("logN,q_bits,p_bits", [(13, 40, 50), (15, 54, 60), (17, 36, 59), (14, 57, 58)])
 def test_two_pass_generic_rings_key_switching(logN, q_bits, p_bits):
-    """Ring sizes above 2^12 other than 2^16 (the paper's N = 2^15 and 2^17 among them) run the generic
-    transform in two passes with gathered sources, per-limb output scaling and the stand-alone ModDown
-    epilogue: key switch, hoisted and single rotations, conjugation, rescale and ct x ct multiply against the
-    oracle, at the top level (three digits, the last one partial) and at a level with two digits."""
+    """Ring sizes above 2^12 other than 2^16 (the paper's N = 2^15 and 2^17 among them; at 2^17 the conversions and
+    their column passes are separate kernels): key switch, hoisted and single rotations, conjugation, rescale and
+    ct x ct multiply against the oracle, at the top level (three digits, the last one partial) and at a level
+    with two digits."""
     from gpu_util import dev, host, zeros
     prm = toy_params(logN=logN, q_bits=q_bits, nq=5, p_bits=p_bits, np_=2, dnum=3, hamming=64, seed=300 + logN)
     rng, orc, ctx, cl = _setup(prm, 300 + logN)
@@ -461,10 +461,10 @@ def test_two_pass_generic_rings_key_switching(logN, q_bits, p_bits):
 
 def test_low_levels_single_launch_conversions():
     """N = 2^16 at the low levels the networks run at, where a single key switch is a handful of limbs: the
-    conversions take the single-launch column kernel (inverse column pass, basis conversion and forward column
-    pass in one).  One full digit (levels 5, 7), two digits (8, 15: a one-limb and a full second digit), singly,
-    hoisted in pairs and as a conjugation, bit for bit against the oracle; a batch of three rotations (large
-    enough to take the separate kernels) must give the same bits as the single calls."""
+    conversions of one or two digits of one source take the 256-point tiles.  One full digit (levels 5, 7), two
+    digits (8, 15: a one-limb and a full second digit), singly, hoisted in pairs and as a conjugation, bit for
+    bit against the oracle; a batch of three rotations, whose ModDowns take the 1024-point tiles, must give the
+    same bits as the single calls."""
     from gpu_util import dev, host, zeros
     prm = config_params(2)
     rng, orc, ctx, cl = _setup(prm, 77)

@@ -11,11 +11,14 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("logN,counts", [
     (13, (2, 1, 3)),            # few limbs: rows of 64 threads, the smallest ring
-    (14, (90, 91, 76)),         # one limb more than those take, runs of 16 with 10, 11 and 12 left over
+    (14, (90, 91, 76)),         # one limb more than those take: runs of 4 with 2, 3 and none left over
     (16, (21, 21, 22)),         # the last launch of 64 threads to a row ...
     (16, (17, 16, 32)),         # ... and the first of runs, one limb more than a run holds
     (16, (1, 34, 32)),          # a lone limb among full runs
-    (17, (12, 12, 9)),          # exactly three of four lanes in the last run
+    (17, (12, 12, 9)),          # one limb in the last run of its modulus
+    (16, (133, 134, 135)),      # runs of 8, two rounds of four: 5, 6 and 7 left over
+    (16, (129, 130, 131)),      # ... and 1, 2 and 3
+    (17, (130, 135, 141)),      # runs of 16: 2, 7 and 13 left over
 ])
 def test_row_runs(logN, counts):
     from gpu_util import dev, host
