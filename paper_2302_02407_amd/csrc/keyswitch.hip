@@ -3,7 +3,9 @@
 //
 //   ModUp   : digit limbs -> coefficient form (iNTT with the factor (Q_j/q_i)^-1 folded into
 //             the N^-1 scaling) -> fast basis conversion to every other limb of
-//             {q_0..q_l, p_*} (128-bit accumulation, one Barrett step) -> NTT.
+//             {q_0..q_l, p_*} -> NTT.  For N = 2^13 .. 2^16, at most 8 sources and moduli of at least 36 bits the conversion
+//             runs on the matrix cores, in one launch with the column passes before and after it (colconv.hip);
+//             elsewhere it is a launch of its own with 128-bit sums and a Barrett step (baseconv_kernel).
 //   inner   : acc_c[r] = sum_j sigma_g(raised_j)[r] * evk_j,c[r]   (sigma_g as a gather).  From N = 2^13 this
 //             sum is evaluated inside the transforms of ModDown that consume it (special-prime limbs as
 //             the first inverse pass loads its rows, q-limbs in the epilogue of the last forward pass)
@@ -239,22 +241,6 @@ int32_t launch_moddown_final(he_ctx* c, const u64* conv, uint32_t n_jobs, const 
     return HE_OK;
 }
 
-// ---------------------------------------------------------------- rescale kernels
-// grid: (N/256, level, 2*n).  t = coefficient-form limb `level` of (job, comp) (tmp[job*2+comp][N]);
-// delta[job][comp][r] = (h mod q_r) - ((t + h mod q_l) mod q_r), h = floor(q_l/2); negate != 0 stores -delta (for the
-// forward transform whose epilogue subtracts what it transformed).
-__global__ __launch_bounds__(KS_THREADS) void rescale_delta_kernel(const u64* __restrict__ tmp, u64* __restrict__ delta,
-                                                                   const ModConst* mc, uint32_t logN, uint32_t level, uint32_t negate) {
-    const uint32_t n = blockIdx.x * KS_THREADS + threadIdx.x;
-    const uint32_t r = blockIdx.y, jc = blockIdx.z;
-    const ModConst ml = mc[level], mr = mc[r];
-    u64 h = ml.q >> 1;
-    u64 t = addmod(tmp[((size_t)jc << logN) + n], h, ml.q);
-    u64 tr = barrett64(t, mr.q, mr.mu, mr.bits);
-    u64 hr = barrett64(h, mr.q, mr.mu, mr.bits);
-    delta[((size_t)(jc * level + r) << logN) + n] = negate ? submod(tr, hr, mr.q) : submod(hr, tr, mr.q);
-}
-
 // ---------------------------------------------------------------- host: tables
 
 static uint32_t num_digits(const he_ctx* c, uint32_t level) { return (level + c->alpha) / c->alpha; }
@@ -414,8 +400,9 @@ static void engine_shape(const he_ctx* c, uint32_t level, uint32_t n_src, uint32
     cb = std::min<uint32_t>(std::min<uint32_t>(n_src, HE_MAX_SEGS), std::max<uint32_t>(1, HE_MAX_LAUNCH_LIMBS / (level + 1)));
     jb = std::min<uint32_t>(n_jobs, moddown_most_jobs(c, level));
     // Sources that each serve one job come in launch sets as large as the jobs' where 16 jobs fit: smaller rings and lower
-    // levels do not fill the chip with 8 (six ciphertexts by eight rotations at N = 2^14: 460 -> 370 us, nine by six at level
-    // 5 of N = 2^16: 1512 -> 1377).  Sources that serve several jobs stay at 8, so that the jobs of one key are as many as the
+    // levels do not fill the chip with 8 (six ciphertexts by eight rotations at N = 2^14: 441 us with 8, 336 with 16; four by
+    // seven at 2^15 755 and 693; nine by six at level 5 of N = 2^16 1489 and 1356).  The raised digits then take twice
+    // the memory.  Sources that serve several jobs stay at 8, so that the jobs of one key are as many as the
     // work groups that share its limbs' cache.
     const bool pairs = n_src == n_jobs && jb == std::min<uint32_t>(n_jobs, HE_MAX_KS_JOBS);
     cb = std::min<uint32_t>(cb, pairs ? HE_MAX_KS_JOBS : 8);
@@ -1310,19 +1297,13 @@ int32_t rescale_batch(he_ctx* ctx, const u64* const* cts, u64* const* outs, uint
         t.mod_idx = mods.data(); t.src_seg = seg.data(); t.src_limb = lim.data();
         int32_t rc = launch_transform(ctx, t);
         if (rc != HE_OK) return rc;
-        // forward transform of -delta whose epilogue writes (c - (-delta)) * q_l^-1: the input limb plays the stored
-        // accumulator (component stride level+1 limbs), q_l^-1 mod q_r the constant of the final product.  From N = 2^13
-        // the first pass forms -delta from the dropped limb's coefficients as it reads them; otherwise a kernel does.
+        // forward transform of -delta, delta = h - ((t + h) mod q_l) with h = floor(q_l / 2), which the first pass forms from the dropped
+        // limb's coefficients t as it reads them; its epilogue writes (c - (-delta)) * q_l^-1: the input limb plays the
+        // stored accumulator (component stride level+1 limbs), q_l^-1 mod q_r the constant of the final product
         const uint32_t total = 2 * nb * level;
-        const bool fused_delta = two_pass(ctx);
         std::vector<uint32_t> dm(total);
         std::vector<uint16_t> dsrc(total);
         for (uint32_t i = 0; i < total; i++) { dm[i] = i % level; dsrc[i] = (uint16_t)(i / level); }
-        if (!fused_delta) {
-            dim3 grid(N / KS_THREADS, level, 2 * nb), block(KS_THREADS);
-            hipLaunchKernelGGL(rescale_delta_kernel, grid, block, 0, ctx->stream, tmp, delta, ctx->d_mc, ctx->logN, level, 1u);
-            HE_HIP(ctx, hipGetLastError());
-        }
         ModDownEpilogue ep = {};
         ep.acc = cts[b0]; ep.R = L1; ep.L1 = level;
         ep.pinv = ctx->d_qlinv + (size_t)level * ctx->nq; ep.pinv_sh = ctx->d_qlinv_sh + (size_t)level * ctx->nq;
@@ -1332,9 +1313,9 @@ int32_t rescale_batch(he_ctx* ctx, const u64* const* cts, u64* const* outs, uint
             ep.out0[i] = outs[b0 + i]; ep.out1[i] = outs[b0 + i] + (size_t)level * N;
         }
         TransformDesc f = {};
-        f.fwd = true; f.seg[0] = delta; f.n_seg = 1; f.dst = delta; f.n = total; f.mod_idx = dm.data(); f.ep = &ep;
+        f.fwd = true; f.seg[0] = tmp; f.n_seg = 1; f.src_limb = dsrc.data(); f.dst = delta; f.n = total; f.mod_idx = dm.data(); f.ep = &ep;
         f.lazy_out = true;
-        if (fused_delta) { f.seg[0] = tmp; f.src_limb = dsrc.data(); f.rescale_from = level + 1; }
+        f.rescale_from = level + 1;
         rc = launch_transform(ctx, f);
         if (rc != HE_OK) return rc;
         ctx->cnt.rescale += nb;

@@ -47,8 +47,8 @@ extern "C" int32_t he_rescale_noalloc(he_ctx* ctx, const uint64_t* d_ct, uint32_
     if (rc != HE_OK) return rc;
     u64* ptr = g_scratch_ptr[ctx->device];
     // every scratch element that is read has been written earlier in the same call (the inverse transform
-    // writes the coefficient form, the correction kernel writes every term before it is transformed), so
-    // nothing has to be cleared between calls
+    // writes the coefficient form, the forward transform's first pass the correction terms that its second
+    // reads), so nothing has to be cleared between calls
     const u64* cts[1] = {(const u64*)d_ct};
     u64* outs[1] = {(u64*)d_out};
     return rescale_batch(ctx, cts, outs, 1, level, ptr);
