@@ -123,15 +123,19 @@ const char* he_last_error(const he_ctx* ctx);
 int32_t he_ctx_psi(const he_ctx* ctx, uint32_t mod_idx, uint64_t* h_psi_out);
 int32_t he_counters(const he_ctx* ctx, he_counters_t* h_out);
 int32_t he_counters_reset(he_ctx* ctx);
-/* Timing of the transform kernels (the dominant kernels of every entry point) with a HIP event
- * pair around each launch on the context's stream.  he_profile_begin starts collecting;
+/* Timing of the transform kernels (the dominant kernels of every entry point above N = 2^12) with
+ * a HIP event pair around each launch on the context's stream.  he_profile_begin starts collecting;
  * he_profile_end synchronises the stream, sums the spans and stops.  transform_limb_passes
- * counts limbs per launch (a full NTT of one limb at N > 2^12 is two launches = two passes).
+ * counts limbs per launch (a full NTT of one limb at N > 2^12 is two launches = two passes; a
+ * basis conversion that is one launch with its column passes counts its sources and its targets).
  * inner_product_digit_limbs counts the raised-digit limbs that passes carrying the key-switch
- * inner product have to read besides their own limb (N = 2^16 path; 0 elsewhere).
- * pass_* split the same launches by kind: 0 forward column pass, 1 forward row pass, 2 forward row
- * pass carrying the inner product of the q-limbs and the ModDown epilogue, 3 inverse row pass,
- * 4 inverse row pass computing the inner product of the special-prime limbs, 5 inverse column pass.
+ * inner product have to read besides their own limb (N > 2^12 with at most 8 digits; 0 elsewhere).
+ * pass_* split the same launches by kind: 0 forward column pass, or basis conversion with the
+ * inverse column pass of its sources and the forward column pass of its targets (N = 2^13 .. 2^16),
+ * 1 forward row pass, 2 forward row pass carrying the epilogue of ModDown or Rescale and, for a key
+ * switch, the inner product of the q-limbs, 3 inverse row pass, 4 inverse row pass computing the
+ * inner product of the special-prime limbs, 5 inverse column pass.  Up to N = 2^12 whole transforms
+ * count as kinds 1 and 3, and the kernels that run a key switch or a Rescale in one or two launches are not timed.
  * key_limbs_read counts the evaluation-key limbs the inner products had to read in the order the
  * engine ran them (one pass over a key per group of same-key jobs of a launch set). */
 typedef struct {
@@ -147,7 +151,7 @@ typedef struct {
 int32_t he_profile_begin(he_ctx* ctx);
 int32_t he_profile_end(he_ctx* ctx, he_profile_t* h_out);
 /* Vector-ALU roof of the transforms on this GPU, measured: radix-2 butterflies per second when the
- * register blocks of the N = 2^16 passes (Shoup twiddle product from 32-bit multiplies, lazy ranges)
+ * register blocks of the two-launch passes (Shoup twiddle product from 32-bit multiplies, lazy ranges)
  * run back to back out of registers: forward and inverse on the first ciphertext prime, forward on
  * the first modulus wider than 57 bits (0 if there is none).  Synchronises the stream. */
 typedef struct {
@@ -163,9 +167,9 @@ const char* he_build_id(void);
 int32_t he_sync(he_ctx* ctx);
 
 /* Workspace.  The context owns one device workspace.  It is sized at creation for every call that works
- * on one ciphertext at the top level (he_keyswitch, he_rotate, he_conjugate, he_rotate_hoisted, he_mulct,
- * he_rescale); the batched calls and the convolutions may need more and then grow it on entry, which
- * synchronises the stream, frees and reallocates.  To keep that out of a timed or latency-critical
+ * on one ciphertext at the top level and switches at most one key (he_keyswitch, he_rotate, he_conjugate,
+ * he_mulct, he_rescale); several rotations at once, the batched calls and the convolutions may need more and then grow it
+ * on entry, which synchronises the stream, frees and reallocates.  To keep that out of a timed or latency-critical
  * region, ask the matching he_ws_query_* for the size (bytes, host output) and call he_ws_reserve once
  * beforehand.  he_ws_reserve never shrinks the workspace; he_ws_bytes reports its current size.
  * A size also serves the same call at that level with fewer ciphertexts, steps or outputs.

@@ -13,12 +13,13 @@
 // is a product over k = (source, byte), 64 of them, whose right factors split into 8 signed base-256 digits b:
 // v_mfma_i32_16x16x64_i8 with the digits as rows and 16 points as columns.  A source residue in memory order IS the operand
 // (each byte minus 128, which the constant term returns).  Two instructions give 16 points x 4 targets x 8 digits, laid
-// out so that a lane gets the 8 digit sums of one (point, target); they are put together and reduced below 2q in 17
-// vector instructions, where the vector-unit form of the same sum takes 52.
+// out so that a lane gets the 8 digit sums of one (point, target); they are put together and reduced below 2q in 22
+// vector instructions (counted in the compiled loops), where the vector-unit form of the same sum takes 68 (baseconv_kernel).
 //
-// What bounds it is vector issue: about 6300 instructions per wavefront for 8 + 24 limbs, 4.5 cycles each, are 47 of the 50 us
-// that two work groups per compute unit take.  ModUp and ModDown of 8 rotations at the benchmark's top level: 162 -> 151 us
-// once a round's operands came without dependent vector loads and nothing was kept in scratch memory.
+// What bounds it is vector issue: 5965 instructions per wavefront for 8 + 24 limbs (counters), 4 cycles each, fill 0.69 of the
+// issue slots (2.4 GHz) of the benchmark's launches; the rest goes to barriers between the phases and to last waves of work groups.
+// A launch of the benchmark's single rotations went from 162 to 151 us once a round's operands came without dependent vector
+// loads and nothing was kept in scratch memory; it takes 145 now, 8.7 of the 23.3 ms of 240 rotations.
 #include <algorithm>
 
 #include "modarith.h"
@@ -331,12 +332,18 @@ int32_t launch_col_conv(he_ctx* ctx, ColConv& cc, const ScaleList& sc, uint32_t 
         HE_HIP(ctx, hipEventRecord(e0, ctx->stream));
     }
     const uint32_t tiles16 = 1u << (LC - 2);
-    // Tiles of 256 points while the rounds of all 1024-point tiles would not give every second compute unit a work group: one
-    // rotation at level 5 66 -> 59 us; at twice that a ciphertext product (level 11) took 143 us instead of 136.
+    // Tiles of 256 points while the rounds of all 1024-point tiles would not give every second compute unit a work group (the
+    // sources of a tile are at most 8, one phase, and are not counted).  One rotation at level 5 of N = 2^16: 63.0 us with the
+    // large tiles, 55.3 with the small ones; at level 5 of 2^14 44.6 and 35.2, at level 2 of 2^13 36.1 and 30.2.  With the line at
+    // 192 three rotations at level 5 take 106.2 us instead of 101.3 and eight at level 2 of 2^13 44.1 instead of 41.4; at 256 one at
+    // level 11 takes 93.5 instead of 84.8.  At 64 one at level 5 takes 56.9.
     const bool small = groups * tiles16 * rounds <= 128;
     const uint32_t work = groups * tiles16 * (small ? 4 : 1);
-    // while two work groups per compute unit have room for it, the rounds of a tile run side by side (a relinearisation at
-    // level 11 and its rescale: 161 -> 156 us)
+    // While two work groups per compute unit have room for it, the rounds of a tile run side by side, each with the inverse pass
+    // of its own: a ciphertext product and its rescale at level 11 takes 127 us instead of 136, one rotation at level 15 92
+    // instead of 104, at level 20 of the six-digit set 184 instead of 190.  Where the tiles alone fill most of a work group per
+    // compute unit the repeated pass costs what the shorter chain gives or more (at level 23 156 us instead of 152, two
+    // at level 11 128 instead of 119; one work group per compute unit as the limit gives 147 and 119, but 185 at that level 20).
     const uint32_t parts = std::max(1u, std::min(rounds, 512 / work));
     cc.share = (rounds + parts - 1) / parts * CC_WAVES;
     cc.parts = (rounds * CC_WAVES + cc.share - 1) / cc.share;

@@ -213,9 +213,9 @@ int32_t he_ctx_create(he_ctx** out, uint32_t logN, const uint64_t* h_q, uint32_t
             return rc;
         }
     }
-    // workspace for every one-ciphertext call at the top level: one key switch (raised digits +
-    // temporaries) with the three tensor-product polynomials of a ct x ct multiplication behind it, or
-    // one rescale; only the batched calls and the convolutions can need more (he_ws_reserve)
+    // workspace for every call at the top level that switches one key: raised digits and temporaries
+    // with the three tensor-product polynomials of a ct x ct multiplication behind them, or
+    // one rescale; several rotations at once and the convolutions can need more (he_ws_reserve)
     if (np > 0) {
         size_t elems = ks_engine_ws_elems(c, nq - 1, 1, 1) + (size_t)3 * nq * N;
         if (nq > 1) elems = elems > rescale_ws_elems(c, nq - 1, 1) ? elems : rescale_ws_elems(c, nq - 1, 1);

@@ -49,8 +49,8 @@ struct ProfSpan {
     hipEvent_t e0, e1;
     uint32_t limbs;   // limbs transformed by the launch between the two events
     uint32_t digit_limbs; // raised-digit limbs a pass that carries the key-switch inner product has to read
-    uint32_t kind;        // he_profile_t::pass_ms index: 0 fwd column, 1 fwd row, 2 fwd row + inner product/epilogue,
-                          // 3 inv row, 4 inv row + inner product, 5 inv column
+    uint32_t kind;        // he_profile_t::pass_ms index: 0 fwd column or conversion with its columns, 1 fwd row, 2 fwd row +
+                          // inner product/epilogue, 3 inv row, 4 inv row + inner product, 5 inv column
 };
 
 struct he_ctx {

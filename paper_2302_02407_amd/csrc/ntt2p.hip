@@ -975,9 +975,11 @@ int32_t launch_transform2p(he_ctx* ctx, const TransformDesc& d) {
     for (uint32_t i = live; i < padded; i++) tab.e[i] = TAB_NONE;
     // A row is shared by 64 threads instead of 16 while 16 would make at most 4 wavefronts per SIMD, about what the chip holds at
     // once: such a launch is as long as one wavefront's chain of loads and butterflies, which is a fourth as long on four
-    // times the wavefronts.  One rotation at level 5: 72 -> 63 us; up to 2 wavefronts per SIMD a rotation pair at level 12
-    // took 174 us instead of 171, beyond 8 a block of layers 1262 instead of 1254.  A sum of several terms is always one
-    // output's limbs, each with a long chain of its own.
+    // times the wavefronts.  One rotation at level 5: 65 us with 16 threads, 55 with 64; at level 11 of N = 2^15 70 and 57.
+    // With the line at 2048 two rotations at level 11 take 131.5 us instead of 129.1 and one at level 20 of the six-digit
+    // set 187 instead of 182; at 8192 a block of layers takes 1255 instead of 1251, at 16384 that rotation 186 again.  Eight
+    // at level 5 take 220 instead of 215 because their smallest launch falls under the line.  A sum of several terms is
+    // always one output's limbs, each with a long chain of its own.
     const bool terms = (d.ep && d.ep->fused && d.ep->n_terms) || (d.ip && d.ip->n_terms);
     const bool wide_rows = terms || live * (ctx->N >> 10) <= 4096;
     const dim3 block(P2_THREADS), grid_cols(live * tiles), grid_rows(padded * tiles * (wide_rows ? 4 : 1));
