@@ -1,14 +1,15 @@
 #!/usr/bin/env python3
 """Benchmark of the MI355X homomorphic-convolution hot path (one GPU).
 
-Primary workload (BASELINE configs[2]): rotation / key-switch benchmark at N = 2^16, 24 ciphertext
+Primary workload: rotation / key-switch benchmark at N = 2^16, 24 ciphertext
 limbs of 54 bits + 8 special primes of 60 bits, dnum = 3.  One step = a batch of ciphertexts, each
 rotated by all 15 power-of-two steps 2^0..2^14, once singly (own ModUp per rotation) and once
 hoisted (one shared ModUp), both through the batched entry point he_rotate_batch: 30 key switches
 per ciphertext per step.  value = key switches / s.
-The same run also reports the NTT round-trip rate of configs[1] and the he_conv2d latency of
-configs[3] as extra fields, the roofline of the dominant kernel (the NTT tile kernel) from HIP
-events around each of its launches, and the CPU oracle timed on a bounded sample.
+The same run also reports the rate of NTT round trips of 384 limbs and the he_conv2d latency of a
+16 -> 16 channel layer as extra fields, the roofline of the dominant kernels (the transform passes, with the
+conversions, inner products and epilogues they carry) from HIP events around each of their
+launches, and the CPU oracle timed on a bounded sample.
 
 All inputs are synthetic and seeded; ciphertexts, keys and plaintexts are uniform residues (what
 real ones look like limb by limb), generated on the device, so the timed region starts with
@@ -52,7 +53,7 @@ def uniform_dev(torch, gen, moduli, N, lead=()):
 
 
 def run_only(args, torch, ctx, prm, gen):
-    """One extra workload in isolation: configs[1] NTT round trip or configs[3] CAConv."""
+    """One extra workload in isolation."""
     N, level = prm.N, len(prm.q) - 1
     if args.only == "crot5":
         # one rotation of a 6-limb ciphertext (the levels the paper's networks work at), in isolation
@@ -115,7 +116,7 @@ def main():
     ap.add_argument("--gpus", type=int, default=1)
     ap.add_argument("--steps", type=int, default=3)
     ap.add_argument("--warmup", type=int, default=1)
-    ap.add_argument("--batch", type=int, default=64, help="ciphertexts per step (configs[2] names 64)")
+    ap.add_argument("--batch", type=int, default=64, help="ciphertexts per step (the benchmark takes 64)")
     ap.add_argument("--no-cpu", action="store_true", help="skip the oracle timing leg")
     ap.add_argument("--no-extras", action="store_true", help="skip the NTT and conv2d extra measurements")
     ap.add_argument("--only", choices=["ntt", "conv2d", "conv0", "crot5", "conv5", "raconv", "convh", "conv5h"], help="run just this extra workload --steps times (for profiling "
@@ -148,7 +149,7 @@ def main():
     del calib_src, calib_dst
 
     if args.only == "conv0":
-        # configs[0]: tiny CAConv at N = 2^12 in isolation (for a kernel trace of the latency path)
+        # tiny CAConv at N = 2^12 in isolation (for a kernel trace of the latency path)
         prm0 = config_params(0)
         ctx0 = HEContext.from_params(prm0)
         N0, lv0 = prm0.N, len(prm0.q) - 1
@@ -212,15 +213,19 @@ def main():
 
 
     # roofline of the dominant kernels: one more, identical step with an event pair around every
-    # transform launch (kept out of the timed steps so the events do not perturb `value`)
+    # transform launch (kept out of the timed steps so the events do not perturb `value`); the share of the
+    # step is taken of this step, whose launches the events hold apart
+    t0 = time.perf_counter()
     ctx.he_profile_begin()
     step()
-    prof = ctx.he_profile_end()
+    prof = ctx.he_profile_end()                          # synchronises
+    prof_step_ms = (time.perf_counter() - t0) * 1e3
     build_id = ctx.he_build_id()
     limb_bytes = N * 8
     passes_per_transform = 2 if prm.logN > 12 else 1
     # algorithmic bytes: a limb transform reads and writes its limb once (2*N*8 B = 1 MiB at N = 2^16);
-    # it runs as two passes, each credited half: 0.5 MiB per limb pass and nothing else
+    # it runs as two passes, each credited half: 0.5 MiB per limb pass and nothing else.  A conversion counts its
+    # sources (inverse columns) and its targets (forward columns), which are the limbs it reads and writes
     alg_bytes = prof["transform_limb_passes"] * (2.0 * limb_bytes) / passes_per_transform
     t_s = prof["transform_ms"] * 1e-3
     launches = max(1, prof["transform_launches"])
@@ -229,7 +234,8 @@ def main():
     # stamped with the build it was taken on and is not quoted for any other build
     bplp = _profile_constant(TRAFFIC_FILE, "transform_bytes_per_limb_pass", build_id)
     ops = _profile_constant(VALU_FILE, "transform_valu_lane_ops_per_limb_pass", build_id)
-    kinds = ["fwd_column", "fwd_row", "fwd_row_inner_product_moddown", "inv_row", "inv_row_inner_product", "inv_column"]
+    # at N = 2^16 a key switch has no column pass of its own: kind 0 is the conversion with the columns around it
+    kinds = ["conversion_with_columns", "fwd_row", "fwd_row_inner_product_moddown", "inv_row", "inv_row_inner_product", "inv_column"]
     by_pass = {}
     for i, name in enumerate(kinds):
         if prof["pass_launches"][i]:
@@ -239,7 +245,7 @@ def main():
                              "us_per_limb_pass": round(ms_i * 1e3 / prof["pass_limbs"][i], 4),
                              "frac": round(prof["pass_limbs"][i] * limb_bytes / (ms_i * 1e-3) / 1e9 / HBM_PEAK_GBS, 4)}
     roofline = {
-        "kernel": "ntt16_* (the four passes of the N=2^16 transform, incl. the passes that carry the key-switch inner product and the ModDown epilogue)",
+        "kernel": "ntt_row_*_kernel and col_conv_kernel (the row passes, two of them carrying the key-switch inner product and the ModDown epilogue, and the basis conversion with the column passes around it: everything a key switch launches)",
         "bound": "hbm",
         "achieved": round(achieved, 1),          # 0.5 MiB per limb pass / time, nothing else counted
         "peak": HBM_PEAK_GBS,
@@ -251,7 +257,7 @@ def main():
         "measured_GBps": None if bplp is None else round(bplp * prof["transform_limb_passes"] / t_s / 1e9, 1),
         "launches": prof["transform_launches"],
         "avg_launch_us": round(prof["transform_ms"] * 1e3 / launches, 2),
-        "share_of_step": round(prof["transform_ms"] / ms_per_step, 3),
+        "share_of_step": round(prof["transform_ms"] / prof_step_ms, 3),
         "by_pass": by_pass,
         # the same with the raised-digit limbs the inner-product passes have to read added (N*8 B each; keys not counted)
         "frac_with_digit_reads": round((alg_bytes + prof["inner_product_digit_limbs"] * limb_bytes) / t_s / 1e9 / HBM_PEAK_GBS, 4),
@@ -286,8 +292,8 @@ def main():
         ms_one_hoisted = timed(lambda: ctx.he_rotate_hoisted(cts[0], level, steps15, outs[:15]))
         # the whole key switch against the HBM roof.  Compulsory bytes of one key switch = input polynomial
         # (L1 limbs) + outputs (2*L1 limbs) + its share of the key (2*dnum*(L1+k) limbs).  Loop order of this
-        # engine: rotations are ordered step-major within a wave of 8 raised sources and run in launch sets
-        # of up to 10 jobs; jobs of a set that use the same key share one pass over it, so the key is counted
+        # engine at this level: rotations are ordered step-major within a wave of 8 raised sources and run in launch
+        # sets of up to 10 jobs; jobs of a set that use the same key share one pass over it, so the key is counted
         # once per (launch set, key) - the engine reports those key limbs (key_limbs_read).  The own-key
         # figure (every key switch reads its whole key) is given beside it.
         own_bytes = (L1 + 2 * prm.dnum * (L1 + k) + 2 * L1) * limb_bytes
@@ -309,7 +315,7 @@ def main():
             "one_ct_hoisted_keyswitch_per_s": round(15 / (ms_one_hoisted * 1e-3), 1),
         })
     if not args.no_extras:
-        # configs[1]: NTT + iNTT round trip of 16 polys x 24 limbs; limb-GB/s counts the limb read and
+        # NTT + iNTT round trip of 16 polys x 24 limbs; limb-GB/s counts the limb read and
         # written once per transform
         idx = list(range(L1)) * 16
         data = uniform_dev(torch, gen, prm.q, N, lead=(16,))
@@ -355,7 +361,7 @@ def main():
         extras["table1_ms"] = {k_: round(v, 4) for k_, v in t1.items()}
         del lo_ct, lo_out
         del pt, acc, res, pt_rot
-        # configs[3]: ResNet-20-shaped CAConv, 16 -> 16 channels on 32x32, R = 2, level 23
+        # ResNet-20-shaped CAConv, 16 -> 16 channels on 32x32, R = 2, level 23
         conv_steps = sorted(set(((dy * 32 + dx) * 2) % (N // 2) for dy in (-1, 0, 1) for dx in (-1, 0, 1)) - {0}
                             | {2048, 4096, 8192, 16384})
         for s in conv_steps:
@@ -442,7 +448,7 @@ def main():
         del blk_out
         conv_weights_h = weights if not args.no_cpu else None
         del weights, conv_out, ra_w, ra_out, ra_w2
-        # configs[4]: downsampling block, 16 -> 32 channels, stride 2: 3x3 and 1x1 CAConv (16 outputs each),
+        # downsampling block, 16 -> 32 channels, stride 2: 3x3 and 1x1 CAConv (16 outputs each),
         # one-hot merges, p(p(u)) with four ct x ct multiplies, shortcut add (constants are arbitrary here:
         # the timing does not depend on values)
         w3 = [uniform_dev(torch, gen, prm.q, N) for _ in range(16 * 9)]
@@ -470,7 +476,7 @@ def main():
         del w3, w1, masks
 
     if not args.no_extras:
-        # configs[0]: tiny CAConv, N = 2^12, 4 -> 4 channels on 8x8, R = 8, level 2 (latency in microseconds)
+        # tiny CAConv, N = 2^12, 4 -> 4 channels on 8x8, R = 8, level 2 (latency in microseconds)
         prm0 = config_params(0)
         ctx0 = HEContext.from_params(prm0)
         N0, lv0 = prm0.N, len(prm0.q) - 1
@@ -529,7 +535,7 @@ def main():
         "metric": "HRot keyswitches/s", "value": round(value, 1), "unit": "keyswitch/s", "n_gpus": 1,
         "steps": args.steps, "warmup": args.warmup, "ms_per_step": round(ms_per_step, 3), "higher_is_better": True,
         "scaling": "weak", "vs_baseline": None, "dtype": "u64", "data": "synthetic",
-        "config": {"workload": "configs[2] rotation/key-switch: N=2^16, 24x54-bit + 8x60-bit primes, dnum=3, "
+        "config": {"workload": "rotation/key-switch benchmark: N=2^16, 24x54-bit + 8x60-bit primes, dnum=3, "
                                "%d ciphertexts x 15 steps, singly and hoisted" % B,
                    "batch": B, "keyswitches_per_step": ks_per_step},
         "roofline": roofline, "cpu_baseline": cpu,
