@@ -16,10 +16,10 @@
 // out so that a lane gets the 8 digit sums of one (point, target); they are put together and reduced below 2q in 22
 // vector instructions (counted in the compiled loops), where the vector-unit form of the same sum takes 68 (baseconv_kernel).
 //
-// What bounds it is vector issue: 5965 instructions per wavefront for 8 + 24 limbs (counters), 4 cycles each, fill 0.69 of the
-// issue slots (2.4 GHz) of the benchmark's launches; the rest goes to barriers between the phases and to last waves of work groups.
+// What bounds it is vector issue: 5965 instructions per wavefront for 8 + 24 limbs (counters), 4 cycles each, fill 0.68 of the
+// issue slots (2.4 GHz) of the benchmark's launches, which move 2.4 TB/s; wavefronts wait 0.45 of their cycles.
 // A launch of the benchmark's single rotations went from 162 to 151 us once a round's operands came without dependent vector
-// loads and nothing was kept in scratch memory; it takes 145 now, 8.7 of the 23.3 ms of 240 rotations.
+// loads and nothing was kept in scratch memory; it takes 147 now, 8.8 of the 23.4 ms of 240 rotations.
 #include <algorithm>
 
 #include "modarith.h"

@@ -940,7 +940,7 @@ struct HoistIp {
 // for h = 30: (period+3)*2^2h < 2^64, and period*2^(2*bits-2h) + 3q < 100q) the middle sum is formed, the carries of the
 // low and middle sums move up, the high sum is brought below 3q, and the signed accumulator is set to what keeps the
 // identity; the three sums are put together and reduced once at the end.  Digits are made canonical (the forward
-// transform may leave them below 69q) and split while they are staged into LDS, the low half in the low word.  JT = size
+// transform leaves them below 2q) and split while they are staged into LDS, the low half in the low word.  JT = size
 // of the register tile: ciphertexts a.J..JT-1 repeat ciphertext 0 and are not stored.
 #define HSL_MAX_TILES 24      // J * beta digit tiles of 2 KiB: 48 KiB of LDS
 #define HSL_RING 2            // (term, digit) pairs whose key values are in registers or on their way

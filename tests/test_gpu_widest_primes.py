@@ -92,3 +92,25 @@ def test_plaintext_sums(logN, bits, n):
         assert (host(acc) == want).all(), fill
         ctx.he_ptct_mac_rot(acc, d_cts, d_pts, gs, level, init=False)
         assert (host(acc) == orc.add(want, want, level)).all(), fill
+
+
+@pytest.mark.parametrize("logN", [9, 13, 16])
+@pytest.mark.parametrize("bits", [54, 55, 60])
+def test_hoisted_sums(logN, bits):
+    """The rotate-and-sum of he_conv2d as one hoisted sum: 15 terms of 3 digits, more than one fold of its split accumulators at
+    either width, keys at their top; it is the rotation sum of the rescaled output, repeated."""
+    from gpu_util import dev, host, zeros
+    prm, orc, ctx, residues = _setup(logN, bits, 4, 1, 4)
+    N, level, C_a = prm.N, 3, 16
+    block = N // 2 // C_a
+    gs = [orc.galois_elt(block * i) for i in range(1, C_a)]
+    for fill in ("top", "mixed"):
+        keys = [residues(prm.moduli, 8, fill).reshape(4, 2, -1, N) for _ in gs]
+        d_keys = [dev(k) for k in keys]
+        for g, k in zip(gs, d_keys):
+            ctx.he_evk_register(g, k)
+        ct, pts = residues(prm.q, 2, "uniform"), [residues(prm.q, 1, f)[0] for f in (fill, "uniform", "mixed")]
+        outs = ctx.he_conv2d(C_a, 1, block, 1, 1, level, [dev(p) for p in pts], dev(ct), [zeros(2, level, N) for _ in pts], hoisted_ras=True)
+        for p, o in zip(pts, outs):
+            x = orc.rescale(orc.ptct_mac(None, ct, p, level, init=True), level)
+            assert (host(o) == orc.rotate_sum_deferred([x] * C_a, level - 1, [1] + gs, [None] + keys)).all(), fill
