@@ -85,13 +85,14 @@ __global__ __launch_bounds__(CV_THREADS) void mac_many_kernel(MacMany a, const M
             SplitSum s0 = {0, 0, 0}, s1 = {0, 0, 0};
 #pragma unroll
             for (uint32_t i = 0; i < NI; i++) {
-                if (i && i % SPLIT_MAX == 0) {           // running totals below q + 2*5q
+                if (i && i % SPLIT_MAX == 0) {           // running totals below q + 6q, after a second time below 2q again
                     r0.v[k] += split_reduce(s0, m); r1.v[k] += split_reduce(s1, m);
+                    if (i > SPLIT_MAX) { r0.v[k] = reduce_lazy<4>(r0.v[k], m.q, m.bits, m.rec); r1.v[k] = reduce_lazy<4>(r1.v[k], m.q, m.bits, m.rec); }
                     s0 = s1 = SplitSum{0, 0, 0};
                 }
                 if (i < a.n_in) { split_mac(s0, c0[i].v[k], p[i].v[k]); split_mac(s1, c1[i].v[k], p[i].v[k]); }
             }
-            static_assert(NI <= 2 * SPLIT_MAX || NI == 16, "totals stay below 16q");
+            static_assert(NI <= 3 * SPLIT_MAX, "totals stay below 16q");
             r0.v[k] = reduce_full<7>(r0.v[k] + split_reduce(s0, m), m.q, m.bits, m.rec);
             r1.v[k] = reduce_full<7>(r1.v[k] + split_reduce(s1, m), m.q, m.bits, m.rec);
         }

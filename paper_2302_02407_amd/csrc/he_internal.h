@@ -172,6 +172,33 @@ struct IpPrologue {
     uint32_t n_terms;                   // as in ModDownEpilogue: > 0 = one output, arrays indexed by term
 };
 
+// Row passes of key switches whose sources serve one job each, or of one sum of rotations (ksrows.hip): raised digits in the state
+// the column pass leaves them.  Special primes: mid [J][2][k][N] receives the inverse rows of the inner products; q-limbs: mid
+// [J][2][L1][N] holds the converted part in the state the forward column pass leaves it, outputs as in ModDownEpilogue.
+#define KS_ROW_PRODUCTS 7           // products in one sum (modarith.h)
+struct KsRows {
+    const u64* raised[HE_MAX_KS_JOBS];  // [beta][R][N], by job (sum: by term, as own, evk and g)
+    const u64* own[HE_MAX_KS_JOBS];     // [L1][N]
+    const u64* evk[HE_MAX_KS_JOBS];     // [dnum][2][M][N]
+    const u64* c0[HE_MAX_KS_JOBS];
+    const u64* self0[HE_MAX_KS_JOBS];
+    const u64* self1[HE_MAX_KS_JOBS];
+    u64* out0[HE_MAX_KS_JOBS];
+    u64* out1[HE_MAX_KS_JOBS];
+    uint32_t g[HE_MAX_KS_JOBS];
+    u64* mid;
+    const u64* pinv;     // [nq]
+    const u64* pinv_sh;
+    uint32_t J, n_terms, beta, alpha, R, M, L1, k, nq;
+    uint32_t sum;                       // one output (J = 1), the sum over n_terms terms; else n_terms = 1
+    uint32_t count_up, count_down;      // whether the digits' / the ModDown's transforms are counted with these rows
+    // set by the launch
+    uint32_t logN;
+    const ModConst* mc;
+    const ulonglong2 *tw, *itw;
+};
+int32_t launch_ks_rows(he_ctx* ctx, KsRows& a, bool special);
+
 // One batched transform launch (both passes).  Limb i is read at seg[src_seg[i]] + src_limb[i]*N
 // by the first pass and lives at dst + i*N afterwards; mod_idx[i] == 0xFF leaves limb i alone.
 struct TransformDesc {

@@ -434,8 +434,14 @@ static void col_conv_widths(const he_ctx* c, ColConv& cc) {
     }
 }
 
-// ModUp of `cb` sources at once.  raised [cb][beta][R][N] (own limbs left unwritten), tmp [cb][L1][N].
-static int32_t modup_batch(he_ctx* c, const KsSrc* srcs, uint32_t cb, uint32_t level, u64* raised, u64* tmp) {
+static bool modup_by_columns(const he_ctx* c, uint32_t level) {
+    const uint32_t beta = num_digits(c, level);
+    return c->d_up_dig && beta <= CC_MAX_SETS && beta * (level + 1 + c->np) <= HE_MAX_LAUNCH_LIMBS;
+}
+
+// ModUp of `cb` sources at once.  raised [cb][beta][R][N] (own limbs left unwritten), tmp [cb][L1][N].  rows = false: the last
+// pass of the digits' transforms, their rows, is left to launch_ks_rows.
+static int32_t modup_batch(he_ctx* c, const KsSrc* srcs, uint32_t cb, uint32_t level, u64* raised, u64* tmp, bool rows = true) {
     const uint32_t N = c->N, L1 = level + 1, R = L1 + c->np, beta = num_digits(c, level), al = c->alpha;
     if (small_ring_path(c, level)) return sr_modup(c, srcs, cb, level, raised);   // one launch: every output limb start to finish
     // coefficient form of all limbs, each pre-multiplied by N^-1 * (Q_j/q_i)^-1
@@ -445,7 +451,8 @@ static int32_t modup_batch(he_ctx* c, const KsSrc* srcs, uint32_t cb, uint32_t l
         u64 qi = c->mod[i];
         scale_entry(c, sc, i, i, h_mulmod(c->h_mc[i].ninv, c->h_up_invhat[(size_t)(j * al + (sz - 1)) * al + (i - lo)], qi));
     }
-    const bool cc_on = c->d_up_dig && beta <= CC_MAX_SETS && beta * R <= HE_MAX_LAUNCH_LIMBS;
+    const bool cc_on = modup_by_columns(c, level);
+    c->cnt.modup += cb;
     {
         std::vector<uint32_t> mods(cb * L1);
         std::vector<uint8_t> seg(cb * L1);
@@ -514,7 +521,9 @@ static int32_t modup_batch(he_ctx* c, const KsSrc* srcs, uint32_t cb, uint32_t l
         if (rc != HE_OK) return rc;
     }
     }
-    // NTT of every converted limb (its rows only where the columns are done); own limbs are marked "skip"
+    if (cc_on && !rows) return HE_OK;
+    // NTT of every converted limb (its rows only where the columns are done, its columns only where the rows are left); own limbs
+    // are marked "skip"
     const uint32_t per_src = beta * R;
     std::vector<uint32_t> mods(per_src);
     for (uint32_t j = 0; j < beta; j++) {
@@ -533,19 +542,21 @@ static int32_t modup_batch(he_ctx* c, const KsSrc* srcs, uint32_t cb, uint32_t l
             t.fwd = true; t.seg[0] = raised + (size_t)s0 * per_src * N; t.n_seg = 1; t.dst = raised + (size_t)s0 * per_src * N;
             t.n = ns * per_src; t.mod_idx = rep.data();
             t.lazy_out = true;      // raised digits are only ever multiplied into sums with room for values below 2q
-            t.only_pass = cc_on ? 2u : 0u;
+            t.only_pass = cc_on ? 2u : rows ? 0u : 1u;
             int32_t rc = launch_transform(c, t);
             if (rc != HE_OK) return rc;
         }
     } else {
         for (uint32_t s = 0; s < cb; s++)
             for (uint32_t o = 0; o < per_src; o += HE_MAX_LAUNCH_LIMBS) {
-                uint32_t n = std::min<uint32_t>(HE_MAX_LAUNCH_LIMBS, per_src - o);
-                int32_t rc = launch_ntt(c, raised + ((size_t)s * per_src + o) * N, mods.data() + o, n);
+                TransformDesc t = {};
+                t.fwd = true; t.seg[0] = t.dst = raised + ((size_t)s * per_src + o) * N; t.n_seg = 1;
+                t.n = std::min<uint32_t>(HE_MAX_LAUNCH_LIMBS, per_src - o); t.mod_idx = mods.data() + o;
+                t.only_pass = rows ? 0u : 1u;
+                int32_t rc = launch_transform(c, t);
                 if (rc != HE_OK) return rc;
             }
     }
-    c->cnt.modup += cb;
     return HE_OK;
 }
 
@@ -568,9 +579,10 @@ static int32_t launch_inner_product(he_ctx* c, uint32_t level, const IpBatch& ib
 
 // The ModDown of J accumulators (each [2][R][N]; from N = 2^13 they are never stored and `ip` / `ep`
 // describe how the transforms compute them): special-prime limbs -> coefficient form (pre-multiplied by
-// N^-1 * (P/p_t)^-1), conversion to q_0..q_level, forward transform with the epilogue described by `ep`.
+// N^-1 * (P/p_t)^-1), conversion to q_0..q_level, forward transform with the epilogue described by `ep`.  With `rows` its
+// launches take the place of the row passes, and ip and ep say nothing.
 static int32_t moddown_chain(he_ctx* c, uint32_t level, uint32_t J, u64* acc, u64* tmp_dn, u64* conv, const IpPrologue* ip,
-                             const ModDownEpilogue& ep) {
+                             const ModDownEpilogue& ep, KsRows* rows = nullptr) {
     const uint32_t N = c->N, L1 = level + 1, k = c->np, R = L1 + k;
     const bool cc_on = c->d_dn_dig != nullptr;
     ScaleList sc;
@@ -592,7 +604,13 @@ static int32_t moddown_chain(he_ctx* c, uint32_t level, uint32_t J, u64* acc, u6
         t.mod_idx = mods.data(); t.src_limb = lim.data(); t.scale = &sc; t.scale_period = k;
         t.ip = ip;
         t.only_pass = cc_on ? 1u : 0u;
-        int32_t rc = launch_transform(c, t);
+        int32_t rc = HE_OK;
+        if (rows) {
+            rows->mid = tmp_dn; rows->count_down = cc_on ? 1u : 0u;
+            rc = launch_ks_rows(c, *rows, true);
+            t.seg[0] = tmp_dn; t.src_limb = nullptr; t.only_pass = 2u;
+        }
+        if (rc == HE_OK && !(rows && cc_on)) rc = launch_transform(c, t);
         if (rc != HE_OK) return rc;
     }
     if (cc_on) {
@@ -624,17 +642,27 @@ static int32_t moddown_chain(he_ctx* c, uint32_t level, uint32_t J, u64* acc, u6
         t.fwd = true; t.seg[0] = conv; t.n_seg = 1; t.dst = conv; t.n = n; t.mod_idx = mods.data(); t.ep = &ep;
         t.lazy_out = true;
         t.only_pass = cc_on ? 2u : 0u;
-        int32_t rc = launch_transform(c, t);
+        int32_t rc = HE_OK;
+        if (rows) { t.ep = nullptr; t.only_pass = 1u; }
+        if (!(rows && cc_on)) rc = launch_transform(c, t);
+        if (rc == HE_OK && rows) { rows->mid = conv; rc = launch_ks_rows(c, *rows, false); }
         if (rc != HE_OK) return rc;
     }
     c->cnt.moddown += J;
     return HE_OK;
 }
 
+static void ks_rows_shape(const he_ctx* c, uint32_t level, KsRows& a) {
+    a.beta = num_digits(c, level); a.alpha = c->alpha; a.R = level + 1 + c->np; a.M = c->M; a.L1 = level + 1; a.k = c->np; a.nq = c->nq;
+    a.pinv = c->d_pinv; a.pinv_sh = c->d_pinv_sh;
+    a.count_up = modup_by_columns(c, level) ? 1u : 0u;
+}
+
 // Inner product + ModDown of up to HE_MAX_KS_JOBS jobs whose sources are already raised.
-// raised_of[i] / srcs give job i's raised digits and source; scratch: acc, tmp_dn, conv.
+// raised_of[i] / srcs give job i's raised digits and source; scratch: acc, tmp_dn, conv.  rows_left: the digits' rows are not
+// transformed yet.
 static int32_t inner_moddown_batch(he_ctx* c, uint32_t level, const KsSrc* srcs, const KsJob* jobs, const u64* const* raised_of,
-                                   uint32_t J, u64* acc, u64* tmp_dn, u64* conv) {
+                                   uint32_t J, u64* acc, u64* tmp_dn, u64* conv, bool rows_left) {
     const uint32_t N = c->N, L1 = level + 1, k = c->np, R = L1 + k, beta = num_digits(c, level);
     // group consecutive jobs that use the same key and Galois element (the caller sorts them)
     IpBatch ib;
@@ -654,6 +682,24 @@ static int32_t inner_moddown_batch(he_ctx* c, uint32_t level, const KsSrc* srcs,
     // computed by the first pass of their inverse transform, the q-limbs inside the ModDown epilogue (they would
     // only be written here and read back there).  Other rings run the stand-alone kernel.
     const bool fused = two_pass(c) && beta <= 8;
+    if (rows_left) {
+        KsRows a = {};
+        ks_rows_shape(c, level, a);
+        a.J = J; a.n_terms = 1;
+        for (uint32_t i = 0; i < J; i++) {
+            const KsSrc& src = srcs[jobs[i].src];
+            a.raised[i] = raised_of[i]; a.own[i] = src.c1; a.evk[i] = jobs[i].evk; a.g[i] = jobs[i].g;
+            a.c0[i] = src.c0;
+            a.self0[i] = jobs[i].add_self ? src.s0 : nullptr;
+            a.self1[i] = jobs[i].add_self ? src.s1 : nullptr;
+            a.out0[i] = jobs[i].out0; a.out1[i] = jobs[i].out1;
+            if (a.c0[i]) c->cnt.automorph += L1;
+        }
+        int32_t rc = moddown_chain(c, level, J, acc, tmp_dn, conv, nullptr, ModDownEpilogue{}, &a);
+        if (rc != HE_OK) return rc;
+        c->cnt.keyswitch += J;
+        return HE_OK;
+    }
     // small rings: inner product, ModDown and epilogue of every output limb in one work group, one launch
     const bool small = !fused && small_ring_path(c, level);
     IpPrologue ip = {};
@@ -711,7 +757,11 @@ int32_t ks_engine(he_ctx* c, uint32_t level, const KsSrc* srcs, uint32_t n_src, 
         size_t end = pos;
         while (end < n_jobs && jobs[order[end]].src / cb == s0 / cb) end++;
         if (end == pos) continue;                       // no job uses these sources
-        rc = modup_batch(c, srcs + s0, ns, level, raised, tmp_up);
+        // digits that one job uses are transformed where it uses them (ksrows.hip)
+        bool rows_left = two_pass(c) && beta <= 8;
+        uint32_t uses[HE_MAX_SEGS] = {0};
+        for (size_t i = pos; i < end; i++) rows_left = rows_left && ++uses[jobs[order[i]].src - s0] == 1;
+        rc = modup_batch(c, srcs + s0, ns, level, raised, tmp_up, !rows_left);
         if (rc != HE_OK) return rc;
         while (pos < end) {
             uint32_t J = (uint32_t)std::min<size_t>(jb, end - pos);
@@ -728,7 +778,7 @@ int32_t ks_engine(he_ctx* c, uint32_t level, const KsSrc* srcs, uint32_t n_src, 
                 chunk[i] = jobs[order[pos + i]];
                 raised_of[i] = raised + (size_t)(chunk[i].src - s0) * beta * R * N;
             }
-            rc = inner_moddown_batch(c, level, srcs, chunk, raised_of, J, acc, tmp_dn, conv);
+            rc = inner_moddown_batch(c, level, srcs, chunk, raised_of, J, acc, tmp_dn, conv, rows_left);
             if (rc != HE_OK) return rc;
             pos += J;
         }
@@ -830,8 +880,9 @@ int32_t ks_rotate_sum_deferred(he_ctx* c, uint32_t level, const KsSumTerm* terms
         src_of[t] = u;
     }
     const uint32_t n_src = (uint32_t)srcs.size();
+    const bool rows_left = fused && n_src == n_rot;     // digits that one term uses are transformed where it uses them (ksrows.hip)
     for (uint32_t t0 = 0; t0 < n_src; t0 += cb) {
-        int32_t rc = modup_batch(c, srcs.data() + t0, std::min(cb, n_src - t0), level, raised + (size_t)t0 * beta * R * N, tmp_up);
+        int32_t rc = modup_batch(c, srcs.data() + t0, std::min(cb, n_src - t0), level, raised + (size_t)t0 * beta * R * N, tmp_up, !rows_left);
         if (rc != HE_OK) return rc;
     }
     // the rotated c0 parts and the plain terms, summed
@@ -844,7 +895,18 @@ int32_t ks_rotate_sum_deferred(he_ctx* c, uint32_t level, const KsSumTerm* terms
     ep.fused = fused ? 1u : 0u; ep.beta = beta; ep.alpha = c->alpha; ep.M = c->M;
     ep.c0[0] = nullptr; ep.self0[0] = s0; ep.self1[0] = n_plain ? s1 : nullptr;
     ep.out0[0] = out0; ep.out1[0] = out1; ep.g[0] = 1;
-    if (fused) {
+    KsRows kr = {};
+    if (rows_left) {
+        ks_rows_shape(c, level, kr);
+        kr.J = 1; kr.sum = 1; kr.n_terms = n_rot;
+        for (uint32_t t = 0; t < n_rot; t++) {
+            kr.raised[t] = raised + (size_t)src_of[t] * beta * R * N;
+            kr.own[t] = rot[t]->c1; kr.evk[t] = rot[t]->evk; kr.g[t] = rot[t]->g;
+        }
+        kr.self0[0] = s0; kr.self1[0] = ep.self1[0];
+        kr.out0[0] = out0; kr.out1[0] = out1;
+        if (c->prof_on) c->prof_key_limbs += (uint64_t)n_rot * 2 * beta * R;
+    } else if (fused) {
         ip.beta = beta; ip.R = R; ip.M = c->M; ip.L1 = L1; ip.k = k; ip.nq = c->nq; ip.n_terms = n_rot;
         ep.n_terms = n_rot;
         for (uint32_t t = 0; t < n_rot; t++) {
@@ -871,7 +933,7 @@ int32_t ks_rotate_sum_deferred(he_ctx* c, uint32_t level, const KsSumTerm* terms
             if (c->prof_on) c->prof_key_limbs += (uint64_t)cnt * 2 * beta * R;
         }
     }
-    int32_t rc = moddown_chain(c, level, 1, acc, tmp_dn, conv, fused ? &ip : nullptr, ep);
+    int32_t rc = moddown_chain(c, level, 1, acc, tmp_dn, conv, fused ? &ip : nullptr, ep, rows_left ? &kr : nullptr);
     if (rc != HE_OK) return rc;
     c->cnt.keyswitch += n_rot;
     return HE_OK;

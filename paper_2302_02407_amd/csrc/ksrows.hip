@@ -1,0 +1,410 @@
+// The row passes of a key switch whose source serves one job (or one term of a sum of rotations), N = 2^13 .. 2^17: the
+// digits' last eight stages, the inner product and the transforms of ModDown around it, a wavefront per row.
+//
+// The Galois map takes whole rows of the 2^LC x 256 view to whole rows: k' = g*k + (g-1)/2 and the row of a position is the
+// low LC bits of k (bit-reversed order).  So row b of an inner product needs exactly one row of every digit, row sigma(b), and
+// that row can be transformed where it is used: it is read once in the state the column pass leaves it and permuted in LDS,
+// where a transform launch of its own wrote and read back 72 of some 580 limb moves of a key switch at the benchmark's top
+// level, and both components read it again.  Digits that several jobs use are transformed once instead (ntt2p.hip).
+//
+//   special primes: rows of the digits -> products with both components of the key -> inverse rows of both sums;
+//   q-limbs:        rows of the digits -> products -> rows of both converted components -> (acc - conv) * P^-1 + addends.
+//
+// What bounds it: bytes for the q-limbs (eight key switches at level 23 of N = 2^16 in 221 us, 885 MiB moved at 4.2 TB/s, vector
+// issue 0.66 of the slots), vector issue for the special primes (85 us, 0.72: their 60-bit ranges take a reduction every other stage).
+// A key switch of a batch takes 27.9 + 10.7 us in these two launches where rows of the digits, sums with inverse rows and sums
+// with the ModDown took 18 + 9 + 26.  A row is shared by a whole wavefront, 4 points a lane, because then the sums of both
+// components stay in registers (8 sums of three words) and every product is formed once from digits that both components share.
+// With two wavefronts to a row, a component each, the same batch took 24.9 ms instead of 19.4 (twice the preparation and twice
+// the misses of the key rows in the first-level cache); three wavefronts to a SIMD instead of four 20.1.
+//
+// No kernel of this file may spill registers: a build of the work-group form that did gave wrong sums wherever two work groups
+// shared a compute unit, and the same code without spills right ones.
+//
+// Work order: jobs (they come sorted by key) are the fastest index, then rows; each XCD works on every eighth (limb, row), so
+// that jobs under one key find its row and the twiddles in that XCD's L2.
+#include <algorithm>
+
+#include "modarith.h"
+#include "ntt_blocks.h"
+
+#define KR_WAVES 4
+#define KR_THREADS (KR_WAVES * 64)
+// Up to this many rows in a launch, one for each SIMD, a work group takes a row and spreads its digits over the wavefronts: the
+// launch is then as long as one row's chain of transforms.  One rotation at level 2 of N = 2^13 (32 and 96 rows): 34.7 us with a
+// wavefront to a row, 29.5 with a work group; level 5 of 2^14 39.5 and 34.8.  At 2048 one at level 5 of 2^16 (2048 and 1536
+// rows) takes 59.9 instead of 56.6, six ciphertexts by eight amounts at 2^14 352 instead of 329.
+#define KR_GROUP_ROWS 1024
+
+// A lane works on points 4T .. 4T+3 of a row (row4_last) in the last block of a transform and on points 2t, 2t+1, 128+2t, 129+2t
+// elsewhere, so that whatever it reads from memory there lies side by side.
+__device__ __forceinline__ void kr_load(u64 (&x)[4], const u64* row, uint32_t t) {
+    const ulonglong2 v = LOAD2(row + 2 * t), u = LOAD2(row + 128 + 2 * t);
+    x[0] = v.x; x[1] = v.y; x[2] = u.x; x[3] = u.y;
+}
+// LDS words of point 2t and of the values that the lane's four points take from row bs
+struct KrRow {
+    uint32_t pos, src[4], bs;
+    __device__ __forceinline__ explicit KrRow(uint32_t t) : pos(row4_word(2 * t)), src{}, bs(0) {}
+    __device__ __forceinline__ void map(uint32_t row0, uint32_t t, uint32_t g, uint32_t logN) {
+#pragma unroll
+        for (int p = 0; p < 2; p++) {
+            const uint32_t v = galois_pos(row0 + 2 * t + 128 * p, g, logN);
+            src[2 * p] = row4_word(v & 255u);
+            src[2 * p + 1] = src[2 * p] ^ 1u;            // aligned pairs come from aligned pairs
+            bs = __builtin_amdgcn_readfirstlane(v >> 8);
+        }
+    }
+    __device__ __forceinline__ void put(u64* buf, const u64 (&x)[4]) const {
+        *reinterpret_cast<ulonglong2*>(buf + pos) = make_ulonglong2(x[0], x[1]);
+        *reinterpret_cast<ulonglong2*>(buf + (pos ^ 2u) + 128) = make_ulonglong2(x[2], x[3]);
+    }
+    __device__ __forceinline__ void get(u64 (&x)[4], const u64* buf) const {
+        const ulonglong2 v = *reinterpret_cast<const ulonglong2*>(buf + pos), u = *reinterpret_cast<const ulonglong2*>(buf + (pos ^ 2u) + 128);
+        x[0] = v.x; x[1] = v.y; x[2] = u.x; x[3] = u.y;
+    }
+};
+
+// W: 0 = at most 54 bits, 1 = 55 to 57, 2 = wider: the forward ranges of ntt_blocks.h change at 57 bits, the inverse ones at 54.
+//
+// Both components of the inner products of row b of limb r for one (source, key) term, added to the sums s0 and s1; `spill`
+// empties them when they hold KS_ROW_PRODUCTS products.  Digits enter as the row transform leaves them where W = 0 (below 73q <
+// 2^60.2: 31-bit high halves, 11 products fit a sum), else below 2q (1) or canonical (2).  buf: a row for each digit, of which
+// digits j0, j0 + step .. are worked on (j0 < beta).  AHEAD: the next digit's row and the own one are asked for ahead of their turn.
+template <int W, bool SP, bool AHEAD, class Spill>
+__device__ __forceinline__ void ks_row_products(const KsRows& a, uint32_t id, uint32_t r, uint32_t b, uint32_t t, u64* buf, const ModConst& m, const Row4& at,
+                                                KrRow& kr, SplitSum (&s0)[4], SplitSum (&s1)[4], uint32_t j0, uint32_t step, Spill&& spill) {
+    const uint32_t logN = a.logN, mi = SP ? a.nq + r : r, row0 = b * 256;
+    const size_t ro = (size_t)(SP ? a.L1 + r : r) << logN, dig_stride = (size_t)a.R << logN, comp_stride = (size_t)a.M << logN;
+    const uint32_t own_j = SP ? 0xFFFFFFFFu : r / a.alpha;
+    kr.map(row0, t, a.g[id], logN);
+    const u64* row = a.raised[id] + ro + (size_t)kr.bs * 256;
+    const u64* key = a.evk[id] + ((size_t)mi << logN) + row0;
+    u64 own[4], kb[2][4], ka[2][4], w[4][6], x[1][4];
+    const bool owns = !SP && own_j % step == j0;
+    const u64* own_row = owns ? a.own[id] + ro + (size_t)kr.bs * 256 : nullptr;
+    if (AHEAD && owns) kr_load(own, own_row, t);
+    uint32_t j = j0 == own_j ? j0 + step : j0;
+    if (j < a.beta) {
+#pragma unroll
+        for (int k = 0; k < 4; k++) x[0][k] = (row + j * dig_stride)[t + 64 * k];
+        tw_row4(w, a.tw + ((size_t)mi << logN), logN - 8, kr.bs, t);
+#pragma unroll 1
+        while (true) {
+            const uint32_t jn = j + step == own_j ? j + 2 * step : j + step;
+            u64 nx[4];
+            if (AHEAD && jn < a.beta) {
+#pragma unroll
+                for (int k = 0; k < 4; k++) nx[k] = (row + jn * dig_stride)[t + 64 * k];
+            }
+            SCHED_FENCE();
+            row4_fwd<W == 2, 1>(x, w, buf + 256 * j, 256, at, m.q);
+#pragma unroll
+            for (int k = 0; k < 4; k++) {
+                if (W == 1) x[0][k] = reduce_lazy<7>(x[0][k], m.q, m.bits, m.rec);
+                if (W == 2) x[0][k] = reduce_full<7>(x[0][k], m.q, m.bits, m.rec);
+            }
+            wave_exchange();
+            at.store(3, x[0], buf + 256 * j);
+            if (jn >= a.beta) break;
+            j = jn;
+#pragma unroll
+            for (int k = 0; k < 4; k++) x[0][k] = AHEAD ? nx[k] : (row + jn * dig_stride)[t + 64 * k];
+        }
+    }
+    if (!AHEAD && owns) kr_load(own, own_row, t);
+    const size_t step_stride = 2 * step * comp_stride;
+    key += 2 * j0 * comp_stride;
+    kr_load(kb[0], key, t);
+    kr_load(ka[0], key + comp_stride, t);
+    if (owns) kr.put(buf + 256 * own_j, own);
+    wave_exchange();
+    auto digit = [&](const u64 (&b4)[4], const u64 (&a4)[4], u64 (&nb)[4], u64 (&na)[4]) {
+        key += step_stride;
+        if (j + step < a.beta) {
+            kr_load(nb, key, t);
+            kr_load(na, key + comp_stride, t);
+        }
+        u64 d[4];
+#pragma unroll
+        for (int k = 0; k < 4; k++) d[k] = buf[256 * j + kr.src[k]];
+        SCHED_FENCE();
+        spill();
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+            split_mac(s0[k], d[k], b4[k]);
+            split_mac(s1[k], d[k], a4[k]);
+        }
+        j += step;
+    };
+#pragma unroll 1
+    for (j = j0; j < a.beta;) {
+        digit(kb[0], ka[0], kb[1], ka[1]);
+        if (j < a.beta) digit(kb[1], ka[1], kb[0], ka[0]);
+    }
+    wave_exchange();
+}
+
+// What follows the sums v of components c0 .. c0+NX-1 (below 6q; special primes: below 2q): inverse rows of the special primes, or
+// rows of the converted components and the ModDown's last step.  w, cv: factors and input of the transform; buf: NX rows.
+template <int W, int NX>
+__device__ __forceinline__ void ks_row_special(const KsRows& a, uint32_t job, uint32_t c0, uint32_t r, uint32_t b, uint32_t t, u64* buf, const ModConst& m,
+                                               const Row4& at, const KrRow& kr, const u64 (&w)[4][6], u64 (&v)[NX][4]) {
+#pragma unroll
+    for (int c = 0; c < NX; c++) kr.put(buf + 256 * c, v[c]);
+    wave_exchange();
+#pragma unroll
+    for (int c = 0; c < NX; c++) at.load(3, v[c], buf + 256 * c);
+    wave_exchange();
+    row4_inv<W >= 1, NX>(v, w, buf, 256, at, m.q, m);
+    u64* out = a.mid + ((size_t)((2 * job + c0) * a.k + r) << a.logN) + b * 256;
+#pragma unroll
+    for (int c = 0; c < NX; c++)
+#pragma unroll
+        for (int k = 0; k < 4; k++) (out + ((size_t)(c * a.k) << a.logN))[t + 64 * k] = v[c][k];
+}
+template <int NX>
+__device__ __forceinline__ void ks_row_converted(u64 (&cv)[NX][4], const KsRows& a, uint32_t job, uint32_t c0, uint32_t r, uint32_t b, uint32_t t) {
+    const u64* conv = a.mid + ((size_t)((2 * job + c0) * a.L1 + r) << a.logN) + b * 256;
+#pragma unroll
+    for (int c = 0; c < NX; c++)
+#pragma unroll
+        for (int k = 0; k < 4; k++) cv[c][k] = (conv + ((size_t)(c * a.L1) << a.logN))[t + 64 * k];
+}
+// addends: the Galois image of c0 (row bs), and values that are added as they are
+template <int NX>
+struct KrAdd {
+    u64 add[NX][4], rot[4];
+    bool rotated;
+    __device__ __forceinline__ void load(const KsRows& a, uint32_t job, uint32_t c0, uint32_t r, uint32_t b, uint32_t t, uint32_t bs) {
+        const size_t qo = (size_t)r << a.logN;
+        const u64* rp = c0 == 0 ? a.c0[job] : nullptr;
+        rotated = rp != nullptr;
+        if (rotated) kr_load(rot, rp + qo + (size_t)bs * 256, t);
+#pragma unroll
+        for (int c = 0; c < NX; c++) {
+            const u64* self = c0 + c ? a.self1[job] : a.self0[job];
+#pragma unroll
+            for (int k = 0; k < 4; k++) add[c][k] = 0;
+            if (self) kr_load(add[c], self + qo + b * 256, t);
+        }
+    }
+};
+template <int W, int NX>
+__device__ __forceinline__ void ks_row_down(const KsRows& a, uint32_t job, uint32_t c0, uint32_t r, uint32_t b, uint32_t t, u64* buf, const ModConst& m,
+                                            const Row4& at, const KrRow& kr, const u64 (&w)[4][6], u64 (&cv)[NX][4], const u64 (&v)[NX][4], KrAdd<NX>& ad) {
+    const uint32_t row0 = b * 256;
+    const size_t qo = (size_t)r << a.logN;
+    SCHED_FENCE();
+    row4_fwd<W == 2, NX>(cv, w, buf, 256, at, m.q);
+    // out = (acc - conv) * P^-1 + addends: the product is below 4q whatever its factor, so the transform value may stay as it is
+    // where 128q plus the accumulator fits 64 bits, else below 2q; the sum is below 6q
+    const bool raw = W < 2 && m.bits <= 55;
+    const u64 bias = raw ? (m.q << 7) : 2 * m.q, pinv = ((const_u64)(uintptr_t)a.pinv)[r], pinv_sh = ((const_u64)(uintptr_t)a.pinv_sh)[r];
+    wave_exchange();
+#pragma unroll
+    for (int c = 0; c < NX; c++) {
+        if (!raw) {
+#pragma unroll
+            for (int k = 0; k < 4; k++) cv[c][k] = reduce_lazy<7>(cv[c][k], m.q, m.bits, m.rec);
+        }
+        at.store(3, cv[c], buf + 256 * c);
+    }
+    wave_exchange();
+#pragma unroll
+    for (int c = 0; c < NX; c++) kr.get(cv[c], buf + 256 * c);
+    if (ad.rotated) {
+        wave_exchange();
+        kr.put(buf, ad.rot);
+        wave_exchange();
+#pragma unroll
+        for (int k = 0; k < 4; k++) ad.add[0][k] += buf[kr.src[k]];
+    }
+#pragma unroll
+    for (int c = 0; c < NX; c++) {
+        u64* out = (c0 + c ? a.out1[job] : a.out0[job]) + qo + row0 + 2 * t;
+        u64 o[4];
+#pragma unroll
+        for (int k = 0; k < 4; k++)
+            o[k] = reduce_full<7>(shoup_acc(ad.add[c][k], v[c][k] + bias - cv[c][k], pinv, pinv_sh, m.q), m.q, m.bits, m.rec);
+        STORE2(out) = make_ulonglong2(o[0], o[1]);
+        STORE2(out + 128) = make_ulonglong2(o[2], o[3]);
+    }
+}
+// v = (v + sums) below 2q, the sums empty again
+__device__ __forceinline__ void kr_flush(u64 (&v)[2][4], SplitSum (&s0)[4], SplitSum (&s1)[4], const ModConst& m) {
+#pragma unroll
+    for (int c = 0; c < 2; c++) {
+        u64 p[4];
+        split_reduce(p, c ? s1 : s0, m);
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+            v[c][k] = reduce_lazy<7>(v[c][k] + p[k], m.q, m.bits, m.rec);
+            (c ? s1 : s0)[k] = SplitSum{0, 0, 0};
+        }
+        SCHED_FENCE();
+    }
+}
+
+// One wavefront: row b of limb r for one job.  MANY: more than KS_ROW_PRODUCTS digits.
+template <int W, bool SP, bool MANY>
+__device__ __forceinline__ void ks_row(const KsRows& a, uint32_t job, uint32_t r, uint32_t b, uint32_t t, u64* buf) {
+    const uint32_t mi = SP ? a.nq + r : r, lc = a.logN - 8;
+    const ModConst m = mod_const(a.mc, mi);
+    const Row4 at(t);
+    KrRow kr(t);
+    u64 w[4][6], v[2][4] = {}, cv[2][4];
+    SplitSum s0[4] = {}, s1[4] = {};
+    uint32_t pending = 0;
+    ks_row_products<W, SP, true>(a, job, r, b, t, buf, m, at, kr, s0, s1, 0, 1, [&]() {
+        if (MANY && pending == KS_ROW_PRODUCTS) { kr_flush(v, s0, s1, m); pending = 0; }
+        pending++;
+    });
+    SCHED_FENCE();
+    if (MANY) kr_flush(v, s0, s1, m);
+    else split_reduce(v[0], s0, m);
+    SCHED_FENCE();
+    asm("" : "+v"(t));                                   // what follows from the lane is worked out anew, not kept in registers
+    if (!SP) ks_row_converted(cv, a, job, 0, r, b, t);
+    tw_row4(w, (SP ? a.itw : a.tw) + ((size_t)mi << a.logN), lc, b, t);
+    SCHED_FENCE();
+    if (!MANY) split_reduce(v[1], s1, m);
+    SCHED_FENCE();
+    if (SP) {
+        if (!MANY) {
+#pragma unroll
+            for (int i = 0; i < 8; i++) v[i / 4][i % 4] = reduce_lazy<7>(v[i / 4][i % 4], m.q, m.bits, m.rec);
+        }
+        ks_row_special<W, 2>(a, job, 0, r, b, t, buf, m, Row4(t), kr, w, v);
+    } else {
+        KrAdd<2> ad;
+        ad.load(a, job, 0, r, b, t, kr.bs);
+        ks_row_down<W, 2>(a, job, 0, r, b, t, buf, m, Row4(t), kr, w, cv, v, ad);
+    }
+}
+// A work group of nw wavefronts: row b of limb r, the terms (sum) or the digits spread over the wavefronts; the first two then take
+// a component each.  buf: LDS of the work group, max(beta, 2) rows a wavefront.
+template <int W, bool SP, bool SUM>
+__device__ __forceinline__ void ks_row_group(const KsRows& a, uint32_t job, uint32_t r, uint32_t b, uint32_t wave, uint32_t nw, uint32_t t, u64* buf) {
+    const uint32_t mi = SP ? a.nq + r : r, lc = a.logN - 8;
+    const ModConst m = mod_const(a.mc, mi);
+    KrRow kr(t);
+    const uint32_t per_wave = 256 * max(a.beta, 2u);
+    u64* part = buf + per_wave * wave;                   // the wavefront's digits, then its two sums
+    u64 v[2][4] = {};
+    SplitSum s0[4] = {}, s1[4] = {};
+    uint32_t pending = 0;
+    if (SUM) {
+#pragma unroll 1
+        for (uint32_t i = wave; i < a.n_terms; i += nw) {
+            asm("" : "+v"(t));                           // what follows from the lane is worked out anew, not kept in registers
+            ks_row_products<W, SP, false>(a, i, r, b, t, part, m, Row4(t), kr, s0, s1, 0, 1, [&]() {
+                if (pending == KS_ROW_PRODUCTS) { kr_flush(v, s0, s1, m); pending = 0; }
+                pending++;
+            });
+        }
+    } else if (wave < a.beta) {
+        ks_row_products<W, SP, false>(a, job, r, b, t, part, m, Row4(t), kr, s0, s1, wave, nw, []() {});
+    }
+    SCHED_FENCE();
+    kr_flush(v, s0, s1, m);
+#pragma unroll
+    for (int c = 0; c < 2; c++) kr.put(part + 256 * c, v[c]);
+    SCHED_FENCE();
+    asm("" : "+v"(t));
+    u64 w[4][6], cv[1][4], sum[1][4] = {};
+    KrAdd<1> ad;
+    if (wave < 2) {
+        if (!SUM) kr.map(b * 256, t, a.g[job], a.logN);
+        if (!SP) {
+            ks_row_converted(cv, a, job, wave, r, b, t);
+            ad.load(a, job, wave, r, b, t, kr.bs);
+        }
+        tw_row4(w, (SP ? a.itw : a.tw) + ((size_t)mi << a.logN), lc, b, t);
+    }
+    __syncthreads();
+    if (wave >= 2) return;
+#pragma unroll 1
+    for (uint32_t i = 0; i < nw; i++) {
+        u64 o[4];
+        kr.get(o, buf + per_wave * i + 256 * wave);
+#pragma unroll
+        for (int k = 0; k < 4; k++) sum[0][k] += o[k];
+    }
+#pragma unroll
+    for (int k = 0; k < 4; k++) sum[0][k] = reduce_lazy<7>(sum[0][k], m.q, m.bits, m.rec);
+    u64* mine = buf + 256 * wave;                        // a sum that only this wavefront has read
+    wave_exchange();
+    if (SP) ks_row_special<W, 1>(a, job, wave, r, b, t, mine, m, Row4(t), kr, w, sum);
+    else ks_row_down<W, 1>(a, job, wave, r, b, t, mine, m, Row4(t), kr, w, cv, sum, ad);
+}
+
+template <int W>
+__device__ __forceinline__ uint32_t kr_pin(uint32_t v) {     // keeps the widths' loads apart (see ntt2p.hip)
+    if (W == 0) asm("; 54 bits" : "+s"(v));
+    else if (W == 1) asm("; 57 bits" : "+s"(v));
+    else asm("; wide" : "+s"(v));
+    return v;
+}
+
+// A wavefront per (limb, row, job), jobs fastest; each XCD works on every eighth (limb, row).
+template <bool SP, bool MANY>
+__global__ __launch_bounds__(KR_THREADS, MANY ? 3 : 4) void ks_rows_kernel(KsRows a) {
+    extern __shared__ __attribute__((aligned(16))) u64 sm[];
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), rows = a.logN - 8;
+    const uint32_t item = (blockIdx.x >> 3) * KR_WAVES + wave, un = item / a.J, job = item - un * a.J;
+    const uint32_t u = un * 8 + (blockIdx.x & 7u), r = u >> rows, b = u & ((1u << rows) - 1u);
+    if (r >= (SP ? a.k : a.L1)) return;
+    u64* buf = sm + wave * (256 * max(a.beta, 2u));
+    const uint32_t bits = mod_const(a.mc, SP ? a.nq + r : r).bits, t = threadIdx.x & 63u;
+    if (bits <= 54) ks_row<0, SP, MANY>(a, job, kr_pin<0>(r), b, t, buf);
+    else if (bits <= 57) ks_row<1, SP, MANY>(a, job, kr_pin<1>(r), b, t, buf);
+    else ks_row<2, SP, MANY>(a, job, kr_pin<2>(r), b, t, buf);
+}
+// A work group per (limb, row) of a sum, or per (limb, row, job).
+template <bool SP, bool SUM>
+__global__ __launch_bounds__(KR_THREADS, 3) void ks_rows_group_kernel(KsRows a) {
+    extern __shared__ __attribute__((aligned(16))) u64 sm[];
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = blockDim.x >> 6, rows = a.logN - 8, t = threadIdx.x & 63u;
+    const uint32_t item = blockIdx.x >> 3, un = item / a.J, job = item - un * a.J;
+    const uint32_t u = un * 8 + (blockIdx.x & 7u), r = u >> rows, b = u & ((1u << rows) - 1u);
+    const uint32_t bits = mod_const(a.mc, SP ? a.nq + r : r).bits;
+    if (bits <= 54) ks_row_group<0, SP, SUM>(a, job, kr_pin<0>(r), b, wave, nw, t, sm);
+    else if (bits <= 57) ks_row_group<1, SP, SUM>(a, job, kr_pin<1>(r), b, wave, nw, t, sm);
+    else ks_row_group<2, SP, SUM>(a, job, kr_pin<2>(r), b, wave, nw, t, sm);
+}
+
+int32_t launch_ks_rows(he_ctx* ctx, KsRows& a, bool special) {
+    const uint32_t limbs = special ? a.k : a.L1, units = limbs << (ctx->logN - 8);
+    if (a.J == 0 || a.J > HE_MAX_KS_JOBS || a.n_terms == 0 || a.n_terms > HE_MAX_KS_JOBS || (a.sum && a.J != 1) || (!a.sum && a.n_terms != 1) ||
+        a.beta == 0 || a.beta > 8 || ctx->logN < 13 || ctx->logN > 17 || limbs == 0 || limbs > HE_MAX_MODULI)
+        return he_fail(ctx, HE_ERR_BADARG, "key-switch rows: bad shape");
+    a.mc = ctx->d_mc; a.tw = ctx->d_tw; a.itw = ctx->d_itw; a.logN = ctx->logN;
+    hipEvent_t e0 = nullptr, e1 = nullptr;
+    if (ctx->prof_on) {
+        HE_HIP(ctx, hipEventCreate(&e0));
+        HE_HIP(ctx, hipEventCreate(&e1));
+        HE_HIP(ctx, hipEventRecord(e0, ctx->stream));
+    }
+    const bool group = a.sum || units * a.J <= KR_GROUP_ROWS;
+    const uint32_t nw = group ? std::max(2u, std::min<uint32_t>(KR_WAVES, a.sum ? a.n_terms : a.beta)) : KR_WAVES;
+    const dim3 grid(group ? units * a.J : 8 * ((units / 8 * a.J + KR_WAVES - 1) / KR_WAVES)), block(64 * nw);
+    const size_t lds = (size_t)nw * 256 * std::max(a.beta, 2u) * sizeof(u64);       // at most 64 KiB
+    const bool many = a.beta > KS_ROW_PRODUCTS;
+#define KR_LAUNCH(K) hipLaunchKernelGGL(K, grid, block, lds, ctx->stream, a)
+    if (a.sum) { if (special) KR_LAUNCH((ks_rows_group_kernel<true, true>)); else KR_LAUNCH((ks_rows_group_kernel<false, true>)); }
+    else if (group) { if (special) KR_LAUNCH((ks_rows_group_kernel<true, false>)); else KR_LAUNCH((ks_rows_group_kernel<false, false>)); }
+    else if (many) { if (special) KR_LAUNCH((ks_rows_kernel<true, true>)); else KR_LAUNCH((ks_rows_kernel<false, true>)); }
+    else { if (special) KR_LAUNCH((ks_rows_kernel<true, false>)); else KR_LAUNCH((ks_rows_kernel<false, false>)); }
+#undef KR_LAUNCH
+    HE_HIP(ctx, hipGetLastError());
+    const uint32_t digits = (a.sum ? a.n_terms : a.J) * (special ? a.beta * a.k : (a.beta - 1) * a.L1), sums = 2 * a.J * limbs;
+    if (ctx->prof_on) {
+        HE_HIP(ctx, hipEventRecord(e1, ctx->stream));
+        ctx->prof_events.push_back({e0, e1, digits + sums, 0u, special ? 4u : 2u});
+    }
+    // transforms whose column pass was a launch of its own are counted there
+    if (a.count_up) ctx->cnt.ntt_limbs += digits;
+    if (a.count_down) (special ? ctx->cnt.intt_limbs : ctx->cnt.ntt_limbs) += sums;
+    return HE_OK;
+}

@@ -24,7 +24,6 @@
 #include "ntt_blocks.h"
 
 #define P2_THREADS 256
-#define SCHED_FENCE() __builtin_amdgcn_sched_barrier(0)   // loads above it are issued before the arithmetic below it
 
 // Limbs of a launch, sorted by modulus: destination limb (bits 0-8), modulus (9-14), source segment (27-30) and limb in it
 // (15-26), wide modulus (31).  One 32-bit word per limb, so that a work group gets all of it in one scalar load, and
@@ -72,12 +71,6 @@ __device__ __forceinline__ uint32_t row_decode(const LimbTab& tab, const P2Args&
     const uint32_t pchunk = L >> (lt + lc), rem = L & ((1u << (lt + lc)) - 1u);
     tile = rem >> lc;
     return __builtin_amdgcn_readfirstlane(tab.e[(pchunk << lc) + (rem & ((1u << lc) - 1u))]);
-}
-
-__device__ __forceinline__ uint32_t galois_pos(uint32_t j, uint32_t g, uint32_t logN) {
-    const uint32_t k = __brev(j) >> (32 - logN);
-    const uint32_t kp = (g * k + ((g - 1) >> 1)) & ((1u << logN) - 1u);
-    return __brev(kp) >> (32 - logN);
 }
 
 // ---------------------------------------------------------------- column passes
@@ -226,7 +219,7 @@ __device__ __forceinline__ void col_inv(const P2Args& a, uint32_t e, uint32_t ti
 }
 
 template <int LC, bool CUSTOM_SCALE>
-__global__ __launch_bounds__(P2_THREADS, 4) void ntt_col_inv_kernel(P2Args a, LimbTab tab, ScaleList sc, uint32_t scale_period) {
+__global__ __launch_bounds__(P2_THREADS, LC == 9 ? 3 : 4) void ntt_col_inv_kernel(P2Args a, LimbTab tab, ScaleList sc, uint32_t scale_period) {
     using G = Col<LC>;
     __shared__ u64 sm[G::LDS];
     const uint32_t tile = blockIdx.x & (G::T - 1), e = __builtin_amdgcn_readfirstlane(tab.e[blockIdx.x >> G::LT]);
@@ -300,7 +293,7 @@ __device__ __forceinline__ ulonglong2 ip_order(u64 v0, u64 v1, uint32_t swp) {
 
 // The inner product of a row for one job: chunks of 4 points per thread, the next chunk's operands requested before this
 // chunk's products.  BETA = 1, 2, 3: exactly that many digits; 0: any number up to 8, three at a time.  emit(chunk, pos, sums
-// below 5q in slot order, swaps).
+// below 6q in slot order, swaps).
 template <int DP, int BETA, class Emit>
 __device__ __forceinline__ void ip_row(const IpTerm& tm, uint32_t beta, uint32_t row0, uint32_t t, uint32_t logN, size_t dig_stride,
                                        size_t key_stride, const ModConst& m, Emit&& emit) {
@@ -322,8 +315,7 @@ __device__ __forceinline__ void ip_row(const IpTerm& tm, uint32_t beta, uint32_t
             SplitSum s[4] = {};
             ip_consume(s, cur, NJ);
             u64 v[4];
-#pragma unroll
-            for (int i = 0; i < 4; i++) v[i] = split_reduce(s[i], m);
+            split_reduce(v, s, m);
             emit(ch, pos, v, src, swp);
             if (ch + 1 < NCH) {
                 cur = nxt;
@@ -343,13 +335,16 @@ __device__ __forceinline__ void ip_row(const IpTerm& tm, uint32_t beta, uint32_t
                 const uint32_t nj = beta - j0 < NJ ? beta - j0 : NJ;
                 ip_request<DP>(L, tm, j0, nj, pos, src, swp, dig_stride, key_stride);
                 if (j0 == 6) {                           // seven products at most in one sum
+                    split_reduce(v, s, m);
 #pragma unroll
-                    for (int i = 0; i < 4; i++) { v[i] = split_reduce(s[i], m); s[i] = SplitSum{0, 0, 0}; }
+                    for (int i = 0; i < 4; i++) s[i] = SplitSum{0, 0, 0};
                 }
                 ip_consume(s, L, nj);
             }
+            u64 last[4];
+            split_reduce(last, s, m);
 #pragma unroll
-            for (int i = 0; i < 4; i++) v[i] = beta > 6 ? reduce_lazy<7>(v[i] + split_reduce(s[i], m), m.q, m.bits, m.rec) : split_reduce(s[i], m);
+            for (int i = 0; i < 4; i++) v[i] = beta > 6 ? reduce_lazy<7>(v[i] + last[i], m.q, m.bits, m.rec) : last[i];
             emit(ch, pos, v, src, swp);
         }
     }
@@ -369,9 +364,11 @@ __device__ __forceinline__ void ip_row_terms(Term&& term, uint32_t n_terms, uint
             ip_map<DP>(src, swp, pos, tm.g, logN);
             SplitSum s[4] = {};
             auto flush = [&]() {
+                u64 sv[4];
+                split_reduce(sv, s, m);
 #pragma unroll
                 for (int p = 0; p < 2; p++) {
-                    const ulonglong2 v = ip_order(split_reduce(s[2 * p], m), split_reduce(s[2 * p + 1], m), swp[p]);
+                    const ulonglong2 v = ip_order(sv[2 * p], sv[2 * p + 1], swp[p]);
                     tot[2 * p] = reduce_lazy<7>(tot[2 * p] + v.x, m.q, m.bits, m.rec);
                     tot[2 * p + 1] = reduce_lazy<7>(tot[2 * p + 1] + v.y, m.q, m.bits, m.rec);
                     s[2 * p] = s[2 * p + 1] = SplitSum{0, 0, 0};
@@ -393,22 +390,6 @@ __device__ __forceinline__ void ip_row_terms(Term&& term, uint32_t n_terms, uint
     }
 }
 
-// ---------------------------------------------------------------- rows with 4 points per thread
-// Factors of the four two-stage blocks of row b for thread t of 64, and the LDS word of point k before and after block i.
-__device__ __forceinline__ void tw_row4(u64 (&w)[4][6], const ulonglong2* __restrict__ tw, uint32_t lc, uint32_t b, uint32_t t) {
-    tw_block2(w[0], tw, lc, b);
-    tw_block2(w[1], tw, lc + 2, 4 * b + (t >> 4));
-    const uint32_t G = 16 * b + (t >> 2), g = t & 3u, NG = 1u << (lc + 4);      // the last four stages' order: tw_pos
-    const ulonglong2* p = tw + NG + G;
-    const ulonglong2 v[6] = {p[0], p[NG], p[2 * NG], p[(3 + g) * NG], p[(7 + 2 * g) * NG], p[(8 + 2 * g) * NG]};
-#pragma unroll
-    for (int i = 0; i < 6; i++) { w[2 + i / 3][2 * (i % 3)] = v[i].x; w[2 + i / 3][2 * (i % 3) + 1] = v[i].y; }
-}
-__device__ __forceinline__ uint32_t row4_at(int i, uint32_t t, int k) {
-    const uint32_t ls = 6 - 2 * i, e = ((t >> ls) << (ls + 2)) + (t & ((1u << ls) - 1u)) + ((uint32_t)k << ls);
-    return e + (e >> 4);
-}
-
 // ---------------------------------------------------------------- forward row pass
 // Pass B: workgroup = 16 consecutive rows (256-point blocks); tid = blk*16 + t.  A row stays inside 16 lanes of one wavefront,
 // so its exchanges need no barrier and the wavefronts run apart.
@@ -427,7 +408,6 @@ __device__ __forceinline__ void row_fwd(const P2Args& a, uint32_t e, uint32_t ti
     u64* s = sm + blk * 272;
     const ModConst m = a.mc[mi];
     const u64 q = uni64(m.q);
-    // the transform: x[j] = point PTS*t + j of the row
     constexpr int PTS = 256 / LANES;
     u64 x[PTS];
     if constexpr (LANES == 16) {
@@ -455,19 +435,7 @@ __device__ __forceinline__ void row_fwd(const P2Args& a, uint32_t e, uint32_t ti
 #pragma unroll
         for (int k = 0; k < 4; k++) x[k] = row[t + 64 * k];
         tw_row4(w, tw, lc, b, t);
-#pragma unroll
-        for (int i = 0; i < 4; i++) {
-            if (i) {
-                wave_exchange();
-#pragma unroll
-                for (int k = 0; k < 4; k++) x[k] = s[row4_at(i, t, k)];
-            }
-            fwd_block2_r<WIDE>(x, w[i], q, 4 * q);
-            if (i < 3) {
-#pragma unroll
-                for (int k = 0; k < 4; k++) s[row4_at(i, t, k)] = x[k];
-            }
-        }
+        row4_fwd<WIDE, 1>(reinterpret_cast<u64 (&)[1][4]>(x), w, s, 272, Row4(t), q);
     }
     if (EPI == 0) {
         if (!WIDE && a.lazy) {
@@ -485,8 +453,13 @@ __device__ __forceinline__ void row_fwd(const P2Args& a, uint32_t e, uint32_t ti
 #pragma unroll
             for (int k = 0; k < 16; k++) row[t + 16 * k] = s[t + 17 * k];
         } else {
-#pragma unroll
-            for (int j = 0; j < 4; j += 2) STORE2(row + 4 * t + j) = make_ulonglong2(x[j], x[j + 1]);
+            const Row4 at(t);
+            wave_exchange();
+            at.store(3, x, s);
+            wave_exchange();
+            const ulonglong2 v = *reinterpret_cast<const ulonglong2*>(s + row4_word(2 * t)), u = *reinterpret_cast<const ulonglong2*>(s + row4_word(128 + 2 * t));
+            STORE2(row + 2 * t) = v;
+            STORE2(row + 128 + 2 * t) = u;
         }
         return;
     }
@@ -498,8 +471,9 @@ __device__ __forceinline__ void row_fwd(const P2Args& a, uint32_t e, uint32_t ti
         for (int j = 0; j < PTS; j++) x[j] = reduce_lazy<7>(x[j], q, m.bits, m.rec);
     }
     wave_exchange();
+    const uint32_t e0 = LANES == 16 ? 16 * t : 4 * row4_last(t);       // x[j] = point e0 + j of the row
 #pragma unroll
-    for (int j = 0; j < PTS; j++) s[PTS * t + j + ((PTS * t + j) >> 4)] = x[j];
+    for (int j = 0; j < PTS; j++) s[e0 + j + ((e0 + j) >> 4)] = x[j];
     const u64 bias = raw ? (q << 7) : 2 * q;
     const uint32_t pc = limb / ep.L1, r = limb - pc * ep.L1, job = pc >> 1, comp = pc & 1u, row0 = b * 256;
     const u64 pinv = ep.pinv[r], pinv_sh = ep.pinv_sh[r];
@@ -511,7 +485,7 @@ __device__ __forceinline__ void row_fwd(const P2Args& a, uint32_t e, uint32_t ti
     const u64* c0 = has_c0 ? c0p + ro : nullptr;
     const u64* self = has_self ? sp + ro : nullptr;
     wave_exchange();
-    // v: accumulator values in slot order, below 5q
+    // v: accumulator values in slot order, below 6q
     auto emit = [&](int ch, uint32_t pos, const u64 (&v)[4], const uint32_t (&src)[2], const uint32_t (&swp)[2]) {
         ulonglong2 cv[2], sv[2];
 #pragma unroll
@@ -564,8 +538,8 @@ __device__ __forceinline__ void row_fwd(const P2Args& a, uint32_t e, uint32_t ti
 }
 
 template <int EPI, int BETA, int LANES>
-__global__ __launch_bounds__(P2_THREADS, LANES == 16 && EPI >= 2 ? 3 : 4) void ntt_row_fwd_kernel(P2Args a, LimbTab tab, ModDownEpilogue ep) {
-    __shared__ u64 sm[P2_THREADS / LANES * 272];         // 16 groups of 17: conflict-free both ways
+__global__ __launch_bounds__(P2_THREADS, EPI == 3 || (LANES == 16 && EPI >= 2) ? 3 : 4) void ntt_row_fwd_kernel(P2Args a, LimbTab tab, ModDownEpilogue ep) {
+    __shared__ alignas(16) u64 sm[P2_THREADS / LANES * 272];         // 16 groups of 17: conflict-free both ways
     uint32_t tile;
     const uint32_t e = row_decode<LANES>(tab, a, tile);
     if (e == TAB_NONE) return;
@@ -604,12 +578,12 @@ __device__ __forceinline__ void row_inv(const P2Args& a, const LimbTab& tab, uin
 #pragma unroll
             for (int k = 0; k < 16; k++) s[t + 17 * k] = x[k];
         } else {
-#pragma unroll
-            for (int j = 0; j < 4; j += 2) {
-                const ulonglong2 v = LOAD2(in + 4 * t + j);
-                x[j] = v.x; x[j + 1] = v.y;
-            }
+            const ulonglong2 v = LOAD2(in + 2 * t), u = LOAD2(in + 128 + 2 * t);
             factors();
+            *reinterpret_cast<ulonglong2*>(s + row4_word(2 * t)) = v;
+            *reinterpret_cast<ulonglong2*>(s + row4_word(128 + 2 * t)) = u;
+            wave_exchange();
+            Row4(t).load(3, x, s);
         }
     } else {
         const uint32_t pc = limb / ip.k, tp = limb - pc * ip.k, job = pc >> 1, comp = pc & 1u, row0 = b * 256;
@@ -666,19 +640,13 @@ __device__ __forceinline__ void row_inv(const P2Args& a, const LimbTab& tab, uin
 #pragma unroll
         for (int k = 0; k < 16; k++) out[t + 16 * k] = x[k];
     } else {
+        if (IP) {
+            wave_exchange();
 #pragma unroll
-        for (int i = 3; i >= 0; i--) {
-            if (i < 3 || IP) {
-                wave_exchange();
-#pragma unroll
-                for (int k = 0; k < 4; k++) x[k] = s[row4_at(i, t, k)];
-            }
-            inv_block2_r(x, w4[i], q);
-            if (i) {
-#pragma unroll
-                for (int k = 0; k < 4; k++) s[row4_at(i, t, k)] = x[k];
-            }
+            for (int k = 0; k < 4; k++) x[k] = s[4 * row4_last(t) + k + (row4_last(t) >> 2)];
+            wave_exchange();
         }
+        row4_inv<WIDE, 1>(reinterpret_cast<u64 (&)[1][4]>(x), w4, s, 272, Row4(t), q, m);
 #pragma unroll
         for (int k = 0; k < 4; k++) out[t + 64 * k] = x[k];
     }
@@ -686,7 +654,7 @@ __device__ __forceinline__ void row_inv(const P2Args& a, const LimbTab& tab, uin
 
 template <int IP, int BETA, int LANES>
 __global__ __launch_bounds__(P2_THREADS, LANES == 16 && IP ? 3 : 4) void ntt_row_inv_kernel(P2Args a, LimbTab tab, IpPrologue ip) {
-    __shared__ u64 sm[P2_THREADS / LANES * 272];
+    __shared__ alignas(16) u64 sm[P2_THREADS / LANES * 272];
     uint32_t tile;
     const uint32_t e = row_decode<LANES>(tab, a, tile);
     if (e == TAB_NONE) return;
@@ -711,8 +679,7 @@ __device__ __forceinline__ auto run_pick(const LimbTab& tab, uint32_t first, uin
     const auto v2 = f(tab.e[first + min(4 * it + 2, n - 1)]), v3 = f(tab.e[first + min(4 * it + 3, n - 1)]);
     return quarter & 2 ? (quarter & 1 ? v3 : v2) : (quarter & 1 ? v1 : v0);
 }
-// the first block's factors into scalar registers: through a pointer to constant memory, which no store can change
-typedef const __attribute__((address_space(4))) u64* const_u64;
+// the first block's factors into scalar registers
 __device__ __forceinline__ void run_tw1(ulonglong2 (&w)[15], const ulonglong2* tw, uint32_t s0, uint32_t b) {
 #pragma unroll
     for (int u = 0; u < 4; u++)

@@ -4,6 +4,8 @@
 #pragma once
 #include "modarith.h"
 
+#define SCHED_FENCE() __builtin_amdgcn_sched_barrier(0)   // loads above it are issued before the arithmetic below it
+
 // q4 = 4q throughout this file.
 //
 // A butterfly is counted in instructions: on gfx950 the 32-bit multiplies, v_mad_u64_u32 and v_lshl_add_u64 all issue at
@@ -136,6 +138,14 @@ __device__ __forceinline__ void inv_block2_r(u64 (&x)[4], const u64 (&r)[6], u64
     gs_bfly<true>(x[1], x[3], b[1], b[3], r[0], r[1], q);
     settle4(x, b, q);
 }
+// The same for moduli of at most 54 bits, without a reduction: inputs below bound*q, results below 4*bound*q (bound at least 2).
+__device__ __forceinline__ void inv_block2_n(u64 (&x)[4], const u64 (&r)[6], u64 q, int bound) {
+    int b[4] = {bound, bound, bound, bound};
+    gs_bfly<false>(x[0], x[1], b[0], b[1], r[2], r[3], q);
+    gs_bfly<false>(x[2], x[3], b[2], b[3], r[4], r[5], q);
+    gs_bfly<false>(x[0], x[2], b[0], b[2], r[0], r[1], q);
+    gs_bfly<false>(x[1], x[3], b[1], b[3], r[0], r[1], q);
+}
 // the three twiddles of such a block (and Shoup companions): r = {w0, w0', w1, w1', w2, w2'}
 __device__ __forceinline__ void tw_block2(u64 (&r)[6], const ulonglong2* tw, uint32_t s0, uint32_t G) {
     const uint32_t b0 = (1u << s0) + G, b1 = (2u << s0) + 2 * G;
@@ -159,4 +169,120 @@ __device__ __forceinline__ void wave_exchange() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Position in bit-reversed order that the Galois map X -> X^g takes the value of position j from.
+__device__ __forceinline__ uint32_t galois_pos(uint32_t j, uint32_t g, uint32_t logN) {
+    const uint32_t k = __brev(j) >> (32 - logN);
+    const uint32_t kp = (g * k + ((g - 1) >> 1)) & ((1u << logN) - 1u);
+    return __brev(kp) >> (32 - logN);
+}
+
+// ---------------------------------------------------------------- rows with 4 points per thread
+// a pointer to constant memory, which no store can change: loads through it stay scalar after stores
+typedef const __attribute__((address_space(4))) u64* const_u64;
+// what the row kernels need of a modulus, in scalar registers
+__device__ __forceinline__ ModConst mod_const(const ModConst* mc, uint32_t mi) {
+    const const_u64 p = (const_u64)(uintptr_t)uni64((u64)(mc + mi));
+    ModConst m = {};
+    m.q = p[offsetof(ModConst, q) / 8];
+    m.mu = p[offsetof(ModConst, mu) / 8];
+    const u64 v = p[offsetof(ModConst, bits) / 8];
+    m.bits = (uint32_t)v; m.rec = (uint32_t)(v >> 32);
+    return m;
+}
+// In the last block (four neighbours a lane) lane t takes points 4T .. 4T+3, T = row4_last(t): 16 lanes then read factors that lie
+// side by side (tw_pos), where T = t made every quad of lanes read from four places.
+__device__ __forceinline__ uint32_t row4_last(uint32_t t) { return ((t & 15u) << 2) | (t >> 4); }
+// Factors of the four two-stage blocks of row b for thread t of 64 (b the same for the whole wavefront).
+__device__ __forceinline__ void tw_row4(u64 (&w)[4][6], const ulonglong2* __restrict__ tw, uint32_t lc, uint32_t b, uint32_t t) {
+    const uint32_t bu = __builtin_amdgcn_readfirstlane(b);
+    const const_u64 f0 = (const_u64)(uintptr_t)uni64((u64)(tw + ((1u << lc) + bu))), f1 = (const_u64)(uintptr_t)uni64((u64)(tw + ((2u << lc) + 2 * bu)));
+    w[0][0] = f0[0]; w[0][1] = f0[1];                    // the same for the whole row (scalar registers)
+#pragma unroll
+    for (int i = 0; i < 4; i++) w[0][2 + i] = f1[i];
+    tw_block2(w[1], tw, lc + 2, 4 * b + (t >> 4));
+    const uint32_t NG = 1u << (lc + 4), T = row4_last(t), g = T & 3u;           // the last four stages' order: tw_pos
+    const ulonglong2 *p = tw + NG + 16 * b + (t >> 2), *l = tw + NG + 16 * b + (T >> 2);
+    const ulonglong2 v[6] = {p[0], p[NG], p[2 * NG], l[(3 + g) * NG], l[(7 + 2 * g) * NG], l[(8 + 2 * g) * NG]};
+#pragma unroll
+    for (int i = 0; i < 6; i++) { w[2 + i / 3][2 * (i % 3)] = v[i].x; w[2 + i / 3][2 * (i % 3) + 1] = v[i].y; }
+}
+// LDS words of a row of 256 points shared by 64 threads (256 words): point e lies at e ^ 6*e5 ^ 24*e6 ^ 2*e7 (e5, e6, e7: its bits),
+// so that every access below, 8 bytes a lane in the first three blocks and 16 in the others, falls on 64 different banks per
+// half or quarter wavefront.  Pairs of points stay pairs, in order.
+__device__ __forceinline__ uint32_t row4_word(uint32_t e) { return e ^ ((e >> 5 & 1u) * 6u) ^ ((e >> 6 & 1u) * 24u) ^ ((e >> 6 & 2u)); }
+struct Row4 {
+    uint32_t b0, b1, b2, b3;                             // words of thread t's first point in blocks 0 .. 3
+    __device__ __forceinline__ explicit Row4(uint32_t t)
+        : b0(row4_word(t)), b1(row4_word((t >> 4 << 6) | (t & 15u))), b2(row4_word((t >> 2 << 4) | (t & 3u))), b3(row4_word(4 * row4_last(t))) {}
+    __device__ __forceinline__ uint32_t at(int i, int k) const {     // i < 3
+        if (i == 0) return (b0 ^ ((k & 1 ? 24u : 0u) ^ (k & 2 ? 2u : 0u))) + 64u * k;
+        if (i == 1) return (b1 ^ ((k & 1 ? 16u : 0u) ^ (k & 2 ? 6u : 0u))) + (k & 2 ? 32u : 0u);
+        return b2 ^ (4u * k);
+    }
+    __device__ __forceinline__ void load(int i, u64 (&x)[4], const u64* s) const {
+        if (i < 3) {
+#pragma unroll
+            for (int k = 0; k < 4; k++) x[k] = s[at(i, k)];
+        } else {
+            const ulonglong2 v = *reinterpret_cast<const ulonglong2*>(s + b3), u = *reinterpret_cast<const ulonglong2*>(s + (b3 ^ 2u));
+            x[0] = v.x; x[1] = v.y; x[2] = u.x; x[3] = u.y;
+        }
+    }
+    __device__ __forceinline__ void store(int i, const u64 (&x)[4], u64* s) const {
+        if (i < 3) {
+#pragma unroll
+            for (int k = 0; k < 4; k++) s[at(i, k)] = x[k];
+        } else {
+            *reinterpret_cast<ulonglong2*>(s + b3) = make_ulonglong2(x[0], x[1]);
+            *reinterpret_cast<ulonglong2*>(s + (b3 ^ 2u)) = make_ulonglong2(x[2], x[3]);
+        }
+    }
+};
+// The eight stages of NX rows at once, 64 threads to a row: values 64k + t in, 4T + k out (forward, T = row4_last(t)), the other way round
+// (inverse; narrow moduli: inputs below 2q, results below 2q; wide: below 4q).  s: 256 LDS words for each row, `stride` apart, on
+// a multiple of 16 bytes.  A block's values are written where they were read, so a lane waits for no other between the two.
+template <bool WIDE, int NX>
+__device__ __forceinline__ void row4_fwd(u64 (&x)[NX][4], const u64 (&w)[4][6], u64* s, uint32_t stride, const Row4& at, u64 q) {
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+        if (i) {
+            wave_exchange();
+#pragma unroll
+            for (int c = 0; c < NX; c++) at.load(i, x[c], s + c * stride);
+        }
+#pragma unroll
+        for (int c = 0; c < NX; c++) fwd_block2_r<WIDE>(x[c], w[i], q, 4 * q);
+        if (i < 3) {
+#pragma unroll
+            for (int c = 0; c < NX; c++) at.store(i, x[c], s + c * stride);
+        }
+    }
+}
+template <bool WIDE, int NX>
+__device__ __forceinline__ void row4_inv(u64 (&x)[NX][4], const u64 (&w)[4][6], u64* s, uint32_t stride, const Row4& at, u64 q, const ModConst& m) {
+#pragma unroll
+    for (int i = 3; i >= 0; i--) {
+        if (i < 3) {
+            wave_exchange();
+#pragma unroll
+            for (int c = 0; c < NX; c++) at.load(i, x[c], s + c * stride);
+        }
+#pragma unroll
+        for (int c = 0; c < NX; c++) {
+            if (WIDE) inv_block2_r(x[c], w[i], q);
+            else inv_block2_n(x[c], w[i], q, 2 << (2 * (3 - i)));
+        }
+        if (i) {
+#pragma unroll
+            for (int c = 0; c < NX; c++) at.store(i, x[c], s + c * stride);
+        }
+    }
+    if (!WIDE) {
+#pragma unroll
+        for (int c = 0; c < NX; c++)
+#pragma unroll
+            for (int k = 0; k < 4; k++) x[c][k] = reduce_lazy<10>(x[c][k], q, m.bits, m.rec);
+    }
 }
