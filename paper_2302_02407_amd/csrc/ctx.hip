@@ -1,4 +1,5 @@
 // Context: parameter validation, root/twiddle tables, device constants, workspace, errors.
+#include <algorithm>
 #include <stdarg.h>
 #include <new>
 #include <stdio.h>
@@ -111,6 +112,14 @@ static uint32_t tw_pos(uint32_t i, uint32_t logN) {
     return (1u << s) + ((at & ((1u << u) - 1u)) << s0) + (at >> u);
 }
 
+// The same for the FP64 kernels of rings up to 2^12 (smallring.hip): blocks of three stages from stage 0, the last one from stage
+// logN-3, and a block's 2^u factors of one of its 2^s0 groups lie 2^s0 apart.
+static uint32_t ftw_pos(uint32_t i, uint32_t logN) {
+    if (i == 0) return 0;
+    const uint32_t s = 31 - __builtin_clz(i), nb = (logN + 2) / 3, b = std::min(s / 3, nb - 1), s0 = b + 1 < nb ? 3 * b : logN - 3, u = s - s0, at = i - (1u << s);
+    return (1u << s) + ((at & ((1u << u) - 1u)) << s0) + (at >> u);
+}
+
 int32_t he_ctx_create(he_ctx** out, uint32_t logN, const uint64_t* h_q, uint32_t nq, const uint64_t* h_p,
                       uint32_t np, uint32_t dnum, void* hip_stream) {
     return he_guard(nullptr, "he_ctx_create: host allocation failed", [&]() -> int32_t {
@@ -143,7 +152,7 @@ int32_t he_ctx_create(he_ctx** out, uint32_t logN, const uint64_t* h_q, uint32_t
     c->alpha = (nq + dnum - 1) / dnum;
     c->srf = logN <= 12;
     c->stream = (hipStream_t)hip_stream;
-    c->d_mc = nullptr; c->d_tw = c->d_itw = nullptr;
+    c->d_mc = nullptr; c->d_tw = c->d_itw = nullptr; c->d_ftw = c->d_fitw = nullptr;
     c->d_ws = nullptr; c->ws_bytes = 0;
     c->d_up_dig = c->d_dn_dig = nullptr;
     c->d_up_bias = c->d_dn_bias = nullptr;
@@ -194,6 +203,19 @@ int32_t he_ctx_create(he_ctx** out, uint32_t logN, const uint64_t* h_q, uint32_t
     if (e == hipSuccess) e = hipMemcpy(c->d_mc, c->h_mc, sizeof(ModConst) * M, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(c->d_tw, tw.data(), tb, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(c->d_itw, itw.data(), tb, hipMemcpyHostToDevice);
+    if (c->srf && e == hipSuccess) {
+        std::vector<double> f((size_t)2 * M * N);                // both tables in one allocation
+        for (uint32_t k = 0; k < N; k++) {
+            const uint32_t pos = ftw_pos(k, logN);
+            for (uint32_t i = 0; i < M; i++) {
+                f[(size_t)i * N + pos] = (double)tw[(size_t)i * N + k].x;
+                f[(size_t)(M + i) * N + pos] = (double)itw[(size_t)i * N + k].x;
+            }
+        }
+        e = hipMalloc(&c->d_ftw, f.size() * sizeof(double));
+        if (e == hipSuccess) e = hipMemcpy(c->d_ftw, f.data(), f.size() * sizeof(double), hipMemcpyHostToDevice);
+        c->d_fitw = c->d_ftw + (size_t)M * N;
+    }
     if (e == hipSuccess) e = hipDeviceSynchronize();
     if (e != hipSuccess) {
         he_fail(nullptr, e == hipErrorOutOfMemory ? HE_ERR_ALLOC : HE_ERR_HIP, "he_ctx_create: %s", hipGetErrorString(e));
@@ -238,6 +260,7 @@ int32_t he_ctx_destroy(he_ctx* c) {
     if (c->d_mc) (void)hipFree(c->d_mc);
     if (c->d_tw) (void)hipFree(c->d_tw);
     if (c->d_itw) (void)hipFree(c->d_itw);
+    if (c->d_ftw) (void)hipFree(c->d_ftw);
     if (c->d_ws) (void)hipFree(c->d_ws);
     for (auto& s : c->prof_events) { (void)hipEventDestroy(s.e0); (void)hipEventDestroy(s.e1); }
     ks_free_tables(c);

@@ -66,6 +66,7 @@ struct he_ctx {
     ModConst* d_mc;    // [M]
     ulonglong2* d_tw;  // [M][N]  psi^bitrev(i) and its Shoup companion, one 16-byte load
     ulonglong2* d_itw; // [M][N]  psi^-bitrev(i), likewise
+    double *d_ftw, *d_fitw; // [M][N] the same factors for the FP64 kernels, in their order (ctx.hip, ftw_pos); null elsewhere
     // basis-conversion tables (keyswitch.hip); present when np > 0
     u64* d_up_hat;     // [dnum][alpha][alpha][M]: (Q_j/q_i) mod m for digit j holding sz limbs, [j][sz-1][i][m]
     std::vector<u64> h_up_invhat; // [dnum][alpha][alpha]: ((Q_j/q_i)^-1 mod q_i), [j][sz-1][i]

@@ -133,6 +133,7 @@ __device__ __forceinline__ uint32_t galois_src_sr(uint32_t j, uint32_t g, uint32
 struct SrTables {
     const ModConst* mc;
     const ulonglong2 *tw, *itw;   // [M][N]: factor, Shoup companion
+    const double *ftw, *fitw;     // [M][N]: the factors in the FP64 kernels' order (ctx.hip, ftw_pos), where those run
     uint32_t logN;
 };
 
@@ -378,21 +379,14 @@ __global__ __launch_bounds__(SR_THREADS) void sr_rescale_kernel(SrRescaleArgs a,
 // registers, nothing spilled).  Block b of thread t = G*R + r, R = N/8^(b+1), holds points G*8R + k*R + r; the last block, where
 // LN is no multiple of 3, the 8 points 8t + k and only its last stages.  From block 1 on a wavefront holds the same
 // 512 points in every block, so one barrier per transform is left; transformed limbs are read and written at 8t + k.
-// N = 2^12, one 40-bit limb per digit, one special prime: ModUp 20 -> 10.5 us, ModDown 29 -> 18.4, rescale 20 -> 10.2 against the
-// integer kernels above; what is left is two memory round trips, two transforms of about 2.5 us and the store.
+// N = 2^12, one 40-bit limb per digit, one special prime (three digits): ModUp 9.6 us, ModDown 14.6, rescale 8.6, where the integer
+// kernels above take 20, 29 and 20; what is left is the operands (a compute unit takes 64 bytes a cycle: 400 KB in 2.6 us), inner
+// products of 1.8 us a limb, and transforms of 2.4 to 3.0 us, a compute unit's FP64 rate.
 #pragma clang fp contract(off)
 #define SRF_LDS(LN) ((1 << (LN)) + (1 << ((LN) - 3)))
 #define SRF_DIG 3                  // digits whose operands are requested together
 #define EACH8(k) _Pragma("unroll") for (int k = 0; k < 8; k++)
 
-__device__ __forceinline__ void load8(u64 (&v)[8], const u64* __restrict__ p) {
-#pragma unroll
-    for (int k = 0; k < 8; k += 2) { const ulonglong2 u = LOAD2(p + k); v[k] = u.x; v[k + 1] = u.y; }
-}
-__device__ __forceinline__ void store8(u64* p, const u64 (&v)[8]) {
-#pragma unroll
-    for (int k = 0; k < 8; k += 2) STORE2(p + k) = make_ulonglong2(v[k], v[k + 1]);
-}
 struct FMod { double q, qi; u64 n; };
 __device__ __forceinline__ FMod f_mod(const ModConst& m) { return {(double)m.q, m.qinv, m.q}; }
 __device__ __forceinline__ double f_of(u64 v) { return __longlong_as_double((long long)(v | 0x4330000000000000ull)) - 4503599627370496.0; }   // v < 2^52
@@ -419,25 +413,103 @@ struct Srf {
     static constexpr int s0(int b) { return b + 1 < NB ? 3 * b : LN - 3; }
     static constexpr int u0(int b) { return b + 1 < NB ? 0 : U0; }
 };
-// Factors of a transform's blocks 1 ... (block 0's are the same for every thread: scalar loads at their use).
+// The 8W points of a wavefront (W lanes; half of one at N = 2^8) between memory and its transform: read and written in pairs at
+// 2l + 2W*i of lane l, so that every access is one run of 16 W bytes, and turned into the transform's order in LDS.  A Galois
+// map takes aligned runs of 2^m positions to aligned runs, so a wavefront's points come from the points of one wavefront:
+// digits and rotated addends are read as they lie and permuted there too, with no barrier.  What a lane reads for itself at
+// 8t + k (or gathers) is 64 lines an instruction in the first-level cache, which takes one a cycle; with all of it read that way
+// ModUp took 10.7 us instead of 9.6, ModDown 18.2 instead of 14.6, rescale 9.9 instead of 8.6.
 template <int LN>
-struct SrfTw { u64 w[Srf<LN>::NB][7]; };
+struct SrfRow {
+    using G = Srf<LN>;
+    static constexpr uint32_t W = G::T < 64 ? G::T : 64, S = 8 * W;
+    uint32_t l, wb;                                    // lane, the wavefront's first point
+    __device__ __forceinline__ explicit SrfRow(uint32_t t) : l(t % W), wb(t / W * S) {}
+    static __device__ __forceinline__ uint32_t at(uint32_t e) { return e ^ ((e >> 5 & 3u) << 1); }      // 16-byte accesses to different banks
+    template <class V>
+    __device__ __forceinline__ V* words(double* sm) const { return reinterpret_cast<V*>(sm + G::word(wb)); }
+    __device__ __forceinline__ void load(u64 (&v)[8], const u64* __restrict__ p) const {                // p: the wavefront's first point
+#pragma unroll
+        for (int i = 0; i < 4; i++) { const ulonglong2 u = LOAD2(p + 2 * l + 2 * W * i); v[2 * i] = u.x; v[2 * i + 1] = u.y; }
+    }
+    __device__ __forceinline__ void store(u64* p, const u64 (&v)[8]) const {
+#pragma unroll
+        for (int i = 0; i < 4; i++) STORE2(p + 2 * l + 2 * W * i) = make_ulonglong2(v[2 * i], v[2 * i + 1]);
+    }
+    // values in pairs <-> values at 8t + k, through the wavefront's words of LDS
+    template <class V>
+    __device__ __forceinline__ void pairs_in(const V (&v)[8], double* sm) const {
+#pragma unroll
+        for (int i = 0; i < 4; i++) { V* w = words<V>(sm) + at(2 * l + 2 * W * i); w[0] = v[2 * i]; w[1] = v[2 * i + 1]; }
+        wave_exchange();
+    }
+    template <class V>
+    __device__ __forceinline__ void to_own(V (&v)[8], double* sm) const {
+        pairs_in(v, sm);
+#pragma unroll
+        for (int i = 0; i < 4; i++) { const V* w = words<V>(sm) + at(8 * l + 2 * i); v[2 * i] = w[0]; v[2 * i + 1] = w[1]; }
+        wave_exchange();
+    }
+    template <class V>
+    __device__ __forceinline__ void to_pairs(V (&v)[8], double* sm) const {
+        wave_exchange();
+#pragma unroll
+        for (int i = 0; i < 4; i++) { V* w = words<V>(sm) + at(8 * l + 2 * i); w[0] = v[2 * i]; w[1] = v[2 * i + 1]; }
+        wave_exchange();
+#pragma unroll
+        for (int i = 0; i < 4; i++) { const V* w = words<V>(sm) + at(2 * l + 2 * W * i); v[2 * i] = w[0]; v[2 * i + 1] = w[1]; }
+    }
+};
+// Where the Galois image of a wavefront's points comes from: its first point, and the words of the lane's pairs in it.
+template <int LN>
+struct SrfGalois {
+    uint32_t first, src[4];
+    __device__ __forceinline__ SrfGalois(const SrfRow<LN>& row, uint32_t g) {
+        using Q = SrfRow<LN>;
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            const uint32_t s = galois_src_sr(row.wb + 2 * row.l + 2 * Q::W * i, g, LN);
+            first = __builtin_amdgcn_readfirstlane(s & ~(Q::S - 1));
+            src[i] = Q::at(s & (Q::S - 1));
+        }
+    }
+    __device__ __forceinline__ void apply(u64 (&v)[8], const SrfRow<LN>& row, double* sm) const {
+        row.pairs_in(v, sm);
+        const u64* w = row.template words<u64>(sm);
+#pragma unroll
+        for (int i = 0; i < 4; i++) { v[2 * i] = w[src[i]]; v[2 * i + 1] = w[src[i] ^ 1u]; }             // aligned pairs come from aligned pairs
+        wave_exchange();
+    }
+};
+// Factors of a transform's blocks.
+template <int LN>
+struct SrfTw { double w[Srf<LN>::NB][7]; };
 template <int LN, int B>
-__device__ __forceinline__ void srf_tw(u64 (&w)[7], const ulonglong2* __restrict__ tw, uint32_t t) {
+__device__ __forceinline__ void srf_tw(double (&w)[7], const double* __restrict__ tw, uint32_t t) {
     const uint32_t G = t / Srf<LN>::R(B);
 #pragma unroll
     for (int u = Srf<LN>::u0(B); u < 3; u++)
 #pragma unroll
-        for (int g = 0; g < (1 << u); g++) w[(1 << u) - 1 + g] = tw[(1u << (Srf<LN>::s0(B) + u)) + (G << u) + g].x;
+        for (int g = 0; g < (1 << u); g++) w[(1 << u) - 1 + g] = tw[(1u << (Srf<LN>::s0(B) + u)) + (g << Srf<LN>::s0(B)) + G];
+}
+// block 0's are the same for every thread: scalar loads, through a pointer to constant memory
+typedef const __attribute__((address_space(4))) double* const_f64;
+template <int LN>
+__device__ __forceinline__ void srf_tw0(double (&w)[7], const double* tw) {
+    const const_f64 p = (const_f64)(uintptr_t)tw;
+#pragma unroll
+    for (int i = 0; i < 7; i++) w[i] = p[1 + i];
 }
 template <int LN, int B = 1>
-__device__ __forceinline__ void srf_tw_all(SrfTw<LN>& w, const ulonglong2* __restrict__ tw, uint32_t t) {
+__device__ __forceinline__ void srf_tw_all(SrfTw<LN>& w, const double* __restrict__ tw, uint32_t t) {
+    if (B == 1) srf_tw0<LN>(w.w[0], tw);
     srf_tw<LN, B>(w.w[B], tw, t);
     if constexpr (B + 1 < Srf<LN>::NB) srf_tw_all<LN, B + 1>(w, tw, t);
 }
 // block B's points -> block D's
 template <int LN, int B, int D>
 __device__ __forceinline__ void srf_move(double (&x)[8], double* sm, uint32_t t) {
+    asm("" : "+v"(t));                             // the words are worked out here, not kept in registers
     EACH8(k) sm[Srf<LN>::pos(B, t, k)] = x[k];
     if (B == 0 || D == 0) __syncthreads();
     else wave_exchange();
@@ -445,11 +517,10 @@ __device__ __forceinline__ void srf_move(double (&x)[8], double* sm, uint32_t t)
 }
 // In: strided points (block 0's) below 2q in size.  Out: points 8t + k, not reduced (below 10q).
 template <int LN, int B = 0>
-__device__ __forceinline__ void srf_fwd(double (&x)[8], SrfTw<LN>& tw, const ulonglong2* __restrict__ table, double* sm, uint32_t t, const FMod& m) {
-    if (B == 0) srf_tw<LN, 0>(tw.w[0], table, 0);
+__device__ __forceinline__ void srf_fwd(double (&x)[8], SrfTw<LN>& tw, const double* __restrict__ table, double* sm, uint32_t t, const FMod& m) {
     double w[7];
 #pragma unroll
-    for (int i = (1 << Srf<LN>::u0(B)) - 1; i < 7; i++) w[i] = f_of(tw.w[B][i]);
+    for (int i = (1 << Srf<LN>::u0(B)) - 1; i < 7; i++) w[i] = tw.w[B][i];
 #pragma unroll
     for (int u = Srf<LN>::u0(B); u < 3; u++) {
         const int dist = 4 >> u;
@@ -471,13 +542,13 @@ __device__ __forceinline__ void srf_fwd(double (&x)[8], SrfTw<LN>& tw, const ulo
 // In: points 8t + k below q in size.  Out: strided points times scale (which carries N^-1), in [0, q).  The factors of the
 // transform after this one (next) are requested as soon as this one has used its own.
 template <int LN, int B = Srf<LN>::NB - 1>
-__device__ __forceinline__ void srf_inv(double (&x)[8], SrfTw<LN>& tw, const ulonglong2* __restrict__ table, const ulonglong2* __restrict__ next, double scale,
+__device__ __forceinline__ void srf_inv(double (&x)[8], SrfTw<LN>& tw, const double* __restrict__ table, const double* __restrict__ next, double scale,
                                         double* sm, uint32_t t, const FMod& m) {
-    if (B == 0) srf_tw<LN, 0>(tw.w[0], table, 0);
     double w[7];
 #pragma unroll
-    for (int i = (1 << Srf<LN>::u0(B)) - 1; i < 7; i++) w[i] = f_of(tw.w[B][i]);
+    for (int i = (1 << Srf<LN>::u0(B)) - 1; i < 7; i++) w[i] = tw.w[B][i];
     if (B > 0) srf_tw<LN, B>(tw.w[B], next, t);
+    else srf_tw0<LN>(tw.w[0], next);
 #pragma unroll
     for (int u = 2; u >= Srf<LN>::u0(B); u--) {
         const int dist = 4 >> u;
@@ -520,64 +591,75 @@ __device__ __forceinline__ void srf_convert(double (&x)[8], const double* keep, 
 template <int LN>
 __global__ __launch_bounds__(Srf<LN>::T, 2) void srf_modup_kernel(SrUpArgs a, SrTables tb) {
     using G = Srf<LN>;
-    __shared__ double sm[SRF_LDS(LN)], keep[(SR_MAX_SRC - 1) * G::N];
+    __shared__ __attribute__((aligned(16))) double sm[SRF_LDS(LN)];
+    __shared__ double keep[(SR_MAX_SRC - 1) * G::N];
     const uint32_t t = threadIdx.x;
+    const SrfRow<LN> row(t);
     const uint32_t s = blockIdx.x / a.n_out, o = blockIdx.x % a.n_out;
     const uint32_t j = a.oj[o], r = a.orr[o];
     const uint32_t lo = j * a.alpha, sz = min(a.alpha, a.L1 - lo);
     const uint32_t mr = r <= a.level ? r : a.nq + (r - a.level - 1);
-    const u64* c1 = a.c1[s] + ((size_t)lo << LN) + 8 * t;
-    const ulonglong2 *itw = tb.itw + ((size_t)lo << LN), *ftw = tb.tw + ((size_t)mr << LN);
+    const u64* c1 = a.c1[s] + ((size_t)lo << LN) + row.wb;
+    const double *itw = tb.fitw + ((size_t)lo << LN), *ftw = tb.ftw + ((size_t)mr << LN);
     u64 in[8];
     SrfTw<LN> w;
-    load8(in, c1);
+    row.load(in, c1);
     srf_tw_all<LN>(w, itw, t);
     const FMod m = f_mod(tb.mc[mr]);
     const u64* hat = a.hat + ((size_t)(j * a.alpha + (sz - 1)) * a.M + mr) * a.aw;
     double x[8];
     for (uint32_t i = 0; i < sz; i++) {
         const bool last = i + 1 == sz;
-        EACH8(k) x[k] = f_of(in[k]);
-        if (!last) load8(in, c1 += G::N);
         if (i) __syncthreads();                    // the words of the transform before have been read
+        row.to_own(in, sm);
+        EACH8(k) x[k] = f_of(in[k]);
+        if (!last) row.load(in, c1 += G::N);
         srf_inv<LN>(x, w, itw, last ? ftw : itw + G::N, f_of(a.scale[lo + i]), sm, t, f_mod(tb.mc[lo + i]));
         itw += G::N;
         if (!last) { EACH8(k) keep[i * G::N + t + k * G::T] = x[k]; }
     }
     srf_convert<LN>(x, keep, hat, sz, t, m);
     srf_fwd<LN>(x, w, ftw, sm, t, m);
-    u64* dst = a.raised + ((size_t)((s * a.beta + j) * a.R + r) << LN) + 8 * t;
+    u64* dst = a.raised + ((size_t)((s * a.beta + j) * a.R + r) << LN) + row.wb;
     EACH8(k) in[k] = f_canon(f_red(x[k], m), m);
-    store8(dst, in);
+    row.to_pairs(in, sm);
+    row.store(dst, in);
 }
 
-// One limb's inner product at points 8t + k.  The operands of the first SRF_DIG digits are requested together, and a transform
-// ahead of their use.
+// One limb's inner product at the wavefront's pairs.  The operands of the first SRF_DIG digits are requested together, and a
+// transform ahead of their use.
 struct SrfOps { u64 d[SRF_DIG][8], kv[SRF_DIG][8]; };
 struct SrfInner {
     const u64 *raised, *own, *key;     // this limb's digits (own: of digit own_j, null elsewhere) and key rows
     uint32_t own_j;
 };
-__device__ __forceinline__ void srf_digit(u64 (&d)[8], u64 (&kv)[8], const SrfInner& in, uint32_t j, size_t ds, size_t ks, const uint32_t (&src)[8], uint32_t t) {
-    const u64* p = j == in.own_j ? in.own : in.raised + j * ds;
-    EACH8(k) d[k] = p[src[k]];
-    load8(kv, in.key + j * ks + 8 * t);
+template <int LN>
+__device__ __forceinline__ void srf_digit(u64 (&d)[8], u64 (&kv)[8], const SrfInner& in, uint32_t j, size_t ds, size_t ks, const SrfRow<LN>& row, const SrfGalois<LN>& ga) {
+    row.load(d, (j == in.own_j ? in.own : in.raised + j * ds) + ga.first);
+    row.load(kv, in.key + j * ks + row.wb);
 }
-__device__ __forceinline__ void srf_request(SrfOps& o, const SrfInner& in, uint32_t beta, size_t ds, size_t ks, const uint32_t (&src)[8], uint32_t t) {
+template <int LN>
+__device__ __forceinline__ void srf_request(SrfOps& o, const SrfInner& in, uint32_t beta, size_t ds, size_t ks, const SrfRow<LN>& row, const SrfGalois<LN>& ga) {
 #pragma unroll
     for (uint32_t j = 0; j < SRF_DIG; j++)
-        if (j < beta) srf_digit(o.d[j], o.kv[j], in, j, ds, ks, src, t);
+        if (j < beta) srf_digit(o.d[j], o.kv[j], in, j, ds, ks, row, ga);
 }
-// |result| < q; o holds the first SRF_DIG digits
-__device__ __forceinline__ void srf_inner(double (&out)[8], const SrfOps& o, const SrfInner& in, uint32_t beta, size_t ds, size_t ks,
-                                          const uint32_t (&src)[8], uint32_t t, const FMod& m) {
+// |result| < q; o holds the first SRF_DIG digits.  The wavefront's words of sm are overwritten.
+template <int LN>
+__device__ __forceinline__ void srf_inner(double (&out)[8], SrfOps& o, const SrfInner& in, uint32_t beta, size_t ds, size_t ks, const SrfRow<LN>& row,
+                                          const SrfGalois<LN>& ga, double* sm, const FMod& m) {
+    ga.apply(o.d[0], row, sm);
     EACH8(k) out[k] = f_mul(f_of(o.d[0][k]), f_of(o.kv[0][k]), m);
 #pragma unroll
     for (uint32_t j = 1; j < SRF_DIG; j++)
-        if (j < beta) { EACH8(k) out[k] += f_mul(f_of(o.d[j][k]), f_of(o.kv[j][k]), m); }
+        if (j < beta) {
+            ga.apply(o.d[j], row, sm);
+            EACH8(k) out[k] += f_mul(f_of(o.d[j][k]), f_of(o.kv[j][k]), m);
+        }
     for (uint32_t j = SRF_DIG; j < beta; j++) {
         u64 d[8], kv[8];
-        srf_digit(d, kv, in, j, ds, ks, src, t);
+        srf_digit(d, kv, in, j, ds, ks, row, ga);
+        ga.apply(d, row, sm);
         EACH8(k) out[k] += f_mul(f_of(d[k]), f_of(kv[k]), m);
     }
     EACH8(k) out[k] = f_red(out[k], m);
@@ -586,73 +668,81 @@ __device__ __forceinline__ void srf_inner(double (&out)[8], const SrfOps& o, con
 template <int LN>
 __global__ __launch_bounds__(Srf<LN>::T, 2) void srf_moddown_kernel(ModDownEpilogue ep, SrDownArgs a, SrTables tb) {
     using G = Srf<LN>;
-    __shared__ double sm[SRF_LDS(LN)], keep[(SR_MAX_SRC - 1) * G::N];
+    __shared__ __attribute__((aligned(16))) double sm[SRF_LDS(LN)];
+    __shared__ double keep[(SR_MAX_SRC - 1) * G::N];
     const uint32_t L1 = ep.L1, R = ep.R, beta = ep.beta, t = threadIdx.x;
+    const SrfRow<LN> row(t);
     const uint32_t pc = blockIdx.x / L1, r = blockIdx.x - pc * L1, job = pc >> 1, comp = pc & 1u;
-    const uint32_t g = ep.g[job];
+    const SrfGalois<LN> ga(row, ep.g[job]);
     const size_t ds = (size_t)R << LN, ks = (size_t)(2 * ep.M) << LN, ro = (size_t)r << LN;
     const u64* raised = ep.raised[job];
     const u64* evk = ep.evk[job] + ((size_t)(comp * ep.M) << LN);
-    const ulonglong2 *itw = tb.itw + ((size_t)a.nq << LN), *ftw = tb.tw + ro;
-    uint32_t src[8];
-    EACH8(k) src[k] = galois_src_sr(8 * t + k, g, LN);
+    const double *itw = tb.fitw + ((size_t)a.nq << LN), *ftw = tb.ftw + ro;
     SrfTw<LN> w;
     SrfOps o;
     SrfInner in = {raised + ((size_t)L1 << LN), nullptr, evk + ((size_t)a.nq << LN), 0xFFFFFFFFu};
-    srf_request(o, in, beta, ds, ks, src, t);
+    srf_request(o, in, beta, ds, ks, row, ga);
     srf_tw_all<LN>(w, itw, t);
     const FMod m = f_mod(tb.mc[r]);
     double x[8];
     for (uint32_t i = 0; i < a.k; i++) {
         const bool last = i + 1 == a.k;
         const FMod mp = f_mod(tb.mc[a.nq + i]);
-        srf_inner(x, o, in, beta, ds, ks, src, t, mp);
+        if (i) __syncthreads();                    // the words of the transform before have been read
+        srf_inner(x, o, in, beta, ds, ks, row, ga, sm, mp);
+        row.to_own(x, sm);
         // next: another special-prime limb, or after them limb r
         if (last) in = {raised + ro, ep.own[job] + ro, evk + ro, r / ep.alpha};
         else { in.raised += G::N; in.key += G::N; }
-        srf_request(o, in, beta, ds, ks, src, t);
-        if (i) __syncthreads();
+        srf_request(o, in, beta, ds, ks, row, ga);
         srf_inv<LN>(x, w, itw, last ? ftw : itw + G::N, f_of(a.scale[i]), sm, t, mp);
         itw += G::N;
         if (!last) { EACH8(k) keep[i * G::N + t + k * G::T] = x[k]; }
     }
     srf_convert<LN>(x, keep, a.dn_hat + (size_t)r * a.pw, a.k, t, m);
+    __syncthreads();                               // the words of the inverse transform have been read
+    double aq[8];
+    srf_inner(aq, o, in, beta, ds, ks, row, ga, sm, m);
     // the addends travel while the forward transform runs
     const u64* c0 = comp == 0 ? ep.c0[job] : nullptr;
     const u64* self = comp ? ep.self1[job] : ep.self0[job];
-    double aq[8];
-    srf_inner(aq, o, in, beta, ds, ks, src, t, m);
     u64 add0[8], add1[8];
     EACH8(k) add0[k] = add1[k] = 0;
-    if (c0) { EACH8(k) add0[k] = c0[ro + src[k]]; }
-    if (self) load8(add1, self + ro + 8 * t);
+    if (c0) row.load(add0, c0 + ro + ga.first);
+    if (self) row.load(add1, self + ro + row.wb);
+    __syncthreads();                               // the forward transform writes everybody's words
     srf_fwd<LN>(x, w, ftw, sm, t, m);
-    u64* out = (comp ? ep.out1[job] : ep.out0[job]) + ro + 8 * t;
+    row.to_pairs(x, sm);
+    wave_exchange();
+    if (c0) ga.apply(add0, row, sm);
+    u64* out = (comp ? ep.out1[job] : ep.out0[job]) + ro + row.wb;
     const double pinv = f_of(ep.pinv[r]);
     EACH8(k) {
         const double v = f_mul(aq[k] - x[k], pinv, m) + (f_of(add0[k]) + f_of(add1[k]));     // below 3q in size
         add0[k] = f_canon(f_red(v, m), m);
     }
-    store8(out, add0);
+    row.store(out, add0);
 }
 
 template <int LN>
 __global__ __launch_bounds__(Srf<LN>::T, 2) void srf_rescale_kernel(SrRescaleArgs a, SrTables tb) {
     using G = Srf<LN>;
-    __shared__ double sm[SRF_LDS(LN)];
+    __shared__ __attribute__((aligned(16))) double sm[SRF_LDS(LN)];
     const uint32_t level = a.level, t = threadIdx.x;
+    const SrfRow<LN> row(t);
     const uint32_t jc = blockIdx.x / level, r = blockIdx.x - jc * level, job = jc >> 1, comp = jc & 1u;
-    const u64* top = a.ct[job] + ((size_t)(comp * (level + 1) + level) << LN) + 8 * t;
-    const u64* in = a.ct[job] + ((size_t)(comp * (level + 1) + r) << LN) + 8 * t;
-    const ulonglong2 *itw = tb.itw + ((size_t)level << LN), *ftw = tb.tw + ((size_t)r << LN);
+    const u64* top = a.ct[job] + ((size_t)(comp * (level + 1) + level) << LN) + row.wb;
+    const u64* in = a.ct[job] + ((size_t)(comp * (level + 1) + r) << LN) + row.wb;
+    const double *itw = tb.fitw + ((size_t)level << LN), *ftw = tb.ftw + ((size_t)r << LN);
     u64 tp[8], cr[8];
     SrfTw<LN> w;
-    load8(tp, top);
+    row.load(tp, top);
     srf_tw_all<LN>(w, itw, t);
-    load8(cr, in);
+    row.load(cr, in);
     const FMod ml = f_mod(tb.mc[level]), m = f_mod(tb.mc[r]);
     const double qlinv = f_of(a.qlinv[r]), h = f_of(ml.n >> 1);
     double x[8];
+    row.to_own(tp, sm);
     EACH8(k) x[k] = f_of(tp[k]);
     srf_inv<LN>(x, w, itw, ftw, f_of(tb.mc[level].ninv), sm, t, ml);
     EACH8(k) {                                       // (h mod q_r) - ((x + h mod q_l) mod q_r), below 2q_r in size
@@ -660,14 +750,15 @@ __global__ __launch_bounds__(Srf<LN>::T, 2) void srf_rescale_kernel(SrRescaleArg
         x[k] = f_red(h, m) - f_red(v < ml.q ? v : v - ml.q, m);
     }
     srf_fwd<LN>(x, w, ftw, sm, t, m);
-    u64* out = a.out[job] + ((size_t)(comp * level + r) << LN) + 8 * t;
+    row.to_pairs(x, sm);
+    u64* out = a.out[job] + ((size_t)(comp * level + r) << LN) + row.wb;
     EACH8(k) cr[k] = f_canon(f_mul(f_of(cr[k]) + x[k], qlinv, m), m);
-    store8(out, cr);
+    row.store(out, cr);
 }
 #pragma clang fp contract(on)
 
 // ---------------------------------------------------------------- host
-static SrTables sr_tables(const he_ctx* c) { return {c->d_mc, c->d_tw, c->d_itw, c->logN}; }
+static SrTables sr_tables(const he_ctx* c) { return {c->d_mc, c->d_tw, c->d_itw, c->d_ftw, c->d_fitw, c->logN}; }
 
 // FP64 kernels where every modulus of the context allows them (their values stay exact up to 45 bits), else the integer ones
 #define SR_LAUNCH(NAME, GRID, ...)                                                                                             \
