@@ -149,33 +149,18 @@ struct ModDownEpilogue {
     u64* out0[HE_MAX_KS_JOBS];
     u64* out1[HE_MAX_KS_JOBS];
     uint32_t g[HE_MAX_KS_JOBS];
-    // Two-launch transforms only.  fused != 0: the q-limbs of acc are never materialised; the epilogue computes
-    // acc_c[r] = sum_j digit_j[r] (gathered by the Galois map) * evk_j,c[r] itself, digit j's own limbs
-    // taken from the switched polynomial.  beta <= 8.
-    uint32_t fused, beta, alpha, M;
-    // n_terms > 0 (fused only): the launch serves ONE output whose accumulator is the sum over n_terms
-    // (polynomial, Galois element, key) terms, a sum of rotations brought down by one ModDown; raised/own/evk/g
-    // are then indexed by term, c0[0] must be null (the rotated c0 parts arrive summed through self0[0]).
-    uint32_t n_terms;
+    // small rings only (smallring.hip), whose kernel computes the accumulator itself: sum_j digit_j (gathered by the Galois map) *
+    // evk_j, digit j's own limbs taken from the switched polynomial
+    uint32_t beta, alpha, M;
     const u64* raised[HE_MAX_KS_JOBS];  // [beta][R][N]
     const u64* own[HE_MAX_KS_JOBS];     // [L1][N]
     const u64* evk[HE_MAX_KS_JOBS];     // [dnum][2][M][N]
 };
 
-// Key-switch inner product of the special-prime limbs computed by the first pass of their inverse transform
-// (two-launch transforms): limb i of the launch is job i/(2k), component (i/k)&1, special prime i%k; its input value at
-// position n is sum_j raised_j[L1 + i%k][galois(n)] * evk_j,comp[nq + i%k][n] and is never stored.  beta <= 8.
-struct IpPrologue {
-    const u64* raised[HE_MAX_KS_JOBS];  // [beta][R][N]
-    const u64* evk[HE_MAX_KS_JOBS];     // [dnum][2][M][N]
-    uint32_t g[HE_MAX_KS_JOBS];
-    uint32_t beta, R, M, L1, k, nq;
-    uint32_t n_terms;                   // as in ModDownEpilogue: > 0 = one output, arrays indexed by term
-};
-
-// Row passes of key switches whose sources serve one job each, or of one sum of rotations (ksrows.hip): raised digits in the state
-// the column pass leaves them.  Special primes: mid [J][2][k][N] receives the inverse rows of the inner products; q-limbs: mid
-// [J][2][L1][N] holds the converted part in the state the forward column pass leaves it, outputs as in ModDownEpilogue.
+// Row passes of key switches, or of one sum of rotations, with the inner products in them (ksrows.hip).  Special primes: mid
+// [J][2][k][N] receives the inverse rows of the inner products; q-limbs: mid [J][2][L1][N] holds the converted part in the state the
+// forward column pass leaves it, outputs as in ModDownEpilogue.  Digits are transformed already (done) or in the state the column
+// pass leaves them.
 #define KS_ROW_PRODUCTS 7           // products in one sum (modarith.h)
 struct KsRows {
     const u64* raised[HE_MAX_KS_JOBS];  // [beta][R][N], by job (sum: by term, as own, evk and g)
@@ -192,9 +177,11 @@ struct KsRows {
     const u64* pinv_sh;
     uint32_t J, n_terms, beta, alpha, R, M, L1, k, nq;
     uint32_t sum;                       // one output (J = 1), the sum over n_terms terms; else n_terms = 1
+    uint32_t done;                      // the digits' rows are transformed already
     uint32_t count_up, count_down;      // whether the digits' / the ModDown's transforms are counted with these rows
     // set by the launch
     uint32_t logN;
+    u64 above54, above57;               // bit per modulus
     const ModConst* mc;
     const ulonglong2 *tw, *itw;
 };
@@ -214,7 +201,6 @@ struct TransformDesc {
     const ScaleList* scale;      // inverse only: limb i is multiplied by scale[i % scale_period]
     uint32_t scale_period;       //   (must include N^-1); nullptr = plain N^-1
     const ModDownEpilogue* ep;   // forward only, or nullptr
-    const IpPrologue* ip;        // inverse, two-launch transforms only, or nullptr: inputs are computed, not read
     bool lazy_out;               // forward only: outputs may stay below 2q for moduli of at most 57 bits
                                  // (internal buffers whose consumers allow for it)
     uint32_t only_pass;          // two-launch transforms: 0 = both passes; 1 = the first pass only (inverse: rows, reading the

@@ -6,10 +6,9 @@
 //             {q_0..q_l, p_*} -> NTT.  For N = 2^13 .. 2^16, at most 8 sources and moduli of at least 36 bits the conversion
 //             runs on the matrix cores, in one launch with the column passes before and after it (colconv.hip);
 //             elsewhere it is a launch of its own with 128-bit sums and a Barrett step (baseconv_kernel).
-//   inner   : acc_c[r] = sum_j sigma_g(raised_j)[r] * evk_j,c[r]   (sigma_g as a gather).  From N = 2^13 this
-//             sum is evaluated inside the transforms of ModDown that consume it (special-prime limbs as
-//             the first inverse pass loads its rows, q-limbs in the epilogue of the last forward pass)
-//             and acc is never stored; smaller rings run the stand-alone kernels below.
+//   inner   : acc_c[r] = sum_j sigma_g(raised_j)[r] * evk_j,c[r]   (sigma_g as a gather).  From N = 2^13 and up to 8
+//             digits this sum is evaluated between the row passes of ModDown that surround it (ksrows.hip) and acc is
+//             never stored; elsewhere the stand-alone kernels below run.
 //   ModDown : p-limbs -> coefficient form (iNTT with (P/p_t)^-1 folded in) -> conversion to
 //             q_0..q_l -> NTT -> (acc - conv) * P^-1 (+ sigma_g(c0) for a rotation).
 // Neither conversion corrects the overflow multiple; each term is a canonical residue and
@@ -581,8 +580,8 @@ static int32_t launch_inner_product(he_ctx* c, uint32_t level, const IpBatch& ib
 // describe how the transforms compute them): special-prime limbs -> coefficient form (pre-multiplied by
 // N^-1 * (P/p_t)^-1), conversion to q_0..q_level, forward transform with the epilogue described by `ep`.  With `rows` its
 // launches take the place of the row passes, and ip and ep say nothing.
-static int32_t moddown_chain(he_ctx* c, uint32_t level, uint32_t J, u64* acc, u64* tmp_dn, u64* conv, const IpPrologue* ip,
-                             const ModDownEpilogue& ep, KsRows* rows = nullptr) {
+static int32_t moddown_chain(he_ctx* c, uint32_t level, uint32_t J, u64* acc, u64* tmp_dn, u64* conv, const ModDownEpilogue& ep,
+                             KsRows* rows = nullptr) {
     const uint32_t N = c->N, L1 = level + 1, k = c->np, R = L1 + k;
     const bool cc_on = c->d_dn_dig != nullptr;
     ScaleList sc;
@@ -602,7 +601,6 @@ static int32_t moddown_chain(he_ctx* c, uint32_t level, uint32_t J, u64* acc, u6
         TransformDesc t = {};
         t.fwd = false; t.seg[0] = acc; t.n_seg = 1; t.dst = tmp_dn; t.n = n;
         t.mod_idx = mods.data(); t.src_limb = lim.data(); t.scale = &sc; t.scale_period = k;
-        t.ip = ip;
         t.only_pass = cc_on ? 1u : 0u;
         int32_t rc = HE_OK;
         if (rows) {
@@ -682,10 +680,10 @@ static int32_t inner_moddown_batch(he_ctx* c, uint32_t level, const KsSrc* srcs,
     // computed by the first pass of their inverse transform, the q-limbs inside the ModDown epilogue (they would
     // only be written here and read back there).  Other rings run the stand-alone kernel.
     const bool fused = two_pass(c) && beta <= 8;
-    if (rows_left) {
+    if (fused) {
         KsRows a = {};
         ks_rows_shape(c, level, a);
-        a.J = J; a.n_terms = 1;
+        a.J = J; a.n_terms = 1; a.done = rows_left ? 0u : 1u;
         for (uint32_t i = 0; i < J; i++) {
             const KsSrc& src = srcs[jobs[i].src];
             a.raised[i] = raised_of[i]; a.own[i] = src.c1; a.evk[i] = jobs[i].evk; a.g[i] = jobs[i].g;
@@ -695,24 +693,20 @@ static int32_t inner_moddown_batch(he_ctx* c, uint32_t level, const KsSrc* srcs,
             a.out0[i] = jobs[i].out0; a.out1[i] = jobs[i].out1;
             if (a.c0[i]) c->cnt.automorph += L1;
         }
-        int32_t rc = moddown_chain(c, level, J, acc, tmp_dn, conv, nullptr, ModDownEpilogue{}, &a);
+        int32_t rc = moddown_chain(c, level, J, acc, tmp_dn, conv, ModDownEpilogue{}, &a);
         if (rc != HE_OK) return rc;
         c->cnt.keyswitch += J;
         return HE_OK;
     }
     // small rings: inner product, ModDown and epilogue of every output limb in one work group, one launch
-    const bool small = !fused && small_ring_path(c, level);
-    IpPrologue ip = {};
-    if (fused) {
-        ip.beta = beta; ip.R = R; ip.M = c->M; ip.L1 = L1; ip.k = k; ip.nq = c->nq;
-        for (uint32_t i = 0; i < J; i++) { ip.raised[i] = raised_of[i]; ip.evk[i] = jobs[i].evk; ip.g[i] = jobs[i].g; }
-    } else if (!small) {
+    const bool small = small_ring_path(c, level);
+    if (!small) {
         int32_t rc = launch_inner_product(c, level, ib, groups, acc);
         if (rc != HE_OK) return rc;
     }
     ModDownEpilogue ep = {};
     ep.acc = acc; ep.pinv = c->d_pinv; ep.pinv_sh = c->d_pinv_sh; ep.R = R; ep.L1 = L1;
-    ep.fused = fused ? 1u : 0u; ep.beta = beta; ep.alpha = c->alpha; ep.M = c->M;
+    ep.beta = beta; ep.alpha = c->alpha; ep.M = c->M;
     for (uint32_t i = 0; i < J; i++) {
         const KsSrc& src = srcs[jobs[i].src];
         ep.raised[i] = raised_of[i]; ep.own[i] = src.c1; ep.evk[i] = jobs[i].evk;
@@ -723,7 +717,7 @@ static int32_t inner_moddown_batch(he_ctx* c, uint32_t level, const KsSrc* srcs,
         ep.g[i] = jobs[i].g;
         if (ep.c0[i]) c->cnt.automorph += L1;
     }
-    int32_t rc = small ? sr_moddown(c, level, J, ep) : moddown_chain(c, level, J, acc, tmp_dn, conv, fused ? &ip : nullptr, ep);
+    int32_t rc = small ? sr_moddown(c, level, J, ep) : moddown_chain(c, level, J, acc, tmp_dn, conv, ep);
     if (rc != HE_OK) return rc;
     c->cnt.keyswitch += J;
     return HE_OK;
@@ -889,32 +883,20 @@ int32_t ks_rotate_sum_deferred(he_ctx* c, uint32_t level, const KsSumTerm* terms
     hipLaunchKernelGGL(rot_sum_kernel, dim3(N / KS_THREADS, L1, n_plain ? 2 : 1), dim3(KS_THREADS), 0, c->stream, ra, s0, s1, c->d_mc, c->logN);
     HE_HIP(c, hipGetLastError());
     c->cnt.automorph += (uint64_t)n_rot * L1;
-    IpPrologue ip = {};
     ModDownEpilogue ep = {};
     ep.acc = acc; ep.pinv = c->d_pinv; ep.pinv_sh = c->d_pinv_sh; ep.R = R; ep.L1 = L1;
-    ep.fused = fused ? 1u : 0u; ep.beta = beta; ep.alpha = c->alpha; ep.M = c->M;
     ep.c0[0] = nullptr; ep.self0[0] = s0; ep.self1[0] = n_plain ? s1 : nullptr;
     ep.out0[0] = out0; ep.out1[0] = out1; ep.g[0] = 1;
     KsRows kr = {};
-    if (rows_left) {
+    if (fused) {
         ks_rows_shape(c, level, kr);
-        kr.J = 1; kr.sum = 1; kr.n_terms = n_rot;
+        kr.J = 1; kr.sum = 1; kr.n_terms = n_rot; kr.done = rows_left ? 0u : 1u;
         for (uint32_t t = 0; t < n_rot; t++) {
             kr.raised[t] = raised + (size_t)src_of[t] * beta * R * N;
             kr.own[t] = rot[t]->c1; kr.evk[t] = rot[t]->evk; kr.g[t] = rot[t]->g;
         }
         kr.self0[0] = s0; kr.self1[0] = ep.self1[0];
         kr.out0[0] = out0; kr.out1[0] = out1;
-        if (c->prof_on) c->prof_key_limbs += (uint64_t)n_rot * 2 * beta * R;
-    } else if (fused) {
-        ip.beta = beta; ip.R = R; ip.M = c->M; ip.L1 = L1; ip.k = k; ip.nq = c->nq; ip.n_terms = n_rot;
-        ep.n_terms = n_rot;
-        for (uint32_t t = 0; t < n_rot; t++) {
-            ip.raised[t] = ep.raised[t] = raised + (size_t)src_of[t] * beta * R * N;
-            ip.evk[t] = ep.evk[t] = rot[t]->evk;
-            ip.g[t] = ep.g[t] = rot[t]->g;
-            ep.own[t] = rot[t]->c1;
-        }
         if (c->prof_on) c->prof_key_limbs += (uint64_t)n_rot * 2 * beta * R;
     } else {
         for (uint32_t t0 = 0; t0 < n_rot; t0 += HE_MAX_KS_JOBS) {
@@ -933,7 +915,7 @@ int32_t ks_rotate_sum_deferred(he_ctx* c, uint32_t level, const KsSumTerm* terms
             if (c->prof_on) c->prof_key_limbs += (uint64_t)cnt * 2 * beta * R;
         }
     }
-    int32_t rc = moddown_chain(c, level, 1, acc, tmp_dn, conv, fused ? &ip : nullptr, ep, rows_left ? &kr : nullptr);
+    int32_t rc = moddown_chain(c, level, 1, acc, tmp_dn, conv, ep, fused ? &kr : nullptr);
     if (rc != HE_OK) return rc;
     c->cnt.keyswitch += n_rot;
     return HE_OK;
@@ -1215,7 +1197,6 @@ int32_t ks_hoisted_sum(he_ctx* c, uint32_t level, const KsSrc* srcs, uint32_t J,
         c->cnt.automorph += (uint64_t)nb * T * L1;
         ModDownEpilogue ep = {};
         ep.acc = acc; ep.pinv = c->d_pinv; ep.pinv_sh = c->d_pinv_sh; ep.R = R; ep.L1 = L1;
-        ep.fused = 0; ep.beta = beta; ep.alpha = c->alpha; ep.M = c->M;
         for (uint32_t j = 0; j < nb; j++) {
             ep.c0[j] = nullptr; ep.g[j] = 1;
             ep.self0[j] = s0 + (size_t)j * L1 * N;
@@ -1253,7 +1234,7 @@ int32_t ks_hoisted_sum(he_ctx* c, uint32_t level, const KsSrc* srcs, uint32_t J,
             HE_HIP(c, hipGetLastError());
         }
         if (c->prof_on) c->prof_key_limbs += (uint64_t)T * 2 * beta * R;
-        int32_t rc = moddown_chain(c, level, nb, acc, tmp_dn, conv, nullptr, ep);
+        int32_t rc = moddown_chain(c, level, nb, acc, tmp_dn, conv, ep);
         if (rc != HE_OK) return rc;
         c->cnt.keyswitch += (uint64_t)nb * T;
     }
@@ -1315,13 +1296,12 @@ int32_t ks_moddown_stored(he_ctx* c, uint32_t level, uint32_t J, u64* acc, const
         u64* conv = tmp_dn + (size_t)nb * 2 * k * N;
         ModDownEpilogue ep = {};
         ep.acc = a; ep.pinv = c->d_pinv; ep.pinv_sh = c->d_pinv_sh; ep.R = R; ep.L1 = L1;
-        ep.fused = 0; ep.beta = num_digits(c, level); ep.alpha = c->alpha; ep.M = c->M;
         for (uint32_t i = 0; i < nb; i++) {
             ep.c0[i] = nullptr; ep.g[i] = 1;
             ep.self0[i] = add0 ? add0[j0 + i] : nullptr; ep.self1[i] = add1 ? add1[j0 + i] : nullptr;
             ep.out0[i] = out0[j0 + i]; ep.out1[i] = out1[j0 + i];
         }
-        int32_t rc = moddown_chain(c, level, nb, a, tmp_dn, conv, nullptr, ep);
+        int32_t rc = moddown_chain(c, level, nb, a, tmp_dn, conv, ep);
         if (rc != HE_OK) return rc;
     }
     return HE_OK;
@@ -1369,7 +1349,6 @@ int32_t rescale_batch(he_ctx* ctx, const u64* const* cts, u64* const* outs, uint
         ModDownEpilogue ep = {};
         ep.acc = cts[b0]; ep.R = L1; ep.L1 = level;
         ep.pinv = ctx->d_qlinv + (size_t)level * ctx->nq; ep.pinv_sh = ctx->d_qlinv_sh + (size_t)level * ctx->nq;
-        ep.fused = 0; ep.beta = 1; ep.alpha = ctx->alpha; ep.M = ctx->M;
         for (uint32_t i = 0; i < nb; i++) {
             ep.c0[i] = nullptr; ep.self0[i] = nullptr; ep.self1[i] = nullptr; ep.g[i] = 1;
             ep.out0[i] = outs[b0 + i]; ep.out1[i] = outs[b0 + i] + (size_t)level * N;

@@ -1,11 +1,13 @@
-// The row passes of a key switch whose source serves one job (or one term of a sum of rotations), N = 2^13 .. 2^17: the
-// digits' last eight stages, the inner product and the transforms of ModDown around it, a wavefront per row.
+// The row passes of key switches, N = 2^13 .. 2^17: the inner product and the transforms of ModDown around it, a wavefront per
+// row, and before them the last eight stages of the digits whose source serves one job or one term of a sum of rotations.
 //
 // The Galois map takes whole rows of the 2^LC x 256 view to whole rows: k' = g*k + (g-1)/2 and the row of a position is the
 // low LC bits of k (bit-reversed order).  So row b of an inner product needs exactly one row of every digit, row sigma(b), and
 // that row can be transformed where it is used: it is read once in the state the column pass leaves it and permuted in LDS,
 // where a transform launch of its own wrote and read back 72 of some 580 limb moves of a key switch at the benchmark's top
-// level, and both components read it again.  Digits that several jobs use are transformed once instead (ntt2p.hip).
+// level, and both components read it again.  Digits that several jobs use are transformed once instead (ntt2p.hip) and come
+// here complete (DONE); nineteen limbs by sixteen rotations of one source take 1782 us so, where sums formed inside the
+// transforms of each component, which read every digit twice, took 1910.
 //
 //   special primes: rows of the digits -> products with both components of the key -> inverse rows of both sums;
 //   q-limbs:        rows of the digits -> products -> rows of both converted components -> (acc - conv) * P^-1 + addends.
@@ -35,6 +37,12 @@
 // wavefront to a row, 29.5 with a work group; level 5 of 2^14 39.5 and 34.8.  At 2048 one at level 5 of 2^16 (2048 and 1536
 // rows) takes 59.9 instead of 56.6, six ciphertexts by eight amounts at 2^14 352 instead of 329.
 #define KR_GROUP_ROWS 1024
+// Digits that are transformed already leave a wavefront so little to do that up to this many rows each component gets one of its
+// own, which transforms the converted component while the first digit is on its way.  The launches are then two rounds of
+// wavefronts at most.  Four rotations of one source at level 5 of N = 2^14 46.2 us with one wavefront to a row, 42.1 so; two at
+// level 11 of 2^16 (4096 and 6144 rows) 119.7 and 116.4; at 16384 eight rotations at level 5 of 2^16 (16384 and 12288 rows) 174.6
+// instead of 171.2.
+#define KR_HALF_ROWS 8192
 
 // A lane works on points 4T .. 4T+3 of a row (row4_last) in the last block of a transform and on points 2t, 2t+1, 128+2t, 129+2t
 // elsewhere, so that whatever it reads from memory there lies side by side.
@@ -67,13 +75,13 @@ struct KrRow {
 
 // W: 0 = at most 54 bits, 1 = 55 to 57, 2 = wider: the forward ranges of ntt_blocks.h change at 57 bits, the inverse ones at 54.
 //
-// Both components of the inner products of row b of limb r for one (source, key) term, added to the sums s0 and s1; `spill`
+// Both components of the inner products of row b of limb r for one (source, key) term, added to the sums s; `spill`
 // empties them when they hold KS_ROW_PRODUCTS products.  Digits enter as the row transform leaves them where W = 0 (below 73q <
 // 2^60.2: 31-bit high halves, 11 products fit a sum), else below 2q (1) or canonical (2).  buf: a row for each digit, of which
 // digits j0, j0 + step .. are worked on (j0 < beta).  AHEAD: the next digit's row and the own one are asked for ahead of their turn.
 template <int W, bool SP, bool AHEAD, class Spill>
 __device__ __forceinline__ void ks_row_products(const KsRows& a, uint32_t id, uint32_t r, uint32_t b, uint32_t t, u64* buf, const ModConst& m, const Row4& at,
-                                                KrRow& kr, SplitSum (&s0)[4], SplitSum (&s1)[4], uint32_t j0, uint32_t step, Spill&& spill) {
+                                                KrRow& kr, SplitSum (&s)[2][4], uint32_t j0, uint32_t step, Spill&& spill) {
     const uint32_t logN = a.logN, mi = SP ? a.nq + r : r, row0 = b * 256;
     const size_t ro = (size_t)(SP ? a.L1 + r : r) << logN, dig_stride = (size_t)a.R << logN, comp_stride = (size_t)a.M << logN;
     const uint32_t own_j = SP ? 0xFFFFFFFFu : r / a.alpha;
@@ -132,8 +140,8 @@ __device__ __forceinline__ void ks_row_products(const KsRows& a, uint32_t id, ui
         spill();
 #pragma unroll
         for (int k = 0; k < 4; k++) {
-            split_mac(s0[k], d[k], b4[k]);
-            split_mac(s1[k], d[k], a4[k]);
+            split_mac(s[0][k], d[k], b4[k]);
+            split_mac(s[1][k], d[k], a4[k]);
         }
         j += step;
     };
@@ -141,6 +149,48 @@ __device__ __forceinline__ void ks_row_products(const KsRows& a, uint32_t id, ui
     for (j = j0; j < a.beta;) {
         digit(kb[0], ka[0], kb[1], ka[1]);
         if (j < a.beta) digit(kb[1], ka[1], kb[0], ka[0]);
+    }
+    wave_exchange();
+}
+
+// The same from digits that are transformed already (below 2q, canonical for moduli above 57 bits), for components c0 .. c0+NX-1.
+// buf: two rows.  `first` runs while the first digit is on its way.
+template <bool SP, int NX, class Spill, class First>
+__device__ __forceinline__ void ks_row_products_done(const KsRows& a, uint32_t id, uint32_t r, uint32_t b, uint32_t t, u64* buf, KrRow& kr,
+                                                     SplitSum (&s)[NX][4], uint32_t c0, Spill&& spill, First&& first) {
+    const uint32_t logN = a.logN, mi = SP ? a.nq + r : r, row0 = b * 256, own_j = SP ? 0xFFFFFFFFu : r / a.alpha;
+    const size_t ro = (size_t)(SP ? a.L1 + r : r) << logN, dig_stride = (size_t)a.R << logN, comp_stride = (size_t)a.M << logN;
+    kr.map(row0, t, a.g[id], logN);
+    const u64* row = a.raised[id] + ro + (size_t)kr.bs * 256;
+    const u64* own = SP ? row : a.own[id] + ro + (size_t)kr.bs * 256;
+    const u64* key = a.evk[id] + ((size_t)mi << logN) + row0 + c0 * comp_stride;
+    u64 d[2][4], kv[2][NX][4];
+    auto load = [&](uint32_t j, int n) {
+        kr_load(d[n], j == own_j ? own : row + j * dig_stride, t);
+#pragma unroll
+        for (int c = 0; c < NX; c++) kr_load(kv[n][c], key + (2 * j + c) * comp_stride, t);
+    };
+    auto digit = [&](uint32_t j, int n) {
+        kr.put(buf + 256 * n, d[n]);
+        if (j + 1 < a.beta) load(j + 1, 1 - n);
+        wave_exchange();
+        u64 v[4];
+#pragma unroll
+        for (int k = 0; k < 4; k++) v[k] = buf[256 * n + kr.src[k]];
+        SCHED_FENCE();
+        spill();
+#pragma unroll
+        for (int k = 0; k < 4; k++)
+#pragma unroll
+            for (int c = 0; c < NX; c++) split_mac(s[c][k], v[k], kv[n][c][k]);
+    };
+    load(0, 0);
+    SCHED_FENCE();
+    first();
+#pragma unroll 1
+    for (uint32_t j = 0; j < a.beta; j += 2) {
+        digit(j, 0);
+        if (j + 1 < a.beta) digit(j + 1, 1);
     }
     wave_exchange();
 }
@@ -190,17 +240,15 @@ struct KrAdd {
         }
     }
 };
+// bit 55 and less: the transform's values go into the difference as they are
+template <int W>
+__device__ __forceinline__ bool kr_raw(const ModConst& m) { return W < 2 && m.bits <= 55; }
+// rows of the converted components, in the order of the sums
 template <int W, int NX>
-__device__ __forceinline__ void ks_row_down(const KsRows& a, uint32_t job, uint32_t c0, uint32_t r, uint32_t b, uint32_t t, u64* buf, const ModConst& m,
-                                            const Row4& at, const KrRow& kr, const u64 (&w)[4][6], u64 (&cv)[NX][4], const u64 (&v)[NX][4], KrAdd<NX>& ad) {
-    const uint32_t row0 = b * 256;
-    const size_t qo = (size_t)r << a.logN;
+__device__ __forceinline__ void ks_row_transformed(u64 (&cv)[NX][4], u64* buf, const ModConst& m, const Row4& at, const KrRow& kr, const u64 (&w)[4][6]) {
     SCHED_FENCE();
     row4_fwd<W == 2, NX>(cv, w, buf, 256, at, m.q);
-    // out = (acc - conv) * P^-1 + addends: the product is below 4q whatever its factor, so the transform value may stay as it is
-    // where 128q plus the accumulator fits 64 bits, else below 2q; the sum is below 6q
-    const bool raw = W < 2 && m.bits <= 55;
-    const u64 bias = raw ? (m.q << 7) : 2 * m.q, pinv = ((const_u64)(uintptr_t)a.pinv)[r], pinv_sh = ((const_u64)(uintptr_t)a.pinv_sh)[r];
+    const bool raw = kr_raw<W>(m);
     wave_exchange();
 #pragma unroll
     for (int c = 0; c < NX; c++) {
@@ -213,8 +261,18 @@ __device__ __forceinline__ void ks_row_down(const KsRows& a, uint32_t job, uint3
     wave_exchange();
 #pragma unroll
     for (int c = 0; c < NX; c++) kr.get(cv[c], buf + 256 * c);
+    wave_exchange();
+}
+template <int W, int NX>
+__device__ __forceinline__ void ks_row_down(const KsRows& a, uint32_t job, uint32_t c0, uint32_t r, uint32_t b, uint32_t t, u64* buf, const ModConst& m,
+                                            const KrRow& kr, u64 (&cv)[NX][4], const u64 (&v)[NX][4], KrAdd<NX>& ad) {
+    const uint32_t row0 = b * 256;
+    const size_t qo = (size_t)r << a.logN;
+    // out = (acc - conv) * P^-1 + addends: the product is below 4q whatever its factor, so the transform value may stay as it is
+    // where 128q plus the accumulator fits 64 bits, else below 2q; the sum is below 6q
+    const bool raw = kr_raw<W>(m);
+    const u64 bias = raw ? (m.q << 7) : 2 * m.q, pinv = ((const_u64)(uintptr_t)a.pinv)[r], pinv_sh = ((const_u64)(uintptr_t)a.pinv_sh)[r];
     if (ad.rotated) {
-        wave_exchange();
         kr.put(buf, ad.rot);
         wave_exchange();
 #pragma unroll
@@ -232,43 +290,45 @@ __device__ __forceinline__ void ks_row_down(const KsRows& a, uint32_t job, uint3
     }
 }
 // v = (v + sums) below 2q, the sums empty again
-__device__ __forceinline__ void kr_flush(u64 (&v)[2][4], SplitSum (&s0)[4], SplitSum (&s1)[4], const ModConst& m) {
+template <int NX>
+__device__ __forceinline__ void kr_flush(u64 (&v)[NX][4], SplitSum (&s)[NX][4], const ModConst& m) {
 #pragma unroll
-    for (int c = 0; c < 2; c++) {
+    for (int c = 0; c < NX; c++) {
         u64 p[4];
-        split_reduce(p, c ? s1 : s0, m);
+        split_reduce(p, s[c], m);
 #pragma unroll
         for (int k = 0; k < 4; k++) {
             v[c][k] = reduce_lazy<7>(v[c][k] + p[k], m.q, m.bits, m.rec);
-            (c ? s1 : s0)[k] = SplitSum{0, 0, 0};
+            s[c][k] = SplitSum{0, 0, 0};
         }
         SCHED_FENCE();
     }
 }
 
 // One wavefront: row b of limb r for one job.  MANY: more than KS_ROW_PRODUCTS digits.
-template <int W, bool SP, bool MANY>
+template <int W, bool SP, bool MANY, bool DONE>
 __device__ __forceinline__ void ks_row(const KsRows& a, uint32_t job, uint32_t r, uint32_t b, uint32_t t, u64* buf) {
     const uint32_t mi = SP ? a.nq + r : r, lc = a.logN - 8;
     const ModConst m = mod_const(a.mc, mi);
-    const Row4 at(t);
     KrRow kr(t);
     u64 w[4][6], v[2][4] = {}, cv[2][4];
-    SplitSum s0[4] = {}, s1[4] = {};
+    SplitSum s[2][4] = {};
     uint32_t pending = 0;
-    ks_row_products<W, SP, true>(a, job, r, b, t, buf, m, at, kr, s0, s1, 0, 1, [&]() {
-        if (MANY && pending == KS_ROW_PRODUCTS) { kr_flush(v, s0, s1, m); pending = 0; }
+    auto spill = [&]() {
+        if (MANY && pending == KS_ROW_PRODUCTS) { kr_flush(v, s, m); pending = 0; }
         pending++;
-    });
+    };
+    if constexpr (DONE) ks_row_products_done<SP, 2>(a, job, r, b, t, buf, kr, s, 0, spill, []() {});
+    else ks_row_products<W, SP, true>(a, job, r, b, t, buf, m, Row4(t), kr, s, 0, 1, spill);
     SCHED_FENCE();
-    if (MANY) kr_flush(v, s0, s1, m);
-    else split_reduce(v[0], s0, m);
+    if (MANY) kr_flush(v, s, m);
+    else split_reduce(v[0], s[0], m);
     SCHED_FENCE();
     asm("" : "+v"(t));                                   // what follows from the lane is worked out anew, not kept in registers
     if (!SP) ks_row_converted(cv, a, job, 0, r, b, t);
     tw_row4(w, (SP ? a.itw : a.tw) + ((size_t)mi << a.logN), lc, b, t);
     SCHED_FENCE();
-    if (!MANY) split_reduce(v[1], s1, m);
+    if (!MANY) split_reduce(v[1], s[1], m);
     SCHED_FENCE();
     if (SP) {
         if (!MANY) {
@@ -279,35 +339,60 @@ __device__ __forceinline__ void ks_row(const KsRows& a, uint32_t job, uint32_t r
     } else {
         KrAdd<2> ad;
         ad.load(a, job, 0, r, b, t, kr.bs);
-        ks_row_down<W, 2>(a, job, 0, r, b, t, buf, m, Row4(t), kr, w, cv, v, ad);
+        ks_row_transformed<W, 2>(cv, buf, m, Row4(t), kr, w);
+        ks_row_down<W, 2>(a, job, 0, r, b, t, buf, m, kr, cv, v, ad);
     }
 }
-// A work group of nw wavefronts: row b of limb r, the terms (sum) or the digits spread over the wavefronts; the first two then take
+// One wavefront: one component of that, from digits that are transformed already.  buf: two rows.
+template <int W, bool SP>
+__device__ __forceinline__ void ks_row_half(const KsRows& a, uint32_t job, uint32_t c, uint32_t r, uint32_t b, uint32_t t, u64* buf) {
+    const uint32_t mi = SP ? a.nq + r : r;
+    const ModConst m = mod_const(a.mc, mi);
+    KrRow kr(t);
+    u64 w[4][6], v[1][4] = {}, cv[1][4];
+    SplitSum s[1][4] = {};
+    KrAdd<1> ad;
+    if (!SP) ks_row_converted(cv, a, job, c, r, b, t);
+    tw_row4(w, (SP ? a.itw : a.tw) + ((size_t)mi << a.logN), a.logN - 8, b, t);
+    ks_row_products_done<SP, 1>(a, job, r, b, t, buf, kr, s, c, []() {}, [&]() {
+        if (SP) return;
+        ks_row_transformed<W, 1>(cv, buf, m, Row4(t), kr, w);
+        asm("" : "+v"(t));                               // what follows from the lane is worked out anew, not kept in registers
+        ad.load(a, job, c, r, b, t, kr.bs);
+    });
+    SCHED_FENCE();
+    kr_flush(v, s, m);
+    if (SP) ks_row_special<W, 1>(a, job, c, r, b, t, buf, m, Row4(t), kr, w, v);
+    else ks_row_down<W, 1>(a, job, c, r, b, t, buf, m, kr, cv, v, ad);
+}
+// A work group of nw wavefronts: row b of limb r, the terms (SUM) or the digits spread over the wavefronts; the first two then take
 // a component each.  buf: LDS of the work group, max(beta, 2) rows a wavefront.
-template <int W, bool SP, bool SUM>
+template <int W, bool SP, bool SUM, bool DONE>
 __device__ __forceinline__ void ks_row_group(const KsRows& a, uint32_t job, uint32_t r, uint32_t b, uint32_t wave, uint32_t nw, uint32_t t, u64* buf) {
     const uint32_t mi = SP ? a.nq + r : r, lc = a.logN - 8;
     const ModConst m = mod_const(a.mc, mi);
     KrRow kr(t);
-    const uint32_t per_wave = 256 * max(a.beta, 2u);
+    const uint32_t per_wave = 256 * (DONE ? 2u : max(a.beta, 2u));
     u64* part = buf + per_wave * wave;                   // the wavefront's digits, then its two sums
     u64 v[2][4] = {};
-    SplitSum s0[4] = {}, s1[4] = {};
+    SplitSum s[2][4] = {};
     uint32_t pending = 0;
+    auto spill = [&]() {
+        if (SUM && pending == KS_ROW_PRODUCTS) { kr_flush(v, s, m); pending = 0; }
+        pending++;
+    };
     if (SUM) {
 #pragma unroll 1
         for (uint32_t i = wave; i < a.n_terms; i += nw) {
             asm("" : "+v"(t));                           // what follows from the lane is worked out anew, not kept in registers
-            ks_row_products<W, SP, false>(a, i, r, b, t, part, m, Row4(t), kr, s0, s1, 0, 1, [&]() {
-                if (pending == KS_ROW_PRODUCTS) { kr_flush(v, s0, s1, m); pending = 0; }
-                pending++;
-            });
+            if constexpr (DONE) ks_row_products_done<SP, 2>(a, i, r, b, t, part, kr, s, 0, spill, []() {});
+            else ks_row_products<W, SP, false>(a, i, r, b, t, part, m, Row4(t), kr, s, 0, 1, spill);
         }
     } else if (wave < a.beta) {
-        ks_row_products<W, SP, false>(a, job, r, b, t, part, m, Row4(t), kr, s0, s1, wave, nw, []() {});
+        ks_row_products<W, SP, false>(a, job, r, b, t, part, m, Row4(t), kr, s, wave, nw, spill);
     }
     SCHED_FENCE();
-    kr_flush(v, s0, s1, m);
+    kr_flush(v, s, m);
 #pragma unroll
     for (int c = 0; c < 2; c++) kr.put(part + 256 * c, v[c]);
     SCHED_FENCE();
@@ -336,9 +421,14 @@ __device__ __forceinline__ void ks_row_group(const KsRows& a, uint32_t job, uint
     u64* mine = buf + 256 * wave;                        // a sum that only this wavefront has read
     wave_exchange();
     if (SP) ks_row_special<W, 1>(a, job, wave, r, b, t, mine, m, Row4(t), kr, w, sum);
-    else ks_row_down<W, 1>(a, job, wave, r, b, t, mine, m, Row4(t), kr, w, cv, sum, ad);
+    else {
+        ks_row_transformed<W, 1>(cv, mine, m, Row4(t), kr, w);
+        ks_row_down<W, 1>(a, job, wave, r, b, t, mine, m, kr, cv, sum, ad);
+    }
 }
 
+// W of a modulus, from the argument list: the branch waits for no load of its constants
+__device__ __forceinline__ uint32_t kr_width(const KsRows& a, uint32_t mi) { return (uint32_t)(a.above54 >> mi & 1u) + (uint32_t)(a.above57 >> mi & 1u); }
 template <int W>
 __device__ __forceinline__ uint32_t kr_pin(uint32_t v) {     // keeps the widths' loads apart (see ntt2p.hip)
     if (W == 0) asm("; 54 bits" : "+s"(v));
@@ -348,30 +438,44 @@ __device__ __forceinline__ uint32_t kr_pin(uint32_t v) {     // keeps the widths
 }
 
 // A wavefront per (limb, row, job), jobs fastest; each XCD works on every eighth (limb, row).
-template <bool SP, bool MANY>
+template <bool SP, bool MANY, bool DONE>
 __global__ __launch_bounds__(KR_THREADS, MANY ? 3 : 4) void ks_rows_kernel(KsRows a) {
     extern __shared__ __attribute__((aligned(16))) u64 sm[];
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), rows = a.logN - 8;
     const uint32_t item = (blockIdx.x >> 3) * KR_WAVES + wave, un = item / a.J, job = item - un * a.J;
     const uint32_t u = un * 8 + (blockIdx.x & 7u), r = u >> rows, b = u & ((1u << rows) - 1u);
     if (r >= (SP ? a.k : a.L1)) return;
-    u64* buf = sm + wave * (256 * max(a.beta, 2u));
-    const uint32_t bits = mod_const(a.mc, SP ? a.nq + r : r).bits, t = threadIdx.x & 63u;
-    if (bits <= 54) ks_row<0, SP, MANY>(a, job, kr_pin<0>(r), b, t, buf);
-    else if (bits <= 57) ks_row<1, SP, MANY>(a, job, kr_pin<1>(r), b, t, buf);
-    else ks_row<2, SP, MANY>(a, job, kr_pin<2>(r), b, t, buf);
+    u64* buf = sm + wave * (256 * (DONE ? 2u : max(a.beta, 2u)));
+    const uint32_t width = kr_width(a, SP ? a.nq + r : r), t = threadIdx.x & 63u;
+    if (width == 0) ks_row<0, SP, MANY, DONE>(a, job, kr_pin<0>(r), b, t, buf);
+    else if (width == 1) ks_row<1, SP, MANY, DONE>(a, job, kr_pin<1>(r), b, t, buf);
+    else ks_row<2, SP, MANY, DONE>(a, job, kr_pin<2>(r), b, t, buf);
+}
+// A wavefront per (limb, row, job, component).
+template <bool SP>
+__global__ __launch_bounds__(KR_THREADS, 4) void ks_rows_half_kernel(KsRows a) {
+    __shared__ __attribute__((aligned(16))) u64 sm[KR_WAVES * 512];
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), rows = a.logN - 8, t = threadIdx.x & 63u;
+    const uint32_t at = (blockIdx.x >> 3) * KR_WAVES + wave, item = at >> 1, un = item / a.J, job = item - un * a.J;
+    const uint32_t u = un * 8 + (blockIdx.x & 7u), r = u >> rows, b = u & ((1u << rows) - 1u);
+    if (r >= (SP ? a.k : a.L1)) return;
+    u64* buf = sm + 512 * wave;
+    const uint32_t width = kr_width(a, SP ? a.nq + r : r);
+    if (width == 0) ks_row_half<0, SP>(a, job, at & 1u, kr_pin<0>(r), b, t, buf);
+    else if (width == 1) ks_row_half<1, SP>(a, job, at & 1u, kr_pin<1>(r), b, t, buf);
+    else ks_row_half<2, SP>(a, job, at & 1u, kr_pin<2>(r), b, t, buf);
 }
 // A work group per (limb, row) of a sum, or per (limb, row, job).
-template <bool SP, bool SUM>
-__global__ __launch_bounds__(KR_THREADS, 3) void ks_rows_group_kernel(KsRows a) {
+template <bool SP, bool SUM, bool DONE>
+__global__ __launch_bounds__(KR_THREADS, SUM && DONE ? 2 : 3) void ks_rows_group_kernel(KsRows a) {
     extern __shared__ __attribute__((aligned(16))) u64 sm[];
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = blockDim.x >> 6, rows = a.logN - 8, t = threadIdx.x & 63u;
     const uint32_t item = blockIdx.x >> 3, un = item / a.J, job = item - un * a.J;
     const uint32_t u = un * 8 + (blockIdx.x & 7u), r = u >> rows, b = u & ((1u << rows) - 1u);
-    const uint32_t bits = mod_const(a.mc, SP ? a.nq + r : r).bits;
-    if (bits <= 54) ks_row_group<0, SP, SUM>(a, job, kr_pin<0>(r), b, wave, nw, t, sm);
-    else if (bits <= 57) ks_row_group<1, SP, SUM>(a, job, kr_pin<1>(r), b, wave, nw, t, sm);
-    else ks_row_group<2, SP, SUM>(a, job, kr_pin<2>(r), b, wave, nw, t, sm);
+    const uint32_t width = kr_width(a, SP ? a.nq + r : r);
+    if (width == 0) ks_row_group<0, SP, SUM, DONE>(a, job, kr_pin<0>(r), b, wave, nw, t, sm);
+    else if (width == 1) ks_row_group<1, SP, SUM, DONE>(a, job, kr_pin<1>(r), b, wave, nw, t, sm);
+    else ks_row_group<2, SP, SUM, DONE>(a, job, kr_pin<2>(r), b, wave, nw, t, sm);
 }
 
 int32_t launch_ks_rows(he_ctx* ctx, KsRows& a, bool special) {
@@ -380,28 +484,43 @@ int32_t launch_ks_rows(he_ctx* ctx, KsRows& a, bool special) {
         a.beta == 0 || a.beta > 8 || ctx->logN < 13 || ctx->logN > 17 || limbs == 0 || limbs > HE_MAX_MODULI)
         return he_fail(ctx, HE_ERR_BADARG, "key-switch rows: bad shape");
     a.mc = ctx->d_mc; a.tw = ctx->d_tw; a.itw = ctx->d_itw; a.logN = ctx->logN;
+    a.above54 = a.above57 = 0;
+    for (uint32_t i = 0; i < ctx->M; i++) {
+        a.above54 |= (u64)(ctx->h_mc[i].bits > 54) << i;
+        a.above57 |= (u64)(ctx->h_mc[i].bits > 57) << i;
+    }
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (ctx->prof_on) {
         HE_HIP(ctx, hipEventCreate(&e0));
         HE_HIP(ctx, hipEventCreate(&e1));
         HE_HIP(ctx, hipEventRecord(e0, ctx->stream));
     }
-    const bool group = a.sum || units * a.J <= KR_GROUP_ROWS;
-    const uint32_t nw = group ? std::max(2u, std::min<uint32_t>(KR_WAVES, a.sum ? a.n_terms : a.beta)) : KR_WAVES;
-    const dim3 grid(group ? units * a.J : 8 * ((units / 8 * a.J + KR_WAVES - 1) / KR_WAVES)), block(64 * nw);
-    const size_t lds = (size_t)nw * 256 * std::max(a.beta, 2u) * sizeof(u64);       // at most 64 KiB
+    const uint32_t n_rows = units * a.J;
     const bool many = a.beta > KS_ROW_PRODUCTS;
-#define KR_LAUNCH(K) hipLaunchKernelGGL(K, grid, block, lds, ctx->stream, a)
-    if (a.sum) { if (special) KR_LAUNCH((ks_rows_group_kernel<true, true>)); else KR_LAUNCH((ks_rows_group_kernel<false, true>)); }
-    else if (group) { if (special) KR_LAUNCH((ks_rows_group_kernel<true, false>)); else KR_LAUNCH((ks_rows_group_kernel<false, false>)); }
-    else if (many) { if (special) KR_LAUNCH((ks_rows_kernel<true, true>)); else KR_LAUNCH((ks_rows_kernel<false, true>)); }
-    else { if (special) KR_LAUNCH((ks_rows_kernel<true, false>)); else KR_LAUNCH((ks_rows_kernel<false, false>)); }
-#undef KR_LAUNCH
+    const bool group = a.sum || (!a.done && n_rows <= KR_GROUP_ROWS), half = !a.sum && a.done && !many && n_rows <= KR_HALF_ROWS;
+    const uint32_t nw = group ? std::max(2u, std::min<uint32_t>(KR_WAVES, a.sum ? a.n_terms : a.beta)) : KR_WAVES;
+    const dim3 grid(group ? n_rows : 8 * ((n_rows / 8 * (half ? 2 : 1) + KR_WAVES - 1) / KR_WAVES)), block(64 * nw);
+    const size_t lds = half ? 0 : (size_t)nw * 256 * (a.done ? 2u : std::max(a.beta, 2u)) * sizeof(u64);       // at most 64 KiB
+#define KR_LAUNCH(...) hipLaunchKernelGGL((__VA_ARGS__), grid, block, lds, ctx->stream, a)
+#define KR_DISPATCH(SP)                                                                                                             \
+    do {                                                                                                                            \
+        if (a.sum && a.done) KR_LAUNCH(ks_rows_group_kernel<SP, true, true>);                                                       \
+        else if (a.sum) KR_LAUNCH(ks_rows_group_kernel<SP, true, false>);                                                           \
+        else if (half) KR_LAUNCH(ks_rows_half_kernel<SP>);                                                                          \
+        else if (group) KR_LAUNCH(ks_rows_group_kernel<SP, false, false>);                                                          \
+        else if (many && a.done) KR_LAUNCH(ks_rows_kernel<SP, true, true>);                                                         \
+        else if (many) KR_LAUNCH(ks_rows_kernel<SP, true, false>);                                                                  \
+        else if (a.done) KR_LAUNCH(ks_rows_kernel<SP, false, true>);                                                                \
+        else KR_LAUNCH(ks_rows_kernel<SP, false, false>);                                                                           \
+    } while (0)
+    if (special) KR_DISPATCH(true);
+    else KR_DISPATCH(false);
     HE_HIP(ctx, hipGetLastError());
-    const uint32_t digits = (a.sum ? a.n_terms : a.J) * (special ? a.beta * a.k : (a.beta - 1) * a.L1), sums = 2 * a.J * limbs;
+    const uint32_t sources = a.sum ? a.n_terms : a.J, sums = 2 * a.J * limbs;
+    const uint32_t digits = a.done ? 0 : sources * (special ? a.beta * a.k : (a.beta - 1) * a.L1);      // transformed here
     if (ctx->prof_on) {
         HE_HIP(ctx, hipEventRecord(e1, ctx->stream));
-        ctx->prof_events.push_back({e0, e1, digits + sums, 0u, special ? 4u : 2u});
+        ctx->prof_events.push_back({e0, e1, digits + sums, a.done ? sources * a.beta * limbs : 0u, special ? 4u : 2u});
     }
     // transforms whose column pass was a launch of its own are counted there
     if (a.count_up) ctx->cnt.ntt_limbs += digits;

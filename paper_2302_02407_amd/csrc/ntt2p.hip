@@ -227,178 +227,13 @@ __global__ __launch_bounds__(P2_THREADS, LC == 9 ? 3 : 4) void ntt_col_inv_kerne
     else col_inv<LC, CUSTOM_SCALE, false>(a, branch_pin<false>(e), tile, sm, sc, scale_period);
 }
 
-// ---------------------------------------------------------------- key-switch inner products inside the row passes
-// sum over the digits of digit_j (gathered by the Galois map) * key_j for adjacent pairs of positions.  An aligned pair of
-// positions comes from an aligned pair, in order or swapped, so a digit's two values are one 16-byte load; they are
-// multiplied in the order they arrive ("slots": slot s belongs to output position pos + (s ^ swap)) and the key is read in
-// that order.  Products go into split sums (modarith.h).  Digits are below 2q for moduli of at most 57 bits and canonical
-// above, keys canonical: SPLIT_MAX products fit, 15 for the narrow moduli.
-// What one (polynomial, key) term contributes to a limb: base pointers of the digits and keys of this limb.
-struct IpTerm {
-    const u64 *raised, *own, *key;                       // own: digit own_j's limb, which is not materialised in raised
-    uint32_t own_j, g;
-};
-// Two pairs of positions (4 points) of a row: positions row0 + e and row0 + e + DP, where DP = 2 * (lanes that share the row)
-// and a thread has 128 / DP such chunks.
-template <int NJ>
-struct IpLoad {
-    ulonglong2 d[NJ][2];
-    u64 k[NJ][2][2];
-};
-template <int DP>
-__device__ __forceinline__ void ip_map(uint32_t (&src)[2], uint32_t (&swp)[2], uint32_t pos, uint32_t g, uint32_t logN) {
-#pragma unroll
-    for (int p = 0; p < 2; p++) {
-        const uint32_t s = galois_pos(pos + DP * p, g, logN);
-        src[p] = s & ~1u;
-        swp[p] = s & 1u;
-    }
-}
-template <int DP, int NJ>
-__device__ __forceinline__ void ip_request(IpLoad<NJ>& L, const IpTerm& tm, uint32_t j0, uint32_t nj, uint32_t pos, const uint32_t (&src)[2],
-                                           const uint32_t (&swp)[2], size_t dig_stride, size_t key_stride) {
-#pragma unroll
-    for (int jj = 0; jj < NJ; jj++) {
-        if ((uint32_t)jj < nj) {
-            const uint32_t j = j0 + jj;
-            const u64* dj = j == tm.own_j ? tm.own : tm.raised + j * dig_stride;
-            const u64* kj = tm.key + j * key_stride;
-#pragma unroll
-            for (int p = 0; p < 2; p++) {
-                L.d[jj][p] = LOAD2(dj + src[p]);
-                const uint32_t kp = (pos + DP * p) | swp[p];
-                L.k[jj][p][0] = kj[kp];
-                L.k[jj][p][1] = kj[kp ^ 1u];
-            }
-        }
-    }
-}
-template <int NJ>
-__device__ __forceinline__ void ip_consume(SplitSum (&s)[4], const IpLoad<NJ>& L, uint32_t nj) {
-#pragma unroll
-    for (int jj = 0; jj < NJ; jj++) {
-        if ((uint32_t)jj < nj) {
-#pragma unroll
-            for (int p = 0; p < 2; p++) {
-                split_mac(s[2 * p], L.d[jj][p].x, L.k[jj][p][0]);
-                split_mac(s[2 * p + 1], L.d[jj][p].y, L.k[jj][p][1]);
-            }
-        }
-    }
-}
-// the two slots of a pair in position order
-__device__ __forceinline__ ulonglong2 ip_order(u64 v0, u64 v1, uint32_t swp) {
-    return swp ? make_ulonglong2(v1, v0) : make_ulonglong2(v0, v1);
-}
-
-// The inner product of a row for one job: chunks of 4 points per thread, the next chunk's operands requested before this
-// chunk's products.  BETA = 1, 2, 3: exactly that many digits; 0: any number up to 8, three at a time.  emit(chunk, pos, sums
-// below 6q in slot order, swaps).
-template <int DP, int BETA, class Emit>
-__device__ __forceinline__ void ip_row(const IpTerm& tm, uint32_t beta, uint32_t row0, uint32_t t, uint32_t logN, size_t dig_stride,
-                                       size_t key_stride, const ModConst& m, Emit&& emit) {
-    constexpr int NJ = BETA ? BETA : 3, NCH = 128 / DP;
-    uint32_t src[2], swp[2];
-    if (BETA) {
-        IpLoad<NJ> cur, nxt;
-        ip_map<DP>(src, swp, row0 + 2 * t, tm.g, logN);
-        ip_request<DP>(cur, tm, 0, NJ, row0 + 2 * t, src, swp, dig_stride, key_stride);
-#pragma unroll
-        for (int ch = 0; ch < NCH; ch++) {
-            const uint32_t pos = row0 + 2 * t + 2 * DP * ch;
-            uint32_t nsrc[2] = {0, 0}, nswp[2] = {0, 0};
-            if (ch + 1 < NCH) {
-                ip_map<DP>(nsrc, nswp, pos + 2 * DP, tm.g, logN);
-                ip_request<DP>(nxt, tm, 0, NJ, pos + 2 * DP, nsrc, nswp, dig_stride, key_stride);
-            }
-            SCHED_FENCE();
-            SplitSum s[4] = {};
-            ip_consume(s, cur, NJ);
-            u64 v[4];
-            split_reduce(v, s, m);
-            emit(ch, pos, v, src, swp);
-            if (ch + 1 < NCH) {
-                cur = nxt;
-#pragma unroll
-                for (int p = 0; p < 2; p++) { src[p] = nsrc[p]; swp[p] = nswp[p]; }
-            }
-        }
-    } else {
-#pragma unroll
-        for (int ch = 0; ch < 128 / DP; ch++) {
-            const uint32_t pos = row0 + 2 * t + 2 * DP * ch;
-            ip_map<DP>(src, swp, pos, tm.g, logN);
-            SplitSum s[4] = {};
-            u64 v[4] = {0, 0, 0, 0};
-            for (uint32_t j0 = 0; j0 < beta; j0 += NJ) {
-                IpLoad<NJ> L;
-                const uint32_t nj = beta - j0 < NJ ? beta - j0 : NJ;
-                ip_request<DP>(L, tm, j0, nj, pos, src, swp, dig_stride, key_stride);
-                if (j0 == 6) {                           // seven products at most in one sum
-                    split_reduce(v, s, m);
-#pragma unroll
-                    for (int i = 0; i < 4; i++) s[i] = SplitSum{0, 0, 0};
-                }
-                ip_consume(s, L, nj);
-            }
-            u64 last[4];
-            split_reduce(last, s, m);
-#pragma unroll
-            for (int i = 0; i < 4; i++) v[i] = beta > 6 ? reduce_lazy<7>(v[i] + last[i], m.q, m.bits, m.rec) : last[i];
-            emit(ch, pos, v, src, swp);
-        }
-    }
-}
-// The same for the sum over n_terms terms (a sum of rotations with one ModDown); term(i) describes term i.
-template <int DP, class Term, class Emit>
-__device__ __forceinline__ void ip_row_terms(Term&& term, uint32_t n_terms, uint32_t beta, uint32_t row0, uint32_t t, uint32_t logN,
-                                             size_t dig_stride, size_t key_stride, const ModConst& m, Emit&& emit) {
-    const uint32_t most = m.bits > 57 ? SPLIT_MAX : 15;
-#pragma unroll 1
-    for (int ch = 0; ch < 128 / DP; ch++) {
-        const uint32_t pos = row0 + 2 * t + 2 * DP * ch;
-        u64 tot[4] = {0, 0, 0, 0};                       // in position order
-        for (uint32_t i = 0; i < n_terms; i++) {
-            const IpTerm tm = term(i);
-            uint32_t src[2], swp[2], pending = 0;
-            ip_map<DP>(src, swp, pos, tm.g, logN);
-            SplitSum s[4] = {};
-            auto flush = [&]() {
-                u64 sv[4];
-                split_reduce(sv, s, m);
-#pragma unroll
-                for (int p = 0; p < 2; p++) {
-                    const ulonglong2 v = ip_order(sv[2 * p], sv[2 * p + 1], swp[p]);
-                    tot[2 * p] = reduce_lazy<7>(tot[2 * p] + v.x, m.q, m.bits, m.rec);
-                    tot[2 * p + 1] = reduce_lazy<7>(tot[2 * p + 1] + v.y, m.q, m.bits, m.rec);
-                    s[2 * p] = s[2 * p + 1] = SplitSum{0, 0, 0};
-                }
-                pending = 0;
-            };
-            for (uint32_t j0 = 0; j0 < beta; j0 += 3) {
-                IpLoad<3> L;
-                const uint32_t nj = beta - j0 < 3 ? beta - j0 : 3;
-                ip_request<DP>(L, tm, j0, nj, pos, src, swp, dig_stride, key_stride);
-                if (pending + nj > most) flush();
-                ip_consume(s, L, nj);
-                pending += nj;
-            }
-            flush();
-        }
-        const uint32_t src[2] = {pos, pos + DP}, swp[2] = {0, 0};
-        emit(ch, pos, tot, src, swp);
-    }
-}
-
 // ---------------------------------------------------------------- forward row pass
 // Pass B: workgroup = 16 consecutive rows (256-point blocks); tid = blk*16 + t.  A row stays inside 16 lanes of one wavefront,
 // so its exchanges need no barrier and the wavefronts run apart.
-// EPI: 0 = plain transform; 1 = ModDown epilogue with the accumulator read from memory; 2 = ModDown epilogue that also
-// computes the accumulator (the key-switch inner product of this limb) from the raised digits and the key, so that the
-// q-limbs of the accumulator never exist in memory (BETA as in ip_row); 3 = the same for a sum over several terms.
+// EPI: whether the pass ends in the ModDown (or Rescale) epilogue, with the accumulator read from memory.
 // LANES: threads that share a row, 16 points each in two register blocks of four stages or, for small launches, 4 points each
 // in four blocks of two (see launch_transform2p).
-template <bool WIDE, int EPI, int BETA, int LANES>
+template <bool WIDE, bool EPI, int LANES>
 __device__ __forceinline__ void row_fwd(const P2Args& a, uint32_t e, uint32_t tile, u64* sm, const ModDownEpilogue& ep) {
     const uint32_t mi = tab_mod(e), limb = tab_dst(e), logN = a.logN, lc = logN - 8;
     const ulonglong2* tw = a.tw + ((size_t)mi << logN);
@@ -437,7 +272,7 @@ __device__ __forceinline__ void row_fwd(const P2Args& a, uint32_t e, uint32_t ti
         tw_row4(w, tw, lc, b, t);
         row4_fwd<WIDE, 1>(reinterpret_cast<u64 (&)[1][4]>(x), w, s, 272, Row4(t), q);
     }
-    if (EPI == 0) {
+    if (!EPI) {
         if (!WIDE && a.lazy) {
 #pragma unroll
             for (int j = 0; j < PTS; j++) x[j] = reduce_lazy<7>(x[j], q, m.bits, m.rec);
@@ -485,76 +320,45 @@ __device__ __forceinline__ void row_fwd(const P2Args& a, uint32_t e, uint32_t ti
     const u64* c0 = has_c0 ? c0p + ro : nullptr;
     const u64* self = has_self ? sp + ro : nullptr;
     wave_exchange();
-    // v: accumulator values in slot order, below 6q
-    auto emit = [&](int ch, uint32_t pos, const u64 (&v)[4], const uint32_t (&src)[2], const uint32_t (&swp)[2]) {
-        ulonglong2 cv[2], sv[2];
+    const u64* acc = ep.acc + ((size_t)(pc * ep.R + r) << logN);
+    const uint32_t g = ep.g[job];
+    // an aligned pair of positions takes its rotated addends from an aligned pair, in order or swapped: one 16-byte load
+    ulonglong2 av[PTS / 2];
 #pragma unroll
-        for (int p = 0; p < 2; p++) {
-            cv[p] = has_c0 ? LOAD2(c0 + src[p]) : make_ulonglong2(0, 0);
-            sv[p] = has_self ? LOAD2(self + pos + DP * p) : make_ulonglong2(0, 0);
+    for (int p = 0; p < PTS / 2; p++) av[p] = LOAD2(acc + row0 + 2 * t + DP * p);
+#pragma unroll
+    for (int p = 0; p < PTS / 2; p++) {
+        const uint32_t pos = row0 + 2 * t + DP * p, e = pos - row0, l = e + (e >> 4);
+        ulonglong2 add = has_self ? LOAD2(self + pos) : make_ulonglong2(0, 0);
+        if (has_c0) {
+            const uint32_t src = g == 1 ? pos : galois_pos(pos, g, logN);
+            const ulonglong2 c = LOAD2(c0 + (src & ~1u));
+            add.x += src & 1u ? c.y : c.x;
+            add.y += src & 1u ? c.x : c.y;
         }
-#pragma unroll
-        for (int p = 0; p < 2; p++) {
-            const uint32_t e = pos - row0 + DP * p, l = e + (e >> 4);
-            const ulonglong2 acc = ip_order(v[2 * p], v[2 * p + 1], swp[p]), c = ip_order(cv[p].x, cv[p].y, swp[p]);
-            ulonglong2 o;
-            o.x = shoup_acc(c.x + sv[p].x, acc.x + bias - s[l], pinv, pinv_sh, q);
-            o.y = shoup_acc(c.y + sv[p].y, acc.y + bias - s[l + 1], pinv, pinv_sh, q);
-            o.x = reduce_full<7>(o.x, q, m.bits, m.rec);
-            o.y = reduce_full<7>(o.y, q, m.bits, m.rec);
-            STORE2(out + pos + DP * p) = o;
-        }
-    };
-    const size_t dig_stride = (size_t)ep.R << logN, key_stride = (size_t)(2 * ep.M) << logN;
-    const size_t ko = (size_t)(comp * ep.M + r) << logN;
-    if (EPI == 1) {
-        const u64* acc = ep.acc + ((size_t)(pc * ep.R + r) << logN);
-        const uint32_t g = ep.g[job];
-        ulonglong2 av[PTS / 2];
-#pragma unroll
-        for (int p = 0; p < PTS / 2; p++) av[p] = LOAD2(acc + row0 + 2 * t + DP * p);
-#pragma unroll
-        for (int ch = 0; ch < PTS / 4; ch++) {
-            const uint32_t pos = row0 + 2 * t + 2 * DP * ch;
-            uint32_t src[2] = {pos, pos + DP}, swp[2] = {0, 0};
-            u64 v[4] = {av[2 * ch].x, av[2 * ch].y, av[2 * ch + 1].x, av[2 * ch + 1].y};
-            if (has_c0 && g != 1) {                      // accumulator values into slot order
-                ip_map<DP>(src, swp, pos, g, logN);
-#pragma unroll
-                for (int p = 0; p < 2; p++) {
-                    const ulonglong2 o = ip_order(v[2 * p], v[2 * p + 1], swp[p]);
-                    v[2 * p] = o.x; v[2 * p + 1] = o.y;
-                }
-            }
-            emit(ch, pos, v, src, swp);
-        }
-    } else if (EPI == 2) {
-        const IpTerm tm = {ep.raised[job] + ro, ep.own[job] + ro, ep.evk[job] + ko, r / ep.alpha, ep.g[job]};
-        ip_row<DP, BETA>(tm, ep.beta, row0, t, logN, dig_stride, key_stride, m, emit);
-    } else {
-        ip_row_terms<DP>([&](uint32_t i) { return IpTerm{ep.raised[i] + ro, ep.own[i] + ro, ep.evk[i] + ko, r / ep.alpha, ep.g[i]}; }, ep.n_terms,
-                     ep.beta, row0, t, logN, dig_stride, key_stride, m, emit);
+        ulonglong2 o;
+        o.x = reduce_full<7>(shoup_acc(add.x, av[p].x + bias - s[l], pinv, pinv_sh, q), q, m.bits, m.rec);
+        o.y = reduce_full<7>(shoup_acc(add.y, av[p].y + bias - s[l + 1], pinv, pinv_sh, q), q, m.bits, m.rec);
+        STORE2(out + pos) = o;
     }
 }
 
-template <int EPI, int BETA, int LANES>
-__global__ __launch_bounds__(P2_THREADS, EPI == 3 || (LANES == 16 && EPI >= 2) ? 3 : 4) void ntt_row_fwd_kernel(P2Args a, LimbTab tab, ModDownEpilogue ep) {
+template <bool EPI, int LANES>
+__global__ __launch_bounds__(P2_THREADS, 4) void ntt_row_fwd_kernel(P2Args a, LimbTab tab, ModDownEpilogue ep) {
     __shared__ alignas(16) u64 sm[P2_THREADS / LANES * 272];         // 16 groups of 17: conflict-free both ways
     uint32_t tile;
     const uint32_t e = row_decode<LANES>(tab, a, tile);
     if (e == TAB_NONE) return;
-    if (e & TAB_WIDE) row_fwd<true, EPI, BETA, LANES>(a, branch_pin<true>(e), tile, sm, ep);
-    else row_fwd<false, EPI, BETA, LANES>(a, branch_pin<false>(e), tile, sm, ep);
+    if (e & TAB_WIDE) row_fwd<true, EPI, LANES>(a, branch_pin<true>(e), tile, sm, ep);
+    else row_fwd<false, EPI, LANES>(a, branch_pin<false>(e), tile, sm, ep);
 }
 
 // ---------------------------------------------------------------- inverse row pass
 // Stages LC+7 .. LC+4 on contiguous points, exchange, stages LC+3 .. LC on strided points: inputs canonical, results below
 // 4q.  Narrow moduli: bounds 1 -> 32 after the first block, -> 512 after the second, one quotient step at the end.
-// With IP the inputs are not read: they are the key-switch inner product of the special-prime limbs, computed here from the
-// raised digits and the key.  IP: 0 = none, 1 = one job per limb (BETA as in ip_row), 2 = a sum over several terms.
 // LANES as in row_fwd.
-template <bool WIDE, int IP, int BETA, int LANES>
-__device__ __forceinline__ void row_inv(const P2Args& a, const LimbTab& tab, uint32_t e, uint32_t tile, u64* sm, const IpPrologue& ip) {
+template <bool WIDE, int LANES>
+__device__ __forceinline__ void row_inv(const P2Args& a, const LimbTab& tab, uint32_t e, uint32_t tile, u64* sm) {
     const uint32_t mi = tab_mod(e), limb = tab_dst(e), logN = a.logN, lc = logN - 8;
     const ModConst m = a.mc[mi];
     const ulonglong2* tw = a.tw + ((size_t)mi << logN);
@@ -564,48 +368,21 @@ __device__ __forceinline__ void row_inv(const P2Args& a, const LimbTab& tab, uin
     u64* s = sm + blk * 272;
     u64 x[PTS], w4[4][6];                                // w4: LANES == 64
     ulonglong2 w2[15];                                   // LANES == 16
-    auto factors = [&]() {
-        if constexpr (LANES == 16) tw_load_last<0, 4>(w2, tw, lc + 4, 16 * b + t);
-        else tw_row4(w4, tw, lc, b, t);
-    };
-    if (IP == 0) {
-        const u64* in = tab_src(tab, e, logN) + (size_t)b * 256;
-        if constexpr (LANES == 16) {
+    const u64* in = tab_src(tab, e, logN) + (size_t)b * 256;
+    if constexpr (LANES == 16) {
 #pragma unroll
-            for (int k = 0; k < 16; k++) x[k] = in[t + 16 * k];
-            factors();
-            SCHED_FENCE();
+        for (int k = 0; k < 16; k++) x[k] = in[t + 16 * k];
+        tw_load_last<0, 4>(w2, tw, lc + 4, 16 * b + t);
+        SCHED_FENCE();
 #pragma unroll
-            for (int k = 0; k < 16; k++) s[t + 17 * k] = x[k];
-        } else {
-            const ulonglong2 v = LOAD2(in + 2 * t), u = LOAD2(in + 128 + 2 * t);
-            factors();
-            *reinterpret_cast<ulonglong2*>(s + row4_word(2 * t)) = v;
-            *reinterpret_cast<ulonglong2*>(s + row4_word(128 + 2 * t)) = u;
-            wave_exchange();
-            Row4(t).load(3, x, s);
-        }
+        for (int k = 0; k < 16; k++) s[t + 17 * k] = x[k];
     } else {
-        const uint32_t pc = limb / ip.k, tp = limb - pc * ip.k, job = pc >> 1, comp = pc & 1u, row0 = b * 256;
-        const size_t dig_stride = (size_t)ip.R << logN, key_stride = (size_t)(2 * ip.M) << logN;
-        const size_t ro = (size_t)(ip.L1 + tp) << logN, ko = (size_t)(comp * ip.M + ip.nq + tp) << logN;
-        auto emit = [&](int, uint32_t pos, const u64 (&v)[4], const uint32_t (&)[2], const uint32_t (&swp)[2]) {
-#pragma unroll
-            for (int p = 0; p < 2; p++) {
-                const uint32_t at = pos - row0 + DP * p, l = at + (at >> 4);
-                const ulonglong2 o = ip_order(v[2 * p], v[2 * p + 1], swp[p]);
-                s[l] = reduce_full<7>(o.x, m.q, m.bits, m.rec);
-                s[l + 1] = reduce_full<7>(o.y, m.q, m.bits, m.rec);
-            }
-        };
-        if (IP == 1) {
-            const IpTerm tm = {ip.raised[job] + ro, nullptr, ip.evk[job] + ko, 0xFFFFFFFFu, ip.g[job]};
-            ip_row<DP, BETA>(tm, ip.beta, row0, t, logN, dig_stride, key_stride, m, emit);
-        } else {
-            ip_row_terms<DP>([&](uint32_t i) { return IpTerm{ip.raised[i] + ro, nullptr, ip.evk[i] + ko, 0xFFFFFFFFu, ip.g[i]}; }, ip.n_terms, ip.beta,
-                         row0, t, logN, dig_stride, key_stride, m, emit);
-        }
-        factors();
+        const ulonglong2 v = LOAD2(in + 2 * t), u = LOAD2(in + 128 + 2 * t);
+        tw_row4(w4, tw, lc, b, t);
+        *reinterpret_cast<ulonglong2*>(s + row4_word(2 * t)) = v;
+        *reinterpret_cast<ulonglong2*>(s + row4_word(128 + 2 * t)) = u;
+        wave_exchange();
+        Row4(t).load(3, x, s);
     }
     const u64 q = uni64(m.q);
     if constexpr (LANES == 16) {
@@ -640,26 +417,20 @@ __device__ __forceinline__ void row_inv(const P2Args& a, const LimbTab& tab, uin
 #pragma unroll
         for (int k = 0; k < 16; k++) out[t + 16 * k] = x[k];
     } else {
-        if (IP) {
-            wave_exchange();
-#pragma unroll
-            for (int k = 0; k < 4; k++) x[k] = s[4 * row4_last(t) + k + (row4_last(t) >> 2)];
-            wave_exchange();
-        }
         row4_inv<WIDE, 1>(reinterpret_cast<u64 (&)[1][4]>(x), w4, s, 272, Row4(t), q, m);
 #pragma unroll
         for (int k = 0; k < 4; k++) out[t + 64 * k] = x[k];
     }
 }
 
-template <int IP, int BETA, int LANES>
-__global__ __launch_bounds__(P2_THREADS, LANES == 16 && IP ? 3 : 4) void ntt_row_inv_kernel(P2Args a, LimbTab tab, IpPrologue ip) {
+template <int LANES>
+__global__ __launch_bounds__(P2_THREADS, 4) void ntt_row_inv_kernel(P2Args a, LimbTab tab) {
     __shared__ alignas(16) u64 sm[P2_THREADS / LANES * 272];
     uint32_t tile;
     const uint32_t e = row_decode<LANES>(tab, a, tile);
     if (e == TAB_NONE) return;
-    if (e & TAB_WIDE) row_inv<true, IP, BETA, LANES>(a, tab, branch_pin<true>(e), tile, sm, ip);
-    else row_inv<false, IP, BETA, LANES>(a, tab, branch_pin<false>(e), tile, sm, ip);
+    if (e & TAB_WIDE) row_inv<true, LANES>(a, tab, branch_pin<true>(e), tile, sm);
+    else row_inv<false, LANES>(a, tab, branch_pin<false>(e), tile, sm);
 }
 
 // ---------------------------------------------------------------- row passes of several limbs of one modulus
@@ -877,17 +648,6 @@ int32_t probe_butterfly_rates(he_ctx* ctx, u64* d_out, uint32_t groups, double r
     case 8: hipLaunchKernelGGL((K<8, SECOND>), __VA_ARGS__); break;                                                  \
     default: hipLaunchKernelGGL((K<9, SECOND>), __VA_ARGS__); break;                                                 \
     }
-#define ROW_DISPATCH(K, FIRST, BETA_, ...)                                                                        \
-    if (wide_rows) hipLaunchKernelGGL((K<FIRST, BETA_, 64>), grid_rows, block, 0, ctx->stream, a, tab, __VA_ARGS__);  \
-    else hipLaunchKernelGGL((K<FIRST, BETA_, 16>), grid_rows, block, 0, ctx->stream, a, tab, __VA_ARGS__);
-#define BETA_DISPATCH(K, FIRST, BETA_, ...)                                                                       \
-    switch (BETA_) {                                                                                                 \
-    case 1: ROW_DISPATCH(K, FIRST, 1, __VA_ARGS__) break;                                                            \
-    case 2: ROW_DISPATCH(K, FIRST, 2, __VA_ARGS__) break;                                                            \
-    case 3: ROW_DISPATCH(K, FIRST, 3, __VA_ARGS__) break;                                                            \
-    default: ROW_DISPATCH(K, FIRST, 0, __VA_ARGS__) break;                                                           \
-    }
-
 int32_t launch_transform2p(he_ctx* ctx, const TransformDesc& d) {
     const uint32_t n = d.n, logN = ctx->logN;
     const bool fwd = d.fwd;
@@ -945,10 +705,8 @@ int32_t launch_transform2p(he_ctx* ctx, const TransformDesc& d) {
     // times the wavefronts.  One rotation at level 5: 65 us with 16 threads, 55 with 64; at level 11 of N = 2^15 70 and 57.
     // With the line at 2048 two rotations at level 11 take 131.5 us instead of 129.1 and one at level 20 of the six-digit
     // set 187 instead of 182; at 8192 a block of layers takes 1255 instead of 1251, at 16384 that rotation 186 again.  Eight
-    // at level 5 take 220 instead of 215 because their smallest launch falls under the line.  A sum of several terms is
-    // always one output's limbs, each with a long chain of its own.
-    const bool terms = (d.ep && d.ep->fused && d.ep->n_terms) || (d.ip && d.ip->n_terms);
-    const bool wide_rows = terms || live * (ctx->N >> 10) <= 4096;
+    // at level 5 take 220 instead of 215 because their smallest launch falls under the line. 
+    const bool wide_rows = live * (ctx->N >> 10) <= 4096;
     const dim3 block(P2_THREADS), grid_cols(live * tiles), grid_rows(padded * tiles * (wide_rows ? 4 : 1));
     for (int pass = 0; pass < 2; pass++) {
         if (d.only_pass && d.only_pass != (uint32_t)pass + 1) continue;
@@ -962,17 +720,17 @@ int32_t launch_transform2p(he_ctx* ctx, const TransformDesc& d) {
             if (d.rescale_from) { COL_DISPATCH(ntt_col_fwd_kernel, true, grid_cols, block, 0, ctx->stream, a, tab) }
             else { COL_DISPATCH(ntt_col_fwd_kernel, false, grid_cols, block, 0, ctx->stream, a, tab) }
         } else if (fwd) {
-            if (d.ep && d.ep->fused && d.ep->n_terms) hipLaunchKernelGGL((ntt_row_fwd_kernel<3, 0, 64>), grid_rows, block, 0, ctx->stream, a, tab, *d.ep);
-            else if (d.ep && d.ep->fused) { BETA_DISPATCH(ntt_row_fwd_kernel, 2, d.ep->beta, *d.ep) }
-            else if (d.ep) { ROW_DISPATCH(ntt_row_fwd_kernel, 1, 0, *d.ep) }
+            ModDownEpilogue none = {};
+            if (d.ep && wide_rows) hipLaunchKernelGGL((ntt_row_fwd_kernel<true, 64>), grid_rows, block, 0, ctx->stream, a, tab, *d.ep);
+            else if (d.ep) hipLaunchKernelGGL((ntt_row_fwd_kernel<true, 16>), grid_rows, block, 0, ctx->stream, a, tab, *d.ep);
             else if (by_runs && !wide_rows && a.lazy) hipLaunchKernelGGL((ntt_row_run_kernel<true, true>), dim3(n_runs * (ctx->N >> 10)), block, 0, ctx->stream, a, tab, runs);
             else if (by_runs && !wide_rows) hipLaunchKernelGGL((ntt_row_run_kernel<true, false>), dim3(n_runs * (ctx->N >> 10)), block, 0, ctx->stream, a, tab, runs);
-            else { ModDownEpilogue none = {}; ROW_DISPATCH(ntt_row_fwd_kernel, 0, 0, none) }
+            else if (wide_rows) hipLaunchKernelGGL((ntt_row_fwd_kernel<false, 64>), grid_rows, block, 0, ctx->stream, a, tab, none);
+            else hipLaunchKernelGGL((ntt_row_fwd_kernel<false, 16>), grid_rows, block, 0, ctx->stream, a, tab, none);
         } else if (pass == 0) {
-            if (d.ip && d.ip->n_terms) hipLaunchKernelGGL((ntt_row_inv_kernel<2, 0, 64>), grid_rows, block, 0, ctx->stream, a, tab, *d.ip);
-            else if (d.ip) { BETA_DISPATCH(ntt_row_inv_kernel, 1, d.ip->beta, *d.ip) }
-            else if (by_runs && !wide_rows) hipLaunchKernelGGL((ntt_row_run_kernel<false, false>), dim3(n_runs * (ctx->N >> 10)), block, 0, ctx->stream, a, tab, runs);
-            else { IpPrologue none = {}; ROW_DISPATCH(ntt_row_inv_kernel, 0, 0, none) }
+            if (by_runs && !wide_rows) hipLaunchKernelGGL((ntt_row_run_kernel<false, false>), dim3(n_runs * (ctx->N >> 10)), block, 0, ctx->stream, a, tab, runs);
+            else if (wide_rows) hipLaunchKernelGGL((ntt_row_inv_kernel<64>), grid_rows, block, 0, ctx->stream, a, tab);
+            else hipLaunchKernelGGL((ntt_row_inv_kernel<16>), grid_rows, block, 0, ctx->stream, a, tab);
         } else {
             if (d.scale) { COL_DISPATCH(ntt_col_inv_kernel, true, grid_cols, block, 0, ctx->stream, a, tab, *d.scale, d.scale_period) }
             else { ScaleList none; COL_DISPATCH(ntt_col_inv_kernel, false, grid_cols, block, 0, ctx->stream, a, tab, none, 1u) }
@@ -980,12 +738,8 @@ int32_t launch_transform2p(he_ctx* ctx, const TransformDesc& d) {
         HE_HIP(ctx, hipGetLastError());
         if (ctx->prof_on) {
             HE_HIP(ctx, hipEventRecord(e1, ctx->stream));
-            // the two components of a job share the gathered digit limbs: beta per pair of limbs
-            uint32_t dig = 0;
-            if (!fwd && pass == 0 && d.ip) dig = d.ip->beta * (live / 2);
-            if (fwd && pass == 1 && d.ep && d.ep->fused) dig = d.ep->beta * (live / 2);
-            const uint32_t kind = fwd ? (pass == 0 ? 0u : (d.ep ? 2u : 1u)) : (pass == 0 ? (d.ip ? 4u : 3u) : 5u);
-            ctx->prof_events.push_back({e0, e1, live, dig, kind});
+            const uint32_t kind = fwd ? (pass == 0 ? 0u : (d.ep ? 2u : 1u)) : (pass == 0 ? 3u : 5u);
+            ctx->prof_events.push_back({e0, e1, live, 0u, kind});
         }
     }
     if (fwd) ctx->cnt.ntt_limbs += live; else ctx->cnt.intt_limbs += live;

@@ -69,3 +69,51 @@ def test_one_job_sources(logN, q_bits, p_bits, nq, np_, dnum, levels, n_ct, fill
             ctx.he_rotate_sum(d_cts[:n] + [d_cts[0]], level, ts, out, deferred=True)
             want = orc.rotate_sum_deferred(cts[:n] + [cts[0]], level, [orc.galois_elt(s) for s in ts], [keys.get(s) for s in ts])
             assert (host(out) == want).all(), ("sum", level, n)
+
+
+@pytest.mark.parametrize("logN,q_bits,p_bits,nq,np_,dnum,levels,n_ct", [
+    (13, 30, 31, 4, 1, 4, (3, 0), 1),        # a wavefront to a component
+    (13, 54, 60, 8, 1, 8, (7, 4), 3),        # eight digits and five
+    (14, 58, 57, 6, 2, 3, (5, 2), 5),
+    (16, 54, 54, 3, 3, 2, (2,), 4),          # 9216 rows: a wavefront to both components
+    (16, 57, 55, 3, 3, 1, (2, 1), 4),
+    (16, 60, 60, 3, 3, 2, (2,), 4),
+    (17, 55, 58, 2, 2, 2, (1,), 4),
+])
+@pytest.mark.parametrize("fill", ["uniform", "extreme"])
+def test_shared_sources(logN, q_bits, p_bits, nq, np_, dnum, levels, n_ct, fill):
+    """Sources that serve three jobs, or several terms of one sum: the row kernels take digits that are transformed already."""
+    from gpu_util import dev, host, zeros
+    from oracle.he_oracle import Oracle
+    from paper_2302_02407_amd.binding import HEContext
+    q = primes_below(1 << q_bits, 2 << logN, nq)
+    p = primes_below(1 << p_bits, 2 << logN, np_, skip=q)
+    prm = HEParams(logN=logN, q=q, p=p, dnum=dnum, scale=2.0 ** 20, hamming=64, name="rows")
+    rng, orc, ctx = S.make_rng(700 + logN + q_bits), Oracle.from_params(prm), HEContext.from_params(prm)
+    N = prm.N
+    steps = [1, N // 4 + 3, N // 2 - 6]
+
+    def residues(moduli, n):
+        if fill == "uniform":
+            return S.uniform_limbs(rng, moduli, N, n)
+        top = np.array(moduli, dtype=np.uint64)[None, :, None] - np.uint64(1)
+        return np.where(rng.integers(0, 4, size=(n, len(moduli), N)) > 0, top, np.uint64(0))
+
+    keys = {s: residues(prm.moduli, 2 * dnum).reshape(dnum, 2, len(prm.moduli), N) for s in steps}
+    for s, k in keys.items():
+        ctx.he_evk_register(ctx.galois_elt(s), dev(k))
+    rot = lambda c, level, s: orc.rotate_from_raised(c, orc.modup(c[1], level), level, orc.galois_elt(s), keys[s])
+    for level in levels:
+        cts = [residues(prm.q[:level + 1], 2) for _ in range(n_ct)]
+        d_cts = [dev(c) for c in cts]
+        outs = [zeros(2, level + 1, N) for _ in range(3 * n_ct)]
+        ctx.he_rotate_batch(d_cts, level, steps, outs, hoisted=True)
+        for i in {0, n_ct - 1}:
+            for j, s in enumerate(steps):
+                assert (host(outs[3 * i + j]) == rot(cts[i], level, s)).all(), ("batch", level, i, s)
+        for n in {2, 3 * n_ct - 1}:
+            src, ts = [i // 3 for i in range(n)], [steps[i % 3] for i in range(n)]
+            out = zeros(2, level + 1, N)
+            ctx.he_rotate_sum([d_cts[i] for i in src], level, ts, out, deferred=True)
+            want = orc.rotate_sum_deferred([cts[i] for i in src], level, [orc.galois_elt(s) for s in ts], [keys[s] for s in ts])
+            assert (host(out) == want).all(), ("sum", level, n)
