@@ -233,6 +233,16 @@ struct ColConv {
     uint32_t parts, share;     // work groups that share a tile's targets, `share` targets each (set by the launch)
 };
 int32_t launch_col_conv(he_ctx* ctx, ColConv& cc, const ScaleList& sc, uint32_t reps, uint32_t limb_passes);
+// Column passes of Rescale (rescale.hip): src [n][N] holds the dropped limbs (modulus `level`) in the state the inverse row pass
+// leaves them, dst [n][level][N] receives the negated rounding terms in the state the forward column pass leaves them.
+struct RescaleCols {
+    const u64* src;
+    u64* dst;
+    uint32_t level, parts, share;      // work groups that share a tile's moduli, `share` each (set by the launch)
+    u64 wide;                          // bit per modulus: wide in the forward ranges
+};
+bool rescale_cols_pays(const he_ctx* ctx, uint32_t n, uint32_t level);
+int32_t launch_rescale_cols(he_ctx* ctx, const u64* src, u64* dst, uint32_t n, uint32_t level);
 // fills w / w_sh of entry i from s (modulus index mi)
 void scale_entry(const he_ctx* c, ScaleList& sc, uint32_t i, uint32_t mi, u64 s);
 int32_t launch_transform(he_ctx* ctx, const TransformDesc& d);

@@ -1337,7 +1337,10 @@ int32_t rescale_batch(he_ctx* ctx, const u64* const* cts, u64* const* outs, uint
             lim[2 * i] = (uint16_t)level; lim[2 * i + 1] = (uint16_t)(L1 + level);
         }
         t.mod_idx = mods.data(); t.src_seg = seg.data(); t.src_limb = lim.data();
+        const bool cols = rescale_cols_pays(ctx, 2 * nb, level);     // both column passes in one launch
+        t.only_pass = cols ? 1u : 0u;
         int32_t rc = launch_transform(ctx, t);
+        if (rc == HE_OK && cols) rc = launch_rescale_cols(ctx, tmp, delta, 2 * nb, level);
         if (rc != HE_OK) return rc;
         // forward transform of -delta, delta = h - ((t + h) mod q_l) with h = floor(q_l / 2), which the first pass forms from the dropped
         // limb's coefficients t as it reads them; its epilogue writes (c - (-delta)) * q_l^-1: the input limb plays the
@@ -1356,7 +1359,8 @@ int32_t rescale_batch(he_ctx* ctx, const u64* const* cts, u64* const* outs, uint
         TransformDesc f = {};
         f.fwd = true; f.seg[0] = tmp; f.n_seg = 1; f.src_limb = dsrc.data(); f.dst = delta; f.n = total; f.mod_idx = dm.data(); f.ep = &ep;
         f.lazy_out = true;
-        f.rescale_from = level + 1;
+        if (cols) f.only_pass = 2;
+        else f.rescale_from = level + 1;
         rc = launch_transform(ctx, f);
         if (rc != HE_OK) return rc;
         ctx->cnt.rescale += nb;
