@@ -18,6 +18,10 @@
 //
 // What bounds it is vector issue: 5965 instructions per wavefront for 8 + 24 limbs (counters), 4 cycles each, fill 0.68 of the
 // issue slots (2.4 GHz) of the benchmark's launches, which move 2.4 TB/s; wavefronts wait 0.45 of their cycles.
+// Small launches are chains: of 10.6 us of a work group (level 5, tiles of 256 points) 4.4 go by until a source is transformed, 2.3
+// while the slower wavefronts finish theirs, 2.3 until a round's operands are there and 1.6 in the conversion and the targets; its
+// SIMDs' issue slots are half full.  Asking for the round's list before the sources takes one rotation at level 5 from 57.3 to 56.8 us,
+// with six digits at level 6 from 61.0 to 59.6; asking for the operands themselves as well gave nothing.
 // A launch of the benchmark's single rotations went from 162 to 151 us once a round's operands came without dependent vector
 // loads and nothing was kept in scratch memory; it takes 147 now, 8.8 of the 23.4 ms of 240 rotations.
 #include <algorithm>
@@ -230,6 +234,9 @@ __global__ __launch_bounds__(CC_THREADS, 4) void col_conv_kernel(ColConv cc, Sca
     const uint32_t set = grp % cc.n_sets, rep = grp / cc.n_sets, c0 = tile << LCOLS;
     const ColConvSet& st = cc.set[set];
     u64* reg = lds + w * REGION;
+    const uint32_t tb = (gp - grp * cc.parts) * cc.share, nt = min(st.nt, tb + cc.share);
+    // the first round's list is asked for before the sources: everything else of the round waits for it
+    u64 mods_v = *reinterpret_cast<const u64*>(st.mod + tb), lims_v = *reinterpret_cast<const u64*>(st.limb + tb);
     if (w < st.ns) {
         const u64* src = st.src + (size_t)rep * cc.src_stride + ((size_t)w << (LC + 8));
         const uint32_t mi = st.mod0 + w;
@@ -248,14 +255,17 @@ __global__ __launch_bounds__(CC_THREADS, 4) void col_conv_kernel(ColConv cc, Sca
         const u64 y1 = 2 * g + 1 < st.ns ? lds[(2 * g + 1) * REGION + word] : 0;
         frag[b] = v4i{(int)(uint32_t)y0, (int)(uint32_t)(y0 >> 32), (int)(uint32_t)y1, (int)(uint32_t)(y1 >> 32)};
     }
-    const uint32_t tb = (gp - grp * cc.parts) * cc.share, nt = min(st.nt, tb + cc.share);
     uint32_t ln = lane;
     for (uint32_t t0 = tb; t0 < nt; t0 += CC_WAVES) {
         asm("" : "+v"(ln));                                  // what follows from the lane is worked out anew, not kept in registers
         const uint32_t g = ln >> 4, p16 = ln & 15;
         // operands of this round's eight targets, four (s) at a time: lane group g works on target t0 + 4s + g and this lane
         // supplies row lane % 16 = (target (lane % 16) / 4, digit lane % 4) of the left factor
-        const u64 mods = uni64(*reinterpret_cast<const u64*>(st.mod + t0)), lims = uni64(*reinterpret_cast<const u64*>(st.limb + t0));
+        if (t0 != tb) {
+            mods_v = *reinterpret_cast<const u64*>(st.mod + t0);
+            lims_v = *reinterpret_cast<const u64*>(st.limb + t0);
+        }
+        const u64 mods = uni64(mods_v), lims = uni64(lims_v);
         const uint32_t mod_first = (uint32_t)mods & 255u;
         v4i a0[2], a1[2], k0[2], k1[2];
         uint32_t n0[2], n1[2], rec[2], bits[2];
