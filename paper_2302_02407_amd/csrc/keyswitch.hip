@@ -394,10 +394,18 @@ static uint32_t moddown_most_jobs(const he_ctx* c, uint32_t level) {
     return std::max<uint32_t>(1, jb);
 }
 
+// The most jobs of the engine: where its row kernels and the column conversion do all of a ModDown no launch has a list of limbs.
+// Sixteen jobs a set at the benchmark's top level, where such a list holds ten (and one-job sources then go eight at a time): 240
+// rotations of 16 ciphertexts 19.0 ms instead of 19.5, 24 with six digits 2.59 instead of 2.66, 45 of 3 sources with six digits
+// 2.33 instead of 2.44.
+static uint32_t engine_most_jobs(const he_ctx* c, uint32_t level) {
+    return two_pass(c) && num_digits(c, level) <= 8 && c->d_dn_dig ? HE_MAX_KS_JOBS : moddown_most_jobs(c, level);
+}
+
 // How many sources are raised at once and how many jobs share one ModDown launch set.
 static void engine_shape(const he_ctx* c, uint32_t level, uint32_t n_src, uint32_t n_jobs, uint32_t& cb, uint32_t& jb) {
     cb = std::min<uint32_t>(std::min<uint32_t>(n_src, HE_MAX_SEGS), std::max<uint32_t>(1, HE_MAX_LAUNCH_LIMBS / (level + 1)));
-    jb = std::min<uint32_t>(n_jobs, moddown_most_jobs(c, level));
+    jb = std::min<uint32_t>(n_jobs, engine_most_jobs(c, level));
     // Sources that each serve one job come in launch sets as large as the jobs' where 16 jobs fit: smaller rings and lower
     // levels do not fill the chip with 8 (six ciphertexts by eight rotations at N = 2^14: 441 us with 8, 336 with 16; four by
     // seven at 2^15 755 and 693; nine by six at level 5 of N = 2^16 1489 and 1356).  The raised digits then take twice
@@ -576,10 +584,9 @@ static int32_t launch_inner_product(he_ctx* c, uint32_t level, const IpBatch& ib
     return HE_OK;
 }
 
-// The ModDown of J accumulators (each [2][R][N]; from N = 2^13 they are never stored and `ip` / `ep`
-// describe how the transforms compute them): special-prime limbs -> coefficient form (pre-multiplied by
+// The ModDown of J accumulators (each [2][R][N]): special-prime limbs -> coefficient form (pre-multiplied by
 // N^-1 * (P/p_t)^-1), conversion to q_0..q_level, forward transform with the epilogue described by `ep`.  With `rows` its
-// launches take the place of the row passes, and ip and ep say nothing.
+// launches take the place of the row passes, form the accumulators, which are not stored, and ep says nothing.
 static int32_t moddown_chain(he_ctx* c, uint32_t level, uint32_t J, u64* acc, u64* tmp_dn, u64* conv, const ModDownEpilogue& ep,
                              KsRows* rows = nullptr) {
     const uint32_t N = c->N, L1 = level + 1, k = c->np, R = L1 + k;
@@ -589,7 +596,12 @@ static int32_t moddown_chain(he_ctx* c, uint32_t level, uint32_t J, u64* acc, u6
         u64 p = c->mod[c->nq + t];
         scale_entry(c, sc, t, c->nq + t, h_mulmod(c->h_mc[c->nq + t].ninv, c->h_dn_invhat[t], p));
     }
-    {
+    int32_t rc = HE_OK;
+    if (rows) {
+        rows->mid = tmp_dn; rows->count_down = cc_on ? 1u : 0u;
+        rc = launch_ks_rows(c, *rows, true);
+    }
+    if (rc == HE_OK && !(rows && cc_on)) {
         const uint32_t n = J * 2 * k;
         std::vector<uint32_t> mods(n);
         std::vector<uint16_t> lim(n);
@@ -599,18 +611,12 @@ static int32_t moddown_chain(he_ctx* c, uint32_t level, uint32_t J, u64* acc, u6
             lim[i] = (uint16_t)(pc * R + L1 + t);
         }
         TransformDesc t = {};
-        t.fwd = false; t.seg[0] = acc; t.n_seg = 1; t.dst = tmp_dn; t.n = n;
-        t.mod_idx = mods.data(); t.src_limb = lim.data(); t.scale = &sc; t.scale_period = k;
-        t.only_pass = cc_on ? 1u : 0u;
-        int32_t rc = HE_OK;
-        if (rows) {
-            rows->mid = tmp_dn; rows->count_down = cc_on ? 1u : 0u;
-            rc = launch_ks_rows(c, *rows, true);
-            t.seg[0] = tmp_dn; t.src_limb = nullptr; t.only_pass = 2u;
-        }
-        if (rc == HE_OK && !(rows && cc_on)) rc = launch_transform(c, t);
-        if (rc != HE_OK) return rc;
+        t.fwd = false; t.seg[0] = rows ? tmp_dn : acc; t.n_seg = 1; t.dst = tmp_dn; t.n = n;
+        t.mod_idx = mods.data(); t.src_limb = rows ? nullptr : lim.data(); t.scale = &sc; t.scale_period = k;
+        t.only_pass = rows ? 2u : cc_on ? 1u : 0u;
+        rc = launch_transform(c, t);
     }
+    if (rc != HE_OK) return rc;
     if (cc_on) {
         ColConv cc = {};
         col_conv_widths(c, cc);
@@ -619,8 +625,7 @@ static int32_t moddown_chain(he_ctx* c, uint32_t level, uint32_t J, u64* acc, u6
         st.src = tmp_dn; st.dst = conv; st.digits = c->d_dn_dig; st.bias = c->d_dn_bias;
         st.ns = k; st.mod0 = c->nq; st.sc0 = 0; st.nt = L1;
         for (uint32_t r = 0; r < L1; r++) { st.limb[r] = (uint8_t)r; st.mod[r] = (uint8_t)r; }
-        int32_t rc = launch_col_conv(c, cc, sc, 2 * J, 2 * J * (k + L1));
-        if (rc != HE_OK) return rc;
+        rc = launch_col_conv(c, cc, sc, 2 * J, 2 * J * (k + L1));
     } else {
         ConvBatch b;
         b.njobs = 1; b.reps = 2 * J;
@@ -629,23 +634,20 @@ static int32_t moddown_chain(he_ctx* c, uint32_t level, uint32_t J, u64* acc, u6
         ConvJob& job = b.job[0];
         job.src = tmp_dn; job.dst = conv; job.hat = c->d_dn_hat; job.hat_w = pad8(k); job.ns = k; job.nt = L1;
         for (uint32_t r = 0; r < L1; r++) { job.tgt_limb[r] = (uint8_t)r; job.tgt_mod[r] = (uint8_t)r; }
-        int32_t rc = launch_baseconv(c, b, L1, k);
-        if (rc != HE_OK) return rc;
+        rc = launch_baseconv(c, b, L1, k);
     }
-    {
+    if (rc == HE_OK && !(rows && cc_on)) {
         const uint32_t n = J * 2 * L1;
         std::vector<uint32_t> mods(n);
         for (uint32_t i = 0; i < n; i++) mods[i] = i % L1;
         TransformDesc t = {};
-        t.fwd = true; t.seg[0] = conv; t.n_seg = 1; t.dst = conv; t.n = n; t.mod_idx = mods.data(); t.ep = &ep;
+        t.fwd = true; t.seg[0] = conv; t.n_seg = 1; t.dst = conv; t.n = n; t.mod_idx = mods.data(); t.ep = rows ? nullptr : &ep;
         t.lazy_out = true;
-        t.only_pass = cc_on ? 2u : 0u;
-        int32_t rc = HE_OK;
-        if (rows) { t.ep = nullptr; t.only_pass = 1u; }
-        if (!(rows && cc_on)) rc = launch_transform(c, t);
-        if (rc == HE_OK && rows) { rows->mid = conv; rc = launch_ks_rows(c, *rows, false); }
-        if (rc != HE_OK) return rc;
+        t.only_pass = rows ? 1u : cc_on ? 2u : 0u;
+        rc = launch_transform(c, t);
     }
+    if (rc == HE_OK && rows) { rows->mid = conv; rc = launch_ks_rows(c, *rows, false); }
+    if (rc != HE_OK) return rc;
     c->cnt.moddown += J;
     return HE_OK;
 }
@@ -676,9 +678,8 @@ static int32_t inner_moddown_batch(he_ctx* c, uint32_t level, const KsSrc* srcs,
         }
     }
     if (c->prof_on) c->prof_key_limbs += (uint64_t)groups * 2 * beta * R;
-    // From N = 2^13 no accumulator is materialised: the special-prime limbs of the inner product are
-    // computed by the first pass of their inverse transform, the q-limbs inside the ModDown epilogue (they would
-    // only be written here and read back there).  Other rings run the stand-alone kernel.
+    // From N = 2^13 no accumulator is materialised: the row kernels form it where they use it (it would only be written here
+    // and read back there).  Other rings run the stand-alone kernel.
     const bool fused = two_pass(c) && beta <= 8;
     if (fused) {
         KsRows a = {};
@@ -1140,9 +1141,7 @@ static bool hoisted_sum_local(const he_ctx* c, uint32_t level, const uint32_t* g
 
 // ciphertexts per launch set: the engine's limits, the kernel's register tile, and for the LDS form its digit tiles
 static uint32_t hoisted_sum_jb(const he_ctx* c, uint32_t level, uint32_t J) {
-    uint32_t cb, jb;
-    engine_shape(c, level, J, J, cb, jb);
-    jb = std::min<uint32_t>(jb, HS_JOBS);
+    uint32_t jb = std::min<uint32_t>(std::min<uint32_t>(J, HS_JOBS), moddown_most_jobs(c, level));
     const uint32_t beta = num_digits(c, level);
     if (beta <= HSL_MAX_TILES) jb = std::min<uint32_t>(jb, HSL_MAX_TILES / beta);
     return jb;

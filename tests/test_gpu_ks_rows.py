@@ -22,6 +22,7 @@ def primes_below(top, two_n, count, skip=()):
 @pytest.mark.parametrize("logN,q_bits,p_bits,nq,np_,dnum,levels,n_ct", [
     (13, 30, 31, 4, 1, 4, (3, 0), 3),        # primes below 2^32: sums put together in 128 bits
     (13, 54, 60, 8, 1, 8, (7, 4), 16),       # eight digits: special primes by work groups, the others by wavefronts
+    (13, 40, 41, 20, 4, 5, (19,), 16),       # sixteen jobs a set, more limbs than one transform launch lists
     (13, 55, 54, 5, 2, 3, (4, 1), 2),        # two digits of two and one of one
     (14, 57, 58, 6, 2, 3, (5, 2), 7),
     (15, 60, 60, 8, 1, 8, (7,), 9),          # more products than one sum holds, in both launches
@@ -73,6 +74,7 @@ def test_one_job_sources(logN, q_bits, p_bits, nq, np_, dnum, levels, n_ct, fill
 
 @pytest.mark.parametrize("logN,q_bits,p_bits,nq,np_,dnum,levels,n_ct", [
     (13, 30, 31, 4, 1, 4, (3, 0), 1),        # a wavefront to a component
+    (13, 40, 41, 20, 4, 5, (19,), 6),        # a set of sixteen jobs and one of two
     (13, 54, 60, 8, 1, 8, (7, 4), 3),        # eight digits and five
     (14, 58, 57, 6, 2, 3, (5, 2), 5),
     (16, 54, 54, 3, 3, 2, (2,), 4),          # 9216 rows: a wavefront to both components
