@@ -245,7 +245,7 @@ def main():
                              "us_per_limb_pass": round(ms_i * 1e3 / prof["pass_limbs"][i], 4),
                              "frac": round(prof["pass_limbs"][i] * limb_bytes / (ms_i * 1e-3) / 1e9 / HBM_PEAK_GBS, 4)}
     roofline = {
-        "kernel": "ntt_row_*_kernel and col_conv_kernel (the row passes, two of them carrying the key-switch inner product and the ModDown epilogue, and the basis conversion with the column passes around it: everything a key switch launches)",
+        "kernel": "ntt_row_run_kernel, col_conv_kernel and ks_rows_kernel (row passes, the basis conversion with the column passes around it, and the row passes with the key-switch inner product and the ModDown between them: everything a key switch launches)",
         "bound": "hbm",
         "achieved": round(achieved, 1),          # 0.5 MiB per limb pass / time, nothing else counted
         "peak": HBM_PEAK_GBS,
@@ -292,15 +292,15 @@ def main():
         ms_one_hoisted = timed(lambda: ctx.he_rotate_hoisted(cts[0], level, steps15, outs[:15]))
         # the whole key switch against the HBM roof.  Compulsory bytes of one key switch = input polynomial
         # (L1 limbs) + outputs (2*L1 limbs) + its share of the key (2*dnum*(L1+k) limbs).  Loop order of this
-        # engine at this level: rotations are ordered step-major within a wave of 8 raised sources and run in launch
-        # sets of up to 10 jobs; jobs of a set that use the same key share one pass over it, so the key is counted
+        # engine at this level: rotations are ordered step-major within a wave of 8 raised sources (16 where each serves
+        # one job) and run in launch sets of up to 16 jobs; jobs of a set that use the same key share one pass over it, so the key is counted
         # once per (launch set, key) - the engine reports those key limbs (key_limbs_read).  The own-key
         # figure (every key switch reads its whole key) is given beside it.
         own_bytes = (L1 + 2 * prm.dnum * (L1 + k) + 2 * L1) * limb_bytes
         sched_bytes = (3 * L1) * limb_bytes + prof["key_limbs_read"] * limb_bytes / ks_per_step
         rate_s, rate_h = 15 * B / (ms_single * 1e-3), 15 * B / (ms_hoisted * 1e-3)
         roofline["keyswitch"] = {
-            "loop_order": "step-major; 8 sources raised per wave; launch sets of <= 10 jobs; one key pass per (launch set, key)",
+            "loop_order": "step-major; 8 sources raised per wave (16 of one job each); launch sets of <= 16 jobs; one key pass per (launch set, key)",
             "bytes_as_scheduled": round(sched_bytes),
             "frac_single": round(rate_s * sched_bytes / 1e9 / HBM_PEAK_GBS, 4),
             "frac_hoisted": round(rate_h * sched_bytes / 1e9 / HBM_PEAK_GBS, 4),

@@ -705,7 +705,7 @@ int32_t launch_transform2p(he_ctx* ctx, const TransformDesc& d) {
     // times the wavefronts.  One rotation at level 5: 65 us with 16 threads, 55 with 64; at level 11 of N = 2^15 70 and 57.
     // With the line at 2048 two rotations at level 11 take 131.5 us instead of 129.1 and one at level 20 of the six-digit
     // set 187 instead of 182; at 8192 a block of layers takes 1255 instead of 1251, at 16384 that rotation 186 again.  Eight
-    // at level 5 take 220 instead of 215 because their smallest launch falls under the line. 
+    // at level 5 take 220 instead of 215 because their smallest launch falls under the line.
     const bool wide_rows = live * (ctx->N >> 10) <= 4096;
     const dim3 block(P2_THREADS), grid_cols(live * tiles), grid_rows(padded * tiles * (wide_rows ? 4 : 1));
     for (int pass = 0; pass < 2; pass++) {
