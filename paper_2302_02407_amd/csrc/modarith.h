@@ -15,6 +15,14 @@ __device__ __forceinline__ u64 mulhi64(u64 a, u64 b) { return __umul64hi(a, b); 
 typedef ulonglong2 pair64 __attribute__((aligned(8)));
 #define LOAD2(p) (*reinterpret_cast<const pair64*>(p))
 #define STORE2(p) (*reinterpret_cast<pair64*>(p))
+// The same for data that no launch soon reads again (the results of a key switch or a rescale, operands of sums larger than the
+// caches), without taking the place of what one does.
+typedef u64 stream64 __attribute__((ext_vector_type(2), aligned(8)));
+__device__ __forceinline__ ulonglong2 load2_stream(const u64* p) {
+    const stream64 v = __builtin_nontemporal_load(reinterpret_cast<const stream64*>(p));
+    return make_ulonglong2(v.x, v.y);
+}
+__device__ __forceinline__ void store2_stream(u64* p, u64 a, u64 b) { __builtin_nontemporal_store((stream64){a, b}, reinterpret_cast<stream64*>(p)); }
 
 // w*y mod q in [0, 2q) for any y < 2^64, given w < q and w_sh = floor(w*2^64/q)  (Shoup).
 __device__ __forceinline__ u64 shoup_lazy(u64 y, u64 w, u64 w_sh, u64 q) {
