@@ -349,12 +349,12 @@ int32_t launch_col_conv(he_ctx* ctx, ColConv& cc, const ScaleList& sc, uint32_t 
     // level 11 takes 93.5 instead of 84.8.  At 64 one at level 5 takes 56.9.
     const bool small = groups * tiles16 * rounds <= 128;
     const uint32_t work = groups * tiles16 * (small ? 4 : 1);
-    // While two work groups per compute unit have room for it, the rounds of a tile run side by side, each with the inverse pass
-    // of its own: a ciphertext product and its rescale at level 11 takes 127 us instead of 136, one rotation at level 15 92
-    // instead of 104, at level 20 of the six-digit set 184 instead of 190.  Where the tiles alone fill most of a work group per
-    // compute unit the repeated pass costs what the shorter chain gives or more (at level 23 156 us instead of 152, two
-    // at level 11 128 instead of 119; one work group per compute unit as the limit gives 147 and 119, but 185 at that level 20).
-    const uint32_t parts = std::max(1u, std::min(rounds, 512 / work));
+    // While every compute unit has at most one work group, the rounds of a tile run side by side, each with the inverse pass of
+    // its own: a ciphertext product and its rescale at level 11 takes 127 us instead of 136, one rotation at level 15 92 instead of
+    // 104.  Up to two work groups per compute unit, where the tiles alone are 192 or 256, one rotation at level 23 takes 140.0 us
+    // instead of 130.1, at level 19 132.0 instead of 122.7, two at level 11 124.1 instead of 115.7, a product at level 23 208.4 instead of
+    // 198.5; nothing measured was faster so by more than the runs differ.
+    const uint32_t parts = std::max(1u, std::min(rounds, 256 / work));
     cc.share = (rounds + parts - 1) / parts * CC_WAVES;
     cc.parts = (rounds * CC_WAVES + cc.share - 1) / cc.share;
     const dim3 grid(work * cc.parts), block(CC_THREADS);
