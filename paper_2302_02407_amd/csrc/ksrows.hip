@@ -20,8 +20,9 @@
 // With two wavefronts to a row, a component each, the same batch took 24.9 ms instead of 19.4 (twice the preparation and twice
 // the misses of the key rows in the first-level cache); three wavefronts to a SIMD instead of four 20.1.
 //
-// No kernel of this file may spill registers: a build of the work-group form that did gave wrong sums wherever two work groups
-// shared a compute unit, and the same code without spills right ones.
+// No kernel may spill registers, and the build refuses one that does (build.py): a build of the work-group form with 84 bytes of scratch a
+// lane gave wrong sums, other ones each time, wherever two work groups shared a compute unit; the same code without spills gave
+// right ones.  Why is not known.
 //
 // Digits and converted components are read once, in whole lines, and the results are not read again here: they go past the caches'
 // usual replacement, so that the key's rows and the next launches' sources stay.  One key switch at level 23 149.9 -> 143.3 us, eight
