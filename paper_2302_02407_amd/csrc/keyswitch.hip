@@ -386,6 +386,9 @@ static int32_t launch_baseconv(he_ctx* c, const ConvBatch& b, uint32_t nt_max, u
     return HE_OK;
 }
 
+// Key switches whose accumulators are formed where they are used and never stored (ksrows.hip; smallring.hip for small rings)
+static bool ks_rows_path(const he_ctx* c, uint32_t level) { return two_pass(c) && num_digits(c, level) <= 8; }
+
 // The most jobs whose ModDown one set of launches takes: both components of all their limbs in one list.
 static uint32_t moddown_most_jobs(const he_ctx* c, uint32_t level) {
     const uint32_t L1 = level + 1, k = c->np;
@@ -399,7 +402,7 @@ static uint32_t moddown_most_jobs(const he_ctx* c, uint32_t level) {
 // rotations of 16 ciphertexts 19.0 ms instead of 19.5, 24 with six digits 2.59 instead of 2.66, 45 of 3 sources with six digits
 // 2.33 instead of 2.44.
 static uint32_t engine_most_jobs(const he_ctx* c, uint32_t level) {
-    return two_pass(c) && num_digits(c, level) <= 8 && c->d_dn_dig ? HE_MAX_KS_JOBS : moddown_most_jobs(c, level);
+    return ks_rows_path(c, level) && c->d_dn_dig ? HE_MAX_KS_JOBS : moddown_most_jobs(c, level);
 }
 
 // How many sources are raised at once and how many jobs share one ModDown launch set.
@@ -425,13 +428,27 @@ static uint32_t engine_most_sources(uint32_t level, uint32_t n_src, uint32_t jb)
     return std::max<uint32_t>(1, std::min(std::min(n_src, cap), std::max<uint32_t>(8, jb)));
 }
 
-// raised[cb][beta][R] + tmp_up[cb][L1] + acc[jb][2][R] + tmp_dn[jb][2][k] + conv[jb][2][L1]; not less for a larger batch
+// The engine's region of the workspace: raised[cb][beta][R], behind it what is needed at different times in the same place, tmp_up[cb][L1]
+// while sources are raised and tmp_dn[jb][2][k] + conv[jb][2][L1] + acc[jb][2][R] (only where accumulators are stored) after that.  240
+// rotations of 16 ciphertexts at the benchmark's top level: 1.34 GB (2.08 with all of them side by side, accumulators included).
+struct KsEngineWs {
+    size_t tmp_up, tmp_dn, conv, acc, total;             // offsets in residues
+};
+static KsEngineWs ks_engine_ws(const he_ctx* c, uint32_t level, uint32_t cb, uint32_t jb) {
+    const size_t N = c->N, L1 = level + 1, k = c->np, R = L1 + k;
+    KsEngineWs w;
+    w.tmp_up = w.tmp_dn = (size_t)cb * num_digits(c, level) * R * N;
+    w.conv = w.tmp_dn + (size_t)jb * 2 * k * N;
+    w.acc = w.conv + (size_t)jb * 2 * L1 * N;
+    const size_t end = w.acc + (ks_rows_path(c, level) || small_ring_path(c, level) ? 0 : (size_t)jb * 2 * R * N);
+    w.total = std::max(w.tmp_up + (size_t)cb * L1 * N, end);
+    return w;
+}
+// not less for a larger batch
 size_t ks_engine_ws_elems(const he_ctx* c, uint32_t level, uint32_t n_src, uint32_t n_jobs) {
     uint32_t cb, jb;
     engine_shape(c, level, n_src, n_jobs, cb, jb);
-    cb = engine_most_sources(level, n_src, jb);
-    const size_t L1 = level + 1, k = c->np, R = L1 + k, beta = num_digits(c, level);
-    return ((size_t)cb * (beta * R + L1) + (size_t)jb * (2 * R + 2 * k + 2 * L1)) * c->N;
+    return ks_engine_ws(c, level, engine_most_sources(level, n_src, jb), jb).total;
 }
 
 static void col_conv_widths(const he_ctx* c, ColConv& cc) {
@@ -680,8 +697,7 @@ static int32_t inner_moddown_batch(he_ctx* c, uint32_t level, const KsSrc* srcs,
     if (c->prof_on) c->prof_key_limbs += (uint64_t)groups * 2 * beta * R;
     // From N = 2^13 no accumulator is materialised: the row kernels form it where they use it (it would only be written here
     // and read back there).  Other rings run the stand-alone kernel.
-    const bool fused = two_pass(c) && beta <= 8;
-    if (fused) {
+    if (ks_rows_path(c, level)) {
         KsRows a = {};
         ks_rows_shape(c, level, a);
         a.J = J; a.n_terms = 1; a.done = rows_left ? 0u : 1u;
@@ -726,17 +742,14 @@ static int32_t inner_moddown_batch(he_ctx* c, uint32_t level, const KsSrc* srcs,
 
 int32_t ks_engine(he_ctx* c, uint32_t level, const KsSrc* srcs, uint32_t n_src, const KsJob* jobs, uint32_t n_jobs) {
     if (n_jobs == 0) return HE_OK;
-    const uint32_t N = c->N, L1 = level + 1, k = c->np, R = L1 + k, beta = num_digits(c, level);
-    if (2 * k > HE_MAX_MODULI) return he_fail(c, HE_ERR_BADARG, "key switch: more than %d special primes", HE_MAX_MODULI / 2);
+    const uint32_t N = c->N, R = level + 1 + c->np, beta = num_digits(c, level);
+    if (2 * c->np > HE_MAX_MODULI) return he_fail(c, HE_ERR_BADARG, "key switch: more than %d special primes", HE_MAX_MODULI / 2);
     int32_t rc = he_ensure_ws(c, ks_engine_ws_elems(c, level, n_src, n_jobs) * sizeof(u64));
     if (rc != HE_OK) return rc;
     uint32_t cb, jb;
     engine_shape(c, level, n_src, n_jobs, cb, jb);
-    u64* raised = c->d_ws;
-    u64* tmp_up = raised + (size_t)cb * beta * R * N;
-    u64* acc = tmp_up + (size_t)cb * L1 * N;
-    u64* tmp_dn = acc + (size_t)jb * 2 * R * N;
-    u64* conv = tmp_dn + (size_t)jb * 2 * k * N;
+    const KsEngineWs w = ks_engine_ws(c, level, cb, jb);
+    u64 *raised = c->d_ws, *tmp_up = c->d_ws + w.tmp_up, *tmp_dn = c->d_ws + w.tmp_dn, *conv = c->d_ws + w.conv, *acc = c->d_ws + w.acc;
     // jobs ordered by source wave, then by key so that equal keys are adjacent
     std::vector<uint32_t> order(n_jobs);
     for (uint32_t i = 0; i < n_jobs; i++) order[i] = i;
@@ -753,7 +766,7 @@ int32_t ks_engine(he_ctx* c, uint32_t level, const KsSrc* srcs, uint32_t n_src, 
         while (end < n_jobs && jobs[order[end]].src / cb == s0 / cb) end++;
         if (end == pos) continue;                       // no job uses these sources
         // digits that one job uses are transformed where it uses them (ksrows.hip)
-        bool rows_left = two_pass(c) && beta <= 8;
+        bool rows_left = ks_rows_path(c, level);
         uint32_t uses[HE_MAX_SEGS] = {0};
         for (size_t i = pos; i < end; i++) rows_left = rows_left && ++uses[jobs[order[i]].src - s0] == 1;
         rc = modup_batch(c, srcs + s0, ns, level, raised, tmp_up, !rows_left);
@@ -828,7 +841,7 @@ static uint32_t rot_sum_cb(const he_ctx* c, uint32_t level, uint32_t n_rot) {
     return cb;
 }
 static bool rot_sum_fused(const he_ctx* c, uint32_t level, uint32_t n_rot) {
-    return two_pass(c) && num_digits(c, level) <= 8 && n_rot <= HE_MAX_KS_JOBS;
+    return ks_rows_path(c, level) && n_rot <= HE_MAX_KS_JOBS;
 }
 
 // raised[n_rot][beta][R] + tmp_up[cb][L1] + s0[L1] + s1[L1] + tmp_dn[2][k] + conv[2][L1] (+ acc[1 + min(n_rot,16)][2][R]

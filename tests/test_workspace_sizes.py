@@ -1,15 +1,19 @@
 """The sizes that the workspace queries return, without a GPU: a query reads the ring degree, the prime counts and the digit
-width of its context and nothing else, so a block of memory that starts with those words stands in for one."""
+width of its context, and whether the column conversion's tables are there, so a block of memory that starts with those words
+stands in for one, with every pointer behind them null or (operands) none of them."""
 import ctypes as C
 
 import pytest
 
-# logN, ciphertext primes, special primes, digits
-SETS = [(16, 24, 8, 3), (16, 24, 4, 6), (15, 12, 4, 3), (9, 25, 1, 25), (12, 3, 1, 3), (17, 24, 8, 3)]
+# logN, ciphertext primes, special primes, digits, operands
+SETS = [(16, 24, 8, 3), (16, 24, 4, 6), (15, 12, 4, 3), (9, 25, 1, 25), (12, 3, 1, 3), (17, 24, 8, 3),
+        (16, 24, 8, 3, True), (16, 24, 4, 6, True), (15, 12, 4, 3, True)]
 
 
-def context(logN, nq, np_, dnum):
+def context(logN, nq, np_, dnum, operands=False):
     words = (C.c_uint32 * 65536)()
+    if operands:
+        words[:] = [1] * 65536
     words[:7] = [logN, 1 << logN, nq, np_, dnum, -(-nq // dnum), nq + np_]
     return words
 
@@ -47,6 +51,23 @@ def test_the_hoisted_sum_of_a_block_leaves_room_for_its_square(prm):
                 plan = BlockPlan(2, 8, slots // 16, 1, 3, 1, 2 * group, level, group, 0, hoisted)
                 need.append(query("he_ws_query_ca_ra_block", ctx, C.byref(plan)))
             assert need[0] <= need[1], (level, group)
+
+
+@pytest.mark.parametrize("prm", SETS)
+def test_nothing_is_reserved_that_no_launch_uses(prm):
+    """One key switch holds its digits and, in one place, either the limbs it raises or those of its ModDown; accumulators over the
+    raised basis only where they are stored: more than 8 digits."""
+    logN, nq, k, dnum = prm[:4]
+    ctx, N, alpha = context(*prm), 1 << logN, -(-nq // dnum)
+    for level in range(nq):
+        L1, beta = level + 1, -(-(level + 1) // alpha)
+        down = 2 * k + 2 * L1 + (2 * (L1 + k) if beta > 8 else 0)
+        assert query("he_ws_query_rotate_batch", ctx, level, 1, 1, 0) == (beta * (L1 + k) + max(L1, down)) * N * 8, level
+
+
+def test_the_benchmarks_batch_of_rotations():
+    """240 rotations of 16 ciphertexts at the top level: sixteen sources' digits and sixteen jobs' ModDown at most."""
+    assert query("he_ws_query_rotate_batch", context(16, 24, 8, 3, True), 23, 16, 15, 0) <= 16 * (3 * 32 + 2 * 8 + 2 * 24) << 19
 
 
 def test_a_chain_without_special_primes_is_refused():
