@@ -675,26 +675,19 @@ static void ks_rows_shape(const he_ctx* c, uint32_t level, KsRows& a) {
     a.count_up = modup_by_columns(c, level) ? 1u : 0u;
 }
 
+static bool same_key(const KsJob& a, const KsJob& b) { return a.evk == b.evk && a.g == b.g; }
+
 // Inner product + ModDown of up to HE_MAX_KS_JOBS jobs whose sources are already raised.
 // raised_of[i] / srcs give job i's raised digits and source; scratch: acc, tmp_dn, conv.  rows_left: the digits' rows are not
 // transformed yet.
 static int32_t inner_moddown_batch(he_ctx* c, uint32_t level, const KsSrc* srcs, const KsJob* jobs, const u64* const* raised_of,
                                    uint32_t J, u64* acc, u64* tmp_dn, u64* conv, bool rows_left) {
     const uint32_t N = c->N, L1 = level + 1, k = c->np, R = L1 + k, beta = num_digits(c, level);
-    // group consecutive jobs that use the same key and Galois element (the caller sorts them)
-    IpBatch ib;
-    uint32_t groups = 0;
-    for (uint32_t i = 0; i < J; i++) {
-        ib.raised[i] = raised_of[i];
-        ib.own[i] = srcs[jobs[i].src].c1;
-        if (groups && ib.evk[groups - 1] == jobs[i].evk && ib.g[groups - 1] == jobs[i].g) {
-            ib.count[groups - 1]++;
-        } else {
-            ib.evk[groups] = jobs[i].evk; ib.g[groups] = jobs[i].g; ib.start[groups] = i; ib.count[groups] = 1;
-            groups++;
-        }
+    if (c->prof_on) {                                   // one pass over a key for each run of jobs that use it (the caller sorts them)
+        uint32_t runs = 0;
+        for (uint32_t i = 0; i < J; i++) runs += i == 0 || !same_key(jobs[i - 1], jobs[i]);
+        c->prof_key_limbs += (uint64_t)runs * 2 * beta * R;
     }
-    if (c->prof_on) c->prof_key_limbs += (uint64_t)groups * 2 * beta * R;
     // From N = 2^13 no accumulator is materialised: the row kernels form it where they use it (it would only be written here
     // and read back there).  Other rings run the stand-alone kernel.
     if (ks_rows_path(c, level)) {
@@ -718,6 +711,18 @@ static int32_t inner_moddown_batch(he_ctx* c, uint32_t level, const KsSrc* srcs,
     // small rings: inner product, ModDown and epilogue of every output limb in one work group, one launch
     const bool small = small_ring_path(c, level);
     if (!small) {
+        IpBatch ib;
+        uint32_t groups = 0;
+        for (uint32_t i = 0; i < J; i++) {
+            ib.raised[i] = raised_of[i];
+            ib.own[i] = srcs[jobs[i].src].c1;
+            if (groups && same_key(jobs[i - 1], jobs[i])) {
+                ib.count[groups - 1]++;
+            } else {
+                ib.evk[groups] = jobs[i].evk; ib.g[groups] = jobs[i].g; ib.start[groups] = i; ib.count[groups] = 1;
+                groups++;
+            }
+        }
         int32_t rc = launch_inner_product(c, level, ib, groups, acc);
         if (rc != HE_OK) return rc;
     }
