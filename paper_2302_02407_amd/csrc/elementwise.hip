@@ -60,9 +60,15 @@ __global__ __launch_bounds__(EW_THREADS) void ptct_mac_kernel(u64* __restrict__ 
 // swapped, so every access is 16 bytes; four terms' operands are requested before the first is used (bound by reading
 // them).  Products in split sums, reduced once per 4 terms.  limb = blockIdx.y.
 // STREAM: the ciphertexts are read past the caches' usual replacement, for sums whose operands do not fit the Infinity Cache: what
-// is written back or kept there then does not make room for data that is used once.  Merge and rescale of 16 ciphertexts at level
-// 22 of N = 2^16 (552 MiB of operands): 165.6 us read the usual way and 139.6 so, 211 and 193 after a gigabyte of other writes; of 6
-// (207 MiB) 82.7 and 80.4, 119 and 102; of 4 (138 MiB) 68.6 and 70.6, 99 and 86.
+// is written back or kept there then does not make room for data that is used once.  Plaintexts are read the usual way: in use a merge
+// follows the layers that make its ciphertexts, and that is the order the choice was made for.  Merge and rescale at N = 2^16, us, everything
+// the usual way / ciphertexts as streams / plaintexts too, (a) after those layers, (b) again on the same operands, (c) after a gigabyte
+// of other writes:
+//   16 at level 22 (552 MiB of operands)  (a) 164 / 153 / 157  (b) 167 / 142 / 155  (c) 210 / 191 / 164
+//    8 at level 22 (276 MiB)              (a) 105 / 102 / 103  (b) 107 /  95 / 104  (c) 144 / 123 / 108
+//   16 at level 11 (288 MiB)              (a)  98 /  93 /  89  (b)  90 /  81 /  86  (c) 133 / 108 /  89
+//    6 at level 22 (207 MiB)              (a)  91 /  89 /  90  (b)  84 /  83 /  89  (c) 121 / 103 /  93
+// and 4 at level 22 (138 MiB) as streams although they fit: (b) 70.6 instead of 68.6, (c) 86 instead of 99.
 #define MACROT_MAX 16
 #define MACROT_STREAM_BYTES ((size_t)192 << 20)
 struct MacRot {

@@ -6,27 +6,35 @@
 // that row can be transformed where it is used: it is read once in the state the column pass leaves it and permuted in LDS,
 // where a transform launch of its own wrote and read back 72 of some 580 limb moves of a key switch at the benchmark's top
 // level, and both components read it again.  Digits that several jobs use are transformed once instead (ntt2p.hip) and come
-// here complete (DONE); nineteen limbs by sixteen rotations of one source take 1782 us so, where sums formed inside the
-// transforms of each component, which read every digit twice, took 1910.
+// here complete (DONE); fifteen rotations of each of three sources at level 18 of N = 2^16 (45 key switches) took 1782 us so, where
+// sums formed inside the transforms of each component, which read every digit twice, took 1910.
 //
 //   special primes: rows of the digits -> products with both components of the key -> inverse rows of both sums;
 //   q-limbs:        rows of the digits -> products -> rows of both converted components -> (acc - conv) * P^-1 + addends.
 //
-// What bounds it: bytes for the q-limbs (eight key switches at level 23 of N = 2^16 in 221 us, 885 MiB moved at 4.2 TB/s, vector
-// issue 0.66 of the slots), vector issue for the special primes (85 us, 0.72: their 60-bit ranges take a reduction every other stage).
-// A key switch of a batch takes 27.9 + 10.7 us in these two launches where rows of the digits, sums with inverse rows and sums
-// with the ModDown took 18 + 9 + 26.  A row is shared by a whole wavefront, 4 points a lane, because then the sums of both
-// components stay in registers (8 sums of three words) and every product is formed once from digits that both components share.
-// With two wavefronts to a row, a component each, the same batch took 24.9 ms instead of 19.4 (twice the preparation and twice
-// the misses of the key rows in the first-level cache); three wavefronts to a SIMD instead of four 20.1.
+// What bounds it: bytes for the q-limbs (sixteen key switches at level 23 of N = 2^16 in 409 us, 1.6 GiB moved at 4.2 TB/s, vector
+// issue 0.74 of the slots; 5.1 TB/s and 0.66 where the digits are complete), vector issue for the special primes (162 us, 0.78: their
+// 60-bit ranges take a reduction every other stage).  A key switch of a batch takes 26 + 10 us in these two launches where rows
+// of the digits, sums with inverse rows and sums with the ModDown took 18 + 9 + 26.  A row is shared by a whole wavefront, 4 points
+// a lane, because then the sums of both components stay in registers (8 sums of three words) and every product is formed once from
+// digits that both components share.  With two wavefronts to a row, a component each, a batch of 240 (in sets of eight) took 24.9 ms
+// instead of 19.4 (twice the preparation and twice the misses of the key rows in the first-level cache); three wavefronts to a SIMD
+// instead of four 20.1.  Reading a digit back in the Galois map's order (KrRow::src) is not free of bank conflicts: 0.30 to 0.33 of the
+// LDS cycles of these kernels, which issue an LDS instruction for every 17 to 21 vector ones.
 //
 // No kernel may spill registers, and the build refuses one that does (build.py): a build of the work-group form with 84 bytes of scratch a
 // lane gave wrong sums, other ones each time, wherever two work groups shared a compute unit; the same code without spills gave
 // right ones.  Why is not known.
 //
-// Digits and converted components are read once, in whole lines, and the results are not read again here: they go past the caches'
-// usual replacement, so that the key's rows and the next launches' sources stay.  One key switch at level 23 149.9 -> 143.3 us, eight
-// hoisted ones at level 5 174.4 -> 165.9, 28 of N = 2^15 at level 11 579 -> 562, 240 of a batch 18.91 -> 18.72 ms.
+// Digits and converted components are read once, in whole lines; they and the results go past the caches' usual replacement, so
+// that the key's rows and the next launches' sources stay.  Calls whose results nobody reads: one key switch at level 23 149.9 -> 143.3
+// us, eight hoisted ones at level 5 174.4 -> 165.9, 28 of N = 2^15 at level 11 579 -> 562, 240 of a batch 18.91 -> 18.72 ms.  In a layer
+// the next launch reads the results; there it is about even, for small ciphertexts a little worse and for large ones better.  As streams /
+// stored the usual way wherever the call itself reads them: 16 channels in the paper's order, 8 outputs, level 5 1016 / 1018 us on one
+// card, 1125 / 1115 on another, 1050 / 1033 on a third, level 8 1289 / 1290, 14 2024 / 2043, 23 3376 / 3410 and 3550 / 3580; 16 outputs at
+// level 5 1709 / 1720; its hoisted form at level 5 656 / 658; reordered layer, a ModDown per rotation, level 5 305 / 306, 20 967 / 974;
+// five rotate-and-sum rounds of one ciphertext at level 5 279 / 277, of 16 at level 11 3158 / 3179.  Choosing by a flag of the launch
+// costs one rotation at level 5 0.7 of its 57.5 us, so there is none.
 //
 // Work order: jobs (they come sorted by key) are the fastest index, then rows; each XCD works on every eighth (limb, row), so
 // that jobs under one key find its row and the twiddles in that XCD's L2.

@@ -15,8 +15,8 @@ __device__ __forceinline__ u64 mulhi64(u64 a, u64 b) { return __umul64hi(a, b); 
 typedef ulonglong2 pair64 __attribute__((aligned(8)));
 #define LOAD2(p) (*reinterpret_cast<const pair64*>(p))
 #define STORE2(p) (*reinterpret_cast<pair64*>(p))
-// The same for data that no launch soon reads again (the results of a key switch or a rescale, operands of sums larger than the
-// caches), without taking the place of what one does.
+// The same past the caches' usual replacement: data that is read once (operands of sums larger than the caches) or that is no faster
+// for its reader where it would stay (the results of a key switch or a rescale) does not take the place of what is read again.
 typedef u64 stream64 __attribute__((ext_vector_type(2), aligned(8)));
 __device__ __forceinline__ ulonglong2 load2_stream(const u64* p) {
     const stream64 v = __builtin_nontemporal_load(reinterpret_cast<const stream64*>(p));
