@@ -16,15 +16,15 @@
 // out so that a lane gets the 8 digit sums of one (point, target); they are put together and reduced below 2q in 22
 // vector instructions (counted in the compiled loops), where the vector-unit form of the same sum takes 68 (baseconv_kernel).
 //
-// What bounds it is vector issue: 5969 instructions per wavefront for 8 + 24 limbs (counters), 4 cycles each, fill 0.65 of the
-// issue slots (2.4 GHz) of the benchmark's launches, which move 2.3 TB/s; wavefronts wait 0.47 of their cycles.
+// What bounds it is vector issue: 5969 instructions per wavefront for 8 + 24 limbs (counters), 4 cycles each, fill 0.65 to
+// 0.68 (by card) of the issue slots (2.4 GHz) of the benchmark's launches, which move 2.4 TB/s; wavefronts wait 0.47 of their cycles.
 // Small launches are chains: of 10.6 us of a work group (level 5, tiles of 256 points) 4.4 go by until a source is transformed, 2.3
 // while the slower wavefronts finish theirs, 2.3 until a round's operands are there and 1.6 in the conversion and the targets; its
 // SIMDs' issue slots are half full.  Asking for the round's list before the sources takes one rotation at level 5 from 57.3 to 56.8 us,
 // with six digits at level 6 from 61.0 to 59.6; asking for the operands themselves as well gave nothing.
 // A launch for eight of the benchmark's single rotations went from 162 to 151 us once a round's operands came without dependent
-// vector loads and nothing was kept in scratch memory; sets are sixteen now, 306 us a launch, 9.2 of the 19.0 ms of kernel time of 240
-// rotations.
+// vector loads and nothing was kept in scratch memory; sets are sixteen now, 290 to 306 us a launch, 48 % of the kernel time
+// of 240 rotations.
 #include <algorithm>
 
 #include "modarith.h"
