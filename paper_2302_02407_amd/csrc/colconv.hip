@@ -81,8 +81,8 @@ __device__ __forceinline__ void cc_source(u64* reg, const u64* src, const ColCon
     wave_exchange();
 #pragma unroll
     for (int k = 0; k < 16; k++) x[k] = reg[cc_word(k, lane)];
-    bounds_all(bd, WIDE ? 4 : 4 << (4 - U0));
-    inv_stages<WIDE, 1, 4>(x, bd, w1, q);
+    bounds_all(bd, WIDE ? 4 : narrow_after(4, 4 - U0));
+    inv_stages<WIDE, 1, 4, true>(x, bd, w1, q);
     if (WIDE) settle4(x, bd, q);
     const u64 bq = WIDE ? 4 * q : 512 * q;
 #pragma unroll
@@ -98,19 +98,21 @@ __device__ __forceinline__ void cc_source(u64* reg, const u64* src, const ColCon
 }
 
 // Forward column stages of one target limb from its LDS region (below 2q) to memory.
-template <int LC, bool WIDE>
-__device__ __forceinline__ void cc_target(u64* reg, u64* dst, uint32_t mi, const ulonglong2 (&w1)[15], uint32_t lane, uint32_t c0, const ModConst* mc, const ulonglong2* ftw) {
+// `before`: what goes ahead of the stores, for which later loads wait.
+template <int LC, bool WIDE, class Before>
+__device__ __forceinline__ void cc_target(u64* reg, u64* dst, uint32_t mi, const ulonglong2 (&w1)[15], uint32_t lane, uint32_t c0, const ModConst* mc, const ulonglong2* ftw,
+                                          Before&& before) {
     constexpr int LCOLS = 10 - LC, U0 = 8 - LC;
     const uint32_t t = lane >> LCOLS, cl = lane & ((1u << LCOLS) - 1u), c = c0 + cl;
     const ctw_t tw = (ctw_t)(uintptr_t)(ftw + ((size_t)mi << (LC + 8)));
     const cu64_t mp = (cu64_t)(uintptr_t)(mc + mi);
-    const u64 q = uni64(mp[0]), q4 = 4 * q;
+    const u64 q = uni64(mp[0]);
     ulonglong2 w2[15];
     tw_load_c<(U0 < 3 ? U0 : 3), 3>(w2, tw, LC - 4, t);
     u64 x[16];
 #pragma unroll
     for (int k = 0; k < 16; k++) x[k] = reg[cc_word(k, lane)];
-    fwd_stages<WIDE, 0, 4>(x, w1, q);
+    fwd_stages<WIDE, 0, 4, true>(x, w1, q);
     wave_exchange();
 #pragma unroll
     for (int k = 0; k < 16; k++) reg[cc_word(k, lane)] = x[k];
@@ -132,9 +134,12 @@ __device__ __forceinline__ void cc_target(u64* reg, u64* dst, uint32_t mi, const
     for (int g = 0; g < 4; g++) wb[g] = p3[4 + g];
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int g = 0; g < 4; g++) ct_bfly_u<WIDE>(0, x[2 * g], x[2 * g + 1], wa[g].x, wa[g].y, q, q4);
+    for (int g = 0; g < 4; g++)
+        ct_stage<WIDE, false, 1>(0, [&](int) -> u64& { return x[2 * g]; }, [&](int) -> u64& { return x[2 * g + 1]; }, wa[g].x, wa[g].y, q);
 #pragma unroll
-    for (int g = 0; g < 4; g++) ct_bfly_u<WIDE>(0, x[8 + 2 * g], x[9 + 2 * g], wb[g].x, wb[g].y, q, q4);
+    for (int g = 0; g < 4; g++)
+        ct_stage<WIDE, false, 1>(0, [&](int) -> u64& { return x[8 + 2 * g]; }, [&](int) -> u64& { return x[9 + 2 * g]; }, wb[g].x, wb[g].y, q);
+    before();
 #pragma unroll
     for (int j = 0; j < 16; j++) (dst + j * 256)[t * 4096 + c] = x[j];
 }
@@ -158,7 +163,7 @@ __device__ __forceinline__ void c4_factors(u64 (&w)[4][6], const ulonglong2* tw,
 #pragma unroll
     for (int i = 0; i < C4<LC>::NB; i++) tw_block2(w[i], tw, 2 * i, t >> (6 - 2 * i));
 }
-template <int LC>
+template <int LC, bool WIDE>
 __device__ __forceinline__ void c4_source(u64* reg, const u64* src, const ScaleList& sc, uint32_t mi, uint32_t si, uint32_t t, uint32_t c0,
                                           const ModConst* mc, const ulonglong2* itw) {
     using G = C4<LC>;
@@ -167,6 +172,7 @@ __device__ __forceinline__ void c4_source(u64* reg, const u64* src, const ScaleL
     for (int k = 0; k < 4; k++) x[k] = src[G::at(c4_point(G::NB - 1, t, k), c0)];
     c4_factors<LC>(w, itw + ((size_t)mi << (LC + 8)), t);
     const u64 q = uni64(mc[mi].q), cs = sc.s[si], cs_sh = sc.s_sh[si];
+    int bound = WIDE ? 4 : 2;                            // narrow rows arrive below 2q: 2, 10, 40, 160, at the end 640
 #pragma unroll
     for (int i = G::NB - 1; i >= 0; i--) {
         if (i + 1 < G::NB) {
@@ -174,40 +180,34 @@ __device__ __forceinline__ void c4_source(u64* reg, const u64* src, const ScaleL
 #pragma unroll
             for (int k = 0; k < 4; k++) x[k] = reg[c4_word(c4_point(i, t, k))];
         }
-        if (2 * i + 1 < LC) {
-            inv_block2_r(x, w[i], q);
-        } else {
-            int b[4] = {4, 4, 4, 4};
-            gs_bfly<true>(x[0], x[2], b[0], b[2], w[i][0], w[i][1], q);
-            gs_bfly<true>(x[1], x[3], b[1], b[3], w[i][0], w[i][1], q);
-            settle4(x, b, q);
-        }
+        if (2 * i + 1 >= LC) inv_block2_r<WIDE, false, true>(x, w[i], q, bound);
+        else if (i == 0) inv_block2_r<WIDE, true>(x, w[i], q, bound);         // its factors are the same for the whole limb
+        else inv_block2_r<WIDE>(x, w[i], q, bound);
+        if (!WIDE) bound = narrow_after(bound, 2 * i + 1 >= LC ? 1 : 2);
 #pragma unroll
         for (int k = 0; k < 4; k++)
             reg[c4_word(c4_point(i, t, k))] = i ? x[k] : csub(shoup_lazy(x[k], cs, cs_sh, q), q) ^ 0x8080808080808080ull;
     }
 }
-template <int LC, bool WIDE>
-__device__ __forceinline__ void c4_target(u64* reg, u64* dst, uint32_t mi, const u64 (&w)[4][6], uint32_t t, uint32_t c0, const ModConst* mc) {
+template <int LC, bool WIDE, class Before>
+__device__ __forceinline__ void c4_target(u64* reg, u64* dst, uint32_t mi, const u64 (&w)[4][6], uint32_t t, uint32_t c0, const ModConst* mc, Before&& before) {
     using G = C4<LC>;
-    const u64 q = uni64(mc[mi].q), q4 = 4 * q;
+    const u64 q = uni64(mc[mi].q);
     u64 x[4];
 #pragma unroll
     for (int i = 0; i < G::NB; i++) {
         if (i) wave_exchange();
 #pragma unroll
         for (int k = 0; k < 4; k++) x[k] = reg[c4_word(c4_point(i, t, k))];
-        if (2 * i + 1 < LC) {
-            fwd_block2_r<WIDE>(x, w[i], q, q4);
-        } else {
-            ct_bfly_u<WIDE>(0, x[0], x[2], w[i][0], w[i][1], q, q4);
-            ct_bfly_u<WIDE>(0, x[1], x[3], w[i][0], w[i][1], q, q4);
-        }
+        if (2 * i + 1 >= LC) fwd_block2_r<WIDE, false, true>(x, w[i], q);
+        else if (i == 0) fwd_block2_r<WIDE, true>(x, w[i], q);                // its factors are the same for the whole limb
+        else fwd_block2_r<WIDE>(x, w[i], q);
         if (i + 1 < G::NB) {
 #pragma unroll
             for (int k = 0; k < 4; k++) reg[c4_word(c4_point(i, t, k))] = x[k];
         }
     }
+    before();
 #pragma unroll
     for (int k = 0; k < 4; k++) dst[G::at(c4_point(G::NB - 1, t, k), c0)] = x[k];
 }
@@ -227,6 +227,7 @@ __global__ __launch_bounds__(CC_THREADS, 4) void col_conv_kernel(ColConv cc, Sca
     constexpr int LCOLS = (PTS == 16 ? 10 : 8) - LC, TPX = (256 >> LCOLS) / 8;       // tiles of a group per XCD
     constexpr int REGION = PTS == 16 ? CC_REGION : 272, NB = PTS / 2;                // LDS words of a limb's tile, blocks of 16 points per wavefront
     __shared__ u64 lds[CC_WAVES * REGION];
+    __shared__ ConvOperand ops[CC_WAVES];                                              // of a round's targets
     auto point = [](uint32_t w, int b, uint32_t p16) {
         return PTS == 16 ? cc_word(2 * w + (b >> 2), 16 * (b & 3) + p16) : c4_word(32 * w + 16 * b + p16);
     };
@@ -237,14 +238,32 @@ __global__ __launch_bounds__(CC_THREADS, 4) void col_conv_kernel(ColConv cc, Sca
     u64* reg = lds + w * REGION;
     const uint32_t tb = (gp - grp * cc.parts) * cc.share, nt = min(st.nt, tb + cc.share);
     // the first round's list is asked for before the sources: everything else of the round waits for it
-    u64 mods_v = *reinterpret_cast<const u64*>(st.mod + tb), lims_v = *reinterpret_cast<const u64*>(st.limb + tb);
+    u64 mods = uni64(*reinterpret_cast<const u64*>(st.mod + tb)), lims = uni64(*reinterpret_cast<const u64*>(st.limb + tb));
+    // this wavefront's part of the next round's operands on its way to LDS; a target beyond the list: the round's first
+    u64 op_dig;
+    uint32_t op_rest;
+    auto op_load = [&](uint32_t t0) {
+        const uint32_t m = t0 + w < nt ? (uint32_t)(mods >> (8 * w)) & 255u : (uint32_t)mods & 255u;
+        const ConvOperand* p = st.op + m;
+        op_dig = reinterpret_cast<const u64*>(p)[lane];
+        op_rest = reinterpret_cast<const uint32_t*>(p)[128 + (lane & 15u)];
+    };
+    auto op_store = [&]() {
+        reinterpret_cast<u64*>(ops + w)[lane] = op_dig;
+        if (lane < 16) reinterpret_cast<uint32_t*>(ops + w)[128 + lane] = op_rest;
+    };
+    op_load(tb);
     if (w < st.ns) {
         const u64* src = st.src + (size_t)rep * cc.src_stride + ((size_t)w << (LC + 8));
         const uint32_t mi = st.mod0 + w;
-        if constexpr (PTS == 4) c4_source<LC>(reg, src, sc, mi, st.sc0 + w, lane, c0, mc, itw);
+        if constexpr (PTS == 4) {
+            if (cc.wide_inv >> mi & 1u) c4_source<LC, true>(reg, src, sc, cc_pin<true>(mi), st.sc0 + w, lane, c0, mc, itw);
+            else c4_source<LC, false>(reg, src, sc, cc_pin<false>(mi), st.sc0 + w, lane, c0, mc, itw);
+        }
         else if (cc.wide_inv >> mi & 1u) cc_source<LC, true>(reg, src, cc, sc, cc_pin<true>(mi), st.sc0 + w, lane, c0, mc, itw);
         else cc_source<LC, false>(reg, src, cc, sc, cc_pin<false>(mi), st.sc0 + w, lane, c0, mc, itw);
     }
+    op_store();
     __syncthreads();
     // this wavefront's eighth of the points of every source; lane group g = lane / 16 holds sources 2g, 2g+1 of 16
     // points, in memory order the bytes k = 16g .. 16g+15 of the contraction
@@ -260,66 +279,57 @@ __global__ __launch_bounds__(CC_THREADS, 4) void col_conv_kernel(ColConv cc, Sca
     for (uint32_t t0 = tb; t0 < nt; t0 += CC_WAVES) {
         asm("" : "+v"(ln));                                  // what follows from the lane is worked out anew, not kept in registers
         const uint32_t g = ln >> 4, p16 = ln & 15;
-        // operands of this round's eight targets, four (s) at a time: lane group g works on target t0 + 4s + g and this lane
-        // supplies row lane % 16 = (target (lane % 16) / 4, digit lane % 4) of the left factor
-        if (t0 != tb) {
-            mods_v = *reinterpret_cast<const u64*>(st.mod + t0);
-            lims_v = *reinterpret_cast<const u64*>(st.limb + t0);
-        }
-        const u64 mods = uni64(mods_v), lims = uni64(lims_v);
-        const uint32_t mod_first = (uint32_t)mods & 255u;
-        v4i a0[2], a1[2], k0[2], k1[2];
-        uint32_t n0[2], n1[2], rec[2], bits[2];
-#pragma unroll
-        for (int s = 0; s < 2; s++) {
-            const uint32_t ta = t0 + 4 * s + (p16 >> 2), tg = t0 + 4 * s + g;
-            const uint32_t ma = ta < nt ? (uint32_t)(mods >> (8 * (4 * s + (p16 >> 2)))) & 255u : mod_first;
-            const uint32_t mg = tg < nt ? (uint32_t)(mods >> (8 * (4 * s + g))) & 255u : mod_first;
-            const v4i* A = reinterpret_cast<const v4i*>(st.digits + (size_t)ma * 512 + (p16 & 3) * 64 + g * 16);
-            a0[s] = A[0]; a1[s] = A[16];                     // digits 0..3, digits 4..7 (256 bytes on)
-            const v4i* K = reinterpret_cast<const v4i*>(st.bias + (size_t)mg * 8);
-            k0[s] = K[0]; k1[s] = K[1];
-            const u64 nq = 0 - mc[mg].q;
-            n0[s] = (uint32_t)nq; n1[s] = (uint32_t)(nq >> 32);
-            rec[s] = mc[mg].rec; bits[s] = mc[mg].bits;
-        }
         // this wavefront's target and the factors of its first block, which arrive during the conversion
         const bool have = t0 + w < nt;
-        const uint32_t mi = have ? (uint32_t)(mods >> (8 * w)) & 255u : mod_first;
+        const uint32_t mi = have ? (uint32_t)(mods >> (8 * w)) & 255u : (uint32_t)mods & 255u, li = (uint32_t)(lims >> (8 * w)) & 255u;
         ulonglong2 w1[15];                                   // 16 points per lane
         u64 w4[4][6];                                        // 4 points: all factors
         if constexpr (PTS == 16) tw_load_c<0, 4>(w1, (ctw_t)(uintptr_t)(ftw + ((size_t)mi << (LC + 8))), 0, 0);
         else c4_factors<LC>(w4, ftw + ((size_t)mi << (LC + 8)), ln);
         __syncthreads();                                     // the regions are free (operands read, last targets done)
+        // four targets (s) at a time: lane group g works on target t0 + 4s + g and this lane supplies row lane % 16 = (target (lane
+        // % 16) / 4, digit lane % 4) of the left factor
 #pragma unroll
         for (int s = 0; s < 2; s++) {
             if (t0 + 4 * s >= nt) break;
-            const uint32_t tg = t0 + 4 * s + g;
+            const v4i* A = reinterpret_cast<const v4i*>(ops[4 * s + (p16 >> 2)].dig + (p16 & 3) * 64 + g * 16);
+            const v4i* K = reinterpret_cast<const v4i*>(ops[4 * s + g].bias);
+            const v4i a0 = A[0], a1 = A[16], k0 = K[0], k1 = K[1], mk = K[2];      // digits 0..3, digits 4..7 (256 bytes on); -q, rec, bits
+            const uint32_t n0 = (uint32_t)mk.x, n1 = (uint32_t)mk.y, rec = (uint32_t)mk.z, bits = (uint32_t)mk.w;
             // quotient of a value below 2^(bits+14) from its top: sh = bits - 18 (at least 32)
-            const uint32_t sh = bits[s] > 50 ? bits[s] - 18 : 32, e = bits[s] - 1 - sh;
+            const uint32_t sh = bits > 50 ? bits - 18 : 32, e = bits - 1 - sh;
             u64* out = lds + (4 * s + g) * REGION;
+            const bool mine = t0 + 4 * s + g < nt;
 #pragma unroll
             for (int b = 0; b < NB; b++) {
-                const v4i d0 = __builtin_amdgcn_mfma_i32_16x16x64_i8(a0[s], frag[b], k0[s], 0, 0, 0);
-                const v4i d1 = __builtin_amdgcn_mfma_i32_16x16x64_i8(a1[s], frag[b], k1[s], 0, 0, 0);
+                const v4i d0 = __builtin_amdgcn_mfma_i32_16x16x64_i8(a0, frag[b], k0, 0, 0, 0);
+                const v4i d1 = __builtin_amdgcn_mfma_i32_16x16x64_i8(a1, frag[b], k1, 0, 0, 0);
                 const int p01 = d0.x + (d0.y << 8), p23 = d0.z + (d0.w << 8), p45 = d1.x + (d1.y << 8), p67 = d1.z + (d1.w << 8);
                 const int64_t lo = (int64_t)p23 * 65536 + p01, hi = (int64_t)p67 * 65536 + p45 + (lo >> 32);
-                const uint32_t qh = __umulhi((uint32_t)((u64)hi >> (sh - 32)), rec[s]) >> e;
+                const uint32_t qh = __umulhi((uint32_t)((u64)hi >> (sh - 32)), rec) >> e;
                 u64 v = ((u64)(uint32_t)hi << 32) | (uint32_t)lo;
-                v += (u64)qh * n0[s];
-                v = ((u64)add3((uint32_t)(v >> 32), qh * n1[s], 0) << 32) | (uint32_t)v;
-                if (tg < nt) out[point(w, b, p16)] = v;
+                v += (u64)qh * n0;
+                v = ((u64)add3((uint32_t)(v >> 32), qh * n1, 0) << 32) | (uint32_t)v;
+                if (mine) out[point(w, b, p16)] = v;
             }
         }
         __syncthreads();
+        // The next round's operands are asked for here and put down before this round's results are stored: loads behind the stores
+        // would wait for them, which took a fourth of a wavefront's time.
+        const bool more = t0 + CC_WAVES < nt;
+        if (more) {
+            mods = uni64(*reinterpret_cast<const u64*>(st.mod + t0 + CC_WAVES));
+            lims = uni64(*reinterpret_cast<const u64*>(st.limb + t0 + CC_WAVES));
+            op_load(t0 + CC_WAVES);
+        }
+        auto before = [&]() { if (more) op_store(); };
         if (have) {
-            const uint32_t li = (uint32_t)(lims >> (8 * w)) & 255u;
             u64* dst = st.dst + (size_t)rep * cc.dst_stride + ((size_t)li << (LC + 8));
             if constexpr (PTS == 4) {
-                if (cc.wide_fwd >> mi & 1u) c4_target<LC, true>(reg, dst, mi, w4, ln, c0, mc);
-                else c4_target<LC, false>(reg, dst, mi, w4, ln, c0, mc);
-            } else if (cc.wide_fwd >> mi & 1u) cc_target<LC, true>(reg, dst, cc_pin<true>(mi), w1, ln, c0, mc, ftw);
-            else cc_target<LC, false>(reg, dst, cc_pin<false>(mi), w1, ln, c0, mc, ftw);
+                if (cc.wide_fwd >> mi & 1u) c4_target<LC, true>(reg, dst, mi, w4, ln, c0, mc, before);
+                else c4_target<LC, false>(reg, dst, mi, w4, ln, c0, mc, before);
+            } else if (cc.wide_fwd >> mi & 1u) cc_target<LC, true>(reg, dst, cc_pin<true>(mi), w1, ln, c0, mc, ftw, before);
+            else cc_target<LC, false>(reg, dst, cc_pin<false>(mi), w1, ln, c0, mc, ftw, before);
         }
     }
 }
@@ -333,7 +343,7 @@ int32_t launch_col_conv(he_ctx* ctx, ColConv& cc, const ScaleList& sc, uint32_t 
         const ColConvSet& st = cc.set[s];
         rounds = std::max(rounds, (st.nt + CC_WAVES - 1) / CC_WAVES);
         if (st.ns == 0 || st.ns > CC_WAVES || st.nt == 0 || st.nt > HE_MAX_MODULI || st.mod0 + st.ns > ctx->M || st.sc0 + st.ns > HE_MAX_MODULI ||
-            !st.src || !st.dst || !st.digits || !st.bias)
+            !st.src || !st.dst || !st.op)
             return he_fail(ctx, HE_ERR_BADARG, "column conversion: bad group %u", s);
     }
     hipEvent_t e0 = nullptr, e1 = nullptr;

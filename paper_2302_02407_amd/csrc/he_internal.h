@@ -15,6 +15,12 @@ typedef unsigned __int128 u128;
 #define HE_MAX_MODULI 64        // nq + np
 #define HE_MAX_LAUNCH_LIMBS 512 // limbs described by one kernel-argument list
 
+// Moduli whose transforms of N = 2^13 and more take the nine-instruction products (split_acc, modarith.h) and are never reduced on
+// the way: every product's operand has to stay below 2^63, and points reach 90q in 17 forward stages that start below 5q, 640q in
+// eight inverse ones (ntt_blocks.h).  Any other modulus is wide: it takes products with Shoup's companion, and reductions.
+static inline bool narrow_fwd(u64 q) { return q <= (1ull << 63) / 96; }       // all of 56 bits, and up to 2^56.4
+static inline bool narrow_inv(u64 q) { return q <= (1ull << 63) / 640; }      // all of 53 bits, and up to 2^53.6
+
 // Per-modulus constants, resident on the device (array indexed by modulus index).
 struct ModConst {
     u64 q;          // the prime
@@ -45,6 +51,16 @@ struct ScaleList {
     u64 w_sh[HE_MAX_MODULI];
 };
 
+// One target modulus of a conversion on the matrix cores (colconv.hip; filled by conv_operand in keyswitch.hip).  A wavefront loads one as
+// eight bytes a lane and four of the rest a lane.
+struct ConvOperand {
+    uint8_t dig[512];
+    int32_t bias[8];
+    u64 nq;            // -q modulo 2^64
+    uint32_t rec, bits;
+    uint32_t unused[4];
+};
+
 struct ProfSpan {
     hipEvent_t e0, e1;
     uint32_t limbs;   // limbs transformed by the launch between the two events
@@ -64,7 +80,7 @@ struct he_ctx {
     ModConst h_mc[HE_MAX_MODULI];
     // device tables
     ModConst* d_mc;    // [M]
-    ulonglong2* d_tw;  // [M][N]  psi^bitrev(i) and its Shoup companion, one 16-byte load
+    ulonglong2* d_tw;  // [M][N]  psi^bitrev(i) and its companion (Shoup's, or h_tw_split's: ctx.hip), one 16-byte load
     ulonglong2* d_itw; // [M][N]  psi^-bitrev(i), likewise
     double *d_ftw, *d_fitw; // [M][N] the same factors for the FP64 kernels, in their order (ctx.hip, ftw_pos); null elsewhere
     // basis-conversion tables (keyswitch.hip); present when np > 0
@@ -74,8 +90,7 @@ struct he_ctx {
     std::vector<u64> h_dn_invhat; // [np]: (P/p_t)^-1 mod p_t
     // the same constants as operands of the matrix instruction (colconv.hip): [dnum][alpha][M] and [M], null where that path
     // does not apply
-    uint8_t *d_up_dig, *d_dn_dig;   // 512 bytes per modulus
-    int32_t *d_up_bias, *d_dn_bias; // 8 per modulus
+    ConvOperand *d_up_op, *d_dn_op;
     u64* d_pinv;       // [nq] P^-1 mod q_r
     u64* d_pinv_sh;    // [nq] Shoup companions
     // rescale tables: q_l^-1 mod q_r for r < l, [nq][nq]
@@ -99,6 +114,7 @@ u64 h_mulmod(u64 a, u64 b, u64 m);
 u64 h_powmod(u64 a, u64 e, u64 m);
 u64 h_invmod(u64 a, u64 m);
 u64 h_shoup(u64 w, u64 m);
+u64 h_tw_split(u64 w, u64 m);
 uint32_t h_galois_of_step(const he_ctx* ctx, int32_t step);
 
 // Rings whose limb does not fit one work group's LDS: two launches per transform (ntt2p.hip)
@@ -181,7 +197,7 @@ struct KsRows {
     uint32_t count_up, count_down;      // whether the digits' / the ModDown's transforms are counted with these rows
     // set by the launch
     uint32_t logN;
-    u64 above54, above57;               // bit per modulus
+    u64 wide_fwd, wide_inv;             // bit per modulus (narrow_fwd, narrow_inv)
     const ModConst* mc;
     const ulonglong2 *tw, *itw;
 };
@@ -201,7 +217,7 @@ struct TransformDesc {
     const ScaleList* scale;      // inverse only: limb i is multiplied by scale[i % scale_period]
     uint32_t scale_period;       //   (must include N^-1); nullptr = plain N^-1
     const ModDownEpilogue* ep;   // forward only, or nullptr
-    bool lazy_out;               // forward only: outputs may stay below 2q for moduli of at most 57 bits
+    bool lazy_out;               // forward only: outputs may stay below 2q for narrow moduli
                                  // (internal buffers whose consumers allow for it)
     uint32_t only_pass;          // two-launch transforms: 0 = both passes; 1 = the first pass only (inverse: rows, reading the
                                  // sources; forward: columns); 2 = the second pass only, in place at dst
@@ -213,22 +229,21 @@ struct TransformDesc {
 // Basis conversion with the column passes around it (colconv.hip).  Set s (a digit of ModUp; the special primes of ModDown):
 // sources src + rep*src_stride + i*N (i < ns, moduli mod0 + i, output scaling sc entry sc0 + i) in the state the inverse
 // row pass leaves them; target t has modulus mod[t] and is written, in the state the forward column pass leaves it, at
-// dst + rep*dst_stride + limb[t]*N.  digits / bias: conversion constants per modulus (conv_operand).
+// dst + rep*dst_stride + limb[t]*N.  op: conversion constants per modulus.
 // The arrays of bytes start at multiples of 8 and are read eight at a time: a scalar load of a narrower field could be split
 // into a base and an offset register that are each misaligned, whose low bits the hardware drops one by one.
 #define CC_MAX_SETS 8
 struct ColConvSet {
     const u64* src;
     u64* dst;
-    const uint8_t* digits;     // [modulus][512]
-    const int32_t* bias;       // [modulus][8]
+    const ConvOperand* op;     // [modulus]
     uint32_t ns, mod0, sc0, nt;
     uint8_t limb[HE_MAX_MODULI], mod[HE_MAX_MODULI];
 };
 struct ColConv {
     ColConvSet set[CC_MAX_SETS];
     size_t src_stride, dst_stride;
-    u64 wide_fwd, wide_inv;    // bit per modulus: wide in the forward (above 57 bits) / inverse (above 54) ranges
+    u64 wide_fwd, wide_inv;    // bit per modulus: wide in the forward / inverse ranges (narrow_fwd, narrow_inv)
     uint32_t n_sets;
     uint32_t parts, share;     // work groups that share a tile's targets, `share` targets each (set by the launch)
 };
@@ -239,7 +254,7 @@ struct RescaleCols {
     const u64* src;
     u64* dst;
     uint32_t level, parts, share;      // work groups that share a tile's moduli, `share` each (set by the launch)
-    u64 wide;                          // bit per modulus: wide in the forward ranges
+    u64 wide_fwd, wide_inv;            // bit per modulus: wide in the forward / inverse ranges
 };
 bool rescale_cols_pays(const he_ctx* ctx, uint32_t n, uint32_t level);
 int32_t launch_rescale_cols(he_ctx* ctx, const u64* src, u64* dst, uint32_t n, uint32_t level);

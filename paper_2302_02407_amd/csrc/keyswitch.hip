@@ -249,7 +249,9 @@ static uint32_t pad8(uint32_t x) { return (x + 7u) & ~7u; }
 // (i < ns <= 8).  V_(i,a) = hat_i * 2^(8a) mod m, centred, in 8 signed base-256 digits; dig: [digit / 4][digit % 4][byte
 // group of 2 sources][16], bias: base-256 digits of 128 * sum V + 4096 m, which returns the 128 taken from every source
 // byte and keeps the sum from becoming negative (64 products of at most 128 and m/2).
-static void conv_operand(const u64* hat, uint32_t ns, u64 m, uint8_t* dig, int32_t* bias) {
+static void conv_operand(const u64* hat, uint32_t ns, const ModConst& mc, ConvOperand& op) {
+    const u64 m = mc.q;
+    uint8_t* dig = op.dig;
     u64 total = 0;
     for (uint32_t i = 0; i < ns; i++) {
         u64 v = hat[i] % m;
@@ -265,8 +267,11 @@ static void conv_operand(const u64* hat, uint32_t ns, u64 m, uint8_t* dig, int32
         }
     }
     u128 k = (u128)h_mulmod(total, 128, m) + ((u128)m << 12);
-    for (uint32_t b = 0; b < 7; b++) { bias[b] = (int32_t)(k & 0xFF); k >>= 8; }
-    bias[7] = (int32_t)k;
+    for (uint32_t b = 0; b < 7; b++) { op.bias[b] = (int32_t)(k & 0xFF); k >>= 8; }
+    op.bias[7] = (int32_t)k;
+    op.nq = 0 - m;
+    op.rec = mc.rec;
+    op.bits = mc.bits;
 }
 
 int32_t ks_init_tables(he_ctx* c) {
@@ -331,24 +336,18 @@ int32_t ks_init_tables(he_ctx* c) {
     bool operands = two_pass(c) && c->logN <= 16;
     for (uint32_t m = 0; m < M; m++) operands = operands && c->h_mc[m].bits >= 36;
     if (operands && al <= 8) {
-        std::vector<uint8_t> dig((size_t)dn * al * M * 512, 0);
-        std::vector<int32_t> bias((size_t)dn * al * M * 8, 0);
+        std::vector<ConvOperand> op((size_t)dn * al * M, ConvOperand{});
         for (uint32_t sl = 0; sl < dn * al; sl++)
             for (uint32_t m = 0; m < M; m++)
-                conv_operand(&hat[((size_t)sl * M + m) * aw], sl % al + 1, c->mod[m], &dig[((size_t)sl * M + m) * 512], &bias[((size_t)sl * M + m) * 8]);
-        HE_HIP(c, hipMalloc(&c->d_up_dig, dig.size()));
-        HE_HIP(c, hipMalloc(&c->d_up_bias, bias.size() * sizeof(int32_t)));
-        HE_HIP(c, hipMemcpy(c->d_up_dig, dig.data(), dig.size(), hipMemcpyHostToDevice));
-        HE_HIP(c, hipMemcpy(c->d_up_bias, bias.data(), bias.size() * sizeof(int32_t), hipMemcpyHostToDevice));
+                conv_operand(&hat[((size_t)sl * M + m) * aw], sl % al + 1, c->h_mc[m], op[(size_t)sl * M + m]);
+        HE_HIP(c, hipMalloc(&c->d_up_op, op.size() * sizeof(ConvOperand)));
+        HE_HIP(c, hipMemcpy(c->d_up_op, op.data(), op.size() * sizeof(ConvOperand), hipMemcpyHostToDevice));
     }
     if (operands && np <= 8) {
-        std::vector<uint8_t> dig((size_t)M * 512, 0);
-        std::vector<int32_t> bias((size_t)M * 8, 0);
-        for (uint32_t m = 0; m < M; m++) conv_operand(&dhat[(size_t)m * pw], np, c->mod[m], &dig[(size_t)m * 512], &bias[(size_t)m * 8]);
-        HE_HIP(c, hipMalloc(&c->d_dn_dig, dig.size()));
-        HE_HIP(c, hipMalloc(&c->d_dn_bias, bias.size() * sizeof(int32_t)));
-        HE_HIP(c, hipMemcpy(c->d_dn_dig, dig.data(), dig.size(), hipMemcpyHostToDevice));
-        HE_HIP(c, hipMemcpy(c->d_dn_bias, bias.data(), bias.size() * sizeof(int32_t), hipMemcpyHostToDevice));
+        std::vector<ConvOperand> op(M, ConvOperand{});
+        for (uint32_t m = 0; m < M; m++) conv_operand(&dhat[(size_t)m * pw], np, c->h_mc[m], op[m]);
+        HE_HIP(c, hipMalloc(&c->d_dn_op, op.size() * sizeof(ConvOperand)));
+        HE_HIP(c, hipMemcpy(c->d_dn_op, op.data(), op.size() * sizeof(ConvOperand), hipMemcpyHostToDevice));
     }
     HE_HIP(c, hipMalloc(&c->d_up_hat, hat.size() * sizeof(u64)));
     HE_HIP(c, hipMalloc(&c->d_dn_hat, dhat.size() * sizeof(u64)));
@@ -364,10 +363,8 @@ int32_t ks_init_tables(he_ctx* c) {
 void ks_free_tables(he_ctx* c) {
     if (c->d_up_hat) (void)hipFree(c->d_up_hat);
     if (c->d_dn_hat) (void)hipFree(c->d_dn_hat);
-    if (c->d_up_dig) (void)hipFree(c->d_up_dig);
-    if (c->d_up_bias) (void)hipFree(c->d_up_bias);
-    if (c->d_dn_dig) (void)hipFree(c->d_dn_dig);
-    if (c->d_dn_bias) (void)hipFree(c->d_dn_bias);
+    if (c->d_up_op) (void)hipFree(c->d_up_op);
+    if (c->d_dn_op) (void)hipFree(c->d_dn_op);
     if (c->d_pinv) (void)hipFree(c->d_pinv);
     if (c->d_pinv_sh) (void)hipFree(c->d_pinv_sh);
     if (c->d_qlinv) (void)hipFree(c->d_qlinv);
@@ -402,7 +399,7 @@ static uint32_t moddown_most_jobs(const he_ctx* c, uint32_t level) {
 // rotations of 16 ciphertexts 19.0 ms instead of 19.5, 24 with six digits 2.59 instead of 2.66, 45 of 3 sources with six digits
 // 2.33 instead of 2.44.
 static uint32_t engine_most_jobs(const he_ctx* c, uint32_t level) {
-    return ks_rows_path(c, level) && c->d_dn_dig ? HE_MAX_KS_JOBS : moddown_most_jobs(c, level);
+    return ks_rows_path(c, level) && c->d_dn_op ? HE_MAX_KS_JOBS : moddown_most_jobs(c, level);
 }
 
 // How many sources are raised at once and how many jobs share one ModDown launch set.
@@ -453,14 +450,14 @@ size_t ks_engine_ws_elems(const he_ctx* c, uint32_t level, uint32_t n_src, uint3
 
 static void col_conv_widths(const he_ctx* c, ColConv& cc) {
     for (uint32_t m = 0; m < c->M; m++) {
-        cc.wide_fwd |= (u64)(c->h_mc[m].bits > 57) << m;
-        cc.wide_inv |= (u64)(c->h_mc[m].bits > 54) << m;
+        cc.wide_fwd |= (u64)!narrow_fwd(c->mod[m]) << m;
+        cc.wide_inv |= (u64)!narrow_inv(c->mod[m]) << m;
     }
 }
 
 static bool modup_by_columns(const he_ctx* c, uint32_t level) {
     const uint32_t beta = num_digits(c, level);
-    return c->d_up_dig && beta <= CC_MAX_SETS && beta * (level + 1 + c->np) <= HE_MAX_LAUNCH_LIMBS;
+    return c->d_up_op && beta <= CC_MAX_SETS && beta * (level + 1 + c->np) <= HE_MAX_LAUNCH_LIMBS;
 }
 
 // ModUp of `cb` sources at once.  raised [cb][beta][R][N] (own limbs left unwritten), tmp [cb][L1][N].  rows = false: the last
@@ -504,7 +501,7 @@ static int32_t modup_batch(he_ctx* c, const KsSrc* srcs, uint32_t cb, uint32_t l
             const size_t slab = (size_t)(j * al + (sz - 1)) * c->M;
             ColConvSet& st = cc.set[j];
             st.src = tmp + (size_t)lo * N; st.dst = raised + (size_t)j * R * N;
-            st.digits = c->d_up_dig + slab * 512; st.bias = c->d_up_bias + slab * 8;
+            st.op = c->d_up_op + slab;
             st.ns = sz; st.mod0 = lo; st.sc0 = lo;
             for (uint32_t r = 0; r < R; r++) {
                 if (r >= lo && r < hi) continue;
@@ -607,7 +604,7 @@ static int32_t launch_inner_product(he_ctx* c, uint32_t level, const IpBatch& ib
 static int32_t moddown_chain(he_ctx* c, uint32_t level, uint32_t J, u64* acc, u64* tmp_dn, u64* conv, const ModDownEpilogue& ep,
                              KsRows* rows = nullptr) {
     const uint32_t N = c->N, L1 = level + 1, k = c->np, R = L1 + k;
-    const bool cc_on = c->d_dn_dig != nullptr;
+    const bool cc_on = c->d_dn_op != nullptr;
     ScaleList sc;
     for (uint32_t t = 0; t < k; t++) {
         u64 p = c->mod[c->nq + t];
@@ -639,7 +636,7 @@ static int32_t moddown_chain(he_ctx* c, uint32_t level, uint32_t J, u64* acc, u6
         col_conv_widths(c, cc);
         cc.n_sets = 1; cc.src_stride = (size_t)k * N; cc.dst_stride = (size_t)L1 * N;
         ColConvSet& st = cc.set[0];
-        st.src = tmp_dn; st.dst = conv; st.digits = c->d_dn_dig; st.bias = c->d_dn_bias;
+        st.src = tmp_dn; st.dst = conv; st.op = c->d_dn_op;
         st.ns = k; st.mod0 = c->nq; st.sc0 = 0; st.nt = L1;
         for (uint32_t r = 0; r < L1; r++) { st.limb[r] = (uint8_t)r; st.mod[r] = (uint8_t)r; }
         rc = launch_col_conv(c, cc, sc, 2 * J, 2 * J * (k + L1));

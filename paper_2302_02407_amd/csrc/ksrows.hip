@@ -86,11 +86,12 @@ struct KrRow {
     }
 };
 
-// W: 0 = at most 54 bits, 1 = 55 to 57, 2 = wider: the forward ranges of ntt_blocks.h change at 57 bits, the inverse ones at 54.
+// W: 0 = narrow in both directions (ntt_blocks.h), 1 = only forward, 2 = in neither.
 //
 // Both components of the inner products of row b of limb r for one (source, key) term, added to the sums s; `spill`
-// empties them when they hold KS_ROW_PRODUCTS products.  Digits enter as the row transform leaves them where W = 0 (below 73q <
-// 2^60.2: 31-bit high halves, 11 products fit a sum), else below 2q (1) or canonical (2).  buf: a row for each digit, of which
+// empties them when they hold KS_ROW_PRODUCTS products.  Digits enter as the row transform leaves them where W = 0 (below 90q <
+// 2^60.2: 31-bit high halves; seven products with key values below q, together below 2^117, fit the sums and split_reduce), else below
+// 2q (1) or canonical (2).  buf: a row for each digit, of which
 // digits j0, j0 + step .. are worked on (j0 < beta).  AHEAD: the next digit's row and the own one are asked for ahead of their turn.
 template <int W, bool SP, bool AHEAD, class Spill>
 __device__ __forceinline__ void ks_row_products(const KsRows& a, uint32_t id, uint32_t r, uint32_t b, uint32_t t, u64* buf, const ModConst& m, const Row4& at,
@@ -119,6 +120,10 @@ __device__ __forceinline__ void ks_row_products(const KsRows& a, uint32_t id, ui
                 for (int k = 0; k < 4; k++) nx[k] = __builtin_nontemporal_load(&(row + jn * dig_stride)[t + 64 * k]);
             }
             SCHED_FENCE();
+            if (!AHEAD) {                                // the factors' second words are formed anew, not kept in registers
+#pragma unroll
+                for (int i = 0; i < 18; i++) asm("" : "+v"(w[1 + i / 6][i % 6]));
+            }
             row4_fwd<W == 2, 1>(x, w, buf + 256 * j, 256, at, m.q);
 #pragma unroll
             for (int k = 0; k < 4; k++) {
@@ -166,7 +171,7 @@ __device__ __forceinline__ void ks_row_products(const KsRows& a, uint32_t id, ui
     wave_exchange();
 }
 
-// The same from digits that are transformed already (below 2q, canonical for moduli above 57 bits), for components c0 .. c0+NX-1.
+// The same from digits that are transformed already (below 2q, canonical for wide moduli), for components c0 .. c0+NX-1.
 // buf: two rows.  `first` runs while the first digit is on its way.
 template <bool SP, int NX, class Spill, class First>
 __device__ __forceinline__ void ks_row_products_done(const KsRows& a, uint32_t id, uint32_t r, uint32_t b, uint32_t t, u64* buf, KrRow& kr,
@@ -441,11 +446,11 @@ __device__ __forceinline__ void ks_row_group(const KsRows& a, uint32_t job, uint
 }
 
 // W of a modulus, from the argument list: the branch waits for no load of its constants
-__device__ __forceinline__ uint32_t kr_width(const KsRows& a, uint32_t mi) { return (uint32_t)(a.above54 >> mi & 1u) + (uint32_t)(a.above57 >> mi & 1u); }
+__device__ __forceinline__ uint32_t kr_width(const KsRows& a, uint32_t mi) { return (uint32_t)(a.wide_inv >> mi & 1u) + (uint32_t)(a.wide_fwd >> mi & 1u); }
 template <int W>
 __device__ __forceinline__ uint32_t kr_pin(uint32_t v) {     // keeps the widths' loads apart (see ntt2p.hip)
-    if (W == 0) asm("; 54 bits" : "+s"(v));
-    else if (W == 1) asm("; 57 bits" : "+s"(v));
+    if (W == 0) asm("; narrow" : "+s"(v));
+    else if (W == 1) asm("; narrow forward" : "+s"(v));
     else asm("; wide" : "+s"(v));
     return v;
 }
@@ -497,10 +502,10 @@ int32_t launch_ks_rows(he_ctx* ctx, KsRows& a, bool special) {
         a.beta == 0 || a.beta > 8 || ctx->logN < 13 || ctx->logN > 17 || limbs == 0 || limbs > HE_MAX_MODULI)
         return he_fail(ctx, HE_ERR_BADARG, "key-switch rows: bad shape");
     a.mc = ctx->d_mc; a.tw = ctx->d_tw; a.itw = ctx->d_itw; a.logN = ctx->logN;
-    a.above54 = a.above57 = 0;
+    a.wide_fwd = a.wide_inv = 0;
     for (uint32_t i = 0; i < ctx->M; i++) {
-        a.above54 |= (u64)(ctx->h_mc[i].bits > 54) << i;
-        a.above57 |= (u64)(ctx->h_mc[i].bits > 57) << i;
+        a.wide_fwd |= (u64)!narrow_fwd(ctx->mod[i]) << i;
+        a.wide_inv |= (u64)!narrow_inv(ctx->mod[i]) << i;
     }
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (ctx->prof_on) {

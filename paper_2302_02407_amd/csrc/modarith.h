@@ -80,6 +80,48 @@ __device__ __forceinline__ u64 shoup_acc(u64 x, u64 y, u64 w, u64 w_sh, u64 q) {
     return ((u64)hi << 32) | (uint32_t)s;
 }
 
+// ---- products by a factor known in advance, in nine instructions (narrow moduli of the two-launch transforms)
+// w*y = w*y0 + w'*y1 with y = y0 + 2^32 y1 and w' = 2^32 w mod q: the quotient of the sum then fits one word and takes two multiply-adds,
+// h = (a0*y0 + a1*y1) / 2^32, where the quotient of a 64-bit y is two words of three products.  (a0, a1) are the words of floor(w * 2^63 / q)
+// (h_tw_split): one bit less than Shoup's companion, so that the sum of the two products fits 64 bits for every y below 2^63, at
+// the price of a quotient that counts in units of 2q.  w' is 2^32 w - a0 * 2q, below 2q; a1 / 2^31 is then w' / q up to rounding.
+// Error of the quotient in units of q: below 2 for a0 (y0 / 2^31), 1 for a1 (y1 / 2^31), 2 for the division: results below 5q.
+
+// the same value in scalar registers, from which nothing is concluded about its factors
+__device__ __forceinline__ u64 opaque_s(u64 v) {
+    asm("" : "+s"(v));
+    return v;
+}
+// s with h added to its upper word: as one 32-bit addition, which the compiler would widen to 64 bits and a move
+__device__ __forceinline__ u64 add_upper(u64 s, u64 h) {
+    uint32_t r;
+    asm("v_add_u32 %0, %1, %2" : "=v"(r) : "v"((uint32_t)(s >> 32)), "v"((uint32_t)h));
+    return ((u64)r << 32) | (uint32_t)s;
+}
+// w' of a factor; n2q = -2q.  UNI: factor and modulus are the same for the whole wavefront (scalar instructions).
+template <bool UNI>
+__device__ __forceinline__ u64 split_factor(u64 w, u64 a, u64 n2q) {
+    const uint32_t a0 = (uint32_t)(a >> 32);
+    if (UNI) return (w << 32) + (u64)a0 * n2q;
+    u64 h = (u64)a0 * (uint32_t)(n2q >> 32) + w;
+    asm("" : "+v"(h));
+    return add_upper((u64)a0 * (uint32_t)n2q, h);
+}
+// x + (w*y mod q), the product below 5q, for y below 2^63.  Both words are chains of multiply-adds: the upper one's carries are
+// dropped with its upper half.
+__device__ __forceinline__ u64 split_acc(u64 x, u64 y, u64 w, u64 a, u64 wh, u64 n2q) {
+    const uint32_t y0 = (uint32_t)y, y1 = (uint32_t)(y >> 32);
+    const uint32_t h = (uint32_t)(((u64)(uint32_t)(a >> 32) * y0 + (u64)(uint32_t)a * y1) >> 32);
+    u64 s = (u64)(uint32_t)w * y0 + x;
+    s += (u64)(uint32_t)wh * y1;
+    s += (u64)h * (uint32_t)n2q;
+    u64 u = (u64)(uint32_t)(w >> 32) * y0;
+    u += (u64)(uint32_t)(wh >> 32) * y1;
+    u += (u64)h * (uint32_t)(n2q >> 32);
+    asm("" : "+v"(u));
+    return add_upper(s, u);
+}
+
 // w*y mod q in [0, 4q)
 __device__ __forceinline__ u64 shoup_lazy4(u64 y, u64 w, u64 w_sh, u64 q) { return shoup_acc(0, y, w, w_sh, q); }
 

@@ -16,8 +16,8 @@
 // thread after the other (ctx.hip, tw_pos) a load covers 8 cache lines where a thread's own side by side made it 64:
 // inverse row pass of 384 limbs 124 -> 102 us, forward 110 -> 105.
 //
-// Arithmetic: ntt_blocks.h.  Forward values are never reduced inside a transform for moduli below 2^57 (16 or 17 stages end
-// below 73q < 2^64) and once in two stages above; a small-quotient step makes them canonical at the end.
+// Arithmetic: ntt_blocks.h.  Forward values are never reduced inside a transform for narrow moduli (16 or 17 stages end
+// below 90q) and once in two stages for others; a small-quotient step makes them canonical at the end.
 #include <algorithm>
 
 #include "modarith.h"
@@ -110,7 +110,7 @@ __device__ __forceinline__ void col_fwd(const P2Args& a, const LimbTab& tab, uin
 #pragma unroll
         for (int k = 0; k < 16; k++) x[k] = shoup_lazy4(addmod(x[k], h, ml.q), 1, m.one_sh, q) + (q - hr);      // below 5q
     }
-    fwd_stages<WIDE, 0, 4>(x, w1, q);
+    fwd_stages<WIDE, 0, 4, true>(x, w1, q);
 #pragma unroll
     for (int k = 0; k < 16; k++) sm[G::pos(t + (k << G::LT), cl)] = x[k];
     __syncthreads();
@@ -149,7 +149,7 @@ __global__ __launch_bounds__(P2_THREADS, 4) void ntt_col_fwd_kernel(P2Args a, Li
 
 // Inverse column stages and output scaling: inputs below 4q, results canonical.  Stage 0 (one twiddle for the whole limb)
 // carries the scaling: the sum is multiplied by the scale, the difference by scale * twiddle.  Narrow moduli: bounds
-// 4 -> at most 64 (128 for N = 2^17) -> 1024, where the last sum still fits 64 bits.
+// 4 -> at most 64 (128 for N = 2^17) -> 1024, where the last sum still fits 64 bits (its products, which take any value, are Shoup's).
 template <int LC, bool CUSTOM_SCALE, bool WIDE>
 __device__ __forceinline__ void col_inv(const P2Args& a, uint32_t e, uint32_t tile, u64* sm, const ScaleList& sc, uint32_t scale_period) {
     using G = Col<LC>;
@@ -176,7 +176,7 @@ __device__ __forceinline__ void col_inv(const P2Args& a, uint32_t e, uint32_t ti
         if (WIDE) settle4(x, bd, q);
 #pragma unroll
         for (int j = 0; j < 16; j++) sm[G::pos(16 * t + j, cl)] = x[j];
-        after = 4 << (4 - G::U0);
+        after = narrow_after(4, 4 - G::U0);
     } else {
         ulonglong2 w3[15];
         tw_load<3, 4>(w3, tw, 5, t);
@@ -205,7 +205,7 @@ __device__ __forceinline__ void col_inv(const P2Args& a, uint32_t e, uint32_t ti
 #pragma unroll
     for (int k = 0; k < 16; k++) x[k] = sm[G::pos(t + (k << G::LT), cl)];
     bounds_all(bd, WIDE ? 4 : after);
-    inv_stages<WIDE, 1, 4>(x, bd, w1, q);
+    inv_stages<WIDE, 1, 4, true>(x, bd, w1, q);
     if (WIDE) settle4(x, bd, q);
     const u64 bq = WIDE ? 4 * q : 512 * q;
 #pragma unroll
@@ -359,7 +359,7 @@ __global__ __launch_bounds__(P2_THREADS, 4) void ntt_row_fwd_kernel(P2Args a, Li
 
 // ---------------------------------------------------------------- inverse row pass
 // Stages LC+7 .. LC+4 on contiguous points, exchange, stages LC+3 .. LC on strided points: inputs canonical, results below
-// 4q.  Narrow moduli: bounds 1 -> 32 after the first block, -> 512 after the second, one quotient step at the end.
+// 4q (narrow moduli: 2q).  Narrow moduli: bounds 1 -> 40 after the first block, -> 640 after the second, one quotient step at the end.
 // LANES as in row_fwd.
 template <bool WIDE, int LANES>
 __device__ __forceinline__ void row_inv(const P2Args& a, const LimbTab& tab, uint32_t e, uint32_t tile, u64* sm) {
@@ -411,7 +411,7 @@ __device__ __forceinline__ void row_inv(const P2Args& a, const LimbTab& tab, uin
         wave_exchange();
 #pragma unroll
         for (int k = 0; k < 16; k++) x[k] = s[t + 17 * k];
-        bounds_all(bd, WIDE ? 4 : 32);
+        bounds_all(bd, WIDE ? 4 : 40);
         inv_stages<WIDE, 0, 4>(x, bd, w1, q);
         if (WIDE) settle4(x, bd, q);
         else {
@@ -489,7 +489,7 @@ __device__ __forceinline__ void row_run_fwd(const P2Args& a, const LimbTab& tab,
 #pragma unroll
         for (int k = 0; k < 16; k++) x[k] = base[((size_t)dl << logN) + 16 * k];
         SCHED_FENCE();
-        fwd_stages<WIDE, 0, 4>(x, w1, q);
+        fwd_stages<WIDE, 0, 4, true>(x, w1, q);
 #pragma unroll
         for (int k = 0; k < 16; k++) s[t + 17 * k] = x[k];
         wave_exchange();
@@ -556,8 +556,8 @@ __device__ __forceinline__ void row_run_inv(const P2Args& a, const LimbTab& tab,
         wave_exchange();
 #pragma unroll
         for (int k = 0; k < 16; k++) x[k] = s[t + 17 * k];
-        bounds_all(bd, WIDE ? 4 : 32);
-        inv_stages<WIDE, 0, 4>(x, bd, w1, q);
+        bounds_all(bd, WIDE ? 4 : 40);
+        inv_stages<WIDE, 0, 4, true>(x, bd, w1, q);
         if (WIDE) settle4(x, bd, q);
         else {
 #pragma unroll
@@ -615,19 +615,19 @@ __global__ __launch_bounds__(P2_THREADS) void bfly_probe_kernel(const ulonglong2
 int32_t probe_butterfly_rates(he_ctx* ctx, u64* d_out, uint32_t groups, double rate_out[3]) {
     const uint32_t rounds = 64;                          // 32 butterflies per thread per round
     uint32_t narrow = 0, wide = ctx->M;
-    for (uint32_t i = 0; i < ctx->M; i++) if (ctx->h_mc[i].bits > 57) { wide = i; break; }
+    for (uint32_t i = 0; i < ctx->M; i++) if (!narrow_fwd(ctx->mod[i])) { wide = i; break; }
     hipEvent_t e0, e1;
     HE_HIP(ctx, hipEventCreate(&e0));
     HE_HIP(ctx, hipEventCreate(&e1));
     for (int which = 0; which < 3; which++) {
         const uint32_t mi = which == 2 ? wide : narrow;
         rate_out[which] = 0.0;
-        if (mi >= ctx->M || (which != 2 && ctx->h_mc[mi].bits > 57)) continue;
+        if (mi >= ctx->M || (which == 0 && !narrow_fwd(ctx->mod[mi]))) continue;
         const ulonglong2* tw = (which == 1 ? ctx->d_itw : ctx->d_tw) + (size_t)mi * ctx->N;
         for (int rep = 0; rep < 2; rep++) {              // the first launch warms up
             HE_HIP(ctx, hipEventRecord(e0, ctx->stream));
             if (which == 0) hipLaunchKernelGGL((bfly_probe_kernel<true, false>), dim3(groups), dim3(P2_THREADS), 0, ctx->stream, tw, ctx->mod[mi], d_out, rounds);
-            else if (which == 1 && ctx->h_mc[mi].bits > 54) hipLaunchKernelGGL((bfly_probe_kernel<false, true>), dim3(groups), dim3(P2_THREADS), 0, ctx->stream, tw, ctx->mod[mi], d_out, rounds);
+            else if (which == 1 && !narrow_inv(ctx->mod[mi])) hipLaunchKernelGGL((bfly_probe_kernel<false, true>), dim3(groups), dim3(P2_THREADS), 0, ctx->stream, tw, ctx->mod[mi], d_out, rounds);
             else if (which == 1) hipLaunchKernelGGL((bfly_probe_kernel<false, false>), dim3(groups), dim3(P2_THREADS), 0, ctx->stream, tw, ctx->mod[mi], d_out, rounds);
             else hipLaunchKernelGGL((bfly_probe_kernel<true, true>), dim3(groups), dim3(P2_THREADS), 0, ctx->stream, tw, ctx->mod[mi], d_out, rounds);
             HE_HIP(ctx, hipGetLastError());
@@ -673,7 +673,7 @@ int32_t launch_transform2p(he_ctx* ctx, const TransformDesc& d) {
         if (mi == 0xFFu) continue;
         const uint32_t seg = d.src_seg ? d.src_seg[i] : 0, lim = d.src_limb ? d.src_limb[i] : i;
         if (seg >= HE_MAX_SEGS || seg >= d.n_seg || lim >= 4096) return he_fail(ctx, HE_ERR_BADARG, "transform: source limb out of range");
-        tab.e[start[mi]++] = i | (mi << 9) | (lim << 15) | (seg << 27) | (ctx->h_mc[mi].bits > (fwd ? 57u : 54u) ? TAB_WIDE : 0u);
+        tab.e[start[mi]++] = i | (mi << 9) | (lim << 15) | (seg << 27) | ((fwd ? narrow_fwd(ctx->mod[mi]) : narrow_inv(ctx->mod[mi])) ? 0u : TAB_WIDE);
     }
     // Plain row passes by runs of one modulus: fours of limbs, up to 16 in a run, shorter runs where the launch would not
     // fill the chip four times over.  Where more than a quarter of the lanes would have no limb, one limb at a time.
@@ -687,7 +687,7 @@ int32_t launch_transform2p(he_ctx* ctx, const TransformDesc& d) {
         while (piece > 4 && (live / piece) * groups < 4 * 768) piece >>= 1;
         for (uint32_t m = 0, at = 0; m < ctx->M; at += count[m++])
             for (uint32_t i = 0; i < count[m]; i += piece)
-                runs.r[n_runs++] = (at + i) | (std::min(piece, count[m] - i) << 9) | (ctx->h_mc[m].bits > (fwd ? 57u : 54u) ? TAB_WIDE : 0u);
+                runs.r[n_runs++] = (at + i) | (std::min(piece, count[m] - i) << 9) | ((fwd ? narrow_fwd(ctx->mod[m]) : narrow_inv(ctx->mod[m])) ? 0u : TAB_WIDE);
     }
     P2Args a;
     a.dst = d.dst; a.mc = ctx->d_mc;

@@ -1,53 +1,82 @@
 // Register blocks of the radix-2 negacyclic transforms shared by the two-launch kernels, the column conversion and the small-ring kernels:
-// four butterfly stages on 16 points, or two on 4 points, held by one thread (Harvey butterflies, Shoup twiddle
-// products with the three-multiply approximate quotient, lazy ranges).
+// four butterfly stages on 16 points, or two on 4 points, held by one thread (Harvey butterflies, lazy ranges).
 #pragma once
 #include "modarith.h"
 
 #define SCHED_FENCE() __builtin_amdgcn_sched_barrier(0)   // loads above it are issued before the arithmetic below it
 
-// q4 = 4q throughout this file.
-//
 // A butterfly is counted in instructions: on gfx950 the 32-bit multiplies, v_mad_u64_u32 and v_lshl_add_u64 all issue at
 // one per lane and cycle (28-35 T/s measured), so what costs is how many there are.  The product enters the sum through
 // the multiply-adds' own addend (X + w*Y - h*q accumulated in one chain with -q as the factor), and the difference is
-// 2X + 4q minus that sum: 5 instructions for the quotient h, 8 for the sum, 3 for the difference, against 20 for a
-// product formed on its own and then added and subtracted.
+// 2X + c*q minus that sum.  Narrow moduli: two instructions for the quotient h, 7 for the sum, 3 for the difference (split_acc), and
+// 3 for a factor's second word where it is not the same for the whole wavefront (scalar instructions there).  Wide ones: 5, 8 and 3
+// with Shoup's companion.  A product formed on its own and then added and subtracted takes 20.
 //
-// Ranges are kept in units of q and known when the code is compiled: a twiddle product is below 4q whatever its factor,
-// a forward stage therefore adds 4 to the bound of every point, an inverse stage adds the bounds of its two points.  A
-// conditional subtraction is made only where the next sum would leave 64 bits: nowhere for narrow moduli (forward: at
-// most 57 bits, 16 stages end below 69q; inverse: at most 54 bits, a pass ends below 512q), every other forward stage and
-// a few inverse points for wide ones (below 2^60, so that 16q fits).
+// Which moduli are narrow stands at narrow_fwd / narrow_inv (he_internal.h); their factors are stored with h_tw_split's companion, the
+// others' with Shoup's (ctx.hip).
+//
+// Ranges are kept in units of q and known when the code is compiled: a twiddle product is below 5q (narrow) or 4q (wide) whatever
+// its factor, a forward stage therefore adds that to the bound of every point, an inverse stage adds the bounds of its two points.  A
+// conditional subtraction is made only where the next sum would leave 64 bits: nowhere for narrow moduli (forward: 17 stages
+// from below 5q end below 90q; inverse: a pass ends below 640q), every other forward stage and a few inverse points for wide ones
+// (below 2^60, so that 16q fits).
 __device__ __forceinline__ void ct_bfly(u64& X, u64& Y, u64 w, u64 w_sh, u64 q, u64 q4) {
     const u64 S = shoup_acc(X, Y, w, w_sh, q);
     Y = (X + X + q4) - S;
     X = S;
 }
-// The same with X brought below 8q first (wide moduli; inputs below 16q) in every other stage.
-template <bool WIDE>
-__device__ __forceinline__ void ct_bfly_u(int n, u64& X, u64& Y, u64 w, u64 w_sh, u64 q, u64 q4) {
-    if (WIDE && (n & 1) == 0) X = csub_u(X, 2 * q4);
-    ct_bfly(X, Y, w, w_sh, q, q4);
+// what the narrow butterflies need of a modulus, in scalar registers
+struct NarrowQ {
+    u64 n2q, q5;
+    __device__ __forceinline__ explicit NarrowQ(u64 q) : n2q(opaque_s(0 - 2 * q)), q5(opaque_s(5 * q)) {}
+};
+__device__ __forceinline__ void ct_bfly_n(u64& X, u64& Y, u64 w, u64 a, u64 wh, const NarrowQ& n) {
+    const u64 S = split_acc(X, Y, w, a, wh, n.n2q);
+    Y = (X + X + n.q5) - S;
+    X = S;
 }
-
-// Inverse butterfly on points below bx*q and by*q; the bounds of the results replace them.  They are constants of the
-// unrolled code.
-template <bool WIDE>
-__device__ __forceinline__ void gs_bfly(u64& X, u64& Y, int& bx, int& by, u64 w, u64 w_sh, u64 q) {
+// One factor on K pairs of points (X[i], Y[i]), stage n of a block.  Wide moduli: X brought below 8q first in every other stage
+// (inputs below 16q).
+template <bool WIDE, bool UNI, int K, class PX, class PY>
+__device__ __forceinline__ void ct_stage(int n, PX&& X, PY&& Y, u64 w, u64 a, u64 q) {
     if (WIDE) {
 #pragma unroll
-        for (int r = 0; r < 3; r++) {                    // at most three steps are ever needed; constants once unrolled
-            if (bx + by <= 16) continue;
-            if (bx >= by) { const int b = bx > 8 ? 8 : 4; X = csub_u(X, q * b); bx = b; }
-            else { const int b = by > 8 ? 8 : 4; Y = csub_u(Y, q * b); by = b; }
+        for (int k = 0; k < K; k++) {
+            if ((n & 1) == 0) X(k) = csub_u(X(k), 8 * q);
+            ct_bfly(X(k), Y(k), w, a, q, 4 * q);
         }
+    } else {
+        const NarrowQ nq(q);
+        const u64 wh = split_factor<UNI>(w, a, nq.n2q);
+#pragma unroll
+        for (int k = 0; k < K; k++) ct_bfly_n(X(k), Y(k), w, a, wh, nq);
     }
-    const u64 d = (X + q * (u64)by) - Y;
-    X = X + Y;
-    Y = shoup_lazy4(d, w, w_sh, q);
-    bx += by;
-    by = 4;
+}
+
+// Inverse butterflies of one factor on K pairs of points below bx*q and by*q; the bounds of the results replace them.  They are
+// constants of the unrolled code.
+template <bool WIDE, bool UNI, int K, class PX, class PY, class BX, class BY>
+__device__ __forceinline__ void gs_stage(PX&& PX_, PY&& PY_, BX&& bx_, BY&& by_, u64 w, u64 a, u64 q) {
+    const NarrowQ nq(q);
+    const u64 wh = WIDE ? 0 : split_factor<UNI>(w, a, nq.n2q);
+#pragma unroll
+    for (int k = 0; k < K; k++) {
+        u64 &X = PX_(k), &Y = PY_(k);
+        int &bx = bx_(k), &by = by_(k);
+        if (WIDE) {
+#pragma unroll
+            for (int r = 0; r < 3; r++) {                // at most three steps are ever needed; constants once unrolled
+                if (bx + by <= 16) continue;
+                if (bx >= by) { const int b = bx > 8 ? 8 : 4; X = csub_u(X, q * b); bx = b; }
+                else { const int b = by > 8 ? 8 : 4; Y = csub_u(Y, q * b); by = b; }
+            }
+        }
+        const u64 d = (X + q * (u64)by) - Y;
+        X = X + Y;
+        Y = WIDE ? shoup_lazy4(d, w, a, q) : split_acc(0, d, w, a, wh, nq.n2q);
+        bx += by;
+        by = WIDE ? 4 : 5;
+    }
 }
 // Every point of a register block below 4q again (wide moduli, before an exchange mixes the points).
 template <int N>
@@ -59,10 +88,13 @@ __device__ __forceinline__ void settle4(u64 (&x)[N], int (&b)[N], u64 q) {
         b[k] = 4;
     }
 }
+// Bound of every point of narrow inverse blocks of n stages that start below b*q: sums double it, a product is below 5q and may be
+// doubled by the stages behind its own.
+__device__ constexpr int narrow_after(int b, int n) { return (b << n) > (5 << n) / 2 ? b << n : (5 << n) / 2; }
 
 // Register blocks of four stages on 16 points.  Stage u pairs (k, k + (8>>u)); the twiddle of the pair's group g =
 // k >> (4-u) is tw[(1 << (s0+u)) + (G << u) + g], G = group of the 16 points at stage s0, kept at index (1 << u) - 1 + g.
-// A factor and its Shoup companion lie next to each other, one 16-byte load.  Loading is separate from use: a pass that
+// A factor and its companion lie next to each other, one 16-byte load.  Loading is separate from use: a pass that
 // fetched its factors where it needs them spent 40 of 104 us (row pass, 384 limbs) waiting for them.
 template <int U0, int U1>
 __device__ __forceinline__ void tw_load(ulonglong2 (&w)[15], const ulonglong2* __restrict__ tw, uint32_t s0, uint32_t G) {
@@ -83,35 +115,42 @@ __device__ __forceinline__ void tw_load_last(ulonglong2 (&w)[15], const ulonglon
 #pragma unroll
         for (int g = 0; g < (1 << u); g++) w[(1 << u) - 1 + g] = tw[(size_t)((1u << u) - 1u + g) << s0];
 }
-// Forward stages U0 .. U1-1.  Wide moduli: inputs and results below 16q.
-template <bool WIDE, int U0, int U1>
+// Forward stages U0 .. U1-1; UNI: the factors are the same for the whole wavefront.  Wide moduli: inputs and results below 16q.
+template <bool WIDE, int U0, int U1, bool UNI = false>
 __device__ __forceinline__ void fwd_stages(u64 (&x)[16], const ulonglong2 (&w)[15], u64 q) {
-    const u64 q4 = 4 * q;
 #pragma unroll
     for (int u = U0; u < U1; u++) {
         const int dist = 8 >> u;
 #pragma unroll
-        for (int g = 0; g < (1 << u); g++)
-#pragma unroll
-            for (int k = 0; k < dist; k++) {
-                const int a = g * 2 * dist + k;
-                ct_bfly_u<WIDE>(u - U0, x[a], x[a + dist], w[(1 << u) - 1 + g].x, w[(1 << u) - 1 + g].y, q, q4);
-            }
+        for (int g = 0; g < (1 << u); g++) {
+            const ulonglong2 f = w[(1 << u) - 1 + g];
+            auto X = [&](int k) -> u64& { return x[g * 2 * dist + k]; };
+            auto Y = [&](int k) -> u64& { return x[g * 2 * dist + dist + k]; };
+            if (u == 0) ct_stage<WIDE, UNI, 8>(u - U0, X, Y, f.x, f.y, q);
+            else if (u == 1) ct_stage<WIDE, UNI, 4>(u - U0, X, Y, f.x, f.y, q);
+            else if (u == 2) ct_stage<WIDE, UNI, 2>(u - U0, X, Y, f.x, f.y, q);
+            else ct_stage<WIDE, UNI, 1>(u - U0, X, Y, f.x, f.y, q);
+        }
     }
 }
 // Inverse stages U1-1 down to U0, bounds b per point.
-template <bool WIDE, int U0, int U1>
+template <bool WIDE, int U0, int U1, bool UNI = false>
 __device__ __forceinline__ void inv_stages(u64 (&x)[16], int (&b)[16], const ulonglong2 (&w)[15], u64 q) {
 #pragma unroll
     for (int u = U1 - 1; u >= U0; u--) {
         const int dist = 8 >> u;
 #pragma unroll
-        for (int g = 0; g < (1 << u); g++)
-#pragma unroll
-            for (int k = 0; k < dist; k++) {
-                const int a = g * 2 * dist + k;
-                gs_bfly<WIDE>(x[a], x[a + dist], b[a], b[a + dist], w[(1 << u) - 1 + g].x, w[(1 << u) - 1 + g].y, q);
-            }
+        for (int g = 0; g < (1 << u); g++) {
+            const ulonglong2 f = w[(1 << u) - 1 + g];
+            auto X = [&](int k) -> u64& { return x[g * 2 * dist + k]; };
+            auto Y = [&](int k) -> u64& { return x[g * 2 * dist + dist + k]; };
+            auto BX = [&](int k) -> int& { return b[g * 2 * dist + k]; };
+            auto BY = [&](int k) -> int& { return b[g * 2 * dist + dist + k]; };
+            if (u == 0) gs_stage<WIDE, UNI, 8>(X, Y, BX, BY, f.x, f.y, q);
+            else if (u == 1) gs_stage<WIDE, UNI, 4>(X, Y, BX, BY, f.x, f.y, q);
+            else if (u == 2) gs_stage<WIDE, UNI, 2>(X, Y, BX, BY, f.x, f.y, q);
+            else gs_stage<WIDE, UNI, 1>(X, Y, BX, BY, f.x, f.y, q);
+        }
     }
 }
 // the largest bound of a block holds for all of its points once an exchange has mixed them
@@ -121,49 +160,50 @@ __device__ __forceinline__ void bounds_all(int (&b)[N], int v) {
     for (int k = 0; k < N; k++) b[k] = v;
 }
 
-// Two forward / inverse stages on 4 register points (same pairing and twiddle indexing as the 16-point blocks).  Forward:
-// ranges as above.  Inverse: inputs and results below 4q, for any modulus below 2^60.
-template <bool WIDE>
-__device__ __forceinline__ void fwd_block2_r(u64 (&x)[4], const u64 (&r)[6], u64 q, u64 q4) {
-    ct_bfly_u<WIDE>(0, x[0], x[2], r[0], r[1], q, q4);
-    ct_bfly_u<WIDE>(0, x[1], x[3], r[0], r[1], q, q4);
-    ct_bfly_u<WIDE>(1, x[0], x[1], r[2], r[3], q, q4);
-    ct_bfly_u<WIDE>(1, x[2], x[3], r[4], r[5], q, q4);
+// Two forward / inverse stages on 4 register points of NX rows (same pairing and twiddle indexing as the 16-point blocks), factors
+// r = {w0, a0, w1, a1, w2, a2}.  ONE: only the first of the two stages.  Ranges as above.
+template <bool WIDE, bool UNI, int NX, bool ONE = false>
+__device__ __forceinline__ void fwd_block2_x(u64 (&x)[NX][4], const u64 (&r)[6], u64 q) {
+    ct_stage<WIDE, UNI, 2 * NX>(0, [&](int k) -> u64& { return x[k >> 1][k & 1]; }, [&](int k) -> u64& { return x[k >> 1][2 + (k & 1)]; }, r[0], r[1], q);
+    if (ONE) return;
+    ct_stage<WIDE, UNI, NX>(1, [&](int k) -> u64& { return x[k][0]; }, [&](int k) -> u64& { return x[k][1]; }, r[2], r[3], q);
+    ct_stage<WIDE, UNI, NX>(1, [&](int k) -> u64& { return x[k][2]; }, [&](int k) -> u64& { return x[k][3]; }, r[4], r[5], q);
 }
-__device__ __forceinline__ void inv_block2_r(u64 (&x)[4], const u64 (&r)[6], u64 q) {
-    int b[4] = {4, 4, 4, 4};
-    gs_bfly<true>(x[0], x[1], b[0], b[1], r[2], r[3], q);
-    gs_bfly<true>(x[2], x[3], b[2], b[3], r[4], r[5], q);
-    gs_bfly<true>(x[0], x[2], b[0], b[2], r[0], r[1], q);
-    gs_bfly<true>(x[1], x[3], b[1], b[3], r[0], r[1], q);
-    settle4(x, b, q);
+// Inverse: inputs below bound*q.  Narrow: results below narrow_after(bound, 2 or 1 stages) * q; wide: bound 4, results below 4q.
+template <bool WIDE, bool UNI, int NX, bool ONE = false>
+__device__ __forceinline__ void inv_block2_x(u64 (&x)[NX][4], const u64 (&r)[6], u64 q, int bound) {
+    int b[NX][4];
+#pragma unroll
+    for (int i = 0; i < NX; i++)
+#pragma unroll
+        for (int k = 0; k < 4; k++) b[i][k] = WIDE ? 4 : bound;
+    if (!ONE) {
+        gs_stage<WIDE, UNI, NX>([&](int k) -> u64& { return x[k][0]; }, [&](int k) -> u64& { return x[k][1]; },
+                                [&](int k) -> int& { return b[k][0]; }, [&](int k) -> int& { return b[k][1]; }, r[2], r[3], q);
+        gs_stage<WIDE, UNI, NX>([&](int k) -> u64& { return x[k][2]; }, [&](int k) -> u64& { return x[k][3]; },
+                                [&](int k) -> int& { return b[k][2]; }, [&](int k) -> int& { return b[k][3]; }, r[4], r[5], q);
+    }
+    gs_stage<WIDE, UNI, 2 * NX>([&](int k) -> u64& { return x[k >> 1][k & 1]; }, [&](int k) -> u64& { return x[k >> 1][2 + (k & 1)]; },
+                                [&](int k) -> int& { return b[k >> 1][k & 1]; }, [&](int k) -> int& { return b[k >> 1][2 + (k & 1)]; }, r[0], r[1], q);
+    if (WIDE) {
+#pragma unroll
+        for (int i = 0; i < NX; i++) settle4(x[i], b[i], q);
+    }
 }
-// The same for moduli of at most 54 bits, without a reduction: inputs below bound*q, results below 4*bound*q (bound at least 2).
-__device__ __forceinline__ void inv_block2_n(u64 (&x)[4], const u64 (&r)[6], u64 q, int bound) {
-    int b[4] = {bound, bound, bound, bound};
-    gs_bfly<false>(x[0], x[1], b[0], b[1], r[2], r[3], q);
-    gs_bfly<false>(x[2], x[3], b[2], b[3], r[4], r[5], q);
-    gs_bfly<false>(x[0], x[2], b[0], b[2], r[0], r[1], q);
-    gs_bfly<false>(x[1], x[3], b[1], b[3], r[0], r[1], q);
+template <bool WIDE, bool UNI = false, bool ONE = false>
+__device__ __forceinline__ void fwd_block2_r(u64 (&x)[4], const u64 (&r)[6], u64 q) {
+    fwd_block2_x<WIDE, UNI, 1, ONE>(reinterpret_cast<u64 (&)[1][4]>(x), r, q);
 }
-// the three twiddles of such a block (and Shoup companions): r = {w0, w0', w1, w1', w2, w2'}
+template <bool WIDE, bool UNI = false, bool ONE = false>
+__device__ __forceinline__ void inv_block2_r(u64 (&x)[4], const u64 (&r)[6], u64 q, int bound) {
+    inv_block2_x<WIDE, UNI, 1, ONE>(reinterpret_cast<u64 (&)[1][4]>(x), r, q, bound);
+}
+// the three twiddles of such a block and their companions
 __device__ __forceinline__ void tw_block2(u64 (&r)[6], const ulonglong2* tw, uint32_t s0, uint32_t G) {
     const uint32_t b0 = (1u << s0) + G, b1 = (2u << s0) + 2 * G;
     const ulonglong2 w0 = tw[b0], w1 = tw[b1], w2 = tw[b1 + 1];
     r[0] = w0.x; r[1] = w0.y; r[2] = w1.x; r[3] = w1.y; r[4] = w2.x; r[5] = w2.y;
 }
-template <bool WIDE>
-__device__ __forceinline__ void fwd_block2(u64 (&x)[4], const ulonglong2* tw, uint32_t s0, uint32_t G, u64 q, u64 q4) {
-    u64 r[6];
-    tw_block2(r, tw, s0, G);
-    fwd_block2_r<WIDE>(x, r, q, q4);
-}
-__device__ __forceinline__ void inv_block2(u64 (&x)[4], const ulonglong2* tw, uint32_t s0, uint32_t G, u64 q) {
-    u64 r[6];
-    tw_block2(r, tw, s0, G);
-    inv_block2_r(x, r, q);
-}
-
 // lanes of one wavefront exchange through LDS: its own accesses are in order, the compiler has to keep them so
 __device__ __forceinline__ void wave_exchange() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -252,8 +292,8 @@ __device__ __forceinline__ void row4_fwd(u64 (&x)[NX][4], const u64 (&w)[4][6], 
 #pragma unroll
             for (int c = 0; c < NX; c++) at.load(i, x[c], s + c * stride);
         }
-#pragma unroll
-        for (int c = 0; c < NX; c++) fwd_block2_r<WIDE>(x[c], w[i], q, 4 * q);
+        if (i == 0) fwd_block2_x<WIDE, true, NX>(x, w[i], q);            // its factors are the same for the whole row
+        else fwd_block2_x<WIDE, false, NX>(x, w[i], q);
         if (i < 3) {
 #pragma unroll
             for (int c = 0; c < NX; c++) at.store(i, x[c], s + c * stride);
@@ -262,6 +302,7 @@ __device__ __forceinline__ void row4_fwd(u64 (&x)[NX][4], const u64 (&w)[4][6], 
 }
 template <bool WIDE, int NX>
 __device__ __forceinline__ void row4_inv(u64 (&x)[NX][4], const u64 (&w)[4][6], u64* s, uint32_t stride, const Row4& at, u64 q, const ModConst& m) {
+    int bound = 2;                                       // narrow: 2, 10, 40, 160, at the end 640
 #pragma unroll
     for (int i = 3; i >= 0; i--) {
         if (i < 3) {
@@ -269,11 +310,9 @@ __device__ __forceinline__ void row4_inv(u64 (&x)[NX][4], const u64 (&w)[4][6], 
 #pragma unroll
             for (int c = 0; c < NX; c++) at.load(i, x[c], s + c * stride);
         }
-#pragma unroll
-        for (int c = 0; c < NX; c++) {
-            if (WIDE) inv_block2_r(x[c], w[i], q);
-            else inv_block2_n(x[c], w[i], q, 2 << (2 * (3 - i)));
-        }
+        if (i == 0) inv_block2_x<WIDE, true, NX>(x, w[i], q, bound);     // its factors are the same for the whole row
+        else inv_block2_x<WIDE, false, NX>(x, w[i], q, bound);
+        bound = narrow_after(bound, 2);
         if (i) {
 #pragma unroll
             for (int c = 0; c < NX; c++) at.store(i, x[c], s + c * stride);

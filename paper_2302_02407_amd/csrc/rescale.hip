@@ -48,8 +48,10 @@ struct RsTile {
 #pragma unroll
         for (int k = 0; k < 4; k++) buf[word(point(i, k))] = x[k];
     }
-    // points of the last block to points of the first, below 4q before and after
-    __device__ __forceinline__ void inverse(u64 (&x)[4], u64* buf, const u64 (&w)[NB][6], u64 q) const {
+    // points of the last block to points of the first: below 4q before and after for wide moduli, below 2q and 640q for narrow ones
+    template <bool WIDE>
+    __device__ __forceinline__ void inverse(u64 (&x)[4], u64* buf, const u64 (&w)[NB][6], u64 q, const ModConst& m) const {
+        int bound = WIDE ? 4 : 2;
 #pragma unroll
         for (int i = NB - 1; i >= 0; i--) {
             if (i + 1 < NB) {
@@ -57,14 +59,15 @@ struct RsTile {
                 else __syncthreads();
                 load(x, buf, i);
             }
-            if (2 * i + 1 < LC) {
-                inv_block2_r(x, w[i], q);
-            } else {
-                int b[4] = {4, 4, 4, 4};
-                gs_bfly<true>(x[0], x[2], b[0], b[2], w[i][0], w[i][1], q);
-                gs_bfly<true>(x[1], x[3], b[1], b[3], w[i][0], w[i][1], q);
-                settle4(x, b, q);
+            if (!WIDE && LC == 9 && i == 0) {            // nine stages: the last two would leave the range
+#pragma unroll
+                for (int k = 0; k < 4; k++) x[k] = reduce_lazy<10>(x[k], q, m.bits, m.rec);
+                bound = 2;
             }
+            if (2 * i + 1 >= LC) inv_block2_r<WIDE, false, true>(x, w[i], q, bound);
+            else if (i < 2) inv_block2_r<WIDE, true>(x, w[i], q, bound);
+            else inv_block2_r<WIDE>(x, w[i], q, bound);
+            if (!WIDE) bound = narrow_after(bound, 2 * i + 1 >= LC ? 1 : 2);
             if (i) store(buf, x, i);
         }
     }
@@ -77,12 +80,9 @@ struct RsTile {
                 else __syncthreads();
                 load(x, buf, i);
             }
-            if (2 * i + 1 < LC) {
-                fwd_block2_r<WIDE>(x, w[i], q, 4 * q);
-            } else {
-                ct_bfly_u<WIDE>(0, x[0], x[2], w[i][0], w[i][1], q, 4 * q);
-                ct_bfly_u<WIDE>(0, x[1], x[3], w[i][0], w[i][1], q, 4 * q);
-            }
+            if (2 * i + 1 >= LC) fwd_block2_r<WIDE, false, true>(x, w[i], q);
+            else if (i < 2) fwd_block2_r<WIDE, true>(x, w[i], q);
+            else fwd_block2_r<WIDE>(x, w[i], q);
             if (i + 1 < NB) store(buf, x, i);
         }
     }
@@ -106,7 +106,8 @@ __global__ __launch_bounds__(RS_THREADS, 4) void rescale_cols_kernel(RescaleCols
     g.factors(w, itw + ((size_t)rc.level << (LC + 8)));
     const ModConst ml = mod_const(mc, rc.level);
     const u64 h = ml.q >> 1;
-    g.inverse(x, lds + RS_LDS, w, ml.q);
+    if (rc.wide_inv >> rc.level & 1u) g.template inverse<true>(x, lds + RS_LDS, w, ml.q, ml);
+    else g.template inverse<false>(x, lds + RS_LDS, w, ml.q, ml);
     g.factors(w, ftw + ((size_t)r0 << (LC + 8)));
     {
         const const_u64 p = (const_u64)(uintptr_t)uni64((u64)&mc[rc.level].ninv);
@@ -121,7 +122,7 @@ __global__ __launch_bounds__(RS_THREADS, 4) void rescale_cols_kernel(RescaleCols
         u64 y[4], *buf = lds + ((r - r0) & 1u) * RS_LDS;
 #pragma unroll
         for (int k = 0; k < 4; k++) y[k] = shoup_lazy4(x[k], 1, one_sh, q) + up;      // below 5q
-        if (rc.wide >> r & 1u) g.template forward<true>(y, buf, w, q);
+        if (rc.wide_fwd >> r & 1u) g.template forward<true>(y, buf, w, q);
         else g.template forward<false>(y, buf, w, q);
         u64* dst = rc.dst + ((size_t)(limb * rc.level + r) << (LC + 8));
         if (++r < r1) g.factors(w, ftw + ((size_t)r << (LC + 8)));
@@ -141,8 +142,11 @@ bool rescale_cols_pays(const he_ctx* ctx, uint32_t n, uint32_t level) { return (
 int32_t launch_rescale_cols(he_ctx* ctx, const u64* src, u64* dst, uint32_t n, uint32_t level) {
     if (n == 0) return HE_OK;
     if (ctx->logN < 13 || ctx->logN > 17 || level == 0 || level >= ctx->nq) return he_fail(ctx, HE_ERR_BADARG, "rescale columns: bad shape");
-    RescaleCols rc = {src, dst, level, 0, 0, 0};
-    for (uint32_t i = 0; i < level; i++) rc.wide |= (u64)(ctx->h_mc[i].bits > 57) << i;
+    RescaleCols rc = {src, dst, level, 0, 0, 0, 0};
+    for (uint32_t i = 0; i <= level; i++) {
+        rc.wide_fwd |= (u64)!narrow_fwd(ctx->mod[i]) << i;
+        rc.wide_inv |= (u64)!narrow_inv(ctx->mod[i]) << i;
+    }
     // The moduli of a tile are shared out, each share with the inverse columns of its own, while that makes at most three work groups
     // per compute unit: a rescale after a product at level 11 of N = 2^16 117.4 us with up to 768 or 1024, 120.4 with 2048, 123.6 with
     // 256 (a build with more registers); at level 23 206.6, 206.8, 208.8 and 225.

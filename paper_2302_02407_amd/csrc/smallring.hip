@@ -45,13 +45,31 @@ __device__ __forceinline__ void tw_commit(const TwRegs& r, ulonglong2* twl, uint
     }
 }
 
+// Two stages on 4 points, factors with Shoup's companion from the LDS table.  Forward: wide moduli below 16q in and out, others up by 8q.
+// Inverse: below 4q in and out, for any modulus below 2^60.
+template <bool WIDE>
+__device__ __forceinline__ void sr_fwd2(u64 (&x)[4], const ulonglong2* tw, uint32_t s0, uint32_t G, u64 q) {
+    u64 r[6];
+    tw_block2(r, tw, s0, G);
+    if (WIDE) { x[0] = csub_u(x[0], 8 * q); x[1] = csub_u(x[1], 8 * q); }
+    ct_bfly(x[0], x[2], r[0], r[1], q, 4 * q);
+    ct_bfly(x[1], x[3], r[0], r[1], q, 4 * q);
+    ct_bfly(x[0], x[1], r[2], r[3], q, 4 * q);
+    ct_bfly(x[2], x[3], r[4], r[5], q, 4 * q);
+}
+__device__ __forceinline__ void sr_inv2(u64 (&x)[4], const ulonglong2* tw, uint32_t s0, uint32_t G, u64 q) {
+    u64 r[6];
+    tw_block2(r, tw, s0, G);
+    inv_block2_r<true>(x, r, q, 4);
+}
+
 // Forward transform of the whole limb in LDS (decimation in time, psi folded into the twiddles; natural order in,
 // bit-reversed out): register blocks of two stages on 4 points per thread with one LDS exchange between blocks,
 // then one radix-2 stage when logN is odd.  Twiddles from the LDS table.  Inputs below 4q, results canonical.
 // Ends with a barrier.
 template <bool WIDE>
 __device__ __forceinline__ void lds_ntt_fwd_t(u64* sm, const ulonglong2* twl, const ModConst& m, uint32_t logN) {
-    const u64 q = m.q, q2 = 2 * q, q4 = 4 * q;
+    const u64 q = m.q, q2 = 2 * q;
     const uint32_t N = 1u << logN, nb = logN >> 1;
     // the blocks leave values below 52q (never reduced) or, for the widest moduli, below 16q
     for (uint32_t blk = 0; blk < nb; blk++) {
@@ -61,7 +79,7 @@ __device__ __forceinline__ void lds_ntt_fwd_t(u64* sm, const ulonglong2* twl, co
             u64 x[4];
 #pragma unroll
             for (int k = 0; k < 4; k++) x[k] = sm[sp(base + (k << log_span))];
-            fwd_block2<WIDE>(x, twl, s0, G, q, q4);
+            sr_fwd2<WIDE>(x, twl, s0, G, q);
             if (blk + 1 == nb) {
 #pragma unroll
                 for (int k = 0; k < 4; k++) x[k] = reduce_full<7>(x[k], q, m.bits, m.rec);
@@ -112,7 +130,7 @@ __device__ __forceinline__ void lds_ntt_inv(u64* sm, const ulonglong2* twl, cons
             u64 x[4];
 #pragma unroll
             for (int k = 0; k < 4; k++) x[k] = sm[sp(base + (k << log_span))];
-            inv_block2(x, twl, s0, G, q);
+            sr_inv2(x, twl, s0, G, q);
             if (blk == 0) {
 #pragma unroll
                 for (int k = 0; k < 4; k++) x[k] = csub(shoup_lazy(x[k], scale, scale_sh, q), q);
