@@ -26,6 +26,7 @@
 // vector loads and nothing was kept in scratch memory; sets are sixteen now, 290 to 306 us a launch, 48 % of the kernel time
 // of 240 rotations.
 #include <algorithm>
+#include <type_traits>
 
 #include "modarith.h"
 #include "ntt_blocks.h"
@@ -35,9 +36,6 @@
 #define CC_REGION 1088            // LDS words of one limb's tile: 16 runs of 64, 4 spare words after each
 
 typedef int v4i __attribute__((ext_vector_type(4)));
-typedef u64 v2u64 __attribute__((ext_vector_type(2)));
-typedef const __attribute__((address_space(4))) v2u64* ctw_t;      // constant memory: scalar loads also after stores
-typedef const __attribute__((address_space(4))) u64* cu64_t;
 
 // Word of (run k, lane): a lane that holds rows t + k*T of column cl keeps them at run k, lane t*C + cl.
 __device__ __forceinline__ uint32_t cc_word(uint32_t k, uint32_t lane) { return 68 * k + lane; }
@@ -47,17 +45,8 @@ __device__ __forceinline__ uint32_t cc_row(uint32_t r, uint32_t cl) {
     constexpr uint32_t LT = LC - 4, LCOLS = 10 - LC;
     return cc_word(r >> LT, ((r & ((1u << LT) - 1u)) << LCOLS) + cl);
 }
-template <int U0, int U1>
-__device__ __forceinline__ void tw_load_c(ulonglong2 (&w)[15], ctw_t tw, uint32_t s0, uint32_t G) {
-#pragma unroll
-    for (int u = U0; u < U1; u++) {
-        ctw_t p = tw + ((1u << (s0 + u)) + (G << u));
-#pragma unroll
-        for (int g = 0; g < (1 << u); g++) { const v2u64 v = p[g]; w[(1 << u) - 1 + g] = make_ulonglong2(v.x, v.y); }
-    }
-}
 // Inverse column stages of one source limb, output scaling, canonical residues into the limb's LDS region.
-template <int LC, bool WIDE>
+template <int LC, int W>
 __device__ __forceinline__ void cc_source(u64* reg, const u64* src, const ColConv& cc, const ScaleList& sc, uint32_t mi, uint32_t si,
                                           uint32_t lane, uint32_t c0, const ModConst* mc, const ulonglong2* itw) {
     constexpr int LT = LC - 4, LCOLS = 10 - LC, U0 = 8 - LC;
@@ -68,51 +57,47 @@ __device__ __forceinline__ void cc_source(u64* reg, const u64* src, const ColCon
     for (int j = 0; j < 16; j++) x[j] = (src + j * 256)[t * 4096 + c];
     ulonglong2 w1[15], w2[15];
     tw_load_c<U0, 4>(w2, tw, LC - 4, t);
-    const cu64_t mp = (cu64_t)(uintptr_t)(mc + mi);
+    const const_u64 mp = (const_u64)(uintptr_t)(mc + mi);
     const u64 q = uni64(mp[0]);
     const u64 cs = sc.s[si], cs_sh = sc.s_sh[si], cw = sc.w[si], cw_sh = sc.w_sh[si];
-    int bd[16];
-    bounds_all(bd, 4);
-    inv_stages<WIDE, U0, 4>(x, bd, w2, q);
-    if (WIDE) settle4(x, bd, q);
+    int bound = W ? w_half(W) : 2;
+    inv_stages<W, U0, 4>(x, w2, q, bound);
 #pragma unroll
     for (int j = 0; j < 16; j++) reg[cc_row<LC>(16 * t + j, cl)] = x[j];
     tw_load_c<1, 4>(w1, tw, 0, 0);
     wave_exchange();
 #pragma unroll
     for (int k = 0; k < 16; k++) x[k] = reg[cc_word(k, lane)];
-    bounds_all(bd, WIDE ? 4 : narrow_after(4, 4 - U0));
-    inv_stages<WIDE, 1, 4, true>(x, bd, w1, q);
-    if (WIDE) settle4(x, bd, q);
-    const u64 bq = WIDE ? 4 * q : 512 * q;
+    inv_stages<W, 1, 4, true>(x, w1, q, bound);
 #pragma unroll
     for (int k = 0; k < 8; k++) {
         const u64 X = x[k], Y = x[k + 8];
         x[k] = shoup_lazy4(X + Y, cs, cs_sh, q);
-        x[k + 8] = shoup_lazy4((X + bq) - Y, cw, cw_sh, q);
+        x[k + 8] = shoup_lazy4((X + q * (u64)bound) - Y, cw, cw_sh, q);        // any value below 2^64
     }
     // each byte less 128, as the signed operand of the matrix instruction
 #pragma unroll
-    for (int k = 0; k < 16; k++) reg[cc_word(k, lane)] = csub_u(csub_u(x[k], 2 * q), q) ^ 0x8080808080808080ull;
+    for (int k = 0; k < 16; k++) reg[cc_word(k, lane)] = csub_min(csub_min(x[k], 2 * q), q) ^ 0x8080808080808080ull;
     (void)LT;
 }
 
 // Forward column stages of one target limb from its LDS region (below 2q) to memory.
 // `before`: what goes ahead of the stores, for which later loads wait.
-template <int LC, bool WIDE, class Before>
+template <int LC, int W, class Before>
 __device__ __forceinline__ void cc_target(u64* reg, u64* dst, uint32_t mi, const ulonglong2 (&w1)[15], uint32_t lane, uint32_t c0, const ModConst* mc, const ulonglong2* ftw,
                                           Before&& before) {
     constexpr int LCOLS = 10 - LC, U0 = 8 - LC;
     const uint32_t t = lane >> LCOLS, cl = lane & ((1u << LCOLS) - 1u), c = c0 + cl;
     const ctw_t tw = (ctw_t)(uintptr_t)(ftw + ((size_t)mi << (LC + 8)));
-    const cu64_t mp = (cu64_t)(uintptr_t)(mc + mi);
+    const const_u64 mp = (const_u64)(uintptr_t)(mc + mi);
     const u64 q = uni64(mp[0]);
     ulonglong2 w2[15];
     tw_load_c<(U0 < 3 ? U0 : 3), 3>(w2, tw, LC - 4, t);
     u64 x[16];
 #pragma unroll
     for (int k = 0; k < 16; k++) x[k] = reg[cc_word(k, lane)];
-    fwd_stages<WIDE, 0, 4, true>(x, w1, q);
+    int b = 2;
+    fwd_stages<W, 0, 4, true>(x, w1, q, b);
     wave_exchange();
 #pragma unroll
     for (int k = 0; k < 16; k++) reg[cc_word(k, lane)] = x[k];
@@ -121,24 +106,24 @@ __device__ __forceinline__ void cc_target(u64* reg, u64* dst, uint32_t mi, const
     for (int j = 0; j < 16; j++) x[j] = reg[cc_row<LC>(16 * t + j, cl)];
     // the last stage's eight factors arrive in two halves, each into the registers that earlier factors leave: with the
     // source bytes that stay for the next targets there is no room for all of them
-    if (U0 < 2) fwd_stages<WIDE, (U0 < 2 ? U0 : 2), 2>(x, w2, q);
+    if (U0 < 2) fwd_stages<W, (U0 < 2 ? U0 : 2), 2>(x, w2, q, b);
     ctw_t p3 = tw + ((1u << (LC - 1)) + (t << 3));
     v2u64 wa[4], wb[4];
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int g = 0; g < 4; g++) wa[g] = p3[g];
     __builtin_amdgcn_sched_barrier(0);
-    if (U0 < 3) fwd_stages<WIDE, (U0 < 2 ? 2 : U0), (U0 < 3 ? 3 : U0)>(x, w2, q);
+    if (U0 < 3) fwd_stages<W, (U0 < 2 ? 2 : U0), (U0 < 3 ? 3 : U0)>(x, w2, q, b);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int g = 0; g < 4; g++) wb[g] = p3[4 + g];
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int g = 0; g < 4; g++)
-        ct_stage<WIDE, false, 1>(0, [&](int) -> u64& { return x[2 * g]; }, [&](int) -> u64& { return x[2 * g + 1]; }, wa[g].x, wa[g].y, q);
+        ct_stage<W, false, 1>(b, [&](int) -> u64& { return x[2 * g]; }, [&](int) -> u64& { return x[2 * g + 1]; }, wa[g].x, wa[g].y, q);
 #pragma unroll
     for (int g = 0; g < 4; g++)
-        ct_stage<WIDE, false, 1>(0, [&](int) -> u64& { return x[8 + 2 * g]; }, [&](int) -> u64& { return x[9 + 2 * g]; }, wb[g].x, wb[g].y, q);
+        ct_stage<W, false, 1>(b, [&](int) -> u64& { return x[8 + 2 * g]; }, [&](int) -> u64& { return x[9 + 2 * g]; }, wb[g].x, wb[g].y, q);
     before();
 #pragma unroll
     for (int j = 0; j < 16; j++) (dst + j * 256)[t * 4096 + c] = x[j];
@@ -163,7 +148,7 @@ __device__ __forceinline__ void c4_factors(u64 (&w)[4][6], const ulonglong2* tw,
 #pragma unroll
     for (int i = 0; i < C4<LC>::NB; i++) tw_block2(w[i], tw, 2 * i, t >> (6 - 2 * i));
 }
-template <int LC, bool WIDE>
+template <int LC, int W>
 __device__ __forceinline__ void c4_source(u64* reg, const u64* src, const ScaleList& sc, uint32_t mi, uint32_t si, uint32_t t, uint32_t c0,
                                           const ModConst* mc, const ulonglong2* itw) {
     using G = C4<LC>;
@@ -172,7 +157,7 @@ __device__ __forceinline__ void c4_source(u64* reg, const u64* src, const ScaleL
     for (int k = 0; k < 4; k++) x[k] = src[G::at(c4_point(G::NB - 1, t, k), c0)];
     c4_factors<LC>(w, itw + ((size_t)mi << (LC + 8)), t);
     const u64 q = uni64(mc[mi].q), cs = sc.s[si], cs_sh = sc.s_sh[si];
-    int bound = WIDE ? 4 : 2;                            // narrow rows arrive below 2q: 2, 10, 40, 160, at the end 640
+    int bound = W ? w_half(W) : 2;                     // narrow rows arrive below 2q: 2, 10, 40, 160, at the end 640
 #pragma unroll
     for (int i = G::NB - 1; i >= 0; i--) {
         if (i + 1 < G::NB) {
@@ -180,28 +165,28 @@ __device__ __forceinline__ void c4_source(u64* reg, const u64* src, const ScaleL
 #pragma unroll
             for (int k = 0; k < 4; k++) x[k] = reg[c4_word(c4_point(i, t, k))];
         }
-        if (2 * i + 1 >= LC) inv_block2_r<WIDE, false, true>(x, w[i], q, bound);
-        else if (i == 0) inv_block2_r<WIDE, true>(x, w[i], q, bound);         // its factors are the same for the whole limb
-        else inv_block2_r<WIDE>(x, w[i], q, bound);
-        if (!WIDE) bound = narrow_after(bound, 2 * i + 1 >= LC ? 1 : 2);
+        if (2 * i + 1 >= LC) inv_block2_r<W, false, true>(x, w[i], q, bound);
+        else if (i == 0) inv_block2_r<W, true>(x, w[i], q, bound);         // its factors are the same for the whole limb
+        else inv_block2_r<W>(x, w[i], q, bound);
 #pragma unroll
         for (int k = 0; k < 4; k++)
-            reg[c4_word(c4_point(i, t, k))] = i ? x[k] : csub(shoup_lazy(x[k], cs, cs_sh, q), q) ^ 0x8080808080808080ull;
+            reg[c4_word(c4_point(i, t, k))] = i ? x[k] : csub_min(shoup_lazy(x[k], cs, cs_sh, q), q) ^ 0x8080808080808080ull;
     }
 }
-template <int LC, bool WIDE, class Before>
+template <int LC, int W, class Before>
 __device__ __forceinline__ void c4_target(u64* reg, u64* dst, uint32_t mi, const u64 (&w)[4][6], uint32_t t, uint32_t c0, const ModConst* mc, Before&& before) {
     using G = C4<LC>;
     const u64 q = uni64(mc[mi].q);
     u64 x[4];
+    int b = 2;
 #pragma unroll
     for (int i = 0; i < G::NB; i++) {
         if (i) wave_exchange();
 #pragma unroll
         for (int k = 0; k < 4; k++) x[k] = reg[c4_word(c4_point(i, t, k))];
-        if (2 * i + 1 >= LC) fwd_block2_r<WIDE, false, true>(x, w[i], q);
-        else if (i == 0) fwd_block2_r<WIDE, true>(x, w[i], q);                // its factors are the same for the whole limb
-        else fwd_block2_r<WIDE>(x, w[i], q);
+        if (2 * i + 1 >= LC) fwd_block2_r<W, false, true>(x, w[i], q, b);
+        else if (i == 0) fwd_block2_r<W, true>(x, w[i], q, b);                // its factors are the same for the whole limb
+        else fwd_block2_r<W>(x, w[i], q, b);
         if (i + 1 < G::NB) {
 #pragma unroll
             for (int k = 0; k < 4; k++) reg[c4_word(c4_point(i, t, k))] = x[k];
@@ -212,11 +197,19 @@ __device__ __forceinline__ void c4_target(u64* reg, u64* dst, uint32_t mi, const
     for (int k = 0; k < 4; k++) dst[G::at(c4_point(G::NB - 1, t, k), c0)] = x[k];
 }
 
-template <bool WIDE>
-__device__ __forceinline__ uint32_t cc_pin(uint32_t v) {   // keeps the two widths' loads apart (see ntt2p.hip)
-    if (WIDE) asm("; wide" : "+s"(v));
-    else asm("; narrow" : "+s"(v));
-    return v;
+// f(std::integral_constant<int, W>, mi) for the class W of modulus mi, whose copies' loads are kept apart (see ntt2p.hip)
+template <class F>
+__device__ __forceinline__ void cc_class(u64 wide, u64 widest, uint32_t mi, F&& f) {
+    if (!(wide >> mi & 1u)) {
+        asm("; narrow" : "+s"(mi));
+        f(std::integral_constant<int, 0>(), mi);
+    } else if (!(widest >> mi & 1u)) {
+        asm("; wide" : "+s"(mi));
+        f(std::integral_constant<int, 1>(), mi);
+    } else {
+        asm("; widest" : "+s"(mi));
+        f(std::integral_constant<int, 2>(), mi);
+    }
 }
 
 // grid: groups * tiles.  Work groups go to the XCDs round-robin: each XCD gets neighbouring tiles of a group, so that the
@@ -224,6 +217,7 @@ __device__ __forceinline__ uint32_t cc_pin(uint32_t v) {   // keeps the two widt
 template <int LC, int PTS>
 __global__ __launch_bounds__(CC_THREADS, 4) void col_conv_kernel(ColConv cc, ScaleList sc, const ModConst* mc, const ulonglong2* ftw,
                                                                  const ulonglong2* itw) {
+    ieee_off();
     constexpr int LCOLS = (PTS == 16 ? 10 : 8) - LC, TPX = (256 >> LCOLS) / 8;       // tiles of a group per XCD
     constexpr int REGION = PTS == 16 ? CC_REGION : 272, NB = PTS / 2;                // LDS words of a limb's tile, blocks of 16 points per wavefront
     __shared__ u64 lds[CC_WAVES * REGION];
@@ -256,12 +250,10 @@ __global__ __launch_bounds__(CC_THREADS, 4) void col_conv_kernel(ColConv cc, Sca
     if (w < st.ns) {
         const u64* src = st.src + (size_t)rep * cc.src_stride + ((size_t)w << (LC + 8));
         const uint32_t mi = st.mod0 + w;
-        if constexpr (PTS == 4) {
-            if (cc.wide_inv >> mi & 1u) c4_source<LC, true>(reg, src, sc, cc_pin<true>(mi), st.sc0 + w, lane, c0, mc, itw);
-            else c4_source<LC, false>(reg, src, sc, cc_pin<false>(mi), st.sc0 + w, lane, c0, mc, itw);
-        }
-        else if (cc.wide_inv >> mi & 1u) cc_source<LC, true>(reg, src, cc, sc, cc_pin<true>(mi), st.sc0 + w, lane, c0, mc, itw);
-        else cc_source<LC, false>(reg, src, cc, sc, cc_pin<false>(mi), st.sc0 + w, lane, c0, mc, itw);
+        cc_class(cc.wide_inv, cc.widest, mi, [&](auto W, uint32_t m) {
+            if constexpr (PTS == 4) c4_source<LC, W>(reg, src, sc, m, st.sc0 + w, lane, c0, mc, itw);
+            else cc_source<LC, W>(reg, src, cc, sc, m, st.sc0 + w, lane, c0, mc, itw);
+        });
     }
     op_store();
     __syncthreads();
@@ -325,11 +317,10 @@ __global__ __launch_bounds__(CC_THREADS, 4) void col_conv_kernel(ColConv cc, Sca
         auto before = [&]() { if (more) op_store(); };
         if (have) {
             u64* dst = st.dst + (size_t)rep * cc.dst_stride + ((size_t)li << (LC + 8));
-            if constexpr (PTS == 4) {
-                if (cc.wide_fwd >> mi & 1u) c4_target<LC, true>(reg, dst, mi, w4, ln, c0, mc, before);
-                else c4_target<LC, false>(reg, dst, mi, w4, ln, c0, mc, before);
-            } else if (cc.wide_fwd >> mi & 1u) cc_target<LC, true>(reg, dst, cc_pin<true>(mi), w1, ln, c0, mc, ftw, before);
-            else cc_target<LC, false>(reg, dst, cc_pin<false>(mi), w1, ln, c0, mc, ftw, before);
+            cc_class(cc.wide_fwd, cc.widest, mi, [&](auto W, uint32_t m) {
+                if constexpr (PTS == 4) c4_target<LC, W>(reg, dst, m, w4, ln, c0, mc, before);
+                else cc_target<LC, W>(reg, dst, m, w1, ln, c0, mc, ftw, before);
+            });
         }
     }
 }

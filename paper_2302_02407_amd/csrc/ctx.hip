@@ -38,8 +38,9 @@ u64 h_powmod(u64 a, u64 e, u64 m) {
 }
 u64 h_invmod(u64 a, u64 m) { return h_powmod(a % m, m - 2, m); }
 u64 h_shoup(u64 w, u64 m) { return (u64)(((u128)w << 64) / m); }
-// companion of a factor for split_acc (modarith.h): floor(w * 2^63 / m), w < m
-u64 h_tw_split(u64 w, u64 m) { return h_shoup(w, m) >> 1; }
+// Companion of a factor w < m in the tables of a ring: floor(w * 2^63 / m) for split_acc (modarith.h) in the rings of the two-launch
+// transforms, Shoup's floor(w * 2^64 / m) in smaller ones.
+u64 h_companion(uint32_t logN, u64 w, u64 m) { return logN > 12 ? h_shoup(w, m) >> 1 : h_shoup(w, m); }
 
 static bool h_is_prime(u64 n) {
     if (n < 2) return false;
@@ -172,14 +173,13 @@ int32_t he_ctx_create(he_ctx** out, uint32_t logN, const uint64_t* h_q, uint32_t
         u64 psi = h_powmod(g, (m - 1) / (2ull * N), m);
         c->psi[i] = psi;
         u64 ipsi = h_invmod(psi, m);
-        const bool split_f = logN > 12 && narrow_fwd(m), split_i = logN > 12 && narrow_inv(m);
         u64 pw = 1, ipw = 1;
         ulonglong2* t = &tw[(size_t)i * N];
         ulonglong2* it = &itw[(size_t)i * N];
         for (uint32_t e = 0; e < N; e++) {                      // psi^e stored at bitrev(e)
             const uint32_t pos = tw_pos(bitrev(e, logN), logN);
-            t[pos] = make_ulonglong2(pw, split_f ? h_tw_split(pw, m) : h_shoup(pw, m));
-            it[pos] = make_ulonglong2(ipw, split_i ? h_tw_split(ipw, m) : h_shoup(ipw, m));
+            t[pos] = make_ulonglong2(pw, h_companion(logN, pw, m));
+            it[pos] = make_ulonglong2(ipw, h_companion(logN, ipw, m));
             pw = h_mulmod(pw, psi, m);
             ipw = h_mulmod(ipw, ipsi, m);
         }

@@ -15,11 +15,12 @@ typedef unsigned __int128 u128;
 #define HE_MAX_MODULI 64        // nq + np
 #define HE_MAX_LAUNCH_LIMBS 512 // limbs described by one kernel-argument list
 
-// Moduli whose transforms of N = 2^13 and more take the nine-instruction products (split_acc, modarith.h) and are never reduced on
+// Moduli whose points are never reduced inside the transforms of N = 2^13 and more (products: split_acc, modarith.h) on
 // the way: every product's operand has to stay below 2^63, and points reach 90q in 17 forward stages that start below 5q, 640q in
-// eight inverse ones (ntt_blocks.h).  Any other modulus is wide: it takes products with Shoup's companion, and reductions.
+// eight inverse ones (ntt_blocks.h).  Any other modulus is wide and takes conditional subtractions, more of them the widest ones.
 static inline bool narrow_fwd(u64 q) { return q <= (1ull << 63) / 96; }       // all of 56 bits, and up to 2^56.4
 static inline bool narrow_inv(u64 q) { return q <= (1ull << 63) / 640; }      // all of 53 bits, and up to 2^53.6
+static inline bool widest(u64 q) { return q > (1ull << 63) / 13; }            // above 2^59.29
 
 // Per-modulus constants, resident on the device (array indexed by modulus index).
 struct ModConst {
@@ -80,7 +81,7 @@ struct he_ctx {
     ModConst h_mc[HE_MAX_MODULI];
     // device tables
     ModConst* d_mc;    // [M]
-    ulonglong2* d_tw;  // [M][N]  psi^bitrev(i) and its companion (Shoup's, or h_tw_split's: ctx.hip), one 16-byte load
+    ulonglong2* d_tw;  // [M][N]  psi^bitrev(i) and its companion (h_companion), one 16-byte load
     ulonglong2* d_itw; // [M][N]  psi^-bitrev(i), likewise
     double *d_ftw, *d_fitw; // [M][N] the same factors for the FP64 kernels, in their order (ctx.hip, ftw_pos); null elsewhere
     // basis-conversion tables (keyswitch.hip); present when np > 0
@@ -92,7 +93,7 @@ struct he_ctx {
     // does not apply
     ConvOperand *d_up_op, *d_dn_op;
     u64* d_pinv;       // [nq] P^-1 mod q_r
-    u64* d_pinv_sh;    // [nq] Shoup companions
+    u64* d_pinv_sh;    // [nq] companions (h_companion)
     // rescale tables: q_l^-1 mod q_r for r < l, [nq][nq]
     u64* d_qlinv;
     u64* d_qlinv_sh;
@@ -114,7 +115,7 @@ u64 h_mulmod(u64 a, u64 b, u64 m);
 u64 h_powmod(u64 a, u64 e, u64 m);
 u64 h_invmod(u64 a, u64 m);
 u64 h_shoup(u64 w, u64 m);
-u64 h_tw_split(u64 w, u64 m);
+u64 h_companion(uint32_t logN, u64 w, u64 m);
 uint32_t h_galois_of_step(const he_ctx* ctx, int32_t step);
 
 // Rings whose limb does not fit one work group's LDS: two launches per transform (ntt2p.hip)
@@ -197,7 +198,7 @@ struct KsRows {
     uint32_t count_up, count_down;      // whether the digits' / the ModDown's transforms are counted with these rows
     // set by the launch
     uint32_t logN;
-    u64 wide_fwd, wide_inv;             // bit per modulus (narrow_fwd, narrow_inv)
+    u64 wide_fwd, wide_inv, widest;     // bit per modulus (narrow_fwd, narrow_inv, widest)
     const ModConst* mc;
     const ulonglong2 *tw, *itw;
 };
@@ -243,7 +244,7 @@ struct ColConvSet {
 struct ColConv {
     ColConvSet set[CC_MAX_SETS];
     size_t src_stride, dst_stride;
-    u64 wide_fwd, wide_inv;    // bit per modulus: wide in the forward / inverse ranges (narrow_fwd, narrow_inv)
+    u64 wide_fwd, wide_inv, widest;    // bit per modulus (narrow_fwd, narrow_inv, widest)
     uint32_t n_sets;
     uint32_t parts, share;     // work groups that share a tile's targets, `share` targets each (set by the launch)
 };
@@ -254,7 +255,7 @@ struct RescaleCols {
     const u64* src;
     u64* dst;
     uint32_t level, parts, share;      // work groups that share a tile's moduli, `share` each (set by the launch)
-    u64 wide_fwd, wide_inv;            // bit per modulus: wide in the forward / inverse ranges
+    u64 wide_fwd, wide_inv, widest;    // bit per modulus (narrow_fwd, narrow_inv, widest)
 };
 bool rescale_cols_pays(const he_ctx* ctx, uint32_t n, uint32_t level);
 int32_t launch_rescale_cols(he_ctx* ctx, const u64* src, u64* dst, uint32_t n, uint32_t level);

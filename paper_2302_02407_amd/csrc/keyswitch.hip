@@ -284,7 +284,7 @@ int32_t ks_init_tables(he_ctx* c) {
                 if (r == l) continue;
                 u64 v = h_invmod(c->mod[l] % c->mod[r], c->mod[r]);
                 inv[(size_t)l * nq + r] = v;
-                inv_sh[(size_t)l * nq + r] = h_shoup(v, c->mod[r]);
+                inv_sh[(size_t)l * nq + r] = h_companion(c->logN, v, c->mod[r]);
             }
         size_t b = inv.size() * sizeof(u64);
         HE_HIP(c, hipMalloc(&c->d_qlinv, b));
@@ -330,7 +330,7 @@ int32_t ks_init_tables(he_ctx* c) {
         u64 P = 1;
         for (uint32_t k = 0; k < np; k++) P = h_mulmod(P, c->mod[nq + k] % c->mod[r], c->mod[r]);
         pinv[r] = h_invmod(P, c->mod[r]);
-        pinv_sh[r] = h_shoup(pinv[r], c->mod[r]);
+        pinv_sh[r] = h_companion(c->logN, pinv[r], c->mod[r]);
     }
     // operands of the fused column conversion: rings of 2^13 .. 2^16, at most 8 sources, moduli of at least 36 bits
     bool operands = two_pass(c) && c->logN <= 16;
@@ -452,6 +452,7 @@ static void col_conv_widths(const he_ctx* c, ColConv& cc) {
     for (uint32_t m = 0; m < c->M; m++) {
         cc.wide_fwd |= (u64)!narrow_fwd(c->mod[m]) << m;
         cc.wide_inv |= (u64)!narrow_inv(c->mod[m]) << m;
+        cc.widest |= (u64)widest(c->mod[m]) << m;
     }
 }
 

@@ -86,12 +86,15 @@ struct KrRow {
     }
 };
 
-// W: 0 = narrow in both directions (ntt_blocks.h), 1 = only forward, 2 = in neither.
+// W: 0 = narrow in both directions (ntt_blocks.h), 1 = only forward, 2 = in neither, 3 = the widest.
+__device__ constexpr int kr_fwd(int W) { return W < 2 ? 0 : W - 1; }      // classes of the transforms
+__device__ constexpr int kr_inv(int W) { return W == 0 ? 0 : W == 3 ? 2 : 1; }
+
 //
 // Both components of the inner products of row b of limb r for one (source, key) term, added to the sums s; `spill`
 // empties them when they hold KS_ROW_PRODUCTS products.  Digits enter as the row transform leaves them where W = 0 (below 90q <
 // 2^60.2: 31-bit high halves; seven products with key values below q, together below 2^117, fit the sums and split_reduce), else below
-// 2q (1) or canonical (2).  buf: a row for each digit, of which
+// 2q (1) or canonical (2, 3).  buf: a row for each digit, of which
 // digits j0, j0 + step .. are worked on (j0 < beta).  AHEAD: the next digit's row and the own one are asked for ahead of their turn.
 template <int W, bool SP, bool AHEAD, class Spill>
 __device__ __forceinline__ void ks_row_products(const KsRows& a, uint32_t id, uint32_t r, uint32_t b, uint32_t t, u64* buf, const ModConst& m, const Row4& at,
@@ -124,11 +127,11 @@ __device__ __forceinline__ void ks_row_products(const KsRows& a, uint32_t id, ui
 #pragma unroll
                 for (int i = 0; i < 18; i++) asm("" : "+v"(w[1 + i / 6][i % 6]));
             }
-            row4_fwd<W == 2, 1>(x, w, buf + 256 * j, 256, at, m.q);
+            row4_fwd<kr_fwd(W), 1>(x, w, buf + 256 * j, 256, at, m.q);
 #pragma unroll
             for (int k = 0; k < 4; k++) {
                 if (W == 1) x[0][k] = reduce_lazy<7>(x[0][k], m.q, m.bits, m.rec);
-                if (W == 2) x[0][k] = reduce_full<7>(x[0][k], m.q, m.bits, m.rec);
+                if (W >= 2) x[0][k] = reduce_min<7>(x[0][k], m.q, m.bits, m.rec);
             }
             wave_exchange();
             at.store(3, x[0], buf + 256 * j);
@@ -224,7 +227,7 @@ __device__ __forceinline__ void ks_row_special(const KsRows& a, uint32_t job, ui
 #pragma unroll
     for (int c = 0; c < NX; c++) at.load(3, v[c], buf + 256 * c);
     wave_exchange();
-    row4_inv<W >= 1, NX>(v, w, buf, 256, at, m.q, m);
+    row4_inv<kr_inv(W), NX>(v, w, buf, 256, at, m.q, m);
     u64* out = a.mid + ((size_t)((2 * job + c0) * a.k + r) << a.logN) + b * 256;
 #pragma unroll
     for (int c = 0; c < NX; c++)
@@ -265,7 +268,7 @@ __device__ __forceinline__ bool kr_raw(const ModConst& m) { return W < 2 && m.bi
 template <int W, int NX>
 __device__ __forceinline__ void ks_row_transformed(u64 (&cv)[NX][4], u64* buf, const ModConst& m, const Row4& at, const KrRow& kr, const u64 (&w)[4][6]) {
     SCHED_FENCE();
-    row4_fwd<W == 2, NX>(cv, w, buf, 256, at, m.q);
+    row4_fwd<kr_fwd(W), NX>(cv, w, buf, 256, at, m.q);
     const bool raw = kr_raw<W>(m);
     wave_exchange();
 #pragma unroll
@@ -286,10 +289,11 @@ __device__ __forceinline__ void ks_row_down(const KsRows& a, uint32_t job, uint3
                                             const KrRow& kr, u64 (&cv)[NX][4], const u64 (&v)[NX][4], KrAdd<NX>& ad) {
     const uint32_t row0 = b * 256;
     const size_t qo = (size_t)r << a.logN;
-    // out = (acc - conv) * P^-1 + addends: the product is below 4q whatever its factor, so the transform value may stay as it is
-    // where 128q plus the accumulator fits 64 bits, else below 2q; the sum is below 6q
+    // out = (acc - conv) * P^-1 + addends: the product is below 5q whatever its factor, so the transform value may stay as it is
+    // where 128q plus the accumulator (below 6q) fits 63 bits, else below 2q; the sum is below 7q
     const bool raw = kr_raw<W>(m);
     const u64 bias = raw ? (m.q << 7) : 2 * m.q, pinv = ((const_u64)(uintptr_t)a.pinv)[r], pinv_sh = ((const_u64)(uintptr_t)a.pinv_sh)[r];
+    const u64 n2q = opaque_s(0 - 2 * m.q), pinv_h = split_factor<true>(pinv, pinv_sh, n2q);
     if (ad.rotated) {
         kr.put(buf, ad.rot);
         wave_exchange();
@@ -302,7 +306,7 @@ __device__ __forceinline__ void ks_row_down(const KsRows& a, uint32_t job, uint3
         u64 o[4];
 #pragma unroll
         for (int k = 0; k < 4; k++)
-            o[k] = reduce_full<7>(shoup_acc(ad.add[c][k], v[c][k] + bias - cv[c][k], pinv, pinv_sh, m.q), m.q, m.bits, m.rec);
+            o[k] = reduce_min<7>(split_acc(ad.add[c][k], v[c][k] + bias - cv[c][k], pinv, pinv_sh, pinv_h, n2q), m.q, m.bits, m.rec);
         store2_stream(out, o[0], o[1]);
         store2_stream(out + 128, o[2], o[3]);
     }
@@ -446,18 +450,20 @@ __device__ __forceinline__ void ks_row_group(const KsRows& a, uint32_t job, uint
 }
 
 // W of a modulus, from the argument list: the branch waits for no load of its constants
-__device__ __forceinline__ uint32_t kr_width(const KsRows& a, uint32_t mi) { return (uint32_t)(a.wide_inv >> mi & 1u) + (uint32_t)(a.wide_fwd >> mi & 1u); }
+__device__ __forceinline__ uint32_t kr_width(const KsRows& a, uint32_t mi) { return (uint32_t)(a.wide_inv >> mi & 1u) + (uint32_t)(a.wide_fwd >> mi & 1u) + (uint32_t)(a.widest >> mi & 1u); }
 template <int W>
 __device__ __forceinline__ uint32_t kr_pin(uint32_t v) {     // keeps the widths' loads apart (see ntt2p.hip)
     if (W == 0) asm("; narrow" : "+s"(v));
     else if (W == 1) asm("; narrow forward" : "+s"(v));
-    else asm("; wide" : "+s"(v));
+    else if (W == 2) asm("; wide" : "+s"(v));
+    else asm("; widest" : "+s"(v));
     return v;
 }
 
 // A wavefront per (limb, row, job), jobs fastest; each XCD works on every eighth (limb, row).
 template <bool SP, bool MANY, bool DONE>
 __global__ __launch_bounds__(KR_THREADS, MANY ? 3 : 4) void ks_rows_kernel(KsRows a) {
+    ieee_off();
     extern __shared__ __attribute__((aligned(16))) u64 sm[];
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), rows = a.logN - 8;
     const uint32_t item = (blockIdx.x >> 3) * KR_WAVES + wave, un = item / a.J, job = item - un * a.J;
@@ -467,11 +473,13 @@ __global__ __launch_bounds__(KR_THREADS, MANY ? 3 : 4) void ks_rows_kernel(KsRow
     const uint32_t width = kr_width(a, SP ? a.nq + r : r), t = threadIdx.x & 63u;
     if (width == 0) ks_row<0, SP, MANY, DONE>(a, job, kr_pin<0>(r), b, t, buf);
     else if (width == 1) ks_row<1, SP, MANY, DONE>(a, job, kr_pin<1>(r), b, t, buf);
-    else ks_row<2, SP, MANY, DONE>(a, job, kr_pin<2>(r), b, t, buf);
+    else if (width == 2) ks_row<2, SP, MANY, DONE>(a, job, kr_pin<2>(r), b, t, buf);
+    else ks_row<3, SP, MANY, DONE>(a, job, kr_pin<3>(r), b, t, buf);
 }
 // A wavefront per (limb, row, job, component).
 template <bool SP>
 __global__ __launch_bounds__(KR_THREADS, 4) void ks_rows_half_kernel(KsRows a) {
+    ieee_off();
     __shared__ __attribute__((aligned(16))) u64 sm[KR_WAVES * 512];
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), rows = a.logN - 8, t = threadIdx.x & 63u;
     const uint32_t at = (blockIdx.x >> 3) * KR_WAVES + wave, item = at >> 1, un = item / a.J, job = item - un * a.J;
@@ -481,11 +489,13 @@ __global__ __launch_bounds__(KR_THREADS, 4) void ks_rows_half_kernel(KsRows a) {
     const uint32_t width = kr_width(a, SP ? a.nq + r : r);
     if (width == 0) ks_row_half<0, SP>(a, job, at & 1u, kr_pin<0>(r), b, t, buf);
     else if (width == 1) ks_row_half<1, SP>(a, job, at & 1u, kr_pin<1>(r), b, t, buf);
-    else ks_row_half<2, SP>(a, job, at & 1u, kr_pin<2>(r), b, t, buf);
+    else if (width == 2) ks_row_half<2, SP>(a, job, at & 1u, kr_pin<2>(r), b, t, buf);
+    else ks_row_half<3, SP>(a, job, at & 1u, kr_pin<3>(r), b, t, buf);
 }
 // A work group per (limb, row) of a sum, or per (limb, row, job).
 template <bool SP, bool SUM, bool DONE>
 __global__ __launch_bounds__(KR_THREADS, SUM && DONE ? 2 : 3) void ks_rows_group_kernel(KsRows a) {
+    ieee_off();
     extern __shared__ __attribute__((aligned(16))) u64 sm[];
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = blockDim.x >> 6, rows = a.logN - 8, t = threadIdx.x & 63u;
     const uint32_t item = blockIdx.x >> 3, un = item / a.J, job = item - un * a.J;
@@ -493,7 +503,8 @@ __global__ __launch_bounds__(KR_THREADS, SUM && DONE ? 2 : 3) void ks_rows_group
     const uint32_t width = kr_width(a, SP ? a.nq + r : r);
     if (width == 0) ks_row_group<0, SP, SUM, DONE>(a, job, kr_pin<0>(r), b, wave, nw, t, sm);
     else if (width == 1) ks_row_group<1, SP, SUM, DONE>(a, job, kr_pin<1>(r), b, wave, nw, t, sm);
-    else ks_row_group<2, SP, SUM, DONE>(a, job, kr_pin<2>(r), b, wave, nw, t, sm);
+    else if (width == 2) ks_row_group<2, SP, SUM, DONE>(a, job, kr_pin<2>(r), b, wave, nw, t, sm);
+    else ks_row_group<3, SP, SUM, DONE>(a, job, kr_pin<3>(r), b, wave, nw, t, sm);
 }
 
 int32_t launch_ks_rows(he_ctx* ctx, KsRows& a, bool special) {
@@ -502,10 +513,11 @@ int32_t launch_ks_rows(he_ctx* ctx, KsRows& a, bool special) {
         a.beta == 0 || a.beta > 8 || ctx->logN < 13 || ctx->logN > 17 || limbs == 0 || limbs > HE_MAX_MODULI)
         return he_fail(ctx, HE_ERR_BADARG, "key-switch rows: bad shape");
     a.mc = ctx->d_mc; a.tw = ctx->d_tw; a.itw = ctx->d_itw; a.logN = ctx->logN;
-    a.wide_fwd = a.wide_inv = 0;
+    a.wide_fwd = a.wide_inv = a.widest = 0;
     for (uint32_t i = 0; i < ctx->M; i++) {
         a.wide_fwd |= (u64)!narrow_fwd(ctx->mod[i]) << i;
         a.wide_inv |= (u64)!narrow_inv(ctx->mod[i]) << i;
+        a.widest |= (u64)widest(ctx->mod[i]) << i;
     }
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (ctx->prof_on) {

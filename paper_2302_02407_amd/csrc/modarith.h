@@ -47,6 +47,29 @@ __device__ __forceinline__ u64 uni64(u64 v) {
 }
 __device__ __forceinline__ u64 csub_u(u64 x, u64 q) { return mask_add(x + neg_u(q), q); }
 
+// x >= q ? x - q : x for x < 2^63 in two instructions: the smaller of x and the difference, taken as doubles, which order bit patterns
+// below 2^63 as the integers they are.  Where the difference is negative, clearing its sign leaves 2^63 - (q - x), which is above x
+// or not a number, and the minimum of a number and none is the number.  For signalling ones that holds with the wavefront's IEEE mode
+// off: kernels that use this start with ieee_off().  q: the same for the whole wavefront.
+__device__ __forceinline__ void ieee_off() { asm volatile("s_setreg_imm32_b32 hwreg(HW_REG_MODE, 9, 1), 0"); }
+__device__ __forceinline__ u64 csub_min(u64 x, u64 q) {
+    u64 r;
+    asm("v_min_f64 %0, |%1|, %2" : "=v"(r) : "v"(x + neg_u(q)), "v"(x));
+    return r;
+}
+
+// the same value in scalar registers, from which nothing is concluded about its factors
+__device__ __forceinline__ u64 opaque_s(u64 v) {
+    asm("" : "+s"(v));
+    return v;
+}
+// s with h added to its upper word: as one 32-bit addition, which the compiler would widen to 64 bits and a move
+__device__ __forceinline__ u64 add_upper(u64 s, u64 h) {
+    uint32_t r;
+    asm("v_add_u32 %0, %1, %2" : "=v"(r) : "v"((uint32_t)(s >> 32)), "v"((uint32_t)h));
+    return ((u64)r << 32) | (uint32_t)s;
+}
+
 // High word of a*b from three 32x32 products (the low*low product and the carries out of the
 // middle column are dropped): never above the true value, at most 2 below it.  The last 32-bit term is added by a
 // multiply-add with the factor 1, which takes it as it is; written as an addition it is widened to a register pair first,
@@ -87,17 +110,6 @@ __device__ __forceinline__ u64 shoup_acc(u64 x, u64 y, u64 w, u64 w_sh, u64 q) {
 // the price of a quotient that counts in units of 2q.  w' is 2^32 w - a0 * 2q, below 2q; a1 / 2^31 is then w' / q up to rounding.
 // Error of the quotient in units of q: below 2 for a0 (y0 / 2^31), 1 for a1 (y1 / 2^31), 2 for the division: results below 5q.
 
-// the same value in scalar registers, from which nothing is concluded about its factors
-__device__ __forceinline__ u64 opaque_s(u64 v) {
-    asm("" : "+s"(v));
-    return v;
-}
-// s with h added to its upper word: as one 32-bit addition, which the compiler would widen to 64 bits and a move
-__device__ __forceinline__ u64 add_upper(u64 s, u64 h) {
-    uint32_t r;
-    asm("v_add_u32 %0, %1, %2" : "=v"(r) : "v"((uint32_t)(s >> 32)), "v"((uint32_t)h));
-    return ((u64)r << 32) | (uint32_t)s;
-}
 // w' of a factor; n2q = -2q.  UNI: factor and modulus are the same for the whole wavefront (scalar instructions).
 template <bool UNI>
 __device__ __forceinline__ u64 split_factor(u64 w, u64 a, u64 n2q) {
@@ -204,4 +216,9 @@ __device__ __forceinline__ u64 reduce_lazy(u64 v, u64 q, uint32_t bits, uint32_t
 template <int LOGV>
 __device__ __forceinline__ u64 reduce_full(u64 v, u64 q, uint32_t bits, uint32_t rec) {
     return csub(reduce_lazy<LOGV>(v, q, bits, rec), q);
+}
+// the same for a q of the whole wavefront, after ieee_off()
+template <int LOGV>
+__device__ __forceinline__ u64 reduce_min(u64 v, u64 q, uint32_t bits, uint32_t rec) {
+    return csub_min(reduce_lazy<LOGV>(v, q, bits, rec), q);
 }

@@ -17,8 +17,9 @@
 // inverse row pass of 384 limbs 124 -> 102 us, forward 110 -> 105.
 //
 // Arithmetic: ntt_blocks.h.  Forward values are never reduced inside a transform for narrow moduli (16 or 17 stages end
-// below 90q) and once in two stages for others; a small-quotient step makes them canonical at the end.
+// below 90q); a small-quotient step makes them canonical at the end.
 #include <algorithm>
+#include <type_traits>
 
 #include "modarith.h"
 #include "ntt_blocks.h"
@@ -43,14 +44,22 @@ struct P2Args {
     uint32_t lazy;            // forward, last pass: outputs may stay below 2q
     uint32_t rs_mod;          // forward, first pass reading the Rescale rounding term: modulus index of the dropped limb
     uint32_t log_chunk;       // row passes, see row_decode
+    u64 widest;               // bit per modulus
 };
-// Keeps the loads of the two width branches apart: merged above the branch (they look alike) they would stay live across
-// all of it, 240 registers instead of 109.
-template <bool WIDE>
-__device__ __forceinline__ uint32_t branch_pin(uint32_t e) {
-    if (WIDE) asm("; wide" : "+s"(e));
-    else asm("; narrow" : "+s"(e));
-    return e;
+// f(std::integral_constant<int, W>, e) for the class W of the modulus of entry e.  Keeps the loads of the branches apart: merged above
+// them (they look alike) they would stay live across all of it, 240 registers instead of 109.
+template <class F>
+__device__ __forceinline__ void by_class(u64 widest, uint32_t mi, uint32_t e, F&& f) {
+    if (!(e & TAB_WIDE)) {
+        asm("; narrow" : "+s"(e));
+        f(std::integral_constant<int, 0>(), e);
+    } else if (!(widest >> mi & 1u)) {
+        asm("; wide" : "+s"(e));
+        f(std::integral_constant<int, 1>(), e);
+    } else {
+        asm("; widest" : "+s"(e));
+        f(std::integral_constant<int, 2>(), e);
+    }
 }
 __device__ __forceinline__ uint32_t tab_dst(uint32_t e) { return e & 511u; }
 __device__ __forceinline__ uint32_t tab_mod(uint32_t e) { return (e >> 9) & 63u; }
@@ -87,7 +96,7 @@ struct Col {
 
 // RS: the source is the coefficient form of the limb that Rescale drops (modulus ml); what is transformed is the negated
 // rounding term ((v + h) mod q_l) mod q - (h mod q), h = floor(q_l / 2), of this limb's modulus m.
-template <int LC, bool RS, bool WIDE>
+template <int LC, bool RS, int W>
 __device__ __forceinline__ void col_fwd(const P2Args& a, const LimbTab& tab, uint32_t e, uint32_t tile, u64* sm) {
     using G = Col<LC>;
     const uint32_t mi = tab_mod(e), logN = LC + 8;
@@ -100,30 +109,30 @@ __device__ __forceinline__ void col_fwd(const P2Args& a, const LimbTab& tab, uin
     ulonglong2 w1[15], w2[15];                           // w1: the same for the whole limb (scalar registers)
     if (LC <= 8) tw_load<G::U0, 4>(w2, tw, LC - 4, t);
     else tw_load<0, 4>(w2, tw, 4, t >> 1);
-    tw_load<0, 4>(w1, tw, 0, 0);
-    const ModConst m = a.mc[mi];
-    const ModConst ml = a.mc[RS ? a.rs_mod : mi];
+    tw_load_c<0, 4>(w1, (ctw_t)(uintptr_t)tw, 0, 0);
+    const ModConst m = mod_const(a.mc, mi), ml = RS ? mod_const(a.mc, a.rs_mod) : m;
     u64* dst = a.dst + ((size_t)tab_dst(e) << logN);
-    const u64 q = uni64(m.q);
+    const u64 q = m.q;
     if (RS) {
         const u64 h = ml.q >> 1, hr = barrett64(h, q, m.mu, m.bits);
 #pragma unroll
         for (int k = 0; k < 16; k++) x[k] = shoup_lazy4(addmod(x[k], h, ml.q), 1, m.one_sh, q) + (q - hr);      // below 5q
     }
-    fwd_stages<WIDE, 0, 4, true>(x, w1, q);
+    int b = 5;
+    fwd_stages<W, 0, 4, true>(x, w1, q, b);
 #pragma unroll
     for (int k = 0; k < 16; k++) sm[G::pos(t + (k << G::LT), cl)] = x[k];
     __syncthreads();
     if (LC <= 8) {
 #pragma unroll
         for (int j = 0; j < 16; j++) x[j] = sm[G::pos(16 * t + j, cl)];
-        fwd_stages<WIDE, G::U0, 4>(x, w2, q);
+        fwd_stages<W, G::U0, 4>(x, w2, q, b);
     } else {
         // nine stages: rows 32G + e + 2j for stages 4..7 (t = 2G + e), then contiguous rows for stage 8
         const uint32_t r0 = (t >> 1) * 32 + (t & 1);
 #pragma unroll
         for (int j = 0; j < 16; j++) x[j] = sm[G::pos(r0 + 2 * j, cl)];
-        fwd_stages<WIDE, 0, 4>(x, w2, q);
+        fwd_stages<W, 0, 4>(x, w2, q, b);
         ulonglong2 w3[15];
         tw_load<3, 4>(w3, tw, 5, t);
         __syncthreads();
@@ -132,7 +141,7 @@ __device__ __forceinline__ void col_fwd(const P2Args& a, const LimbTab& tab, uin
         __syncthreads();
 #pragma unroll
         for (int j = 0; j < 16; j++) x[j] = sm[G::pos(16 * t + j, cl)];
-        fwd_stages<WIDE, 3, 4>(x, w3, q);
+        fwd_stages<W, 3, 4>(x, w3, q, b);
     }
 #pragma unroll
     for (int j = 0; j < 16; j++) (dst + j * 256)[t * 4096 + c] = x[j];
@@ -140,17 +149,17 @@ __device__ __forceinline__ void col_fwd(const P2Args& a, const LimbTab& tab, uin
 
 template <int LC, bool RS>
 __global__ __launch_bounds__(P2_THREADS, 4) void ntt_col_fwd_kernel(P2Args a, LimbTab tab) {
+    ieee_off();
     using G = Col<LC>;
     __shared__ u64 sm[G::LDS];
     const uint32_t tile = blockIdx.x & (G::T - 1), e = __builtin_amdgcn_readfirstlane(tab.e[blockIdx.x >> G::LT]);
-    if (e & TAB_WIDE) col_fwd<LC, RS, true>(a, tab, branch_pin<true>(e), tile, sm);
-    else col_fwd<LC, RS, false>(a, tab, branch_pin<false>(e), tile, sm);
+    by_class(a.widest, tab_mod(e), e, [&](auto W, uint32_t v) { col_fwd<LC, RS, W>(a, tab, v, tile, sm); });
 }
 
-// Inverse column stages and output scaling: inputs below 4q, results canonical.  Stage 0 (one twiddle for the whole limb)
+// Inverse column stages and output scaling: inputs below 2q (wide moduli: w_half), results canonical.  Stage 0 (one twiddle for the whole limb)
 // carries the scaling: the sum is multiplied by the scale, the difference by scale * twiddle.  Narrow moduli: bounds
-// 4 -> at most 64 (128 for N = 2^17) -> 1024, where the last sum still fits 64 bits (its products, which take any value, are Shoup's).
-template <int LC, bool CUSTOM_SCALE, bool WIDE>
+// 2 -> 40 (N = 2^17: 80, reduced) -> 320 -> 640 (products that take any value, Shoup's).
+template <int LC, bool CUSTOM_SCALE, int W>
 __device__ __forceinline__ void col_inv(const P2Args& a, uint32_t e, uint32_t tile, u64* sm, const ScaleList& sc, uint32_t scale_period) {
     using G = Col<LC>;
     const uint32_t mi = tab_mod(e), logN = LC + 8, limb = tab_dst(e);
@@ -163,70 +172,60 @@ __device__ __forceinline__ void col_inv(const P2Args& a, uint32_t e, uint32_t ti
     ulonglong2 w1[15], w2[15];
     if (LC <= 8) tw_load<G::U0, 4>(w2, tw, LC - 4, t);
     else tw_load<0, 4>(w2, tw, 4, t >> 1);
-    const ModConst m = a.mc[mi];
+    const ModConst m = mod_const(a.mc, mi);
     const uint32_t si = CUSTOM_SCALE ? limb % scale_period : 0;
     const u64 cs = CUSTOM_SCALE ? sc.s[si] : m.ninv, cs_sh = CUSTOM_SCALE ? sc.s_sh[si] : m.ninv_sh;
     const u64 cw = CUSTOM_SCALE ? sc.w[si] : m.ninv_w, cw_sh = CUSTOM_SCALE ? sc.w_sh[si] : m.ninv_w_sh;
-    const u64 q = uni64(m.q);
-    int bd[16];
-    bounds_all(bd, 4);
-    int after;                                           // bound of every point after the exchange, narrow moduli
+    const u64 q = m.q;
+    int bound = W ? w_half(W) : 2;
     if (LC <= 8) {
-        inv_stages<WIDE, G::U0, 4>(x, bd, w2, q);
-        if (WIDE) settle4(x, bd, q);
+        inv_stages<W, G::U0, 4>(x, w2, q, bound);
 #pragma unroll
         for (int j = 0; j < 16; j++) sm[G::pos(16 * t + j, cl)] = x[j];
-        after = narrow_after(4, 4 - G::U0);
     } else {
         ulonglong2 w3[15];
         tw_load<3, 4>(w3, tw, 5, t);
-        inv_stages<WIDE, 3, 4>(x, bd, w3, q);
-        if (WIDE) settle4(x, bd, q);
+        inv_stages<W, 3, 4>(x, w3, q, bound);
         const uint32_t r0 = (t >> 1) * 32 + (t & 1);
 #pragma unroll
         for (int j = 0; j < 16; j++) sm[G::pos(16 * t + j, cl)] = x[j];
         __syncthreads();
 #pragma unroll
         for (int j = 0; j < 16; j++) x[j] = sm[G::pos(r0 + 2 * j, cl)];
-        bounds_all(bd, WIDE ? 4 : 8);
-        inv_stages<WIDE, 0, 4>(x, bd, w2, q);
-        if (WIDE) settle4(x, bd, q);
-        else {
+        inv_stages<W, 0, 4>(x, w2, q, bound);
+        if (W == 0) {
+            bound = 2;
 #pragma unroll
             for (int j = 0; j < 16; j++) x[j] = reduce_lazy<10>(x[j], q, m.bits, m.rec);
         }
         __syncthreads();
 #pragma unroll
         for (int j = 0; j < 16; j++) sm[G::pos(r0 + 2 * j, cl)] = x[j];
-        after = 2;
     }
-    tw_load<1, 4>(w1, tw, 0, 0);                         // the same for the whole limb (scalar registers)
+    tw_load_c<1, 4>(w1, (ctw_t)(uintptr_t)tw, 0, 0);     // the same for the whole limb (scalar registers)
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < 16; k++) x[k] = sm[G::pos(t + (k << G::LT), cl)];
-    bounds_all(bd, WIDE ? 4 : after);
-    inv_stages<WIDE, 1, 4, true>(x, bd, w1, q);
-    if (WIDE) settle4(x, bd, q);
-    const u64 bq = WIDE ? 4 * q : 512 * q;
+    inv_stages<W, 1, 4, true>(x, w1, q, bound);
 #pragma unroll
     for (int k = 0; k < 8; k++) {
         const u64 X = x[k], Y = x[k + 8];
         x[k] = shoup_lazy4(X + Y, cs, cs_sh, q);
-        x[k + 8] = shoup_lazy4((X + bq) - Y, cw, cw_sh, q);
+        x[k + 8] = shoup_lazy4((X + q * (u64)bound) - Y, cw, cw_sh, q);        // any value below 2^64
     }
 #pragma unroll
-    for (int k = 0; k < 16; k++) (data + ((size_t)k << (G::LT + 8)))[t * 256 + c] = csub_u(csub_u(x[k], 2 * q), q);
+    for (int k = 0; k < 16; k++) (data + ((size_t)k << (G::LT + 8)))[t * 256 + c] = csub_min(csub_min(x[k], 2 * q), q);
 }
 
 // N = 2^17 (LC = 9) runs three wavefronts to a SIMD: held to four, its three register blocks spilled 12 bytes a lane.  Inverse
 // transforms of 24 limbs 44 us so and 42 without spills, of 192 limbs 203 and 200.
 template <int LC, bool CUSTOM_SCALE>
 __global__ __launch_bounds__(P2_THREADS, LC == 9 ? 3 : 4) void ntt_col_inv_kernel(P2Args a, LimbTab tab, ScaleList sc, uint32_t scale_period) {
+    ieee_off();
     using G = Col<LC>;
     __shared__ u64 sm[G::LDS];
     const uint32_t tile = blockIdx.x & (G::T - 1), e = __builtin_amdgcn_readfirstlane(tab.e[blockIdx.x >> G::LT]);
-    if (e & TAB_WIDE) col_inv<LC, CUSTOM_SCALE, true>(a, branch_pin<true>(e), tile, sm, sc, scale_period);
-    else col_inv<LC, CUSTOM_SCALE, false>(a, branch_pin<false>(e), tile, sm, sc, scale_period);
+    by_class(a.widest, tab_mod(e), e, [&](auto W, uint32_t v) { col_inv<LC, CUSTOM_SCALE, W>(a, v, tile, sm, sc, scale_period); });
 }
 
 // ---------------------------------------------------------------- forward row pass
@@ -237,7 +236,7 @@ __global__ __launch_bounds__(P2_THREADS, LC == 9 ? 3 : 4) void ntt_col_inv_kerne
 // 16 channels with a hoisted sum at level 12 1203 -> 1191, at level 5 628 -> 625; other layers within 0.3 % either way.
 // LANES: threads that share a row, 16 points each in two register blocks of four stages or, for small launches, 4 points each
 // in four blocks of two (see launch_transform2p).
-template <bool WIDE, bool EPI, int LANES>
+template <int W, bool EPI, int LANES>
 __device__ __forceinline__ void row_fwd(const P2Args& a, uint32_t e, uint32_t tile, u64* sm, const ModDownEpilogue& ep) {
     const uint32_t mi = tab_mod(e), limb = tab_dst(e), logN = a.logN, lc = logN - 8;
     const ulonglong2* tw = a.tw + ((size_t)mi << logN);
@@ -245,8 +244,8 @@ __device__ __forceinline__ void row_fwd(const P2Args& a, uint32_t e, uint32_t ti
     const uint32_t blk = threadIdx.x / LANES, t = threadIdx.x % LANES, b = tile * (P2_THREADS / LANES) + blk;
     u64* row = a.dst + ((size_t)limb << logN) + (size_t)b * 256;
     u64* s = sm + blk * 272;
-    const ModConst m = a.mc[mi];
-    const u64 q = uni64(m.q);
+    const ModConst m = mod_const(a.mc, mi);
+    const u64 q = m.q;
     constexpr int PTS = 256 / LANES;
     u64 x[PTS];
     if constexpr (LANES == 16) {
@@ -255,11 +254,12 @@ __device__ __forceinline__ void row_fwd(const P2Args& a, uint32_t e, uint32_t ti
 #pragma unroll
         for (int k = 0; k < 16; k++) x[k] = row[t + 16 * k];
         SCHED_FENCE();
-        fwd_stages<WIDE, 0, 3>(x, w1, q);
+        int bound = w_lim(W);
+        fwd_stages<W, 0, 3>(x, w1, q, bound);
         SCHED_FENCE();
         tw_load_last<0, 3>(w2, tw, lc + 4, 16 * b + t);      // into the registers that the first three stages' factors leave
         SCHED_FENCE();
-        fwd_stages<WIDE, 3, 4>(x, w1, q);
+        fwd_stages<W, 3, 4>(x, w1, q, bound);
         SCHED_FENCE();
         tw_load_last<3, 4>(w2, tw, lc + 4, 16 * b + t);
         SCHED_FENCE();
@@ -268,21 +268,21 @@ __device__ __forceinline__ void row_fwd(const P2Args& a, uint32_t e, uint32_t ti
         wave_exchange();
 #pragma unroll
         for (int j = 0; j < 16; j++) x[j] = s[17 * t + j];
-        fwd_stages<WIDE, 0, 4>(x, w2, q);
+        fwd_stages<W, 0, 4>(x, w2, q, bound);
     } else {
         u64 w[4][6];
 #pragma unroll
         for (int k = 0; k < 4; k++) x[k] = row[t + 64 * k];
         tw_row4(w, tw, lc, b, t);
-        row4_fwd<WIDE, 1>(reinterpret_cast<u64 (&)[1][4]>(x), w, s, 272, Row4(t), q);
+        row4_fwd<W, 1>(reinterpret_cast<u64 (&)[1][4]>(x), w, s, 272, Row4(t), q);
     }
     if (!EPI) {
-        if (!WIDE && a.lazy) {
+        if (W == 0 && a.lazy) {
 #pragma unroll
             for (int j = 0; j < PTS; j++) x[j] = reduce_lazy<7>(x[j], q, m.bits, m.rec);
         } else {
 #pragma unroll
-            for (int j = 0; j < PTS; j++) x[j] = reduce_full<7>(x[j], q, m.bits, m.rec);
+            for (int j = 0; j < PTS; j++) x[j] = reduce_min<7>(x[j], q, m.bits, m.rec);
         }
         if constexpr (LANES == 16) {
             wave_exchange();
@@ -302,9 +302,9 @@ __device__ __forceinline__ void row_fwd(const P2Args& a, uint32_t e, uint32_t ti
         }
         return;
     }
-    // out = (acc - ntt) * P^-1 + sigma(c0) + self: the product is below 4q whatever its factor, so the transform value may
-    // stay as it is where 128q plus the accumulator fits 64 bits, else below 2q; the sum is below 6q
-    const bool raw = !WIDE && m.bits <= 55;
+    // out = (acc - ntt) * P^-1 + sigma(c0) + self: the product is below 5q whatever its factor, so the transform value may
+    // stay as it is where 128q plus the accumulator (below 6q) fits 63 bits, else below 2q; the sum is below 7q
+    const bool raw = W == 0 && m.bits <= 55;
     if (!raw) {
 #pragma unroll
         for (int j = 0; j < PTS; j++) x[j] = reduce_lazy<7>(x[j], q, m.bits, m.rec);
@@ -315,7 +315,7 @@ __device__ __forceinline__ void row_fwd(const P2Args& a, uint32_t e, uint32_t ti
     for (int j = 0; j < PTS; j++) s[e0 + j + ((e0 + j) >> 4)] = x[j];
     const u64 bias = raw ? (q << 7) : 2 * q;
     const uint32_t pc = limb / ep.L1, r = limb - pc * ep.L1, job = pc >> 1, comp = pc & 1u, row0 = b * 256;
-    const u64 pinv = ep.pinv[r], pinv_sh = ep.pinv_sh[r];
+    const u64 pinv = uni64(ep.pinv[r]), pinv_sh = uni64(ep.pinv_sh[r]), n2q = opaque_s(0 - 2 * q), pinv_h = split_factor<true>(pinv, pinv_sh, n2q);
     const size_t ro = (size_t)r << logN;
     u64* out = (comp ? ep.out1[job] : ep.out0[job]) + ro;
     const u64* c0p = comp == 0 ? ep.c0[job] : nullptr;
@@ -341,30 +341,30 @@ __device__ __forceinline__ void row_fwd(const P2Args& a, uint32_t e, uint32_t ti
             add.y += src & 1u ? c.x : c.y;
         }
         ulonglong2 o;
-        o.x = reduce_full<7>(shoup_acc(add.x, av[p].x + bias - s[l], pinv, pinv_sh, q), q, m.bits, m.rec);
-        o.y = reduce_full<7>(shoup_acc(add.y, av[p].y + bias - s[l + 1], pinv, pinv_sh, q), q, m.bits, m.rec);
+        o.x = reduce_min<7>(split_acc(add.x, av[p].x + bias - s[l], pinv, pinv_sh, pinv_h, n2q), q, m.bits, m.rec);
+        o.y = reduce_min<7>(split_acc(add.y, av[p].y + bias - s[l + 1], pinv, pinv_sh, pinv_h, n2q), q, m.bits, m.rec);
         store2_stream(out + pos, o.x, o.y);
     }
 }
 
 template <bool EPI, int LANES>
 __global__ __launch_bounds__(P2_THREADS, 4) void ntt_row_fwd_kernel(P2Args a, LimbTab tab, ModDownEpilogue ep) {
+    ieee_off();
     __shared__ alignas(16) u64 sm[P2_THREADS / LANES * 272];         // 16 groups of 17: conflict-free both ways
     uint32_t tile;
     const uint32_t e = row_decode<LANES>(tab, a, tile);
     if (e == TAB_NONE) return;
-    if (e & TAB_WIDE) row_fwd<true, EPI, LANES>(a, branch_pin<true>(e), tile, sm, ep);
-    else row_fwd<false, EPI, LANES>(a, branch_pin<false>(e), tile, sm, ep);
+    by_class(a.widest, tab_mod(e), e, [&](auto W, uint32_t v) { row_fwd<W, EPI, LANES>(a, v, tile, sm, ep); });
 }
 
 // ---------------------------------------------------------------- inverse row pass
 // Stages LC+7 .. LC+4 on contiguous points, exchange, stages LC+3 .. LC on strided points: inputs canonical, results below
-// 4q (narrow moduli: 2q).  Narrow moduli: bounds 1 -> 40 after the first block, -> 640 after the second, one quotient step at the end.
+// 2q (wide moduli: w_half).  Narrow moduli: bounds 1 -> 40 after the first block, -> 640 after the second, one quotient step at the end.
 // LANES as in row_fwd.
-template <bool WIDE, int LANES>
+template <int W, int LANES>
 __device__ __forceinline__ void row_inv(const P2Args& a, const LimbTab& tab, uint32_t e, uint32_t tile, u64* sm) {
     const uint32_t mi = tab_mod(e), limb = tab_dst(e), logN = a.logN, lc = logN - 8;
-    const ModConst m = a.mc[mi];
+    const ModConst m = mod_const(a.mc, mi);
     const ulonglong2* tw = a.tw + ((size_t)mi << logN);
     constexpr int DP = 2 * LANES, PTS = 256 / LANES;
     const uint32_t blk = threadIdx.x / LANES, t = threadIdx.x % LANES, b = tile * (P2_THREADS / LANES) + blk;
@@ -388,20 +388,18 @@ __device__ __forceinline__ void row_inv(const P2Args& a, const LimbTab& tab, uin
         wave_exchange();
         Row4(t).load(3, x, s);
     }
-    const u64 q = uni64(m.q);
+    const u64 q = m.q;
     if constexpr (LANES == 16) {
         wave_exchange();
 #pragma unroll
         for (int j = 0; j < 16; j++) x[j] = s[17 * t + j];
         ulonglong2 w1[15];
-        int bd[16];
-        bounds_all(bd, 1);
-        inv_stages<WIDE, 2, 4>(x, bd, w2, q);
+        int bound = 1;
+        inv_stages<W, 2, 4>(x, w2, q, bound);
         SCHED_FENCE();
         tw_load<2, 4>(w1, tw, lc, b);                        // into the registers that the first two stages' factors leave
         SCHED_FENCE();
-        inv_stages<WIDE, 0, 2>(x, bd, w2, q);
-        if (WIDE) settle4(x, bd, q);
+        inv_stages<W, 0, 2>(x, w2, q, bound);
         SCHED_FENCE();
         tw_load<0, 2>(w1, tw, lc, b);
         SCHED_FENCE();
@@ -411,17 +409,15 @@ __device__ __forceinline__ void row_inv(const P2Args& a, const LimbTab& tab, uin
         wave_exchange();
 #pragma unroll
         for (int k = 0; k < 16; k++) x[k] = s[t + 17 * k];
-        bounds_all(bd, WIDE ? 4 : 40);
-        inv_stages<WIDE, 0, 4>(x, bd, w1, q);
-        if (WIDE) settle4(x, bd, q);
-        else {
+        inv_stages<W, 0, 4>(x, w1, q, bound);
+        if (W == 0) {
 #pragma unroll
             for (int k = 0; k < 16; k++) x[k] = reduce_lazy<10>(x[k], q, m.bits, m.rec);
         }
 #pragma unroll
         for (int k = 0; k < 16; k++) out[t + 16 * k] = x[k];
     } else {
-        row4_inv<WIDE, 1>(reinterpret_cast<u64 (&)[1][4]>(x), w4, s, 272, Row4(t), q, m);
+        row4_inv<W, 1>(reinterpret_cast<u64 (&)[1][4]>(x), w4, s, 272, Row4(t), q, m);
 #pragma unroll
         for (int k = 0; k < 4; k++) out[t + 64 * k] = x[k];
     }
@@ -429,12 +425,12 @@ __device__ __forceinline__ void row_inv(const P2Args& a, const LimbTab& tab, uin
 
 template <int LANES>
 __global__ __launch_bounds__(P2_THREADS, 4) void ntt_row_inv_kernel(P2Args a, LimbTab tab) {
+    ieee_off();
     __shared__ alignas(16) u64 sm[P2_THREADS / LANES * 272];
     uint32_t tile;
     const uint32_t e = row_decode<LANES>(tab, a, tile);
     if (e == TAB_NONE) return;
-    if (e & TAB_WIDE) row_inv<true, LANES>(a, tab, branch_pin<true>(e), tile, sm);
-    else row_inv<false, LANES>(a, tab, branch_pin<false>(e), tile, sm);
+    by_class(a.widest, tab_mod(e), e, [&](auto W, uint32_t v) { row_inv<W, LANES>(a, tab, v, tile, sm); });
 }
 
 // ---------------------------------------------------------------- row passes of several limbs of one modulus
@@ -445,7 +441,7 @@ __global__ __launch_bounds__(P2_THREADS, 4) void ntt_row_inv_kernel(P2Args a, Li
 // 102 -> 95, near what the points alone take (403 MB, 82 us at copy rate).  Asking for the next four limbs' points ahead
 // costs a third of the wavefronts and gave 110.
 struct RunTab {
-    uint32_t r[HE_MAX_LAUNCH_LIMBS / 4 + HE_MAX_MODULI];     // first entry of LimbTab (bits 0-8), limbs (9-13), wide (31)
+    uint32_t r[HE_MAX_LAUNCH_LIMBS / 4 + HE_MAX_MODULI];     // first entry of LimbTab (bits 0-8), limbs (9-13), modulus (14-19), wide (31)
 };
 // what entry 4*it + i of the run gives for lane quarter i (the last entry's again where the run has fewer)
 template <class F>
@@ -470,7 +466,7 @@ __device__ __forceinline__ void run_keep(ulonglong2 (&w)[15]) {
 #pragma unroll
     for (int i = 0; i < 15; i++) asm("" : "+v"(w[i].x), "+v"(w[i].y));
 }
-template <bool WIDE, bool LAZY>
+template <int W, bool LAZY>
 __device__ __forceinline__ void row_run_fwd(const P2Args& a, const LimbTab& tab, uint32_t run, uint32_t b, u64* sm) {
     const uint32_t first = run & 511u, n = (run >> 9) & 31u, logN = a.logN, lc = logN - 8, mi = tab_mod(tab.e[first]);
     const uint32_t quarter = (threadIdx.x >> 4) & 3u, t = threadIdx.x & 15u;
@@ -482,14 +478,15 @@ __device__ __forceinline__ void row_run_fwd(const P2Args& a, const LimbTab& tab,
     u64* base = a.dst + b * 256u + t;
     run_tw1(w1, tw, lc, b);
     tw_load_last<0, 4>(w2, tw, lc + 4, 16 * b + t);
-    const ModConst m = a.mc[mi];
-    const u64 q = uni64(m.q);
+    const ModConst m = mod_const(a.mc, mi);
+    const u64 q = m.q;
     for (uint32_t it = 0;; it++) {
         const uint32_t dl = run_pick(tab, first, n, it, quarter, dst);
 #pragma unroll
         for (int k = 0; k < 16; k++) x[k] = base[((size_t)dl << logN) + 16 * k];
         SCHED_FENCE();
-        fwd_stages<WIDE, 0, 4, true>(x, w1, q);
+        int bound = w_lim(W);
+        fwd_stages<W, 0, 4, true>(x, w1, q, bound);
 #pragma unroll
         for (int k = 0; k < 16; k++) s[t + 17 * k] = x[k];
         wave_exchange();
@@ -497,14 +494,14 @@ __device__ __forceinline__ void row_run_fwd(const P2Args& a, const LimbTab& tab,
         for (int j = 0; j < 16; j++) x[j] = s[17 * t + j];
         SCHED_FENCE();
         run_keep(w2);
-        fwd_stages<WIDE, 0, 4>(x, w2, q);
+        fwd_stages<W, 0, 4>(x, w2, q, bound);
         SCHED_FENCE();
-        if (!WIDE && LAZY) {
+        if (W == 0 && LAZY) {
 #pragma unroll
             for (int j = 0; j < 16; j++) x[j] = reduce_lazy<7>(x[j], q, m.bits, m.rec);
         } else {
 #pragma unroll
-            for (int j = 0; j < 16; j++) x[j] = reduce_full<7>(x[j], q, m.bits, m.rec);
+            for (int j = 0; j < 16; j++) x[j] = reduce_min<7>(x[j], q, m.bits, m.rec);
         }
         wave_exchange();
 #pragma unroll
@@ -518,7 +515,7 @@ __device__ __forceinline__ void row_run_fwd(const P2Args& a, const LimbTab& tab,
         wave_exchange();
     }
 }
-template <bool WIDE>
+template <int W>
 __device__ __forceinline__ void row_run_inv(const P2Args& a, const LimbTab& tab, uint32_t run, uint32_t b, u64* sm) {
     const uint32_t first = run & 511u, n = (run >> 9) & 31u, logN = a.logN, lc = logN - 8, mi = tab_mod(tab.e[first]);
     const uint32_t quarter = (threadIdx.x >> 4) & 3u, t = threadIdx.x & 15u;
@@ -531,8 +528,8 @@ __device__ __forceinline__ void row_run_inv(const P2Args& a, const LimbTab& tab,
     auto src = [&](uint32_t e) { return uni64((u64)tab_src(tab, e, logN)); };
     tw_load_last<0, 4>(w2, tw, lc + 4, 16 * b + t);
     run_tw1(w1, tw, lc, b);
-    const ModConst m = a.mc[mi];
-    const u64 q = uni64(m.q);
+    const ModConst m = mod_const(a.mc, mi);
+    const u64 q = m.q;
     for (uint32_t it = 0;; it++) {
         const u64* in = (const u64*)run_pick(tab, first, n, it, quarter, src) + at;
 #pragma unroll
@@ -544,22 +541,18 @@ __device__ __forceinline__ void row_run_inv(const P2Args& a, const LimbTab& tab,
         SCHED_FENCE();
 #pragma unroll
         for (int j = 0; j < 16; j++) x[j] = s[17 * t + j];
-        int bd[16];
-        bounds_all(bd, 1);
+        int bound = 1;
         run_keep(w2);
-        inv_stages<WIDE, 0, 4>(x, bd, w2, q);
+        inv_stages<W, 0, 4>(x, w2, q, bound);
         SCHED_FENCE();
-        if (WIDE) settle4(x, bd, q);
         wave_exchange();
 #pragma unroll
         for (int j = 0; j < 16; j++) s[17 * t + j] = x[j];
         wave_exchange();
 #pragma unroll
         for (int k = 0; k < 16; k++) x[k] = s[t + 17 * k];
-        bounds_all(bd, WIDE ? 4 : 40);
-        inv_stages<WIDE, 0, 4, true>(x, bd, w1, q);
-        if (WIDE) settle4(x, bd, q);
-        else {
+        inv_stages<W, 0, 4, true>(x, w1, q, bound);
+        if (W == 0) {
 #pragma unroll
             for (int k = 0; k < 16; k++) x[k] = reduce_lazy<10>(x[k], q, m.bits, m.rec);
         }
@@ -575,16 +568,14 @@ __device__ __forceinline__ void row_run_inv(const P2Args& a, const LimbTab& tab,
 // work group: 4 adjacent rows of one run
 template <bool FWD, bool LAZY>
 __global__ __launch_bounds__(P2_THREADS, 4) void ntt_row_run_kernel(P2Args a, LimbTab tab, RunTab runs) {
+    ieee_off();
     __shared__ u64 sm[16 * 272];
     const uint32_t lb = a.logN - 10, b = (blockIdx.x & ((1u << lb) - 1u)) * 4u + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t run = __builtin_amdgcn_readfirstlane(runs.r[blockIdx.x >> lb]);
-    if (FWD) {
-        if (run & TAB_WIDE) row_run_fwd<true, LAZY>(a, tab, branch_pin<true>(run), b, sm);
-        else row_run_fwd<false, LAZY>(a, tab, branch_pin<false>(run), b, sm);
-    } else {
-        if (run & TAB_WIDE) row_run_inv<true>(a, tab, branch_pin<true>(run), b, sm);
-        else row_run_inv<false>(a, tab, branch_pin<false>(run), b, sm);
-    }
+    by_class(a.widest, run >> 14 & 63u, run, [&](auto W, uint32_t v) {
+        if constexpr (FWD) row_run_fwd<W, LAZY>(a, tab, v, b, sm);
+        else row_run_inv<W>(a, tab, v, b, sm);
+    });
 }
 
 // ---------------------------------------------------------------- butterfly-rate probe
@@ -592,19 +583,19 @@ __global__ __launch_bounds__(P2_THREADS, 4) void ntt_row_run_kernel(P2Args a, Li
 // above (four stages on 16 points, twiddles from a 256-entry table that stays in the first-level cache)
 // run back to back with no other memory traffic.  Values wrap around after a few rounds; the timing does
 // not depend on them.
-template <bool FWD, bool WIDE>
+template <bool FWD, int W>
 __global__ __launch_bounds__(P2_THREADS) void bfly_probe_kernel(const ulonglong2* __restrict__ tw, u64 q,
                                                                  u64* __restrict__ out, uint32_t rounds) {
     const uint32_t t = threadIdx.x & 15;
     ulonglong2 w[15];
     u64 x[16];
-    int bd[16];
 #pragma unroll
     for (int k = 0; k < 16; k++) x[k] = (u64)(blockIdx.x * P2_THREADS + threadIdx.x) * 16 + k;
     for (uint32_t r = 0; r < rounds; r++) {
         tw_load<0, 4>(w, tw, 4, t);
-        if (FWD) fwd_stages<WIDE, 0, 4>(x, w, q);
-        else { bounds_all(bd, 4); inv_stages<WIDE, 0, 4>(x, bd, w, q); if (WIDE) settle4(x, bd, q); }
+        int b = FWD ? w_lim(W) : w_half(W);
+        if (FWD) fwd_stages<W, 0, 4>(x, w, q, b);
+        else inv_stages<W, 0, 4>(x, w, q, b);
     }
     u64 v = 0;
 #pragma unroll
@@ -626,10 +617,10 @@ int32_t probe_butterfly_rates(he_ctx* ctx, u64* d_out, uint32_t groups, double r
         const ulonglong2* tw = (which == 1 ? ctx->d_itw : ctx->d_tw) + (size_t)mi * ctx->N;
         for (int rep = 0; rep < 2; rep++) {              // the first launch warms up
             HE_HIP(ctx, hipEventRecord(e0, ctx->stream));
-            if (which == 0) hipLaunchKernelGGL((bfly_probe_kernel<true, false>), dim3(groups), dim3(P2_THREADS), 0, ctx->stream, tw, ctx->mod[mi], d_out, rounds);
-            else if (which == 1 && !narrow_inv(ctx->mod[mi])) hipLaunchKernelGGL((bfly_probe_kernel<false, true>), dim3(groups), dim3(P2_THREADS), 0, ctx->stream, tw, ctx->mod[mi], d_out, rounds);
-            else if (which == 1) hipLaunchKernelGGL((bfly_probe_kernel<false, false>), dim3(groups), dim3(P2_THREADS), 0, ctx->stream, tw, ctx->mod[mi], d_out, rounds);
-            else hipLaunchKernelGGL((bfly_probe_kernel<true, true>), dim3(groups), dim3(P2_THREADS), 0, ctx->stream, tw, ctx->mod[mi], d_out, rounds);
+            if (which == 0) hipLaunchKernelGGL((bfly_probe_kernel<true, 0>), dim3(groups), dim3(P2_THREADS), 0, ctx->stream, tw, ctx->mod[mi], d_out, rounds);
+            else if (which == 1 && !narrow_inv(ctx->mod[mi])) hipLaunchKernelGGL((bfly_probe_kernel<false, 1>), dim3(groups), dim3(P2_THREADS), 0, ctx->stream, tw, ctx->mod[mi], d_out, rounds);
+            else if (which == 1) hipLaunchKernelGGL((bfly_probe_kernel<false, 0>), dim3(groups), dim3(P2_THREADS), 0, ctx->stream, tw, ctx->mod[mi], d_out, rounds);
+            else hipLaunchKernelGGL((bfly_probe_kernel<true, 1>), dim3(groups), dim3(P2_THREADS), 0, ctx->stream, tw, ctx->mod[mi], d_out, rounds);
             HE_HIP(ctx, hipGetLastError());
             HE_HIP(ctx, hipEventRecord(e1, ctx->stream));
             HE_HIP(ctx, hipEventSynchronize(e1));
@@ -687,12 +678,14 @@ int32_t launch_transform2p(he_ctx* ctx, const TransformDesc& d) {
         while (piece > 4 && (live / piece) * groups < 4 * 768) piece >>= 1;
         for (uint32_t m = 0, at = 0; m < ctx->M; at += count[m++])
             for (uint32_t i = 0; i < count[m]; i += piece)
-                runs.r[n_runs++] = (at + i) | (std::min(piece, count[m] - i) << 9) | ((fwd ? narrow_fwd(ctx->mod[m]) : narrow_inv(ctx->mod[m])) ? 0u : TAB_WIDE);
+                runs.r[n_runs++] = (at + i) | (std::min(piece, count[m] - i) << 9) | (m << 14) | ((fwd ? narrow_fwd(ctx->mod[m]) : narrow_inv(ctx->mod[m])) ? 0u : TAB_WIDE);
     }
     P2Args a;
     a.dst = d.dst; a.mc = ctx->d_mc;
     a.tw = fwd ? ctx->d_tw : ctx->d_itw;
     a.logN = logN;
+    a.widest = 0;
+    for (uint32_t m = 0; m < ctx->M; m++) a.widest |= (u64)widest(ctx->mod[m]) << m;
     a.lazy = (fwd && d.lazy_out) ? 1u : 0u;
     a.rs_mod = d.rescale_from ? d.rescale_from - 1 : 0;
     uint32_t lc = 0;

@@ -5,93 +5,89 @@
 
 #define SCHED_FENCE() __builtin_amdgcn_sched_barrier(0)   // loads above it are issued before the arithmetic below it
 
-// A butterfly is counted in instructions: on gfx950 the 32-bit multiplies, v_mad_u64_u32 and v_lshl_add_u64 all issue at
-// one per lane and cycle (28-35 T/s measured), so what costs is how many there are.  The product enters the sum through
-// the multiply-adds' own addend (X + w*Y - h*q accumulated in one chain with -q as the factor), and the difference is
-// 2X + c*q minus that sum.  Narrow moduli: two instructions for the quotient h, 7 for the sum, 3 for the difference (split_acc), and
-// 3 for a factor's second word where it is not the same for the whole wavefront (scalar instructions there).  Wide ones: 5, 8 and 3
-// with Shoup's companion.  A product formed on its own and then added and subtracted takes 20.
+// A butterfly is counted in instructions: on gfx950 the 32-bit multiplies, v_mad_u64_u32, v_lshl_add_u64 and the FP64 instructions all
+// issue at one per lane and cycle, plain 32-bit additions and bit operations at two, so what costs is how many there are.  The product
+// enters the sum through the multiply-adds' own addend (X + w*Y - h*2q accumulated in one chain), and the difference is
+// 2X + 5q minus that sum: two instructions for the quotient h, 7 for the sum (split_acc), 3 for the difference, and 3 for a factor's second
+// word where it is not the same for the whole wavefront (scalar instructions there).  With a quotient of two words it were 16, a
+// product formed on its own and then added and subtracted takes 20.
 //
-// Which moduli are narrow stands at narrow_fwd / narrow_inv (he_internal.h); their factors are stored with h_tw_split's companion, the
-// others' with Shoup's (ctx.hip).
-//
-// Ranges are kept in units of q and known when the code is compiled: a twiddle product is below 5q (narrow) or 4q (wide) whatever
-// its factor, a forward stage therefore adds that to the bound of every point, an inverse stage adds the bounds of its two points.  A
-// conditional subtraction is made only where the next sum would leave 64 bits: nowhere for narrow moduli (forward: 17 stages
-// from below 5q end below 90q; inverse: a pass ends below 640q), every other forward stage and a few inverse points for wide ones
-// (below 2^60, so that 16q fits).
-__device__ __forceinline__ void ct_bfly(u64& X, u64& Y, u64 w, u64 w_sh, u64 q, u64 q4) {
-    const u64 S = shoup_acc(X, Y, w, w_sh, q);
-    Y = (X + X + q4) - S;
-    X = S;
-}
-// what the narrow butterflies need of a modulus, in scalar registers
-struct NarrowQ {
+// Ranges are kept in units of q and known when the code is compiled: a product is below 5q whatever its factor, a forward stage therefore
+// adds that to the bound of every point, an inverse stage doubles it.  What multiplies a factor has to stay
+// below 2^63.  Three classes of moduli, a template parameter W of everything here, one for each direction (he_internal.h):
+//   0  narrow: never reduced.  Forward: 17 stages from below 5q end below 90q; inverse: a pass ends below 640q.
+//   1  up to 2^63 / 13: points stay below 13q, which takes one conditional subtraction of two instructions (csub_min) a forward butterfly.
+//   2  the others (below 2^60): below 8q, two of them.
+__device__ constexpr int w_lim(int W) { return W == 1 ? 13 : 8; }         // sums and products' operands (W > 0)
+__device__ constexpr int w_half(int W) { return w_lim(W) / 2; }            // inverse: points between stages (W > 0)
+// what the butterflies need of a modulus, in scalar registers
+struct StageQ {
     u64 n2q, q5;
-    __device__ __forceinline__ explicit NarrowQ(u64 q) : n2q(opaque_s(0 - 2 * q)), q5(opaque_s(5 * q)) {}
+    __device__ __forceinline__ explicit StageQ(u64 q) : n2q(opaque_s(0 - 2 * q)), q5(opaque_s(5 * q)) {}
 };
-__device__ __forceinline__ void ct_bfly_n(u64& X, u64& Y, u64 w, u64 a, u64 wh, const NarrowQ& n) {
-    const u64 S = split_acc(X, Y, w, a, wh, n.n2q);
-    Y = (X + X + n.q5) - S;
-    X = S;
+// x < b*q to below half of that, rounded up
+__device__ __forceinline__ void halve(u64& x, int& b, u64 q) {
+    const int h = (b + 1) / 2;
+    x = csub_min(x, q * (u64)h);
+    b = h;
 }
-// One factor on K pairs of points (X[i], Y[i]), stage n of a block.  Wide moduli: X brought below 8q first in every other stage
-// (inputs below 16q).
-template <bool WIDE, bool UNI, int K, class PX, class PY>
-__device__ __forceinline__ void ct_stage(int n, PX&& X, PY&& Y, u64 w, u64 a, u64 q) {
-    if (WIDE) {
-#pragma unroll
-        for (int k = 0; k < K; k++) {
-            if ((n & 1) == 0) X(k) = csub_u(X(k), 8 * q);
-            ct_bfly(X(k), Y(k), w, a, q, 4 * q);
-        }
-    } else {
-        const NarrowQ nq(q);
-        const u64 wh = split_factor<UNI>(w, a, nq.n2q);
-#pragma unroll
-        for (int k = 0; k < K; k++) ct_bfly_n(X(k), Y(k), w, a, wh, nq);
-    }
-}
-
-// Inverse butterflies of one factor on K pairs of points below bx*q and by*q; the bounds of the results replace them.  They are
-// constants of the unrolled code.
-template <bool WIDE, bool UNI, int K, class PX, class PY, class BX, class BY>
-__device__ __forceinline__ void gs_stage(PX&& PX_, PY&& PY_, BX&& bx_, BY&& by_, u64 w, u64 a, u64 q) {
-    const NarrowQ nq(q);
-    const u64 wh = WIDE ? 0 : split_factor<UNI>(w, a, nq.n2q);
+// One factor on K pairs of points X(k), Y(k) below b*q; returns the bound of the results.
+template <int W, bool UNI, int K, class PX, class PY>
+__device__ __forceinline__ int ct_stage(int b, PX&& X, PY&& Y, u64 w, u64 a, u64 q) {
+    const StageQ sq(q);
+    const u64 wh = split_factor<UNI>(w, a, sq.n2q);
+    int after = b;
 #pragma unroll
     for (int k = 0; k < K; k++) {
-        u64 &X = PX_(k), &Y = PY_(k);
-        int &bx = bx_(k), &by = by_(k);
-        if (WIDE) {
+        u64 &x = X(k), &y = Y(k);
+        int bx = b;
 #pragma unroll
-            for (int r = 0; r < 3; r++) {                // at most three steps are ever needed; constants once unrolled
-                if (bx + by <= 16) continue;
-                if (bx >= by) { const int b = bx > 8 ? 8 : 4; X = csub_u(X, q * b); bx = b; }
-                else { const int b = by > 8 ? 8 : 4; Y = csub_u(Y, q * b); by = b; }
-            }
-        }
-        const u64 d = (X + q * (u64)by) - Y;
-        X = X + Y;
-        Y = WIDE ? shoup_lazy4(d, w, a, q) : split_acc(0, d, w, a, wh, nq.n2q);
-        bx += by;
-        by = WIDE ? 4 : 5;
+        for (int r = 0; r < 2; r++) if (W && bx + 5 > w_lim(W)) halve(x, bx, q);
+        const u64 S = split_acc(x, y, w, a, wh, sq.n2q);
+        y = (x + x + sq.q5) - S;
+        x = S;
+        after = bx + 5;
     }
+    return after;
 }
-// Every point of a register block below 4q again (wide moduli, before an exchange mixes the points).
-template <int N>
-__device__ __forceinline__ void settle4(u64 (&x)[N], int (&b)[N], u64 q) {
+// Inverse butterflies of one factor on K pairs of points below b*q; returns the bound of the results.  Wide moduli: twice the bound of what
+// goes in stays within w_lim, so sums (and, of the widest, products) are halved where the next stage would leave it.
+template <int W, bool UNI, int K, class PX, class PY>
+__device__ __forceinline__ int gs_stage(int b, PX&& X, PY&& Y, u64 w, u64 a, u64 q) {
+    const StageQ sq(q);
+    const u64 wh = split_factor<UNI>(w, a, sq.n2q);
+    int after = b;
 #pragma unroll
-    for (int k = 0; k < N; k++) {
-        if (b[k] > 8) x[k] = csub_u(x[k], q * 8);
-        if (b[k] > 4) x[k] = csub_u(x[k], q * 4);
-        b[k] = 4;
+    for (int k = 0; k < K; k++) {
+        u64 &x = X(k), &y = Y(k);
+        int bx = 2 * b, by = 5;
+        const u64 d = (x + q * (u64)b) - y;
+        x = x + y;
+        y = split_acc(0, d, w, a, wh, sq.n2q);
+        if (W && 2 * bx > w_lim(W)) halve(x, bx, q);
+        if (W && 2 * by > w_lim(W)) halve(y, by, q);
+        after = bx > by ? bx : by;
     }
+    return after;
 }
-// Bound of every point of narrow inverse blocks of n stages that start below b*q: sums double it, a product is below 5q and may be
-// doubled by the stages behind its own.
-__device__ constexpr int narrow_after(int b, int n) { return (b << n) > (5 << n) / 2 ? b << n : (5 << n) / 2; }
 
+// a pointer to constant memory, which no store can change: loads through it stay scalar after stores and after ieee_off()
+typedef const __attribute__((address_space(4))) u64* const_u64;
+// a modulus' constants, in scalar registers
+__device__ __forceinline__ ModConst mod_const(const ModConst* mc, uint32_t mi) {
+    const const_u64 p = (const_u64)(uintptr_t)uni64((u64)(mc + mi));
+    ModConst m = {};
+    m.q = p[offsetof(ModConst, q) / 8];
+    m.mu = p[offsetof(ModConst, mu) / 8];
+    m.ninv = p[offsetof(ModConst, ninv) / 8];
+    m.ninv_sh = p[offsetof(ModConst, ninv_sh) / 8];
+    m.ninv_w = p[offsetof(ModConst, ninv_w) / 8];
+    m.ninv_w_sh = p[offsetof(ModConst, ninv_w_sh) / 8];
+    m.one_sh = p[offsetof(ModConst, one_sh) / 8];
+    const u64 v = p[offsetof(ModConst, bits) / 8];
+    m.bits = (uint32_t)v; m.rec = (uint32_t)(v >> 32);
+    return m;
+}
 // Register blocks of four stages on 16 points.  Stage u pairs (k, k + (8>>u)); the twiddle of the pair's group g =
 // k >> (4-u) is tw[(1 << (s0+u)) + (G << u) + g], G = group of the 16 points at stage s0, kept at index (1 << u) - 1 + g.
 // A factor and its companion lie next to each other, one 16-byte load.  Loading is separate from use: a pass that
@@ -105,6 +101,18 @@ __device__ __forceinline__ void tw_load(ulonglong2 (&w)[15], const ulonglong2* _
         for (int g = 0; g < (1 << u); g++) w[(1 << u) - 1 + g] = p[g];
     }
 }
+// The same through constant memory: scalar loads where s0 and G are the same for the wavefront.
+typedef u64 v2u64 __attribute__((ext_vector_type(2)));
+typedef const __attribute__((address_space(4))) v2u64* ctw_t;
+template <int U0, int U1>
+__device__ __forceinline__ void tw_load_c(ulonglong2 (&w)[15], ctw_t tw, uint32_t s0, uint32_t G) {
+#pragma unroll
+    for (int u = U0; u < U1; u++) {
+        ctw_t p = tw + ((1u << (s0 + u)) + (G << u));
+#pragma unroll
+        for (int g = 0; g < (1 << u); g++) { const v2u64 v = p[g]; w[(1 << u) - 1 + g] = make_ulonglong2(v.x, v.y); }
+    }
+}
 // The same for the last four stages of the two-launch transforms, whose tables keep one factor of every group after the
 // other (ctx.hip, tw_pos); G of 2^s0 groups.
 template <int U0, int U1>
@@ -115,88 +123,74 @@ __device__ __forceinline__ void tw_load_last(ulonglong2 (&w)[15], const ulonglon
 #pragma unroll
         for (int g = 0; g < (1 << u); g++) w[(1 << u) - 1 + g] = tw[(size_t)((1u << u) - 1u + g) << s0];
 }
-// Forward stages U0 .. U1-1; UNI: the factors are the same for the whole wavefront.  Wide moduli: inputs and results below 16q.
-template <bool WIDE, int U0, int U1, bool UNI = false>
-__device__ __forceinline__ void fwd_stages(u64 (&x)[16], const ulonglong2 (&w)[15], u64 q) {
+// Forward stages U0 .. U1-1 on points below b*q, the bound of the results replaces it; UNI: the factors are the same for the whole
+// wavefront.
+template <int W, int U0, int U1, bool UNI = false>
+__device__ __forceinline__ void fwd_stages(u64 (&x)[16], const ulonglong2 (&w)[15], u64 q, int& b) {
 #pragma unroll
     for (int u = U0; u < U1; u++) {
         const int dist = 8 >> u;
+        int after = b;
 #pragma unroll
         for (int g = 0; g < (1 << u); g++) {
             const ulonglong2 f = w[(1 << u) - 1 + g];
             auto X = [&](int k) -> u64& { return x[g * 2 * dist + k]; };
             auto Y = [&](int k) -> u64& { return x[g * 2 * dist + dist + k]; };
-            if (u == 0) ct_stage<WIDE, UNI, 8>(u - U0, X, Y, f.x, f.y, q);
-            else if (u == 1) ct_stage<WIDE, UNI, 4>(u - U0, X, Y, f.x, f.y, q);
-            else if (u == 2) ct_stage<WIDE, UNI, 2>(u - U0, X, Y, f.x, f.y, q);
-            else ct_stage<WIDE, UNI, 1>(u - U0, X, Y, f.x, f.y, q);
+            if (u == 0) after = ct_stage<W, UNI, 8>(b, X, Y, f.x, f.y, q);
+            else if (u == 1) after = ct_stage<W, UNI, 4>(b, X, Y, f.x, f.y, q);
+            else if (u == 2) after = ct_stage<W, UNI, 2>(b, X, Y, f.x, f.y, q);
+            else after = ct_stage<W, UNI, 1>(b, X, Y, f.x, f.y, q);
         }
+        b = after;
     }
 }
-// Inverse stages U1-1 down to U0, bounds b per point.
-template <bool WIDE, int U0, int U1, bool UNI = false>
-__device__ __forceinline__ void inv_stages(u64 (&x)[16], int (&b)[16], const ulonglong2 (&w)[15], u64 q) {
+// Inverse stages U1-1 down to U0, likewise.
+template <int W, int U0, int U1, bool UNI = false>
+__device__ __forceinline__ void inv_stages(u64 (&x)[16], const ulonglong2 (&w)[15], u64 q, int& b) {
 #pragma unroll
     for (int u = U1 - 1; u >= U0; u--) {
         const int dist = 8 >> u;
+        int after = b;
 #pragma unroll
         for (int g = 0; g < (1 << u); g++) {
             const ulonglong2 f = w[(1 << u) - 1 + g];
             auto X = [&](int k) -> u64& { return x[g * 2 * dist + k]; };
             auto Y = [&](int k) -> u64& { return x[g * 2 * dist + dist + k]; };
-            auto BX = [&](int k) -> int& { return b[g * 2 * dist + k]; };
-            auto BY = [&](int k) -> int& { return b[g * 2 * dist + dist + k]; };
-            if (u == 0) gs_stage<WIDE, UNI, 8>(X, Y, BX, BY, f.x, f.y, q);
-            else if (u == 1) gs_stage<WIDE, UNI, 4>(X, Y, BX, BY, f.x, f.y, q);
-            else if (u == 2) gs_stage<WIDE, UNI, 2>(X, Y, BX, BY, f.x, f.y, q);
-            else gs_stage<WIDE, UNI, 1>(X, Y, BX, BY, f.x, f.y, q);
+            if (u == 0) after = gs_stage<W, UNI, 8>(b, X, Y, f.x, f.y, q);
+            else if (u == 1) after = gs_stage<W, UNI, 4>(b, X, Y, f.x, f.y, q);
+            else if (u == 2) after = gs_stage<W, UNI, 2>(b, X, Y, f.x, f.y, q);
+            else after = gs_stage<W, UNI, 1>(b, X, Y, f.x, f.y, q);
         }
+        b = after;
     }
-}
-// the largest bound of a block holds for all of its points once an exchange has mixed them
-template <int N>
-__device__ __forceinline__ void bounds_all(int (&b)[N], int v) {
-#pragma unroll
-    for (int k = 0; k < N; k++) b[k] = v;
 }
 
 // Two forward / inverse stages on 4 register points of NX rows (same pairing and twiddle indexing as the 16-point blocks), factors
-// r = {w0, a0, w1, a1, w2, a2}.  ONE: only the first of the two stages.  Ranges as above.
-template <bool WIDE, bool UNI, int NX, bool ONE = false>
-__device__ __forceinline__ void fwd_block2_x(u64 (&x)[NX][4], const u64 (&r)[6], u64 q) {
-    ct_stage<WIDE, UNI, 2 * NX>(0, [&](int k) -> u64& { return x[k >> 1][k & 1]; }, [&](int k) -> u64& { return x[k >> 1][2 + (k & 1)]; }, r[0], r[1], q);
+// r = {w0, a0, w1, a1, w2, a2}.  ONE: only the first of the two stages.
+template <int W, bool UNI, int NX, bool ONE = false>
+__device__ __forceinline__ void fwd_block2_x(u64 (&x)[NX][4], const u64 (&r)[6], u64 q, int& b) {
+    b = ct_stage<W, UNI, 2 * NX>(b, [&](int k) -> u64& { return x[k >> 1][k & 1]; }, [&](int k) -> u64& { return x[k >> 1][2 + (k & 1)]; }, r[0], r[1], q);
     if (ONE) return;
-    ct_stage<WIDE, UNI, NX>(1, [&](int k) -> u64& { return x[k][0]; }, [&](int k) -> u64& { return x[k][1]; }, r[2], r[3], q);
-    ct_stage<WIDE, UNI, NX>(1, [&](int k) -> u64& { return x[k][2]; }, [&](int k) -> u64& { return x[k][3]; }, r[4], r[5], q);
+    const int after = ct_stage<W, UNI, NX>(b, [&](int k) -> u64& { return x[k][0]; }, [&](int k) -> u64& { return x[k][1]; }, r[2], r[3], q);
+    ct_stage<W, UNI, NX>(b, [&](int k) -> u64& { return x[k][2]; }, [&](int k) -> u64& { return x[k][3]; }, r[4], r[5], q);
+    b = after;
 }
-// Inverse: inputs below bound*q.  Narrow: results below narrow_after(bound, 2 or 1 stages) * q; wide: bound 4, results below 4q.
-template <bool WIDE, bool UNI, int NX, bool ONE = false>
-__device__ __forceinline__ void inv_block2_x(u64 (&x)[NX][4], const u64 (&r)[6], u64 q, int bound) {
-    int b[NX][4];
-#pragma unroll
-    for (int i = 0; i < NX; i++)
-#pragma unroll
-        for (int k = 0; k < 4; k++) b[i][k] = WIDE ? 4 : bound;
+template <int W, bool UNI, int NX, bool ONE = false>
+__device__ __forceinline__ void inv_block2_x(u64 (&x)[NX][4], const u64 (&r)[6], u64 q, int& b) {
     if (!ONE) {
-        gs_stage<WIDE, UNI, NX>([&](int k) -> u64& { return x[k][0]; }, [&](int k) -> u64& { return x[k][1]; },
-                                [&](int k) -> int& { return b[k][0]; }, [&](int k) -> int& { return b[k][1]; }, r[2], r[3], q);
-        gs_stage<WIDE, UNI, NX>([&](int k) -> u64& { return x[k][2]; }, [&](int k) -> u64& { return x[k][3]; },
-                                [&](int k) -> int& { return b[k][2]; }, [&](int k) -> int& { return b[k][3]; }, r[4], r[5], q);
+        const int after = gs_stage<W, UNI, NX>(b, [&](int k) -> u64& { return x[k][0]; }, [&](int k) -> u64& { return x[k][1]; }, r[2], r[3], q);
+        gs_stage<W, UNI, NX>(b, [&](int k) -> u64& { return x[k][2]; }, [&](int k) -> u64& { return x[k][3]; }, r[4], r[5], q);
+        b = after;
     }
-    gs_stage<WIDE, UNI, 2 * NX>([&](int k) -> u64& { return x[k >> 1][k & 1]; }, [&](int k) -> u64& { return x[k >> 1][2 + (k & 1)]; },
-                                [&](int k) -> int& { return b[k >> 1][k & 1]; }, [&](int k) -> int& { return b[k >> 1][2 + (k & 1)]; }, r[0], r[1], q);
-    if (WIDE) {
-#pragma unroll
-        for (int i = 0; i < NX; i++) settle4(x[i], b[i], q);
-    }
+    b = gs_stage<W, UNI, 2 * NX>(b, [&](int k) -> u64& { return x[k >> 1][k & 1]; }, [&](int k) -> u64& { return x[k >> 1][2 + (k & 1)]; }, r[0], r[1], q);
 }
-template <bool WIDE, bool UNI = false, bool ONE = false>
-__device__ __forceinline__ void fwd_block2_r(u64 (&x)[4], const u64 (&r)[6], u64 q) {
-    fwd_block2_x<WIDE, UNI, 1, ONE>(reinterpret_cast<u64 (&)[1][4]>(x), r, q);
+template <int W, bool UNI = false, bool ONE = false>
+__device__ __forceinline__ void fwd_block2_r(u64 (&x)[4], const u64 (&r)[6], u64 q, int& b) {
+    fwd_block2_x<W, UNI, 1, ONE>(reinterpret_cast<u64 (&)[1][4]>(x), r, q, b);
 }
-template <bool WIDE, bool UNI = false, bool ONE = false>
-__device__ __forceinline__ void inv_block2_r(u64 (&x)[4], const u64 (&r)[6], u64 q, int bound) {
-    inv_block2_x<WIDE, UNI, 1, ONE>(reinterpret_cast<u64 (&)[1][4]>(x), r, q, bound);
+template <int W, bool UNI = false, bool ONE = false>
+__device__ __forceinline__ void inv_block2_r(u64 (&x)[4], const u64 (&r)[6], u64 q, int& bound) {
+    inv_block2_x<W, UNI, 1, ONE>(reinterpret_cast<u64 (&)[1][4]>(x), r, q, bound);
 }
 // the three twiddles of such a block and their companions
 __device__ __forceinline__ void tw_block2(u64 (&r)[6], const ulonglong2* tw, uint32_t s0, uint32_t G) {
@@ -219,18 +213,6 @@ __device__ __forceinline__ uint32_t galois_pos(uint32_t j, uint32_t g, uint32_t 
 }
 
 // ---------------------------------------------------------------- rows with 4 points per thread
-// a pointer to constant memory, which no store can change: loads through it stay scalar after stores
-typedef const __attribute__((address_space(4))) u64* const_u64;
-// what the row kernels need of a modulus, in scalar registers
-__device__ __forceinline__ ModConst mod_const(const ModConst* mc, uint32_t mi) {
-    const const_u64 p = (const_u64)(uintptr_t)uni64((u64)(mc + mi));
-    ModConst m = {};
-    m.q = p[offsetof(ModConst, q) / 8];
-    m.mu = p[offsetof(ModConst, mu) / 8];
-    const u64 v = p[offsetof(ModConst, bits) / 8];
-    m.bits = (uint32_t)v; m.rec = (uint32_t)(v >> 32);
-    return m;
-}
 // In the last block (four neighbours a lane) lane t takes points 4T .. 4T+3, T = row4_last(t): 16 lanes then read factors that lie
 // side by side (tw_pos), where T = t made every quad of lanes read from four places.
 __device__ __forceinline__ uint32_t row4_last(uint32_t t) { return ((t & 15u) << 2) | (t >> 4); }
@@ -280,11 +262,13 @@ struct Row4 {
         }
     }
 };
-// The eight stages of NX rows at once, 64 threads to a row: values 64k + t in, 4T + k out (forward, T = row4_last(t)), the other way round
-// (inverse; narrow moduli: inputs below 2q, results below 2q; wide: below 4q).  s: 256 LDS words for each row, `stride` apart, on
-// a multiple of 16 bytes.  A block's values are written where they were read, so a lane waits for no other between the two.
-template <bool WIDE, int NX>
+// The eight stages of NX rows at once, 64 threads to a row: values 64k + t in, 4T + k out (forward, T = row4_last(t); W > 0: inputs below
+// w_lim), the other way round (inverse: inputs below 2q, results below 2q, W > 0: below w_half).  s: 256 LDS words for each row,
+// `stride` apart, on a multiple of 16 bytes.  A block's values are written where they were read, so a lane waits for no other between
+// the two.
+template <int W, int NX>
 __device__ __forceinline__ void row4_fwd(u64 (&x)[NX][4], const u64 (&w)[4][6], u64* s, uint32_t stride, const Row4& at, u64 q) {
+    int b = w_lim(W);
 #pragma unroll
     for (int i = 0; i < 4; i++) {
         if (i) {
@@ -292,15 +276,15 @@ __device__ __forceinline__ void row4_fwd(u64 (&x)[NX][4], const u64 (&w)[4][6], 
 #pragma unroll
             for (int c = 0; c < NX; c++) at.load(i, x[c], s + c * stride);
         }
-        if (i == 0) fwd_block2_x<WIDE, true, NX>(x, w[i], q);            // its factors are the same for the whole row
-        else fwd_block2_x<WIDE, false, NX>(x, w[i], q);
+        if (i == 0) fwd_block2_x<W, true, NX>(x, w[i], q, b);             // its factors are the same for the whole row
+        else fwd_block2_x<W, false, NX>(x, w[i], q, b);
         if (i < 3) {
 #pragma unroll
             for (int c = 0; c < NX; c++) at.store(i, x[c], s + c * stride);
         }
     }
 }
-template <bool WIDE, int NX>
+template <int W, int NX>
 __device__ __forceinline__ void row4_inv(u64 (&x)[NX][4], const u64 (&w)[4][6], u64* s, uint32_t stride, const Row4& at, u64 q, const ModConst& m) {
     int bound = 2;                                       // narrow: 2, 10, 40, 160, at the end 640
 #pragma unroll
@@ -310,15 +294,14 @@ __device__ __forceinline__ void row4_inv(u64 (&x)[NX][4], const u64 (&w)[4][6], 
 #pragma unroll
             for (int c = 0; c < NX; c++) at.load(i, x[c], s + c * stride);
         }
-        if (i == 0) inv_block2_x<WIDE, true, NX>(x, w[i], q, bound);     // its factors are the same for the whole row
-        else inv_block2_x<WIDE, false, NX>(x, w[i], q, bound);
-        bound = narrow_after(bound, 2);
+        if (i == 0) inv_block2_x<W, true, NX>(x, w[i], q, bound);         // its factors are the same for the whole row
+        else inv_block2_x<W, false, NX>(x, w[i], q, bound);
         if (i) {
 #pragma unroll
             for (int c = 0; c < NX; c++) at.store(i, x[c], s + c * stride);
         }
     }
-    if (!WIDE) {
+    if (W == 0) {
 #pragma unroll
         for (int c = 0; c < NX; c++)
 #pragma unroll

@@ -48,10 +48,10 @@ struct RsTile {
 #pragma unroll
         for (int k = 0; k < 4; k++) buf[word(point(i, k))] = x[k];
     }
-    // points of the last block to points of the first: below 4q before and after for wide moduli, below 2q and 640q for narrow ones
-    template <bool WIDE>
+    // points of the last block to points of the first: below 2q and 640q (narrow moduli), below w_half before and after (others)
+    template <int W>
     __device__ __forceinline__ void inverse(u64 (&x)[4], u64* buf, const u64 (&w)[NB][6], u64 q, const ModConst& m) const {
-        int bound = WIDE ? 4 : 2;
+        int bound = W ? w_half(W) : 2;
 #pragma unroll
         for (int i = NB - 1; i >= 0; i--) {
             if (i + 1 < NB) {
@@ -59,20 +59,21 @@ struct RsTile {
                 else __syncthreads();
                 load(x, buf, i);
             }
-            if (!WIDE && LC == 9 && i == 0) {            // nine stages: the last two would leave the range
+            if (W == 0 && LC == 9 && i == 0) {            // nine stages: the last two would leave the range
 #pragma unroll
                 for (int k = 0; k < 4; k++) x[k] = reduce_lazy<10>(x[k], q, m.bits, m.rec);
                 bound = 2;
             }
-            if (2 * i + 1 >= LC) inv_block2_r<WIDE, false, true>(x, w[i], q, bound);
-            else if (i < 2) inv_block2_r<WIDE, true>(x, w[i], q, bound);
-            else inv_block2_r<WIDE>(x, w[i], q, bound);
-            if (!WIDE) bound = narrow_after(bound, 2 * i + 1 >= LC ? 1 : 2);
+            if (2 * i + 1 >= LC) inv_block2_r<W, false, true>(x, w[i], q, bound);
+            else if (i < 2) inv_block2_r<W, true>(x, w[i], q, bound);
+            else inv_block2_r<W>(x, w[i], q, bound);
             if (i) store(buf, x, i);
         }
     }
-    template <bool WIDE>
+    // points of the first block below 5q to points of the last
+    template <int W>
     __device__ __forceinline__ void forward(u64 (&x)[4], u64* buf, const u64 (&w)[NB][6], u64 q) const {
+        int b = 5;
 #pragma unroll
         for (int i = 0; i < NB; i++) {
             if (i) {
@@ -80,9 +81,9 @@ struct RsTile {
                 else __syncthreads();
                 load(x, buf, i);
             }
-            if (2 * i + 1 >= LC) fwd_block2_r<WIDE, false, true>(x, w[i], q);
-            else if (i < 2) fwd_block2_r<WIDE, true>(x, w[i], q);
-            else fwd_block2_r<WIDE>(x, w[i], q);
+            if (2 * i + 1 >= LC) fwd_block2_r<W, false, true>(x, w[i], q, b);
+            else if (i < 2) fwd_block2_r<W, true>(x, w[i], q, b);
+            else fwd_block2_r<W>(x, w[i], q, b);
             if (i + 1 < NB) store(buf, x, i);
         }
     }
@@ -93,6 +94,7 @@ struct RsTile {
 // which every wavefront reaches after its last access to that buffer.
 template <int LC>
 __global__ __launch_bounds__(RS_THREADS, 4) void rescale_cols_kernel(RescaleCols rc, const ModConst* mc, const ulonglong2* ftw, const ulonglong2* itw) {
+    ieee_off();
     using G = RsTile<LC>;
     constexpr uint32_t TPX = 1u << (LC - 5);             // tiles of a limb per XCD
     __shared__ u64 lds[2 * RS_LDS];
@@ -106,24 +108,23 @@ __global__ __launch_bounds__(RS_THREADS, 4) void rescale_cols_kernel(RescaleCols
     g.factors(w, itw + ((size_t)rc.level << (LC + 8)));
     const ModConst ml = mod_const(mc, rc.level);
     const u64 h = ml.q >> 1;
-    if (rc.wide_inv >> rc.level & 1u) g.template inverse<true>(x, lds + RS_LDS, w, ml.q, ml);
-    else g.template inverse<false>(x, lds + RS_LDS, w, ml.q, ml);
+    if (!(rc.wide_inv >> rc.level & 1u)) g.template inverse<0>(x, lds + RS_LDS, w, ml.q, ml);
+    else if (!(rc.widest >> rc.level & 1u)) g.template inverse<1>(x, lds + RS_LDS, w, ml.q, ml);
+    else g.template inverse<2>(x, lds + RS_LDS, w, ml.q, ml);
     g.factors(w, ftw + ((size_t)r0 << (LC + 8)));
-    {
-        const const_u64 p = (const_u64)(uintptr_t)uni64((u64)&mc[rc.level].ninv);
 #pragma unroll
-        for (int k = 0; k < 4; k++) x[k] = addmod(csub(shoup_lazy(x[k], p[0], p[1], ml.q), ml.q), h, ml.q);
-    }
+    for (int k = 0; k < 4; k++) x[k] = csub_min(csub_min(shoup_lazy(x[k], ml.ninv, ml.ninv_sh, ml.q), ml.q) + h, ml.q);
 #pragma unroll 1
     for (uint32_t r = r0;;) {
         asm("" : "+v"(g.t));                             // what follows from the lane is worked out anew, not kept in registers
         const ModConst m = mod_const(mc, r);
-        const u64 q = m.q, one_sh = *(const_u64)(uintptr_t)uni64((u64)&mc[r].one_sh), up = uni64(q - barrett64(h, q, m.mu, m.bits));
+        const u64 q = m.q, one_sh = m.one_sh, up = uni64(q - barrett64(h, q, m.mu, m.bits));
         u64 y[4], *buf = lds + ((r - r0) & 1u) * RS_LDS;
 #pragma unroll
         for (int k = 0; k < 4; k++) y[k] = shoup_lazy4(x[k], 1, one_sh, q) + up;      // below 5q
-        if (rc.wide_fwd >> r & 1u) g.template forward<true>(y, buf, w, q);
-        else g.template forward<false>(y, buf, w, q);
+        if (!(rc.wide_fwd >> r & 1u)) g.template forward<0>(y, buf, w, q);
+        else if (!(rc.widest >> r & 1u)) g.template forward<1>(y, buf, w, q);
+        else g.template forward<2>(y, buf, w, q);
         u64* dst = rc.dst + ((size_t)(limb * rc.level + r) << (LC + 8));
         if (++r < r1) g.factors(w, ftw + ((size_t)r << (LC + 8)));
 #pragma unroll
@@ -142,10 +143,11 @@ bool rescale_cols_pays(const he_ctx* ctx, uint32_t n, uint32_t level) { return (
 int32_t launch_rescale_cols(he_ctx* ctx, const u64* src, u64* dst, uint32_t n, uint32_t level) {
     if (n == 0) return HE_OK;
     if (ctx->logN < 13 || ctx->logN > 17 || level == 0 || level >= ctx->nq) return he_fail(ctx, HE_ERR_BADARG, "rescale columns: bad shape");
-    RescaleCols rc = {src, dst, level, 0, 0, 0, 0};
+    RescaleCols rc = {src, dst, level, 0, 0, 0, 0, 0};
     for (uint32_t i = 0; i <= level; i++) {
         rc.wide_fwd |= (u64)!narrow_fwd(ctx->mod[i]) << i;
         rc.wide_inv |= (u64)!narrow_inv(ctx->mod[i]) << i;
+        rc.widest |= (u64)widest(ctx->mod[i]) << i;
     }
     // The moduli of a tile are shared out, each share with the inverse columns of its own, while that makes at most three work groups
     // per compute unit: a rescale after a product at level 11 of N = 2^16 117.4 us with up to 768 or 1024, 120.4 with 2048, 123.6 with

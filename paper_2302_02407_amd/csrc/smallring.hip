@@ -47,20 +47,35 @@ __device__ __forceinline__ void tw_commit(const TwRegs& r, ulonglong2* twl, uint
 
 // Two stages on 4 points, factors with Shoup's companion from the LDS table.  Forward: wide moduli below 16q in and out, others up by 8q.
 // Inverse: below 4q in and out, for any modulus below 2^60.
+__device__ __forceinline__ void sr_ct(u64& X, u64& Y, u64 w, u64 w_sh, u64 q) {
+    const u64 S = shoup_acc(X, Y, w, w_sh, q);
+    Y = (X + X + 4 * q) - S;
+    X = S;
+}
+__device__ __forceinline__ void sr_gs(u64& X, u64& Y, u64 bq, u64 w, u64 w_sh, u64 q) {
+    const u64 d = (X + bq) - Y;
+    X = X + Y;
+    Y = shoup_lazy4(d, w, w_sh, q);
+}
 template <bool WIDE>
 __device__ __forceinline__ void sr_fwd2(u64 (&x)[4], const ulonglong2* tw, uint32_t s0, uint32_t G, u64 q) {
     u64 r[6];
     tw_block2(r, tw, s0, G);
     if (WIDE) { x[0] = csub_u(x[0], 8 * q); x[1] = csub_u(x[1], 8 * q); }
-    ct_bfly(x[0], x[2], r[0], r[1], q, 4 * q);
-    ct_bfly(x[1], x[3], r[0], r[1], q, 4 * q);
-    ct_bfly(x[0], x[1], r[2], r[3], q, 4 * q);
-    ct_bfly(x[2], x[3], r[4], r[5], q, 4 * q);
+    sr_ct(x[0], x[2], r[0], r[1], q);
+    sr_ct(x[1], x[3], r[0], r[1], q);
+    sr_ct(x[0], x[1], r[2], r[3], q);
+    sr_ct(x[2], x[3], r[4], r[5], q);
 }
 __device__ __forceinline__ void sr_inv2(u64 (&x)[4], const ulonglong2* tw, uint32_t s0, uint32_t G, u64 q) {
     u64 r[6];
     tw_block2(r, tw, s0, G);
-    inv_block2_r<true>(x, r, q, 4);
+    sr_gs(x[0], x[1], 4 * q, r[2], r[3], q);
+    sr_gs(x[2], x[3], 4 * q, r[4], r[5], q);
+    sr_gs(x[0], x[2], 8 * q, r[0], r[1], q);
+    sr_gs(x[1], x[3], 4 * q, r[0], r[1], q);
+    x[0] = csub_u(csub_u(x[0], 8 * q), 4 * q);
+    x[1] = csub_u(x[1], 4 * q);
 }
 
 // Forward transform of the whole limb in LDS (decimation in time, psi folded into the twiddles; natural order in,

@@ -8,7 +8,7 @@ from he_inputs.params import HEParams, is_prime
 
 pytestmark = pytest.mark.gpu
 
-LINES = {"inverse": (1 << 63) // 640, "forward": (1 << 63) // 96}
+LINES = {"inverse": (1 << 63) // 640, "forward": (1 << 63) // 96, "widest": (1 << 63) // 13}
 
 
 def primes_from(start, step, count):
