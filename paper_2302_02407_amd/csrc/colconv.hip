@@ -45,6 +45,41 @@ __device__ __forceinline__ uint32_t cc_row(uint32_t r, uint32_t cl) {
     constexpr uint32_t LT = LC - 4, LCOLS = 10 - LC;
     return cc_word(r >> LT, ((r & ((1u << LT) - 1u)) << LCOLS) + cl);
 }
+// Factors of the second register block (rows 16t .. 16t+15): 2^LC - 16 entries of the table in a row, which a wavefront reads once, side by side,
+// and keeps in its LDS region.  Read from memory where they are used, the four or more lanes of a row group each asked for the same
+// 16 bytes fifteen times over, as much work for the memory pipeline as the points themselves: without those loads (uniform factors, wrong
+// results) the conversions of 240 rotations took 8449 us instead of 8947.
+template <int LC>
+struct CcFactors {
+    static constexpr int N = LC >= 8 ? 4 : LC == 7 ? 2 : 1;       // loads of 64 entries from the table's first
+    static constexpr uint32_t LAST = 1u << (LC - 1);              // first entry of the last stage, whose eight a row group are one apart from the next eight
+    v2u64 v[N];
+    static __device__ __forceinline__ uint32_t word(uint32_t k, uint32_t lane) {
+        if (64 * k >= LAST) return 64 * k + (64 * k - LAST) / 8 + lane + (lane >> 3);
+        return 64 * k + lane + (64 * k + 63 >= LAST && lane >= LAST ? (lane - LAST) >> 3 : 0);
+    }
+    __device__ __forceinline__ void load(ctw_t tw, uint32_t lane) {
+#pragma unroll
+        for (int k = 0; k < N; k++) v[k] = (tw + 64 * k)[lane];
+    }
+    __device__ __forceinline__ void put(u64* reg, uint32_t lane) const {
+#pragma unroll
+        for (int k = 0; k < N; k++) reinterpret_cast<v2u64*>(reg)[word(k, lane)] = v[k];
+    }
+    // factors G0 .. G1-1 of stage LC-4+u for rows 16t .. 16t+15
+    template <int G0, int G1>
+    static __device__ __forceinline__ void get(ulonglong2 (&w)[15], const u64* reg, int u, uint32_t t) {
+        const v2u64* p = reinterpret_cast<const v2u64*>(reg) + (u == 3 ? 9 * t : t << u);
+#pragma unroll
+        for (int g = G0; g < G1; g++) { const v2u64 f = p[(1u << (LC - 4 + u)) + g]; w[(1 << u) - 1 + g] = make_ulonglong2(f.x, f.y); }
+    }
+    template <int U0>
+    static __device__ __forceinline__ void first(ulonglong2 (&w)[15], const u64* reg, uint32_t t) {       // the stages before the last
+        if (U0 < 1) get<0, 1>(w, reg, 0, t);
+        if (U0 < 2) get<0, 2>(w, reg, 1, t);
+        if (U0 < 3) get<0, 4>(w, reg, 2, t);
+    }
+};
 // Inverse column stages of one source limb, output scaling, canonical residues into the limb's LDS region.
 template <int LC, int W>
 __device__ __forceinline__ void cc_source(u64* reg, const u64* src, const ColConv& cc, const ScaleList& sc, uint32_t mi, uint32_t si,
@@ -53,15 +88,21 @@ __device__ __forceinline__ void cc_source(u64* reg, const u64* src, const ColCon
     const uint32_t t = lane >> LCOLS, cl = lane & ((1u << LCOLS) - 1u), c = c0 + cl;
     const ctw_t tw = (ctw_t)(uintptr_t)(itw + ((size_t)mi << (LC + 8)));
     u64 x[16];
+    ulonglong2 w1[15], w2[15];
+    CcFactors<LC> f;
+    f.load(tw, lane);
 #pragma unroll
     for (int j = 0; j < 16; j++) x[j] = (src + j * 256)[t * 4096 + c];
-    ulonglong2 w1[15], w2[15];
-    tw_load_c<U0, 4>(w2, tw, LC - 4, t);
     const const_u64 mp = (const_u64)(uintptr_t)(mc + mi);
     const u64 q = uni64(mp[0]);
     const u64 cs = sc.s[si], cs_sh = sc.s_sh[si], cw = sc.w[si], cw_sh = sc.w_sh[si];
     int bound = W ? w_half(W) : 2;
+    f.put(reg, lane);
+    wave_exchange();
+    f.template first<U0>(w2, reg, t);
+    f.template get<0, 8>(w2, reg, 3, t);
     inv_stages<W, U0, 4>(x, w2, q, bound);
+    wave_exchange();
 #pragma unroll
     for (int j = 0; j < 16; j++) reg[cc_row<LC>(16 * t + j, cl)] = x[j];
     tw_load_c<1, 4>(w1, tw, 0, 0);
@@ -92,7 +133,8 @@ __device__ __forceinline__ void cc_target(u64* reg, u64* dst, uint32_t mi, const
     const const_u64 mp = (const_u64)(uintptr_t)(mc + mi);
     const u64 q = uni64(mp[0]);
     ulonglong2 w2[15];
-    tw_load_c<(U0 < 3 ? U0 : 3), 3>(w2, tw, LC - 4, t);
+    CcFactors<LC> f;
+    f.load(tw, lane);
     u64 x[16];
 #pragma unroll
     for (int k = 0; k < 16; k++) x[k] = reg[cc_word(k, lane)];
@@ -104,26 +146,21 @@ __device__ __forceinline__ void cc_target(u64* reg, u64* dst, uint32_t mi, const
     wave_exchange();
 #pragma unroll
     for (int j = 0; j < 16; j++) x[j] = reg[cc_row<LC>(16 * t + j, cl)];
-    // the last stage's eight factors arrive in two halves, each into the registers that earlier factors leave: with the
+    wave_exchange();
+    f.put(reg, lane);
+    wave_exchange();
+    f.template first<U0>(w2, reg, t);
+    // the last stage's eight factors come in two halves, each into the registers that earlier factors leave: with the
     // source bytes that stay for the next targets there is no room for all of them
     if (U0 < 2) fwd_stages<W, (U0 < 2 ? U0 : 2), 2>(x, w2, q, b);
-    ctw_t p3 = tw + ((1u << (LC - 1)) + (t << 3));
-    v2u64 wa[4], wb[4];
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int g = 0; g < 4; g++) wa[g] = p3[g];
-    __builtin_amdgcn_sched_barrier(0);
+    SCHED_FENCE();
+    f.template get<0, 4>(w2, reg, 3, t);
+    SCHED_FENCE();
     if (U0 < 3) fwd_stages<W, (U0 < 2 ? 2 : U0), (U0 < 3 ? 3 : U0)>(x, w2, q, b);
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int g = 0; g < 4; g++) wb[g] = p3[4 + g];
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int g = 0; g < 4; g++)
-        ct_stage<W, false, 1>(b, [&](int) -> u64& { return x[2 * g]; }, [&](int) -> u64& { return x[2 * g + 1]; }, wa[g].x, wa[g].y, q);
-#pragma unroll
-    for (int g = 0; g < 4; g++)
-        ct_stage<W, false, 1>(b, [&](int) -> u64& { return x[8 + 2 * g]; }, [&](int) -> u64& { return x[9 + 2 * g]; }, wb[g].x, wb[g].y, q);
+    SCHED_FENCE();
+    f.template get<4, 8>(w2, reg, 3, t);
+    SCHED_FENCE();
+    fwd_stages<W, 3, 4>(x, w2, q, b);
     before();
 #pragma unroll
     for (int j = 0; j < 16; j++) (dst + j * 256)[t * 4096 + c] = x[j];
@@ -220,7 +257,7 @@ __global__ __launch_bounds__(CC_THREADS, 4) void col_conv_kernel(ColConv cc, Sca
     ieee_off();
     constexpr int LCOLS = (PTS == 16 ? 10 : 8) - LC, TPX = (256 >> LCOLS) / 8;       // tiles of a group per XCD
     constexpr int REGION = PTS == 16 ? CC_REGION : 272, NB = PTS / 2;                // LDS words of a limb's tile, blocks of 16 points per wavefront
-    __shared__ u64 lds[CC_WAVES * REGION];
+    __shared__ __attribute__((aligned(16))) u64 lds[CC_WAVES * REGION];
     __shared__ ConvOperand ops[CC_WAVES];                                              // of a round's targets
     auto point = [](uint32_t w, int b, uint32_t p16) {
         return PTS == 16 ? cc_word(2 * w + (b >> 2), 16 * (b & 3) + p16) : c4_word(32 * w + 16 * b + p16);
@@ -288,21 +325,21 @@ __global__ __launch_bounds__(CC_THREADS, 4) void col_conv_kernel(ColConv cc, Sca
             const v4i* K = reinterpret_cast<const v4i*>(ops[4 * s + g].bias);
             const v4i a0 = A[0], a1 = A[16], k0 = K[0], k1 = K[1], mk = K[2];      // digits 0..3, digits 4..7 (256 bytes on); -q, rec, bits
             const uint32_t n0 = (uint32_t)mk.x, n1 = (uint32_t)mk.y, rec = (uint32_t)mk.z, bits = (uint32_t)mk.w;
-            // quotient of a value below 2^(bits+14) from its top: sh = bits - 18 (at least 32)
-            const uint32_t sh = bits > 50 ? bits - 18 : 32, e = bits - 1 - sh;
+            // quotient of a value below 2^(bits+14) from its 32 bits above bit 32 + sh (sh at most 10)
+            const uint32_t sh = bits > 50 ? bits - 50 : 0, e = bits - 33 - sh, up = 16 - sh;
             u64* out = lds + (4 * s + g) * REGION;
-            const bool mine = t0 + 4 * s + g < nt;
 #pragma unroll
             for (int b = 0; b < NB; b++) {
                 const v4i d0 = __builtin_amdgcn_mfma_i32_16x16x64_i8(a0, frag[b], k0, 0, 0, 0);
                 const v4i d1 = __builtin_amdgcn_mfma_i32_16x16x64_i8(a1, frag[b], k1, 0, 0, 0);
+                // p01 and p23 are positive (conv_operand), the upper two of either sign; the value is lo + 2^32 * (p45 + 2^16 p67)
                 const int p01 = d0.x + (d0.y << 8), p23 = d0.z + (d0.w << 8), p45 = d1.x + (d1.y << 8), p67 = d1.z + (d1.w << 8);
-                const int64_t lo = (int64_t)p23 * 65536 + p01, hi = (int64_t)p67 * 65536 + p45 + (lo >> 32);
-                const uint32_t qh = __umulhi((uint32_t)((u64)hi >> (sh - 32)), rec) >> e;
-                u64 v = ((u64)(uint32_t)hi << 32) | (uint32_t)lo;
-                v += (u64)qh * n0;
-                v = ((u64)add3((uint32_t)(v >> 32), qh * n1, 0) << 32) | (uint32_t)v;
-                if (mine) out[point(w, b, p16)] = v;
+                const u64 lo = mad_wide((uint32_t)p23, 65536u, (uint32_t)p01);
+                const int top = p45 + (int)(uint32_t)(lo >> 32);
+                const uint32_t qh = __umulhi(((uint32_t)p67 << up) + (uint32_t)(top >> sh), rec) >> e;
+                const u64 v = (u64)qh * n0 + lo;
+                const uint32_t vh = add3((uint32_t)(v >> 32), ((uint32_t)p67 << 16) + (uint32_t)p45, qh * n1);
+                out[point(w, b, p16)] = ((u64)vh << 32) | (uint32_t)v;       // a target beyond the list: a region that nobody reads
             }
         }
         __syncthreads();

@@ -269,6 +269,9 @@ static void conv_operand(const u64* hat, uint32_t ns, const ModConst& mc, ConvOp
     u128 k = (u128)h_mulmod(total, 128, m) + ((u128)m << 12);
     for (uint32_t b = 0; b < 7; b++) { op.bias[b] = (int32_t)(k & 0xFF); k >>= 8; }
     op.bias[7] = (int32_t)k;
+    // a digit sum is at most 2^20 either way: what makes digits 0, 1 and 2, 3 together positive is taken from digits 2 and 4
+    op.bias[1] += 1 << 21; op.bias[2] -= 1 << 13;
+    op.bias[3] += 1 << 22; op.bias[4] -= 1 << 14;
     op.nq = 0 - m;
     op.rec = mc.rec;
     op.bits = mc.bits;

@@ -89,6 +89,13 @@ __device__ __forceinline__ uint32_t add3(uint32_t a, uint32_t b, uint32_t c) {
     return r;
 }
 
+// a * b + c as one instruction where the compiler sees a shift
+__device__ __forceinline__ u64 mad_wide(uint32_t a, uint32_t b, uint32_t c) {
+    u64 r, carry;
+    asm("v_mad_u64_u32 %0, %1, %2, %3, %4" : "=v"(r), "=s"(carry) : "v"(a), "s"(b), "v"((u64)c));
+    return r;
+}
+
 // x + (w*y mod q), the product in [0, 4q): Shoup's product with the approximate quotient above (one multiply fewer and
 // no carry chain; the quotient is at most 2 short, each unit adds q to the remainder).  One multiply-add chain modulo
 // 2^64 with x as its first addend and -q as the quotient's factor: two wide multiply-adds for the low columns, four
