@@ -249,6 +249,13 @@ __device__ __forceinline__ void cc_class(u64 wide, u64 widest, uint32_t mi, F&& 
     }
 }
 
+// The lane's number: what follows from it is worked out anew, not kept in registers
+__device__ __forceinline__ uint32_t lane_again() {
+    uint32_t l;
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=&v"(l));
+    return l;
+}
+
 // grid: groups * tiles.  Work groups go to the XCDs round-robin: each XCD gets neighbouring tiles of a group, so that the
 // tiles that share a memory line are read and written through one L2.
 template <int LC, int PTS>
@@ -276,12 +283,14 @@ __global__ __launch_bounds__(CC_THREADS, 4) void col_conv_kernel(ColConv cc, Sca
     auto op_load = [&](uint32_t t0) {
         const uint32_t m = t0 + w < nt ? (uint32_t)(mods >> (8 * w)) & 255u : (uint32_t)mods & 255u;
         const ConvOperand* p = st.op + m;
-        op_dig = reinterpret_cast<const u64*>(p)[lane];
-        op_rest = reinterpret_cast<const uint32_t*>(p)[128 + (lane & 15u)];
+        const uint32_t l = lane_again();
+        op_dig = reinterpret_cast<const u64*>(p)[l];
+        op_rest = reinterpret_cast<const uint32_t*>(p)[128 + (l & 15u)];
     };
     auto op_store = [&]() {
-        reinterpret_cast<u64*>(ops + w)[lane] = op_dig;
-        if (lane < 16) reinterpret_cast<uint32_t*>(ops + w)[128 + lane] = op_rest;
+        const uint32_t l = lane_again();
+        reinterpret_cast<u64*>(ops + w)[l] = op_dig;
+        if (l < 16) reinterpret_cast<uint32_t*>(ops + w)[128 + l] = op_rest;
     };
     op_load(tb);
     if (w < st.ns) {
@@ -304,9 +313,8 @@ __global__ __launch_bounds__(CC_THREADS, 4) void col_conv_kernel(ColConv cc, Sca
         const u64 y1 = 2 * g + 1 < st.ns ? lds[(2 * g + 1) * REGION + word] : 0;
         frag[b] = v4i{(int)(uint32_t)y0, (int)(uint32_t)(y0 >> 32), (int)(uint32_t)y1, (int)(uint32_t)(y1 >> 32)};
     }
-    uint32_t ln = lane;
     for (uint32_t t0 = tb; t0 < nt; t0 += CC_WAVES) {
-        asm("" : "+v"(ln));                                  // what follows from the lane is worked out anew, not kept in registers
+        uint32_t ln = lane_again();
         const uint32_t g = ln >> 4, p16 = ln & 15;
         // this wavefront's target and the factors of its first block, which arrive during the conversion
         const bool have = t0 + w < nt;
@@ -352,6 +360,7 @@ __global__ __launch_bounds__(CC_THREADS, 4) void col_conv_kernel(ColConv cc, Sca
             op_load(t0 + CC_WAVES);
         }
         auto before = [&]() { if (more) op_store(); };
+        ln = lane_again();
         if (have) {
             u64* dst = st.dst + (size_t)rep * cc.dst_stride + ((size_t)li << (LC + 8));
             cc_class(cc.wide_fwd, cc.widest, mi, [&](auto W, uint32_t m) {
