@@ -259,7 +259,7 @@ __device__ __forceinline__ uint32_t lane_again() {
 // grid: groups * tiles.  Work groups go to the XCDs round-robin: each XCD gets neighbouring tiles of a group, so that the
 // tiles that share a memory line are read and written through one L2.
 template <int LC, int PTS>
-__global__ __launch_bounds__(CC_THREADS, 4) void col_conv_kernel(ColConv cc, ScaleList sc, const ModConst* mc, const ulonglong2* ftw,
+__global__ __launch_bounds__(CC_THREADS, PTS == 16 ? 4 : 2) void col_conv_kernel(ColConv cc, ScaleList sc, const ModConst* mc, const ulonglong2* ftw,
                                                                  const ulonglong2* itw) {
     ieee_off();
     constexpr int LCOLS = (PTS == 16 ? 10 : 8) - LC, TPX = (256 >> LCOLS) / 8;       // tiles of a group per XCD
@@ -293,6 +293,13 @@ __global__ __launch_bounds__(CC_THREADS, 4) void col_conv_kernel(ColConv cc, Sca
         if (l < 16) reinterpret_cast<uint32_t*>(ops + w)[128 + l] = op_rest;
     };
     op_load(tb);
+    // 4 points: all factors, of the first round's target ahead of the sources (small launches have the registers, and a round each)
+    u64 w4[4][6];
+    auto factors4 = [&](uint32_t t0) {
+        const uint32_t m = t0 + w < nt ? (uint32_t)(mods >> (8 * w)) & 255u : (uint32_t)mods & 255u;
+        c4_factors<LC>(w4, ftw + ((size_t)m << (LC + 8)), lane_again());
+    };
+    if (PTS == 4) factors4(tb);
     if (w < st.ns) {
         const u64* src = st.src + (size_t)rep * cc.src_stride + ((size_t)w << (LC + 8));
         const uint32_t mi = st.mod0 + w;
@@ -320,9 +327,8 @@ __global__ __launch_bounds__(CC_THREADS, 4) void col_conv_kernel(ColConv cc, Sca
         const bool have = t0 + w < nt;
         const uint32_t mi = have ? (uint32_t)(mods >> (8 * w)) & 255u : (uint32_t)mods & 255u, li = (uint32_t)(lims >> (8 * w)) & 255u;
         ulonglong2 w1[15];                                   // 16 points per lane
-        u64 w4[4][6];                                        // 4 points: all factors
         if constexpr (PTS == 16) tw_load_c<0, 4>(w1, (ctw_t)(uintptr_t)(ftw + ((size_t)mi << (LC + 8))), 0, 0);
-        else c4_factors<LC>(w4, ftw + ((size_t)mi << (LC + 8)), ln);
+        else if (t0 != tb) factors4(t0);
         __syncthreads();                                     // the regions are free (operands read, last targets done)
         // four targets (s) at a time: lane group g works on target t0 + 4s + g and this lane supplies row lane % 16 = (target (lane
         // % 16) / 4, digit lane % 4) of the left factor
