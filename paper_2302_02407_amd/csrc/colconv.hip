@@ -256,8 +256,9 @@ __device__ __forceinline__ uint32_t lane_again() {
     return l;
 }
 
-// grid: groups * tiles.  Work groups go to the XCDs round-robin: each XCD gets neighbouring tiles of a group, so that the
-// tiles that share a memory line are read and written through one L2.
+// grid: (parts * tiles, sets, repetitions), so that nothing has to be divided, or loaded first, to find the set.  Work groups go to the
+// XCDs round-robin: each XCD gets neighbouring tiles of a group, so that the tiles that share a memory line are read and written
+// through one L2.
 template <int LC, int PTS>
 __global__ __launch_bounds__(CC_THREADS, PTS == 16 ? 4 : 2) void col_conv_kernel(ColConv cc, ScaleList sc, const ModConst* mc, const ulonglong2* ftw,
                                                                  const ulonglong2* itw) {
@@ -270,11 +271,10 @@ __global__ __launch_bounds__(CC_THREADS, PTS == 16 ? 4 : 2) void col_conv_kernel
         return PTS == 16 ? cc_word(2 * w + (b >> 2), 16 * (b & 3) + p16) : c4_word(32 * w + 16 * b + p16);
     };
     const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const uint32_t slot = blockIdx.x >> 3, tile = (blockIdx.x & 7u) * TPX + slot % TPX, gp = slot / TPX, grp = gp / cc.parts;
-    const uint32_t set = grp % cc.n_sets, rep = grp / cc.n_sets, c0 = tile << LCOLS;
-    const ColConvSet& st = cc.set[set];
+    const uint32_t slot = blockIdx.x >> 3, tile = (blockIdx.x & 7u) * TPX + slot % TPX, rep = blockIdx.z, c0 = tile << LCOLS;
+    const ColConvSet& st = cc.set[blockIdx.y];
     u64* reg = lds + w * REGION;
-    const uint32_t tb = (gp - grp * cc.parts) * cc.share, nt = min(st.nt, tb + cc.share);
+    const uint32_t tb = slot / TPX * cc.share, nt = min(st.nt, tb + cc.share);
     // the first round's list is asked for before the sources: everything else of the round waits for it
     u64 mods = uni64(*reinterpret_cast<const u64*>(st.mod + tb)), lims = uni64(*reinterpret_cast<const u64*>(st.limb + tb));
     // this wavefront's part of the next round's operands on its way to LDS; a target beyond the list: the round's first
@@ -410,8 +410,7 @@ int32_t launch_col_conv(he_ctx* ctx, ColConv& cc, const ScaleList& sc, uint32_t 
     // 198.5; nothing measured was faster so by more than the runs differ.
     const uint32_t parts = std::max(1u, std::min(rounds, 256 / work));
     cc.share = (rounds + parts - 1) / parts * CC_WAVES;
-    cc.parts = (rounds * CC_WAVES + cc.share - 1) / cc.share;
-    const dim3 grid(work * cc.parts), block(CC_THREADS);
+    const dim3 grid(tiles16 * (small ? 4 : 1) * ((rounds * CC_WAVES + cc.share - 1) / cc.share), cc.n_sets, reps), block(CC_THREADS);
 #define CC_LAUNCH(LC_)                                                                                                                        \
     case LC_:                                                                                                                                 \
         if (small) hipLaunchKernelGGL((col_conv_kernel<LC_, 4>), grid, block, 0, ctx->stream, cc, sc, ctx->d_mc, ctx->d_tw, ctx->d_itw);        \

@@ -246,7 +246,7 @@ struct ColConv {
     size_t src_stride, dst_stride;
     u64 wide_fwd, wide_inv, widest;    // bit per modulus (narrow_fwd, narrow_inv, widest)
     uint32_t n_sets;
-    uint32_t parts, share;     // work groups that share a tile's targets, `share` targets each (set by the launch)
+    uint32_t share;            // targets of a work group of those that share a tile (set by the launch)
 };
 int32_t launch_col_conv(he_ctx* ctx, ColConv& cc, const ScaleList& sc, uint32_t reps, uint32_t limb_passes);
 // Column passes of Rescale (rescale.hip): src [n][N] holds the dropped limbs (modulus `level`) in the state the inverse row pass
