@@ -260,7 +260,7 @@ __device__ __forceinline__ uint32_t lane_again() {
 // XCDs round-robin: each XCD gets neighbouring tiles of a group, so that the tiles that share a memory line are read and written
 // through one L2.
 template <int LC, int PTS>
-__global__ __launch_bounds__(CC_THREADS, PTS == 16 ? 4 : 2) void col_conv_kernel(ColConv cc, ScaleList sc, const ModConst* mc, const ulonglong2* ftw,
+__global__ __launch_bounds__(CC_THREADS, 4) void col_conv_kernel(ColConv cc, ScaleList sc, const ModConst* mc, const ulonglong2* ftw,
                                                                  const ulonglong2* itw) {
     ieee_off();
     constexpr int LCOLS = (PTS == 16 ? 10 : 8) - LC, TPX = (256 >> LCOLS) / 8;       // tiles of a group per XCD
