@@ -994,54 +994,53 @@ struct HoistIp {
 // every term: they are loaded once into LDS and each term reads them back permuted, so that the only global loads left
 // per (term, digit) are the two key values.  LDS: J*beta*2 KiB.  grid (N/256, number of limbs in sel).
 //
-// Products are taken in halves, three multiplications each: the kernel is bound by its vector instructions (measured:
-// they issue nearly all the time with three wavefronts per SIMD), so their count per product is what matters.  With
-// h = 27 for moduli of at most 54 bits and h = 30 for wider ones (up to 60 bits), a canonical digit value d = d1*2^h + d0 and a canonical key value
-// k = k1*2^h + k0 give d*k = d0*k0 + (d0*k1 + d1*k0)*2^h + d1*k1*2^2h with d0*k1 + d1*k0 = (d0-d1)*(k1-k0) + d0*k0 + d1*k1.
-// Three 64-bit accumulators per output take the sums of d0*k0, of d1*k1 and (signed) of (d0-d1)*(k1-k0) directly from
-// the 32x32+64-bit multiply-adds, with no carries: three instructions per product, against four multiply-adds and ten
-// others (carries, moves) for a 128-bit accumulation.  Every partial product is below 2^2h in magnitude, so after `period` pairs (32 for h = 27, 6
-// for h = 30: (period+3)*2^2h < 2^64, and period*2^(2*bits-2h) + 3q < 100q) the middle sum is formed, the carries of the
-// low and middle sums move up, the high sum is brought below 3q, and the signed accumulator is set to what keeps the
-// identity; the three sums are put together and reduced once at the end.  Digits are made canonical (the forward
-// transform leaves them below 2q) and split while they are staged into LDS, the low half in the low word.  JT = size
-// of the register tile: ciphertexts a.J..JT-1 repeat ciphertext 0 and are not stored.
+// Products are taken in halves that go into three 64-bit sums straight from the 32x32+64-bit multiply-adds, with no carries: what the kernel
+// spends on a product is three or four instructions, against four multiply-adds and ten others (carries, moves) for a 128-bit sum.
+//   at most 54 bits: halves of 27 bits, d*k = d0*k0 + (d0*k1 + d1*k0)*2^27 + d1*k1*2^54 with d0*k1 + d1*k0 = (d0-d1)*(k1-k0) + d0*k0 +
+//     d1*k1, three multiplications; the sums of d0*k0, d1*k1 and (signed) (d0-d1)*(k1-k0) take 2^9 products, more than any call has;
+//   wider: balanced halves of 30 bits, d0 and k0 in [-2^29, 2^29), d taken in (-q/2, q/2), and four multiplications, because the middle
+//     sum's products are then so much smaller than (d0-d1)*(k1-k0) that 20 (q near 2^59) or 10 (2^60) fit, where the three of
+//     unsigned halves let 6 fit, after which every sum had to move its carries up, as many instructions again as the products took.
+// Digits are made canonical (the forward transform leaves them below 2q) and split while they are staged into LDS, the low half in
+// the low word.  JT = size of the register tile: ciphertexts a.J..JT-1 repeat ciphertext 0 and are not stored.
 #define HSL_MAX_TILES 24      // J * beta digit tiles of 2 KiB: 48 KiB of LDS
 #define HSL_RING 2            // (term, digit) pairs whose key values are in registers or on their way
 // the raised-basis limbs one launch works on: blockIdx.y indexes this list
 struct LimbSel {
     uint32_t r[HE_MAX_MODULI];
 };
-template <int JT>
-__global__ __launch_bounds__(KS_THREADS, 3) void hoisted_sum_ip_local_kernel(HoistIp a, LimbSel sel, u64* __restrict__ acc,
-                                                                             const ModConst* mc, uint32_t logN, uint32_t R,
-                                                                             uint32_t beta, uint32_t M, uint32_t level, uint32_t nq,
-                                                                             uint32_t alpha, uint32_t init) {
-    extern __shared__ u64 dig[];                         // a.J * beta tiles of KS_THREADS values
-    const uint32_t n = blockIdx.x * KS_THREADS + threadIdx.x, r = sel.r[blockIdx.y];
-    const uint32_t mi = r <= level ? r : nq + (r - level - 1);
-    const ModConst m = mc[mi];
-    const uint32_t h = m.bits > 54 ? 30u : 27u, period = m.bits > 54 ? 6u : 32u;
-    const u64 lo_h = (1ull << h) - 1;
-    const size_t ro = ((size_t)r << logN) + n, cstride = (size_t)R << logN;
+template <int JT, bool WIDE>
+__device__ __forceinline__ void hoisted_sum_ip(const HoistIp& a, uint32_t r, uint32_t mi, const ModConst& m, u64* dig, u64* __restrict__ acc, uint32_t logN,
+                                               uint32_t R, uint32_t beta, uint32_t M, uint32_t level, uint32_t alpha, uint32_t init) {
+    const uint32_t n = blockIdx.x * KS_THREADS + threadIdx.x;
+    constexpr int H = WIDE ? 30 : 27;
+    constexpr u64 lo_h = (1ull << H) - 1;
+    // products a middle sum takes: |d0| k1 + |d1| |k0| of each, below 2^63 together (at most 31, which the low sums take)
+    const uint32_t period = WIDE ? (uint32_t)min((u64)31, ((1ull << 34) - 64) / ((m.q >> 30) + (m.q >> 31) + 3)) : 1u << 9;
+    const size_t ro = (size_t)r << logN, cstride = (size_t)R << logN;
     for (uint32_t j = 0; j < beta; j++) {
         const bool own_digit = r <= level && r / alpha == j;
-        const size_t doff = own_digit ? ro : ((size_t)(j * R + r) << logN) + n;
+        const size_t doff = own_digit ? ro : (size_t)(j * R + r) << logN;
 #pragma unroll
         for (int i = 0; i < JT; i++) {
             if ((uint32_t)i < a.J) {
-                const u64 v = reduce_full<7>((own_digit ? a.own[i] : a.raised[i])[doff], m.q, m.bits, m.rec);
-                dig[(j * a.J + i) * KS_THREADS + threadIdx.x] = (v & lo_h) | ((v >> h) << 32);
+                const u64 v = reduce_full<7>(((own_digit ? a.own[i] : a.raised[i]) + doff)[n], m.q, m.bits, m.rec);
+                u64 lo = v & lo_h, hi = v >> H;
+                if (WIDE) {
+                    const int64_t c = (int64_t)(v > m.q >> 1 ? v - m.q : v), top = (c + (1 << 29)) >> 30;
+                    lo = (uint32_t)(int32_t)(c - (top << 30)); hi = (uint32_t)(int32_t)top;
+                }
+                dig[(j * a.J + i) * KS_THREADS + threadIdx.x] = lo | (hi << 32);
             }
         }
     }
-    // per output and component: low sum, high sum, and the signed sum bm = (middle sum) - low - high
-    // (bm is kept modulo 2^64: the middle sum it stands for is below 2^64, so wrap-around arithmetic recovers it)
+    // per output and component: low sum, high sum, and bm = (middle sum) - low - high (at most 54 bits, modulo 2^64) or the
+    // middle sum (wider moduli; all three signed)
     u64 b0[JT], b2[JT], a0[JT], a2[JT], bm[JT], am[JT];
 #pragma unroll
     for (int i = 0; i < JT; i++) b0[i] = b2[i] = a0[i] = a2[i] = bm[i] = am[i] = 0;
     __syncthreads();
-    const size_t kstride = (size_t)M << logN, koff = ((size_t)mi << logN) + n;
+    const size_t kstride = (size_t)M << logN;
     // lane t (mod 16) keeps term t's key address and Galois element: the loop then picks them with a lane read instead
     // of a scalar load from the argument block, whose latency every step would wait for
     uint32_t kp_lo = 0, kp_hi = 0, g_lane = 1;
@@ -1056,17 +1055,17 @@ __global__ __launch_bounds__(KS_THREADS, 3) void hoisted_sum_ip_local_kernel(Hoi
         return (const u64 __attribute__((address_space(1)))*)(((uintptr_t)hi << 32) | lo);   // a global, not a generic, address
     };
     // Software pipeline, pinned with scheduling barriers (left alone, the compiler issues every LDS read right before its
-    // use and waits for it).  The register tile is worked in two halves: while one half's products run, the digit values
-    // of the other half - of this pair, then of the next pair - are on their way from LDS; the key values of a pair are
+    // use and waits for it).  The register tile is worked in pieces of two outputs: while one piece's products run, the digit values
+    // of the next - of this pair, then of the next pair - are on their way from LDS; the key values of a pair are
     // requested HSL_RING pairs ahead.  Past the end the last key pair is requested again and its products are switched
     // off, so that the loop body has no branch around a load.
-    constexpr int HA = (JT + 1) / 2, HB = JT - HA;
-    u64 kb[HSL_RING], ka[HSL_RING], dA[HA], dB[HB > 0 ? HB : 1];
+    constexpr int PT = JT >= 4 ? 2 : 1, NP = JT / PT;    // outputs of a piece, pieces
+    u64 kb[HSL_RING], ka[HSL_RING], d[2][PT];
     uint32_t tp = 0, jp = 0, pending = 0;
     auto request_key = [&](u64& kbu, u64& kau) {
         const bool more = tp < a.T;
-        const auto e = key_of(more ? tp : a.T - 1) + (size_t)(2 * (more ? jp : beta - 1)) * kstride + koff;
-        kbu = e[0]; kau = e[kstride];
+        const auto e = key_of(more ? tp : a.T - 1) + ((size_t)(2 * (more ? jp : beta - 1)) * kstride + ((size_t)mi << logN));
+        kbu = e[n]; kau = (e + kstride)[n];
         if (more && ++jp == beta) { jp = 0; tp++; }
     };
     // (t, j) = the pair whose digits are read next, lsrc = where this thread's value of term t sits in its tile
@@ -1075,77 +1074,99 @@ __global__ __launch_bounds__(KS_THREADS, 3) void hoisted_sum_ip_local_kernel(Hoi
         return galois_src_ks(n, __builtin_amdgcn_readlane(g_lane, term < a.T ? term : 0), logN) & (KS_THREADS - 1);
     };
     uint32_t lsrc = lsrc_of(0);
-    auto read_a = [&]() {
+    auto read = [&](int p, u64 (&to)[PT]) {
         const u64* dj = dig + (size_t)j * a.J * KS_THREADS + lsrc;
 #pragma unroll
-        for (int i = 0; i < HA; i++) dA[i] = dj[((uint32_t)i < a.J ? i : 0) * KS_THREADS];
+        for (int i = 0; i < PT; i++) to[i] = dj[((uint32_t)(PT * p + i) < a.J ? PT * p + i : 0) * KS_THREADS];
     };
-    auto read_b = [&]() {
-        const u64* dj = dig + (size_t)j * a.J * KS_THREADS + lsrc;
-#pragma unroll
-        for (int i = 0; i < HB; i++) dB[i] = dj[((uint32_t)(HA + i) < a.J ? HA + i : 0) * KS_THREADS];
-    };
-    // the middle sum formed (it is below 2^64, so wrap-around arithmetic gives it exactly), carries moved up (low and
-    // middle sums back below 2^h), the high sum, which stays below 100q, brought below 3q, and the signed sum set to
-    // middle - low - high again: the value of the three sums together is unchanged modulo q
+    // wider moduli: carries moved up, low and middle sums back in [0, 2^30), the high sum (at most 2q + 5.4q either way after `period`
+    // products: period * |d1| k1) made positive by a multiple of q that is at least 8q and brought below 2q
     auto fold1 = [&](u64& lo, u64& mid_s, u64& hi) {
-        u64 mid = mid_s + lo + hi;
-        mid += lo >> h; lo &= lo_h;
-        hi = reduce_lazy<7>(hi + (mid >> h), m.q, m.bits, m.rec); mid &= lo_h;
-        mid_s = mid - lo - hi;
+        mid_s += (u64)((int64_t)lo >> H); lo &= lo_h;
+        hi = reduce_lazy<10>(hi + (u64)((int64_t)mid_s >> H) + (m.q << (63 - m.bits)), m.q, m.bits, m.rec); mid_s &= lo_h;
     };
     auto fold = [&]() {
 #pragma unroll
-        for (int i = 0; i < JT; i++) { fold1(b0[i], bm[i], b2[i]); fold1(a0[i], am[i], a2[i]); }
+        for (int i = 0; i < JT; i++) { fold1(b0[i], bm[i], b2[i]); fold1(a0[i], am[i], a2[i]); __builtin_amdgcn_sched_barrier(0); }
         pending = 0;
     };
     // kbd = kb1 - kb0, kad = ka1 - ka0 (signed)
     auto mac = [&](int i, u64 d, uint32_t kb0, uint32_t kb1, int32_t kbd, uint32_t ka0, uint32_t ka1, int32_t kad) {
         const uint32_t d0 = (uint32_t)d, d1 = (uint32_t)(d >> 32);
         const int32_t dd = (int32_t)(d0 - d1);
+        if (WIDE) {
+            const int32_t e0 = (int32_t)d0, e1 = (int32_t)d1;
+            b0[i] += (u64)((int64_t)e0 * (int32_t)kb0); b2[i] += (u64)((int64_t)e1 * (int32_t)kb1);
+            bm[i] += (u64)((int64_t)e0 * (int32_t)kb1); bm[i] += (u64)((int64_t)e1 * (int32_t)kb0);
+            a0[i] += (u64)((int64_t)e0 * (int32_t)ka0); a2[i] += (u64)((int64_t)e1 * (int32_t)ka1);
+            am[i] += (u64)((int64_t)e0 * (int32_t)ka1); am[i] += (u64)((int64_t)e1 * (int32_t)ka0);
+            return;
+        }
         b0[i] += (u64)d0 * kb0; b2[i] += (u64)d1 * kb1; bm[i] += (u64)((int64_t)dd * kbd);
         a0[i] += (u64)d0 * ka0; a2[i] += (u64)d1 * ka1; am[i] += (u64)((int64_t)dd * kad);
     };
     auto step = [&](u64& kbu, u64& kau, bool valid) {
-        read_b();                                                   // the second half of this pair's digits
-        __builtin_amdgcn_sched_barrier(0);
         const u64 kbv = valid ? kbu : 0, kav = valid ? kau : 0;     // a step past the end adds nothing
-        const uint32_t kb0 = (uint32_t)(kbv & lo_h), kb1 = (uint32_t)(kbv >> h);
-        const uint32_t ka0 = (uint32_t)(kav & lo_h), ka1 = (uint32_t)(kav >> h);
+        // balanced: the low 30 bits with their sign, and what is left of the value above them
+        auto low = [](u64 k) { return WIDE ? (uint32_t)((int32_t)((uint32_t)k << 2) >> 2) : (uint32_t)(k & lo_h); };
+        auto high = [](u64 k) { return WIDE ? (uint32_t)((k + (1u << 29)) >> 30) : (uint32_t)(k >> H); };
+        const uint32_t kb0 = low(kbv), kb1 = high(kbv), ka0 = low(kav), ka1 = high(kav);
         const int32_t kbd = (int32_t)(kb1 - kb0), kad = (int32_t)(ka1 - ka0);
 #pragma unroll
-        for (int i = 0; i < HA; i++) mac(i, dA[i], kb0, kb1, kbd, ka0, ka1, kad);
-        __builtin_amdgcn_sched_barrier(0);
-        if (++j == beta) { j = 0; t++; lsrc = lsrc_of(t); }
-        read_a();                                                   // the first half of the next pair's digits
-        request_key(kbu, kau);
-        __builtin_amdgcn_sched_barrier(0);
+        for (int p = 0; p < NP; p++) {
+            if (p + 1 < NP) {
+                read(p + 1, d[(p + 1) & 1]);
+            } else {                                                // the next pair
+                if (++j == beta) { j = 0; t++; lsrc = lsrc_of(t); }
+                read(0, d[NP & 1]);
+                request_key(kbu, kau);
+            }
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int i = 0; i < HB; i++) mac(HA + i, dB[i], kb0, kb1, kbd, ka0, ka1, kad);
+            for (int i = 0; i < PT; i++) mac(PT * p + i, d[p & 1][i], kb0, kb1, kbd, ka0, ka1, kad);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (NP & 1) d[0][0] = d[1][0];
         pending++;
     };
     const uint32_t total = a.T * beta;
 #pragma unroll
     for (int u = 0; u < HSL_RING; u++) request_key(kb[u], ka[u]);
-    read_a();
+    read(0, d[0]);
     for (uint32_t it = 0; it < total; it += HSL_RING) {  // HSL_RING steps per trip, none of them conditional
-        if (pending + HSL_RING > period) fold();
+        if (WIDE && pending + HSL_RING > period) fold();
 #pragma unroll
         for (int u = 0; u < HSL_RING; u++) step(kb[u], ka[u], it + u < total);
     }
-    fold();
+    if (WIDE) fold();
+    auto total_of = [&](u64 lo, u64 mid, u64 hi) {
+        const SplitSum s = {lo, WIDE ? mid : mid + lo + hi, hi};
+        if (WIDE || m.bits >= 32) return reduce_full<7>(split_reduce_top<H>(s, m), m.q, m.bits, m.rec);
+        return barrett128((u128)s.a0 + ((u128)s.a1 << H) + ((u128)s.a2 << (2 * H)), m.q, m.mu, m.bits);
+    };
 #pragma unroll
     for (int i = 0; i < JT; i++) {
         if ((uint32_t)i < a.J) {
-            const u64 b1 = bm[i] + b0[i] + b2[i], a1 = am[i] + a0[i] + a2[i];
-            const u64 vb = barrett128((u128)b0[i] + ((u128)b1 << h) + ((u128)b2[i] << (2 * h)), m.q, m.mu, m.bits);
-            const u64 va = barrett128((u128)a0[i] + ((u128)a1 << h) + ((u128)a2[i] << (2 * h)), m.q, m.mu, m.bits);
-            u64* o0 = acc + (size_t)(2 * i) * cstride + ro;
-            u64* o1 = acc + (size_t)(2 * i + 1) * cstride + ro;
-            *o0 = init ? vb : addmod(vb, *o0, m.q);
-            *o1 = init ? va : addmod(va, *o1, m.q);
+            __builtin_amdgcn_sched_barrier(0);           // one output at a time: registers
+            const u64 vb = total_of(b0[i], bm[i], b2[i]), va = total_of(a0[i], am[i], a2[i]);
+            u64* o0 = acc + ((size_t)(2 * i) * cstride + ro);
+            u64* o1 = acc + ((size_t)(2 * i + 1) * cstride + ro);
+            o0[n] = init ? vb : addmod(vb, o0[n], m.q);
+            o1[n] = init ? va : addmod(va, o1[n], m.q);
         }
     }
+}
+
+template <int JT>
+__global__ __launch_bounds__(KS_THREADS, 3) void hoisted_sum_ip_local_kernel(HoistIp a, LimbSel sel, u64* __restrict__ acc,
+                                                                             const ModConst* mc, uint32_t logN, uint32_t R,
+                                                                             uint32_t beta, uint32_t M, uint32_t level, uint32_t nq,
+                                                                             uint32_t alpha, uint32_t init) {
+    extern __shared__ u64 dig[];                         // a.J * beta tiles of KS_THREADS values
+    const uint32_t r = sel.r[blockIdx.y], mi = r <= level ? r : nq + (r - level - 1);
+    const ModConst m = mc[mi];
+    if (m.bits > 54) hoisted_sum_ip<JT, true>(a, r, mi, m, dig, acc, logN, R, beta, M, level, alpha, init);
+    else hoisted_sum_ip<JT, false>(a, r, mi, m, dig, acc, logN, R, beta, M, level, alpha, init);
 }
 
 // Whether the Galois elements of a hoisted sum only move values inside aligned blocks of 256 positions, the tile of a
@@ -1228,7 +1249,7 @@ int32_t ks_hoisted_sum(he_ctx* c, uint32_t level, const KsSrc* srcs, uint32_t J,
             for (uint32_t t = 0; t < hi.T; t++) { hi.evk[t] = evks[t0 + t]; hi.g[t] = gs[t0 + t]; }
             for (uint32_t j = 0; j < nb; j++) { hi.raised[j] = raised + (size_t)j * beta * R * N; hi.own[j] = srcs[j0 + j].c1; }
             {
-                // limbs of moduli wider than 54 bits (they move carries every 6 pairs) spread evenly among the others, so
+                // limbs of moduli wider than 54 bits (a product more each, and carries) spread evenly among the others, so
                 // that both kinds are resident together
                 LimbSel sel;
                 {

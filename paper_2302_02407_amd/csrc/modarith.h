@@ -193,10 +193,11 @@ __device__ __forceinline__ u128 split_value(const SplitSum& s) {
 // Congruent to the sums (below 2^(bits+63)), below 6q.  From 32 bits the quotient is taken from a sum's top, a2 * 2^(61-bits) +
 // (a1 + a0 / 2^30) / 2^(bits-31), at most 1.5 below the sum / 2^(bits-1), and the remainder from the sum's low word: 17
 // instructions, where putting the 128-bit sum together first takes 30.
+template <int H = SPLIT_H>
 __device__ __forceinline__ u64 split_reduce_top(const SplitSum& s, const ModConst& m) {
-    const u64 a1 = s.a1 + (s.a0 >> SPLIT_H);
-    const u64 qh = mulhi64_approx((s.a2 << (2 * SPLIT_H + 1 - m.bits)) + (a1 >> (m.bits - SPLIT_H - 1)), m.mu);
-    return s.a0 + (s.a1 << SPLIT_H) + (s.a2 << (2 * SPLIT_H)) - qh * m.q;
+    const u64 a1 = s.a1 + (s.a0 >> H);
+    const u64 qh = mulhi64_approx((s.a2 << (2 * H + 1 - m.bits)) + (a1 >> (m.bits - H - 1)), m.mu);
+    return s.a0 + (s.a1 << H) + (s.a2 << (2 * H)) - qh * m.q;
 }
 template <int N>
 __device__ __forceinline__ void split_reduce(u64 (&v)[N], const SplitSum (&s)[N], const ModConst& m) {
