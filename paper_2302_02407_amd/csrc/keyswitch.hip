@@ -975,7 +975,8 @@ __global__ __launch_bounds__(KS_THREADS) void hoist_c0_sum_kernel(HoistC0 a, con
 // Inner products of a hoisted sum for up to HS_JOBS ciphertexts at once, register-tiled: a thread owns one point of
 // one raised-basis limb for all the ciphertexts and both components; per (term, digit) it loads the two key values
 // once and one digit value per ciphertext, and feeds 2*J multiply-accumulates.
-// acc [J][2][R][N] (canonical); init = 0 continues from its contents (more than HS_TERMS terms).
+// acc [J][2][R][N] (as `settled` leaves it); bit 0 of init clear: the launch continues from its contents (more than HS_TERMS terms); bit 1:
+// two-launch rings.
 #define HS_JOBS 8
 #define HS_TERMS 16
 struct HoistIp {
@@ -1001,8 +1002,7 @@ struct HoistIp {
 //   wider: balanced halves of 30 bits, d0 and k0 in [-2^29, 2^29), d taken in (-q/2, q/2), and four multiplications, because the middle
 //     sum's products are then so much smaller than (d0-d1)*(k1-k0) that 20 (q near 2^59) or 10 (2^60) fit, where the three of
 //     unsigned halves let 6 fit, after which every sum had to move its carries up, as many instructions again as the products took.
-// Digits are made canonical (the forward transform leaves them below 2q) and split while they are staged into LDS, the low half in
-// the low word.  JT = size of the register tile: ciphertexts a.J..JT-1 repeat ciphertext 0 and are not stored.
+// Digits (the forward transform leaves them below 2q) are split while they are staged into LDS, the low half in the low word.  JT = size of the register tile: ciphertexts a.J..JT-1 repeat ciphertext 0 and are not stored.
 #define HSL_MAX_TILES 24      // J * beta digit tiles of 2 KiB: 48 KiB of LDS
 #define HSL_RING 2            // (term, digit) pairs whose key values are in registers or on their way
 // the raised-basis limbs one launch works on: blockIdx.y indexes this list
@@ -1018,20 +1018,26 @@ __device__ __forceinline__ void hoisted_sum_ip(const HoistIp& a, uint32_t r, uin
     // products a middle sum takes: |d0| k1 + |d1| |k0| of each, below 2^63 together (at most 31, which the low sums take)
     const uint32_t period = WIDE ? (uint32_t)min((u64)31, ((1ull << 34) - 64) / ((m.q >> 30) + (m.q >> 31) + 3)) : 1u << 9;
     const size_t ro = (size_t)r << logN, cstride = (size_t)R << logN;
+    // all values of a digit are asked for before the first is worked on
     for (uint32_t j = 0; j < beta; j++) {
         const bool own_digit = r <= level && r / alpha == j;
         const size_t doff = own_digit ? ro : (size_t)(j * R + r) << logN;
+        u64 in[JT];
 #pragma unroll
         for (int i = 0; i < JT; i++) {
-            if ((uint32_t)i < a.J) {
-                const u64 v = reduce_full<7>(((own_digit ? a.own[i] : a.raised[i]) + doff)[n], m.q, m.bits, m.rec);
-                u64 lo = v & lo_h, hi = v >> H;
-                if (WIDE) {
-                    const int64_t c = (int64_t)(v > m.q >> 1 ? v - m.q : v), top = (c + (1 << 29)) >> 30;
-                    lo = (uint32_t)(int32_t)(c - (top << 30)); hi = (uint32_t)(int32_t)top;
-                }
-                dig[(j * a.J + i) * KS_THREADS + threadIdx.x] = lo | (hi << 32);
+            const uint32_t k = (uint32_t)i < a.J ? i : 0;
+            in[i] = ((own_digit ? a.own[k] : a.raised[k]) + doff)[n];
+        }
+#pragma unroll
+        for (int i = 0; i < JT; i++) {
+            // below 2q: split as they are where 2^8 products of 55 bits by 54 fit (at most 54 bits), else canonical
+            const u64 v = WIDE || a.T * beta > 256 ? csub_u(in[i], m.q) : in[i];
+            u64 lo = v & lo_h, hi = v >> H;
+            if (WIDE) {
+                const int64_t c = (int64_t)(v > m.q >> 1 ? v - m.q : v), top = (c + (1 << 29)) >> 30;
+                lo = (uint32_t)(int32_t)(c - (top << 30)); hi = (uint32_t)(int32_t)top;
             }
+            if ((uint32_t)i < a.J) dig[(j * a.J + i) * KS_THREADS + threadIdx.x] = lo | (hi << 32);
         }
     }
     // per output and component: low sum, high sum, and bm = (middle sum) - low - high (at most 54 bits, modulo 2^64) or the
@@ -1141,8 +1147,15 @@ __device__ __forceinline__ void hoisted_sum_ip(const HoistIp& a, uint32_t r, uin
     if (WIDE) fold();
     auto total_of = [&](u64 lo, u64 mid, u64 hi) {
         const SplitSum s = {lo, WIDE ? mid : mid + lo + hi, hi};
-        if (WIDE || m.bits >= 32) return reduce_full<7>(split_reduce_top<H>(s, m), m.q, m.bits, m.rec);
-        return barrett128((u128)s.a0 + ((u128)s.a1 << H) + ((u128)s.a2 << (2 * H)), m.q, m.mu, m.bits);
+        if (WIDE || m.bits >= 32) return split_reduce_top<H>(s, m);
+        return barrett128_lazy((u128)s.a0 + ((u128)s.a1 << H) + ((u128)s.a2 << (2 * H)), m.q, m.mu, m.bits);
+    };
+    // what the transforms behind it take: two-launch rings below 6q (q-limbs, epilogue of the forward rows) or 2q (special primes, inverse
+    // rows; sums that a launch continues), others canonical
+    auto settled = [&](u64 v) {
+        if (init == 3 && r <= level) return v;
+        v = reduce_lazy<7>(v, m.q, m.bits, m.rec);
+        return init & 2u ? v : csub_u(v, m.q);
     };
 #pragma unroll
     for (int i = 0; i < JT; i++) {
@@ -1151,8 +1164,8 @@ __device__ __forceinline__ void hoisted_sum_ip(const HoistIp& a, uint32_t r, uin
             const u64 vb = total_of(b0[i], bm[i], b2[i]), va = total_of(a0[i], am[i], a2[i]);
             u64* o0 = acc + ((size_t)(2 * i) * cstride + ro);
             u64* o1 = acc + ((size_t)(2 * i + 1) * cstride + ro);
-            o0[n] = init ? vb : addmod(vb, o0[n], m.q);
-            o1[n] = init ? va : addmod(va, o1[n], m.q);
+            o0[n] = settled(init & 1u ? vb : vb + o0[n]);
+            o1[n] = settled(init & 1u ? va : va + o1[n]);
         }
     }
 }
@@ -1264,7 +1277,7 @@ int32_t ks_hoisted_sum(he_ctx* c, uint32_t level, const KsSrc* srcs, uint32_t J,
                     }
                 }
                 const dim3 grid(N / KS_THREADS, R), blk(KS_THREADS);
-                const uint32_t init = t0 == 0 ? 1u : 0u;
+                const uint32_t init = (t0 == 0 ? 1u : 0u) | (two_pass(c) ? 2u : 0u);
 #define HSL_LAUNCH(JT) hipLaunchKernelGGL(hoisted_sum_ip_local_kernel<JT>, grid, blk, (size_t)nb * beta * KS_THREADS * sizeof(u64), c->stream, hi, sel, acc, c->d_mc, c->logN, R, beta, \
                                           c->M, level, c->nq, c->alpha, init)
                 if (nb <= 1) HSL_LAUNCH(1); else if (nb <= 2) HSL_LAUNCH(2); else if (nb <= 4) HSL_LAUNCH(4); else HSL_LAUNCH(8);

@@ -358,8 +358,8 @@ __global__ __launch_bounds__(P2_THREADS, 4) void ntt_row_fwd_kernel(P2Args a, Li
 }
 
 // ---------------------------------------------------------------- inverse row pass
-// Stages LC+7 .. LC+4 on contiguous points, exchange, stages LC+3 .. LC on strided points: inputs canonical, results below
-// 2q (wide moduli: w_half).  Narrow moduli: bounds 1 -> 40 after the first block, -> 640 after the second, one quotient step at the end.
+// Stages LC+7 .. LC+4 on contiguous points, exchange, stages LC+3 .. LC on strided points: inputs below 2q, results below
+// 2q (wide moduli: w_half).  Narrow moduli: bounds 2 -> 40 after the first block, -> 640 after the second, one quotient step at the end.
 // LANES as in row_fwd.
 template <int W, int LANES>
 __device__ __forceinline__ void row_inv(const P2Args& a, const LimbTab& tab, uint32_t e, uint32_t tile, u64* sm) {
@@ -394,7 +394,7 @@ __device__ __forceinline__ void row_inv(const P2Args& a, const LimbTab& tab, uin
 #pragma unroll
         for (int j = 0; j < 16; j++) x[j] = s[17 * t + j];
         ulonglong2 w1[15];
-        int bound = 1;
+        int bound = 2;
         inv_stages<W, 2, 4>(x, w2, q, bound);
         SCHED_FENCE();
         tw_load<2, 4>(w1, tw, lc, b);                        // into the registers that the first two stages' factors leave
@@ -541,7 +541,7 @@ __device__ __forceinline__ void row_run_inv(const P2Args& a, const LimbTab& tab,
         SCHED_FENCE();
 #pragma unroll
         for (int j = 0; j < 16; j++) x[j] = s[17 * t + j];
-        int bound = 1;
+        int bound = 2;
         run_keep(w2);
         inv_stages<W, 0, 4>(x, w2, q, bound);
         SCHED_FENCE();
