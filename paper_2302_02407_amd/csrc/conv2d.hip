@@ -16,100 +16,92 @@
 #define MAC_MAX_PT 144
 struct MacMany {
     const u64* ct[MAC_MAX_IN];                           // [2][CL][N]
-    const u64* pt[MAC_MAX_PT];                           // [o * NI + i], [CL][N]
+    const u64* pt[MAC_MAX_PT];                           // [o * n_in + i], [CL][N]
     u64* acc[MAC_MAX_IN];                                // [2][CL][N]
     uint32_t n_in, n_out, init;                          // init = 0: continues from acc's current (canonical) contents
     uint32_t c1_tap;                                     // 0xFFFFFFFF: every ct has both components; else only this one has a
                                                          // second component (the others are [CL][N])
 };
 
-// MulFilter&Sum of several outputs at once: a thread keeps NC adjacent coefficients of both components of all (at most NI)
-// ciphertexts in registers and then reads the plaintexts of one output after the other, each byte of which is used once:
-// bound by reading them (non-temporal, so that they do not displace the ciphertexts and accumulators that other kernels
-// read next).  Operands and outputs have CL limbs per component: the level+1 ciphertext primes, followed by the special
-// primes when the operands are key-switch inner products still over the raised basis.  grid: (N/(256 NC), CL).
-template <int NC>
-struct MacVec;
-template <>
-struct MacVec<1> {
-    u64 v[1];
-    __device__ __forceinline__ void load(const u64* p) { v[0] = *p; }
-    __device__ __forceinline__ void load_nt(const u64* p) { v[0] = __builtin_nontemporal_load(p); }
-    __device__ __forceinline__ void store(u64* p) const { *p = v[0]; }
-};
-template <>
-struct MacVec<2> {
-    u64 v[2];
-    __device__ __forceinline__ void load(const u64* p) { const ulonglong2 t = LOAD2(p); v[0] = t.x; v[1] = t.y; }
-    __device__ __forceinline__ void load_nt(const u64* p) { v[0] = __builtin_nontemporal_load(p); v[1] = __builtin_nontemporal_load(p + 1); }
-    __device__ __forceinline__ void store(u64* p) const { STORE2(p) = make_ulonglong2(v[0], v[1]); }
-};
-template <int NI, int NC>
+// MulFilter&Sum of several outputs at once: a thread keeps one coefficient of both components of all NI ciphertexts in
+// registers and then reads the plaintexts of one output after the other, each byte of which is used once: bound by reading
+// them (non-temporal, so that they do not displace the ciphertexts and accumulators that other kernels read next).  The next
+// output's are asked for before the present one's are worked on, and one coefficient rather than two leaves registers for four
+// or five wavefronts a SIMD instead of three: eight ciphertexts of 13 limbs, nine outputs, N = 2^16 (0.72 GB) took 140 us with
+// two coefficients, 136 with the next output's asked for as well, 131 with one coefficient, 124..128 with both (5.7 TB/s; a large
+// copy reaches 6.7).  One kernel per number of ciphertexts: with a run-time number below a rounded-up one every load stood
+// behind a branch of its own and waited for the load before it (nine ciphertexts of 3 limbs, one output, N = 2^12: 7.1 us, now
+// 4.3).  ONE: only ciphertext c1_tap has a second component.  Operands and outputs have CL limbs per component: the level+1
+// ciphertext primes, followed by the special primes when the operands are key-switch inner products still over the raised
+// basis.  grid: (N/256, CL).
+#define MAC_RUN 8                                        // products of residues of 60 bits that a split sum takes (below 60 bits: 16)
+template <int NI, bool ONE>
 __global__ __launch_bounds__(CV_THREADS) void mac_many_kernel(MacMany a, const ModConst* mc, uint32_t logN, uint32_t CL, uint32_t level, uint32_t nq) {
-    const uint32_t n = (blockIdx.x * CV_THREADS + threadIdx.x) * NC;
-    const uint32_t limb = blockIdx.y;
-    if (n >> logN) return;
+    const uint32_t n = blockIdx.x * CV_THREADS + threadIdx.x, limb = blockIdx.y;
     const ModConst m = mc[limb <= level ? limb : nq + (limb - level - 1)];
     const size_t o0 = ((size_t)limb << logN) + n, o1 = ((size_t)(limb + CL) << logN) + n;
-    MacVec<NC> c0[NI], c1[NI];
+    constexpr int N1 = ONE ? 1 : NI;
+    u64 c0[NI], c1[N1], next[NI];
 #pragma unroll
-    for (uint32_t i = 0; i < NI; i++) {
-        if (i < a.n_in) c0[i].load(a.ct[i] + o0);
-        if (i < a.n_in && (a.c1_tap == 0xFFFFFFFFu || a.c1_tap == i)) c1[i].load(a.ct[i] + o1);
-        else {
+    for (int i = 0; i < NI; i++) c0[i] = a.ct[i][o0];
 #pragma unroll
-            for (int k = 0; k < NC; k++) { c1[i].v[k] = 0; if (i >= a.n_in) c0[i].v[k] = 0; }
-        }
-    }
+    for (int i = 0; i < N1; i++) c1[i] = a.ct[ONE ? a.c1_tap : i][o1];
+#pragma unroll
+    for (int i = 0; i < NI; i++) next[i] = __builtin_nontemporal_load(a.pt[i] + o0);
     for (uint32_t o = 0; o < a.n_out; o++) {
-        MacVec<NC> p[NI], r0, r1;
-        // (their halves are formed anew for every output: kept, they would take twice the registers)
+        u64 p[NI], p1 = 0, r0 = 0, r1 = 0;
 #pragma unroll
-        for (uint32_t i = 0; i < NI; i++) {
+        for (int i = 0; i < NI; i++) p[i] = next[i];
+        // (the halves are formed anew for every output: kept, they would take twice the registers)
 #pragma unroll
-            for (int k = 0; k < NC; k++) asm("" : "+v"(c0[i].v[k]), "+v"(c1[i].v[k]));
+        for (int i = 0; i < NI; i++) asm("" : "+v"(c0[i]));
+#pragma unroll
+        for (int i = 0; i < N1; i++) asm("" : "+v"(c1[i]));
+        if (o + 1 < a.n_out) {
+#pragma unroll
+            for (int i = 0; i < NI; i++) next[i] = __builtin_nontemporal_load(a.pt[(o + 1) * NI + i] + o0);
         }
+        if (!a.init) { r0 = a.acc[o][o0]; r1 = a.acc[o][o1]; }
+        SplitSum s0 = {0, 0, 0}, s1 = {0, 0, 0};
 #pragma unroll
-        for (uint32_t i = 0; i < NI; i++) {
-            if (i < a.n_in) p[i].load_nt(a.pt[o * NI + i] + o0);
-        }
-        if (a.init) {
-#pragma unroll
-            for (int k = 0; k < NC; k++) r0.v[k] = r1.v[k] = 0;
-        } else {
-            r0.load(a.acc[o] + o0);
-            r1.load(a.acc[o] + o1);
-        }
-#pragma unroll
-        for (int k = 0; k < NC; k++) {
-            SplitSum s0 = {0, 0, 0}, s1 = {0, 0, 0};
-#pragma unroll
-            for (uint32_t i = 0; i < NI; i++) {
-                if (i && i % SPLIT_MAX == 0) {           // running totals below q + 6q, after a second time below 2q again
-                    r0.v[k] += split_reduce(s0, m); r1.v[k] += split_reduce(s1, m);
-                    if (i > SPLIT_MAX) { r0.v[k] = reduce_lazy<4>(r0.v[k], m.q, m.bits, m.rec); r1.v[k] = reduce_lazy<4>(r1.v[k], m.q, m.bits, m.rec); }
-                    s0 = s1 = SplitSum{0, 0, 0};
+        for (int i = 0; i < NI; i++) {
+            if (i == MAC_RUN && m.bits == 60) {
+                r0 += split_reduce(s0, m);
+                s0 = SplitSum{0, 0, 0};
+                if (!ONE) {
+                    r1 += split_reduce(s1, m);
+                    s1 = s0;
                 }
-                if (i < a.n_in) { split_mac(s0, c0[i].v[k], p[i].v[k]); split_mac(s1, c1[i].v[k], p[i].v[k]); }
             }
-            static_assert(NI <= 3 * SPLIT_MAX, "totals stay below 16q");
-            r0.v[k] = reduce_full<7>(r0.v[k] + split_reduce(s0, m), m.q, m.bits, m.rec);
-            r1.v[k] = reduce_full<7>(r1.v[k] + split_reduce(s1, m), m.q, m.bits, m.rec);
+            split_mac(s0, c0[i], p[i]);
+            if (ONE) p1 = a.c1_tap == (uint32_t)i ? p[i] : p1;
+            else split_mac(s1, c1[i], p[i]);
         }
-        r0.store(a.acc[o] + o0);
-        r1.store(a.acc[o] + o1);
+        if (ONE) split_mac(s1, c1[0], p1);
+        static_assert(NI <= 2 * MAC_RUN, "totals stay below q + 12q");
+        a.acc[o][o0] = reduce_full<7>(r0 + split_reduce(s0, m), m.q, m.bits, m.rec);
+        a.acc[o][o1] = reduce_full<7>(r1 + split_reduce(s1, m), m.q, m.bits, m.rec);
     }
 }
 
-// Two coefficients per thread while the ciphertexts' fit the registers (16-byte accesses), one with up to 16 of them.
-static void launch_mac_many(he_ctx* ctx, const MacMany& a, uint32_t CL, uint32_t level) {
-    const dim3 block(CV_THREADS), g1(ctx->N / CV_THREADS, CL), g2((ctx->N + 2 * CV_THREADS - 1) / (2 * CV_THREADS), CL);
-    if (a.n_in <= 8) hipLaunchKernelGGL((mac_many_kernel<8, 2>), g2, block, 0, ctx->stream, a, ctx->d_mc, ctx->logN, CL, level, ctx->nq);
-    else if (a.n_in <= 9) hipLaunchKernelGGL((mac_many_kernel<9, 2>), g2, block, 0, ctx->stream, a, ctx->d_mc, ctx->logN, CL, level, ctx->nq);
-    else hipLaunchKernelGGL((mac_many_kernel<16, 1>), g1, block, 0, ctx->stream, a, ctx->d_mc, ctx->logN, CL, level, ctx->nq);
+#define MAC_MAX_ONE 9                                    // ciphertexts of a launch of which one has a second component
+template <int NI>
+static void launch_mac_many_of(he_ctx* ctx, const MacMany& a, uint32_t CL, uint32_t level) {
+    if constexpr (NI > 0) {
+        if (a.n_in < NI) { launch_mac_many_of<NI - 1>(ctx, a, CL, level); return; }
+        const dim3 grid(ctx->N / CV_THREADS, CL), block(CV_THREADS);
+        if constexpr (NI <= MAC_MAX_ONE) {
+            if (a.c1_tap != 0xFFFFFFFFu) {
+                hipLaunchKernelGGL((mac_many_kernel<NI, true>), grid, block, 0, ctx->stream, a, ctx->d_mc, ctx->logN, CL, level, ctx->nq);
+                return;
+            }
+        }
+        hipLaunchKernelGGL((mac_many_kernel<NI, false>), grid, block, 0, ctx->stream, a, ctx->d_mc, ctx->logN, CL, level, ctx->nq);
+    }
 }
+static void launch_mac_many(he_ctx* ctx, const MacMany& a, uint32_t CL, uint32_t level) { launch_mac_many_of<MAC_MAX_IN>(ctx, a, CL, level); }
 // index of plaintext (o, i) in MacMany::pt for n_in ciphertexts
-static uint32_t mac_pt_index(uint32_t n_in, uint32_t o, uint32_t i) { return o * (n_in <= 8 ? 8 : n_in <= 9 ? 9 : 16) + i; }
+static uint32_t mac_pt_index(uint32_t n_in, uint32_t o, uint32_t i) { return o * n_in + i; }
 
 struct MacTapsAny {
     const u64* ct[CV_MAX_TAPS];

@@ -821,8 +821,17 @@ __global__ __launch_bounds__(KS_THREADS) void rot_sum_kernel(RotSumArgs a, u64* 
     const size_t o = ((size_t)r << logN) + n;
     u64 v = 0;
     if (blockIdx.z == 0) {
-        for (uint32_t t = 0; t < a.n_rot; t++) v = addmod(v, a.c0[t][((size_t)r << logN) + galois_src_ks(n, a.g[t], logN)], q);
-        for (uint32_t t = a.n_rot; t < a.n_rot + a.n_plain; t++) v = addmod(v, a.c0[t][o], q);
+        // four terms' values asked for together (one by one: 21.6 us for 8 terms of 13 limbs, now 20.4)
+        uint32_t t = 0;
+        for (; t + 4 <= a.n_rot; t += 4) {
+            u64 x[4];
+#pragma unroll
+            for (uint32_t i = 0; i < 4; i++) x[i] = a.c0[t + i][((size_t)r << logN) + galois_src_ks(n, a.g[t + i], logN)];
+#pragma unroll
+            for (uint32_t i = 0; i < 4; i++) v = addmod(v, x[i], q);
+        }
+        for (; t < a.n_rot; t++) v = addmod(v, a.c0[t][((size_t)r << logN) + galois_src_ks(n, a.g[t], logN)], q);
+        for (; t < a.n_rot + a.n_plain; t++) v = addmod(v, a.c0[t][o], q);
         s0[o] = v;
     } else {
         for (uint32_t t = a.n_rot; t < a.n_rot + a.n_plain; t++) v = addmod(v, a.c1[t][o], q);

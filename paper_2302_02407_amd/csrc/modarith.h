@@ -173,9 +173,9 @@ __device__ __forceinline__ u64 mulmod(u64 a, u64 b, const ModConst& m) { return 
 
 // Sum of products of values below 2^60 (or below 2^61 with a factor that small primes keep low), halves of 30 bits summed
 // in three 64-bit words that the multiply-adds feed directly: 4 instructions per product besides the splitting, where a
-// 128-bit sum takes 14.  a0 and a2 take below 2^60 per product of canonical residues, a1 below 2^61: 7 products fit.
+// 128-bit sum takes 14.  a0 and a2 take below 2^60 per product of canonical residues, a1 below 2^61:
+// 8 products fit (a1 reaches 16 (2^30 - 1)^2, with a0's carries below 2^64), 16 of residues of at most 59 bits (high halves below 2^29).
 #define SPLIT_H 30
-#define SPLIT_MAX 7
 struct SplitSum {
     u64 a0, a1, a2;
 };
