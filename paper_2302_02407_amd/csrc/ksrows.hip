@@ -36,8 +36,10 @@
 // five rotate-and-sum rounds of one ciphertext at level 5 279 / 277, of 16 at level 11 3158 / 3179.  Choosing by a flag of the launch
 // costs one rotation at level 5 0.7 of its 57.5 us, so there is none.
 //
-// Work order: jobs (they come sorted by key) are the fastest index, then rows; each XCD works on every eighth (limb, row), so
-// that jobs under one key find its row and the twiddles in that XCD's L2.
+// Work order: jobs (they come sorted by key) are the fastest index, then rows of the source; each XCD works on every eighth (limb,
+// row), so that jobs under one key, whose rows of the key and of the factors are then one row too, and jobs of one source find
+// them in that XCD's L2.  In the order of the results' rows jobs of one source shared only the factors: the rotations of three
+// sources above 1686 us, so 1675.
 #include <algorithm>
 
 #include "modarith.h"
@@ -85,6 +87,14 @@ struct KrRow {
         x[0] = v.x; x[1] = v.y; x[2] = u.x; x[3] = u.y;
     }
 };
+
+// The row b with sigma_g(b) = bs.  Exponents of a row agree in their low `rows` bits, and 2k' + 1 = g (2k + 1).
+__device__ __forceinline__ uint32_t kr_row_from(uint32_t bs, uint32_t g, uint32_t rows) {
+    uint32_t inv = g;                                    // right in its low 3 bits, then 6, 12, 24
+#pragma unroll
+    for (int i = 0; i < 3; i++) inv *= 2 - g * inv;
+    return __brev((inv * (2 * (__brev(bs) >> (32 - rows)) + 1)) >> 1) >> (32 - rows);
+}
 
 // W: 0 = narrow in both directions (ntt_blocks.h), 1 = only forward, 2 = in neither, 3 = the widest.
 __device__ constexpr int kr_fwd(int W) { return W < 2 ? 0 : W - 1; }      // classes of the transforms
@@ -467,8 +477,9 @@ __global__ __launch_bounds__(KR_THREADS, MANY ? 3 : 4) void ks_rows_kernel(KsRow
     extern __shared__ __attribute__((aligned(16))) u64 sm[];
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), rows = a.logN - 8;
     const uint32_t item = (blockIdx.x >> 3) * KR_WAVES + wave, un = item / a.J, job = item - un * a.J;
-    const uint32_t u = un * 8 + (blockIdx.x & 7u), r = u >> rows, b = u & ((1u << rows) - 1u);
+    const uint32_t u = un * 8 + (blockIdx.x & 7u), r = u >> rows;
     if (r >= (SP ? a.k : a.L1)) return;
+    const uint32_t b = kr_row_from(u & ((1u << rows) - 1u), a.g[job], rows);
     u64* buf = sm + wave * (256 * (DONE ? 2u : max(a.beta, 2u)));
     const uint32_t width = kr_width(a, SP ? a.nq + r : r), t = threadIdx.x & 63u;
     if (width == 0) ks_row<0, SP, MANY, DONE>(a, job, kr_pin<0>(r), b, t, buf);
@@ -483,8 +494,9 @@ __global__ __launch_bounds__(KR_THREADS, 4) void ks_rows_half_kernel(KsRows a) {
     __shared__ __attribute__((aligned(16))) u64 sm[KR_WAVES * 512];
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), rows = a.logN - 8, t = threadIdx.x & 63u;
     const uint32_t at = (blockIdx.x >> 3) * KR_WAVES + wave, item = at >> 1, un = item / a.J, job = item - un * a.J;
-    const uint32_t u = un * 8 + (blockIdx.x & 7u), r = u >> rows, b = u & ((1u << rows) - 1u);
+    const uint32_t u = un * 8 + (blockIdx.x & 7u), r = u >> rows;
     if (r >= (SP ? a.k : a.L1)) return;
+    const uint32_t b = kr_row_from(u & ((1u << rows) - 1u), a.g[job], rows);
     u64* buf = sm + 512 * wave;
     const uint32_t width = kr_width(a, SP ? a.nq + r : r);
     if (width == 0) ks_row_half<0, SP>(a, job, at & 1u, kr_pin<0>(r), b, t, buf);
