@@ -13,18 +13,18 @@
 // is a product over k = (source, byte), 64 of them, whose right factors split into 8 signed base-256 digits b:
 // v_mfma_i32_16x16x64_i8 with the digits as rows and 16 points as columns.  A source residue in memory order IS the operand
 // (each byte minus 128, which the constant term returns).  Two instructions give 16 points x 4 targets x 8 digits, laid
-// out so that a lane gets the 8 digit sums of one (point, target); they are put together and reduced below 2q in 22
-// vector instructions (counted in the compiled loops), where the vector-unit form of the same sum takes 68 (baseconv_kernel).
+// out so that a lane gets the 8 digit sums of one (point, target); they are put together and reduced below 2q in 16
+// vector instructions, where the vector-unit form of the same sum takes 68 (baseconv_kernel).
 //
-// What bounds it is vector issue: 5969 instructions per wavefront for 8 + 24 limbs (counters), 4 cycles each, fill 0.65 to
-// 0.68 (by card) of the issue slots (2.4 GHz) of the benchmark's launches, which move 2.4 TB/s; wavefronts wait 0.47 of their cycles.
-// Small launches are chains: of 10.6 us of a work group (level 5, tiles of 256 points) 4.4 go by until a source is transformed, 2.3
-// while the slower wavefronts finish theirs, 2.3 until a round's operands are there and 1.6 in the conversion and the targets; its
-// SIMDs' issue slots are half full.  Asking for the round's list before the sources takes one rotation at level 5 from 57.3 to 56.8 us,
-// with six digits at level 6 from 61.0 to 59.6; asking for the operands themselves as well gave nothing.
-// A launch for eight of the benchmark's single rotations went from 162 to 151 us once a round's operands came without dependent
-// vector loads and nothing was kept in scratch memory; sets are sixteen now, 290 to 306 us a launch, 48 % of the kernel time
-// of 240 rotations.
+// What bounds it is vector issue: 4850 instructions per wavefront for 8 + 24 limbs (counters; 5969 with products of eleven and more
+// instructions, sums put together in 22 and operands fetched one by one), 4 cycles each, fill 0.62 of the issue slots at 2.4 GHz
+// and 0.73 of those at the 2.05 GHz that the clock has under this load; 2.75 TB/s move and wavefronts wait 0.41 of their cycles.
+// Sets of sixteen, 24 limbs and eight special primes: 311 us a launch so, 261 to 267 now; with the tiles' accesses side by
+// side (wrong results, a probe) 240, without stores 209, and the instructions alone are some 185.
+// Small launches are chains (level 5, tiles of 256 points, in cycles of a work group): sources asked for at 2900 after a start of
+// 5700, 500 of waiting, 4600 until they are transformed (3500 of them issue), 2700 at the barrier and 2500 in the conversion.
+// Asking for the round's list before the sources takes one rotation at level 5 from 57.3 to 56.8 us, with six digits at level 6 from
+// 61.0 to 59.6; asking for the operands themselves as well gave nothing.
 #include <algorithm>
 #include <type_traits>
 

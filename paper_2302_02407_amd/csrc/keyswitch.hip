@@ -1037,7 +1037,9 @@ struct HoistIp {
 //   wider: balanced halves of 30 bits, d0 and k0 in [-2^29, 2^29), d taken in (-q/2, q/2), and four multiplications, because the middle
 //     sum's products are then so much smaller than (d0-d1)*(k1-k0) that 20 (q near 2^59) or 10 (2^60) fit, where the three of
 //     unsigned halves let 6 fit, after which every sum had to move its carries up, as many instructions again as the products took.
-// Digits (the forward transform leaves them below 2q) are split while they are staged into LDS, the low half in the low word.  JT = size of the register tile: ciphertexts a.J..JT-1 repeat ciphertext 0 and are not stored.
+// Digits (the forward transform leaves them below 2q) are split while they are staged into LDS, the low half in the low word.  Issue
+// bounds it: 15 terms of 8 ciphertexts at level 5 (three digits) 118 us with unsigned halves and a carry move every 6 products above
+// 54 bits, 112 so, 105 with the values of a digit asked for together and nothing reduced further than its reader needs.  JT = size of the register tile: ciphertexts a.J..JT-1 repeat ciphertext 0 and are not stored.
 #define HSL_MAX_TILES 24      // J * beta digit tiles of 2 KiB: 48 KiB of LDS
 #define HSL_RING 2            // (term, digit) pairs whose key values are in registers or on their way
 // the raised-basis limbs one launch works on: blockIdx.y indexes this list

@@ -12,9 +12,11 @@
 //   special primes: rows of the digits -> products with both components of the key -> inverse rows of both sums;
 //   q-limbs:        rows of the digits -> products -> rows of both converted components -> (acc - conv) * P^-1 + addends.
 //
-// What bounds it (cards differ by a few percent): bytes for the q-limbs (sixteen key switches at level 23 of N = 2^16 in 410 us, 1.6
-// GiB moved at 4.2 TB/s, vector issue 0.75 of the slots; 5 TB/s and 0.65 where the digits are complete), vector issue for the special
-// primes (160 us, 0.8: their 60-bit ranges take a reduction every other stage).  A key switch of a batch takes 26 + 10 us in these two launches where rows
+// What bounds it (cards differ by a few percent): bytes and issue together for the q-limbs (sixteen key switches at level 23 of N = 2^16
+// in 415 us, 1.6 GiB moved at 4.2 TB/s, vector issue 0.67 of the slots at 2.4 GHz, 0.79 of those at the 2.05 GHz the clock has
+// under this load; 4.5 TB/s and 0.58 or 0.68 where the digits are complete), vector issue for the special primes (161 us, 0.72 or
+// 0.84: their 60-bit ranges take a conditional subtraction every other stage).  Nine-instruction products and two-instruction
+// subtractions took 8 % of the instructions and 1 % of the time.  A key switch of a batch takes 26 + 10 us in these two launches where rows
 // of the digits, sums with inverse rows and sums with the ModDown took 18 + 9 + 26.  A row is shared by a whole wavefront, 4 points
 // a lane, because then the sums of both components stay in registers (8 sums of three words) and every product is formed once from
 // digits that both components share.  With two wavefronts to a row, a component each, a batch of 240 (in sets of eight) took 24.9 ms
