@@ -151,9 +151,9 @@ typedef struct {
 int32_t he_profile_begin(he_ctx* ctx);
 int32_t he_profile_end(he_ctx* ctx, he_profile_t* h_out);
 /* Vector-ALU roof of the transforms on this GPU, measured: radix-2 butterflies per second when the
- * register blocks of the two-launch passes (Shoup twiddle product from 32-bit multiplies, lazy ranges)
+ * register blocks of the two-launch passes (twiddle products from 32-bit multiplies, lazy ranges)
  * run back to back out of registers: forward and inverse on the first ciphertext prime, forward on
- * the first modulus wider than 57 bits (0 if there is none).  Synchronises the stream. */
+ * the first modulus above 2^63/96 (0 if there is none).  Synchronises the stream. */
 typedef struct {
     double fwd_butterflies_per_s;
     double inv_butterflies_per_s;
