@@ -10,7 +10,7 @@
 // enters the sum through the multiply-adds' own addend (X + w*Y - h*2q accumulated in one chain), and the difference is
 // 2X + 5q minus that sum: two instructions for the quotient h, 7 for the sum (split_acc), 3 for the difference, and 3 for a factor's second
 // word where it is not the same for the whole wavefront (scalar instructions there).  With a quotient of two words it were 16, a
-// product formed on its own and then added and subtracted takes 20.
+// product formed on its own and then added and subtracted takes 20.  (tests/test_butterfly_instructions.py counts them.)
 //
 // Ranges are kept in units of q and known when the code is compiled: a product is below 5q whatever its factor, a forward stage therefore
 // adds that to the bound of every point, an inverse stage doubles it.  What multiplies a factor has to stay
@@ -43,6 +43,9 @@ __device__ __forceinline__ int ct_stage(int b, PX&& X, PY&& Y, u64 w, u64 a, u64
         int bx = b;
 #pragma unroll
         for (int r = 0; r < 2; r++) if (W && bx + 5 > w_lim(W)) halve(x, bx, q);
+        // The compiler puts what comes out of an instruction it does not know last in a sum: a halved x was added behind the multiply-adds, in an
+        // instruction of its own, unless y passes one later.  384 limbs forward, N = 2^16: 57-bit primes 149 -> 144 us, just below 2^60 158 -> 154.
+        if (bx < b) asm("" : "+v"(y));
         const u64 S = split_acc(x, y, w, a, wh, sq.n2q);
         y = (x + x + sq.q5) - S;
         x = S;
