@@ -1,8 +1,10 @@
 """Build the HIP library in-tree: python -m paper_2302_02407_amd.build [--incremental]"""
 import os
 import re
+import shutil
 import subprocess
 import sys
+import tempfile
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -53,15 +55,53 @@ def scratch_kernels(lines):
     return found
 
 
+def device_listing(hipcc, obj):
+    """The assembly of an object's kernels, line by line; empty where it has none."""
+    tools = os.path.join(os.path.dirname(os.path.dirname(os.path.realpath(shutil.which(hipcc) or hipcc))), "llvm", "bin")
+    if not os.path.isdir(tools):
+        tools = "/opt/rocm/llvm/bin"
+    with tempfile.TemporaryDirectory() as tmp:
+        fat, dev = os.path.join(tmp, "fat"), os.path.join(tmp, "dev")
+        headers = _run([os.path.join(tools, "llvm-objdump"), "-h", obj], False)
+        if not any(".hip_fatbin " in l for l in headers):
+            return []
+        _run([os.path.join(tools, "llvm-objcopy"), "--dump-section", ".hip_fatbin=" + fat, obj, os.devnull], False)
+        _run([os.path.join(tools, "clang-offload-bundler"), "--unbundle", "--type=o", "--targets=hipv4-amdgcn-amd-amdhsa--gfx950", "--input=" + fat, "--output=" + dev], False)
+        return _run([os.path.join(tools, "llvm-objdump"), "-d", "--no-show-raw-insn", dev], False)
+
+
+def ieee_kernels(listing):
+    """Kernels of a listing that take a minimum of doubles without having switched the wavefront's IEEE mode off before their first branch
+    (csub_min and ieee_off, modarith.h)."""
+    found, name, entry, off = [], None, True, False
+    for l in listing:
+        m = re.match(r"[0-9a-f]+ <(.*)>:$", l)
+        if m:
+            name, entry, off = m.group(1), True, False
+        elif "s_setreg_imm32_b32 hwreg(HW_REG_MODE, 9, 1), 0" in l:
+            off = off or entry
+        elif re.match(r"\s+s_c?branch", l):
+            entry = False
+        elif "v_min_f64" in l and not off and name not in found:
+            found.append(name)
+    return found
+
+
 def compile_object(hipcc, src, obj, extra=(), verbose=False):
-    """One source to one object.  A kernel that uses scratch memory (registers spilled, an array indexed at run time) is an error, and its
-    object is not kept: one that spilled has given wrong results on this GPU, for a reason that is not known (ksrows.hip)."""
+    """One source to one object; where a kernel is refused that is an error and the object is not kept.  Refused are kernels that use scratch
+    memory (registers spilled, an array indexed at run time): one that spilled has given wrong results on this GPU, for a reason that
+    is not known (ksrows.hip).  And kernels with conditional subtractions by csub_min in a mode in which its minimum of a number and a
+    signalling pattern is not the number."""
     lines = _run([hipcc] + FLAGS + list(extra) + ["-c", src, "-o", obj], verbose)
     bad = scratch_kernels(lines)
     if bad:
         os.remove(obj)
         raise RuntimeError("%s: kernels that use scratch memory: %s" % (os.path.basename(src), ", ".join(
             "%s (%s)" % (n, "dynamic" if b is None else "%d bytes a lane" % b) for n, b in bad)))
+    bad = ieee_kernels(device_listing(hipcc, obj))
+    if bad:
+        os.remove(obj)
+        raise RuntimeError("%s: kernels that use csub_min and do not start with ieee_off(): %s" % (os.path.basename(src), ", ".join(bad)))
 
 
 def source_hash() -> str:

@@ -50,7 +50,8 @@ __device__ __forceinline__ u64 csub_u(u64 x, u64 q) { return mask_add(x + neg_u(
 // x >= q ? x - q : x for x < 2^63 in two instructions: the smaller of x and the difference, taken as doubles, which order bit patterns
 // below 2^63 as the integers they are.  Where the difference is negative, clearing its sign leaves 2^63 - (q - x), which is above x
 // or not a number, and the minimum of a number and none is the number.  For signalling ones that holds with the wavefront's IEEE mode
-// off: kernels that use this start with ieee_off().  q: the same for the whole wavefront.
+// off: kernels that use this start with ieee_off().  Nothing in the source ties the two together, so the build refuses an object with a
+// kernel that has the one and not, before its first branch, the other (build.py).  q: the same for the whole wavefront.
 __device__ __forceinline__ void ieee_off() { asm volatile("s_setreg_imm32_b32 hwreg(HW_REG_MODE, 9, 1), 0"); }
 __device__ __forceinline__ u64 csub_min(u64 x, u64 q) {
     u64 r;

@@ -586,6 +586,7 @@ __global__ __launch_bounds__(P2_THREADS, 4) void ntt_row_run_kernel(P2Args a, Li
 template <bool FWD, int W>
 __global__ __launch_bounds__(P2_THREADS) void bfly_probe_kernel(const ulonglong2* __restrict__ tw, u64 q,
                                                                  u64* __restrict__ out, uint32_t rounds) {
+    ieee_off();
     const uint32_t t = threadIdx.x & 15;
     ulonglong2 w[15];
     u64 x[16];
