@@ -581,8 +581,8 @@ __global__ __launch_bounds__(P2_THREADS, 4) void ntt_row_run_kernel(P2Args a, Li
 // ---------------------------------------------------------------- butterfly-rate probe
 // The vector-ALU roof of the transforms, measured rather than derived: the register blocks of the passes
 // above (four stages on 16 points, twiddles from a 256-entry table that stays in the first-level cache)
-// run back to back with no other memory traffic.  Values wrap around after a few rounds; the timing does
-// not depend on them.
+// run back to back with no other memory traffic, for the class of the modulus.  Values wrap around after a few rounds; the timing
+// does not depend on them.
 template <bool FWD, int W>
 __global__ __launch_bounds__(P2_THREADS) void bfly_probe_kernel(const ulonglong2* __restrict__ tw, u64 q,
                                                                  u64* __restrict__ out, uint32_t rounds) {
@@ -605,6 +605,9 @@ __global__ __launch_bounds__(P2_THREADS) void bfly_probe_kernel(const ulonglong2
 }
 
 int32_t probe_butterfly_rates(he_ctx* ctx, u64* d_out, uint32_t groups, double rate_out[3]) {
+    static void (*const probes[2][3])(const ulonglong2*, u64, u64*, uint32_t) = {
+        {bfly_probe_kernel<false, 0>, bfly_probe_kernel<false, 1>, bfly_probe_kernel<false, 2>},
+        {bfly_probe_kernel<true, 0>, bfly_probe_kernel<true, 1>, bfly_probe_kernel<true, 2>}};
     const uint32_t rounds = 64;                          // 32 butterflies per thread per round
     uint32_t narrow = 0, wide = ctx->M;
     for (uint32_t i = 0; i < ctx->M; i++) if (!narrow_fwd(ctx->mod[i])) { wide = i; break; }
@@ -614,14 +617,14 @@ int32_t probe_butterfly_rates(he_ctx* ctx, u64* d_out, uint32_t groups, double r
     for (int which = 0; which < 3; which++) {
         const uint32_t mi = which == 2 ? wide : narrow;
         rate_out[which] = 0.0;
-        if (mi >= ctx->M || (which == 0 && !narrow_fwd(ctx->mod[mi]))) continue;
-        const ulonglong2* tw = (which == 1 ? ctx->d_itw : ctx->d_tw) + (size_t)mi * ctx->N;
+        if (mi >= ctx->M) continue;
+        const bool fwd = which != 1;
+        const ulonglong2* tw = (fwd ? ctx->d_tw : ctx->d_itw) + (size_t)mi * ctx->N;
+        const u64 q = ctx->mod[mi];
+        void (*const kernel)(const ulonglong2*, u64, u64*, uint32_t) = probes[fwd][(fwd ? narrow_fwd(q) : narrow_inv(q)) ? 0 : widest(q) ? 2 : 1];
         for (int rep = 0; rep < 2; rep++) {              // the first launch warms up
             HE_HIP(ctx, hipEventRecord(e0, ctx->stream));
-            if (which == 0) hipLaunchKernelGGL((bfly_probe_kernel<true, 0>), dim3(groups), dim3(P2_THREADS), 0, ctx->stream, tw, ctx->mod[mi], d_out, rounds);
-            else if (which == 1 && !narrow_inv(ctx->mod[mi])) hipLaunchKernelGGL((bfly_probe_kernel<false, 1>), dim3(groups), dim3(P2_THREADS), 0, ctx->stream, tw, ctx->mod[mi], d_out, rounds);
-            else if (which == 1) hipLaunchKernelGGL((bfly_probe_kernel<false, 0>), dim3(groups), dim3(P2_THREADS), 0, ctx->stream, tw, ctx->mod[mi], d_out, rounds);
-            else hipLaunchKernelGGL((bfly_probe_kernel<true, 1>), dim3(groups), dim3(P2_THREADS), 0, ctx->stream, tw, ctx->mod[mi], d_out, rounds);
+            hipLaunchKernelGGL(kernel, dim3(groups), dim3(P2_THREADS), 0, ctx->stream, tw, q, d_out, rounds);
             HE_HIP(ctx, hipGetLastError());
             HE_HIP(ctx, hipEventRecord(e1, ctx->stream));
             HE_HIP(ctx, hipEventSynchronize(e1));
