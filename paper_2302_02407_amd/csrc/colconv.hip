@@ -36,6 +36,7 @@
 #define CC_REGION 1088            // LDS words of one limb's tile: 16 runs of 64, 4 spare words after each
 
 typedef int v4i __attribute__((ext_vector_type(4)));
+static_assert(alignof(ConvOperand) % alignof(v4i) == 0 && offsetof(ConvOperand, bias) % alignof(v4i) == 0, "read as v4i");
 
 // Word of (run k, lane): a lane that holds rows t + k*T of column cl keeps them at run k, lane t*C + cl.
 __device__ __forceinline__ uint32_t cc_word(uint32_t k, uint32_t lane) { return 68 * k + lane; }

@@ -53,8 +53,8 @@ struct ScaleList {
 };
 
 // One target modulus of a conversion on the matrix cores (colconv.hip; filled by conv_operand in keyswitch.hip).  A wavefront loads one as
-// eight bytes a lane and four of the rest a lane.
-struct ConvOperand {
+// eight bytes a lane and four of the rest a lane; from LDS it is read sixteen at a time.
+struct alignas(16) ConvOperand {
     uint8_t dig[512];
     int32_t bias[8];
     u64 nq;            // -q modulo 2^64
