@@ -81,8 +81,8 @@ def test_thirty_two_channel_blocks_two_launches():
 
 
 def test_moduli_of_57_and_59_bits_single_output():
-    # moduli wider than 54 bits take the 30-bit halves of the LDS-staged inner products (with their carry moves every
-    # six products); one output ciphertext is the smallest register tile
+    # moduli wider than 54 bits take the balanced 30-bit halves of the LDS-staged inner products; one output ciphertext is the
+    # smallest register tile
     prm = toy_params(logN=11, q_bits=57, nq=3, p_bits=59, np_=2, dnum=2, scale=2.0 ** 45, hamming=32, seed=86)
     _run(prm, C_a=16, H=4, W=4, c_out=4, level=2, w_std=0.1, tol=1e-3)
 

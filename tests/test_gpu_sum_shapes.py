@@ -1,6 +1,7 @@
 """GPU parity of the sums' kernels at the edges of how they share out work, on the largest primes below 2^60: the rotated c0 parts of hoisted
 sums (four limbs of the outputs to a work group, sums brought down every eight terms, sixteen terms to a launch), and the plaintext sums
-of a layer with one ModDown per output (only one tap has a second component, nine products of residues of 60 bits at their top)."""
+of a layer with one ModDown per output (only one tap has a second component, nine products of residues of 60 bits at their top).  And, on the
+largest primes below 2^54, hoisted sums of as many products as their sums take."""
 import numpy as np
 import pytest
 
@@ -46,3 +47,22 @@ def test_sums_with_one_second_component(logN):
     ctx.he_conv2d(C_a, side, side, geo.R, 3, level, [dev(pts[o, t]) for o in range(geo.n_out) for t in range(len(geo.taps))], dev(ct), outs, deferred_taps=True)
     for o in range(geo.n_out):
         assert (host(outs[o]) == want[o]).all(), o
+
+
+# 16 terms in the first of two launches: 16 digits make 256 products, as many as the sums take of digits below 2q; from 17 on digits are
+# brought below q first
+@pytest.mark.parametrize("digits", [16, 17])
+def test_hoisted_sum_of_many_digits(digits):
+    from gpu_util import dev, host, zeros
+    logN, C_a, level = 13, 32, digits
+    prm, orc, ctx, residues = _setup(logN, 54, level + 1, 1, level + 1)
+    block = prm.N // 2 // C_a
+    gs = [orc.galois_elt(block * i) for i in range(1, C_a)]
+    key = residues(prm.moduli, 2 * (level + 1), "top").reshape(level + 1, 2, -1, prm.N)
+    d_key = dev(key)
+    for g in gs:
+        ctx.he_evk_register(g, d_key)
+    ct, pt = residues(prm.q, 2, "uniform"), residues(prm.q, 1, "mixed")[0]
+    got, = ctx.he_conv2d(C_a, 1, block, 1, 1, level, [dev(pt)], dev(ct), [zeros(2, level, prm.N)], hoisted_ras=True)
+    x = orc.rescale(orc.ptct_mac(None, ct, pt, level, init=True), level)
+    assert (host(got) == orc.rotate_sum_deferred([x] * C_a, level - 1, [1] + gs, [None] + [key] * len(gs))).all()

@@ -1,5 +1,5 @@
-"""GPU parity where the lazy ranges are fullest: the largest primes below 2^54 (narrow in both directions), 2^55 (the last whose
-ModDown takes unreduced transforms), 2^57 (narrow forward, wide inverse) and 2^60 (wide), residues at their top or at zero.
+"""GPU parity where the lazy ranges are fullest: the largest primes below 2^54 (narrow forward, wide inverse), 2^55 (the last whose
+ModDown takes unreduced transforms), 2^57 (wide in both directions) and 2^60 (the widest class), residues at their top or at zero.
 Transforms, a key switch of every kind, rescale, and the sums of plaintext products that fill their split accumulators - against
 the oracle, bit for bit."""
 import numpy as np
@@ -71,7 +71,7 @@ def test_transforms_and_key_switches(logN, bits):
         assert (host(down) == orc.rescale(cts[0], level)).all(), fill
 
 
-# a launch takes 16 terms; 7 products fill a split sum, 8 and 9 terms are the limits of two kernels with two points per thread
+# a launch takes 16 terms; 8 products of 60 bits fill a split sum, 16 below 60 bits
 @pytest.mark.parametrize("n", [1, 6, 7, 8, 9, 10, 14, 15, 16, 17, 33])
 @pytest.mark.parametrize("logN,bits", [(8, 60), (9, 59), (13, 60)])
 def test_plaintext_sums(logN, bits, n):
