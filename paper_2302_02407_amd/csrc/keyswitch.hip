@@ -1188,7 +1188,8 @@ __device__ __forceinline__ void hoisted_sum_ip(const HoistIp& a, uint32_t r, uin
         return barrett128_lazy((u128)s.a0 + ((u128)s.a1 << H) + ((u128)s.a2 << (2 * H)), m.q, m.mu, m.bits);
     };
     // what the transforms behind it take: two-launch rings below 6q (q-limbs, epilogue of the forward rows) or 2q (special primes, inverse
-    // rows; sums that a launch continues), others canonical
+    // rows), others canonical.  A launch that continues q-limbs finds them below 6q after the first, below 12q with its own sum, and leaves
+    // them below 2q.
     auto settled = [&](u64 v) {
         if (init == 3 && r <= level) return v;
         v = reduce_lazy<7>(v, m.q, m.bits, m.rec);

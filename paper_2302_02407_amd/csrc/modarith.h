@@ -114,7 +114,7 @@ __device__ __forceinline__ u64 shoup_acc(u64 x, u64 y, u64 w, u64 w_sh, u64 q) {
 // ---- products by a factor known in advance, in nine instructions (narrow moduli of the two-launch transforms)
 // w*y = w*y0 + w'*y1 with y = y0 + 2^32 y1 and w' = 2^32 w mod q: the quotient of the sum then fits one word and takes two multiply-adds,
 // h = (a0*y0 + a1*y1) / 2^32, where the quotient of a 64-bit y is two words of three products.  (a0, a1) are the words of floor(w * 2^63 / q)
-// (h_tw_split): one bit less than Shoup's companion, so that the sum of the two products fits 64 bits for every y below 2^63, at
+// (h_companion): one bit less than Shoup's companion, so that the sum of the two products fits 64 bits for every y below 2^63, at
 // the price of a quotient that counts in units of 2q.  w' is 2^32 w - a0 * 2q, below 2q; a1 / 2^31 is then w' / q up to rounding.
 // Error of the quotient in units of q: below 2 for a0 (y0 / 2^31), 1 for a1 (y1 / 2^31), 2 for the division: results below 5q.
 
