@@ -31,7 +31,9 @@ struct MacMany {
 // two coefficients, 136 with the next output's asked for as well, 131 with one coefficient, 124..128 with both (5.7 TB/s; a large
 // copy reaches 6.7).  One kernel per number of ciphertexts: with a run-time number below a rounded-up one every load stood
 // behind a branch of its own and waited for the load before it (nine ciphertexts of 3 limbs, one output, N = 2^12: 7.1 us, now
-// 4.3).  ONE: only ciphertext c1_tap has a second component.  Operands and outputs have CL limbs per component: the level+1
+// 4.3).  From 11 ciphertexts on the registers leave three wavefronts; the sum and its rescale at level 11 of N = 2^16 still took
+// 62.3 us instead of 63.4 with 12 ciphertexts, 72.4 instead of 75.1 with 16 (rounded-up number, one coefficient, nothing asked for ahead;
+// nine: 53.3 and 57.8).  ONE: only ciphertext c1_tap has a second component.  Operands and outputs have CL limbs per component: the level+1
 // ciphertext primes, followed by the special primes when the operands are key-switch inner products still over the raised
 // basis.  grid: (N/256, CL).
 #define MAC_RUN 8                                        // products of residues of 60 bits that a split sum takes (below 60 bits: 16)

@@ -18,6 +18,11 @@ typedef unsigned __int128 u128;
 // Moduli whose points are never reduced inside the transforms of N = 2^13 and more (products: split_acc, modarith.h) on
 // the way: every product's operand has to stay below 2^63, and points reach 90q in 17 forward stages that start below 5q, 640q in
 // eight inverse ones (ntt_blocks.h).  Any other modulus is wide and takes conditional subtractions, more of them the widest ones.
+// 384 limbs, N = 2^16, primes just below each power or line (in brackets: with products of sixteen instructions, which take any operand
+// and had their lines at 2^57 and 2^54): forward 2^54 142 us (147), 2^56.4 144 (147), 2^57 152 (148), 2^59.3 152 (158), 2^60 159 (159); inverse
+// 2^53.6 144 (154), 2^54 150 (154), 2^59.3 151 (161), 2^60 157 (160).  The primes from 2^56.4 to 2^57 are the ones that lost, in one
+// direction.  With narrow forward up to 2^57.3, their rows brought below 13q first, they took 149, and every other class paid for the
+// branch in the row passes: one rotation at level 5 53.6 -> 55.2, a product 59.3 -> 61.1, rescale 26.7 -> 27.5.
 static inline bool narrow_fwd(u64 q) { return q <= (1ull << 63) / 96; }       // all of 56 bits, and up to 2^56.4
 static inline bool narrow_inv(u64 q) { return q <= (1ull << 63) / 640; }      // all of 53 bits, and up to 2^53.6
 static inline bool widest(u64 q) { return q > (1ull << 63) / 13; }            // above 2^59.29
