@@ -16,7 +16,7 @@
 // out so that a lane gets the 8 digit sums of one (point, target); they are put together and reduced below 2q in 16
 // vector instructions, where the vector-unit form of the same sum takes 68 (baseconv_kernel).
 //
-// What bounds it is vector issue: 4850 instructions per wavefront for 8 + 24 limbs (counters; 5969 with products of eleven and more
+// What bounds it is vector issue: 4828 instructions per wavefront for 8 + 24 limbs (counters; 5969 with products of eleven and more
 // instructions, sums put together in 22 and operands fetched one by one), 4 cycles each, fill 0.62 of the issue slots at 2.4 GHz
 // and 0.73 of those at the 2.05 GHz that the clock has under this load; 2.75 TB/s move and wavefronts wait 0.41 of their cycles.
 // Sets of sixteen, 24 limbs and eight special primes: 311 us a launch so, 261 to 267 now; with the tiles' accesses side by
