@@ -97,7 +97,7 @@ __device__ __forceinline__ void cc_source(u64* reg, const u64* src, const ColCon
     const const_u64 mp = (const_u64)(uintptr_t)(mc + mi);
     const u64 q = uni64(mp[0]);
     const u64 cs = sc.s[si], cs_sh = sc.s_sh[si], cw = sc.w[si], cw_sh = sc.w_sh[si];
-    int bound = W ? w_half(W) : 2;
+    int bound = w_start(W);
     f.put(reg, lane);
     wave_exchange();
     f.template first<U0>(w2, reg, t);
@@ -114,16 +114,16 @@ __device__ __forceinline__ void cc_source(u64* reg, const u64* src, const ColCon
 #pragma unroll
     for (int k = 0; k < 8; k++) {
         const u64 X = x[k], Y = x[k + 8];
-        x[k] = shoup_lazy4(X + Y, cs, cs_sh, q);
-        x[k + 8] = shoup_lazy4((X + q * (u64)bound) - Y, cw, cw_sh, q);        // any value below 2^64
+        x[k] = inv_scaled<W>(X + Y, cs, cs_sh, q);
+        x[k + 8] = inv_scaled<W>(W == W_NEAR ? X - Y : (X + q * (u64)bound) - Y, cw, cw_sh, q);
     }
     // each byte less 128, as the signed operand of the matrix instruction
 #pragma unroll
-    for (int k = 0; k < 16; k++) reg[cc_word(k, lane)] = csub_min(csub_min(x[k], 2 * q), q) ^ 0x8080808080808080ull;
+    for (int k = 0; k < 16; k++) reg[cc_word(k, lane)] = inv_canonical<W>(x[k], q) ^ 0x8080808080808080ull;
     (void)LT;
 }
 
-// Forward column stages of one target limb from its LDS region (below 2q) to memory.
+// Forward column stages of one target limb from its LDS region (below 2q, or centred) to memory.
 // `before`: what goes ahead of the stores, for which later loads wait.
 template <int LC, int W, class Before>
 __device__ __forceinline__ void cc_target(u64* reg, u64* dst, uint32_t mi, const ulonglong2 (&w1)[15], uint32_t lane, uint32_t c0, const ModConst* mc, const ulonglong2* ftw,
@@ -195,7 +195,7 @@ __device__ __forceinline__ void c4_source(u64* reg, const u64* src, const ScaleL
     for (int k = 0; k < 4; k++) x[k] = src[G::at(c4_point(G::NB - 1, t, k), c0)];
     c4_factors<LC>(w, itw + ((size_t)mi << (LC + 8)), t);
     const u64 q = uni64(mc[mi].q), cs = sc.s[si], cs_sh = sc.s_sh[si];
-    int bound = W ? w_half(W) : 2;                     // narrow rows arrive below 2q: 2, 10, 40, 160, at the end 640
+    int bound = w_start(W);                            // narrow rows arrive below 2q: 2, 10, 40, 160, at the end 640
 #pragma unroll
     for (int i = G::NB - 1; i >= 0; i--) {
         if (i + 1 < G::NB) {
@@ -208,7 +208,7 @@ __device__ __forceinline__ void c4_source(u64* reg, const u64* src, const ScaleL
         else inv_block2_r<W>(x, w[i], q, bound);
 #pragma unroll
         for (int k = 0; k < 4; k++)
-            reg[c4_word(c4_point(i, t, k))] = i ? x[k] : csub_min(shoup_lazy(x[k], cs, cs_sh, q), q) ^ 0x8080808080808080ull;
+            reg[c4_word(c4_point(i, t, k))] = i ? x[k] : csub_min(W == W_NEAR ? near_acc<true>(q, x[k], make_ulonglong2(cs, cs_sh), NearQ(q)) : shoup_lazy(x[k], cs, cs_sh, q), q) ^ 0x8080808080808080ull;
     }
 }
 template <int LC, int W, class Before>
@@ -237,8 +237,11 @@ __device__ __forceinline__ void c4_target(u64* reg, u64* dst, uint32_t mi, const
 
 // f(std::integral_constant<int, W>, mi) for the class W of modulus mi, whose copies' loads are kept apart (see ntt2p.hip)
 template <class F>
-__device__ __forceinline__ void cc_class(u64 wide, u64 widest, uint32_t mi, F&& f) {
-    if (!(wide >> mi & 1u)) {
+__device__ __forceinline__ void cc_class(u64 near, u64 wide, u64 widest, uint32_t mi, F&& f) {
+    if (near >> mi & 1u) {
+        asm("; near" : "+s"(mi));
+        f(std::integral_constant<int, W_NEAR>(), mi);
+    } else if (!(wide >> mi & 1u)) {
         asm("; narrow" : "+s"(mi));
         f(std::integral_constant<int, 0>(), mi);
     } else if (!(widest >> mi & 1u)) {
@@ -304,7 +307,7 @@ __global__ __launch_bounds__(CC_THREADS, 4) void col_conv_kernel(ColConv cc, Sca
     if (w < st.ns) {
         const u64* src = st.src + (size_t)rep * cc.src_stride + ((size_t)w << (LC + 8));
         const uint32_t mi = st.mod0 + w;
-        cc_class(cc.wide_inv, cc.widest, mi, [&](auto W, uint32_t m) {
+        cc_class(cc.near_inv, cc.wide_inv, cc.widest, mi, [&](auto W, uint32_t m) {
             if constexpr (PTS == 4) c4_source<LC, W>(reg, src, sc, m, st.sc0 + w, lane, c0, mc, itw);
             else cc_source<LC, W>(reg, src, cc, sc, m, st.sc0 + w, lane, c0, mc, itw);
         });
@@ -339,6 +342,7 @@ __global__ __launch_bounds__(CC_THREADS, 4) void col_conv_kernel(ColConv cc, Sca
             const v4i* A = reinterpret_cast<const v4i*>(ops[4 * s + (p16 >> 2)].dig + (p16 & 3) * 64 + g * 16);
             const v4i* K = reinterpret_cast<const v4i*>(ops[4 * s + g].bias);
             const v4i a0 = A[0], a1 = A[16], k0 = K[0], k1 = K[1], mk = K[2];      // digits 0..3, digits 4..7 (256 bytes on); -q, rec, bits
+            const uint32_t centre = (uint32_t)K[3].x;
             const uint32_t n0 = (uint32_t)mk.x, n1 = (uint32_t)mk.y, rec = (uint32_t)mk.z, bits = (uint32_t)mk.w;
             // quotient of a value below 2^(bits+14) from its 32 bits above bit 32 + sh (sh at most 10)
             const uint32_t sh = bits > 50 ? bits - 50 : 0, e = bits - 33 - sh, up = 16 - sh;
@@ -350,7 +354,7 @@ __global__ __launch_bounds__(CC_THREADS, 4) void col_conv_kernel(ColConv cc, Sca
                 // p01 and p23 are positive (conv_operand), the upper two of either sign; the value is lo + 2^32 * (p45 + 2^16 p67)
                 const int p01 = d0.x + (d0.y << 8), p23 = d0.z + (d0.w << 8), p45 = d1.x + (d1.y << 8), p67 = d1.z + (d1.w << 8);
                 const u64 lo = mad_wide((uint32_t)p23, 65536u, (uint32_t)p01);
-                const int top = p45 + (int)(uint32_t)(lo >> 32);
+                const int top = (int)add3((uint32_t)p45, (uint32_t)(lo >> 32), centre);
                 const uint32_t qh = __umulhi(((uint32_t)p67 << up) + (uint32_t)(top >> sh), rec) >> e;
                 const u64 v = (u64)qh * n0 + lo;
                 const uint32_t vh = add3((uint32_t)(v >> 32), ((uint32_t)p67 << 16) + (uint32_t)p45, qh * n1);
@@ -370,7 +374,7 @@ __global__ __launch_bounds__(CC_THREADS, 4) void col_conv_kernel(ColConv cc, Sca
         ln = lane_again();
         if (have) {
             u64* dst = st.dst + (size_t)rep * cc.dst_stride + ((size_t)li << (LC + 8));
-            cc_class(cc.wide_fwd, cc.widest, mi, [&](auto W, uint32_t m) {
+            cc_class(cc.near_fwd, cc.wide_fwd, cc.widest, mi, [&](auto W, uint32_t m) {
                 if constexpr (PTS == 4) c4_target<LC, W>(reg, dst, m, w4, ln, c0, mc, before);
                 else cc_target<LC, W>(reg, dst, m, w1, ln, c0, mc, ftw, before);
             });

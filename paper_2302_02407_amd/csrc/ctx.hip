@@ -42,6 +42,27 @@ u64 h_shoup(u64 w, u64 m) { return (u64)(((u128)w << 64) / m); }
 // transforms, Shoup's floor(w * 2^64 / m) in smaller ones.
 u64 h_companion(uint32_t logN, u64 w, u64 m) { return logN > 12 ? h_shoup(w, m) >> 1 : h_shoup(w, m); }
 
+// A residue's balanced words (near_acc, modarith.h): the residue in (-m/2, m/2), its low word taken as a signed number
+static u64 h_balanced(u64 r, u64 m) {
+    const int64_t a = r > m / 2 ? (int64_t)r - (int64_t)m : (int64_t)r;
+    const int32_t lo = (int32_t)(uint32_t)a;
+    return ((u64)(uint32_t)((a - lo) >> 32) << 32) | (uint32_t)lo;
+}
+// y * w mod m for many y: Shoup's product, no division
+struct HMul {
+    u64 w, w_sh, m;
+    HMul(u64 w_, u64 m_) : w(w_), w_sh(h_shoup(w_, m_)), m(m_) {}
+    u64 operator()(u64 y) const {
+        const u64 r = w * y - (u64)(((u128)w_sh * y) >> 64) * m;
+        return r >= m ? r - m : r;
+    }
+};
+// A factor w and its companion as the products of moduli near a multiple of 2^32 take them: the words of 2^32 w and 2^64 w; by32: by 2^32
+static ulonglong2 h_near_factor(u64 w, const HMul& by32) {
+    const u64 a = by32(w);
+    return make_ulonglong2(h_balanced(a, by32.m), h_balanced(by32(a), by32.m));
+}
+
 static bool h_is_prime(u64 n) {
     if (n < 2) return false;
     static const u64 bases[] = {2, 3, 5, 7, 11, 13, 17, 19, 23, 29, 31, 37};
@@ -78,10 +99,18 @@ uint32_t h_galois_of_step(const he_ctx* ctx, int32_t step) {
 
 void scale_entry(const he_ctx* c, ScaleList& sc, uint32_t i, uint32_t mi, u64 s) {
     const u64 m = c->mod[mi];
+    const u64 w = h_mulmod(s, c->itw1[mi], m);
+    if (two_pass(c) && near_inv(m)) {
+        const HMul by32((1ull << 32) % m, m);
+        const ulonglong2 fs = h_near_factor(s, by32), fw = h_near_factor(w, by32);
+        sc.s[i] = fs.x; sc.s_sh[i] = fs.y;
+        sc.w[i] = fw.x; sc.w_sh[i] = fw.y;
+        return;
+    }
     sc.s[i] = s;
     sc.s_sh[i] = h_shoup(s, m);
-    sc.w[i] = h_mulmod(s, c->itw1[mi], m);
-    sc.w_sh[i] = h_shoup(sc.w[i], m);
+    sc.w[i] = w;
+    sc.w_sh[i] = h_shoup(w, m);
 }
 
 int32_t he_ensure_ws(he_ctx* ctx, size_t bytes) {
@@ -174,14 +203,16 @@ int32_t he_ctx_create(he_ctx** out, uint32_t logN, const uint64_t* h_q, uint32_t
         c->psi[i] = psi;
         u64 ipsi = h_invmod(psi, m);
         u64 pw = 1, ipw = 1;
+        const HMul by_psi(psi, m), by_ipsi(ipsi, m), by32((1ull << 32) % m, m);
+        const bool nf = logN > 12 && near_fwd(m, logN), ni = logN > 12 && near_inv(m);
         ulonglong2* t = &tw[(size_t)i * N];
         ulonglong2* it = &itw[(size_t)i * N];
         for (uint32_t e = 0; e < N; e++) {                      // psi^e stored at bitrev(e)
             const uint32_t pos = tw_pos(bitrev(e, logN), logN);
-            t[pos] = make_ulonglong2(pw, h_companion(logN, pw, m));
-            it[pos] = make_ulonglong2(ipw, h_companion(logN, ipw, m));
-            pw = h_mulmod(pw, psi, m);
-            ipw = h_mulmod(ipw, ipsi, m);
+            t[pos] = nf ? h_near_factor(pw, by32) : make_ulonglong2(pw, h_companion(logN, pw, m));
+            it[pos] = ni ? h_near_factor(ipw, by32) : make_ulonglong2(ipw, h_companion(logN, ipw, m));
+            pw = by_psi(pw);
+            ipw = by_ipsi(ipw);
         }
         ModConst& mc = c->h_mc[i];
         mc.q = m; mc.q2 = 2 * m;
@@ -192,6 +223,9 @@ int32_t he_ctx_create(he_ctx** out, uint32_t logN, const uint64_t* h_q, uint32_t
         c->itw1[i] = h_powmod(ipsi, N / 2, m);
         mc.ninv_w = h_mulmod(mc.ninv, c->itw1[i], m);
         mc.ninv_w_sh = h_shoup(mc.ninv_w, m);
+        const ulonglong2 ns = h_near_factor(mc.ninv, by32), nw = h_near_factor(mc.ninv_w, by32);
+        mc.near_s = ns.x; mc.near_s_sh = ns.y;
+        mc.near_w = nw.x; mc.near_w_sh = nw.y;
         mc.one_sh = h_shoup(1, m);
         mc.rec = (uint32_t)(((u128)1 << (mc.bits + 31)) / m);
         mc.qinv = 1.0 / (double)m;

@@ -26,6 +26,18 @@ typedef unsigned __int128 u128;
 static inline bool narrow_fwd(u64 q) { return q <= (1ull << 63) / 96; }       // all of 56 bits, and up to 2^56.4
 static inline bool narrow_inv(u64 q) { return q <= (1ull << 63) / 640; }      // all of 53 bits, and up to 2^53.6
 static inline bool widest(u64 q) { return q > (1ull << 63) / 13; }            // above 2^59.29
+// Moduli whose low word is near 0 as a signed number, as it is of primes near a power of two.  The products of near_acc (modarith.h) ask for
+// |operand| / 2 + 2^62 + |low word| 2^31 below 2^63 and are below (3/4 + |operand| / 2^65) q.  Points are not reduced on the way:
+//   forward, up to 2^58: 5q at the start, less than q more with every stage, 17 stages: below 22q;
+//   forward, up to 2^59.003 with at most 16 stages, the special primes that are taken above 2^59: 1.5q at the start (whoever writes points for
+//   the first pass centres them, near_top), operands below 14.6q < 2^63 - 2^60, results below 15.6q;
+//   inverse: doubled by each of eight stages from 2q, below 512q.
+static inline bool near_word(u64 q, int64_t most) { return (int32_t)(uint32_t)q < most && (int32_t)(uint32_t)q > -most; }
+static inline bool near_top(u64 q) { return q > 1ull << 58; }
+static inline bool near_fwd(u64 q, uint32_t logN) {
+    return near_top(q) ? logN <= 16 && q <= (1ull << 59) + (1ull << 50) && near_word(q, 1ll << 26) : near_word(q, 1ll << 27);
+}
+static inline bool near_inv(u64 q) { return near_word(q, 1ll << 27) && q <= (1ull << 63) / 550; }      // up to 2^53.896
 
 // Per-modulus constants, resident on the device (array indexed by modulus index).
 struct ModConst {
@@ -36,6 +48,7 @@ struct ModConst {
     u64 ninv_sh;    // Shoup companion floor(ninv * 2^64 / q)
     u64 ninv_w;     // N^-1 * psi^-(N/2): scaling folded into the twiddle of the last inverse stage
     u64 ninv_w_sh;
+    u64 near_s, near_s_sh, near_w, near_w_sh;    // ninv and ninv_w as factors of near_acc (two-launch transforms)
     u64 one_sh;     // floor(2^64 / q): Shoup companion of the constant 1 (a quotient step for any 64-bit value)
     uint32_t bits;  // bit length of q
     uint32_t rec;   // floor(2^(bits+31) / q): 32-bit reciprocal for small quotients
@@ -64,7 +77,8 @@ struct alignas(16) ConvOperand {
     int32_t bias[8];
     u64 nq;            // -q modulo 2^64
     uint32_t rec, bits;
-    uint32_t unused[4];
+    uint32_t centre;   // added to a value's upper word for its quotient: results in [0, 2q), or in [-q, q + 2^32)
+    uint32_t unused[3];
 };
 
 struct ProfSpan {
@@ -203,7 +217,7 @@ struct KsRows {
     uint32_t count_up, count_down;      // whether the digits' / the ModDown's transforms are counted with these rows
     // set by the launch
     uint32_t logN;
-    u64 wide_fwd, wide_inv, widest;     // bit per modulus (narrow_fwd, narrow_inv, widest)
+    u64 wide_fwd, wide_inv, widest, near_fwd, near_inv;     // as in ColConv
     const ModConst* mc;
     const ulonglong2 *tw, *itw;
 };
@@ -249,7 +263,7 @@ struct ColConvSet {
 struct ColConv {
     ColConvSet set[CC_MAX_SETS];
     size_t src_stride, dst_stride;
-    u64 wide_fwd, wide_inv, widest;    // bit per modulus (narrow_fwd, narrow_inv, widest)
+    u64 wide_fwd, wide_inv, widest, near_fwd, near_inv;    // bit per modulus (narrow_fwd, narrow_inv, widest, near_fwd, near_inv)
     uint32_t n_sets;
     uint32_t share;            // targets of a work group of those that share a tile (set by the launch)
 };
@@ -260,7 +274,7 @@ struct RescaleCols {
     const u64* src;
     u64* dst;
     uint32_t level, parts, share;      // work groups that share a tile's moduli, `share` each (set by the launch)
-    u64 wide_fwd, wide_inv, widest;    // bit per modulus (narrow_fwd, narrow_inv, widest)
+    u64 wide_fwd, wide_inv, widest, near_fwd, near_inv;    // as in ColConv
 };
 bool rescale_cols_pays(const he_ctx* ctx, uint32_t n, uint32_t level);
 int32_t launch_rescale_cols(he_ctx* ctx, const u64* src, u64* dst, uint32_t n, uint32_t level);

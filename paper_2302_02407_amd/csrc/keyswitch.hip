@@ -249,7 +249,7 @@ static uint32_t pad8(uint32_t x) { return (x + 7u) & ~7u; }
 // (i < ns <= 8).  V_(i,a) = hat_i * 2^(8a) mod m, centred, in 8 signed base-256 digits; dig: [digit / 4][digit % 4][byte
 // group of 2 sources][16], bias: base-256 digits of 128 * sum V + 4096 m, which returns the 128 taken from every source
 // byte and keeps the sum from becoming negative (64 products of at most 128 and m/2).
-static void conv_operand(const u64* hat, uint32_t ns, const ModConst& mc, ConvOperand& op) {
+static void conv_operand(const u64* hat, uint32_t ns, const ModConst& mc, uint32_t logN, ConvOperand& op) {
     const u64 m = mc.q;
     uint8_t* dig = op.dig;
     u64 total = 0;
@@ -275,6 +275,7 @@ static void conv_operand(const u64* hat, uint32_t ns, const ModConst& mc, ConvOp
     op.nq = 0 - m;
     op.rec = mc.rec;
     op.bits = mc.bits;
+    op.centre = near_top(m) && near_fwd(m, logN) ? (uint32_t)(m >> 32) : 0;
 }
 
 int32_t ks_init_tables(he_ctx* c) {
@@ -342,13 +343,13 @@ int32_t ks_init_tables(he_ctx* c) {
         std::vector<ConvOperand> op((size_t)dn * al * M, ConvOperand{});
         for (uint32_t sl = 0; sl < dn * al; sl++)
             for (uint32_t m = 0; m < M; m++)
-                conv_operand(&hat[((size_t)sl * M + m) * aw], sl % al + 1, c->h_mc[m], op[(size_t)sl * M + m]);
+                conv_operand(&hat[((size_t)sl * M + m) * aw], sl % al + 1, c->h_mc[m], c->logN, op[(size_t)sl * M + m]);
         HE_HIP(c, hipMalloc(&c->d_up_op, op.size() * sizeof(ConvOperand)));
         HE_HIP(c, hipMemcpy(c->d_up_op, op.data(), op.size() * sizeof(ConvOperand), hipMemcpyHostToDevice));
     }
     if (operands && np <= 8) {
         std::vector<ConvOperand> op(M, ConvOperand{});
-        for (uint32_t m = 0; m < M; m++) conv_operand(&dhat[(size_t)m * pw], np, c->h_mc[m], op[m]);
+        for (uint32_t m = 0; m < M; m++) conv_operand(&dhat[(size_t)m * pw], np, c->h_mc[m], c->logN, op[m]);
         HE_HIP(c, hipMalloc(&c->d_dn_op, op.size() * sizeof(ConvOperand)));
         HE_HIP(c, hipMemcpy(c->d_dn_op, op.data(), op.size() * sizeof(ConvOperand), hipMemcpyHostToDevice));
     }
@@ -456,6 +457,8 @@ static void col_conv_widths(const he_ctx* c, ColConv& cc) {
         cc.wide_fwd |= (u64)!narrow_fwd(c->mod[m]) << m;
         cc.wide_inv |= (u64)!narrow_inv(c->mod[m]) << m;
         cc.widest |= (u64)widest(c->mod[m]) << m;
+        cc.near_fwd |= (u64)near_fwd(c->mod[m], c->logN) << m;
+        cc.near_inv |= (u64)near_inv(c->mod[m]) << m;
     }
 }
 

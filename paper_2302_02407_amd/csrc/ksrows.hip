@@ -98,15 +98,16 @@ __device__ __forceinline__ uint32_t kr_row_from(uint32_t bs, uint32_t g, uint32_
     return __brev((inv * (2 * (__brev(bs) >> (32 - rows)) + 1)) >> 1) >> (32 - rows);
 }
 
-// W: 0 = narrow in both directions (ntt_blocks.h), 1 = only forward, 2 = in neither, 3 = the widest.
-__device__ constexpr int kr_fwd(int W) { return W < 2 ? 0 : W - 1; }      // classes of the transforms
-__device__ constexpr int kr_inv(int W) { return W == 0 ? 0 : W == 3 ? 2 : 1; }
+// W: 0 = narrow in both directions (ntt_blocks.h), 1 = only forward, 2 = in neither, 3 = the widest, 4 = near a multiple of 2^32 in both
+// directions, 5 = only forward.
+__device__ constexpr int kr_fwd(int W) { return W >= 4 ? W_NEAR : W < 2 ? 0 : W - 1; }      // classes of the transforms
+__device__ constexpr int kr_inv(int W) { return W == 4 ? W_NEAR : W == 0 ? 0 : W == 3 ? 2 : 1; }
 
 //
 // Both components of the inner products of row b of limb r for one (source, key) term, added to the sums s; `spill`
-// empties them when they hold KS_ROW_PRODUCTS products.  Digits enter as the row transform leaves them where W = 0 (below 90q <
-// 2^60.2: 31-bit high halves; seven products with key values below q, together below 2^117, fit the sums and split_reduce), else below
-// 2q (1) or canonical (2, 3).  buf: a row for each digit, of which
+// empties them when they hold KS_ROW_PRODUCTS products.  Digits enter as the row transform leaves them where W = 0 or 4 (below 90q <
+// 2^60.2, 4: 46q: 31-bit high halves; seven products with key values below q, together below 2^117, fit the sums and split_reduce), else below
+// 2q (1, 5) or canonical (2, 3).  buf: a row for each digit, of which
 // digits j0, j0 + step .. are worked on (j0 < beta).  AHEAD: the next digit's row and the own one are asked for ahead of their turn.
 template <int W, bool SP, bool AHEAD, class Spill>
 __device__ __forceinline__ void ks_row_products(const KsRows& a, uint32_t id, uint32_t r, uint32_t b, uint32_t t, u64* buf, const ModConst& m, const Row4& at,
@@ -142,8 +143,9 @@ __device__ __forceinline__ void ks_row_products(const KsRows& a, uint32_t id, ui
             row4_fwd<kr_fwd(W), 1>(x, w, buf + 256 * j, 256, at, m.q);
 #pragma unroll
             for (int k = 0; k < 4; k++) {
-                if (W == 1) x[0][k] = reduce_lazy<7>(x[0][k], m.q, m.bits, m.rec);
-                if (W >= 2) x[0][k] = reduce_min<7>(x[0][k], m.q, m.bits, m.rec);
+                x[0][k] = fwd_positive<kr_fwd(W)>(x[0][k], m.q);
+                if (W == 1 || W == 5) x[0][k] = reduce_lazy<7>(x[0][k], m.q, m.bits, m.rec);
+                if (W == 2 || W == 3) x[0][k] = reduce_min<7>(x[0][k], m.q, m.bits, m.rec);
             }
             wave_exchange();
             at.store(3, x[0], buf + 256 * j);
@@ -273,21 +275,18 @@ struct KrAdd {
         }
     }
 };
-// bit 55 and less: the transform's values go into the difference as they are
-template <int W>
-__device__ __forceinline__ bool kr_raw(const ModConst& m) { return W < 2 && m.bits <= 55; }
 // rows of the converted components, in the order of the sums
 template <int W, int NX>
 __device__ __forceinline__ void ks_row_transformed(u64 (&cv)[NX][4], u64* buf, const ModConst& m, const Row4& at, const KrRow& kr, const u64 (&w)[4][6]) {
     SCHED_FENCE();
     row4_fwd<kr_fwd(W), NX>(cv, w, buf, 256, at, m.q);
-    const bool raw = kr_raw<W>(m);
+    const bool raw = fwd_raw<kr_fwd(W)>(m);
     wave_exchange();
 #pragma unroll
     for (int c = 0; c < NX; c++) {
         if (!raw) {
 #pragma unroll
-            for (int k = 0; k < 4; k++) cv[c][k] = reduce_lazy<7>(cv[c][k], m.q, m.bits, m.rec);
+            for (int k = 0; k < 4; k++) cv[c][k] = reduce_lazy<7>(fwd_positive<kr_fwd(W)>(cv[c][k], m.q), m.q, m.bits, m.rec);
         }
         at.store(3, cv[c], buf + 256 * c);
     }
@@ -302,9 +301,9 @@ __device__ __forceinline__ void ks_row_down(const KsRows& a, uint32_t job, uint3
     const uint32_t row0 = b * 256;
     const size_t qo = (size_t)r << a.logN;
     // out = (acc - conv) * P^-1 + addends: the product is below 5q whatever its factor, so the transform value may stay as it is
-    // where 128q plus the accumulator (below 6q) fits 63 bits, else below 2q; the sum is below 7q
-    const bool raw = kr_raw<W>(m);
-    const u64 bias = raw ? (m.q << 7) : 2 * m.q, pinv = ((const_u64)(uintptr_t)a.pinv)[r], pinv_sh = ((const_u64)(uintptr_t)a.pinv_sh)[r];
+    // where what it can be plus the accumulator (below 6q) fits 63 bits, else below 2q; the sum is below 7q
+    const bool raw = fwd_raw<kr_fwd(W)>(m);
+    const u64 bias = raw ? fwd_raw_bias<kr_fwd(W)>(m.q) : 2 * m.q, pinv = ((const_u64)(uintptr_t)a.pinv)[r], pinv_sh = ((const_u64)(uintptr_t)a.pinv_sh)[r];
     const u64 n2q = opaque_s(0 - 2 * m.q), pinv_h = split_factor<true>(pinv, pinv_sh, n2q);
     if (ad.rotated) {
         kr.put(buf, ad.rot);
@@ -462,12 +461,17 @@ __device__ __forceinline__ void ks_row_group(const KsRows& a, uint32_t job, uint
 }
 
 // W of a modulus, from the argument list: the branch waits for no load of its constants
-__device__ __forceinline__ uint32_t kr_width(const KsRows& a, uint32_t mi) { return (uint32_t)(a.wide_inv >> mi & 1u) + (uint32_t)(a.wide_fwd >> mi & 1u) + (uint32_t)(a.widest >> mi & 1u); }
+__device__ __forceinline__ uint32_t kr_width(const KsRows& a, uint32_t mi) {
+    if (a.near_fwd >> mi & 1u) return a.near_inv >> mi & 1u ? 4 : 5;
+    return (uint32_t)(a.wide_inv >> mi & 1u) + (uint32_t)(a.wide_fwd >> mi & 1u) + (uint32_t)(a.widest >> mi & 1u);
+}
 template <int W>
 __device__ __forceinline__ uint32_t kr_pin(uint32_t v) {     // keeps the widths' loads apart (see ntt2p.hip)
     if (W == 0) asm("; narrow" : "+s"(v));
     else if (W == 1) asm("; narrow forward" : "+s"(v));
     else if (W == 2) asm("; wide" : "+s"(v));
+    else if (W == 4) asm("; near" : "+s"(v));
+    else if (W == 5) asm("; near forward" : "+s"(v));
     else asm("; widest" : "+s"(v));
     return v;
 }
@@ -484,7 +488,9 @@ __global__ __launch_bounds__(KR_THREADS, MANY ? 3 : 4) void ks_rows_kernel(KsRow
     const uint32_t b = kr_row_from(u & ((1u << rows) - 1u), a.g[job], rows);
     u64* buf = sm + wave * (256 * (DONE ? 2u : max(a.beta, 2u)));
     const uint32_t width = kr_width(a, SP ? a.nq + r : r), t = threadIdx.x & 63u;
-    if (width == 0) ks_row<0, SP, MANY, DONE>(a, job, kr_pin<0>(r), b, t, buf);
+    if (width == 4) ks_row<4, SP, MANY, DONE>(a, job, kr_pin<4>(r), b, t, buf);
+    else if (width == 5) ks_row<5, SP, MANY, DONE>(a, job, kr_pin<5>(r), b, t, buf);
+    else if (width == 0) ks_row<0, SP, MANY, DONE>(a, job, kr_pin<0>(r), b, t, buf);
     else if (width == 1) ks_row<1, SP, MANY, DONE>(a, job, kr_pin<1>(r), b, t, buf);
     else if (width == 2) ks_row<2, SP, MANY, DONE>(a, job, kr_pin<2>(r), b, t, buf);
     else ks_row<3, SP, MANY, DONE>(a, job, kr_pin<3>(r), b, t, buf);
@@ -501,7 +507,9 @@ __global__ __launch_bounds__(KR_THREADS, 4) void ks_rows_half_kernel(KsRows a) {
     const uint32_t b = kr_row_from(u & ((1u << rows) - 1u), a.g[job], rows);
     u64* buf = sm + 512 * wave;
     const uint32_t width = kr_width(a, SP ? a.nq + r : r);
-    if (width == 0) ks_row_half<0, SP>(a, job, at & 1u, kr_pin<0>(r), b, t, buf);
+    if (width == 4) ks_row_half<4, SP>(a, job, at & 1u, kr_pin<4>(r), b, t, buf);
+    else if (width == 5) ks_row_half<5, SP>(a, job, at & 1u, kr_pin<5>(r), b, t, buf);
+    else if (width == 0) ks_row_half<0, SP>(a, job, at & 1u, kr_pin<0>(r), b, t, buf);
     else if (width == 1) ks_row_half<1, SP>(a, job, at & 1u, kr_pin<1>(r), b, t, buf);
     else if (width == 2) ks_row_half<2, SP>(a, job, at & 1u, kr_pin<2>(r), b, t, buf);
     else ks_row_half<3, SP>(a, job, at & 1u, kr_pin<3>(r), b, t, buf);
@@ -515,7 +523,9 @@ __global__ __launch_bounds__(KR_THREADS, SUM && DONE ? 2 : 3) void ks_rows_group
     const uint32_t item = blockIdx.x >> 3, un = item / a.J, job = item - un * a.J;
     const uint32_t u = un * 8 + (blockIdx.x & 7u), r = u >> rows, b = u & ((1u << rows) - 1u);
     const uint32_t width = kr_width(a, SP ? a.nq + r : r);
-    if (width == 0) ks_row_group<0, SP, SUM, DONE>(a, job, kr_pin<0>(r), b, wave, nw, t, sm);
+    if (width == 4) ks_row_group<4, SP, SUM, DONE>(a, job, kr_pin<4>(r), b, wave, nw, t, sm);
+    else if (width == 5) ks_row_group<5, SP, SUM, DONE>(a, job, kr_pin<5>(r), b, wave, nw, t, sm);
+    else if (width == 0) ks_row_group<0, SP, SUM, DONE>(a, job, kr_pin<0>(r), b, wave, nw, t, sm);
     else if (width == 1) ks_row_group<1, SP, SUM, DONE>(a, job, kr_pin<1>(r), b, wave, nw, t, sm);
     else if (width == 2) ks_row_group<2, SP, SUM, DONE>(a, job, kr_pin<2>(r), b, wave, nw, t, sm);
     else ks_row_group<3, SP, SUM, DONE>(a, job, kr_pin<3>(r), b, wave, nw, t, sm);
@@ -527,11 +537,13 @@ int32_t launch_ks_rows(he_ctx* ctx, KsRows& a, bool special) {
         a.beta == 0 || a.beta > 8 || ctx->logN < 13 || ctx->logN > 17 || limbs == 0 || limbs > HE_MAX_MODULI)
         return he_fail(ctx, HE_ERR_BADARG, "key-switch rows: bad shape");
     a.mc = ctx->d_mc; a.tw = ctx->d_tw; a.itw = ctx->d_itw; a.logN = ctx->logN;
-    a.wide_fwd = a.wide_inv = a.widest = 0;
+    a.wide_fwd = a.wide_inv = a.widest = a.near_fwd = a.near_inv = 0;
     for (uint32_t i = 0; i < ctx->M; i++) {
         a.wide_fwd |= (u64)!narrow_fwd(ctx->mod[i]) << i;
         a.wide_inv |= (u64)!narrow_inv(ctx->mod[i]) << i;
         a.widest |= (u64)widest(ctx->mod[i]) << i;
+        a.near_fwd |= (u64)near_fwd(ctx->mod[i], ctx->logN) << i;
+        a.near_inv |= (u64)near_inv(ctx->mod[i]) << i;
     }
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (ctx->prof_on) {

@@ -142,6 +142,93 @@ __device__ __forceinline__ u64 split_acc(u64 x, u64 y, u64 w, u64 a, u64 wh, u64
     return add_upper(s, u);
 }
 
+// ---- products by a factor known in advance, in nine instructions and nothing to prepare (moduli near a multiple of 2^32)
+// Values are signed here.  With y = y0 + 2^32 y1, A = 2^32 w and B = 2^64 w mod q the sum A y0 + B y1 is 2^32 w y mod q, and one step of
+// Montgomery's reduction (Math. Comp. 44, 1985) divides it by 2^32: m = -sum/q mod 2^32, (sum + m q) / 2^32.  All words are balanced: the low word
+// of y, of a factor and of q is a signed number, the upper one rounded to match (y1 is the upper word of y + 2^31).  So the low words' sum A0 y0 +
+// B0 y1 + m q0 stays in 63 bits where q0 is small (near_fwd, near_inv: he_internal.h), and the result is below q/4 + q |y| / 2^65 + q/2 in
+// magnitude.  A factor's table entry is (A, B), so none of its words has to be worked out (split_factor: three instructions), bounds grow by less than
+// q a stage instead of 5q, and 60-bit special primes need no conditional subtractions.  Butterflies of four stages on 16 points, instructions and
+// rate (10^12/s): forward 13.4 -> 12, 2.52 -> 2.69, inverse 14.4 -> 12, 2.36 -> 2.73; at 60 bits forward 15.4 -> 12, 2.22 -> 2.81.
+struct NearQ {
+    int32_t q0, q1, qi;              // balanced words of q, -1/q mod 2^32
+    u64 half;                        // 2^31
+    __device__ __forceinline__ explicit NearQ(u64 q) : q0((int32_t)(uint32_t)q), q1((int32_t)(uint32_t)((q + 0x80000000ull) >> 32)), half(opaque_s(0x80000000ull)) {
+        uint32_t v = 3u * (uint32_t)q ^ 2u;              // 1/q to 5 bits, then 10, 20, 40
+#pragma unroll
+        for (int i = 0; i < 3; i++) v *= 2u - (uint32_t)q * v;
+        qi = (int32_t)(0u - v);
+    }
+};
+// r = x + (w*y mod q); ZERO: without x.  UNI: the factor is the same for the whole wavefront.  One block of instructions (near_acc2: two products): the
+// compiler would take the factors' words as 64-bit numbers, keep their signs in registers of their own and multiply the long way (1.6 instead of
+// 2.7 * 10^12 butterflies/s), and it puts wait states between blocks that follow each other.  What words have to be named of lies in v[2:3].
+#define NEAR_WORDS(F, f) F((uint32_t)f.x), F((uint32_t)(f.x >> 32)), F((uint32_t)f.y), F((uint32_t)(f.y >> 32))
+#define NEAR_PRODUCT(R, A0, A1, B0, B1, YL, Y, START)          \
+    "v_lshl_add_u64 v[2:3], " Y ", 0, %[half]\n\t"             \
+    "v_mad_i64_i32 " R ", %[c], " B1 ", v3, " START "\n\t"     \
+    "v_mad_i64_i32 v[2:3], %[c], " B0 ", v3, 0\n\t"            \
+    "v_mad_i64_i32 " R ", %[c], " A1 ", " YL ", " R "\n\t"     \
+    "v_mad_i64_i32 v[2:3], %[c], " A0 ", " YL ", v[2:3]\n\t"   \
+    "v_mul_lo_u32 %[m], v2, %[qi]\n\t"                         \
+    "v_mad_i64_i32 v[2:3], %[c], %[m], %[q0], v[2:3]\n\t"      \
+    "v_mad_i64_i32 " R ", %[c], %[m], %[q1], " R "\n\t"        \
+    "v_mad_i64_i32 " R ", %[c], v3, 1, " R "\n\t"
+template <bool UNI, bool ZERO = false>
+__device__ __forceinline__ u64 near_acc(u64 x, u64 y, ulonglong2 f, const NearQ& n) {
+    u64 r, carry;
+    uint32_t m;
+#define NEAR_ASM(START, F)                                                                                                           \
+    asm(NEAR_PRODUCT("%0", "%3", "%4", "%5", "%6", "%7", "%8", START)                                                                 \
+        : "=&v"(r), [m] "=&v"(m), [c] "=&s"(carry)                                                                                   \
+        : NEAR_WORDS(F, f), "v"((uint32_t)y), "v"(y), "v"(x), [qi] "s"(n.qi), [q0] "s"(n.q0), [q1] "s"(n.q1), [half] "s"(n.half)      \
+        : "v2", "v3")
+    if (ZERO) x = y;                                     // not used
+    if (UNI && ZERO) NEAR_ASM("0", "s");
+    if (UNI && !ZERO) NEAR_ASM("%9", "s");
+    if (!UNI && ZERO) NEAR_ASM("0", "v");
+    if (!UNI && !ZERO) NEAR_ASM("%9", "v");
+#undef NEAR_ASM
+    return r;
+}
+template <bool UNI, bool ZERO = false>
+__device__ __forceinline__ void near_acc2(u64& r0, u64 x0, u64 y0, ulonglong2 f0, u64& r1, u64 x1, u64 y1, ulonglong2 f1, const NearQ& n) {
+    u64 s0, s1, carry;
+    uint32_t m;
+#define NEAR_ASM(START0, START1, F)                                                                                                  \
+    asm(NEAR_PRODUCT("%0", "%4", "%5", "%6", "%7", "%12", "%14", START0) NEAR_PRODUCT("%1", "%8", "%9", "%10", "%11", "%13", "%15", START1)   \
+        : "=&v"(s0), "=&v"(s1), [m] "=&v"(m), [c] "=&s"(carry)                                                                       \
+        : NEAR_WORDS(F, f0), NEAR_WORDS(F, f1), "v"((uint32_t)y0), "v"((uint32_t)y1), "v"(y0), "v"(y1), "v"(x0), "v"(x1),             \
+          [qi] "s"(n.qi), [q0] "s"(n.q0), [q1] "s"(n.q1), [half] "s"(n.half)                                                         \
+        : "v2", "v3")
+    if (ZERO) x0 = y0, x1 = y1;                          // not used
+    if (UNI && ZERO) NEAR_ASM("0", "0", "s");
+    if (UNI && !ZERO) NEAR_ASM("%16", "%17", "s");
+    if (!UNI && ZERO) NEAR_ASM("0", "0", "v");
+    if (!UNI && !ZERO) NEAR_ASM("%16", "%17", "v");
+#undef NEAR_ASM
+    r0 = s0;
+    r1 = s1;
+}
+// Differences of two pairs of 64-bit numbers.  A borrow may be read two instructions after it is written; the compiler, which
+// keeps all of them in the same flag, waits that long for each.
+__device__ __forceinline__ u64 join32(uint32_t lo, uint32_t hi) { return ((u64)hi << 32) | lo; }
+__device__ __forceinline__ void sub2(u64& d0, u64 a0, u64 b0, u64& d1, u64 a1, u64 b1) {
+    uint32_t l0, h0, l1, h1;
+    u64 c;
+    asm("v_sub_co_u32 %0, vcc, %5, %6\n\t"
+        "v_sub_co_u32 %2, %4, %9, %10\n\t"
+        "s_nop 0\n\t"
+        "v_subb_co_u32 %1, vcc, %7, %8, vcc\n\t"
+        "v_subb_co_u32 %3, %4, %11, %12, %4"
+        : "=&v"(l0), "=&v"(h0), "=&v"(l1), "=&v"(h1), "=&s"(c)
+        : "v"((uint32_t)a0), "v"((uint32_t)b0), "v"((uint32_t)(a0 >> 32)), "v"((uint32_t)(b0 >> 32)), "v"((uint32_t)a1), "v"((uint32_t)b1),
+          "v"((uint32_t)(a1 >> 32)), "v"((uint32_t)(b1 >> 32))
+        : "vcc");
+    d0 = join32(l0, h0);
+    d1 = join32(l1, h1);
+}
+
 // w*y mod q in [0, 4q)
 __device__ __forceinline__ u64 shoup_lazy4(u64 y, u64 w, u64 w_sh, u64 q) { return shoup_acc(0, y, w, w_sh, q); }
 

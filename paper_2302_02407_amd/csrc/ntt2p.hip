@@ -44,16 +44,19 @@ struct P2Args {
     uint32_t lazy;            // forward, last pass: outputs may stay below 2q
     uint32_t rs_mod;          // forward, first pass reading the Rescale rounding term: modulus index of the dropped limb
     uint32_t log_chunk;       // row passes, see row_decode
-    u64 widest;               // bit per modulus
+    u64 widest, near;         // bit per modulus; near: of this direction
 };
 // f(std::integral_constant<int, W>, e) for the class W of the modulus of entry e.  Keeps the loads of the branches apart: merged above
 // them (they look alike) they would stay live across all of it, 240 registers instead of 109.
 template <class F>
-__device__ __forceinline__ void by_class(u64 widest, uint32_t mi, uint32_t e, F&& f) {
-    if (!(e & TAB_WIDE)) {
+__device__ __forceinline__ void by_class(const P2Args& a, uint32_t mi, uint32_t e, F&& f) {
+    if (a.near >> mi & 1u) {
+        asm("; near" : "+s"(e));
+        f(std::integral_constant<int, W_NEAR>(), e);
+    } else if (!(e & TAB_WIDE)) {
         asm("; narrow" : "+s"(e));
         f(std::integral_constant<int, 0>(), e);
-    } else if (!(widest >> mi & 1u)) {
+    } else if (!(a.widest >> mi & 1u)) {
         asm("; wide" : "+s"(e));
         f(std::integral_constant<int, 1>(), e);
     } else {
@@ -118,6 +121,7 @@ __device__ __forceinline__ void col_fwd(const P2Args& a, const LimbTab& tab, uin
 #pragma unroll
         for (int k = 0; k < 16; k++) x[k] = shoup_lazy4(addmod(x[k], h, ml.q), 1, m.one_sh, q) + (q - hr);      // below 5q
     }
+    fwd_centre<W>(x, m);
     int b = 5;
     fwd_stages<W, 0, 4, true>(x, w1, q, b);
 #pragma unroll
@@ -153,7 +157,7 @@ __global__ __launch_bounds__(P2_THREADS, 4) void ntt_col_fwd_kernel(P2Args a, Li
     using G = Col<LC>;
     __shared__ u64 sm[G::LDS];
     const uint32_t tile = blockIdx.x & (G::T - 1), e = __builtin_amdgcn_readfirstlane(tab.e[blockIdx.x >> G::LT]);
-    by_class(a.widest, tab_mod(e), e, [&](auto W, uint32_t v) { col_fwd<LC, RS, W>(a, tab, v, tile, sm); });
+    by_class(a, tab_mod(e), e, [&](auto W, uint32_t v) { col_fwd<LC, RS, W>(a, tab, v, tile, sm); });
 }
 
 // Inverse column stages and output scaling: inputs below 2q (wide moduli: w_half), results canonical.  Stage 0 (one twiddle for the whole limb)
@@ -174,10 +178,11 @@ __device__ __forceinline__ void col_inv(const P2Args& a, uint32_t e, uint32_t ti
     else tw_load<0, 4>(w2, tw, 4, t >> 1);
     const ModConst m = mod_const(a.mc, mi);
     const uint32_t si = CUSTOM_SCALE ? limb % scale_period : 0;
-    const u64 cs = CUSTOM_SCALE ? sc.s[si] : m.ninv, cs_sh = CUSTOM_SCALE ? sc.s_sh[si] : m.ninv_sh;
-    const u64 cw = CUSTOM_SCALE ? sc.w[si] : m.ninv_w, cw_sh = CUSTOM_SCALE ? sc.w_sh[si] : m.ninv_w_sh;
+    constexpr bool NEAR = W == W_NEAR;
+    const u64 cs = CUSTOM_SCALE ? sc.s[si] : NEAR ? m.near_s : m.ninv, cs_sh = CUSTOM_SCALE ? sc.s_sh[si] : NEAR ? m.near_s_sh : m.ninv_sh;
+    const u64 cw = CUSTOM_SCALE ? sc.w[si] : NEAR ? m.near_w : m.ninv_w, cw_sh = CUSTOM_SCALE ? sc.w_sh[si] : NEAR ? m.near_w_sh : m.ninv_w_sh;
     const u64 q = m.q;
-    int bound = W ? w_half(W) : 2;
+    int bound = w_start(W);
     if (LC <= 8) {
         inv_stages<W, G::U0, 4>(x, w2, q, bound);
 #pragma unroll
@@ -193,10 +198,10 @@ __device__ __forceinline__ void col_inv(const P2Args& a, uint32_t e, uint32_t ti
 #pragma unroll
         for (int j = 0; j < 16; j++) x[j] = sm[G::pos(r0 + 2 * j, cl)];
         inv_stages<W, 0, 4>(x, w2, q, bound);
-        if (W == 0) {
+        if (W == 0 || W == W_NEAR) {
             bound = 2;
 #pragma unroll
-            for (int j = 0; j < 16; j++) x[j] = reduce_lazy<10>(x[j], q, m.bits, m.rec);
+            for (int j = 0; j < 16; j++) x[j] = inv_end<W>(x[j], m);
         }
         __syncthreads();
 #pragma unroll
@@ -210,11 +215,11 @@ __device__ __forceinline__ void col_inv(const P2Args& a, uint32_t e, uint32_t ti
 #pragma unroll
     for (int k = 0; k < 8; k++) {
         const u64 X = x[k], Y = x[k + 8];
-        x[k] = shoup_lazy4(X + Y, cs, cs_sh, q);
-        x[k + 8] = shoup_lazy4((X + q * (u64)bound) - Y, cw, cw_sh, q);        // any value below 2^64
+        x[k] = inv_scaled<W>(X + Y, cs, cs_sh, q);
+        x[k + 8] = inv_scaled<W>(W == W_NEAR ? X - Y : (X + q * (u64)bound) - Y, cw, cw_sh, q);
     }
 #pragma unroll
-    for (int k = 0; k < 16; k++) (data + ((size_t)k << (G::LT + 8)))[t * 256 + c] = csub_min(csub_min(x[k], 2 * q), q);
+    for (int k = 0; k < 16; k++) (data + ((size_t)k << (G::LT + 8)))[t * 256 + c] = inv_canonical<W>(x[k], q);
 }
 
 // N = 2^17 (LC = 9) runs three wavefronts to a SIMD: held to four, its three register blocks spilled 12 bytes a lane.  Inverse
@@ -225,7 +230,7 @@ __global__ __launch_bounds__(P2_THREADS, LC == 9 ? 3 : 4) void ntt_col_inv_kerne
     using G = Col<LC>;
     __shared__ u64 sm[G::LDS];
     const uint32_t tile = blockIdx.x & (G::T - 1), e = __builtin_amdgcn_readfirstlane(tab.e[blockIdx.x >> G::LT]);
-    by_class(a.widest, tab_mod(e), e, [&](auto W, uint32_t v) { col_inv<LC, CUSTOM_SCALE, W>(a, v, tile, sm, sc, scale_period); });
+    by_class(a, tab_mod(e), e, [&](auto W, uint32_t v) { col_inv<LC, CUSTOM_SCALE, W>(a, v, tile, sm, sc, scale_period); });
 }
 
 // ---------------------------------------------------------------- forward row pass
@@ -277,12 +282,12 @@ __device__ __forceinline__ void row_fwd(const P2Args& a, uint32_t e, uint32_t ti
         row4_fwd<W, 1>(reinterpret_cast<u64 (&)[1][4]>(x), w, s, 272, Row4(t), q);
     }
     if (!EPI) {
-        if (W == 0 && a.lazy) {
+        if ((W == 0 || W == W_NEAR) && a.lazy) {
 #pragma unroll
-            for (int j = 0; j < PTS; j++) x[j] = reduce_lazy<7>(x[j], q, m.bits, m.rec);
+            for (int j = 0; j < PTS; j++) x[j] = fwd_lazy<W>(x[j], m);
         } else {
 #pragma unroll
-            for (int j = 0; j < PTS; j++) x[j] = reduce_min<7>(x[j], q, m.bits, m.rec);
+            for (int j = 0; j < PTS; j++) x[j] = reduce_min<7>(fwd_positive<W>(x[j], q), q, m.bits, m.rec);
         }
         if constexpr (LANES == 16) {
             wave_exchange();
@@ -304,16 +309,16 @@ __device__ __forceinline__ void row_fwd(const P2Args& a, uint32_t e, uint32_t ti
     }
     // out = (acc - ntt) * P^-1 + sigma(c0) + self: the product is below 5q whatever its factor, so the transform value may
     // stay as it is where 128q plus the accumulator (below 6q) fits 63 bits, else below 2q; the sum is below 7q
-    const bool raw = W == 0 && m.bits <= 55;
+    const bool raw = fwd_raw<W>(m);
     if (!raw) {
 #pragma unroll
-        for (int j = 0; j < PTS; j++) x[j] = reduce_lazy<7>(x[j], q, m.bits, m.rec);
+        for (int j = 0; j < PTS; j++) x[j] = reduce_lazy<7>(fwd_positive<W>(x[j], q), q, m.bits, m.rec);
     }
     wave_exchange();
     const uint32_t e0 = LANES == 16 ? 16 * t : 4 * row4_last(t);       // x[j] = point e0 + j of the row
 #pragma unroll
     for (int j = 0; j < PTS; j++) s[e0 + j + ((e0 + j) >> 4)] = x[j];
-    const u64 bias = raw ? (q << 7) : 2 * q;
+    const u64 bias = raw ? fwd_raw_bias<W>(q) : 2 * q;
     const uint32_t pc = limb / ep.L1, r = limb - pc * ep.L1, job = pc >> 1, comp = pc & 1u, row0 = b * 256;
     const u64 pinv = uni64(ep.pinv[r]), pinv_sh = uni64(ep.pinv_sh[r]), n2q = opaque_s(0 - 2 * q), pinv_h = split_factor<true>(pinv, pinv_sh, n2q);
     const size_t ro = (size_t)r << logN;
@@ -354,7 +359,7 @@ __global__ __launch_bounds__(P2_THREADS, 4) void ntt_row_fwd_kernel(P2Args a, Li
     uint32_t tile;
     const uint32_t e = row_decode<LANES>(tab, a, tile);
     if (e == TAB_NONE) return;
-    by_class(a.widest, tab_mod(e), e, [&](auto W, uint32_t v) { row_fwd<W, EPI, LANES>(a, v, tile, sm, ep); });
+    by_class(a, tab_mod(e), e, [&](auto W, uint32_t v) { row_fwd<W, EPI, LANES>(a, v, tile, sm, ep); });
 }
 
 // ---------------------------------------------------------------- inverse row pass
@@ -410,9 +415,9 @@ __device__ __forceinline__ void row_inv(const P2Args& a, const LimbTab& tab, uin
 #pragma unroll
         for (int k = 0; k < 16; k++) x[k] = s[t + 17 * k];
         inv_stages<W, 0, 4>(x, w1, q, bound);
-        if (W == 0) {
+        if (W == 0 || W == W_NEAR) {
 #pragma unroll
-            for (int k = 0; k < 16; k++) x[k] = reduce_lazy<10>(x[k], q, m.bits, m.rec);
+            for (int k = 0; k < 16; k++) x[k] = inv_end<W>(x[k], m);
         }
 #pragma unroll
         for (int k = 0; k < 16; k++) out[t + 16 * k] = x[k];
@@ -430,7 +435,7 @@ __global__ __launch_bounds__(P2_THREADS, 4) void ntt_row_inv_kernel(P2Args a, Li
     uint32_t tile;
     const uint32_t e = row_decode<LANES>(tab, a, tile);
     if (e == TAB_NONE) return;
-    by_class(a.widest, tab_mod(e), e, [&](auto W, uint32_t v) { row_inv<W, LANES>(a, tab, v, tile, sm); });
+    by_class(a, tab_mod(e), e, [&](auto W, uint32_t v) { row_inv<W, LANES>(a, tab, v, tile, sm); });
 }
 
 // ---------------------------------------------------------------- row passes of several limbs of one modulus
@@ -496,12 +501,12 @@ __device__ __forceinline__ void row_run_fwd(const P2Args& a, const LimbTab& tab,
         run_keep(w2);
         fwd_stages<W, 0, 4>(x, w2, q, bound);
         SCHED_FENCE();
-        if (W == 0 && LAZY) {
+        if ((W == 0 || W == W_NEAR) && LAZY) {
 #pragma unroll
-            for (int j = 0; j < 16; j++) x[j] = reduce_lazy<7>(x[j], q, m.bits, m.rec);
+            for (int j = 0; j < 16; j++) x[j] = fwd_lazy<W>(x[j], m);
         } else {
 #pragma unroll
-            for (int j = 0; j < 16; j++) x[j] = reduce_min<7>(x[j], q, m.bits, m.rec);
+            for (int j = 0; j < 16; j++) x[j] = reduce_min<7>(fwd_positive<W>(x[j], q), q, m.bits, m.rec);
         }
         wave_exchange();
 #pragma unroll
@@ -552,9 +557,9 @@ __device__ __forceinline__ void row_run_inv(const P2Args& a, const LimbTab& tab,
 #pragma unroll
         for (int k = 0; k < 16; k++) x[k] = s[t + 17 * k];
         inv_stages<W, 0, 4, true>(x, w1, q, bound);
-        if (W == 0) {
+        if (W == 0 || W == W_NEAR) {
 #pragma unroll
-            for (int k = 0; k < 16; k++) x[k] = reduce_lazy<10>(x[k], q, m.bits, m.rec);
+            for (int k = 0; k < 16; k++) x[k] = inv_end<W>(x[k], m);
         }
         if (4 * it + quarter < n) {
             u64* out = a.dst + ((size_t)dl << logN) + at;
@@ -572,7 +577,7 @@ __global__ __launch_bounds__(P2_THREADS, 4) void ntt_row_run_kernel(P2Args a, Li
     __shared__ u64 sm[16 * 272];
     const uint32_t lb = a.logN - 10, b = (blockIdx.x & ((1u << lb) - 1u)) * 4u + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t run = __builtin_amdgcn_readfirstlane(runs.r[blockIdx.x >> lb]);
-    by_class(a.widest, run >> 14 & 63u, run, [&](auto W, uint32_t v) {
+    by_class(a, run >> 14 & 63u, run, [&](auto W, uint32_t v) {
         if constexpr (FWD) row_run_fwd<W, LAZY>(a, tab, v, b, sm);
         else row_run_inv<W>(a, tab, v, b, sm);
     });
@@ -605,9 +610,9 @@ __global__ __launch_bounds__(P2_THREADS) void bfly_probe_kernel(const ulonglong2
 }
 
 int32_t probe_butterfly_rates(he_ctx* ctx, u64* d_out, uint32_t groups, double rate_out[3]) {
-    static void (*const probes[2][3])(const ulonglong2*, u64, u64*, uint32_t) = {
-        {bfly_probe_kernel<false, 0>, bfly_probe_kernel<false, 1>, bfly_probe_kernel<false, 2>},
-        {bfly_probe_kernel<true, 0>, bfly_probe_kernel<true, 1>, bfly_probe_kernel<true, 2>}};
+    static void (*const probes[2][4])(const ulonglong2*, u64, u64*, uint32_t) = {
+        {bfly_probe_kernel<false, 0>, bfly_probe_kernel<false, 1>, bfly_probe_kernel<false, 2>, bfly_probe_kernel<false, W_NEAR>},
+        {bfly_probe_kernel<true, 0>, bfly_probe_kernel<true, 1>, bfly_probe_kernel<true, 2>, bfly_probe_kernel<true, W_NEAR>}};
     const uint32_t rounds = 64;                          // 32 butterflies per thread per round
     uint32_t narrow = 0, wide = ctx->M;
     for (uint32_t i = 0; i < ctx->M; i++) if (!narrow_fwd(ctx->mod[i])) { wide = i; break; }
@@ -621,7 +626,7 @@ int32_t probe_butterfly_rates(he_ctx* ctx, u64* d_out, uint32_t groups, double r
         const bool fwd = which != 1;
         const ulonglong2* tw = (fwd ? ctx->d_tw : ctx->d_itw) + (size_t)mi * ctx->N;
         const u64 q = ctx->mod[mi];
-        void (*const kernel)(const ulonglong2*, u64, u64*, uint32_t) = probes[fwd][(fwd ? narrow_fwd(q) : narrow_inv(q)) ? 0 : widest(q) ? 2 : 1];
+        void (*const kernel)(const ulonglong2*, u64, u64*, uint32_t) = probes[fwd][(fwd ? near_fwd(q, ctx->logN) : near_inv(q)) ? W_NEAR : (fwd ? narrow_fwd(q) : narrow_inv(q)) ? 0 : widest(q) ? 2 : 1];
         for (int rep = 0; rep < 2; rep++) {              // the first launch warms up
             HE_HIP(ctx, hipEventRecord(e0, ctx->stream));
             hipLaunchKernelGGL(kernel, dim3(groups), dim3(P2_THREADS), 0, ctx->stream, tw, q, d_out, rounds);
@@ -688,8 +693,11 @@ int32_t launch_transform2p(he_ctx* ctx, const TransformDesc& d) {
     a.dst = d.dst; a.mc = ctx->d_mc;
     a.tw = fwd ? ctx->d_tw : ctx->d_itw;
     a.logN = logN;
-    a.widest = 0;
-    for (uint32_t m = 0; m < ctx->M; m++) a.widest |= (u64)widest(ctx->mod[m]) << m;
+    a.widest = a.near = 0;
+    for (uint32_t m = 0; m < ctx->M; m++) {
+        a.widest |= (u64)widest(ctx->mod[m]) << m;
+        a.near |= (u64)(fwd ? near_fwd(ctx->mod[m], ctx->logN) : near_inv(ctx->mod[m])) << m;
+    }
     a.lazy = (fwd && d.lazy_out) ? 1u : 0u;
     a.rs_mod = d.rescale_from ? d.rescale_from - 1 : 0;
     uint32_t lc = 0;

@@ -5,8 +5,9 @@
 
 #define SCHED_FENCE() __builtin_amdgcn_sched_barrier(0)   // loads above it are issued before the arithmetic below it
 
-// A butterfly is counted in instructions: on gfx950 the 32-bit multiplies, v_mad_u64_u32, v_lshl_add_u64 and the FP64 instructions all
-// issue at one per lane and cycle, plain 32-bit additions and bit operations at two, so what costs is how many there are.  The product
+// A butterfly is counted in instructions: on gfx950 the 32-bit multiplies, multiply-adds, v_lshl_add_u64, carries and the FP64 instructions all
+// issue at one per lane and cycle, and what other instructions there are among them at the same, so what costs is how many there are.  A wavefront by
+// itself issues one in five cycles; a scalar instruction between two vector ones costs it some 20 more, a wait state 4.  The product
 // enters the sum through the multiply-adds' own addend (X + w*Y - h*2q accumulated in one chain), and the difference is
 // 2X + 5q minus that sum: two instructions for the quotient h, 7 for the sum (split_acc), 3 for the difference, and 3 for a factor's second
 // word where it is not the same for the whole wavefront (scalar instructions there).  With a quotient of two words it were 16, a
@@ -14,12 +15,19 @@
 //
 // Ranges are kept in units of q and known when the code is compiled: a product is below 5q whatever its factor, a forward stage therefore
 // adds that to the bound of every point, an inverse stage doubles it.  What multiplies a factor has to stay
-// below 2^63.  Three classes of moduli, a template parameter W of everything here, one for each direction (he_internal.h):
+// below 2^63.  Classes of moduli, a template parameter W of everything here, one for each direction (he_internal.h):
 //   0  narrow: never reduced.  Forward: 17 stages from below 5q end below 90q; inverse: a pass ends below 640q.
 //   1  up to 2^63 / 13: points stay below 13q, which takes one conditional subtraction of two instructions (csub_min) a forward butterfly.
 //   2  the others (below 2^60): below 8q, two of them.
-__device__ constexpr int w_lim(int W) { return W == 1 ? 13 : 8; }         // sums and products' operands (W > 0)
-__device__ constexpr int w_half(int W) { return w_lim(W) / 2; }            // inverse: points between stages (W > 0)
+//   3  W_NEAR, moduli near a multiple of 2^32 (near_acc, modarith.h): signed points, never reduced.  Forward: below 22q at the end (16q above 2^58),
+//      NEAR_ROWS between the passes; inverse: a pass ends below 512q.  What they need at the start: he_internal.h.
+#define W_NEAR 3
+#define NEAR_ROWS 14
+// multiples of q that make any forward result positive, which together stay below 2^64
+__device__ __forceinline__ u64 near_bias(u64 q) { return q * (q > 1ull << 58 ? 16 : 24); }
+__device__ constexpr int w_lim(int W) { return W == W_NEAR ? NEAR_ROWS : W == 1 ? 13 : 8; }         // sums and products' operands (W > 0)
+__device__ constexpr int w_half(int W) { return w_lim(W) / 2; }            // inverse: points between stages (W = 1, 2)
+__device__ constexpr int w_start(int W) { return W == 1 || W == 2 ? w_half(W) : 2; }      // inverse: what a pass starts with
 // what the butterflies need of a modulus, in scalar registers
 struct StageQ {
     u64 n2q, q5;
@@ -31,9 +39,34 @@ __device__ __forceinline__ void halve(u64& x, int& b, u64 q) {
     x = csub_min(x, q * (u64)h);
     b = h;
 }
+// Two butterflies of a near modulus, with a factor each
+template <bool UNI>
+__device__ __forceinline__ void ct_near2(u64& x0, u64& y0, ulonglong2 f0, u64& x1, u64& y1, ulonglong2 f1, const NearQ& n) {
+    u64 s0, s1;
+    near_acc2<UNI>(s0, x0, y0, f0, s1, x1, y1, f1, n);
+    y0 = (x0 << 1) - s0;
+    y1 = (x1 << 1) - s1;
+    x0 = s0;
+    x1 = s1;
+}
+template <bool UNI>
+__device__ __forceinline__ void gs_near2(u64& x0, u64& y0, ulonglong2 f0, u64& x1, u64& y1, ulonglong2 f1, const NearQ& n) {
+    u64 d0, d1;
+    sub2(d0, x0, y0, d1, x1, y1);
+    x0 = x0 + y0;
+    x1 = x1 + y1;
+    near_acc2<UNI, true>(y0, 0, d0, f0, y1, 0, d1, f1, n);
+}
 // One factor on K pairs of points X(k), Y(k) below b*q; returns the bound of the results.
 template <int W, bool UNI, int K, class PX, class PY>
 __device__ __forceinline__ int ct_stage(int b, PX&& X, PY&& Y, u64 w, u64 a, u64 q) {
+    if constexpr (W == W_NEAR) {
+        const NearQ n(q);
+#pragma unroll
+        for (int k = 0; k + 1 < K; k += 2) ct_near2<UNI>(X(k), Y(k), make_ulonglong2(w, a), X(k + 1), Y(k + 1), make_ulonglong2(w, a), n);
+        static_assert(K % 2 == 0, "");
+        return b + 1;
+    }
     const StageQ sq(q);
     const u64 wh = split_factor<UNI>(w, a, sq.n2q);
     int after = b;
@@ -57,6 +90,13 @@ __device__ __forceinline__ int ct_stage(int b, PX&& X, PY&& Y, u64 w, u64 a, u64
 // goes in stays within w_lim, so sums (and, of the widest, products) are halved where the next stage would leave it.
 template <int W, bool UNI, int K, class PX, class PY>
 __device__ __forceinline__ int gs_stage(int b, PX&& X, PY&& Y, u64 w, u64 a, u64 q) {
+    if constexpr (W == W_NEAR) {
+        const NearQ n(q);
+#pragma unroll
+        for (int k = 0; k + 1 < K; k += 2) gs_near2<UNI>(X(k), Y(k), make_ulonglong2(w, a), X(k + 1), Y(k + 1), make_ulonglong2(w, a), n);
+        static_assert(K % 2 == 0, "");
+        return 2 * b;
+    }
     const StageQ sq(q);
     const u64 wh = split_factor<UNI>(w, a, sq.n2q);
     int after = b;
@@ -86,11 +126,46 @@ __device__ __forceinline__ ModConst mod_const(const ModConst* mc, uint32_t mi) {
     m.ninv_sh = p[offsetof(ModConst, ninv_sh) / 8];
     m.ninv_w = p[offsetof(ModConst, ninv_w) / 8];
     m.ninv_w_sh = p[offsetof(ModConst, ninv_w_sh) / 8];
+    m.near_s = p[offsetof(ModConst, near_s) / 8];
+    m.near_s_sh = p[offsetof(ModConst, near_s_sh) / 8];
+    m.near_w = p[offsetof(ModConst, near_w) / 8];
+    m.near_w_sh = p[offsetof(ModConst, near_w_sh) / 8];
     m.one_sh = p[offsetof(ModConst, one_sh) / 8];
     const u64 v = p[offsetof(ModConst, bits) / 8];
     m.bits = (uint32_t)v; m.rec = (uint32_t)(v >> 32);
     return m;
 }
+// Results of a forward transform (W_NEAR: signed) as positive numbers below 2^7 q
+template <int W>
+__device__ __forceinline__ u64 fwd_positive(u64 x, u64 q) { return W == W_NEAR ? x + near_bias(q) : x; }
+// Results where the caller takes them below 2q of narrow moduli and canonical of others (q or 0 is taken off: no branch between the points)
+template <int W>
+__device__ __forceinline__ u64 fwd_lazy(u64 x, const ModConst& m) {
+    const u64 v = reduce_lazy<7>(fwd_positive<W>(x, m.q), m.q, m.bits, m.rec);
+    return W == W_NEAR ? csub_min(v, m.q > (1ull << 63) / 96 ? m.q : 0) : v;
+}
+// Points of up to 2^7 q for the first forward pass of a modulus that needs them centred, below q in magnitude
+template <int W, int N>
+__device__ __forceinline__ void fwd_centre(u64 (&x)[N], const ModConst& m) {
+    if (W != W_NEAR || m.q <= 1ull << 58) return;
+#pragma unroll
+    for (int k = 0; k < N; k++) x[k] = reduce_lazy<7>(x[k], m.q, m.bits, m.rec) - m.q;
+}
+// What an inverse pass ends with, below 2q (narrow and near moduli)
+template <int W>
+__device__ __forceinline__ u64 inv_end(u64 x, const ModConst& m) { return reduce_lazy<10>(W == W_NEAR ? x + (m.q << 9) : x, m.q, m.bits, m.rec); }
+
+// The last inverse stage's products, which carry the output scaling (any operand an inverse pass has), and what makes them canonical.
+template <int W>
+__device__ __forceinline__ u64 inv_scaled(u64 y, u64 w, u64 w_sh, u64 q) { return W == W_NEAR ? near_acc<true>(q, y, make_ulonglong2(w, w_sh), NearQ(q)) : shoup_lazy4(y, w, w_sh, q); }
+template <int W>
+__device__ __forceinline__ u64 inv_canonical(u64 x, u64 q) { return W == W_NEAR ? csub_min(x, q) : csub_min(csub_min(x, 2 * q), q); }
+// Whether a forward transform's results go into a ModDown's difference (accumulator below 6q, less the result, plus the bias, below 2^63) as they are
+template <int W>
+__device__ __forceinline__ bool fwd_raw(const ModConst& m) { return (W == 0 && m.bits <= 55) || (W == W_NEAR && m.bits <= 57); }
+template <int W>
+__device__ __forceinline__ u64 fwd_raw_bias(u64 q) { return W == W_NEAR ? near_bias(q) : q << 7; }
+
 // Register blocks of four stages on 16 points.  Stage u pairs (k, k + (8>>u)); the twiddle of the pair's group g =
 // k >> (4-u) is tw[(1 << (s0+u)) + (G << u) + g], G = group of the 16 points at stage s0, kept at index (1 << u) - 1 + g.
 // A factor and its companion lie next to each other, one 16-byte load.  Loading is separate from use: a pass that
@@ -142,7 +217,12 @@ __device__ __forceinline__ void fwd_stages(u64 (&x)[16], const ulonglong2 (&w)[1
             if (u == 0) after = ct_stage<W, UNI, 8>(b, X, Y, f.x, f.y, q);
             else if (u == 1) after = ct_stage<W, UNI, 4>(b, X, Y, f.x, f.y, q);
             else if (u == 2) after = ct_stage<W, UNI, 2>(b, X, Y, f.x, f.y, q);
-            else after = ct_stage<W, UNI, 1>(b, X, Y, f.x, f.y, q);
+            else if constexpr (W != W_NEAR) after = ct_stage<W, UNI, 1>(b, X, Y, f.x, f.y, q);
+            else if (g & 1) {                            // two factors at a time
+                const ulonglong2 e = w[(1 << u) - 2 + g];
+                ct_near2<UNI>(x[2 * g - 2], x[2 * g - 1], e, x[2 * g], x[2 * g + 1], f, NearQ(q));
+                after = b + 1;
+            }
         }
         b = after;
     }
@@ -162,7 +242,12 @@ __device__ __forceinline__ void inv_stages(u64 (&x)[16], const ulonglong2 (&w)[1
             if (u == 0) after = gs_stage<W, UNI, 8>(b, X, Y, f.x, f.y, q);
             else if (u == 1) after = gs_stage<W, UNI, 4>(b, X, Y, f.x, f.y, q);
             else if (u == 2) after = gs_stage<W, UNI, 2>(b, X, Y, f.x, f.y, q);
-            else after = gs_stage<W, UNI, 1>(b, X, Y, f.x, f.y, q);
+            else if constexpr (W != W_NEAR) after = gs_stage<W, UNI, 1>(b, X, Y, f.x, f.y, q);
+            else if (g & 1) {                            // two factors at a time
+                const ulonglong2 e = w[(1 << u) - 2 + g];
+                gs_near2<UNI>(x[2 * g - 2], x[2 * g - 1], e, x[2 * g], x[2 * g + 1], f, NearQ(q));
+                after = 2 * b;
+            }
         }
         b = after;
     }
@@ -174,13 +259,23 @@ template <int W, bool UNI, int NX, bool ONE = false>
 __device__ __forceinline__ void fwd_block2_x(u64 (&x)[NX][4], const u64 (&r)[6], u64 q, int& b) {
     b = ct_stage<W, UNI, 2 * NX>(b, [&](int k) -> u64& { return x[k >> 1][k & 1]; }, [&](int k) -> u64& { return x[k >> 1][2 + (k & 1)]; }, r[0], r[1], q);
     if (ONE) return;
-    const int after = ct_stage<W, UNI, NX>(b, [&](int k) -> u64& { return x[k][0]; }, [&](int k) -> u64& { return x[k][1]; }, r[2], r[3], q);
-    ct_stage<W, UNI, NX>(b, [&](int k) -> u64& { return x[k][2]; }, [&](int k) -> u64& { return x[k][3]; }, r[4], r[5], q);
-    b = after;
+    if constexpr (W == W_NEAR) {
+#pragma unroll
+        for (int c = 0; c < NX; c++) ct_near2<UNI>(x[c][0], x[c][1], make_ulonglong2(r[2], r[3]), x[c][2], x[c][3], make_ulonglong2(r[4], r[5]), NearQ(q));
+        b += 1;
+    } else {
+        const int after = ct_stage<W, UNI, NX>(b, [&](int k) -> u64& { return x[k][0]; }, [&](int k) -> u64& { return x[k][1]; }, r[2], r[3], q);
+        ct_stage<W, UNI, NX>(b, [&](int k) -> u64& { return x[k][2]; }, [&](int k) -> u64& { return x[k][3]; }, r[4], r[5], q);
+        b = after;
+    }
 }
 template <int W, bool UNI, int NX, bool ONE = false>
 __device__ __forceinline__ void inv_block2_x(u64 (&x)[NX][4], const u64 (&r)[6], u64 q, int& b) {
-    if (!ONE) {
+    if constexpr (!ONE && W == W_NEAR) {
+#pragma unroll
+        for (int c = 0; c < NX; c++) gs_near2<UNI>(x[c][0], x[c][1], make_ulonglong2(r[2], r[3]), x[c][2], x[c][3], make_ulonglong2(r[4], r[5]), NearQ(q));
+        b *= 2;
+    } else if constexpr (!ONE) {
         const int after = gs_stage<W, UNI, NX>(b, [&](int k) -> u64& { return x[k][0]; }, [&](int k) -> u64& { return x[k][1]; }, r[2], r[3], q);
         gs_stage<W, UNI, NX>(b, [&](int k) -> u64& { return x[k][2]; }, [&](int k) -> u64& { return x[k][3]; }, r[4], r[5], q);
         b = after;
@@ -304,10 +399,10 @@ __device__ __forceinline__ void row4_inv(u64 (&x)[NX][4], const u64 (&w)[4][6], 
             for (int c = 0; c < NX; c++) at.store(i, x[c], s + c * stride);
         }
     }
-    if (W == 0) {
+    if (W == 0 || W == W_NEAR) {
 #pragma unroll
         for (int c = 0; c < NX; c++)
 #pragma unroll
-            for (int k = 0; k < 4; k++) x[c][k] = reduce_lazy<10>(x[c][k], q, m.bits, m.rec);
+            for (int k = 0; k < 4; k++) x[c][k] = inv_end<W>(x[c][k], m);
     }
 }

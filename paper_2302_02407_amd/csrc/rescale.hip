@@ -51,7 +51,7 @@ struct RsTile {
     // points of the last block to points of the first: below 2q and 640q (narrow moduli), below w_half before and after (others)
     template <int W>
     __device__ __forceinline__ void inverse(u64 (&x)[4], u64* buf, const u64 (&w)[NB][6], u64 q, const ModConst& m) const {
-        int bound = W ? w_half(W) : 2;
+        int bound = w_start(W);
 #pragma unroll
         for (int i = NB - 1; i >= 0; i--) {
             if (i + 1 < NB) {
@@ -59,9 +59,9 @@ struct RsTile {
                 else __syncthreads();
                 load(x, buf, i);
             }
-            if (W == 0 && LC == 9 && i == 0) {            // nine stages: the last two would leave the range
+            if ((W == 0 || W == W_NEAR) && LC == 9 && i == 0) {            // nine stages: the last two would leave the range
 #pragma unroll
-                for (int k = 0; k < 4; k++) x[k] = reduce_lazy<10>(x[k], q, m.bits, m.rec);
+                for (int k = 0; k < 4; k++) x[k] = inv_end<W>(x[k], m);
                 bound = 2;
             }
             if (2 * i + 1 >= LC) inv_block2_r<W, false, true>(x, w[i], q, bound);
@@ -108,7 +108,11 @@ __global__ __launch_bounds__(RS_THREADS, 4) void rescale_cols_kernel(RescaleCols
     g.factors(w, itw + ((size_t)rc.level << (LC + 8)));
     const ModConst ml = mod_const(mc, rc.level);
     const u64 h = ml.q >> 1;
-    if (!(rc.wide_inv >> rc.level & 1u)) g.template inverse<0>(x, lds + RS_LDS, w, ml.q, ml);
+    if (rc.near_inv >> rc.level & 1u) {
+        g.template inverse<W_NEAR>(x, lds + RS_LDS, w, ml.q, ml);
+#pragma unroll
+        for (int k = 0; k < 4; k++) x[k] += ml.q << 9;   // positive, as the product below takes them
+    } else if (!(rc.wide_inv >> rc.level & 1u)) g.template inverse<0>(x, lds + RS_LDS, w, ml.q, ml);
     else if (!(rc.widest >> rc.level & 1u)) g.template inverse<1>(x, lds + RS_LDS, w, ml.q, ml);
     else g.template inverse<2>(x, lds + RS_LDS, w, ml.q, ml);
     g.factors(w, ftw + ((size_t)r0 << (LC + 8)));
@@ -122,7 +126,11 @@ __global__ __launch_bounds__(RS_THREADS, 4) void rescale_cols_kernel(RescaleCols
         u64 y[4], *buf = lds + ((r - r0) & 1u) * RS_LDS;
 #pragma unroll
         for (int k = 0; k < 4; k++) y[k] = shoup_lazy4(x[k], 1, one_sh, q) + up;      // below 5q
-        if (!(rc.wide_fwd >> r & 1u)) g.template forward<0>(y, buf, w, q);
+        if (rc.near_fwd >> r & 1u) {
+            fwd_centre<W_NEAR>(y, m);
+            g.template forward<W_NEAR>(y, buf, w, q);
+        }
+        else if (!(rc.wide_fwd >> r & 1u)) g.template forward<0>(y, buf, w, q);
         else if (!(rc.widest >> r & 1u)) g.template forward<1>(y, buf, w, q);
         else g.template forward<2>(y, buf, w, q);
         u64* dst = rc.dst + ((size_t)(limb * rc.level + r) << (LC + 8));
@@ -143,11 +151,13 @@ bool rescale_cols_pays(const he_ctx* ctx, uint32_t n, uint32_t level) { return (
 int32_t launch_rescale_cols(he_ctx* ctx, const u64* src, u64* dst, uint32_t n, uint32_t level) {
     if (n == 0) return HE_OK;
     if (ctx->logN < 13 || ctx->logN > 17 || level == 0 || level >= ctx->nq) return he_fail(ctx, HE_ERR_BADARG, "rescale columns: bad shape");
-    RescaleCols rc = {src, dst, level, 0, 0, 0, 0, 0};
+    RescaleCols rc = {src, dst, level, 0, 0, 0, 0, 0, 0, 0};
     for (uint32_t i = 0; i <= level; i++) {
         rc.wide_fwd |= (u64)!narrow_fwd(ctx->mod[i]) << i;
         rc.wide_inv |= (u64)!narrow_inv(ctx->mod[i]) << i;
         rc.widest |= (u64)widest(ctx->mod[i]) << i;
+        rc.near_fwd |= (u64)near_fwd(ctx->mod[i], ctx->logN) << i;
+        rc.near_inv |= (u64)near_inv(ctx->mod[i]) << i;
     }
     // The moduli of a tile are shared out, each share with the inverse columns of its own, while that makes at most three work groups
     // per compute unit: a rescale after a product at level 11 of N = 2^16 117.4 us with up to 768 or 1024, 120.4 with 2048, 123.6 with
