@@ -607,9 +607,10 @@ static int32_t launch_inner_product(he_ctx* c, uint32_t level, const IpBatch& ib
 
 // The ModDown of J accumulators (each [2][R][N]): special-prime limbs -> coefficient form (pre-multiplied by
 // N^-1 * (P/p_t)^-1), conversion to q_0..q_level, forward transform with the epilogue described by `ep`.  With `rows` its
-// launches take the place of the row passes, form the accumulators, which are not stored, and ep says nothing.
+// launches take the place of the row passes, form the accumulators, which are not stored, and ep says nothing.  rows_done: tmp_dn holds
+// the special primes' inverse rows already (conversions with their columns only).
 static int32_t moddown_chain(he_ctx* c, uint32_t level, uint32_t J, u64* acc, u64* tmp_dn, u64* conv, const ModDownEpilogue& ep,
-                             KsRows* rows = nullptr) {
+                             KsRows* rows = nullptr, bool rows_done = false) {
     const uint32_t N = c->N, L1 = level + 1, k = c->np, R = L1 + k;
     const bool cc_on = c->d_dn_op != nullptr;
     ScaleList sc;
@@ -622,7 +623,8 @@ static int32_t moddown_chain(he_ctx* c, uint32_t level, uint32_t J, u64* acc, u6
         rows->mid = tmp_dn; rows->count_down = cc_on ? 1u : 0u;
         rc = launch_ks_rows(c, *rows, true);
     }
-    if (rc == HE_OK && !(rows && cc_on)) {
+    if (rows_done) c->cnt.intt_limbs += (uint64_t)J * 2 * k;
+    else if (rc == HE_OK && !(rows && cc_on)) {
         const uint32_t n = J * 2 * k;
         std::vector<uint32_t> mods(n);
         std::vector<uint16_t> lim(n);
@@ -1045,13 +1047,16 @@ struct HoistIp {
 // 54 bits, 112 so, 105 with the values of a digit asked for together and nothing reduced further than its reader needs.  JT = size of the register tile: ciphertexts a.J..JT-1 repeat ciphertext 0 and are not stored.
 #define HSL_MAX_TILES 24      // J * beta digit tiles of 2 KiB: 48 KiB of LDS
 #define HSL_RING 2            // (term, digit) pairs whose key values are in registers or on their way
-// the raised-basis limbs one launch works on: blockIdx.y indexes this list
+// the raised-basis limbs one launch works on: blockIdx.y indexes this list.  HSL_ROWS: the sums are complete and their inverse rows, class W
+// (ntt_blocks.h) above HSL_CLASS bits, go to `mid`.
+#define HSL_ROWS 0x100u
+#define HSL_CLASS 9
 struct LimbSel {
     uint32_t r[HE_MAX_MODULI];
 };
 template <int JT, bool WIDE>
 __device__ __forceinline__ void hoisted_sum_ip(const HoistIp& a, uint32_t r, uint32_t mi, const ModConst& m, u64* dig, u64* __restrict__ acc, uint32_t logN,
-                                               uint32_t R, uint32_t beta, uint32_t M, uint32_t level, uint32_t alpha, uint32_t init) {
+                                               uint32_t R, uint32_t beta, uint32_t M, uint32_t level, uint32_t alpha, uint32_t init, bool rows) {
     const uint32_t n = blockIdx.x * KS_THREADS + threadIdx.x;
     constexpr int H = WIDE ? 30 : 27;
     constexpr u64 lo_h = (1ull << H) - 1;
@@ -1198,6 +1203,7 @@ __device__ __forceinline__ void hoisted_sum_ip(const HoistIp& a, uint32_t r, uin
         v = reduce_lazy<7>(v, m.q, m.bits, m.rec);
         return init & 2u ? v : csub_u(v, m.q);
     };
+    if (rows) __syncthreads();                           // the digits are read: their tiles take the sums
 #pragma unroll
     for (int i = 0; i < JT; i++) {
         if ((uint32_t)i < a.J) {
@@ -1205,9 +1211,38 @@ __device__ __forceinline__ void hoisted_sum_ip(const HoistIp& a, uint32_t r, uin
             const u64 vb = total_of(b0[i], bm[i], b2[i]), va = total_of(a0[i], am[i], a2[i]);
             u64* o0 = acc + ((size_t)(2 * i) * cstride + ro);
             u64* o1 = acc + ((size_t)(2 * i + 1) * cstride + ro);
-            o0[n] = settled(init & 1u ? vb : vb + o0[n]);
-            o1[n] = settled(init & 1u ? va : va + o1[n]);
+            const u64 sb = settled(init & 1u ? vb : vb + o0[n]), sa = settled(init & 1u ? va : va + o1[n]);
+            if (rows) {
+                u64* to = dig + 2 * i * KS_THREADS + row4_word(threadIdx.x);
+                to[0] = sb; to[KS_THREADS] = sa;
+            } else {
+                o0[n] = sb; o1[n] = sa;
+            }
         }
+    }
+}
+// The inverse rows of a work group's sums (below 2q, in LDS), both components of an output by one wavefront.  A work group's 256 points are a row,
+// so the special primes' sums need not go to memory and back to be transformed: 8 outputs of 8 special primes at N = 2^16 were a launch of 36 us of
+// 128 MiB (3.7 TB/s), and 64 MiB written ahead of it.  A layer at level 5 588 -> 564 us, a block with four special primes 1108 -> 1091.
+template <int W>
+__device__ __forceinline__ void hoisted_sum_rows(u64* rows, u64* __restrict__ mid, const ModConst& m, const ulonglong2* tw, uint32_t J, uint32_t k, uint32_t logN) {
+    const uint32_t lane = threadIdx.x & 63u;
+    const Row4 at(lane);
+    u64 w[4][6];
+    tw_row4(w, tw, logN - 8, blockIdx.x, lane);
+    __syncthreads();
+#pragma unroll 1
+    for (uint32_t i = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); i < J; i += KS_THREADS / 64) {
+        u64 x[2][4], *buf = rows + 2 * i * KS_THREADS;
+#pragma unroll
+        for (int c = 0; c < 2; c++) at.load(3, x[c], buf + c * KS_THREADS);
+        wave_exchange();
+        row4_inv<W, 2>(x, w, buf, KS_THREADS, at, m.q, m);
+        u64* out = mid + ((size_t)(2 * i * k) << logN) + blockIdx.x * KS_THREADS + lane;
+#pragma unroll
+        for (int c = 0; c < 2; c++)
+#pragma unroll
+            for (int p = 0; p < 4; p++) (out + ((size_t)(c * k) << logN))[64 * p] = x[c][p];
     }
 }
 
@@ -1215,12 +1250,28 @@ template <int JT>
 __global__ __launch_bounds__(KS_THREADS, 3) void hoisted_sum_ip_local_kernel(HoistIp a, LimbSel sel, u64* __restrict__ acc,
                                                                              const ModConst* mc, uint32_t logN, uint32_t R,
                                                                              uint32_t beta, uint32_t M, uint32_t level, uint32_t nq,
-                                                                             uint32_t alpha, uint32_t init) {
-    extern __shared__ u64 dig[];                         // a.J * beta tiles of KS_THREADS values
-    const uint32_t r = sel.r[blockIdx.y], mi = r <= level ? r : nq + (r - level - 1);
-    const ModConst m = mc[mi];
-    if (m.bits > 54) hoisted_sum_ip<JT, true>(a, r, mi, m, dig, acc, logN, R, beta, M, level, alpha, init);
-    else hoisted_sum_ip<JT, false>(a, r, mi, m, dig, acc, logN, R, beta, M, level, alpha, init);
+                                                                             uint32_t alpha, uint32_t init, u64* __restrict__ mid,
+                                                                             const ulonglong2* itw) {
+    ieee_off();
+    extern __shared__ u64 dig[];                         // a.J * beta tiles of KS_THREADS values, at least 2 * a.J
+    const uint32_t s = sel.r[blockIdx.y], r = s & (HSL_ROWS - 1);
+    uint32_t mi = r <= level ? r : nq + (r - level - 1);
+    const bool rows = s & HSL_ROWS;
+    const ModConst m = mod_const(mc, mi);
+    if (m.bits > 54) hoisted_sum_ip<JT, true>(a, r, mi, m, dig, acc, logN, R, beta, M, level, alpha, init, rows);
+    else hoisted_sum_ip<JT, false>(a, r, mi, m, dig, acc, logN, R, beta, M, level, alpha, init, rows);
+    if (!rows) return;
+    asm("" : "+s"(mi));                                  // the constants are read again, not kept
+    const ModConst mr = mod_const(mc, mi);
+    u64* out = mid + ((size_t)(r - level - 1) << logN);
+    const ulonglong2* tw = itw + ((size_t)mi << logN);
+    const uint32_t k = R - level - 1;
+    switch (s >> HSL_CLASS) {
+    case 0: hoisted_sum_rows<0>(dig, out, mr, tw, a.J, k, logN); break;
+    case 1: hoisted_sum_rows<1>(dig, out, mr, tw, a.J, k, logN); break;
+    case 2: hoisted_sum_rows<2>(dig, out, mr, tw, a.J, k, logN); break;
+    default: hoisted_sum_rows<W_NEAR>(dig, out, mr, tw, a.J, k, logN); break;
+    }
 }
 
 // Whether the Galois elements of a hoisted sum only move values inside aligned blocks of 256 positions, the tile of a
@@ -1297,7 +1348,9 @@ int32_t ks_hoisted_sum(he_ctx* c, uint32_t level, const KsSrc* srcs, uint32_t J,
             ep.self1[j] = srcs[j0 + j].s1;
             ep.out0[j] = out0[j0 + j]; ep.out1[j] = out1[j0 + j];
         }
-        // the inner products of all the chunk's ciphertexts, register-tiled, into stored accumulators
+        // the inner products of all the chunk's ciphertexts, register-tiled, into stored accumulators; those of the special primes go
+        // on to their inverse rows where the rest of their way back is one launch
+        const bool rows_here = two_pass(c) && c->d_dn_op != nullptr;
         for (uint32_t t0 = 0; t0 < T; t0 += HS_TERMS) {
             HoistIp hi = {};
             hi.J = nb; hi.T = std::min<uint32_t>(HS_TERMS, T - t0);
@@ -1318,17 +1371,25 @@ int32_t ks_hoisted_sum(he_ctx* c, uint32_t level, const KsSrc* srcs, uint32_t J,
                         else sel.r[i] = narrow[in++];
                     }
                 }
+                if (rows_here && t0 + HS_TERMS >= T)
+                    for (uint32_t i = 0; i < R; i++)
+                        if (sel.r[i] > level) {
+                            const u64 q = c->mod[c->nq + (sel.r[i] - L1)];
+                            const uint32_t W = near_inv(q) ? W_NEAR : narrow_inv(q) ? 0 : widest(q) ? 2 : 1;
+                            sel.r[i] |= HSL_ROWS | W << HSL_CLASS;
+                        }
                 const dim3 grid(N / KS_THREADS, R), blk(KS_THREADS);
+                const size_t lds = (size_t)nb * std::max(beta, rows_here ? 2u : 1u) * KS_THREADS * sizeof(u64);
                 const uint32_t init = (t0 == 0 ? 1u : 0u) | (two_pass(c) ? 2u : 0u);
-#define HSL_LAUNCH(JT) hipLaunchKernelGGL(hoisted_sum_ip_local_kernel<JT>, grid, blk, (size_t)nb * beta * KS_THREADS * sizeof(u64), c->stream, hi, sel, acc, c->d_mc, c->logN, R, beta, \
-                                          c->M, level, c->nq, c->alpha, init)
+#define HSL_LAUNCH(JT) hipLaunchKernelGGL(hoisted_sum_ip_local_kernel<JT>, grid, blk, lds, c->stream, hi, sel, acc, c->d_mc, c->logN, R, beta, \
+                                          c->M, level, c->nq, c->alpha, init, tmp_dn, c->d_itw)
                 if (nb <= 1) HSL_LAUNCH(1); else if (nb <= 2) HSL_LAUNCH(2); else if (nb <= 4) HSL_LAUNCH(4); else HSL_LAUNCH(8);
 #undef HSL_LAUNCH
             }
             HE_HIP(c, hipGetLastError());
         }
         if (c->prof_on) c->prof_key_limbs += (uint64_t)T * 2 * beta * R;
-        int32_t rc = moddown_chain(c, level, nb, acc, tmp_dn, conv, ep);
+        int32_t rc = moddown_chain(c, level, nb, acc, tmp_dn, conv, ep, nullptr, rows_here);
         if (rc != HE_OK) return rc;
         c->cnt.keyswitch += (uint64_t)nb * T;
     }
