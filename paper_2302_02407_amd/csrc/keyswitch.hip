@@ -1016,7 +1016,7 @@ __global__ __launch_bounds__(KS_THREADS) void hoist_c0_sum_kernel(HoistC0 a, con
 // one raised-basis limb for all the ciphertexts and both components; per (term, digit) it loads the two key values
 // once and one digit value per ciphertext, and feeds 2*J multiply-accumulates.
 // acc [J][2][R][N] (as `settled` leaves it); bit 0 of init clear: the launch continues from its contents (more than HS_TERMS terms); bit 1:
-// two-launch rings.
+// two-launch rings; bit 2: the digits' rows are not transformed yet.
 #define HS_JOBS 8
 #define HS_TERMS 16
 struct HoistIp {
@@ -1048,16 +1048,17 @@ struct HoistIp {
 #define HSL_MAX_TILES 24      // J * beta digit tiles of 2 KiB: 48 KiB of LDS
 #define HSL_RING 2            // (term, digit) pairs whose key values are in registers or on their way
 // the raised-basis limbs one launch works on: blockIdx.y indexes this list.  HSL_ROWS: the sums are complete and their inverse rows, class W
-// (ntt_blocks.h) above HSL_CLASS bits, go to `mid`.
+// (ntt_blocks.h) two bits from HSL_INV on, go to `mid`; two bits from HSL_FWD on: the class of the digits' rows.
 #define HSL_ROWS 0x100u
-#define HSL_CLASS 9
+#define HSL_INV 9
+#define HSL_FWD 11
 struct LimbSel {
     uint32_t r[HE_MAX_MODULI];
 };
 template <int JT, bool WIDE>
 __device__ __forceinline__ void hoisted_sum_ip(const HoistIp& a, uint32_t r, uint32_t mi, const ModConst& m, u64* dig, u64* __restrict__ acc, uint32_t logN,
                                                uint32_t R, uint32_t beta, uint32_t M, uint32_t level, uint32_t alpha, uint32_t init, bool rows) {
-    const uint32_t n = blockIdx.x * KS_THREADS + threadIdx.x;
+    const uint32_t n = blockIdx.x * KS_THREADS + threadIdx.x, word = row4_word(threadIdx.x);
     constexpr int H = WIDE ? 30 : 27;
     constexpr u64 lo_h = (1ull << H) - 1;
     // products a middle sum takes: |d0| k1 + |d1| |k0| of each, below 2^63 together (at most 31, which the low sums take)
@@ -1068,10 +1069,15 @@ __device__ __forceinline__ void hoisted_sum_ip(const HoistIp& a, uint32_t r, uin
         const bool own_digit = r <= level && r / alpha == j;
         const size_t doff = own_digit ? ro : (size_t)(j * R + r) << logN;
         u64 in[JT];
+        if (init & 4u && !own_digit) {
 #pragma unroll
-        for (int i = 0; i < JT; i++) {
-            const uint32_t k = (uint32_t)i < a.J ? i : 0;
-            in[i] = ((own_digit ? a.own[k] : a.raised[k]) + doff)[n];
+            for (int i = 0; i < JT; i++) in[i] = dig[(j * a.J + ((uint32_t)i < a.J ? i : 0)) * KS_THREADS + word];
+        } else {
+#pragma unroll
+            for (int i = 0; i < JT; i++) {
+                const uint32_t k = (uint32_t)i < a.J ? i : 0;
+                in[i] = ((own_digit ? a.own[k] : a.raised[k]) + doff)[n];
+            }
         }
 #pragma unroll
         for (int i = 0; i < JT; i++) {
@@ -1082,7 +1088,7 @@ __device__ __forceinline__ void hoisted_sum_ip(const HoistIp& a, uint32_t r, uin
                 const int64_t c = (int64_t)(v > m.q >> 1 ? v - m.q : v), top = (c + (1 << 29)) >> 30;
                 lo = (uint32_t)(int32_t)(c - (top << 30)); hi = (uint32_t)(int32_t)top;
             }
-            if ((uint32_t)i < a.J) dig[(j * a.J + i) * KS_THREADS + threadIdx.x] = lo | (hi << 32);
+            if ((uint32_t)i < a.J) dig[(j * a.J + i) * KS_THREADS + word] = lo | (hi << 32);
         }
     }
     // per output and component: low sum, high sum, and bm = (middle sum) - low - high (at most 54 bits, modulo 2^64) or the
@@ -1122,7 +1128,7 @@ __device__ __forceinline__ void hoisted_sum_ip(const HoistIp& a, uint32_t r, uin
     // (t, j) = the pair whose digits are read next, lsrc = where this thread's value of term t sits in its tile
     uint32_t t = 0, j = 0;
     auto lsrc_of = [&](uint32_t term) {
-        return galois_src_ks(n, __builtin_amdgcn_readlane(g_lane, term < a.T ? term : 0), logN) & (KS_THREADS - 1);
+        return row4_word(galois_src_ks(n, __builtin_amdgcn_readlane(g_lane, term < a.T ? term : 0), logN) & (KS_THREADS - 1));
     };
     uint32_t lsrc = lsrc_of(0);
     auto read = [&](int p, u64 (&to)[PT]) {
@@ -1199,7 +1205,7 @@ __device__ __forceinline__ void hoisted_sum_ip(const HoistIp& a, uint32_t r, uin
     // rows), others canonical.  A launch that continues q-limbs finds them below 6q after the first, below 12q with its own sum, and leaves
     // them below 2q.
     auto settled = [&](u64 v) {
-        if (init == 3 && r <= level) return v;
+        if ((init & 3u) == 3 && r <= level) return v;
         v = reduce_lazy<7>(v, m.q, m.bits, m.rec);
         return init & 2u ? v : csub_u(v, m.q);
     };
@@ -1213,13 +1219,50 @@ __device__ __forceinline__ void hoisted_sum_ip(const HoistIp& a, uint32_t r, uin
             u64* o1 = acc + ((size_t)(2 * i + 1) * cstride + ro);
             const u64 sb = settled(init & 1u ? vb : vb + o0[n]), sa = settled(init & 1u ? va : va + o1[n]);
             if (rows) {
-                u64* to = dig + 2 * i * KS_THREADS + row4_word(threadIdx.x);
+                u64* to = dig + 2 * i * KS_THREADS + word;
                 to[0] = sb; to[KS_THREADS] = sa;
             } else {
                 o0[n] = sb; o1[n] = sa;
             }
         }
     }
+}
+// The rows of the digits' limb r, whose column passes are done, into their tiles (below 2q).  A row belongs to one work group, as the sums
+// below do, so the digits' row passes need no launch that reads and writes them: a layer of 8 outputs at level 5 with one digit 564 -> 557 us, a
+// block with two 1091 -> 1070.
+template <int W, int NX>
+__device__ __forceinline__ void hoisted_sum_digits(const HoistIp& a, uint32_t r, const ModConst& m, u64* dig, const ulonglong2* tw, uint32_t logN, uint32_t R,
+                                                   uint32_t beta, uint32_t own_j) {
+    const uint32_t lane = threadIdx.x & 63u, n = (own_j < beta ? beta - 1 : beta) * a.J;
+    const Row4 at(lane);
+    u64 w[4][6];
+    tw_row4(w, tw, logN - 8, blockIdx.x, lane);
+#pragma unroll 1
+    for (uint32_t i0 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); i0 < n; i0 += NX * (KS_THREADS / 64)) {
+        u64 x[NX][4];
+        uint32_t tile[2];
+#pragma unroll
+        for (int c = 0; c < NX; c++) {
+            const uint32_t i = i0 + c * (KS_THREADS / 64) < n ? i0 + c * (KS_THREADS / 64) : i0, jj = i / a.J, j = jj + (jj >= own_j);
+            tile[c] = i + (j - jj) * a.J;
+            const u64* row = a.raised[i - jj * a.J] + ((size_t)(j * R + r) << logN) + blockIdx.x * KS_THREADS;
+#pragma unroll
+            for (int k = 0; k < 4; k++) x[c][k] = __builtin_nontemporal_load(&row[lane + 64 * k]);
+        }
+        u64* buf = dig + tile[0] * KS_THREADS;
+        const uint32_t stride = NX == 2 ? (tile[1] - tile[0]) * KS_THREADS : 0;
+        SCHED_FENCE();
+        row4_fwd<W, NX>(x, w, buf, stride, at, m.q);
+        wave_exchange();
+#pragma unroll
+        for (int c = 0; c < NX; c++) {
+#pragma unroll
+            for (int k = 0; k < 4; k++)
+                x[c][k] = W == 0 || W == W_NEAR ? fwd_lazy<W>(x[c][k], m) : reduce_min<7>(x[c][k], m.q, m.bits, m.rec);
+            at.store(3, x[c], buf + c * stride);
+        }
+    }
+    __syncthreads();
 }
 // The inverse rows of a work group's sums (below 2q, in LDS), both components of an output by one wavefront.  A work group's 256 points are a row,
 // so the special primes' sums need not go to memory and back to be transformed: 8 outputs of 8 special primes at N = 2^16 were a launch of 36 us of
@@ -1251,13 +1294,24 @@ __global__ __launch_bounds__(KS_THREADS, 3) void hoisted_sum_ip_local_kernel(Hoi
                                                                              const ModConst* mc, uint32_t logN, uint32_t R,
                                                                              uint32_t beta, uint32_t M, uint32_t level, uint32_t nq,
                                                                              uint32_t alpha, uint32_t init, u64* __restrict__ mid,
-                                                                             const ulonglong2* itw) {
+                                                                             const ulonglong2* ftw, const ulonglong2* itw) {
     ieee_off();
     extern __shared__ u64 dig[];                         // a.J * beta tiles of KS_THREADS values, at least 2 * a.J
     const uint32_t s = sel.r[blockIdx.y], r = s & (HSL_ROWS - 1);
     uint32_t mi = r <= level ? r : nq + (r - level - 1);
     const bool rows = s & HSL_ROWS;
     const ModConst m = mod_const(mc, mi);
+    if (init & 4u) {
+        constexpr int NX = JT > 4 ? 2 : 1;
+        const ulonglong2* tw = ftw + ((size_t)mi << logN);
+        const uint32_t own_j = r <= level ? r / alpha : beta;
+        switch (s >> HSL_FWD) {
+        case 0: hoisted_sum_digits<0, NX>(a, r, m, dig, tw, logN, R, beta, own_j); break;
+        case 1: hoisted_sum_digits<1, NX>(a, r, m, dig, tw, logN, R, beta, own_j); break;
+        case 2: hoisted_sum_digits<2, NX>(a, r, m, dig, tw, logN, R, beta, own_j); break;
+        default: hoisted_sum_digits<W_NEAR, NX>(a, r, m, dig, tw, logN, R, beta, own_j); break;
+        }
+    }
     if (m.bits > 54) hoisted_sum_ip<JT, true>(a, r, mi, m, dig, acc, logN, R, beta, M, level, alpha, init, rows);
     else hoisted_sum_ip<JT, false>(a, r, mi, m, dig, acc, logN, R, beta, M, level, alpha, init, rows);
     if (!rows) return;
@@ -1266,7 +1320,7 @@ __global__ __launch_bounds__(KS_THREADS, 3) void hoisted_sum_ip_local_kernel(Hoi
     u64* out = mid + ((size_t)(r - level - 1) << logN);
     const ulonglong2* tw = itw + ((size_t)mi << logN);
     const uint32_t k = R - level - 1;
-    switch (s >> HSL_CLASS) {
+    switch (s >> HSL_INV & 3u) {
     case 0: hoisted_sum_rows<0>(dig, out, mr, tw, a.J, k, logN); break;
     case 1: hoisted_sum_rows<1>(dig, out, mr, tw, a.J, k, logN); break;
     case 2: hoisted_sum_rows<2>(dig, out, mr, tw, a.J, k, logN); break;
@@ -1325,9 +1379,10 @@ int32_t ks_hoisted_sum(he_ctx* c, uint32_t level, const KsSrc* srcs, uint32_t J,
     for (uint32_t j0 = 0; j0 < J; j0 += jb) {
         const uint32_t nb = std::min(jb, J - j0);
         for (uint32_t t0 = 0; t0 < nb; t0 += cb) {
-            int32_t rc = modup_batch(c, srcs + j0 + t0, std::min(cb, nb - t0), level, raised + (size_t)t0 * beta * R * N, tmp_up);
+            int32_t rc = modup_batch(c, srcs + j0 + t0, std::min(cb, nb - t0), level, raised + (size_t)t0 * beta * R * N, tmp_up, !two_pass(c));
             if (rc != HE_OK) return rc;
         }
+        if (modup_by_columns(c, level)) c->cnt.ntt_limbs += (uint64_t)nb * (beta * R - L1);      // the digits, whose rows come with the products
         HoistC0 hc = {};
         hc.T = std::min<uint32_t>(T, HE_MAX_KS_JOBS);
         for (uint32_t j = 0; j < nb; j++) { hc.c0[j] = srcs[j0 + j].c0; hc.s0[j] = s0 + (size_t)j * L1 * N; }
@@ -1371,18 +1426,18 @@ int32_t ks_hoisted_sum(he_ctx* c, uint32_t level, const KsSrc* srcs, uint32_t J,
                         else sel.r[i] = narrow[in++];
                     }
                 }
-                if (rows_here && t0 + HS_TERMS >= T)
-                    for (uint32_t i = 0; i < R; i++)
-                        if (sel.r[i] > level) {
-                            const u64 q = c->mod[c->nq + (sel.r[i] - L1)];
-                            const uint32_t W = near_inv(q) ? W_NEAR : narrow_inv(q) ? 0 : widest(q) ? 2 : 1;
-                            sel.r[i] |= HSL_ROWS | W << HSL_CLASS;
-                        }
+                for (uint32_t i = 0; i < R; i++) {
+                    const bool special = sel.r[i] > level;
+                    const u64 q = c->mod[special ? c->nq + (sel.r[i] - L1) : sel.r[i]];
+                    const uint32_t wide = widest(q) ? 2 : 1, inv = near_inv(q) ? W_NEAR : narrow_inv(q) ? 0 : wide;
+                    const uint32_t fwd = near_fwd(q, c->logN) ? W_NEAR : narrow_fwd(q) ? 0 : wide;
+                    sel.r[i] |= (special && rows_here && t0 + HS_TERMS >= T ? HSL_ROWS : 0) | inv << HSL_INV | fwd << HSL_FWD;
+                }
                 const dim3 grid(N / KS_THREADS, R), blk(KS_THREADS);
                 const size_t lds = (size_t)nb * std::max(beta, rows_here ? 2u : 1u) * KS_THREADS * sizeof(u64);
-                const uint32_t init = (t0 == 0 ? 1u : 0u) | (two_pass(c) ? 2u : 0u);
+                const uint32_t init = (t0 == 0 ? 1u : 0u) | (two_pass(c) ? 6u : 0u);
 #define HSL_LAUNCH(JT) hipLaunchKernelGGL(hoisted_sum_ip_local_kernel<JT>, grid, blk, lds, c->stream, hi, sel, acc, c->d_mc, c->logN, R, beta, \
-                                          c->M, level, c->nq, c->alpha, init, tmp_dn, c->d_itw)
+                                          c->M, level, c->nq, c->alpha, init, tmp_dn, c->d_tw, c->d_itw)
                 if (nb <= 1) HSL_LAUNCH(1); else if (nb <= 2) HSL_LAUNCH(2); else if (nb <= 4) HSL_LAUNCH(4); else HSL_LAUNCH(8);
 #undef HSL_LAUNCH
             }
