@@ -5,6 +5,7 @@
 #include <algorithm>
 
 #include "modarith.h"
+#include "ntt_blocks.h"
 
 #define CV_THREADS 256
 #define CV_MAX_TAPS 49
@@ -14,6 +15,13 @@
 // Sums of products of a few ciphertexts with many plaintexts: acc_o = sum_i ct_i * pt_(o,i) for o < n_out, both components.
 #define MAC_MAX_IN 16
 #define MAC_MAX_PT 144
+// The second components of the outputs in `mask` also go through their inverse rows, to out [number of them][CL][N].
+struct MacRows {
+    u64* out;                     // null: none
+    uint32_t mask;
+    const ulonglong2* itw;
+    u64 wide_inv, widest, near_inv;      // bit per modulus (narrow_inv, widest, near_inv)
+};
 struct MacMany {
     const u64* ct[MAC_MAX_IN];                           // [2][CL][N]
     const u64* pt[MAC_MAX_PT];                           // [o * n_in + i], [CL][N]
@@ -21,7 +29,32 @@ struct MacMany {
     uint32_t n_in, n_out, init;                          // init = 0: continues from acc's current (canonical) contents
     uint32_t c1_tap;                                     // 0xFFFFFFFF: every ct has both components; else only this one has a
                                                          // second component (the others are [CL][N])
+    MacRows rows;
 };
+
+// The inverse rows of the `held` sums in LDS, one at a time by a wavefront; sum i goes to out + i * stride.  What is rotated next starts with the
+// inverse rows of its second component, a work group's 256 points are a row, and reading plaintexts leaves the vector units idle: eight ciphertexts of
+// 13 limbs at N = 2^16, eight of nine sums rotated, were a launch of 34 us of 104 MiB besides.  That layer 458 -> 441 us, at 23 limbs 839 -> 814, 16
+// ciphertexts of 21 limbs of 32 channels 1139 -> 1125; two rows at a time by a wavefront (118 registers instead of 98) the same.  The dropped limb of a rescale taken along in the same way (both components of one limb, 32 KiB of LDS)
+// made layers between 0.7 % faster and 1.5 % slower: its few work groups end late.
+template <int W>
+__device__ __forceinline__ void mac_rows(u64* tiles, uint32_t held, u64* out, size_t stride, const ModConst& m, const ulonglong2* tw, uint32_t logN) {
+    const uint32_t lane = threadIdx.x & 63u;
+    const Row4 at(lane);
+    u64 w[4][6];
+    tw_row4(w, tw, logN - 8, blockIdx.x, lane);
+    out += blockIdx.x * CV_THREADS + lane;
+    __syncthreads();
+#pragma unroll 1
+    for (uint32_t i = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); i < held; i += CV_THREADS / 64) {
+        u64 x[1][4], *buf = tiles + i * CV_THREADS;
+        at.load(3, x[0], buf);
+        wave_exchange();
+        row4_inv<W, 1>(x, w, buf, CV_THREADS, at, m.q, m);
+#pragma unroll
+        for (int p = 0; p < 4; p++) (out + i * stride)[64 * p] = x[0][p];
+    }
+}
 
 // MulFilter&Sum of several outputs at once: a thread keeps one coefficient of both components of all NI ciphertexts in
 // registers and then reads the plaintexts of one output after the other, each byte of which is used once: bound by reading
@@ -37,10 +70,13 @@ struct MacMany {
 // ciphertext primes, followed by the special primes when the operands are key-switch inner products still over the raised
 // basis.  grid: (N/256, CL).
 #define MAC_RUN 8                                        // products of residues of 60 bits that a split sum takes (below 60 bits: 16)
-template <int NI, bool ONE>
+template <int NI, bool ONE, bool ROWS>
 __global__ __launch_bounds__(CV_THREADS) void mac_many_kernel(MacMany a, const ModConst* mc, uint32_t logN, uint32_t CL, uint32_t level, uint32_t nq) {
-    const uint32_t n = blockIdx.x * CV_THREADS + threadIdx.x, limb = blockIdx.y;
-    const ModConst m = mc[limb <= level ? limb : nq + (limb - level - 1)];
+    if (ROWS) ieee_off();
+    extern __shared__ u64 tiles[];                       // ROWS: the sums that go through their inverse rows
+    const uint32_t n = blockIdx.x * CV_THREADS + threadIdx.x, limb = blockIdx.y, mi = limb <= level ? limb : nq + (limb - level - 1);
+    const ModConst m = ROWS ? mod_const(mc, mi) : mc[mi];
+    uint32_t held = 0;
     const size_t o0 = ((size_t)limb << logN) + n, o1 = ((size_t)(limb + CL) << logN) + n;
     constexpr int N1 = ONE ? 1 : NI;
     u64 c0[NI], c1[N1], next[NI];
@@ -81,8 +117,22 @@ __global__ __launch_bounds__(CV_THREADS) void mac_many_kernel(MacMany a, const M
         }
         if (ONE) split_mac(s1, c1[0], p1);
         static_assert(NI <= 2 * MAC_RUN, "totals stay below q + 12q");
-        a.acc[o][o0] = reduce_full<7>(r0 + split_reduce(s0, m), m.q, m.bits, m.rec);
-        a.acc[o][o1] = reduce_full<7>(r1 + split_reduce(s1, m), m.q, m.bits, m.rec);
+        r0 = reduce_full<7>(r0 + split_reduce(s0, m), m.q, m.bits, m.rec);
+        r1 = reduce_full<7>(r1 + split_reduce(s1, m), m.q, m.bits, m.rec);
+        a.acc[o][o0] = r0;
+        a.acc[o][o1] = r1;
+        if (ROWS) {
+            if (a.rows.mask >> o & 1u) tiles[held++ * CV_THREADS + row4_word(threadIdx.x)] = r1;
+        }
+    }
+    if constexpr (ROWS) {
+        u64* out = a.rows.out + ((size_t)limb << logN);
+        const size_t stride = (size_t)CL << logN;
+        const ulonglong2* tw = a.rows.itw + ((size_t)mi << logN);
+        if (a.rows.near_inv >> mi & 1u) mac_rows<W_NEAR>(tiles, held, out, stride, m, tw, logN);
+        else if (!(a.rows.wide_inv >> mi & 1u)) mac_rows<0>(tiles, held, out, stride, m, tw, logN);
+        else if (!(a.rows.widest >> mi & 1u)) mac_rows<1>(tiles, held, out, stride, m, tw, logN);
+        else mac_rows<2>(tiles, held, out, stride, m, tw, logN);
     }
 }
 
@@ -94,14 +144,28 @@ static void launch_mac_many_of(he_ctx* ctx, const MacMany& a, uint32_t CL, uint3
         const dim3 grid(ctx->N / CV_THREADS, CL), block(CV_THREADS);
         if constexpr (NI <= MAC_MAX_ONE) {
             if (a.c1_tap != 0xFFFFFFFFu) {
-                hipLaunchKernelGGL((mac_many_kernel<NI, true>), grid, block, 0, ctx->stream, a, ctx->d_mc, ctx->logN, CL, level, ctx->nq);
+                hipLaunchKernelGGL((mac_many_kernel<NI, true, false>), grid, block, 0, ctx->stream, a, ctx->d_mc, ctx->logN, CL, level, ctx->nq);
                 return;
             }
         }
-        hipLaunchKernelGGL((mac_many_kernel<NI, false>), grid, block, 0, ctx->stream, a, ctx->d_mc, ctx->logN, CL, level, ctx->nq);
+        if (a.rows.out) {
+            const uint32_t held = (uint32_t)__builtin_popcount(a.rows.mask);
+            hipLaunchKernelGGL((mac_many_kernel<NI, false, true>), grid, block, held * CV_THREADS * sizeof(u64), ctx->stream, a, ctx->d_mc, ctx->logN, CL, level, ctx->nq);
+            return;
+        }
+        hipLaunchKernelGGL((mac_many_kernel<NI, false, false>), grid, block, 0, ctx->stream, a, ctx->d_mc, ctx->logN, CL, level, ctx->nq);
     }
 }
 static void launch_mac_many(he_ctx* ctx, const MacMany& a, uint32_t CL, uint32_t level) { launch_mac_many_of<MAC_MAX_IN>(ctx, a, CL, level); }
+static MacRows mac_rows_of(const he_ctx* ctx, u64* out, uint32_t mask) {
+    MacRows r = {out, mask, ctx->d_itw, 0, 0, 0};
+    for (uint32_t i = 0; i < ctx->M; i++) {
+        r.wide_inv |= (u64)!narrow_inv(ctx->mod[i]) << i;
+        r.widest |= (u64)widest(ctx->mod[i]) << i;
+        r.near_inv |= (u64)near_inv(ctx->mod[i]) << i;
+    }
+    return r;
+}
 // index of plaintext (o, i) in MacMany::pt for n_in ciphertexts
 static uint32_t mac_pt_index(uint32_t n_in, uint32_t o, uint32_t i) { return o * n_in + i; }
 
@@ -415,9 +479,12 @@ extern "C" int32_t he_conv2d(he_ctx* ctx, const he_conv_plan* plan, const uint64
 // MulFilter&Sum_ci: for every tap the sum over the inputs of input x inversely rotated filter, RA_IN_PER_LAUNCH inputs and 9
 // taps per launch.  pt(i, t): plaintext of input i and tap t; acc(t): accumulator of tap t.
 #define RA_IN_PER_LAUNCH 16
-template <class Ct, class Pt, class Acc>
-static int32_t ra_mac(he_ctx* ctx, uint32_t n_in, uint32_t taps, uint32_t level, bool fresh, Ct&& ct, Pt&& pt, Acc&& acc) {
-    for (uint32_t t0 = 0; t0 < taps; t0 += 9)
+// rows [taps with rot(t)][level+1][N]: receives the inverse rows of those taps' second components (null: not wanted).
+template <class Ct, class Pt, class Acc, class Rot>
+static int32_t ra_mac(he_ctx* ctx, uint32_t n_in, uint32_t taps, uint32_t level, bool fresh, Ct&& ct, Pt&& pt, Acc&& acc, u64* rows, Rot&& rot) {
+    for (uint32_t t0 = 0; t0 < taps; t0 += 9) {
+        uint32_t mask = 0;
+        for (uint32_t t = t0; t < std::min(t0 + 9, taps); t++) mask |= (uint32_t)rot(t) << (t - t0);
         for (uint32_t i0 = 0; i0 < n_in; i0 += RA_IN_PER_LAUNCH) {
             MacMany a = {};
             a.n_out = std::min<uint32_t>(9, taps - t0);
@@ -428,9 +495,12 @@ static int32_t ra_mac(he_ctx* ctx, uint32_t n_in, uint32_t taps, uint32_t level,
                 a.ct[i] = ct(i0 + i);
                 for (uint32_t t = 0; t < a.n_out; t++) a.pt[mac_pt_index(a.n_in, t, i)] = pt(i0 + i, t0 + t);
             }
+            if (rows && mask && i0 + RA_IN_PER_LAUNCH >= n_in) a.rows = mac_rows_of(ctx, rows, mask);
             launch_mac_many(ctx, a, level + 1, level);
             HE_HIP(ctx, hipGetLastError());
         }
+        if (rows) rows += (size_t)__builtin_popcount(mask) * (level + 1) * ctx->N;
+    }
     return HE_OK;
 }
 
@@ -453,15 +523,20 @@ __global__ __launch_bounds__(CV_THREADS) void sum_cts_kernel(SumList l, u64* out
 // Slide_1 & Sum_f (Algorithm 2): total = sum_t Rot(term_t) over ciphertexts at `level`, term t rotated by the Galois
 // element g[t] with key[t] (g = 1: added as it is).  deferred = false: one complete rotation per term, then
 // additions; deferred = true: one ModDown for the whole sum.  `total` may alias term 0 only when !deferred.
-// ws: slide1_sum_ws_elems elements.
+// ws: slide1_sum_ws_elems elements.  src_rows: ws is the start of the workspace and slide1_src_rows holds the inverse rows of the rotated
+// terms' second components.
 static size_t slide1_sum_ws_elems(const he_ctx* ctx, uint32_t level, uint32_t n_rot, bool deferred) {
     if (n_rot == 0) return 0;
     if (deferred) return ks_rotate_sum_ws_elems(ctx, level, n_rot);
     return ks_engine_ws_elems(ctx, level, n_rot, n_rot) + (size_t)n_rot * 2 * (level + 1) * ctx->N;
 }
 
+static u64* slide1_src_rows(const he_ctx* ctx, uint32_t level, uint32_t n_rot, bool deferred) {
+    if (n_rot == 0) return nullptr;
+    return deferred ? ks_rotate_sum_src_rows(ctx, level, n_rot) : ks_engine_src_rows(ctx, level, n_rot, n_rot);
+}
 static int32_t slide1_sum(he_ctx* ctx, uint32_t level, const u64* const* cts, const uint32_t* g, const u64* const* key, uint32_t n,
-                          bool deferred, u64* total, u64* ws) {
+                          bool deferred, u64* total, u64* ws, bool src_rows = false) {
     const uint32_t N = ctx->N, L1 = level + 1;
     const size_t ct_e = (size_t)2 * L1 * N;
     uint32_t n_rot = 0;
@@ -469,7 +544,7 @@ static int32_t slide1_sum(he_ctx* ctx, uint32_t level, const u64* const* cts, co
     if (deferred && n_rot) {
         std::vector<KsSumTerm> terms(n);
         for (uint32_t t = 0; t < n; t++) terms[t] = {cts[t], cts[t] + (size_t)L1 * N, g[t], key[t]};
-        return ks_rotate_sum_deferred(ctx, level, terms.data(), n, total, total + (size_t)L1 * N, ws);
+        return ks_rotate_sum_deferred(ctx, level, terms.data(), n, total, total + (size_t)L1 * N, ws, src_rows);
     }
     SumList sl;
     sl.n = 0;
@@ -484,7 +559,7 @@ static int32_t slide1_sum(he_ctx* ctx, uint32_t level, const u64* const* cts, co
             srcs.push_back({cts[t], cts[t] + (size_t)L1 * N, nullptr, nullptr});
             sl.in[sl.n++] = out;
         }
-        int32_t rc = ks_engine(ctx, level, srcs.data(), (uint32_t)srcs.size(), jobs.data(), (uint32_t)jobs.size());
+        int32_t rc = ks_engine(ctx, level, srcs.data(), (uint32_t)srcs.size(), jobs.data(), (uint32_t)jobs.size(), src_rows);
         if (rc != HE_OK) return rc;
     } else {
         for (uint32_t t = 0; t < n; t++) sl.in[sl.n++] = cts[t];
@@ -582,10 +657,11 @@ extern "C" int32_t he_raconv(he_ctx* ctx, const he_raconv_plan* plan, const uint
     u64* total = deferred ? acc + (size_t)taps * ct_e : acc;   // not deferred: the sum overwrites the first accumulator
                                                                // (each element is read before it is written)
     // MulFilter&Sum_ci: per tap, the sum over all inputs of input x inversely rotated filter
+    u64* rows = slide1_src_rows(ctx, level, n_rot, deferred);
     {
         rc = ra_mac(ctx, n_in, taps, level, true, [&](uint32_t i) { return (const u64*)h_d_ct_in[i]; },
                     [&](uint32_t i, uint32_t t) { return (const u64*)plan->h_d_weights[(size_t)i * taps + t]; },
-                    [&](uint32_t t) { return acc + (size_t)t * ct_e; });
+                    [&](uint32_t t) { return acc + (size_t)t * ct_e; }, rows, [&](uint32_t t) { return tap_g[t] != 1; });
         if (rc != HE_OK) return rc;
         ctx->cnt.mac += (uint64_t)taps * n_in;
     }
@@ -594,7 +670,7 @@ extern "C" int32_t he_raconv(he_ctx* ctx, const he_raconv_plan* plan, const uint
     if (taps > 1) {
         std::vector<const u64*> cts(taps);
         for (uint32_t t = 0; t < taps; t++) cts[t] = acc + (size_t)t * ct_e;
-        rc = slide1_sum(ctx, level, cts.data(), tap_g.data(), tap_key.data(), taps, deferred, total, ctx->d_ws);
+        rc = slide1_sum(ctx, level, cts.data(), tap_g.data(), tap_key.data(), taps, deferred, total, ctx->d_ws, rows != nullptr);
         if (rc != HE_OK) return rc;
         rin = total;
     }
@@ -730,6 +806,7 @@ extern "C" int32_t he_ca_ra_block(he_ctx* ctx, const he_block_plan* plan, const 
             if (rc != HE_OK) return rc;
         }
     }
+    u64* slide_rows = n_ca == 1 ? slide1_src_rows(ctx, lo, n_rot, deferred) : nullptr;      // (its place serves one output at a time)
     for (uint32_t j0 = 0; j0 < n_ra; j0 += G) {
         const uint32_t g = std::min(G, n_ra - j0);
         // MulFilter&Sum_f over every input and tap, for the g intermediates of this group
@@ -826,7 +903,8 @@ extern "C" int32_t he_ca_ra_block(he_ctx* ctx, const he_block_plan* plan, const 
             for (uint32_t l = 0; l < n_ca; l++) {
                 rc = ra_mac(ctx, g, taps, lo, j0 == 0, [&](uint32_t i) { return ct3 + (size_t)i * ct_lo; },
                             [&](uint32_t i, uint32_t t) { return (const u64*)plan->h_d_w_ra[((size_t)l * n_ra + j0 + i) * taps + t]; },
-                            [&](uint32_t t) { return ct4 + ((size_t)l * taps + t) * ct_lo; });
+                            [&](uint32_t t) { return ct4 + ((size_t)l * taps + t) * ct_lo; }, j0 + g == n_ra ? slide_rows : nullptr,
+                            [&](uint32_t t) { return tap_g[t] != 1; });
                 if (rc != HE_OK) return rc;
             }
             ctx->cnt.mac += (uint64_t)g * n_ca * taps;
@@ -839,7 +917,7 @@ extern "C" int32_t he_ca_ra_block(he_ctx* ctx, const he_block_plan* plan, const 
         const u64* rin = cts[0];
         if (taps > 1) {
             u64* tot = deferred ? total : (u64*)cts[0];
-            rc = slide1_sum(ctx, lo, cts.data(), tap_g.data(), tap_key.data(), taps, deferred, tot, ctx->d_ws);
+            rc = slide1_sum(ctx, lo, cts.data(), tap_g.data(), tap_key.data(), taps, deferred, tot, ctx->d_ws, slide_rows != nullptr);
             if (rc != HE_OK) return rc;
             rin = tot;
         }

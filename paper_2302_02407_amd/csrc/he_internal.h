@@ -315,7 +315,11 @@ struct KsJob {
     uint32_t add_self;   // out0 += src.s0, out1 += src.s1 (rotate-and-sum step, relinearisation)
 };
 // Runs every job: one ModUp per source, then inner product + ModDown per job, batched.
-int32_t ks_engine(he_ctx* ctx, uint32_t level, const KsSrc* srcs, uint32_t n_src, const KsJob* jobs, uint32_t n_jobs);
+// src_rows: ks_engine_src_rows holds the sources' inverse rows already.
+int32_t ks_engine(he_ctx* ctx, uint32_t level, const KsSrc* srcs, uint32_t n_src, const KsJob* jobs, uint32_t n_jobs, bool src_rows = false);
+// Where the inverse rows of the sources [n_src][level+1][N] go (in a workspace that is large enough), if the engine can start from them: its
+// conversion does the columns, and it raises all sources at once.  Null otherwise.
+u64* ks_engine_src_rows(const he_ctx* ctx, uint32_t level, uint32_t n_src, uint32_t n_jobs);
 size_t ks_engine_ws_elems(const he_ctx* c, uint32_t level, uint32_t n_src, uint32_t n_jobs);
 // Sum of rotations with one ModDown for the whole sum.  Terms with g == 1 are added as they are (evk unused).
 #define HE_MAX_SUM_TERMS 49
@@ -326,7 +330,9 @@ struct KsSumTerm {
     const u64* evk;
 };
 size_t ks_rotate_sum_ws_elems(const he_ctx* c, uint32_t level, uint32_t n_rot);
-int32_t ks_rotate_sum_deferred(he_ctx* c, uint32_t level, const KsSumTerm* terms, uint32_t n_terms, u64* out0, u64* out1, u64* ws);
+int32_t ks_rotate_sum_deferred(he_ctx* c, uint32_t level, const KsSumTerm* terms, uint32_t n_terms, u64* out0, u64* out1, u64* ws, bool src_rows = false);
+// The same for a sum of n_rot rotations of different ciphertexts, whose ws is the start of the workspace.
+u64* ks_rotate_sum_src_rows(const he_ctx* c, uint32_t level, uint32_t n_rot);
 // sum over T shared (Galois element, key) terms of the rotations of each of J ciphertexts, one ModUp and one ModDown per
 // ciphertext; srcs[j] = {c0_j, c1_j, addend0_j or null, addend1_j or null} (keyswitch.hip)
 size_t ks_hoisted_sum_ws_elems(const he_ctx* c, uint32_t level, uint32_t J, uint32_t T);

@@ -468,8 +468,8 @@ static bool modup_by_columns(const he_ctx* c, uint32_t level) {
 }
 
 // ModUp of `cb` sources at once.  raised [cb][beta][R][N] (own limbs left unwritten), tmp [cb][L1][N].  rows = false: the last
-// pass of the digits' transforms, their rows, is left to launch_ks_rows.
-static int32_t modup_batch(he_ctx* c, const KsSrc* srcs, uint32_t cb, uint32_t level, u64* raised, u64* tmp, bool rows = true) {
+// pass of the digits' transforms, their rows, is left to launch_ks_rows.  src_rows: tmp holds the sources' inverse rows (modup_by_columns only).
+static int32_t modup_batch(he_ctx* c, const KsSrc* srcs, uint32_t cb, uint32_t level, u64* raised, u64* tmp, bool rows = true, bool src_rows = false) {
     const uint32_t N = c->N, L1 = level + 1, R = L1 + c->np, beta = num_digits(c, level), al = c->alpha;
     if (small_ring_path(c, level)) return sr_modup(c, srcs, cb, level, raised);   // one launch: every output limb start to finish
     // coefficient form of all limbs, each pre-multiplied by N^-1 * (Q_j/q_i)^-1
@@ -481,7 +481,8 @@ static int32_t modup_batch(he_ctx* c, const KsSrc* srcs, uint32_t cb, uint32_t l
     }
     const bool cc_on = modup_by_columns(c, level);
     c->cnt.modup += cb;
-    {
+    if (src_rows) c->cnt.intt_limbs += (uint64_t)cb * L1;
+    else {
         std::vector<uint32_t> mods(cb * L1);
         std::vector<uint8_t> seg(cb * L1);
         std::vector<uint16_t> lim(cb * L1);
@@ -751,7 +752,13 @@ static int32_t inner_moddown_batch(he_ctx* c, uint32_t level, const KsSrc* srcs,
     return HE_OK;
 }
 
-int32_t ks_engine(he_ctx* c, uint32_t level, const KsSrc* srcs, uint32_t n_src, const KsJob* jobs, uint32_t n_jobs) {
+u64* ks_engine_src_rows(const he_ctx* c, uint32_t level, uint32_t n_src, uint32_t n_jobs) {
+    uint32_t cb, jb;
+    engine_shape(c, level, n_src, n_jobs, cb, jb);
+    return two_pass(c) && modup_by_columns(c, level) && n_src <= cb ? c->d_ws + ks_engine_ws(c, level, cb, jb).tmp_up : nullptr;
+}
+
+int32_t ks_engine(he_ctx* c, uint32_t level, const KsSrc* srcs, uint32_t n_src, const KsJob* jobs, uint32_t n_jobs, bool src_rows) {
     if (n_jobs == 0) return HE_OK;
     const uint32_t N = c->N, R = level + 1 + c->np, beta = num_digits(c, level);
     if (2 * c->np > HE_MAX_MODULI) return he_fail(c, HE_ERR_BADARG, "key switch: more than %d special primes", HE_MAX_MODULI / 2);
@@ -780,7 +787,7 @@ int32_t ks_engine(he_ctx* c, uint32_t level, const KsSrc* srcs, uint32_t n_src, 
         bool rows_left = ks_rows_path(c, level);
         uint32_t uses[HE_MAX_SEGS] = {0};
         for (size_t i = pos; i < end; i++) rows_left = rows_left && ++uses[jobs[order[i]].src - s0] == 1;
-        rc = modup_batch(c, srcs + s0, ns, level, raised, tmp_up, !rows_left);
+        rc = modup_batch(c, srcs + s0, ns, level, raised, tmp_up, !rows_left, src_rows);
         if (rc != HE_OK) return rc;
         while (pos < end) {
             uint32_t J = (uint32_t)std::min<size_t>(jb, end - pos);
@@ -873,7 +880,11 @@ size_t ks_rotate_sum_ws_elems(const he_ctx* c, uint32_t level, uint32_t n_rot) {
     return e * c->N;
 }
 
-int32_t ks_rotate_sum_deferred(he_ctx* c, uint32_t level, const KsSumTerm* terms, uint32_t n_terms, u64* out0, u64* out1, u64* ws) {
+u64* ks_rotate_sum_src_rows(const he_ctx* c, uint32_t level, uint32_t n_rot) {
+    if (!two_pass(c) || !modup_by_columns(c, level) || n_rot > rot_sum_cb(c, level, n_rot)) return nullptr;
+    return c->d_ws + (size_t)n_rot * num_digits(c, level) * (level + 1 + c->np) * c->N;
+}
+int32_t ks_rotate_sum_deferred(he_ctx* c, uint32_t level, const KsSumTerm* terms, uint32_t n_terms, u64* out0, u64* out1, u64* ws, bool src_rows) {
     const uint32_t N = c->N, L1 = level + 1, k = c->np, R = L1 + k, beta = num_digits(c, level);
     if (n_terms == 0 || n_terms > HE_MAX_SUM_TERMS) return he_fail(c, HE_ERR_BADARG, "rotation sum: between 1 and %d terms", HE_MAX_SUM_TERMS);
     if (2 * k > HE_MAX_MODULI) return he_fail(c, HE_ERR_BADARG, "key switch: more than %d special primes", HE_MAX_MODULI / 2);
@@ -910,7 +921,7 @@ int32_t ks_rotate_sum_deferred(he_ctx* c, uint32_t level, const KsSumTerm* terms
     const uint32_t n_src = (uint32_t)srcs.size();
     const bool rows_left = fused && n_src == n_rot;     // digits that one term uses are transformed where it uses them (ksrows.hip)
     for (uint32_t t0 = 0; t0 < n_src; t0 += cb) {
-        int32_t rc = modup_batch(c, srcs.data() + t0, std::min(cb, n_src - t0), level, raised + (size_t)t0 * beta * R * N, tmp_up, !rows_left);
+        int32_t rc = modup_batch(c, srcs.data() + t0, std::min(cb, n_src - t0), level, raised + (size_t)t0 * beta * R * N, tmp_up, !rows_left, src_rows);
         if (rc != HE_OK) return rc;
     }
     // the rotated c0 parts and the plain terms, summed
