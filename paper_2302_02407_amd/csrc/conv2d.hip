@@ -405,6 +405,7 @@ extern "C" int32_t he_conv2d(he_ctx* ctx, const he_conv_plan* plan, const uint64
     // MulFilter&Sum_f for all outputs, then Rescale of all outputs.  The rotate-and-sum steps
     // ping-pong between the caller's output buffers and the temporaries; start so that the last
     // step lands in the output.
+    u64* raised = nullptr;                                 // small rings: the rescale raises what the first step rotates
     std::vector<u64*> cur(n_out), nxt(n_out);
     for (uint32_t o = 0; o < n_out; o++) {
         u64* a = (u64*)h_d_ct_out[o];
@@ -442,7 +443,8 @@ extern "C" int32_t he_conv2d(he_ctx* ctx, const he_conv_plan* plan, const uint64
         if (!deferred_taps) ctx->cnt.mac += (uint64_t)taps * n_out;
         std::vector<const u64*> accs(n_out);
         for (uint32_t o = 0; o < n_out; o++) accs[o] = acc + (size_t)o * ct_e;
-        rc = rescale_batch(ctx, accs.data(), cur.data(), n_out, level, rs_ws);
+        if (!ras_T && n_ras && sr_rescale_raises(ctx, level, n_out)) raised = ks_engine_raised(ctx, lo, n_out, n_out);
+        rc = raised ? sr_rescale_modup(ctx, accs.data(), cur.data(), n_out, level, raised) : rescale_batch(ctx, accs.data(), cur.data(), n_out, level, rs_ws);
         if (rc != HE_OK) return rc;
     }
     if (ras_T) {
@@ -467,7 +469,7 @@ extern "C" int32_t he_conv2d(he_ctx* ctx, const he_conv_plan* plan, const uint64
             srcs[o] = {cur[o], cur[o] + (size_t)level * N, cur[o], cur[o] + (size_t)level * N};
             jobs[o] = {o, ras_g[s], ras_key[s], nxt[o], nxt[o] + (size_t)level * N, 1};
         }
-        rc = ks_engine(ctx, lo, srcs.data(), n_out, jobs.data(), n_out);
+        rc = ks_engine(ctx, lo, srcs.data(), n_out, jobs.data(), n_out, false, raised && s == 0);
         if (rc != HE_OK) return rc;
         std::swap(cur, nxt);
     }

@@ -758,7 +758,13 @@ u64* ks_engine_src_rows(const he_ctx* c, uint32_t level, uint32_t n_src, uint32_
     return two_pass(c) && modup_by_columns(c, level) && n_src <= cb ? c->d_ws + ks_engine_ws(c, level, cb, jb).tmp_up : nullptr;
 }
 
-int32_t ks_engine(he_ctx* c, uint32_t level, const KsSrc* srcs, uint32_t n_src, const KsJob* jobs, uint32_t n_jobs, bool src_rows) {
+u64* ks_engine_raised(const he_ctx* c, uint32_t level, uint32_t n_src, uint32_t n_jobs) {
+    uint32_t cb, jb;
+    engine_shape(c, level, n_src, n_jobs, cb, jb);
+    return n_src <= cb ? c->d_ws : nullptr;
+}
+
+int32_t ks_engine(he_ctx* c, uint32_t level, const KsSrc* srcs, uint32_t n_src, const KsJob* jobs, uint32_t n_jobs, bool src_rows, bool raised_done) {
     if (n_jobs == 0) return HE_OK;
     const uint32_t N = c->N, R = level + 1 + c->np, beta = num_digits(c, level);
     if (2 * c->np > HE_MAX_MODULI) return he_fail(c, HE_ERR_BADARG, "key switch: more than %d special primes", HE_MAX_MODULI / 2);
@@ -787,7 +793,7 @@ int32_t ks_engine(he_ctx* c, uint32_t level, const KsSrc* srcs, uint32_t n_src, 
         bool rows_left = ks_rows_path(c, level);
         uint32_t uses[HE_MAX_SEGS] = {0};
         for (size_t i = pos; i < end; i++) rows_left = rows_left && ++uses[jobs[order[i]].src - s0] == 1;
-        rc = modup_batch(c, srcs + s0, ns, level, raised, tmp_up, !rows_left, src_rows);
+        if (!raised_done) rc = modup_batch(c, srcs + s0, ns, level, raised, tmp_up, !rows_left, src_rows);
         if (rc != HE_OK) return rc;
         while (pos < end) {
             uint32_t J = (uint32_t)std::min<size_t>(jb, end - pos);
