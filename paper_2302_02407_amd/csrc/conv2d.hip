@@ -210,7 +210,7 @@ static std::vector<uint32_t> tap_slot_steps(uint32_t W, uint32_t R, uint32_t f, 
 }
 
 // he_conv2d workspace: [key-switch engine region][rescale scratch][rotated inputs][n_out accumulators at `level`]
-// [n_out temporaries at level-1]
+// [n_out temporaries at level-1][small rings: raised digits of a step]
 // With the ModDown deferred across the taps the rotated inputs are replaced by (at the start of the region, where the
 // engine's scratch of the rotate-and-sum steps lives later): [ModUp scratch][n_rot inner products over the raised
 // basis][accumulators of one chunk of outputs over the raised basis][ModDown scratch][n_rot rotated c0][the chunk's
@@ -220,18 +220,28 @@ static size_t conv2d_deferred_elems(const he_ctx* ctx, uint32_t level, uint32_t 
     return ks_raised_products_ws_elems(ctx, level) + (size_t)n_rot * 2 * R * N + nb * 2 * R * N + ks_moddown_stored_ws_elems(ctx, level, (uint32_t)nb) +
            (size_t)n_rot * L1 * N + nb * 2 * L1 * N;
 }
+// small rings: where a step of the rotate-and-sum raises what the next one rotates while its own digits, at the start, are read
+static size_t conv2d_raised_elems(const he_ctx* ctx, uint32_t lo, uint32_t n_out, uint32_t n_ras) {
+    return n_ras > 1 && sr_moddown_raises(ctx, lo) ? ks_raised_elems(ctx, lo, std::min<uint32_t>(n_out, HE_MAX_KS_JOBS)) : 0;
+}
+static uint32_t ras_steps(const he_conv_plan* plan) {
+    uint32_t n = 0;
+    for (uint32_t s = 1; !plan->skip_ras && s < plan->C_a; s <<= 1) n++;
+    return n;
+}
 static size_t conv2d_ws_elems(const he_ctx* ctx, uint32_t level, uint32_t n_rot, uint32_t n_out, bool deferred_taps = false,
-                              uint32_t hoisted_ras_terms = 0) {
+                              uint32_t hoisted_ras_terms = 0, uint32_t n_ras = 0) {
     const size_t N = ctx->N, ct_e = (size_t)2 * (level + 1) * N, ct_lo_e = (size_t)2 * level * N;
     // scratch of the rotate-and-sum stage: the engine's (one step at a time) or the hoisted sum's
     const size_t ras_e = hoisted_ras_terms ? ks_hoisted_sum_ws_elems(ctx, level - 1, n_out, hoisted_ras_terms)
                                            : ks_engine_ws_elems(ctx, level - 1, n_out, n_out);
+    const size_t next_e = hoisted_ras_terms ? 0 : conv2d_raised_elems(ctx, level - 1, n_out, n_ras);
     if (deferred_taps && n_rot) {
         const size_t head = std::max(conv2d_deferred_elems(ctx, level, n_rot, n_out), ras_e);
-        return head + rescale_ws_elems(ctx, level, n_out) + (size_t)n_out * ct_e + (size_t)n_out * ct_lo_e;
+        return head + rescale_ws_elems(ctx, level, n_out) + (size_t)n_out * ct_e + (size_t)n_out * ct_lo_e + next_e;
     }
     const size_t ks_e = std::max(n_rot ? ks_engine_ws_elems(ctx, level, 1, n_rot) : 0, ras_e);
-    return ks_e + rescale_ws_elems(ctx, level, n_out) + (size_t)(n_rot + n_out) * ct_e + (size_t)n_out * ct_lo_e;
+    return ks_e + rescale_ws_elems(ctx, level, n_out) + (size_t)(n_rot + n_out) * ct_e + (size_t)n_out * ct_lo_e + next_e;
 }
 // terms of the hoisted rotate-and-sum of a plan (0: the log2 C_a dependent steps are used)
 static uint32_t hoisted_ras_terms(const he_conv_plan* plan) {
@@ -245,7 +255,7 @@ extern "C" int32_t he_ws_query_conv2d(const he_ctx* ctx, const he_conv_plan* pla
     if ((plan->f & 1u) == 0 || plan->f * plan->f > CV_MAX_TAPS || plan->n_out == 0 || ctx->np == 0) return HE_ERR_BADARG;
     uint32_t n_rot = 0;
     for (uint32_t st : tap_slot_steps(plan->W, plan->R, plan->f, ctx->N / 2)) n_rot += st != 0;
-    *h_bytes = conv2d_ws_elems(ctx, plan->level, n_rot, plan->n_out, plan->deferred_taps != 0, hoisted_ras_terms(plan)) * sizeof(u64);
+    *h_bytes = conv2d_ws_elems(ctx, plan->level, n_rot, plan->n_out, plan->deferred_taps != 0, hoisted_ras_terms(plan), ras_steps(plan)) * sizeof(u64);
     return HE_OK;
     });
 }
@@ -299,11 +309,12 @@ extern "C" int32_t he_conv2d(he_ctx* ctx, const he_conv_plan* plan, const uint64
     const bool deferred_taps = plan->deferred_taps != 0 && n_rot > 0;
     if (deferred_taps && n_rot + 1 != taps)
         return he_fail(ctx, HE_ERR_BADARG, "he_conv2d: deferred_taps needs exactly one tap that does not rotate (%u of %u do)", taps - n_rot, taps);
-    const size_t total = conv2d_ws_elems(ctx, level, n_rot, n_out, deferred_taps, ras_T);
+    const size_t total = conv2d_ws_elems(ctx, level, n_rot, n_out, deferred_taps, ras_T, n_ras);
     int32_t rc = he_ensure_ws(ctx, total * sizeof(u64));
     if (rc != HE_OK) return rc;
     // laid out from the end of the region: [engine ...][rescale scratch][rotated inputs][accumulators][temporaries]
-    u64* tmp = ctx->d_ws + total - (size_t)n_out * ct_lo_e;  // [n_out] ciphertexts at level lo
+    u64* raised_b = ctx->d_ws + total - (ras_T ? 0 : conv2d_raised_elems(ctx, lo, n_out, n_ras));
+    u64* tmp = raised_b - (size_t)n_out * ct_lo_e;            // [n_out] ciphertexts at level lo
     u64* acc = tmp - (size_t)n_out * ct_e;                   // [n_out] ciphertexts at `level`
     u64* slid = acc - (size_t)(deferred_taps ? 0 : n_rot) * ct_e;   // [n_rot] rotated inputs
     u64* rs_ws = slid - rescale_ws_elems(ctx, level, n_out);
@@ -443,7 +454,7 @@ extern "C" int32_t he_conv2d(he_ctx* ctx, const he_conv_plan* plan, const uint64
         if (!deferred_taps) ctx->cnt.mac += (uint64_t)taps * n_out;
         std::vector<const u64*> accs(n_out);
         for (uint32_t o = 0; o < n_out; o++) accs[o] = acc + (size_t)o * ct_e;
-        if (!ras_T && n_ras && sr_rescale_raises(ctx, level, n_out)) raised = ks_engine_raised(ctx, lo, n_out, n_out);
+        if (!ras_T && n_ras && sr_rescale_raises(ctx, level, n_out) && ks_engine_at_once(ctx, lo, n_out, n_out)) raised = ctx->d_ws;
         rc = raised ? sr_rescale_modup(ctx, accs.data(), cur.data(), n_out, level, raised) : rescale_batch(ctx, accs.data(), cur.data(), n_out, level, rs_ws);
         if (rc != HE_OK) return rc;
     }
@@ -469,7 +480,9 @@ extern "C" int32_t he_conv2d(he_ctx* ctx, const he_conv_plan* plan, const uint64
             srcs[o] = {cur[o], cur[o] + (size_t)level * N, cur[o], cur[o] + (size_t)level * N};
             jobs[o] = {o, ras_g[s], ras_key[s], nxt[o], nxt[o] + (size_t)level * N, 1};
         }
-        rc = ks_engine(ctx, lo, srcs.data(), n_out, jobs.data(), n_out, false, raised && s == 0);
+        u64* next = raised && s + 1 < n_ras && sr_moddown_raises(ctx, lo) ? (s & 1u ? ctx->d_ws : raised_b) : nullptr;
+        rc = ks_engine(ctx, lo, srcs.data(), n_out, jobs.data(), n_out, false, raised, next);
+        raised = next;
         if (rc != HE_OK) return rc;
         std::swap(cur, nxt);
     }

@@ -315,10 +315,14 @@ struct KsJob {
     uint32_t add_self;   // out0 += src.s0, out1 += src.s1 (rotate-and-sum step, relinearisation)
 };
 // Runs every job: one ModUp per source, then inner product + ModDown per job, batched.
-// src_rows: ks_engine_src_rows holds the sources' inverse rows already; raised: ks_engine_raised their raised digits.
-int32_t ks_engine(he_ctx* ctx, uint32_t level, const KsSrc* srcs, uint32_t n_src, const KsJob* jobs, uint32_t n_jobs, bool src_rows = false, bool raised = false);
-// Where the raised digits of the sources [n_src][beta][R][N] go, if the engine raises all sources at once.  Null otherwise.
-u64* ks_engine_raised(const he_ctx* ctx, uint32_t level, uint32_t n_src, uint32_t n_jobs);
+// src_rows: ks_engine_src_rows holds the sources' inverse rows already; raised: their raised digits, which
+// the call takes from there; raised_next: where the raised digits of the second components of its results go (sr_moddown_raises), for as many jobs,
+// one a source and all under one key, as one launch set takes.
+int32_t ks_engine(he_ctx* ctx, uint32_t level, const KsSrc* srcs, uint32_t n_src, const KsJob* jobs, uint32_t n_jobs, bool src_rows = false,
+                  const u64* raised = nullptr, u64* raised_next = nullptr);
+// Whether the engine raises all sources and runs all jobs at once; raised digits of n sources: ks_raised_elems
+bool ks_engine_at_once(const he_ctx* ctx, uint32_t level, uint32_t n_src, uint32_t n_jobs);
+size_t ks_raised_elems(const he_ctx* c, uint32_t level, uint32_t n);
 // Where the inverse rows of the sources [n_src][level+1][N] go (in a workspace that is large enough), if the engine can start from them: its
 // conversion does the columns, and it raises all sources at once.  Null otherwise.
 u64* ks_engine_src_rows(const he_ctx* ctx, uint32_t level, uint32_t n_src, uint32_t n_jobs);
@@ -349,7 +353,9 @@ int32_t ks_moddown_stored(he_ctx* c, uint32_t level, uint32_t J, u64* acc, const
 // Latency path for rings whose limb fits one work group's LDS (smallring.hip)
 bool small_ring_path(const he_ctx* c, uint32_t level);
 int32_t sr_modup(he_ctx* c, const KsSrc* srcs, uint32_t cb, uint32_t level, u64* raised);
-int32_t sr_moddown(he_ctx* c, uint32_t level, uint32_t J, const ModDownEpilogue& ep);
+// raised_next [J][beta][R][N] or null: in the same launch, the ModUp of the second components it leaves
+bool sr_moddown_raises(const he_ctx* c, uint32_t level);
+int32_t sr_moddown(he_ctx* c, uint32_t level, uint32_t J, const ModDownEpilogue& ep, u64* raised_next = nullptr);
 // Rescale of n ciphertexts at `level` and, in the same launch, the ModUp of the second components it leaves, to raised [n][beta][R][N]
 bool sr_rescale_raises(const he_ctx* c, uint32_t level, uint32_t n);
 int32_t sr_rescale_modup(he_ctx* c, const u64* const* cts, u64* const* outs, uint32_t n, uint32_t level, u64* raised);

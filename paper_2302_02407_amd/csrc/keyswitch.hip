@@ -688,7 +688,7 @@ static bool same_key(const KsJob& a, const KsJob& b) { return a.evk == b.evk && 
 // raised_of[i] / srcs give job i's raised digits and source; scratch: acc, tmp_dn, conv.  rows_left: the digits' rows are not
 // transformed yet.
 static int32_t inner_moddown_batch(he_ctx* c, uint32_t level, const KsSrc* srcs, const KsJob* jobs, const u64* const* raised_of,
-                                   uint32_t J, u64* acc, u64* tmp_dn, u64* conv, bool rows_left) {
+                                   uint32_t J, u64* acc, u64* tmp_dn, u64* conv, bool rows_left, u64* raised_next) {
     const uint32_t N = c->N, L1 = level + 1, k = c->np, R = L1 + k, beta = num_digits(c, level);
     if (c->prof_on) {                                   // one pass over a key for each run of jobs that use it (the caller sorts them)
         uint32_t runs = 0;
@@ -746,7 +746,7 @@ static int32_t inner_moddown_batch(he_ctx* c, uint32_t level, const KsSrc* srcs,
         ep.g[i] = jobs[i].g;
         if (ep.c0[i]) c->cnt.automorph += L1;
     }
-    int32_t rc = small ? sr_moddown(c, level, J, ep) : moddown_chain(c, level, J, acc, tmp_dn, conv, ep);
+    int32_t rc = small ? sr_moddown(c, level, J, ep, raised_next) : moddown_chain(c, level, J, acc, tmp_dn, conv, ep);
     if (rc != HE_OK) return rc;
     c->cnt.keyswitch += J;
     return HE_OK;
@@ -758,14 +758,17 @@ u64* ks_engine_src_rows(const he_ctx* c, uint32_t level, uint32_t n_src, uint32_
     return two_pass(c) && modup_by_columns(c, level) && n_src <= cb ? c->d_ws + ks_engine_ws(c, level, cb, jb).tmp_up : nullptr;
 }
 
-u64* ks_engine_raised(const he_ctx* c, uint32_t level, uint32_t n_src, uint32_t n_jobs) {
+bool ks_engine_at_once(const he_ctx* c, uint32_t level, uint32_t n_src, uint32_t n_jobs) {
     uint32_t cb, jb;
     engine_shape(c, level, n_src, n_jobs, cb, jb);
-    return n_src <= cb ? c->d_ws : nullptr;
+    return n_src <= cb && n_jobs <= jb;
 }
+size_t ks_raised_elems(const he_ctx* c, uint32_t level, uint32_t n) { return (size_t)n * num_digits(c, level) * (level + 1 + c->np) * c->N; }
 
-int32_t ks_engine(he_ctx* c, uint32_t level, const KsSrc* srcs, uint32_t n_src, const KsJob* jobs, uint32_t n_jobs, bool src_rows, bool raised_done) {
+int32_t ks_engine(he_ctx* c, uint32_t level, const KsSrc* srcs, uint32_t n_src, const KsJob* jobs, uint32_t n_jobs, bool src_rows,
+                  const u64* raised_in, u64* raised_next) {
     if (n_jobs == 0) return HE_OK;
+    if ((raised_in || raised_next) && !ks_engine_at_once(c, level, n_src, n_jobs)) return he_fail(c, HE_ERR_BADARG, "key switch: more raised digits than one launch set takes");
     const uint32_t N = c->N, R = level + 1 + c->np, beta = num_digits(c, level);
     if (2 * c->np > HE_MAX_MODULI) return he_fail(c, HE_ERR_BADARG, "key switch: more than %d special primes", HE_MAX_MODULI / 2);
     int32_t rc = he_ensure_ws(c, ks_engine_ws_elems(c, level, n_src, n_jobs) * sizeof(u64));
@@ -793,7 +796,7 @@ int32_t ks_engine(he_ctx* c, uint32_t level, const KsSrc* srcs, uint32_t n_src, 
         bool rows_left = ks_rows_path(c, level);
         uint32_t uses[HE_MAX_SEGS] = {0};
         for (size_t i = pos; i < end; i++) rows_left = rows_left && ++uses[jobs[order[i]].src - s0] == 1;
-        if (!raised_done) rc = modup_batch(c, srcs + s0, ns, level, raised, tmp_up, !rows_left, src_rows);
+        if (!raised_in) rc = modup_batch(c, srcs + s0, ns, level, raised, tmp_up, !rows_left, src_rows);
         if (rc != HE_OK) return rc;
         while (pos < end) {
             uint32_t J = (uint32_t)std::min<size_t>(jb, end - pos);
@@ -808,9 +811,9 @@ int32_t ks_engine(he_ctx* c, uint32_t level, const KsSrc* srcs, uint32_t n_src, 
             const u64* raised_of[HE_MAX_KS_JOBS];
             for (uint32_t i = 0; i < J; i++) {
                 chunk[i] = jobs[order[pos + i]];
-                raised_of[i] = raised + (size_t)(chunk[i].src - s0) * beta * R * N;
+                raised_of[i] = (raised_in ? raised_in : raised) + (size_t)(chunk[i].src - s0) * beta * R * N;
             }
-            rc = inner_moddown_batch(c, level, srcs, chunk, raised_of, J, acc, tmp_dn, conv, rows_left);
+            rc = inner_moddown_batch(c, level, srcs, chunk, raised_of, J, acc, tmp_dn, conv, rows_left, raised_next);
             if (rc != HE_OK) return rc;
             pos += J;
         }

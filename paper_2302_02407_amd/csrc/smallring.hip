@@ -243,6 +243,13 @@ __global__ __launch_bounds__(SR_THREADS) void sr_modup_kernel(SrUpArgs a, SrTabl
     for (uint32_t e = threadIdx.x; e < N; e += SR_THREADS) dst[e] = sm[sp(e)];
 }
 
+// A launch whose first work groups rescale or bring down, and whose others raise what comes of it: per source limb of the ModUp (d Q_j/q_i)^-1
+// mod q_i, d = q_l or P
+struct SrRaise {
+    uint32_t first;
+    u64 factor[HE_MAX_MODULI];
+};
+
 // ---------------------------------------------------------------- inner product + ModDown
 struct SrDownArgs {
     const u64* dn_hat;         // [M][pw]: (P/p_t) mod modulus
@@ -360,12 +367,6 @@ struct SrRescaleArgs {
     u64* out[HE_MAX_KS_JOBS];        // [2][level][N]
     const u64 *qlinv, *qlinv_sh;     // q_level^-1 mod q_r
     uint32_t level;
-};
-
-// Work groups that rescale, and per source limb of the ModUp (q_l (Q_j/q_i))^-1 mod q_i
-struct SrRaise {
-    uint32_t rescales;
-    u64 factor[HE_MAX_MODULI];
 };
 
 __global__ __launch_bounds__(SR_THREADS) void sr_rescale_kernel(SrRescaleArgs a, SrTables tb) {
@@ -705,10 +706,8 @@ __device__ __forceinline__ void srf_inner(double (&out)[8], SrfOps& o, const Srf
 }
 
 template <int LN>
-__global__ __launch_bounds__(Srf<LN>::T, 2) void srf_moddown_kernel(ModDownEpilogue ep, SrDownArgs a, SrTables tb) {
+__device__ __forceinline__ void srf_moddown(const ModDownEpilogue& ep, const SrDownArgs& a, const SrTables& tb, double* sm, double* keep) {
     using G = Srf<LN>;
-    __shared__ __attribute__((aligned(16))) double sm[SRF_LDS(LN)];
-    __shared__ double keep[(SR_MAX_SRC - 1) * G::N];
     const uint32_t L1 = ep.L1, R = ep.R, beta = ep.beta, t = threadIdx.x;
     const SrfRow<LN> row(t);
     const uint32_t pc = blockIdx.x / L1, r = blockIdx.x - pc * L1, job = pc >> 1, comp = pc & 1u;
@@ -764,6 +763,89 @@ __global__ __launch_bounds__(Srf<LN>::T, 2) void srf_moddown_kernel(ModDownEpilo
 }
 
 template <int LN>
+__global__ __launch_bounds__(Srf<LN>::T, 2) void srf_moddown_kernel(ModDownEpilogue ep, SrDownArgs a, SrTables tb) {
+    __shared__ __attribute__((aligned(16))) double sm[SRF_LDS(LN)];
+    __shared__ double keep[(SR_MAX_SRC - 1) * Srf<LN>::N];
+    srf_moddown<LN>(ep, a, tb, sm, keep);
+}
+// ModDown and the ModUp of the second components it leaves, side by side: coefficients of a digit's limb are those of sum / P + addend less
+// those of the converted part / P, so a digit needs the special primes' inverse transforms (as every ModDown work group does) and its own, and
+// not the results.  A layer of N = 2^12 with two steps 79.6 -> 74.9 us (ModDown 14.7 and ModUp 9.6 one after the other).  Digits and special primes of together at most four
+// limbs, which LDS holds; of a digit's limbs only the first is asked for ahead (all of them spill).
+template <int LN>
+__global__ __launch_bounds__(Srf<LN>::T, 2) void srf_moddown_modup_kernel(ModDownEpilogue ep, SrDownArgs a, SrUpArgs u, SrRaise f, SrTables tb) {
+    using G = Srf<LN>;
+    __shared__ __attribute__((aligned(16))) double sm[SRF_LDS(LN)];
+    __shared__ double keep[(SR_MAX_SRC - 1) * G::N];       // the special primes' limbs, then the digit's but the last
+    if (blockIdx.x < f.first) {
+        srf_moddown<LN>(ep, a, tb, sm, keep);
+        return;
+    }
+    const uint32_t t = threadIdx.x, b = blockIdx.x - f.first, job = b / u.n_out, o = b - job * u.n_out, beta = ep.beta;
+    const SrfRow<LN> row(t);
+    const uint32_t j = u.oj[o], r = u.orr[o], lo = j * u.alpha, sz = min(u.alpha, u.L1 - lo);
+    const uint32_t mr = r <= u.level ? r : u.nq + (r - u.level - 1);
+    const SrfGalois<LN> ga(row, ep.g[job]);
+    const size_t ds = (size_t)ep.R << LN, ks = (size_t)(2 * ep.M) << LN;
+    const u64 *raised = ep.raised[job], *evk = ep.evk[job] + ((size_t)ep.M << LN), *self = ep.self1[job];
+    const double *itw = tb.fitw + ((size_t)a.nq << LN), *ftw = tb.ftw + ((size_t)mr << LN);
+    SrfTw<LN> w;
+    SrfOps ops;
+    SrfInner in = {raised + ((size_t)ep.L1 << LN), nullptr, evk + ((size_t)a.nq << LN), 0xFFFFFFFFu};
+    srf_request(ops, in, beta, ds, ks, row, ga);
+    srf_tw_all<LN>(w, itw, t);
+    double x[8];
+    for (uint32_t i = 0; i < a.k; i++) {
+        const bool last = i + 1 == a.k;
+        const FMod mp = f_mod(tb.mc[a.nq + i]);
+        if (i) __syncthreads();                            // the words of the transform before have been read
+        srf_inner(x, ops, in, beta, ds, ks, row, ga, sm, mp);
+        row.to_own(x, sm);
+        // next: another special-prime limb, or after them the digit's first
+        if (last) in = {raised + ((size_t)lo << LN), ep.own[job] + ((size_t)lo << LN), evk + ((size_t)lo << LN), j};
+        else { in.raised += G::N; in.key += G::N; }
+        srf_request(ops, in, beta, ds, ks, row, ga);
+        srf_inv<LN>(x, w, itw, last ? tb.fitw + ((size_t)lo << LN) : itw + G::N, f_of(a.scale[i]), sm, t, mp);
+        itw += G::N;
+        EACH8(k) keep[i * G::N + t + k * G::T] = x[k];
+    }
+    itw = tb.fitw + ((size_t)lo << LN);
+    double* digit = keep + a.k * G::N;
+    for (uint32_t i = 0; i < sz; i++) {
+        const bool last = i + 1 == sz;
+        const uint32_t q = lo + i;
+        const FMod mi = f_mod(tb.mc[q]);
+        const double pinv = f_of(ep.pinv[q]), c = f_of(f.factor[q]);
+        if (i) {
+            in.raised += G::N; in.own += G::N; in.key += G::N;
+            srf_request(ops, in, beta, ds, ks, row, ga);
+        }
+        __syncthreads();                                   // the words of the transform before have been read
+        srf_inner(x, ops, in, beta, ds, ks, row, ga, sm, mi);
+        u64 add[8];
+        EACH8(k) add[k] = 0;
+        if (self) row.load(add, self + ((size_t)q << LN) + row.wb);
+        EACH8(k) x[k] = f_red(f_mul(x[k], pinv, mi) + f_of(add[k]), mi);
+        row.to_own(x, sm);
+        srf_inv<LN>(x, w, itw, last ? ftw : itw + G::N, f_of(u.scale[q]), sm, t, mi);
+        itw += G::N;
+        double v[8];
+        EACH8(k) v[k] = keep[(a.k - 1) * G::N + t + k * G::T];
+        srf_convert<LN>(v, keep, a.dn_hat + (size_t)q * a.pw, a.k, t, mi);
+        EACH8(k) x[k] = f_nonneg(f_red(x[k] - f_mul(v[k], c, mi), mi), mi);
+        if (!last) { EACH8(k) digit[i * G::N + t + k * G::T] = x[k]; }
+    }
+    const FMod m = f_mod(tb.mc[mr]);
+    srf_convert<LN>(x, digit, u.hat + ((size_t)(j * u.alpha + (sz - 1)) * u.M + mr) * u.aw, sz, t, m);
+    srf_fwd<LN>(x, w, ftw, sm, t, m);
+    u64* dst = u.raised + ((size_t)((job * u.beta + j) * u.R + r) << LN) + row.wb;
+    u64 out[8];
+    EACH8(k) out[k] = f_canon(f_red(x[k], m), m);
+    row.to_pairs(out, sm);
+    row.store(dst, out);
+}
+
+template <int LN>
 __device__ __forceinline__ void srf_rescale(const SrRescaleArgs& a, const SrTables& tb, double* sm) {
     const uint32_t level = a.level, t = threadIdx.x;
     const SrfRow<LN> row(t);
@@ -805,11 +887,11 @@ __global__ __launch_bounds__(Srf<LN>::T, 2) void srf_rescale_modup_kernel(SrResc
     using G = Srf<LN>;
     __shared__ __attribute__((aligned(16))) double sm[SRF_LDS(LN)];
     __shared__ double keep[(SR_MAX_SRC - 1) * G::N];
-    if (blockIdx.x < f.rescales) {
+    if (blockIdx.x < f.first) {
         srf_rescale<LN>(a, tb, sm);
         return;
     }
-    const uint32_t t = threadIdx.x, b = blockIdx.x - f.rescales, s = b / u.n_out, o = b - s * u.n_out, level = a.level;
+    const uint32_t t = threadIdx.x, b = blockIdx.x - f.first, s = b / u.n_out, o = b - s * u.n_out, level = a.level;
     const SrfRow<LN> row(t);
     const uint32_t j = u.oj[o], r = u.orr[o], lo = j * u.alpha, sz = min(u.alpha, u.L1 - lo);
     const uint32_t mr = r <= u.level ? r : u.nq + (r - u.level - 1);
@@ -907,7 +989,8 @@ int32_t sr_modup(he_ctx* c, const KsSrc* srcs, uint32_t cb, uint32_t level, u64*
     return HE_OK;
 }
 
-int32_t sr_moddown(he_ctx* c, uint32_t level, uint32_t J, const ModDownEpilogue& ep) {
+bool sr_moddown_raises(const he_ctx* c, uint32_t level) { return c->srf && small_ring_path(c, level) && c->alpha + c->np <= SR_MAX_SRC; }
+int32_t sr_moddown(he_ctx* c, uint32_t level, uint32_t J, const ModDownEpilogue& ep, u64* raised_next) {
     const uint32_t L1 = level + 1, k = c->np;
     SrDownArgs a;
     a.dn_hat = c->d_dn_hat; a.k = k; a.nq = c->nq; a.level = level; a.pw = (k + 7u) & ~7u;
@@ -916,7 +999,23 @@ int32_t sr_moddown(he_ctx* c, uint32_t level, uint32_t J, const ModDownEpilogue&
         a.scale[t] = h_mulmod(c->h_mc[c->nq + t].ninv, c->h_dn_invhat[t], p);
         a.scale_sh[t] = h_shoup(a.scale[t], p);
     }
-    SR_LAUNCH(moddown_kernel, dim3(J * 2 * L1), ep, a, sr_tables(c));
+    if (raised_next) {
+        if (!sr_moddown_raises(c, level)) return he_fail(c, HE_ERR_BADARG, "ModDown with ModUp: bad shape");
+        SrUpArgs u;
+        SrRaise f;
+        sr_up_args(c, level, raised_next, u);
+        f.first = J * 2 * L1;
+        for (uint32_t i = 0; i < L1; i++) {
+            const u64 q = c->mod[i];
+            u64 P = 1;
+            for (uint32_t t = 0; t < k; t++) P = h_mulmod(P, c->mod[c->nq + t] % q, q);
+            f.factor[i] = h_mulmod(h_mulmod(u.scale[i], c->N % q, q), h_invmod(P, q), q);
+        }
+        SRF_LAUNCH(moddown_modup_kernel, dim3(f.first + J * u.n_out), ep, a, u, f, sr_tables(c));
+        c->cnt.intt_limbs += (uint64_t)J * L1;
+        c->cnt.ntt_limbs += (uint64_t)J * u.n_out;
+        c->cnt.modup += J;
+    } else SR_LAUNCH(moddown_kernel, dim3(J * 2 * L1), ep, a, sr_tables(c));
     HE_HIP(c, hipGetLastError());
     c->cnt.intt_limbs += (uint64_t)J * 2 * k;
     c->cnt.ntt_limbs += (uint64_t)J * 2 * L1;
@@ -948,13 +1047,13 @@ int32_t sr_rescale_modup(he_ctx* c, const u64* const* cts, u64* const* outs, uin
     for (uint32_t i = 0; i < n; i++) { a.ct[i] = cts[i]; a.out[i] = outs[i]; }
     a.qlinv = c->d_qlinv + (size_t)level * c->nq; a.qlinv_sh = c->d_qlinv_sh + (size_t)level * c->nq; a.level = level;
     sr_up_args(c, level - 1, raised, u);
-    f.rescales = 2 * n * level;
+    f.first = 2 * n * level;
     for (uint32_t i = 0; i < level; i++) {
         const u64 q = c->mod[i], inv = h_invmod(c->mod[level] % q, q);
         u.scale[i] = h_mulmod(u.scale[i], inv, q);
         f.factor[i] = h_mulmod(u.scale[i], c->N % q, q);
     }
-    SRF_LAUNCH(rescale_modup_kernel, dim3(f.rescales + n * u.n_out), a, u, f, sr_tables(c));
+    SRF_LAUNCH(rescale_modup_kernel, dim3(f.first + n * u.n_out), a, u, f, sr_tables(c));
     HE_HIP(c, hipGetLastError());
     c->cnt.intt_limbs += (uint64_t)n * (2 + level);
     c->cnt.ntt_limbs += (uint64_t)n * (2 * level + u.n_out);

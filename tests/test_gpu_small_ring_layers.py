@@ -1,4 +1,4 @@
-"""GPU parity of rotate-and-sum layers on small rings, where the rescale also raises what the first step rotates: 1 to 4 limbs per digit and special primes, 1 to 8 digits, primes at the widest that FP64 carries, every register-block split of the transforms, no step, one
+"""GPU parity of rotate-and-sum layers on small rings, where the rescale raises what the first step rotates and a step what the next one does: 1 to 4 limbs per digit and special primes, 1 to 8 digits, primes at the widest that FP64 carries, every register-block split of the transforms, no step, one
 and several, one output and as many as a launch takes and more, uniform and extreme residues - against the oracle, bit for bit."""
 import numpy as np
 import pytest
@@ -17,6 +17,9 @@ pytestmark = pytest.mark.gpu
     (11, 45, 5, 2, 3, (4, 3), 4, 17),   # more outputs than a launch takes
     (12, 45, 5, 2, 3, (4, 1), 2, 3),
     (12, 40, 4, 1, 4, (3, 2), 8, 4),
+    (11, 45, 9, 1, 3, (8, 4), 8, 2),    # three limbs a digit and one special prime, the most that a step raises; a partial digit
+    (10, 45, 4, 3, 4, (3,), 16, 1),     # one and three
+    (9, 45, 6, 2, 3, (5, 4), 4, 3),     # two and two
     (12, 40, 3, 1, 3, (2,), 1, 2),      # no step
     (12, 46, 4, 1, 4, (3,), 4, 2),      # one bit more: the integer kernels, a launch each
 ])
