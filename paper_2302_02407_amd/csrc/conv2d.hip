@@ -15,12 +15,10 @@
 // Sums of products of a few ciphertexts with many plaintexts: acc_o = sum_i ct_i * pt_(o,i) for o < n_out, both components.
 #define MAC_MAX_IN 16
 #define MAC_MAX_PT 144
-// The second components of the outputs in `mask` also go through their inverse rows, to out [number of them][CL][N].
+// The second components of the outputs in `mask` also go through their inverse rows.
 struct MacRows {
-    u64* out;                     // null: none
+    RowsOut to;
     uint32_t mask;
-    const ulonglong2* itw;
-    u64 wide_inv, widest, near_inv;      // bit per modulus (narrow_inv, widest, near_inv)
 };
 struct MacMany {
     const u64* ct[MAC_MAX_IN];                           // [2][CL][N]
@@ -126,12 +124,12 @@ __global__ __launch_bounds__(CV_THREADS) void mac_many_kernel(MacMany a, const M
         }
     }
     if constexpr (ROWS) {
-        u64* out = a.rows.out + ((size_t)limb << logN);
+        u64* out = a.rows.to.out + ((size_t)limb << logN);
         const size_t stride = (size_t)CL << logN;
-        const ulonglong2* tw = a.rows.itw + ((size_t)mi << logN);
-        if (a.rows.near_inv >> mi & 1u) mac_rows<W_NEAR>(tiles, held, out, stride, m, tw, logN);
-        else if (!(a.rows.wide_inv >> mi & 1u)) mac_rows<0>(tiles, held, out, stride, m, tw, logN);
-        else if (!(a.rows.widest >> mi & 1u)) mac_rows<1>(tiles, held, out, stride, m, tw, logN);
+        const ulonglong2* tw = a.rows.to.itw + ((size_t)mi << logN);
+        if (a.rows.to.near_inv >> mi & 1u) mac_rows<W_NEAR>(tiles, held, out, stride, m, tw, logN);
+        else if (!(a.rows.to.wide_inv >> mi & 1u)) mac_rows<0>(tiles, held, out, stride, m, tw, logN);
+        else if (!(a.rows.to.widest >> mi & 1u)) mac_rows<1>(tiles, held, out, stride, m, tw, logN);
         else mac_rows<2>(tiles, held, out, stride, m, tw, logN);
     }
 }
@@ -148,7 +146,7 @@ static void launch_mac_many_of(he_ctx* ctx, const MacMany& a, uint32_t CL, uint3
                 return;
             }
         }
-        if (a.rows.out) {
+        if (a.rows.to.out) {
             const uint32_t held = (uint32_t)__builtin_popcount(a.rows.mask);
             hipLaunchKernelGGL((mac_many_kernel<NI, false, true>), grid, block, held * CV_THREADS * sizeof(u64), ctx->stream, a, ctx->d_mc, ctx->logN, CL, level, ctx->nq);
             return;
@@ -157,15 +155,6 @@ static void launch_mac_many_of(he_ctx* ctx, const MacMany& a, uint32_t CL, uint3
     }
 }
 static void launch_mac_many(he_ctx* ctx, const MacMany& a, uint32_t CL, uint32_t level) { launch_mac_many_of<MAC_MAX_IN>(ctx, a, CL, level); }
-static MacRows mac_rows_of(const he_ctx* ctx, u64* out, uint32_t mask) {
-    MacRows r = {out, mask, ctx->d_itw, 0, 0, 0};
-    for (uint32_t i = 0; i < ctx->M; i++) {
-        r.wide_inv |= (u64)!narrow_inv(ctx->mod[i]) << i;
-        r.widest |= (u64)widest(ctx->mod[i]) << i;
-        r.near_inv |= (u64)near_inv(ctx->mod[i]) << i;
-    }
-    return r;
-}
 // index of plaintext (o, i) in MacMany::pt for n_in ciphertexts
 static uint32_t mac_pt_index(uint32_t n_in, uint32_t o, uint32_t i) { return o * n_in + i; }
 
@@ -510,7 +499,7 @@ static int32_t ra_mac(he_ctx* ctx, uint32_t n_in, uint32_t taps, uint32_t level,
                 a.ct[i] = ct(i0 + i);
                 for (uint32_t t = 0; t < a.n_out; t++) a.pt[mac_pt_index(a.n_in, t, i)] = pt(i0 + i, t0 + t);
             }
-            if (rows && mask && i0 + RA_IN_PER_LAUNCH >= n_in) a.rows = mac_rows_of(ctx, rows, mask);
+            if (rows && mask && i0 + RA_IN_PER_LAUNCH >= n_in) a.rows = {rows_out(ctx, rows), mask};
             launch_mac_many(ctx, a, level + 1, level);
             HE_HIP(ctx, hipGetLastError());
         }
@@ -898,7 +887,8 @@ extern "C" int32_t he_ca_ra_block(he_ctx* ctx, const he_block_plan* plan, const 
             std::vector<KsJob> jobs(g);
             std::vector<const u64*> sq(g);
             std::vector<u64*> outs(g);
-            rc = launch_square_lift(ctx, cur[0], g, lv, (const u64*)plan->h_k_in, tens);   // cur[o] == pa + o*ct_mid
+            u64* rows = ks_engine_src_rows(ctx, lv, g, g);
+            rc = launch_square_lift(ctx, cur[0], g, lv, (const u64*)plan->h_k_in, tens, rows);   // cur[o] == pa + o*ct_mid
             if (rc != HE_OK) return rc;
             for (uint32_t o = 0; o < g; o++) {
                 u64* d = tens + (size_t)o * 3 * pe_mid;
@@ -908,7 +898,7 @@ extern "C" int32_t he_ca_ra_block(he_ctx* ctx, const he_block_plan* plan, const 
                 sq[o] = res;
                 outs[o] = ct3 + (size_t)o * ct_lo;
             }
-            rc = ks_engine(ctx, lv, srcs.data(), g, jobs.data(), g);
+            rc = ks_engine(ctx, lv, srcs.data(), g, jobs.data(), g, rows != nullptr);
             if (rc != HE_OK) return rc;
             rc = rescale_batch(ctx, sq.data(), outs.data(), g, lv, rs_ws);
             if (rc != HE_OK) return rc;

@@ -2,6 +2,7 @@
 #include <algorithm>
 
 #include "modarith.h"
+#include "ntt_blocks.h"
 
 #define EW_THREADS 256
 
@@ -155,13 +156,6 @@ __global__ __launch_bounds__(EW_THREADS) void tensor_kernel(const u64* __restric
     d[o2] = mulmod(a1, b1, m);
 }
 
-int32_t launch_tensor(he_ctx* ctx, const u64* a, const u64* b, uint32_t level, u64* d) {
-    dim3 grid(ctx->N / EW_THREADS, level + 1), block(EW_THREADS);
-    hipLaunchKernelGGL(tensor_kernel, grid, block, 0, ctx->stream, a, b, d, ctx->d_mc, ctx->logN, level + 1);
-    HE_HIP(ctx, hipGetLastError());
-    return HE_OK;
-}
-
 // Tensor square of k*u for n ciphertexts that lie one after the other: with v_c = u_c * k[r],
 // d = (v_0^2, 2 v_0 v_1, v_1^2).  One pass instead of a scaling and a tensor product per ciphertext.
 // grid: (N/256, L1, n); u [n][2][L1][N], d [n][3][L1][N].
@@ -182,9 +176,83 @@ __global__ __launch_bounds__(EW_THREADS) void square_lift_kernel(const u64* __re
     d[2 * pe + o] = mulmod(v1, v1, m);
 }
 
-int32_t launch_square_lift(he_ctx* ctx, const u64* u, uint32_t n, uint32_t level, const u64* mul, u64* d) {
+// The same products where a key switch follows, which begins with the inverse rows of d2 (rings from 2^13): a wavefront takes the 256 points of a
+// row, 4 a lane, and transforms its d2 in LDS before it ends, so d2 is not read back and a launch is saved: a product and its rescale at level 11 of
+// N = 2^16 114.9 -> 112.9 us, a block with eight squares of six limbs 1 % less.  Bound by its bytes, for a single product by the chain.  LIFT: square_lift_kernel, else tensor_kernel
+// (n = 1).  grid: (N/1024, L1, n); the inverse rows go to r.out [n][L1][N].
+template <int W>
+__device__ __forceinline__ void tensor_row(u64* buf, const RowsOut& r, size_t at_row, uint32_t limb, uint32_t row, uint32_t lane, const ModConst& m, uint32_t logN) {
+    const Row4 at(lane);
+    u64 w[4][6], x[1][4];
+    tw_row4(w, r.itw + ((size_t)limb << logN), logN - 8, row, lane);
+    at.load(3, x[0], buf);
+    wave_exchange();
+    row4_inv<W, 1>(x, w, buf, 256, at, m.q, m);
+#pragma unroll
+    for (int p = 0; p < 4; p++) r.out[at_row + 64 * p + lane] = x[0][p];
+}
+template <bool LIFT>
+__global__ __launch_bounds__(EW_THREADS) void tensor_rows_kernel(const u64* __restrict__ a, const u64* __restrict__ b, u64* __restrict__ d, LiftArgs k, RowsOut r,
+                                                                 const ModConst* mc, uint32_t logN, uint32_t L1) {
+    ieee_off();
+    __shared__ __attribute__((aligned(16))) u64 tiles[EW_THREADS * 4];
+    const uint32_t lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), limb = blockIdx.y, row = blockIdx.x * (EW_THREADS / 64) + wave;
+    const size_t pe = (size_t)L1 << logN, o = ((size_t)limb << logN) + 256 * row;
+    const ModConst m = mod_const(mc, limb);
+    u64* buf = tiles + 256 * wave;
+    if (LIFT) a += 2 * pe * blockIdx.z;
+    d += 3 * pe * blockIdx.z;
+    u64 a0[4], a1[4], b0[4], b1[4];
+#pragma unroll
+    for (int p = 0; p < 4; p++) {
+        const size_t n = o + 64 * p + lane;
+        a0[p] = a[n];
+        a1[p] = a[pe + n];
+        if (!LIFT) { b0[p] = b[n]; b1[p] = b[pe + n]; }
+    }
+#pragma unroll
+    for (int p = 0; p < 4; p++) {
+        const size_t n = o + 64 * p + lane;
+        u64 d1, d2;
+        if (LIFT) {
+            const u64 v0 = shoup_mul(a0[p], k.mul[limb], k.mul_sh[limb], m.q), v1 = shoup_mul(a1[p], k.mul[limb], k.mul_sh[limb], m.q), x = mulmod(v0, v1, m);
+            d[n] = mulmod(v0, v0, m);
+            d1 = addmod(x, x, m.q);
+            d2 = mulmod(v1, v1, m);
+        } else {
+            d[n] = mulmod(a0[p], b0[p], m);
+            d1 = barrett128((u128)a0[p] * b1[p] + (u128)a1[p] * b0[p], m.q, m.mu, m.bits);
+            d2 = mulmod(a1[p], b1[p], m);
+        }
+        d[pe + n] = d1;
+        d[2 * pe + n] = d2;
+        buf[row4_word(64 * p + lane)] = d2;
+    }
+    wave_exchange();
+    const size_t at_row = pe * blockIdx.z + o;
+    if (r.near_inv >> limb & 1u) tensor_row<W_NEAR>(buf, r, at_row, limb, row, lane, m, logN);
+    else if (!(r.wide_inv >> limb & 1u)) tensor_row<0>(buf, r, at_row, limb, row, lane, m, logN);
+    else if (!(r.widest >> limb & 1u)) tensor_row<1>(buf, r, at_row, limb, row, lane, m, logN);
+    else tensor_row<2>(buf, r, at_row, limb, row, lane, m, logN);
+}
+
+int32_t launch_tensor(he_ctx* ctx, const u64* a, const u64* b, uint32_t level, u64* d, u64* rows) {
+    const dim3 block(EW_THREADS);
+    if (rows) hipLaunchKernelGGL(tensor_rows_kernel<false>, dim3(ctx->N / (4 * EW_THREADS), level + 1), block, 0, ctx->stream, a, b, d, LiftArgs{}, rows_out(ctx, rows), ctx->d_mc, ctx->logN, level + 1);
+    else hipLaunchKernelGGL(tensor_kernel, dim3(ctx->N / EW_THREADS, level + 1), block, 0, ctx->stream, a, b, d, ctx->d_mc, ctx->logN, level + 1);
+    HE_HIP(ctx, hipGetLastError());
+    return HE_OK;
+}
+
+int32_t launch_square_lift(he_ctx* ctx, const u64* u, uint32_t n, uint32_t level, const u64* mul, u64* d, u64* rows) {
     LiftArgs k;
     for (uint32_t r = 0; r <= level; r++) { k.mul[r] = mul[r]; k.mul_sh[r] = h_shoup(mul[r], ctx->mod[r]); }
+    if (rows) {
+        hipLaunchKernelGGL(tensor_rows_kernel<true>, dim3(ctx->N / (4 * EW_THREADS), level + 1, n), dim3(EW_THREADS), 0, ctx->stream, u, u, d, k, rows_out(ctx, rows), ctx->d_mc,
+                           ctx->logN, level + 1);
+        HE_HIP(ctx, hipGetLastError());
+        return HE_OK;
+    }
     hipLaunchKernelGGL(square_lift_kernel, dim3(ctx->N / EW_THREADS, level + 1, n), dim3(EW_THREADS), 0, ctx->stream, u, d, k, ctx->d_mc, ctx->logN,
                        level + 1);
     HE_HIP(ctx, hipGetLastError());

@@ -293,8 +293,24 @@ struct AffineConst {
     u64 mul[HE_MAX_MODULI], add[HE_MAX_MODULI];
 };
 int32_t launch_affine(he_ctx* ctx, const u64* ct, uint32_t level, const AffineConst& k, u64* out);   // out may alias ct
-int32_t launch_square_lift(he_ctx* ctx, const u64* u, uint32_t n, uint32_t level, const u64* mul, u64* d);   // tensor squares of mul*u, n ciphertexts
-int32_t launch_tensor(he_ctx* ctx, const u64* a, const u64* b, uint32_t level, u64* d);   // d = [d0][d1][d2], each [level+1][N]
+// Inverse rows that a launch takes along of polynomials it forms (out null: none), and what they need; a bit per modulus
+struct RowsOut {
+    u64* out;                            // [polynomials][limbs][N]
+    const ulonglong2* itw;
+    u64 wide_inv, widest, near_inv;      // not narrow_inv; widest; near_inv
+};
+static inline RowsOut rows_out(const he_ctx* ctx, u64* out) {
+    RowsOut r = {out, ctx->d_itw, 0, 0, 0};
+    for (uint32_t i = 0; i < ctx->M; i++) {
+        r.wide_inv |= (u64)!narrow_inv(ctx->mod[i]) << i;
+        r.widest |= (u64)widest(ctx->mod[i]) << i;
+        r.near_inv |= (u64)near_inv(ctx->mod[i]) << i;
+    }
+    return r;
+}
+// tensor squares of mul*u, n ciphertexts, and tensor products: d = [d0][d1][d2], each [level+1][N].  rows: receives the inverse rows of every d2 (null: not wanted)
+int32_t launch_square_lift(he_ctx* ctx, const u64* u, uint32_t n, uint32_t level, const u64* mul, u64* d, u64* rows);
+int32_t launch_tensor(he_ctx* ctx, const u64* a, const u64* b, uint32_t level, u64* d, u64* rows);
 int32_t launch_automorph_coef(he_ctx* ctx, const u64* in, u64* out, const uint32_t* mod_idx, uint32_t n, uint32_t g);
 
 // key switching engine (keyswitch.hip)

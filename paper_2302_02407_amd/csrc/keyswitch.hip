@@ -1770,11 +1770,12 @@ int32_t he_mulct(he_ctx* ctx, const uint64_t* d_a, const uint64_t* d_b, uint32_t
     rc = he_ensure_ws(ctx, (ks_e + 3 * pe) * sizeof(u64));
     if (rc != HE_OK) return rc;
     u64* d = ctx->d_ws + ks_e;      // d0, d1, d2 behind the engine's region
-    rc = launch_tensor(ctx, (const u64*)d_a, (const u64*)d_b, level, d);
+    u64* rows = ks_engine_src_rows(ctx, level, 1, 1);
+    rc = launch_tensor(ctx, (const u64*)d_a, (const u64*)d_b, level, d, rows);
     if (rc != HE_OK) return rc;
     KsSrc src = {nullptr, d + 2 * pe, d, d + pe};
     KsJob job = {0, 1, it->second, (u64*)d_out, (u64*)d_out + pe, 1};
-    return ks_engine(ctx, level, &src, 1, &job, 1);
+    return ks_engine(ctx, level, &src, 1, &job, 1, rows != nullptr);
     });
 }
 
