@@ -405,6 +405,7 @@ extern "C" int32_t he_conv2d(he_ctx* ctx, const he_conv_plan* plan, const uint64
     // MulFilter&Sum_f for all outputs, then Rescale of all outputs.  The rotate-and-sum steps
     // ping-pong between the caller's output buffers and the temporaries; start so that the last
     // step lands in the output.
+    u64* sums = nullptr;
     u64* raised = nullptr;                                 // small rings: the rescale raises what the first step rotates
     std::vector<u64*> cur(n_out), nxt(n_out);
     for (uint32_t o = 0; o < n_out; o++) {
@@ -443,6 +444,7 @@ extern "C" int32_t he_conv2d(he_ctx* ctx, const he_conv_plan* plan, const uint64
         if (!deferred_taps) ctx->cnt.mac += (uint64_t)taps * n_out;
         std::vector<const u64*> accs(n_out);
         for (uint32_t o = 0; o < n_out; o++) accs[o] = acc + (size_t)o * ct_e;
+        sums = acc;
         if (!ras_T && n_ras && sr_rescale_raises(ctx, level, n_out) && ks_engine_at_once(ctx, lo, n_out, n_out)) raised = ctx->d_ws;
         rc = raised ? sr_rescale_modup(ctx, accs.data(), cur.data(), n_out, level, raised) : rescale_batch(ctx, accs.data(), cur.data(), n_out, level, rs_ws);
         if (rc != HE_OK) return rc;
@@ -461,7 +463,9 @@ extern "C" int32_t he_conv2d(he_ctx* ctx, const he_conv_plan* plan, const uint64
         return HE_OK;
     }
     // rotate-and-sum over the outermost channel dimension: every step is one batch over all
-    // outputs (same key), the addition ct + Rot(ct) is done by the ModDown epilogue
+    // outputs (same key), the addition ct + Rot(ct) is done by the ModDown epilogue.  What a step leaves goes through the next one's inverse rows
+    // where it is formed, into the space of the sums, which the rescale was the last to read
+    u64 *rows = nullptr, *rows_next = n_ras > 1 && ks_engine_next_rows(ctx, lo, n_out, n_out) ? sums : nullptr;
     for (uint32_t s = 0; s < n_ras; s++) {
         std::vector<KsSrc> srcs(n_out);
         std::vector<KsJob> jobs(n_out);
@@ -470,8 +474,9 @@ extern "C" int32_t he_conv2d(he_ctx* ctx, const he_conv_plan* plan, const uint64
             jobs[o] = {o, ras_g[s], ras_key[s], nxt[o], nxt[o] + (size_t)level * N, 1};
         }
         u64* next = raised && s + 1 < n_ras && sr_moddown_raises(ctx, lo) ? (s & 1u ? ctx->d_ws : raised_b) : nullptr;
-        rc = ks_engine(ctx, lo, srcs.data(), n_out, jobs.data(), n_out, false, raised, next);
+        rc = ks_engine(ctx, lo, srcs.data(), n_out, jobs.data(), n_out, false, raised, next, rows, s + 1 < n_ras ? rows_next : nullptr);
         raised = next;
+        rows = rows_next;
         if (rc != HE_OK) return rc;
         std::swap(cur, nxt);
     }
@@ -870,6 +875,7 @@ extern "C" int32_t he_ca_ra_block(he_ctx* ctx, const he_block_plan* plan, const 
             if (rc != HE_OK) return rc;
             std::swap(cur, nxt);
         }
+        u64 *in_rows = nullptr, *next_rows = n_ras > 1 && !hoisted_ras && ks_engine_next_rows(ctx, lv, g, g) ? acc : nullptr;      // (as in he_conv2d)
         for (uint32_t s = 0; s < n_ras && !hoisted_ras; s++) {
             std::vector<KsSrc> srcs(g);
             std::vector<KsJob> jobs(g);
@@ -877,8 +883,9 @@ extern "C" int32_t he_ca_ra_block(he_ctx* ctx, const he_block_plan* plan, const 
                 srcs[o] = {cur[o], cur[o] + pe_mid, cur[o], cur[o] + pe_mid};
                 jobs[o] = {o, ras_g[s], ras_key[s], nxt[o], nxt[o] + pe_mid, 1};
             }
-            rc = ks_engine(ctx, lv, srcs.data(), g, jobs.data(), g);
+            rc = ks_engine(ctx, lv, srcs.data(), g, jobs.data(), g, false, nullptr, nullptr, in_rows, s + 1 < n_ras ? next_rows : nullptr);
             if (rc != HE_OK) return rc;
+            in_rows = next_rows;
             std::swap(cur, nxt);
         }
         // Square: integer lift and tensor product, relinearisation, Rescale -> ct3, all g at once

@@ -178,7 +178,8 @@ __global__ __launch_bounds__(EW_THREADS) void square_lift_kernel(const u64* __re
 
 // The same products where a key switch follows, which begins with the inverse rows of d2 (rings from 2^13): a wavefront takes the 256 points of a
 // row, 4 a lane, and transforms its d2 in LDS before it ends, so d2 is not read back and a launch is saved: a product and its rescale at level 11 of
-// N = 2^16 114.9 -> 112.9 us, a block with eight squares of six limbs 1 % less.  Bound by its bytes, for a single product by the chain.  LIFT: square_lift_kernel, else tensor_kernel
+// N = 2^16 114.9 -> 112.9 us, a product at level 23 189.6 -> 184.7, a block with eight squares of nine limbs 1609 -> 1602.  Bound by its bytes, for a
+// single product by the chain.  LIFT: square_lift_kernel, else tensor_kernel
 // (n = 1).  grid: (N/1024, L1, n); the inverse rows go to r.out [n][L1][N].
 template <int W>
 __device__ __forceinline__ void tensor_row(u64* buf, const RowsOut& r, size_t at_row, uint32_t limb, uint32_t row, uint32_t lane, const ModConst& m, uint32_t logN) {

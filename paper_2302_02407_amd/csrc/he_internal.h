@@ -207,6 +207,7 @@ struct KsRows {
     const u64* self1[HE_MAX_KS_JOBS];
     u64* out0[HE_MAX_KS_JOBS];
     u64* out1[HE_MAX_KS_JOBS];
+    u64* next[HE_MAX_KS_JOBS];          // receives the inverse rows of out1 (null: not wanted)
     uint32_t g[HE_MAX_KS_JOBS];
     u64* mid;
     const u64* pinv;     // [nq]
@@ -333,15 +334,17 @@ struct KsJob {
 // Runs every job: one ModUp per source, then inner product + ModDown per job, batched.
 // src_rows: ks_engine_src_rows holds the sources' inverse rows already; raised: their raised digits, which
 // the call takes from there; raised_next: where the raised digits of the second components of its results go (sr_moddown_raises), for as many jobs,
-// one a source and all under one key, as one launch set takes.
+// one a source and all under one key, as one launch set takes.  rows: [n_src][level+1][N] outside the engine's workspace, the sources' inverse
+// rows; rows_next: receives those of the second components of its results, one job a source (both: ks_engine_next_rows; may be the same).
 int32_t ks_engine(he_ctx* ctx, uint32_t level, const KsSrc* srcs, uint32_t n_src, const KsJob* jobs, uint32_t n_jobs, bool src_rows = false,
-                  const u64* raised = nullptr, u64* raised_next = nullptr);
+                  const u64* raised = nullptr, u64* raised_next = nullptr, u64* rows = nullptr, u64* rows_next = nullptr);
 // Whether the engine raises all sources and runs all jobs at once; raised digits of n sources: ks_raised_elems
 bool ks_engine_at_once(const he_ctx* ctx, uint32_t level, uint32_t n_src, uint32_t n_jobs);
 size_t ks_raised_elems(const he_ctx* c, uint32_t level, uint32_t n);
 // Where the inverse rows of the sources [n_src][level+1][N] go (in a workspace that is large enough), if the engine can start from them: its
 // conversion does the columns, and it raises all sources at once.  Null otherwise.
 u64* ks_engine_src_rows(const he_ctx* ctx, uint32_t level, uint32_t n_src, uint32_t n_jobs);
+bool ks_engine_next_rows(const he_ctx* ctx, uint32_t level, uint32_t n_src, uint32_t n_jobs);
 size_t ks_engine_ws_elems(const he_ctx* c, uint32_t level, uint32_t n_src, uint32_t n_jobs);
 // Sum of rotations with one ModDown for the whole sum.  Terms with g == 1 are added as they are (evk unused).
 #define HE_MAX_SUM_TERMS 49

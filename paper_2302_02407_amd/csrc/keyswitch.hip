@@ -688,7 +688,7 @@ static bool same_key(const KsJob& a, const KsJob& b) { return a.evk == b.evk && 
 // raised_of[i] / srcs give job i's raised digits and source; scratch: acc, tmp_dn, conv.  rows_left: the digits' rows are not
 // transformed yet.
 static int32_t inner_moddown_batch(he_ctx* c, uint32_t level, const KsSrc* srcs, const KsJob* jobs, const u64* const* raised_of,
-                                   uint32_t J, u64* acc, u64* tmp_dn, u64* conv, bool rows_left, u64* raised_next) {
+                                   uint32_t J, u64* acc, u64* tmp_dn, u64* conv, bool rows_left, u64* raised_next, u64* rows_next) {
     const uint32_t N = c->N, L1 = level + 1, k = c->np, R = L1 + k, beta = num_digits(c, level);
     if (c->prof_on) {                                   // one pass over a key for each run of jobs that use it (the caller sorts them)
         uint32_t runs = 0;
@@ -708,6 +708,7 @@ static int32_t inner_moddown_batch(he_ctx* c, uint32_t level, const KsSrc* srcs,
             a.self0[i] = jobs[i].add_self ? src.s0 : nullptr;
             a.self1[i] = jobs[i].add_self ? src.s1 : nullptr;
             a.out0[i] = jobs[i].out0; a.out1[i] = jobs[i].out1;
+            a.next[i] = rows_next ? rows_next + (size_t)jobs[i].src * L1 * N : nullptr;
             if (a.c0[i]) c->cnt.automorph += L1;
         }
         int32_t rc = moddown_chain(c, level, J, acc, tmp_dn, conv, ModDownEpilogue{}, &a);
@@ -758,6 +759,10 @@ u64* ks_engine_src_rows(const he_ctx* c, uint32_t level, uint32_t n_src, uint32_
     return two_pass(c) && modup_by_columns(c, level) && n_src <= cb ? c->d_ws + ks_engine_ws(c, level, cb, jb).tmp_up : nullptr;
 }
 
+bool ks_engine_next_rows(const he_ctx* c, uint32_t level, uint32_t n_src, uint32_t n_jobs) {
+    return n_src == n_jobs && ks_rows_path(c, level) && ks_engine_src_rows(c, level, n_src, n_jobs);
+}
+
 bool ks_engine_at_once(const he_ctx* c, uint32_t level, uint32_t n_src, uint32_t n_jobs) {
     uint32_t cb, jb;
     engine_shape(c, level, n_src, n_jobs, cb, jb);
@@ -766,8 +771,9 @@ bool ks_engine_at_once(const he_ctx* c, uint32_t level, uint32_t n_src, uint32_t
 size_t ks_raised_elems(const he_ctx* c, uint32_t level, uint32_t n) { return (size_t)n * num_digits(c, level) * (level + 1 + c->np) * c->N; }
 
 int32_t ks_engine(he_ctx* c, uint32_t level, const KsSrc* srcs, uint32_t n_src, const KsJob* jobs, uint32_t n_jobs, bool src_rows,
-                  const u64* raised_in, u64* raised_next) {
+                  const u64* raised_in, u64* raised_next, u64* rows_in, u64* rows_next) {
     if (n_jobs == 0) return HE_OK;
+    if ((rows_in || rows_next) && !ks_engine_next_rows(c, level, n_src, n_jobs)) return he_fail(c, HE_ERR_BADARG, "key switch: inverse rows of a shape that has none");
     if ((raised_in || raised_next) && !ks_engine_at_once(c, level, n_src, n_jobs)) return he_fail(c, HE_ERR_BADARG, "key switch: more raised digits than one launch set takes");
     const uint32_t N = c->N, R = level + 1 + c->np, beta = num_digits(c, level);
     if (2 * c->np > HE_MAX_MODULI) return he_fail(c, HE_ERR_BADARG, "key switch: more than %d special primes", HE_MAX_MODULI / 2);
@@ -776,7 +782,7 @@ int32_t ks_engine(he_ctx* c, uint32_t level, const KsSrc* srcs, uint32_t n_src, 
     uint32_t cb, jb;
     engine_shape(c, level, n_src, n_jobs, cb, jb);
     const KsEngineWs w = ks_engine_ws(c, level, cb, jb);
-    u64 *raised = c->d_ws, *tmp_up = c->d_ws + w.tmp_up, *tmp_dn = c->d_ws + w.tmp_dn, *conv = c->d_ws + w.conv, *acc = c->d_ws + w.acc;
+    u64 *raised = c->d_ws, *tmp_up = rows_in ? rows_in : c->d_ws + w.tmp_up, *tmp_dn = c->d_ws + w.tmp_dn, *conv = c->d_ws + w.conv, *acc = c->d_ws + w.acc;
     // jobs ordered by source wave, then by key so that equal keys are adjacent
     std::vector<uint32_t> order(n_jobs);
     for (uint32_t i = 0; i < n_jobs; i++) order[i] = i;
@@ -796,7 +802,7 @@ int32_t ks_engine(he_ctx* c, uint32_t level, const KsSrc* srcs, uint32_t n_src, 
         bool rows_left = ks_rows_path(c, level);
         uint32_t uses[HE_MAX_SEGS] = {0};
         for (size_t i = pos; i < end; i++) rows_left = rows_left && ++uses[jobs[order[i]].src - s0] == 1;
-        if (!raised_in) rc = modup_batch(c, srcs + s0, ns, level, raised, tmp_up, !rows_left, src_rows);
+        if (!raised_in) rc = modup_batch(c, srcs + s0, ns, level, raised, tmp_up, !rows_left, src_rows || rows_in);
         if (rc != HE_OK) return rc;
         while (pos < end) {
             uint32_t J = (uint32_t)std::min<size_t>(jb, end - pos);
@@ -813,7 +819,7 @@ int32_t ks_engine(he_ctx* c, uint32_t level, const KsSrc* srcs, uint32_t n_src, 
                 chunk[i] = jobs[order[pos + i]];
                 raised_of[i] = (raised_in ? raised_in : raised) + (size_t)(chunk[i].src - s0) * beta * R * N;
             }
-            rc = inner_moddown_batch(c, level, srcs, chunk, raised_of, J, acc, tmp_dn, conv, rows_left, raised_next);
+            rc = inner_moddown_batch(c, level, srcs, chunk, raised_of, J, acc, tmp_dn, conv, rows_left, raised_next, rows_next);
             if (rc != HE_OK) return rc;
             pos += J;
         }

@@ -295,7 +295,27 @@ __device__ __forceinline__ void ks_row_transformed(u64 (&cv)[NX][4], u64* buf, c
     for (int c = 0; c < NX; c++) kr.get(cv[c], buf + 256 * c);
     wave_exchange();
 }
-template <int W, int NX>
+// Inverse rows of a result's second component, where it is what the next key switch raises: the row is in LDS already, and its digits are used
+// once (not DONE: no registers or branch there).  A step of a rotate-and-sum loses the launch it began with.  us before/now, N = 2^16: layer of 16 channels,
+// 8 outputs, level 5, 993/950, with its taps deferred and 3 outputs at level 6 831/809, block at level 6 1490/1453; at level 23, where the rows fill the
+// vector units, 3268/3258.  In the kernel of small launches a branch for it cost one rotation 51.9 -> 52.7, so that has two forms (NEXT).
+template <int W>
+__device__ __forceinline__ void ks_row_next(const KsRows& a, uint32_t job, uint32_t r, uint32_t b, uint32_t t, u64* buf, const ModConst& m, const KrRow& kr, const u64 (&o)[4]) {
+    u64 w[4][6], x[1][4];
+    kr.put(buf, o);
+    SCHED_FENCE();
+    asm("" : "+v"(t));                                   // what follows from the lane is worked out anew, not kept in registers
+    const Row4 at(t);
+    tw_row4(w, a.itw + ((size_t)r << a.logN), a.logN - 8, b, t);
+    wave_exchange();
+    at.load(3, x[0], buf);
+    wave_exchange();
+    row4_inv<kr_inv(W), 1>(x, w, buf, 256, at, m.q, m);
+    u64* out = a.next[job] + ((size_t)r << a.logN) + b * 256;
+#pragma unroll
+    for (int k = 0; k < 4; k++) out[t + 64 * k] = x[0][k];
+}
+template <int W, int NX, bool NEXT>
 __device__ __forceinline__ void ks_row_down(const KsRows& a, uint32_t job, uint32_t c0, uint32_t r, uint32_t b, uint32_t t, u64* buf, const ModConst& m,
                                             const KrRow& kr, u64 (&cv)[NX][4], const u64 (&v)[NX][4], KrAdd<NX>& ad) {
     const uint32_t row0 = b * 256;
@@ -320,6 +340,7 @@ __device__ __forceinline__ void ks_row_down(const KsRows& a, uint32_t job, uint3
             o[k] = reduce_min<7>(split_acc(ad.add[c][k], v[c][k] + bias - cv[c][k], pinv, pinv_sh, pinv_h, n2q), m.q, m.bits, m.rec);
         store2_stream(out, o[0], o[1]);
         store2_stream(out + 128, o[2], o[3]);
+        if (NEXT && c0 + c == 1 && a.next[job]) ks_row_next<W>(a, job, r, b, t, buf, m, kr, o);
     }
 }
 // v = (v + sums) below 2q, the sums empty again
@@ -373,7 +394,7 @@ __device__ __forceinline__ void ks_row(const KsRows& a, uint32_t job, uint32_t r
         KrAdd<2> ad;
         ad.load(a, job, 0, r, b, t, kr.bs);
         ks_row_transformed<W, 2>(cv, buf, m, Row4(t), kr, w);
-        ks_row_down<W, 2>(a, job, 0, r, b, t, buf, m, kr, cv, v, ad);
+        ks_row_down<W, 2, !DONE>(a, job, 0, r, b, t, buf, m, kr, cv, v, ad);
     }
 }
 // One wavefront: one component of that, from digits that are transformed already.  buf: two rows.
@@ -396,11 +417,11 @@ __device__ __forceinline__ void ks_row_half(const KsRows& a, uint32_t job, uint3
     SCHED_FENCE();
     kr_flush(v, s, m);
     if (SP) ks_row_special<W, 1>(a, job, c, r, b, t, buf, m, Row4(t), kr, w, v);
-    else ks_row_down<W, 1>(a, job, c, r, b, t, buf, m, kr, cv, v, ad);
+    else ks_row_down<W, 1, false>(a, job, c, r, b, t, buf, m, kr, cv, v, ad);
 }
 // A work group of nw wavefronts: row b of limb r, the terms (SUM) or the digits spread over the wavefronts; the first two then take
 // a component each.  buf: LDS of the work group, max(beta, 2) rows a wavefront.
-template <int W, bool SP, bool SUM, bool DONE>
+template <int W, bool SP, bool SUM, bool DONE, bool NEXT>
 __device__ __forceinline__ void ks_row_group(const KsRows& a, uint32_t job, uint32_t r, uint32_t b, uint32_t wave, uint32_t nw, uint32_t t, u64* buf) {
     const uint32_t mi = SP ? a.nq + r : r, lc = a.logN - 8;
     const ModConst m = mod_const(a.mc, mi);
@@ -456,7 +477,7 @@ __device__ __forceinline__ void ks_row_group(const KsRows& a, uint32_t job, uint
     if (SP) ks_row_special<W, 1>(a, job, wave, r, b, t, mine, m, Row4(t), kr, w, sum);
     else {
         ks_row_transformed<W, 1>(cv, mine, m, Row4(t), kr, w);
-        ks_row_down<W, 1>(a, job, wave, r, b, t, mine, m, kr, cv, sum, ad);
+        ks_row_down<W, 1, NEXT>(a, job, wave, r, b, t, mine, m, kr, cv, sum, ad);
     }
 }
 
@@ -515,7 +536,7 @@ __global__ __launch_bounds__(KR_THREADS, 4) void ks_rows_half_kernel(KsRows a) {
     else ks_row_half<3, SP>(a, job, at & 1u, kr_pin<3>(r), b, t, buf);
 }
 // A work group per (limb, row) of a sum, or per (limb, row, job).
-template <bool SP, bool SUM, bool DONE>
+template <bool SP, bool SUM, bool DONE, bool NEXT = false>
 __global__ __launch_bounds__(KR_THREADS, SUM && DONE ? 2 : 3) void ks_rows_group_kernel(KsRows a) {
     ieee_off();
     extern __shared__ __attribute__((aligned(16))) u64 sm[];
@@ -523,12 +544,12 @@ __global__ __launch_bounds__(KR_THREADS, SUM && DONE ? 2 : 3) void ks_rows_group
     const uint32_t item = blockIdx.x >> 3, un = item / a.J, job = item - un * a.J;
     const uint32_t u = un * 8 + (blockIdx.x & 7u), r = u >> rows, b = u & ((1u << rows) - 1u);
     const uint32_t width = kr_width(a, SP ? a.nq + r : r);
-    if (width == 4) ks_row_group<4, SP, SUM, DONE>(a, job, kr_pin<4>(r), b, wave, nw, t, sm);
-    else if (width == 5) ks_row_group<5, SP, SUM, DONE>(a, job, kr_pin<5>(r), b, wave, nw, t, sm);
-    else if (width == 0) ks_row_group<0, SP, SUM, DONE>(a, job, kr_pin<0>(r), b, wave, nw, t, sm);
-    else if (width == 1) ks_row_group<1, SP, SUM, DONE>(a, job, kr_pin<1>(r), b, wave, nw, t, sm);
-    else if (width == 2) ks_row_group<2, SP, SUM, DONE>(a, job, kr_pin<2>(r), b, wave, nw, t, sm);
-    else ks_row_group<3, SP, SUM, DONE>(a, job, kr_pin<3>(r), b, wave, nw, t, sm);
+    if (width == 4) ks_row_group<4, SP, SUM, DONE, NEXT>(a, job, kr_pin<4>(r), b, wave, nw, t, sm);
+    else if (width == 5) ks_row_group<5, SP, SUM, DONE, NEXT>(a, job, kr_pin<5>(r), b, wave, nw, t, sm);
+    else if (width == 0) ks_row_group<0, SP, SUM, DONE, NEXT>(a, job, kr_pin<0>(r), b, wave, nw, t, sm);
+    else if (width == 1) ks_row_group<1, SP, SUM, DONE, NEXT>(a, job, kr_pin<1>(r), b, wave, nw, t, sm);
+    else if (width == 2) ks_row_group<2, SP, SUM, DONE, NEXT>(a, job, kr_pin<2>(r), b, wave, nw, t, sm);
+    else ks_row_group<3, SP, SUM, DONE, NEXT>(a, job, kr_pin<3>(r), b, wave, nw, t, sm);
 }
 
 int32_t launch_ks_rows(he_ctx* ctx, KsRows& a, bool special) {
@@ -536,6 +557,7 @@ int32_t launch_ks_rows(he_ctx* ctx, KsRows& a, bool special) {
     if (a.J == 0 || a.J > HE_MAX_KS_JOBS || a.n_terms == 0 || a.n_terms > HE_MAX_KS_JOBS || (a.sum && a.J != 1) || (!a.sum && a.n_terms != 1) ||
         a.beta == 0 || a.beta > 8 || ctx->logN < 13 || ctx->logN > 17 || limbs == 0 || limbs > HE_MAX_MODULI)
         return he_fail(ctx, HE_ERR_BADARG, "key-switch rows: bad shape");
+    if (a.next[0] && (a.sum || a.done)) return he_fail(ctx, HE_ERR_BADARG, "key-switch rows: inverse rows of sums or from complete digits");
     a.mc = ctx->d_mc; a.tw = ctx->d_tw; a.itw = ctx->d_itw; a.logN = ctx->logN;
     a.wide_fwd = a.wide_inv = a.widest = a.near_fwd = a.near_inv = 0;
     for (uint32_t i = 0; i < ctx->M; i++) {
@@ -563,6 +585,7 @@ int32_t launch_ks_rows(he_ctx* ctx, KsRows& a, bool special) {
         if (a.sum && a.done) KR_LAUNCH(ks_rows_group_kernel<SP, true, true>);                                                       \
         else if (a.sum) KR_LAUNCH(ks_rows_group_kernel<SP, true, false>);                                                           \
         else if (half) KR_LAUNCH(ks_rows_half_kernel<SP>);                                                                          \
+        else if (group && a.next[0]) KR_LAUNCH(ks_rows_group_kernel<SP, false, false, !SP>);                                        \
         else if (group) KR_LAUNCH(ks_rows_group_kernel<SP, false, false>);                                                          \
         else if (many && a.done) KR_LAUNCH(ks_rows_kernel<SP, true, true>);                                                         \
         else if (many) KR_LAUNCH(ks_rows_kernel<SP, true, false>);                                                                  \
