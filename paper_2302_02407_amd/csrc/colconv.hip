@@ -26,7 +26,6 @@
 // Asking for the round's list before the sources takes one rotation at level 5 from 57.3 to 56.8 us, with six digits at level 6 from
 // 61.0 to 59.6; asking for the operands themselves as well gave nothing.
 #include <algorithm>
-#include <type_traits>
 
 #include "modarith.h"
 #include "ntt_blocks.h"
@@ -235,24 +234,6 @@ __device__ __forceinline__ void c4_target(u64* reg, u64* dst, uint32_t mi, const
     for (int k = 0; k < 4; k++) dst[G::at(c4_point(G::NB - 1, t, k), c0)] = x[k];
 }
 
-// f(std::integral_constant<int, W>, mi) for the class W of modulus mi, whose copies' loads are kept apart (see ntt2p.hip)
-template <class F>
-__device__ __forceinline__ void cc_class(u64 near, u64 wide, u64 widest, uint32_t mi, F&& f) {
-    if (near >> mi & 1u) {
-        asm("; near" : "+s"(mi));
-        f(std::integral_constant<int, W_NEAR>(), mi);
-    } else if (!(wide >> mi & 1u)) {
-        asm("; narrow" : "+s"(mi));
-        f(std::integral_constant<int, 0>(), mi);
-    } else if (!(widest >> mi & 1u)) {
-        asm("; wide" : "+s"(mi));
-        f(std::integral_constant<int, 1>(), mi);
-    } else {
-        asm("; widest" : "+s"(mi));
-        f(std::integral_constant<int, 2>(), mi);
-    }
-}
-
 // The lane's number: what follows from it is worked out anew, not kept in registers
 __device__ __forceinline__ uint32_t lane_again() {
     uint32_t l;
@@ -307,7 +288,7 @@ __global__ __launch_bounds__(CC_THREADS, 4) void col_conv_kernel(ColConv cc, Sca
     if (w < st.ns) {
         const u64* src = st.src + (size_t)rep * cc.src_stride + ((size_t)w << (LC + 8));
         const uint32_t mi = st.mod0 + w;
-        cc_class(cc.near_inv, cc.wide_inv, cc.widest, mi, [&](auto W, uint32_t m) {
+        by_class(cc.inv, mi, mi, [&](auto W, uint32_t m) {
             if constexpr (PTS == 4) c4_source<LC, W>(reg, src, sc, m, st.sc0 + w, lane, c0, mc, itw);
             else cc_source<LC, W>(reg, src, cc, sc, m, st.sc0 + w, lane, c0, mc, itw);
         });
@@ -374,7 +355,7 @@ __global__ __launch_bounds__(CC_THREADS, 4) void col_conv_kernel(ColConv cc, Sca
         ln = lane_again();
         if (have) {
             u64* dst = st.dst + (size_t)rep * cc.dst_stride + ((size_t)li << (LC + 8));
-            cc_class(cc.near_fwd, cc.wide_fwd, cc.widest, mi, [&](auto W, uint32_t m) {
+            by_class(cc.fwd, mi, mi, [&](auto W, uint32_t m) {
                 if constexpr (PTS == 4) c4_target<LC, W>(reg, dst, m, w4, ln, c0, mc, before);
                 else cc_target<LC, W>(reg, dst, m, w1, ln, c0, mc, ftw, before);
             });

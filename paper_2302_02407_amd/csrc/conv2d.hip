@@ -126,11 +126,7 @@ __global__ __launch_bounds__(CV_THREADS) void mac_many_kernel(MacMany a, const M
     if constexpr (ROWS) {
         u64* out = a.rows.to.out + ((size_t)limb << logN);
         const size_t stride = (size_t)CL << logN;
-        const ulonglong2* tw = a.rows.to.itw + ((size_t)mi << logN);
-        if (a.rows.to.near_inv >> mi & 1u) mac_rows<W_NEAR>(tiles, held, out, stride, m, tw, logN);
-        else if (!(a.rows.to.wide_inv >> mi & 1u)) mac_rows<0>(tiles, held, out, stride, m, tw, logN);
-        else if (!(a.rows.to.widest >> mi & 1u)) mac_rows<1>(tiles, held, out, stride, m, tw, logN);
-        else mac_rows<2>(tiles, held, out, stride, m, tw, logN);
+        by_class(a.rows.to.inv, mi, mi, [&](auto W, uint32_t v) { mac_rows<W>(tiles, held, out, stride, m, a.rows.to.itw + ((size_t)v << logN), logN); });
     }
 }
 

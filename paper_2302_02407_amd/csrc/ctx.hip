@@ -100,7 +100,7 @@ uint32_t h_galois_of_step(const he_ctx* ctx, int32_t step) {
 void scale_entry(const he_ctx* c, ScaleList& sc, uint32_t i, uint32_t mi, u64 s) {
     const u64 m = c->mod[mi];
     const u64 w = h_mulmod(s, c->itw1[mi], m);
-    if (two_pass(c) && near_inv(m)) {
+    if (two_pass(c) && class_inv(m) == W_NEAR) {
         const HMul by32((1ull << 32) % m, m);
         const ulonglong2 fs = h_near_factor(s, by32), fw = h_near_factor(w, by32);
         sc.s[i] = fs.x; sc.s_sh[i] = fs.y;
@@ -204,7 +204,10 @@ int32_t he_ctx_create(he_ctx** out, uint32_t logN, const uint64_t* h_q, uint32_t
         u64 ipsi = h_invmod(psi, m);
         u64 pw = 1, ipw = 1;
         const HMul by_psi(psi, m), by_ipsi(ipsi, m), by32((1ull << 32) % m, m);
-        const bool nf = logN > 12 && near_fwd(m, logN), ni = logN > 12 && near_inv(m);
+        const bool nf = logN > 12 && class_fwd(m, logN) == W_NEAR, ni = logN > 12 && class_inv(m) == W_NEAR;
+        c->cls_fwd.set(i, class_fwd(m, logN));
+        c->cls_inv.set(i, class_inv(m));
+        for (int b = 0; b < 3; b++) c->ks_width[b] |= (u64)(ks_width(m, logN) >> b & 1u) << i;
         ulonglong2* t = &tw[(size_t)i * N];
         ulonglong2* it = &itw[(size_t)i * N];
         for (uint32_t e = 0; e < N; e++) {                      // psi^e stored at bitrev(e)

@@ -231,10 +231,7 @@ __global__ __launch_bounds__(EW_THREADS) void tensor_rows_kernel(const u64* __re
     }
     wave_exchange();
     const size_t at_row = pe * blockIdx.z + o;
-    if (r.near_inv >> limb & 1u) tensor_row<W_NEAR>(buf, r, at_row, limb, row, lane, m, logN);
-    else if (!(r.wide_inv >> limb & 1u)) tensor_row<0>(buf, r, at_row, limb, row, lane, m, logN);
-    else if (!(r.widest >> limb & 1u)) tensor_row<1>(buf, r, at_row, limb, row, lane, m, logN);
-    else tensor_row<2>(buf, r, at_row, limb, row, lane, m, logN);
+    by_class(r.inv, limb, limb, [&](auto W, uint32_t v) { tensor_row<W>(buf, r, at_row, v, row, lane, m, logN); });
 }
 
 int32_t launch_tensor(he_ctx* ctx, const u64* a, const u64* b, uint32_t level, u64* d, u64* rows) {

@@ -38,6 +38,20 @@ static inline bool near_fwd(u64 q, uint32_t logN) {
     return near_top(q) ? logN <= 16 && q <= (1ull << 59) + (1ull << 50) && near_word(q, 1ll << 26) : near_word(q, 1ll << 27);
 }
 static inline bool near_inv(u64 q) { return near_word(q, 1ll << 27) && q <= (1ull << 63) / 550; }      // up to 2^53.896
+// The classes (ntt_blocks.h), and those of all moduli of a context, bit by bit: kernels of short launches ask for both words along with their
+// first arguments, so that the branch to a class waits for no load of its own (inverse rows of one polynomial of six limbs 5.6 -> 5.5 us).
+#define W_NEAR 3
+static inline uint32_t class_fwd(u64 q, uint32_t logN) { return near_fwd(q, logN) ? W_NEAR : narrow_fwd(q) ? 0 : widest(q) ? 2 : 1; }
+static inline uint32_t class_inv(u64 q) { return near_inv(q) ? W_NEAR : narrow_inv(q) ? 0 : widest(q) ? 2 : 1; }
+// W of a modulus in the row kernels of key switches (ksrows.hip), for both directions; what is near for the inverse is so for the forward
+static inline uint32_t ks_width(u64 q, uint32_t logN) {
+    if (near_fwd(q, logN)) return near_inv(q) ? 4 : 5;
+    return (uint32_t)!narrow_inv(q) + (uint32_t)!narrow_fwd(q) + (uint32_t)widest(q);
+}
+struct ModClasses {
+    u64 b[2];
+    void set(uint32_t mi, uint32_t w) { for (int i = 0; i < 2; i++) b[i] |= (u64)(w >> i & 1u) << mi; }
+};
 
 // Per-modulus constants, resident on the device (array indexed by modulus index).
 struct ModConst {
@@ -98,6 +112,8 @@ struct he_ctx {
     u64 psi[HE_MAX_MODULI];
     u64 itw1[HE_MAX_MODULI];    // psi^-(N/2), the single twiddle of inverse stage 0
     ModConst h_mc[HE_MAX_MODULI];
+    ModClasses cls_fwd, cls_inv;
+    u64 ks_width[3];            // of all moduli, bit by bit
     // device tables
     ModConst* d_mc;    // [M]
     ulonglong2* d_tw;  // [M][N]  psi^bitrev(i) and its companion (h_companion), one 16-byte load
@@ -218,7 +234,7 @@ struct KsRows {
     uint32_t count_up, count_down;      // whether the digits' / the ModDown's transforms are counted with these rows
     // set by the launch
     uint32_t logN;
-    u64 wide_fwd, wide_inv, widest, near_fwd, near_inv;     // as in ColConv
+    u64 width[3];        // ks_width
     const ModConst* mc;
     const ulonglong2 *tw, *itw;
 };
@@ -264,7 +280,7 @@ struct ColConvSet {
 struct ColConv {
     ColConvSet set[CC_MAX_SETS];
     size_t src_stride, dst_stride;
-    u64 wide_fwd, wide_inv, widest, near_fwd, near_inv;    // bit per modulus (narrow_fwd, narrow_inv, widest, near_fwd, near_inv)
+    ModClasses fwd, inv;
     uint32_t n_sets;
     uint32_t share;            // targets of a work group of those that share a tile (set by the launch)
 };
@@ -275,7 +291,7 @@ struct RescaleCols {
     const u64* src;
     u64* dst;
     uint32_t level, parts, share;      // work groups that share a tile's moduli, `share` each (set by the launch)
-    u64 wide_fwd, wide_inv, widest, near_fwd, near_inv;    // as in ColConv
+    ModClasses fwd, inv;
 };
 bool rescale_cols_pays(const he_ctx* ctx, uint32_t n, uint32_t level);
 int32_t launch_rescale_cols(he_ctx* ctx, const u64* src, u64* dst, uint32_t n, uint32_t level);
@@ -294,21 +310,13 @@ struct AffineConst {
     u64 mul[HE_MAX_MODULI], add[HE_MAX_MODULI];
 };
 int32_t launch_affine(he_ctx* ctx, const u64* ct, uint32_t level, const AffineConst& k, u64* out);   // out may alias ct
-// Inverse rows that a launch takes along of polynomials it forms (out null: none), and what they need; a bit per modulus
+// Inverse rows that a launch takes along of polynomials it forms (out null: none), and what they need
 struct RowsOut {
     u64* out;                            // [polynomials][limbs][N]
     const ulonglong2* itw;
-    u64 wide_inv, widest, near_inv;      // not narrow_inv; widest; near_inv
+    ModClasses inv;
 };
-static inline RowsOut rows_out(const he_ctx* ctx, u64* out) {
-    RowsOut r = {out, ctx->d_itw, 0, 0, 0};
-    for (uint32_t i = 0; i < ctx->M; i++) {
-        r.wide_inv |= (u64)!narrow_inv(ctx->mod[i]) << i;
-        r.widest |= (u64)widest(ctx->mod[i]) << i;
-        r.near_inv |= (u64)near_inv(ctx->mod[i]) << i;
-    }
-    return r;
-}
+static inline RowsOut rows_out(const he_ctx* ctx, u64* out) { return {out, ctx->d_itw, ctx->cls_inv}; }
 // tensor squares of mul*u, n ciphertexts, and tensor products: d = [d0][d1][d2], each [level+1][N].  rows: receives the inverse rows of every d2 (null: not wanted)
 int32_t launch_square_lift(he_ctx* ctx, const u64* u, uint32_t n, uint32_t level, const u64* mul, u64* d, u64* rows);
 int32_t launch_tensor(he_ctx* ctx, const u64* a, const u64* b, uint32_t level, u64* d, u64* rows);

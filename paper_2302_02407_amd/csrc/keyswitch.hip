@@ -275,7 +275,7 @@ static void conv_operand(const u64* hat, uint32_t ns, const ModConst& mc, uint32
     op.nq = 0 - m;
     op.rec = mc.rec;
     op.bits = mc.bits;
-    op.centre = near_top(m) && near_fwd(m, logN) ? (uint32_t)(m >> 32) : 0;
+    op.centre = near_top(m) && class_fwd(m, logN) == W_NEAR ? (uint32_t)(m >> 32) : 0;
 }
 
 int32_t ks_init_tables(he_ctx* c) {
@@ -452,16 +452,6 @@ size_t ks_engine_ws_elems(const he_ctx* c, uint32_t level, uint32_t n_src, uint3
     return ks_engine_ws(c, level, engine_most_sources(level, n_src, jb), jb).total;
 }
 
-static void col_conv_widths(const he_ctx* c, ColConv& cc) {
-    for (uint32_t m = 0; m < c->M; m++) {
-        cc.wide_fwd |= (u64)!narrow_fwd(c->mod[m]) << m;
-        cc.wide_inv |= (u64)!narrow_inv(c->mod[m]) << m;
-        cc.widest |= (u64)widest(c->mod[m]) << m;
-        cc.near_fwd |= (u64)near_fwd(c->mod[m], c->logN) << m;
-        cc.near_inv |= (u64)near_inv(c->mod[m]) << m;
-    }
-}
-
 static bool modup_by_columns(const he_ctx* c, uint32_t level) {
     const uint32_t beta = num_digits(c, level);
     return c->d_up_op && beta <= CC_MAX_SETS && beta * (level + 1 + c->np) <= HE_MAX_LAUNCH_LIMBS;
@@ -501,7 +491,7 @@ static int32_t modup_batch(he_ctx* c, const KsSrc* srcs, uint32_t cb, uint32_t l
     const uint32_t aw = pad8(al);
     if (cc_on) {
         ColConv cc = {};
-        col_conv_widths(c, cc);
+        cc.fwd = c->cls_fwd; cc.inv = c->cls_inv;
         cc.n_sets = beta; cc.src_stride = (size_t)L1 * N; cc.dst_stride = (size_t)beta * R * N;
         uint32_t passes = 0;
         for (uint32_t j = 0; j < beta; j++) {
@@ -643,7 +633,7 @@ static int32_t moddown_chain(he_ctx* c, uint32_t level, uint32_t J, u64* acc, u6
     if (rc != HE_OK) return rc;
     if (cc_on) {
         ColConv cc = {};
-        col_conv_widths(c, cc);
+        cc.fwd = c->cls_fwd; cc.inv = c->cls_inv;
         cc.n_sets = 1; cc.src_stride = (size_t)k * N; cc.dst_stride = (size_t)L1 * N;
         ColConvSet& st = cc.set[0];
         st.src = tmp_dn; st.dst = conv; st.op = c->d_dn_op;
@@ -1315,6 +1305,8 @@ __device__ __forceinline__ void hoisted_sum_rows(u64* rows, u64* __restrict__ mi
     }
 }
 
+__device__ __forceinline__ ModClasses classes_of(uint32_t two_bits) { return {{two_bits, two_bits >> 1}}; }
+
 template <int JT>
 __global__ __launch_bounds__(KS_THREADS, 3) void hoisted_sum_ip_local_kernel(HoistIp a, LimbSel sel, u64* __restrict__ acc,
                                                                              const ModConst* mc, uint32_t logN, uint32_t R,
@@ -1329,14 +1321,8 @@ __global__ __launch_bounds__(KS_THREADS, 3) void hoisted_sum_ip_local_kernel(Hoi
     const ModConst m = mod_const(mc, mi);
     if (init & 4u) {
         constexpr int NX = JT > 4 ? 2 : 1;
-        const ulonglong2* tw = ftw + ((size_t)mi << logN);
         const uint32_t own_j = r <= level ? r / alpha : beta;
-        switch (s >> HSL_FWD) {
-        case 0: hoisted_sum_digits<0, NX>(a, r, m, dig, tw, logN, R, beta, own_j); break;
-        case 1: hoisted_sum_digits<1, NX>(a, r, m, dig, tw, logN, R, beta, own_j); break;
-        case 2: hoisted_sum_digits<2, NX>(a, r, m, dig, tw, logN, R, beta, own_j); break;
-        default: hoisted_sum_digits<W_NEAR, NX>(a, r, m, dig, tw, logN, R, beta, own_j); break;
-        }
+        by_class(classes_of(s >> HSL_FWD), 0, mi, [&](auto W, uint32_t v) { hoisted_sum_digits<W, NX>(a, r, m, dig, ftw + ((size_t)v << logN), logN, R, beta, own_j); });
     }
     if (m.bits > 54) hoisted_sum_ip<JT, true>(a, r, mi, m, dig, acc, logN, R, beta, M, level, alpha, init, rows);
     else hoisted_sum_ip<JT, false>(a, r, mi, m, dig, acc, logN, R, beta, M, level, alpha, init, rows);
@@ -1344,14 +1330,8 @@ __global__ __launch_bounds__(KS_THREADS, 3) void hoisted_sum_ip_local_kernel(Hoi
     asm("" : "+s"(mi));                                  // the constants are read again, not kept
     const ModConst mr = mod_const(mc, mi);
     u64* out = mid + ((size_t)(r - level - 1) << logN);
-    const ulonglong2* tw = itw + ((size_t)mi << logN);
     const uint32_t k = R - level - 1;
-    switch (s >> HSL_INV & 3u) {
-    case 0: hoisted_sum_rows<0>(dig, out, mr, tw, a.J, k, logN); break;
-    case 1: hoisted_sum_rows<1>(dig, out, mr, tw, a.J, k, logN); break;
-    case 2: hoisted_sum_rows<2>(dig, out, mr, tw, a.J, k, logN); break;
-    default: hoisted_sum_rows<W_NEAR>(dig, out, mr, tw, a.J, k, logN); break;
-    }
+    by_class(classes_of(s >> HSL_INV), 0, mi, [&](auto W, uint32_t v) { hoisted_sum_rows<W>(dig, out, mr, itw + ((size_t)v << logN), a.J, k, logN); });
 }
 
 // Whether the Galois elements of a hoisted sum only move values inside aligned blocks of 256 positions, the tile of a
@@ -1455,9 +1435,7 @@ int32_t ks_hoisted_sum(he_ctx* c, uint32_t level, const KsSrc* srcs, uint32_t J,
                 for (uint32_t i = 0; i < R; i++) {
                     const bool special = sel.r[i] > level;
                     const u64 q = c->mod[special ? c->nq + (sel.r[i] - L1) : sel.r[i]];
-                    const uint32_t wide = widest(q) ? 2 : 1, inv = near_inv(q) ? W_NEAR : narrow_inv(q) ? 0 : wide;
-                    const uint32_t fwd = near_fwd(q, c->logN) ? W_NEAR : narrow_fwd(q) ? 0 : wide;
-                    sel.r[i] |= (special && rows_here && t0 + HS_TERMS >= T ? HSL_ROWS : 0) | inv << HSL_INV | fwd << HSL_FWD;
+                    sel.r[i] |= (special && rows_here && t0 + HS_TERMS >= T ? HSL_ROWS : 0) | class_inv(q) << HSL_INV | class_fwd(q, c->logN) << HSL_FWD;
                 }
                 const dim3 grid(N / KS_THREADS, R), blk(KS_THREADS);
                 const size_t lds = (size_t)nb * std::max(beta, rows_here ? 2u : 1u) * KS_THREADS * sizeof(u64);

@@ -19,7 +19,6 @@
 // Arithmetic: ntt_blocks.h.  Forward values are never reduced inside a transform for narrow moduli (16 or 17 stages end
 // below 90q); a small-quotient step makes them canonical at the end.
 #include <algorithm>
-#include <type_traits>
 
 #include "modarith.h"
 #include "ntt_blocks.h"
@@ -27,15 +26,14 @@
 #define P2_THREADS 256
 
 // Limbs of a launch, sorted by modulus: destination limb (bits 0-8), modulus (9-14), source segment (27-30) and limb in it
-// (15-26), wide modulus (31).  One 32-bit word per limb, so that a work group gets all of it in one scalar load, and
-// branches to the code of its modulus' width before it loads anything else (a branch between the loads and their use
-// doubles the registers that are live across it).  No entry is all ones: modulus 63 with segment 15 is never built.
+// (15-26).  One 32-bit word per limb, so that a work group gets all of it in one scalar load, and
+// branches to the code of its modulus' class before it loads anything else (a branch between the loads and their use
+// doubles the registers that are live across it).
 struct LimbTab {
     const u64* seg[HE_MAX_SEGS];
     uint32_t e[HE_MAX_LAUNCH_LIMBS];
 };
 #define TAB_NONE 0xFFFFFFFFu
-#define TAB_WIDE 0x80000000u
 struct P2Args {
     u64* dst;
     const ModConst* mc;
@@ -44,26 +42,8 @@ struct P2Args {
     uint32_t lazy;            // forward, last pass: outputs may stay below 2q
     uint32_t rs_mod;          // forward, first pass reading the Rescale rounding term: modulus index of the dropped limb
     uint32_t log_chunk;       // row passes, see row_decode
-    u64 widest, near;         // bit per modulus; near: of this direction
+    ModClasses cls;           // of this direction
 };
-// f(std::integral_constant<int, W>, e) for the class W of the modulus of entry e.  Keeps the loads of the branches apart: merged above
-// them (they look alike) they would stay live across all of it, 240 registers instead of 109.
-template <class F>
-__device__ __forceinline__ void by_class(const P2Args& a, uint32_t mi, uint32_t e, F&& f) {
-    if (a.near >> mi & 1u) {
-        asm("; near" : "+s"(e));
-        f(std::integral_constant<int, W_NEAR>(), e);
-    } else if (!(e & TAB_WIDE)) {
-        asm("; narrow" : "+s"(e));
-        f(std::integral_constant<int, 0>(), e);
-    } else if (!(a.widest >> mi & 1u)) {
-        asm("; wide" : "+s"(e));
-        f(std::integral_constant<int, 1>(), e);
-    } else {
-        asm("; widest" : "+s"(e));
-        f(std::integral_constant<int, 2>(), e);
-    }
-}
 __device__ __forceinline__ uint32_t tab_dst(uint32_t e) { return e & 511u; }
 __device__ __forceinline__ uint32_t tab_mod(uint32_t e) { return (e >> 9) & 63u; }
 __device__ __forceinline__ const u64* tab_src(const LimbTab& tab, uint32_t e, uint32_t logN) {
@@ -156,8 +136,9 @@ __global__ __launch_bounds__(P2_THREADS, 4) void ntt_col_fwd_kernel(P2Args a, Li
     ieee_off();
     using G = Col<LC>;
     __shared__ u64 sm[G::LDS];
+    const ModClasses cls = classes_now(a.cls);
     const uint32_t tile = blockIdx.x & (G::T - 1), e = __builtin_amdgcn_readfirstlane(tab.e[blockIdx.x >> G::LT]);
-    by_class(a, tab_mod(e), e, [&](auto W, uint32_t v) { col_fwd<LC, RS, W>(a, tab, v, tile, sm); });
+    by_class(cls, tab_mod(e), e, [&](auto W, uint32_t v) { col_fwd<LC, RS, W>(a, tab, v, tile, sm); });
 }
 
 // Inverse column stages and output scaling: inputs below 2q (wide moduli: w_half), results canonical.  Stage 0 (one twiddle for the whole limb)
@@ -229,8 +210,9 @@ __global__ __launch_bounds__(P2_THREADS, LC == 9 ? 3 : 4) void ntt_col_inv_kerne
     ieee_off();
     using G = Col<LC>;
     __shared__ u64 sm[G::LDS];
+    const ModClasses cls = classes_now(a.cls);
     const uint32_t tile = blockIdx.x & (G::T - 1), e = __builtin_amdgcn_readfirstlane(tab.e[blockIdx.x >> G::LT]);
-    by_class(a, tab_mod(e), e, [&](auto W, uint32_t v) { col_inv<LC, CUSTOM_SCALE, W>(a, v, tile, sm, sc, scale_period); });
+    by_class(cls, tab_mod(e), e, [&](auto W, uint32_t v) { col_inv<LC, CUSTOM_SCALE, W>(a, v, tile, sm, sc, scale_period); });
 }
 
 // ---------------------------------------------------------------- forward row pass
@@ -356,10 +338,11 @@ template <bool EPI, int LANES>
 __global__ __launch_bounds__(P2_THREADS, 4) void ntt_row_fwd_kernel(P2Args a, LimbTab tab, ModDownEpilogue ep) {
     ieee_off();
     __shared__ alignas(16) u64 sm[P2_THREADS / LANES * 272];         // 16 groups of 17: conflict-free both ways
+    const ModClasses cls = classes_now(a.cls);
     uint32_t tile;
     const uint32_t e = row_decode<LANES>(tab, a, tile);
     if (e == TAB_NONE) return;
-    by_class(a, tab_mod(e), e, [&](auto W, uint32_t v) { row_fwd<W, EPI, LANES>(a, v, tile, sm, ep); });
+    by_class(cls, tab_mod(e), e, [&](auto W, uint32_t v) { row_fwd<W, EPI, LANES>(a, v, tile, sm, ep); });
 }
 
 // ---------------------------------------------------------------- inverse row pass
@@ -432,10 +415,11 @@ template <int LANES>
 __global__ __launch_bounds__(P2_THREADS, 4) void ntt_row_inv_kernel(P2Args a, LimbTab tab) {
     ieee_off();
     __shared__ alignas(16) u64 sm[P2_THREADS / LANES * 272];
+    const ModClasses cls = classes_now(a.cls);
     uint32_t tile;
     const uint32_t e = row_decode<LANES>(tab, a, tile);
     if (e == TAB_NONE) return;
-    by_class(a, tab_mod(e), e, [&](auto W, uint32_t v) { row_inv<W, LANES>(a, tab, v, tile, sm); });
+    by_class(cls, tab_mod(e), e, [&](auto W, uint32_t v) { row_inv<W, LANES>(a, tab, v, tile, sm); });
 }
 
 // ---------------------------------------------------------------- row passes of several limbs of one modulus
@@ -446,7 +430,7 @@ __global__ __launch_bounds__(P2_THREADS, 4) void ntt_row_inv_kernel(P2Args a, Li
 // 102 -> 95, near what the points alone take (403 MB, 82 us at copy rate).  Asking for the next four limbs' points ahead
 // costs a third of the wavefronts and gave 110.
 struct RunTab {
-    uint32_t r[HE_MAX_LAUNCH_LIMBS / 4 + HE_MAX_MODULI];     // first entry of LimbTab (bits 0-8), limbs (9-13), modulus (14-19), wide (31)
+    uint32_t r[HE_MAX_LAUNCH_LIMBS / 4 + HE_MAX_MODULI];     // first entry of LimbTab (bits 0-8), limbs (9-13), modulus (14-19)
 };
 // what entry 4*it + i of the run gives for lane quarter i (the last entry's again where the run has fewer)
 template <class F>
@@ -576,8 +560,9 @@ __global__ __launch_bounds__(P2_THREADS, 4) void ntt_row_run_kernel(P2Args a, Li
     ieee_off();
     __shared__ u64 sm[16 * 272];
     const uint32_t lb = a.logN - 10, b = (blockIdx.x & ((1u << lb) - 1u)) * 4u + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const ModClasses cls = classes_now(a.cls);
     const uint32_t run = __builtin_amdgcn_readfirstlane(runs.r[blockIdx.x >> lb]);
-    by_class(a, run >> 14 & 63u, run, [&](auto W, uint32_t v) {
+    by_class(cls, run >> 14 & 63u, run, [&](auto W, uint32_t v) {
         if constexpr (FWD) row_run_fwd<W, LAZY>(a, tab, v, b, sm);
         else row_run_inv<W>(a, tab, v, b, sm);
     });
@@ -626,7 +611,7 @@ int32_t probe_butterfly_rates(he_ctx* ctx, u64* d_out, uint32_t groups, double r
         const bool fwd = which != 1;
         const ulonglong2* tw = (fwd ? ctx->d_tw : ctx->d_itw) + (size_t)mi * ctx->N;
         const u64 q = ctx->mod[mi];
-        void (*const kernel)(const ulonglong2*, u64, u64*, uint32_t) = probes[fwd][(fwd ? near_fwd(q, ctx->logN) : near_inv(q)) ? W_NEAR : (fwd ? narrow_fwd(q) : narrow_inv(q)) ? 0 : widest(q) ? 2 : 1];
+        void (*const kernel)(const ulonglong2*, u64, u64*, uint32_t) = probes[fwd][fwd ? class_fwd(q, ctx->logN) : class_inv(q)];
         for (int rep = 0; rep < 2; rep++) {              // the first launch warms up
             HE_HIP(ctx, hipEventRecord(e0, ctx->stream));
             hipLaunchKernelGGL(kernel, dim3(groups), dim3(P2_THREADS), 0, ctx->stream, tw, q, d_out, rounds);
@@ -673,7 +658,7 @@ int32_t launch_transform2p(he_ctx* ctx, const TransformDesc& d) {
         if (mi == 0xFFu) continue;
         const uint32_t seg = d.src_seg ? d.src_seg[i] : 0, lim = d.src_limb ? d.src_limb[i] : i;
         if (seg >= HE_MAX_SEGS || seg >= d.n_seg || lim >= 4096) return he_fail(ctx, HE_ERR_BADARG, "transform: source limb out of range");
-        tab.e[start[mi]++] = i | (mi << 9) | (lim << 15) | (seg << 27) | ((fwd ? narrow_fwd(ctx->mod[mi]) : narrow_inv(ctx->mod[mi])) ? 0u : TAB_WIDE);
+        tab.e[start[mi]++] = i | (mi << 9) | (lim << 15) | (seg << 27);
     }
     // Plain row passes by runs of one modulus: fours of limbs, up to 16 in a run, shorter runs where the launch would not
     // fill the chip four times over.  Where more than a quarter of the lanes would have no limb, one limb at a time.
@@ -687,17 +672,13 @@ int32_t launch_transform2p(he_ctx* ctx, const TransformDesc& d) {
         while (piece > 4 && (live / piece) * groups < 4 * 768) piece >>= 1;
         for (uint32_t m = 0, at = 0; m < ctx->M; at += count[m++])
             for (uint32_t i = 0; i < count[m]; i += piece)
-                runs.r[n_runs++] = (at + i) | (std::min(piece, count[m] - i) << 9) | (m << 14) | ((fwd ? narrow_fwd(ctx->mod[m]) : narrow_inv(ctx->mod[m])) ? 0u : TAB_WIDE);
+                runs.r[n_runs++] = (at + i) | (std::min(piece, count[m] - i) << 9) | (m << 14);
     }
     P2Args a;
     a.dst = d.dst; a.mc = ctx->d_mc;
     a.tw = fwd ? ctx->d_tw : ctx->d_itw;
     a.logN = logN;
-    a.widest = a.near = 0;
-    for (uint32_t m = 0; m < ctx->M; m++) {
-        a.widest |= (u64)widest(ctx->mod[m]) << m;
-        a.near |= (u64)(fwd ? near_fwd(ctx->mod[m], ctx->logN) : near_inv(ctx->mod[m])) << m;
-    }
+    a.cls = fwd ? ctx->cls_fwd : ctx->cls_inv;
     a.lazy = (fwd && d.lazy_out) ? 1u : 0u;
     a.rs_mod = d.rescale_from ? d.rescale_from - 1 : 0;
     uint32_t lc = 0;

@@ -1,6 +1,8 @@
 // Register blocks of the radix-2 negacyclic transforms shared by the two-launch kernels, the column conversion and the small-ring kernels:
 // four butterfly stages on 16 points, or two on 4 points, held by one thread (Harvey butterflies, lazy ranges).
 #pragma once
+#include <type_traits>
+
 #include "modarith.h"
 
 #define SCHED_FENCE() __builtin_amdgcn_sched_barrier(0)   // loads above it are issued before the arithmetic below it
@@ -21,13 +23,37 @@
 //   2  the others (below 2^60): below 8q, two of them.
 //   3  W_NEAR, moduli near a multiple of 2^32 (near_acc, modarith.h): signed points, never reduced.  Forward: below 22q at the end (16q above 2^58),
 //      NEAR_ROWS between the passes; inverse: a pass ends below 512q.  What they need at the start: he_internal.h.
-#define W_NEAR 3
 #define NEAR_ROWS 14
 // multiples of q that make any forward result positive, which together stay below 2^64
 __device__ __forceinline__ u64 near_bias(u64 q) { return q * (q > 1ull << 58 ? 16 : 24); }
 __device__ constexpr int w_lim(int W) { return W == W_NEAR ? NEAR_ROWS : W == 1 ? 13 : 8; }         // sums and products' operands (W > 0)
 __device__ constexpr int w_half(int W) { return w_lim(W) / 2; }            // inverse: points between stages (W = 1, 2)
 __device__ constexpr int w_start(int W) { return W == 1 || W == 2 ? w_half(W) : 2; }      // inverse: what a pass starts with
+// A context's classes, asked for at the start of a kernel along with what it needs first
+__device__ __forceinline__ ModClasses classes_now(const ModClasses& c) {
+    ModClasses v = c;
+    asm volatile("" : "+s"(v.b[0]), "+s"(v.b[1]));
+    return v;
+}
+// f(std::integral_constant<int, W>, v) for the class W of bits `mi` of c; v: what the loads of a class follow from.  Keeps the loads of the
+// branches apart: merged above them (they look alike) they would stay live across all of it, 240 registers instead of 109.  (A chain of
+// branches: on the class as one number the compiler makes a tree of them, with ten registers more in the rescale's columns.)
+template <class F>
+__device__ __forceinline__ void by_class(const ModClasses& c, uint32_t mi, uint32_t v, F&& f) {
+    if ((c.b[0] & c.b[1]) >> mi & 1u) {
+        asm("; near" : "+s"(v));
+        f(std::integral_constant<int, W_NEAR>(), v);
+    } else if (!((c.b[0] | c.b[1]) >> mi & 1u)) {
+        asm("; narrow" : "+s"(v));
+        f(std::integral_constant<int, 0>(), v);
+    } else if (!(c.b[1] >> mi & 1u)) {
+        asm("; wide" : "+s"(v));
+        f(std::integral_constant<int, 1>(), v);
+    } else {
+        asm("; widest" : "+s"(v));
+        f(std::integral_constant<int, 2>(), v);
+    }
+}
 // what the butterflies need of a modulus, in scalar registers
 struct StageQ {
     u64 n2q, q5;

@@ -108,13 +108,13 @@ __global__ __launch_bounds__(RS_THREADS, 4) void rescale_cols_kernel(RescaleCols
     g.factors(w, itw + ((size_t)rc.level << (LC + 8)));
     const ModConst ml = mod_const(mc, rc.level);
     const u64 h = ml.q >> 1;
-    if (rc.near_inv >> rc.level & 1u) {
-        g.template inverse<W_NEAR>(x, lds + RS_LDS, w, ml.q, ml);
+    by_class(rc.inv, rc.level, 0, [&](auto W, uint32_t) {
+        g.template inverse<W>(x, lds + RS_LDS, w, ml.q, ml);
+        if (W == W_NEAR) {                               // positive, as the product below takes them
 #pragma unroll
-        for (int k = 0; k < 4; k++) x[k] += ml.q << 9;   // positive, as the product below takes them
-    } else if (!(rc.wide_inv >> rc.level & 1u)) g.template inverse<0>(x, lds + RS_LDS, w, ml.q, ml);
-    else if (!(rc.widest >> rc.level & 1u)) g.template inverse<1>(x, lds + RS_LDS, w, ml.q, ml);
-    else g.template inverse<2>(x, lds + RS_LDS, w, ml.q, ml);
+            for (int k = 0; k < 4; k++) x[k] += ml.q << 9;
+        }
+    });
     g.factors(w, ftw + ((size_t)r0 << (LC + 8)));
 #pragma unroll
     for (int k = 0; k < 4; k++) x[k] = csub_min(csub_min(shoup_lazy(x[k], ml.ninv, ml.ninv_sh, ml.q), ml.q) + h, ml.q);
@@ -135,13 +135,10 @@ __global__ __launch_bounds__(RS_THREADS, 4) void rescale_cols_kernel(RescaleCols
 #pragma unroll
             for (int k = 0; k < 4; k++) y[k] = shoup_lazy4(x[k], 1, one_sh, q) + up;      // below 5q
         }
-        if (rc.near_fwd >> r & 1u) {
-            fwd_centre<W_NEAR>(y, m);
-            g.template forward<W_NEAR>(y, buf, w, q);
-        }
-        else if (!(rc.wide_fwd >> r & 1u)) g.template forward<0>(y, buf, w, q);
-        else if (!(rc.widest >> r & 1u)) g.template forward<1>(y, buf, w, q);
-        else g.template forward<2>(y, buf, w, q);
+        by_class(rc.fwd, r, 0, [&](auto W, uint32_t) {
+            fwd_centre<W>(y, m);
+            g.template forward<W>(y, buf, w, q);
+        });
         u64* dst = rc.dst + ((size_t)(limb * rc.level + r) << (LC + 8));
         if (++r < r1) g.factors(w, ftw + ((size_t)r << (LC + 8)));
 #pragma unroll
@@ -160,14 +157,7 @@ bool rescale_cols_pays(const he_ctx* ctx, uint32_t n, uint32_t level) { return (
 int32_t launch_rescale_cols(he_ctx* ctx, const u64* src, u64* dst, uint32_t n, uint32_t level) {
     if (n == 0) return HE_OK;
     if (ctx->logN < 13 || ctx->logN > 17 || level == 0 || level >= ctx->nq) return he_fail(ctx, HE_ERR_BADARG, "rescale columns: bad shape");
-    RescaleCols rc = {src, dst, level, 0, 0, 0, 0, 0, 0, 0};
-    for (uint32_t i = 0; i <= level; i++) {
-        rc.wide_fwd |= (u64)!narrow_fwd(ctx->mod[i]) << i;
-        rc.wide_inv |= (u64)!narrow_inv(ctx->mod[i]) << i;
-        rc.widest |= (u64)widest(ctx->mod[i]) << i;
-        rc.near_fwd |= (u64)near_fwd(ctx->mod[i], ctx->logN) << i;
-        rc.near_inv |= (u64)near_inv(ctx->mod[i]) << i;
-    }
+    RescaleCols rc = {src, dst, level, 0, 0, ctx->cls_fwd, ctx->cls_inv};
     // The moduli of a tile are shared out, each share with the inverse columns of its own, while that makes at most three work groups
     // per compute unit: a rescale after a product at level 11 of N = 2^16 117.4 us with up to 768 or 1024, 120.4 with 2048, 123.6 with
     // 256 (a build with more registers); at level 23 206.6, 206.8, 208.8 and 225.
