@@ -1031,10 +1031,14 @@ __global__ __launch_bounds__(KS_THREADS) void hoist_c0_sum_kernel(HoistC0 a, con
 // Inner products of a hoisted sum for up to HS_JOBS ciphertexts at once, register-tiled: a thread owns one point of
 // one raised-basis limb for all the ciphertexts and both components; per (term, digit) it loads the two key values
 // once and one digit value per ciphertext, and feeds 2*J multiply-accumulates.
-// acc [J][2][R][N] (as `settled` leaves it); bit 0 of init clear: the launch continues from its contents (more than HS_TERMS terms); bit 1:
-// two-launch rings; bit 2: the digits' rows are not transformed yet.
+// acc [J][2][R][N] (as `settled` leaves it); bit 0 of init clear: the launch continues from its contents (more products than one takes, HS_PRODUCTS);
+// bit 1: two-launch rings.  All terms go into one launch where they fit: with 16 to a launch the digits' rows were transformed again for
+// every 16, and the sums went to memory between.  Layers of 31 terms at N = 2^16, one output and eight, level 5 203 -> 173 and 484 -> 407 us, level 22
+// 804 -> 745 and 1900 -> 1666.  Launches that continue transform them again; the counters count them once.
 #define HS_JOBS 8
-#define HS_TERMS 16
+#define HS_TERMS (HE_MAX_SUM_TERMS - 1)      // at most a wavefront's lanes
+#define HS_PRODUCTS 512                      // of a point and component in one launch
+static_assert(HS_TERMS <= 64, "");
 struct HoistIp {
     const u64* raised[HS_JOBS];   // [beta][R][N], own limbs not materialised
     const u64* own[HS_JOBS];      // the switched polynomial [L1][N]
@@ -1054,7 +1058,7 @@ struct HoistIp {
 // Products are taken in halves that go into three 64-bit sums straight from the 32x32+64-bit multiply-adds, with no carries: what the kernel
 // spends on a product is three or four instructions, against four multiply-adds and ten others (carries, moves) for a 128-bit sum.
 //   at most 54 bits: halves of 27 bits, d*k = d0*k0 + (d0*k1 + d1*k0)*2^27 + d1*k1*2^54 with d0*k1 + d1*k0 = (d0-d1)*(k1-k0) + d0*k0 +
-//     d1*k1, three multiplications; the sums of d0*k0, d1*k1 and (signed) (d0-d1)*(k1-k0) take 2^9 products, more than any call has;
+//     d1*k1, three multiplications; the sums of d0*k0, d1*k1 and (signed) (d0-d1)*(k1-k0) take 2^9 products (HS_PRODUCTS);
 //   wider: balanced halves of 30 bits, d0 and k0 in [-2^29, 2^29), d taken in (-q/2, q/2), and four multiplications, because the middle
 //     sum's products are then so much smaller than (d0-d1)*(k1-k0) that 20 (q near 2^59) or 10 (2^60) fit, where the three of
 //     unsigned halves let 6 fit, after which every sum had to move its carries up, as many instructions again as the products took.
@@ -1071,10 +1075,11 @@ struct HoistIp {
 struct LimbSel {
     uint32_t r[HE_MAX_MODULI];
 };
-template <int JT, bool WIDE>
+template <int JT, bool ROWS, bool WIDE>
 __device__ __forceinline__ void hoisted_sum_ip(const HoistIp& a, uint32_t r, uint32_t mi, const ModConst& m, u64* dig, u64* __restrict__ acc, uint32_t logN,
                                                uint32_t R, uint32_t beta, uint32_t M, uint32_t level, uint32_t alpha, uint32_t init, bool rows) {
-    const uint32_t n = blockIdx.x * KS_THREADS + threadIdx.x, word = row4_word(threadIdx.x);
+    auto word_of = [](uint32_t i) { return ROWS ? row4_word(i) : i; };
+    const uint32_t n = blockIdx.x * KS_THREADS + threadIdx.x, word = word_of(threadIdx.x);
     constexpr int H = WIDE ? 30 : 27;
     constexpr u64 lo_h = (1ull << H) - 1;
     // products a middle sum takes: |d0| k1 + |d1| |k0| of each, below 2^63 together (at most 31, which the low sums take)
@@ -1085,7 +1090,7 @@ __device__ __forceinline__ void hoisted_sum_ip(const HoistIp& a, uint32_t r, uin
         const bool own_digit = r <= level && r / alpha == j;
         const size_t doff = own_digit ? ro : (size_t)(j * R + r) << logN;
         u64 in[JT];
-        if (init & 4u && !own_digit) {
+        if (ROWS && !own_digit) {
 #pragma unroll
             for (int i = 0; i < JT; i++) in[i] = dig[(j * a.J + ((uint32_t)i < a.J ? i : 0)) * KS_THREADS + word];
         } else {
@@ -1114,15 +1119,10 @@ __device__ __forceinline__ void hoisted_sum_ip(const HoistIp& a, uint32_t r, uin
     for (int i = 0; i < JT; i++) b0[i] = b2[i] = a0[i] = a2[i] = bm[i] = am[i] = 0;
     __syncthreads();
     const size_t kstride = (size_t)M << logN;
-    // lane t (mod 16) keeps term t's key address and Galois element: the loop then picks them with a lane read instead
+    // lane t keeps term t's key address and Galois element: the loop then picks them with a lane read instead
     // of a scalar load from the argument block, whose latency every step would wait for
-    uint32_t kp_lo = 0, kp_hi = 0, g_lane = 1;
-#pragma unroll
-    for (int tt = 0; tt < HS_TERMS; tt++) {
-        if ((threadIdx.x & (HS_TERMS - 1)) == (uint32_t)tt) {
-            kp_lo = (uint32_t)(uintptr_t)a.evk[tt]; kp_hi = (uint32_t)((uintptr_t)a.evk[tt] >> 32); g_lane = a.g[tt];
-        }
-    }
+    const uint32_t mine = min(threadIdx.x & 63u, a.T - 1);
+    const uint32_t kp_lo = (uint32_t)(uintptr_t)a.evk[mine], kp_hi = (uint32_t)((uintptr_t)a.evk[mine] >> 32), g_lane = a.g[mine];
     auto key_of = [&](uint32_t term) {
         const uint32_t lo = __builtin_amdgcn_readlane(kp_lo, term), hi = __builtin_amdgcn_readlane(kp_hi, term);
         return (const u64 __attribute__((address_space(1)))*)(((uintptr_t)hi << 32) | lo);   // a global, not a generic, address
@@ -1144,7 +1144,7 @@ __device__ __forceinline__ void hoisted_sum_ip(const HoistIp& a, uint32_t r, uin
     // (t, j) = the pair whose digits are read next, lsrc = where this thread's value of term t sits in its tile
     uint32_t t = 0, j = 0;
     auto lsrc_of = [&](uint32_t term) {
-        return row4_word(galois_src_ks(n, __builtin_amdgcn_readlane(g_lane, term < a.T ? term : 0), logN) & (KS_THREADS - 1));
+        return word_of(galois_src_ks(n, __builtin_amdgcn_readlane(g_lane, term < a.T ? term : 0), logN) & (KS_THREADS - 1));
     };
     uint32_t lsrc = lsrc_of(0);
     auto read = [&](int p, u64 (&to)[PT]) {
@@ -1243,6 +1243,11 @@ __device__ __forceinline__ void hoisted_sum_ip(const HoistIp& a, uint32_t r, uin
         }
     }
 }
+// A lane's number for loads that are made anew in every turn of a loop, not kept in registers
+__device__ __forceinline__ uint32_t lane_now(uint32_t lane) {
+    asm volatile("" : "+v"(lane));
+    return lane;
+}
 // The rows of the digits' limb r, whose column passes are done, into their tiles (below 2q).  A row belongs to one work group, as the sums
 // below do, so the digits' row passes need no launch that reads and writes them: a layer of 8 outputs at level 5 with one digit 564 -> 557 us, a
 // block with two 1091 -> 1070.
@@ -1252,7 +1257,7 @@ __device__ __forceinline__ void hoisted_sum_digits(const HoistIp& a, uint32_t r,
     const uint32_t lane = threadIdx.x & 63u, n = (own_j < beta ? beta - 1 : beta) * a.J;
     const Row4 at(lane);
     u64 w[4][6];
-    tw_row4(w, tw, logN - 8, blockIdx.x, lane);
+    if (NX > 1) tw_row4(w, tw, logN - 8, blockIdx.x, lane);
 #pragma unroll 1
     for (uint32_t i0 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); i0 < n; i0 += NX * (KS_THREADS / 64)) {
         u64 x[NX][4];
@@ -1265,6 +1270,7 @@ __device__ __forceinline__ void hoisted_sum_digits(const HoistIp& a, uint32_t r,
 #pragma unroll
             for (int k = 0; k < 4; k++) x[c][k] = __builtin_nontemporal_load(&row[lane + 64 * k]);
         }
+        if (NX == 1) tw_row4(w, tw, logN - 8, blockIdx.x, lane_now(lane));
         u64* buf = dig + tile[0] * KS_THREADS;
         const uint32_t stride = NX == 2 ? (tile[1] - tile[0]) * KS_THREADS : 0;
         SCHED_FENCE();
@@ -1280,26 +1286,27 @@ __device__ __forceinline__ void hoisted_sum_digits(const HoistIp& a, uint32_t r,
     }
     __syncthreads();
 }
-// The inverse rows of a work group's sums (below 2q, in LDS), both components of an output by one wavefront.  A work group's 256 points are a row,
+// The inverse rows of a work group's sums (below 2q, in LDS), NX of them at a time by one wavefront.  A work group's 256 points are a row,
 // so the special primes' sums need not go to memory and back to be transformed: 8 outputs of 8 special primes at N = 2^16 were a launch of 36 us of
 // 128 MiB (3.7 TB/s), and 64 MiB written ahead of it.  A layer at level 5 588 -> 564 us, a block with four special primes 1108 -> 1091.
-template <int W>
-__device__ __forceinline__ void hoisted_sum_rows(u64* rows, u64* __restrict__ mid, const ModConst& m, const ulonglong2* tw, uint32_t J, uint32_t k, uint32_t logN) {
+template <int W, int NX>
+__device__ __forceinline__ void hoisted_sum_rows(u64* rows, u64* __restrict__ mid, const ModConst& m, const ulonglong2* tw, uint32_t n, uint32_t k, uint32_t logN) {
     const uint32_t lane = threadIdx.x & 63u;
     const Row4 at(lane);
     u64 w[4][6];
-    tw_row4(w, tw, logN - 8, blockIdx.x, lane);
+    if (NX > 1) tw_row4(w, tw, logN - 8, blockIdx.x, lane);
     __syncthreads();
 #pragma unroll 1
-    for (uint32_t i = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); i < J; i += KS_THREADS / 64) {
-        u64 x[2][4], *buf = rows + 2 * i * KS_THREADS;
+    for (uint32_t i = NX * __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); i < n; i += NX * (KS_THREADS / 64)) {
+        u64 x[NX][4], *buf = rows + i * KS_THREADS;
+        if (NX == 1) tw_row4(w, tw, logN - 8, blockIdx.x, lane_now(lane));
 #pragma unroll
-        for (int c = 0; c < 2; c++) at.load(3, x[c], buf + c * KS_THREADS);
+        for (int c = 0; c < NX; c++) at.load(3, x[c], buf + c * KS_THREADS);
         wave_exchange();
-        row4_inv<W, 2>(x, w, buf, KS_THREADS, at, m.q, m);
-        u64* out = mid + ((size_t)(2 * i * k) << logN) + blockIdx.x * KS_THREADS + lane;
+        row4_inv<W, NX>(x, w, buf, KS_THREADS, at, m.q, m);
+        u64* out = mid + ((size_t)(i * k) << logN) + blockIdx.x * KS_THREADS + lane;
 #pragma unroll
-        for (int c = 0; c < 2; c++)
+        for (int c = 0; c < NX; c++)
 #pragma unroll
             for (int p = 0; p < 4; p++) (out + ((size_t)(c * k) << logN))[64 * p] = x[c][p];
     }
@@ -1307,31 +1314,36 @@ __device__ __forceinline__ void hoisted_sum_rows(u64* rows, u64* __restrict__ mi
 
 __device__ __forceinline__ ModClasses classes_of(uint32_t two_bits) { return {{two_bits, two_bits >> 1}}; }
 
-template <int JT>
+// ROWS: two-launch rings, whose digits' rows are not transformed yet.  Other rings have a form without that code (one output 56 registers, eight
+// wavefronts to a SIMD).  With one or two outputs a row's factors are loaded for each row (88 registers, five wavefronts; kept 117 and four), and
+// a wavefront takes one row of the sums, not both of an output.
+template <int JT, bool ROWS>
 __global__ __launch_bounds__(KS_THREADS, 3) void hoisted_sum_ip_local_kernel(HoistIp a, LimbSel sel, u64* __restrict__ acc,
                                                                              const ModConst* mc, uint32_t logN, uint32_t R,
                                                                              uint32_t beta, uint32_t M, uint32_t level, uint32_t nq,
                                                                              uint32_t alpha, uint32_t init, u64* __restrict__ mid,
                                                                              const ulonglong2* ftw, const ulonglong2* itw) {
-    ieee_off();
-    extern __shared__ u64 dig[];                         // a.J * beta tiles of KS_THREADS values, at least 2 * a.J
+    if (ROWS) ieee_off();
+    extern __shared__ u64 dig[];                         // a.J * beta tiles of KS_THREADS values, ROWS: at least 2 * a.J
     const uint32_t s = sel.r[blockIdx.y], r = s & (HSL_ROWS - 1);
     uint32_t mi = r <= level ? r : nq + (r - level - 1);
-    const bool rows = s & HSL_ROWS;
+    const bool rows = ROWS && s & HSL_ROWS;
     const ModConst m = mod_const(mc, mi);
-    if (init & 4u) {
+    if constexpr (ROWS) {
         constexpr int NX = JT > 4 ? 2 : 1;
         const uint32_t own_j = r <= level ? r / alpha : beta;
         by_class(classes_of(s >> HSL_FWD), 0, mi, [&](auto W, uint32_t v) { hoisted_sum_digits<W, NX>(a, r, m, dig, ftw + ((size_t)v << logN), logN, R, beta, own_j); });
     }
-    if (m.bits > 54) hoisted_sum_ip<JT, true>(a, r, mi, m, dig, acc, logN, R, beta, M, level, alpha, init, rows);
-    else hoisted_sum_ip<JT, false>(a, r, mi, m, dig, acc, logN, R, beta, M, level, alpha, init, rows);
-    if (!rows) return;
-    asm("" : "+s"(mi));                                  // the constants are read again, not kept
-    const ModConst mr = mod_const(mc, mi);
-    u64* out = mid + ((size_t)(r - level - 1) << logN);
-    const uint32_t k = R - level - 1;
-    by_class(classes_of(s >> HSL_INV), 0, mi, [&](auto W, uint32_t v) { hoisted_sum_rows<W>(dig, out, mr, itw + ((size_t)v << logN), a.J, k, logN); });
+    if (m.bits > 54) hoisted_sum_ip<JT, ROWS, true>(a, r, mi, m, dig, acc, logN, R, beta, M, level, alpha, init, rows);
+    else hoisted_sum_ip<JT, ROWS, false>(a, r, mi, m, dig, acc, logN, R, beta, M, level, alpha, init, rows);
+    if constexpr (ROWS) {
+        if (!rows) return;
+        asm("" : "+s"(mi));                              // the constants are read again, not kept
+        const ModConst mr = mod_const(mc, mi);
+        u64* out = mid + ((size_t)(r - level - 1) << logN);
+        const uint32_t k = R - level - 1;
+        by_class(classes_of(s >> HSL_INV), 0, mi, [&](auto W, uint32_t v) { hoisted_sum_rows<W, (JT > 2 ? 2 : 1)>(dig, out, mr, itw + ((size_t)v << logN), 2 * a.J, k, logN); });
+    }
 }
 
 // Whether the Galois elements of a hoisted sum only move values inside aligned blocks of 256 positions, the tile of a
@@ -1412,9 +1424,10 @@ int32_t ks_hoisted_sum(he_ctx* c, uint32_t level, const KsSrc* srcs, uint32_t J,
         // the inner products of all the chunk's ciphertexts, register-tiled, into stored accumulators; those of the special primes go
         // on to their inverse rows where the rest of their way back is one launch
         const bool rows_here = two_pass(c) && c->d_dn_op != nullptr;
-        for (uint32_t t0 = 0; t0 < T; t0 += HS_TERMS) {
+        const uint32_t most = std::min<uint32_t>(HS_TERMS, HS_PRODUCTS / beta);      // terms of a launch
+        for (uint32_t t0 = 0; t0 < T; t0 += most) {
             HoistIp hi = {};
-            hi.J = nb; hi.T = std::min<uint32_t>(HS_TERMS, T - t0);
+            hi.J = nb; hi.T = std::min<uint32_t>(most, T - t0);
             for (uint32_t t = 0; t < hi.T; t++) { hi.evk[t] = evks[t0 + t]; hi.g[t] = gs[t0 + t]; }
             for (uint32_t j = 0; j < nb; j++) { hi.raised[j] = raised + (size_t)j * beta * R * N; hi.own[j] = srcs[j0 + j].c1; }
             {
@@ -1435,14 +1448,16 @@ int32_t ks_hoisted_sum(he_ctx* c, uint32_t level, const KsSrc* srcs, uint32_t J,
                 for (uint32_t i = 0; i < R; i++) {
                     const bool special = sel.r[i] > level;
                     const u64 q = c->mod[special ? c->nq + (sel.r[i] - L1) : sel.r[i]];
-                    sel.r[i] |= (special && rows_here && t0 + HS_TERMS >= T ? HSL_ROWS : 0) | class_inv(q) << HSL_INV | class_fwd(q, c->logN) << HSL_FWD;
+                    sel.r[i] |= (special && rows_here && t0 + most >= T ? HSL_ROWS : 0) | class_inv(q) << HSL_INV | class_fwd(q, c->logN) << HSL_FWD;
                 }
                 const dim3 grid(N / KS_THREADS, R), blk(KS_THREADS);
                 const size_t lds = (size_t)nb * std::max(beta, rows_here ? 2u : 1u) * KS_THREADS * sizeof(u64);
-                const uint32_t init = (t0 == 0 ? 1u : 0u) | (two_pass(c) ? 6u : 0u);
-#define HSL_LAUNCH(JT) hipLaunchKernelGGL(hoisted_sum_ip_local_kernel<JT>, grid, blk, lds, c->stream, hi, sel, acc, c->d_mc, c->logN, R, beta, \
-                                          c->M, level, c->nq, c->alpha, init, tmp_dn, c->d_tw, c->d_itw)
-                if (nb <= 1) HSL_LAUNCH(1); else if (nb <= 2) HSL_LAUNCH(2); else if (nb <= 4) HSL_LAUNCH(4); else HSL_LAUNCH(8);
+                const uint32_t init = (t0 == 0 ? 1u : 0u) | (two_pass(c) ? 2u : 0u);
+#define HSL_LAUNCH(...) hipLaunchKernelGGL((hoisted_sum_ip_local_kernel<__VA_ARGS__>), grid, blk, lds, c->stream, hi, sel, acc, c->d_mc, c->logN, R, beta, \
+                                           c->M, level, c->nq, c->alpha, init, tmp_dn, c->d_tw, c->d_itw)
+#define HSL_DISPATCH(ROWS) if (nb <= 1) HSL_LAUNCH(1, ROWS); else if (nb <= 2) HSL_LAUNCH(2, ROWS); else if (nb <= 4) HSL_LAUNCH(4, ROWS); else HSL_LAUNCH(8, ROWS)
+                if (two_pass(c)) { HSL_DISPATCH(true); } else { HSL_DISPATCH(false); }
+#undef HSL_DISPATCH
 #undef HSL_LAUNCH
             }
             HE_HIP(c, hipGetLastError());

@@ -1,6 +1,6 @@
 """GPU parity of hoisted sums whose kernel takes the digits through their rows and the special primes' sums through their inverse rows itself:
 moduli of every class side by side in one launch, 1 to 8 outputs of a launch's tile and one beyond it (rows that two and four wavefronts
-share unevenly), sums that one launch finishes and sums that a second one continues, one digit (tiles of LDS for the rows alone) and
+share unevenly), up to 31 terms, one digit (tiles of LDS for the rows alone) and
 several, on rings with and without the conversion with its columns - against the oracle, bit for bit."""
 import pytest
 
