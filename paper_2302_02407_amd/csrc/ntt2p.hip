@@ -136,9 +136,8 @@ __global__ __launch_bounds__(P2_THREADS, 4) void ntt_col_fwd_kernel(P2Args a, Li
     ieee_off();
     using G = Col<LC>;
     __shared__ u64 sm[G::LDS];
-    const ModClasses cls = classes_now(a.cls);
     const uint32_t tile = blockIdx.x & (G::T - 1), e = __builtin_amdgcn_readfirstlane(tab.e[blockIdx.x >> G::LT]);
-    by_class(cls, tab_mod(e), e, [&](auto W, uint32_t v) { col_fwd<LC, RS, W>(a, tab, v, tile, sm); });
+    by_class(a.cls, tab_mod(e), e, [&](auto W, uint32_t v) { col_fwd<LC, RS, W>(a, tab, v, tile, sm); });
 }
 
 // Inverse column stages and output scaling: inputs below 2q (wide moduli: w_half), results canonical.  Stage 0 (one twiddle for the whole limb)
@@ -210,9 +209,8 @@ __global__ __launch_bounds__(P2_THREADS, LC == 9 ? 3 : 4) void ntt_col_inv_kerne
     ieee_off();
     using G = Col<LC>;
     __shared__ u64 sm[G::LDS];
-    const ModClasses cls = classes_now(a.cls);
     const uint32_t tile = blockIdx.x & (G::T - 1), e = __builtin_amdgcn_readfirstlane(tab.e[blockIdx.x >> G::LT]);
-    by_class(cls, tab_mod(e), e, [&](auto W, uint32_t v) { col_inv<LC, CUSTOM_SCALE, W>(a, v, tile, sm, sc, scale_period); });
+    by_class(a.cls, tab_mod(e), e, [&](auto W, uint32_t v) { col_inv<LC, CUSTOM_SCALE, W>(a, v, tile, sm, sc, scale_period); });
 }
 
 // ---------------------------------------------------------------- forward row pass
