@@ -143,7 +143,7 @@ __global__ __launch_bounds__(P2_THREADS, 4) void ntt_col_fwd_kernel(P2Args a, Li
 // Inverse column stages and output scaling: inputs below 2q (wide moduli: w_half), results canonical.  Stage 0 (one twiddle for the whole limb)
 // carries the scaling: the sum is multiplied by the scale, the difference by scale * twiddle.  Narrow moduli: bounds
 // 2 -> 40 (N = 2^17: 80, reduced) -> 320 -> 640 (products that take any value, Shoup's).
-template <int LC, bool CUSTOM_SCALE, int W>
+template <int LC, bool CUSTOM_SCALE, bool AHEAD, int W>
 __device__ __forceinline__ void col_inv(const P2Args& a, uint32_t e, uint32_t tile, u64* sm, const ScaleList& sc, uint32_t scale_period) {
     using G = Col<LC>;
     const uint32_t mi = tab_mod(e), logN = LC + 8, limb = tab_dst(e);
@@ -155,7 +155,7 @@ __device__ __forceinline__ void col_inv(const P2Args& a, uint32_t e, uint32_t ti
     for (int j = 0; j < 16; j++) x[j] = (data + j * 256)[t * 4096 + c];
     ulonglong2 w1[15], w2[15];
     if (LC <= 8) tw_load<G::U0, 4>(w2, tw, LC - 4, t);
-    else tw_load<0, 4>(w2, tw, 4, t >> 1);
+    else if (AHEAD) tw_load<0, 4>(w2, tw, 4, t >> 1);
     const ModConst m = mod_const(a.mc, mi);
     const uint32_t si = CUSTOM_SCALE ? limb % scale_period : 0;
     constexpr bool NEAR = W == W_NEAR;
@@ -171,6 +171,10 @@ __device__ __forceinline__ void col_inv(const P2Args& a, uint32_t e, uint32_t ti
         ulonglong2 w3[15];
         tw_load<3, 4>(w3, tw, 5, t);
         inv_stages<W, 3, 4>(x, w3, q, bound);
+        if (!AHEAD) {
+            SCHED_FENCE();
+            tw_load<0, 4>(w2, tw, 4, t >> 1);
+        }
         const uint32_t r0 = (t >> 1) * 32 + (t & 1);
 #pragma unroll
         for (int j = 0; j < 16; j++) sm[G::pos(16 * t + j, cl)] = x[j];
@@ -202,15 +206,16 @@ __device__ __forceinline__ void col_inv(const P2Args& a, uint32_t e, uint32_t ti
     for (int k = 0; k < 16; k++) (data + ((size_t)k << (G::LT + 8)))[t * 256 + c] = inv_canonical<W>(x[k], q);
 }
 
-// N = 2^17 (LC = 9) runs three wavefronts to a SIMD: held to four, its three register blocks spilled 12 bytes a lane.  Inverse
-// transforms of 24 limbs 44 us so and 42 without spills, of 192 limbs 203 and 200.
-template <int LC, bool CUSTOM_SCALE>
-__global__ __launch_bounds__(P2_THREADS, LC == 9 ? 3 : 4) void ntt_col_inv_kernel(P2Args a, LimbTab tab, ScaleList sc, uint32_t scale_period) {
+// AHEAD: N = 2^17 (LC = 9), the middle block's factors are asked for with the first block's, for which four wavefronts to a SIMD have no
+// registers (8 bytes spilled a lane).  For launches that do not fill four: 8 limbs 13.4 us, 13.9 with the factors behind the first block;
+// 192 limbs 118.5 and 108.5, 96 limbs 66 and 62.
+template <int LC, bool CUSTOM_SCALE, bool AHEAD = false>
+__global__ __launch_bounds__(P2_THREADS, AHEAD ? 3 : 4) void ntt_col_inv_kernel(P2Args a, LimbTab tab, ScaleList sc, uint32_t scale_period) {
     ieee_off();
     using G = Col<LC>;
     __shared__ u64 sm[G::LDS];
     const uint32_t tile = blockIdx.x & (G::T - 1), e = __builtin_amdgcn_readfirstlane(tab.e[blockIdx.x >> G::LT]);
-    by_class(a.cls, tab_mod(e), e, [&](auto W, uint32_t v) { col_inv<LC, CUSTOM_SCALE, W>(a, v, tile, sm, sc, scale_period); });
+    by_class(a.cls, tab_mod(e), e, [&](auto W, uint32_t v) { col_inv<LC, CUSTOM_SCALE, AHEAD, W>(a, v, tile, sm, sc, scale_period); });
 }
 
 // ---------------------------------------------------------------- forward row pass
@@ -720,8 +725,12 @@ int32_t launch_transform2p(he_ctx* ctx, const TransformDesc& d) {
             else if (wide_rows) hipLaunchKernelGGL((ntt_row_inv_kernel<64>), grid_rows, block, 0, ctx->stream, a, tab);
             else hipLaunchKernelGGL((ntt_row_inv_kernel<16>), grid_rows, block, 0, ctx->stream, a, tab);
         } else {
-            if (d.scale) { COL_DISPATCH(ntt_col_inv_kernel, true, grid_cols, block, 0, ctx->stream, a, tab, *d.scale, d.scale_period) }
-            else { ScaleList none; COL_DISPATCH(ntt_col_inv_kernel, false, grid_cols, block, 0, ctx->stream, a, tab, none, 1u) }
+            const bool ahead = logN == 17 && grid_cols.x < 1024;     // four work groups to a compute unit: 25 limbs 23.5 us with it, 24.5 without, 32 both 26.9, 48 34.4 and 33.6
+            const ScaleList none = {};
+            if (ahead && d.scale) hipLaunchKernelGGL((ntt_col_inv_kernel<9, true, true>), grid_cols, block, 0, ctx->stream, a, tab, *d.scale, d.scale_period);
+            else if (ahead) hipLaunchKernelGGL((ntt_col_inv_kernel<9, false, true>), grid_cols, block, 0, ctx->stream, a, tab, none, 1u);
+            else if (d.scale) { COL_DISPATCH(ntt_col_inv_kernel, true, grid_cols, block, 0, ctx->stream, a, tab, *d.scale, d.scale_period) }
+            else { COL_DISPATCH(ntt_col_inv_kernel, false, grid_cols, block, 0, ctx->stream, a, tab, none, 1u) }
         }
         HE_HIP(ctx, hipGetLastError());
         if (ctx->prof_on) {
