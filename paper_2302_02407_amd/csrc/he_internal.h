@@ -128,9 +128,11 @@ struct he_ctx {
     // does not apply
     ConvOperand *d_up_op, *d_dn_op;
     u64* d_pinv;       // [nq] P^-1 mod q_r
+    std::vector<u64> h_pinv;      // the same on the host
     u64* d_pinv_sh;    // [nq] companions (h_companion)
     // rescale tables: q_l^-1 mod q_r for r < l, [nq][nq]
     u64* d_qlinv;
+    std::vector<u64> h_qlinv;
     u64* d_qlinv_sh;
     // workspace (grown on demand)
     u64* d_ws;

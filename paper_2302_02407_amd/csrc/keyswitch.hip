@@ -282,7 +282,9 @@ int32_t ks_init_tables(he_ctx* c) {
     const uint32_t nq = c->nq, np = c->np, M = c->M, al = c->alpha, dn = c->dnum;
     // rescale: q_l^-1 mod q_r
     {
-        std::vector<u64> inv((size_t)nq * nq, 0), inv_sh((size_t)nq * nq, 0);
+        std::vector<u64>& inv = c->h_qlinv;
+        std::vector<u64> inv_sh((size_t)nq * nq, 0);
+        inv.assign((size_t)nq * nq, 0);
         for (uint32_t l = 0; l < nq; l++)
             for (uint32_t r = 0; r < nq; r++) {
                 if (r == l) continue;
@@ -319,7 +321,9 @@ int32_t ks_init_tables(he_ctx* c) {
             }
     }
     // ModDown: P/p_t mod every modulus ([m][t padded to pw]), (P/p_t)^-1 mod p_t, P^-1 mod q_r
-    std::vector<u64> dhat((size_t)M * pw, 0), pinv(nq), pinv_sh(nq);
+    std::vector<u64> dhat((size_t)M * pw, 0), pinv_sh(nq);
+    std::vector<u64>& pinv = c->h_pinv;
+    pinv.assign(nq, 0);
     c->h_dn_invhat.assign(np, 0);
     for (uint32_t t = 0; t < np; t++) {
         for (uint32_t m = 0; m < M; m++) {

@@ -1007,9 +1007,7 @@ int32_t sr_moddown(he_ctx* c, uint32_t level, uint32_t J, const ModDownEpilogue&
         f.first = J * 2 * L1;
         for (uint32_t i = 0; i < L1; i++) {
             const u64 q = c->mod[i];
-            u64 P = 1;
-            for (uint32_t t = 0; t < k; t++) P = h_mulmod(P, c->mod[c->nq + t] % q, q);
-            f.factor[i] = h_mulmod(h_mulmod(u.scale[i], c->N % q, q), h_invmod(P, q), q);
+            f.factor[i] = h_mulmod(h_mulmod(u.scale[i], c->N % q, q), c->h_pinv[i], q);
         }
         SRF_LAUNCH(moddown_modup_kernel, dim3(f.first + J * u.n_out), ep, a, u, f, sr_tables(c));
         c->cnt.intt_limbs += (uint64_t)J * L1;
@@ -1049,8 +1047,8 @@ int32_t sr_rescale_modup(he_ctx* c, const u64* const* cts, u64* const* outs, uin
     sr_up_args(c, level - 1, raised, u);
     f.first = 2 * n * level;
     for (uint32_t i = 0; i < level; i++) {
-        const u64 q = c->mod[i], inv = h_invmod(c->mod[level] % q, q);
-        u.scale[i] = h_mulmod(u.scale[i], inv, q);
+        const u64 q = c->mod[i];
+        u.scale[i] = h_mulmod(u.scale[i], c->h_qlinv[(size_t)level * c->nq + i], q);
         f.factor[i] = h_mulmod(u.scale[i], c->N % q, q);
     }
     SRF_LAUNCH(rescale_modup_kernel, dim3(f.first + n * u.n_out), a, u, f, sr_tables(c));
