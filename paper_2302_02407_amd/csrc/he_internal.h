@@ -27,17 +27,49 @@ static inline bool narrow_fwd(u64 q) { return q <= (1ull << 63) / 96; }       //
 static inline bool narrow_inv(u64 q) { return q <= (1ull << 63) / 640; }      // all of 53 bits, and up to 2^53.6
 static inline bool widest(u64 q) { return q > (1ull << 63) / 13; }            // above 2^59.29
 // Moduli whose low word is near 0 as a signed number, as it is of primes near a power of two.  The products of near_acc (modarith.h) ask for
-// |operand| / 2 + 2^62 + |low word| 2^31 below 2^63 and are below (3/4 + |operand| / 2^65) q.  Points are not reduced on the way:
+// |operand| / 2 + 2^62 + |low word| 2^31 below 2^63 and are below (3/4 + |operand| / 2^65) q.  Points are not reduced on the way (checked below):
 //   forward, up to 2^58: 5q at the start, less than q more with every stage, 17 stages: below 22q;
 //   forward, up to 2^59.003 with at most 16 stages, the special primes that are taken above 2^59: 1.5q at the start (whoever writes points for
-//   the first pass centres them, near_top), operands below 14.6q < 2^63 - 2^60, results below 15.6q;
+//   the first pass centres them, near_top), operands below 14.6q < 2^63 - 2^58, which is what low words below 2^26 leave, results below 15.6q
+//   (made positive by 16q, near_bias: ntt_blocks.h);
 //   inverse: doubled by each of eight stages from 2q, below 512q.
+// The lines are where these ranges end.  384 limbs, N = 2^16, primes with small low words (in brackets: such primes in the other classes):
+// forward 2^54 134.6 us (134.4), just below 2^58 135.6 (142.9), just above 136.1 (143.3), just above 2^59 136.5 (143.4); inverse 2^54 135.8 (145.5),
+// just below 2^53.896 135.6 (149.6).  24 limbs: forward 23.3 (23.5) at 2^54, 23.4 (24.2) below 2^58, 23.8 (24.2) above 2^59; inverse 23.5 (25.0).  Outside
+// the class, now that it is there (in brackets before): inverse just above 2^53.9 150.2 (149.8), forward at 1.2 * 2^59 143.0 (143.7), just below 2^60
+// 153.6 (151.3).  What it costs other moduli is the jump over its code, which comes first in every kernel, an instruction fetch of some 0.3 us a
+// launch: one rotation at level 5 53.3 us (52.0) with narrow ciphertext primes, where the near ones take 51.3.
 static inline bool near_word(u64 q, int64_t most) { return (int32_t)(uint32_t)q < most && (int32_t)(uint32_t)q > -most; }
-static inline bool near_top(u64 q) { return q > 1ull << 58; }
+#define NEAR_WORD (1ll << 27)
+#define NEAR_TOP_WORD (1ll << 26)
+#define NEAR_FWD (1ull << 58)
+#define NEAR_TOP ((1ull << 59) + (1ull << 50))
+#define NEAR_INV ((1ull << 63) / 550)        // 2^53.896
+static inline bool near_top(u64 q) { return q > NEAR_FWD; }
 static inline bool near_fwd(u64 q, uint32_t logN) {
-    return near_top(q) ? logN <= 16 && q <= (1ull << 59) + (1ull << 50) && near_word(q, 1ll << 26) : near_word(q, 1ll << 27);
+    return near_top(q) ? logN <= 16 && q <= NEAR_TOP && near_word(q, NEAR_TOP_WORD) : near_word(q, NEAR_WORD);
 }
-static inline bool near_inv(u64 q) { return near_word(q, 1ll << 27) && q <= (1ull << 63) / 550; }      // up to 2^53.896
+static inline bool near_inv(u64 q) { return near_word(q, NEAR_WORD) && q <= NEAR_INV; }
+// The ranges above: what points below b*q become in `stages` stages, in units of q; -1 where a product's operand leaves its range
+constexpr bool near_takes(double operand, double q, double word) { return operand * q / 2 + 0x1p62 + word * 0x1p31 < 0x1p63; }
+constexpr double near_forward(double b, double q, double word, int stages) {
+    for (int i = 0; i < stages; i++) {
+        if (!near_takes(b, q, word)) return -1;
+        b += 0.75 + b * q * 0x1p-65;
+    }
+    return b;
+}
+constexpr double near_inverse(double b, double q, double word, int stages) {
+    for (int i = 0; i < stages; i++) {
+        b *= 2;
+        if (!near_takes(b, q, word)) return -1;
+    }
+    return b;
+}
+static_assert(near_forward(5, NEAR_FWD, NEAR_WORD, 17) > 5 && near_forward(5, NEAR_FWD, NEAR_WORD, 17) < 22, "");
+static_assert(near_forward(1.5, NEAR_TOP, NEAR_TOP_WORD, 15) < 14.6 && near_forward(1.5, NEAR_TOP, NEAR_TOP_WORD, 16) > 1.5 && near_forward(1.5, NEAR_TOP, NEAR_TOP_WORD, 16) < 15.6, "");
+static_assert(14.6 * NEAR_TOP < 0x1p63 - 0x1p58 && near_forward(1.5, NEAR_TOP, NEAR_TOP_WORD, 17) > 16, "17 stages end beyond what near_bias makes positive");
+static_assert(near_inverse(2, NEAR_INV, NEAR_WORD, 8) == 512 && near_inverse(2, NEAR_INV, NEAR_WORD, 9) < 0, "");
 // The classes (ntt_blocks.h), and those of all moduli of a context, bit by bit: kernels of short launches ask for both words along with their
 // first arguments, so that the branch to a class waits for no load of its own (inverse rows of one polynomial of six limbs 5.6 -> 5.5 us).
 #define W_NEAR 3
