@@ -107,7 +107,8 @@ __device__ constexpr int kr_inv(int W) { return W == 4 ? W_NEAR : W == 0 ? 0 : W
 // Both components of the inner products of row b of limb r for one (source, key) term, added to the sums s; `spill`
 // empties them when they hold KS_ROW_PRODUCTS products.  Digits enter as the row transform leaves them where W = 0 or 4 (below 90q <
 // 2^60.2, 4: 46q: 31-bit high halves; seven products with key values below q, together below 2^117, fit the sums and split_reduce), else below
-// 2q (1, 5) or canonical (2, 3).  buf: a row for each digit, of which
+// 2q (1, 5) or canonical (2, 3).  5 reaches furthest: digits below 2^60.003 and keys of 2^59.003, of which seven products stay below 10.6 * 2^60 in
+// the middle sum and below 2^121.9 together, where 2^(bits + 63) is 2^123.  buf: a row for each digit, of which
 // digits j0, j0 + step .. are worked on (j0 < beta).  AHEAD: the next digit's row and the own one are asked for ahead of their turn.
 template <int W, bool SP, bool AHEAD, class Spill>
 __device__ __forceinline__ void ks_row_products(const KsRows& a, uint32_t id, uint32_t r, uint32_t b, uint32_t t, u64* buf, const ModConst& m, const Row4& at,

@@ -293,7 +293,8 @@ __device__ __forceinline__ void row_fwd(const P2Args& a, uint32_t e, uint32_t ti
         return;
     }
     // out = (acc - ntt) * P^-1 + sigma(c0) + self: the product is below 5q whatever its factor, so the transform value may
-    // stay as it is where 128q plus the accumulator (below 6q) fits 63 bits, else below 2q; the sum is below 7q
+    // stay as it is where what makes it positive (fwd_raw_bias: 128q, near moduli 24q) plus the accumulator (below 6q) fits 63 bits, else below
+    // 2q; the sum is below 7q
     const bool raw = fwd_raw<W>(m);
     if (!raw) {
 #pragma unroll
