@@ -137,7 +137,7 @@ __device__ __forceinline__ void ks_row_products(const KsRows& a, uint32_t id, ui
                 for (int k = 0; k < 4; k++) nx[k] = __builtin_nontemporal_load(&(row + jn * dig_stride)[t + 64 * k]);
             }
             SCHED_FENCE();
-            if (!AHEAD) {                                // the factors' second words are formed anew, not kept in registers
+            if (!AHEAD && kr_fwd(W) != W_NEAR) {         // the factors' second words (near moduli have none) are formed anew, not kept in registers
 #pragma unroll
                 for (int i = 0; i < 18; i++) asm("" : "+v"(w[1 + i / 6][i % 6]));
             }
