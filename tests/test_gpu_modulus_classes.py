@@ -40,11 +40,13 @@ def primes_from(start, step, count):
 @pytest.mark.parametrize("line", sorted(LINES))
 @pytest.mark.parametrize("side", ["below", "above"])
 def test_both_sides_of_a_line(logN, line, side):
+    check_single_calls(logN, primes_at(line, side, logN, 6))
+
+
+def check_single_calls(logN, m):
     from gpu_util import dev, host, zeros
     from oracle.he_oracle import Oracle
     from paper_2302_02407_amd.binding import HEContext
-    m = primes_from(LINES[line], (2 << logN) * (1 if side == "above" else -1), 6)
-    assert all((x > LINES[line]) == (side == "above") for x in m)
     prm = HEParams(logN=logN, q=m[2:], p=m[:2], dnum=2, scale=2.0 ** 40, hamming=64, name="line")
     orc, ctx, N, level, step = Oracle.from_params(prm), HEContext.from_params(prm), prm.N, 3, 3
     rng, g, idx = S.make_rng(77 + logN), orc.galois_elt(step), [0, 1, 2, 3] * 2
@@ -76,10 +78,14 @@ def test_both_sides_of_a_line(logN, line, side):
 @pytest.mark.parametrize("line,side", SIDES)
 @pytest.mark.parametrize("logN,counts", [(14, (85, 88, 85)), (16, (17, 16, 32)), (16, (133, 130, 129)), (16, (5,) * 13), (17, (5,) * 7)])
 def test_rows_of_large_launches(line, side, logN, counts):
+    check_large_launches(logN, counts, primes_at(line, side, logN, len(counts)))
+
+
+def check_large_launches(logN, counts, m):
     from gpu_util import dev, host
     from oracle.he_oracle import Oracle
     from paper_2302_02407_amd.binding import HEContext
-    N, m = 1 << logN, primes_at(line, side, logN, len(counts))
+    N = 1 << logN
     assert sum(counts) * (N >> 10) > 4096
     orc, ctx, rng = Oracle(logN, m[1:], m[:1], 2), HEContext(logN, m[1:], m[:1], 2), S.make_rng(177 + logN + len(counts))
     moduli, idx = m[1:] + m[:1], [i for i, n in enumerate(counts) for _ in range(n)]
@@ -98,6 +104,10 @@ def test_rows_of_large_launches(line, side, logN, counts):
 @pytest.mark.parametrize("logN", [13, 15])
 @pytest.mark.parametrize("line,side", SIDES)
 def test_batches_of_key_switches(line, side, logN):
+    check_batches(logN, primes_at(line, side, logN, 9))
+
+
+def check_batches(logN, m):
     """Nine ciphertexts: conversions in tiles of 1024 points and key-switch rows of a wavefront each, where the tests above have too few (at
     2^13 complete digits still give each component a wavefront); every step on its own and sharing a decomposition, sums of both
     kinds, a product, a hoisted sum."""
@@ -105,7 +115,6 @@ def test_batches_of_key_switches(line, side, logN):
     from oracle.he_oracle import Oracle
     from paper_2302_02407_amd.binding import HEContext
     C_a = 16
-    m = primes_at(line, side, logN, 9)
     prm = HEParams(logN=logN, q=m[3:], p=m[:3], dnum=3, scale=2.0 ** 40, hamming=64, name="line")
     orc, ctx, N, level = Oracle.from_params(prm), HEContext.from_params(prm), prm.N, 5
     rng, block, steps = S.make_rng(277), N // 2 // C_a, [1, 2, 300]

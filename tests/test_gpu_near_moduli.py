@@ -4,8 +4,8 @@ below and above the line of the inverse passes, at the top of the forward ones, 
 both sides of the bound, and moduli of little more than 20 bits."""
 import pytest
 
-import test_gpu_modulus_classes as classes
 from he_inputs.params import is_prime
+from test_gpu_modulus_classes import check_batches, check_large_launches, check_single_calls
 
 pytestmark = pytest.mark.gpu
 
@@ -43,29 +43,18 @@ def near_primes(kind, two_n, count):
 KINDS = ["inverse below", "inverse above", "forward top", "centred top", "centred", "words beyond", "small"]
 
 
-@pytest.fixture
-def near(monkeypatch):
-    def use(kind):
-        monkeypatch.setitem(classes.LINES, kind, 0)
-        monkeypatch.setattr(classes, "primes_from", lambda start, step, count: near_primes(kind, abs(step), count))
-    return use
-
-
 @pytest.mark.parametrize("logN", [13, 16, 17])
 @pytest.mark.parametrize("kind", KINDS)
-def test_single_calls(near, kind, logN):
-    near(kind)
-    classes.test_both_sides_of_a_line(logN, kind, "above")
+def test_single_calls(kind, logN):
+    check_single_calls(logN, near_primes(kind, 2 << logN, 6))
 
 
 @pytest.mark.parametrize("kind", KINDS[:5])
 @pytest.mark.parametrize("logN,counts", [(16, (133, 130, 129)), (16, (5,) * 13), (17, (5,) * 7)])
-def test_large_launches(near, kind, logN, counts):
-    near(kind)
-    classes.test_rows_of_large_launches(kind, "above", logN, counts)
+def test_large_launches(kind, logN, counts):
+    check_large_launches(logN, counts, near_primes(kind, 2 << logN, len(counts)))
 
 
 @pytest.mark.parametrize("kind", KINDS)
-def test_batches(near, kind):
-    near(kind)
-    classes.test_batches_of_key_switches(kind, "above", 13)
+def test_batches(kind):
+    check_batches(13, near_primes(kind, 2 << 13, 9))
