@@ -70,8 +70,8 @@ static_assert(near_forward(5, NEAR_FWD, NEAR_WORD, 17) > 5 && near_forward(5, NE
 static_assert(near_forward(1.5, NEAR_TOP, NEAR_TOP_WORD, 15) < 14.6 && near_forward(1.5, NEAR_TOP, NEAR_TOP_WORD, 16) > 1.5 && near_forward(1.5, NEAR_TOP, NEAR_TOP_WORD, 16) < 15.6, "");
 static_assert(14.6 * NEAR_TOP < 0x1p63 - 0x1p58 && near_forward(1.5, NEAR_TOP, NEAR_TOP_WORD, 17) > 16, "17 stages end beyond what near_bias makes positive");
 static_assert(near_inverse(2, NEAR_INV, NEAR_WORD, 8) == 512 && near_inverse(2, NEAR_INV, NEAR_WORD, 9) < 0, "");
-// The classes (ntt_blocks.h), and those of all moduli of a context, bit by bit: kernels of short launches ask for both words along with their
-// first arguments, so that the branch to a class waits for no load of its own (inverse rows of one polynomial of six limbs 5.6 -> 5.5 us).
+// The classes (ntt_blocks.h), and those of all moduli of a context, bit by bit (a kernel's argument: the branch to a class waits for no load of the
+// modulus' constants)
 #define W_NEAR 3
 static inline uint32_t class_fwd(u64 q, uint32_t logN) { return near_fwd(q, logN) ? W_NEAR : narrow_fwd(q) ? 0 : widest(q) ? 2 : 1; }
 static inline uint32_t class_inv(u64 q) { return near_inv(q) ? W_NEAR : narrow_inv(q) ? 0 : widest(q) ? 2 : 1; }

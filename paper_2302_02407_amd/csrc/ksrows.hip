@@ -482,12 +482,13 @@ __device__ __forceinline__ void ks_row_group(const KsRows& a, uint32_t job, uint
     }
 }
 
-// W of the moduli (ks_width, he_internal.h), asked for at the start of a kernel: the branch waits for no load of its own
-struct KrWidths {
-    u64 b[3];
-    __device__ __forceinline__ explicit KrWidths(const KsRows& a) : b{a.width[0], a.width[1], a.width[2]} { asm volatile("" : "+s"(b[0]), "+s"(b[1]), "+s"(b[2])); }
-    __device__ __forceinline__ uint32_t of(uint32_t mi) const { return (uint32_t)(b[0] >> mi & 1u) | (uint32_t)(b[1] >> mi & 1u) << 1 | (uint32_t)(b[2] >> mi & 1u) << 2; }
-};
+// W of a modulus (ks_width, he_internal.h), from the argument list: the branch waits for no load of its constants.  (Near or not first: on the
+// number put together from its bits the compiler orders the bodies so that one rotation of other moduli at level 5 takes 54.1 us instead of 53.5.)
+__device__ __forceinline__ uint32_t kr_width(const KsRows& a, uint32_t mi) {
+    const uint32_t low = (uint32_t)(a.width[0] >> mi & 1u);
+    if (a.width[2] >> mi & 1u) return low ? 5 : 4;
+    return low + 2 * (uint32_t)(a.width[1] >> mi & 1u);
+}
 template <int W>
 __device__ __forceinline__ uint32_t kr_pin(uint32_t v) {     // keeps the widths' loads apart (by_class, ntt_blocks.h)
     if (W == 0) asm("; narrow" : "+s"(v));
@@ -504,14 +505,13 @@ template <bool SP, bool MANY, bool DONE>
 __global__ __launch_bounds__(KR_THREADS, MANY ? 3 : 4) void ks_rows_kernel(KsRows a) {
     ieee_off();
     extern __shared__ __attribute__((aligned(16))) u64 sm[];
-    const KrWidths widths(a);
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), rows = a.logN - 8;
     const uint32_t item = (blockIdx.x >> 3) * KR_WAVES + wave, un = item / a.J, job = item - un * a.J;
     const uint32_t u = un * 8 + (blockIdx.x & 7u), r = u >> rows;
     if (r >= (SP ? a.k : a.L1)) return;
     const uint32_t b = kr_row_from(u & ((1u << rows) - 1u), a.g[job], rows);
     u64* buf = sm + wave * (256 * (DONE ? 2u : max(a.beta, 2u)));
-    const uint32_t width = widths.of(SP ? a.nq + r : r), t = threadIdx.x & 63u;
+    const uint32_t width = kr_width(a, SP ? a.nq + r : r), t = threadIdx.x & 63u;
     if (width == 4) ks_row<4, SP, MANY, DONE>(a, job, kr_pin<4>(r), b, t, buf);
     else if (width == 5) ks_row<5, SP, MANY, DONE>(a, job, kr_pin<5>(r), b, t, buf);
     else if (width == 0) ks_row<0, SP, MANY, DONE>(a, job, kr_pin<0>(r), b, t, buf);
@@ -524,14 +524,13 @@ template <bool SP>
 __global__ __launch_bounds__(KR_THREADS, 4) void ks_rows_half_kernel(KsRows a) {
     ieee_off();
     __shared__ __attribute__((aligned(16))) u64 sm[KR_WAVES * 512];
-    const KrWidths widths(a);
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), rows = a.logN - 8, t = threadIdx.x & 63u;
     const uint32_t at = (blockIdx.x >> 3) * KR_WAVES + wave, item = at >> 1, un = item / a.J, job = item - un * a.J;
     const uint32_t u = un * 8 + (blockIdx.x & 7u), r = u >> rows;
     if (r >= (SP ? a.k : a.L1)) return;
     const uint32_t b = kr_row_from(u & ((1u << rows) - 1u), a.g[job], rows);
     u64* buf = sm + 512 * wave;
-    const uint32_t width = widths.of(SP ? a.nq + r : r);
+    const uint32_t width = kr_width(a, SP ? a.nq + r : r);
     if (width == 4) ks_row_half<4, SP>(a, job, at & 1u, kr_pin<4>(r), b, t, buf);
     else if (width == 5) ks_row_half<5, SP>(a, job, at & 1u, kr_pin<5>(r), b, t, buf);
     else if (width == 0) ks_row_half<0, SP>(a, job, at & 1u, kr_pin<0>(r), b, t, buf);
@@ -544,11 +543,10 @@ template <bool SP, bool SUM, bool DONE, bool NEXT = false>
 __global__ __launch_bounds__(KR_THREADS, SUM && DONE ? 2 : 3) void ks_rows_group_kernel(KsRows a) {
     ieee_off();
     extern __shared__ __attribute__((aligned(16))) u64 sm[];
-    const KrWidths widths(a);
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = blockDim.x >> 6, rows = a.logN - 8, t = threadIdx.x & 63u;
     const uint32_t item = blockIdx.x >> 3, un = item / a.J, job = item - un * a.J;
     const uint32_t u = un * 8 + (blockIdx.x & 7u), r = u >> rows, b = u & ((1u << rows) - 1u);
-    const uint32_t width = widths.of(SP ? a.nq + r : r);
+    const uint32_t width = kr_width(a, SP ? a.nq + r : r);
     if (width == 4) ks_row_group<4, SP, SUM, DONE, NEXT>(a, job, kr_pin<4>(r), b, wave, nw, t, sm);
     else if (width == 5) ks_row_group<5, SP, SUM, DONE, NEXT>(a, job, kr_pin<5>(r), b, wave, nw, t, sm);
     else if (width == 0) ks_row_group<0, SP, SUM, DONE, NEXT>(a, job, kr_pin<0>(r), b, wave, nw, t, sm);

@@ -342,11 +342,10 @@ template <bool EPI, int LANES>
 __global__ __launch_bounds__(P2_THREADS, 4) void ntt_row_fwd_kernel(P2Args a, LimbTab tab, ModDownEpilogue ep) {
     ieee_off();
     __shared__ alignas(16) u64 sm[P2_THREADS / LANES * 272];         // 16 groups of 17: conflict-free both ways
-    const ModClasses cls = classes_now(a.cls);
     uint32_t tile;
     const uint32_t e = row_decode<LANES>(tab, a, tile);
     if (e == TAB_NONE) return;
-    by_class(cls, tab_mod(e), e, [&](auto W, uint32_t v) { row_fwd<W, EPI, LANES>(a, v, tile, sm, ep); });
+    by_class(a.cls, tab_mod(e), e, [&](auto W, uint32_t v) { row_fwd<W, EPI, LANES>(a, v, tile, sm, ep); });
 }
 
 // ---------------------------------------------------------------- inverse row pass
@@ -419,11 +418,10 @@ template <int LANES>
 __global__ __launch_bounds__(P2_THREADS, 4) void ntt_row_inv_kernel(P2Args a, LimbTab tab) {
     ieee_off();
     __shared__ alignas(16) u64 sm[P2_THREADS / LANES * 272];
-    const ModClasses cls = classes_now(a.cls);
     uint32_t tile;
     const uint32_t e = row_decode<LANES>(tab, a, tile);
     if (e == TAB_NONE) return;
-    by_class(cls, tab_mod(e), e, [&](auto W, uint32_t v) { row_inv<W, LANES>(a, tab, v, tile, sm); });
+    by_class(a.cls, tab_mod(e), e, [&](auto W, uint32_t v) { row_inv<W, LANES>(a, tab, v, tile, sm); });
 }
 
 // ---------------------------------------------------------------- row passes of several limbs of one modulus
@@ -564,9 +562,8 @@ __global__ __launch_bounds__(P2_THREADS, 4) void ntt_row_run_kernel(P2Args a, Li
     ieee_off();
     __shared__ u64 sm[16 * 272];
     const uint32_t lb = a.logN - 10, b = (blockIdx.x & ((1u << lb) - 1u)) * 4u + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const ModClasses cls = classes_now(a.cls);
     const uint32_t run = __builtin_amdgcn_readfirstlane(runs.r[blockIdx.x >> lb]);
-    by_class(cls, run >> 14 & 63u, run, [&](auto W, uint32_t v) {
+    by_class(a.cls, run >> 14 & 63u, run, [&](auto W, uint32_t v) {
         if constexpr (FWD) row_run_fwd<W, LAZY>(a, tab, v, b, sm);
         else row_run_inv<W>(a, tab, v, b, sm);
     });

@@ -29,12 +29,6 @@ __device__ __forceinline__ u64 near_bias(u64 q) { return q * (q > 1ull << 58 ? 1
 __device__ constexpr int w_lim(int W) { return W == W_NEAR ? NEAR_ROWS : W == 1 ? 13 : 8; }         // sums and products' operands (W > 0)
 __device__ constexpr int w_half(int W) { return w_lim(W) / 2; }            // inverse: points between stages (W = 1, 2)
 __device__ constexpr int w_start(int W) { return W == 1 || W == 2 ? w_half(W) : 2; }      // inverse: what a pass starts with
-// A context's classes, asked for at the start of a kernel along with what it needs first
-__device__ __forceinline__ ModClasses classes_now(const ModClasses& c) {
-    ModClasses v = c;
-    asm volatile("" : "+s"(v.b[0]), "+s"(v.b[1]));
-    return v;
-}
 // f(std::integral_constant<int, W>, v) for the class W of bits `mi` of c; v: what the loads of a class follow from.  Keeps the loads of the
 // branches apart: merged above them (they look alike) they would stay live across all of it, 240 registers instead of 109.  (A chain of
 // branches: on the class as one number the compiler makes a tree of them, with ten registers more in the rescale's columns.)
