@@ -38,7 +38,7 @@ static inline bool widest(u64 q) { return q > (1ull << 63) / 13; }            //
 // just below 2^53.896 135.6 (149.6).  24 limbs: forward 23.3 (23.5) at 2^54, 23.4 (24.2) below 2^58, 23.8 (24.2) above 2^59; inverse 23.5 (25.0).  Outside
 // the class, now that it is there (in brackets before): inverse just above 2^53.9 150.2 (149.8), forward at 1.2 * 2^59 143.0 (143.7), just below 2^60
 // 153.6 (151.3).  What it costs other moduli is the jump over its code, which comes first in every kernel, an instruction fetch of some 0.3 us a
-// launch: one rotation at level 5 53.3 us (52.0) with narrow ciphertext primes, where the near ones take 51.3.
+// launch: one rotation at level 5 53.5 us (52.0) with narrow ciphertext primes, where the near ones take 51.
 static inline bool near_word(u64 q, int64_t most) { return (int32_t)(uint32_t)q < most && (int32_t)(uint32_t)q > -most; }
 #define NEAR_WORD (1ll << 27)
 #define NEAR_TOP_WORD (1ll << 26)
